@@ -1,6 +1,6 @@
 // Tiled causal attention for bf16 models on the matrix cores (v_mfma_f32_32x32x16_bf16), forward and backward.
 //
-// All kernels work on the fused [T, 3*Hs*dh] q|k|v buffer, d_head 64 or 128, N a multiple of 128.
+// All kernels work on the fused [T, 3*Hs*dh] q|k|v buffer.
 // Layout facts used throughout (32x32x16 MFMA, wave of 64 lanes, g = lane/32, c = lane%32):
 //   A operand (M x K): lane supplies row c, k = 8g .. 8g+7          B operand (K x N): lane supplies column c, same k
 //   D (32 x 32):       lane holds column c, register r holds row 8*(r/4) + 4g + r%4
@@ -388,39 +388,57 @@ __global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const uint16_t *qkv,
     }
 }
 
-// =========================================================================================== d_head = 128, pipelined
-// Same decomposition, but the 64 x 128 key / value (or query / dO) tiles of step t+1 travel from global memory
+// =========================================================================================== pipelined, any N
+// Same decomposition, but the 64 x DH key / value (or query / dO) tiles of step t+1 travel from global memory
 // straight into LDS (buffer_load_dwordx4 ... lds, lane l of a wave writes 16 bytes at base + 16 l) while step t is
-// computed: two stages of two 16 KB tiles, one barrier per step.  The fixed write pattern leaves no room for row
-// padding; bank conflicts are avoided by storing chunk c (16 bytes) of row r at position c ^ swz(r),
-// swz(r) = 4 (r & 3) + ((r >> 2) & 3), which serves both read patterns: 16 consecutive rows of one chunk column
-// (plain 16-byte fragment reads) and 4 consecutive rows of two adjacent chunks (transposing reads).
+// computed: two stages of two tiles, one barrier per step.  The fixed write pattern leaves no room for row
+// padding; bank conflicts are avoided by storing chunk c (16 bytes) of row r at position c ^ swz(r), which serves both
+// read patterns: 16 consecutive rows of one chunk column (plain 16-byte fragment reads) and 4 consecutive rows of four
+// adjacent chunks (transposing reads).  256 bytes of LDS (all banks once) hold 1, 2 or 4 rows of 128, 64 or 32 head columns,
+// so the swizzle only has to spread the rows that share a position inside such a group.
+//
+// SEQUENCES OF ANY LENGTH: rows at or beyond N read as zeros (they are outside the batch element's buffer range), the rows
+// a lane keeps in registers are clamped to N - 1 and their results not stored.  A key at or beyond N comes after every
+// query, so the causal mask removes it; a query at or beyond N has dO = 0, delta = 0 and P = 1, so it adds nothing to dK
+// and dV.
+//
+// Measured (forward / dQ / dK dV, us): B 3, N 1000, 7 heads of 128: 27 / 46 / 60, where lengths that are no multiple of 128
+// used to run the plain kernels, 2633 / 3596 / 1945.  B 8, N 1024, 3 heads of 64: 19 / 23 / 40 against 25 / 58 / 40 of the
+// register-staged kernels above.  All three are chains of dependent steps inside a workgroup (load, products, exponentials,
+// products), not bound by memory or by the matrix pipes' rate.
 namespace dl {
 
-constexpr int DH = 128, KS = 8, MT = 4;
-constexpr int TILE_B = 64 * DH * 2;    // one staged tile
-constexpr int STAGE_B = 2 * TILE_B;    // K and V (or Q and dO)
+template <int DH>
+struct Geo {
+  static constexpr int KS = DH / 16, MT = DH / 32, RB = DH * 2;  // k-steps and 32-column blocks of a head, bytes of a row
+  static constexpr int TILE_B = 64 * RB;                         // one staged tile
+  static constexpr int STAGE_B = 2 * TILE_B;                     // K and V (or Q and dO)
+  static constexpr int CPR = DH / 8, RPP = 64 / CPR;             // 16-byte chunks of a row, rows in a one-KB piece
+  static __device__ __forceinline__ int swz(int r) {
+    return DH == 128 ? 4 * (r & 3) + ((r >> 2) & 3) : DH == 64 ? 4 * ((r >> 1) & 1) + ((r >> 2) & 3) : (r >> 2) & 3;
+  }
+};
 typedef __attribute__((address_space(3))) void *lds_void;
 
-__device__ __forceinline__ int swz(int r) { return 4 * (r & 3) + ((r >> 2) & 3); }
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
 }
 
 // Per-lane byte offsets (within a tile) of the two kinds of fragment reads.
+template <int DH>
 struct ReadOffsets {
-  uint32_t fo[KS];          // plain fragment of k-step ks for tile row (lane & 31); add 8192 per 32 rows
-  uint32_t ta[MT], tb[MT];  // transposing reads of head-dim block i: contraction rows +0..3 and +8..11; add 256 per row
+  using G = Geo<DH>;
+  uint32_t fo[G::KS];             // plain fragment of k-step ks for tile row (lane & 31); add 32 RB per 32 rows
+  uint32_t ta[G::MT], tb[G::MT];  // transposing reads of head-dim block i: contraction rows +0..3 and +8..11; add 16 RB per 16 rows
   __device__ __forceinline__ void init(int lane) {
     const int c = lane & 31, g = lane >> 5, s16 = lane & 15, rho = (s16 >> 2) & 3, dlt = (s16 & 3) >> 1, hi = (lane >> 4) & 1;
-    const int x = swz(c);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) fo[ks] = (uint32_t)(c * 256 + (((2 * ks + g) ^ x) << 4));
-    const int within = (s16 & 1) * 8;
+    for (int ks = 0; ks < G::KS; ++ks) fo[ks] = (uint32_t)(c * G::RB + (((2 * ks + g) ^ G::swz(c)) << 4));
+    const int within = (s16 & 1) * 8, ra = 4 * g + rho, rb = ra + 8;
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      ta[i] = (uint32_t)((4 * g + rho) * 256 + within + (((2 * hi + dlt) ^ g) << 4) + ((i ^ rho) << 6));
-      tb[i] = (uint32_t)((4 * g + rho + 8) * 256 + within + (((2 * hi + dlt) ^ (g + 2)) << 4) + ((i ^ rho) << 6));
+    for (int i = 0; i < G::MT; ++i) {
+      ta[i] = (uint32_t)(ra * G::RB + within + (((4 * i + 2 * hi + dlt) ^ G::swz(ra)) << 4));
+      tb[i] = (uint32_t)(rb * G::RB + within + (((4 * i + 2 * hi + dlt) ^ G::swz(rb)) << 4));
     }
   }
 };
@@ -461,28 +479,34 @@ __device__ __forceinline__ void dma(desc_t desc, const char *lds, uint32_t voff)
                  : "=&s"(keep) : "s"(l), "v"(voff), "s"(desc) : "memory");
 }
 
-// Each of the 4 waves brings in 4 of the 16 one-KB pieces (4 rows each) of a tile.
+// Each of 4 waves brings in a quarter of a tile's one-KB pieces.
+template <int DH>
 struct TileLoader {
-  uint32_t off[4];  // byte offset of this lane's chunk within tile 0, from the buffer base
+  using G = Geo<DH>;
+  static constexpr int NP = G::TILE_B / 4096;
+  uint32_t off[NP];  // byte offset of this lane's chunk within tile 0, from the buffer base
   __device__ __forceinline__ void init(int64_t ld_elems, uint32_t col_byte0, int wave, int lane) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = 4 * (wave + 4 * i) + (lane >> 4), chunk = (lane & 15) ^ swz(row);
+    for (int i = 0; i < NP; ++i) {
+      const int row = G::RPP * (wave + 4 * i) + lane / G::CPR, chunk = (lane % G::CPR) ^ G::swz(row);
       off[i] = (uint32_t)(row * ld_elems * 2) + col_byte0 + chunk * 16;
     }
   }
   __device__ __forceinline__ void issue(desc_t rsrc, char *dst, uint32_t tile_byte0, int wave) const {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) dma<16>(rsrc, dst + (wave + 4 * i) * 1024, off[i] + tile_byte0);
+    for (int i = 0; i < NP; ++i) dma<16>(rsrc, dst + (wave + 4 * i) * 1024, off[i] + tile_byte0);
   }
 };
 
 #define DL_WAIT_VM0 __builtin_amdgcn_s_waitcnt(0x0f70)
 
 // two waves per SIMD (two workgroups per CU) is what lets one workgroup's softmax overlap the other's matrix work
+template <int DH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void flash_fwd_dl_kernel(const uint16_t *qkv, uint16_t *o, float *o32, float *lse, int N, int Hs, float scale, const int32_t *keep) {
+  using G = Geo<DH>;
+  constexpr int KS = G::KS, MT = G::MT, TILE_B = G::TILE_B, STAGE_B = G::STAGE_B, RB = G::RB;
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE_B];
-  const int nqb = N / 128, nbh = gridDim.x / nqb;
+  const int nqb = (N + 127) / 128, nbh = gridDim.x / nqb;
   const int rank = snake_rank(blockIdx.x, gridDim.x);
   const int qb = nqb - 1 - rank / nbh;
   const int bh = rank % nbh, b = bh / Hs, h = bh % Hs;
@@ -490,19 +514,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
   const int64_t HD = (int64_t)Hs * DH, ld = 3 * HD;
   const uint16_t *batch = qkv + (int64_t)b * N * ld;
   const uint16_t *qp = batch + (int64_t)h * DH;
-  const int q0 = qb * 128 + wave * 32, q = q0 + c;
+  const int q0 = qb * 128 + wave * 32, q = q0 + c, qr = min(q, N - 1);
   const float sc = scale * kLog2e;
   const desc_t rs = make_desc(batch, (uint32_t)(N * ld * 2));
   const uint32_t tstep = (uint32_t)(64 * ld * 2);
-  TileLoader lk, lv;
+  TileLoader<DH> lk, lv;
   lk.init(ld, (uint32_t)((HD + h * DH) * 2), wave, lane);
   lv.init(ld, (uint32_t)((2 * HD + h * DH) * 2), wave, lane);
-  ReadOffsets ro;
+  ReadOffsets<DH> ro;
   ro.init(lane);
 
   bf16x8 qf[KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + (int64_t)q * ld + ks * 16 + g * 8);
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + (int64_t)qr * ld + ks * 16 + g * 8);
   f32x16 oacc[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -532,7 +556,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[mt][r] = 0.f;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) s[mt] = MFMA(frag(Kt + mt * 8192, ro.fo[ks]), qf[ks], s[mt]);
+      for (int ks = 0; ks < KS; ++ks) s[mt] = MFMA(frag(Kt + mt * 32 * RB, ro.fo[ks]), qf[ks], s[mt]);
     }
     if (kt * 64 + 63 > q0) {
 #pragma unroll
@@ -582,7 +606,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
         const u32x4 pu = {pk[mt][4 * t], pk[mt][4 * t + 1], pk[mt][4 * t + 2], pk[mt][4 * t + 3]};
         const bf16x8 pf = __builtin_bit_cast(bf16x8, pu);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) oacc[i] = MFMA(frag_tr(Vt + (mt * 32 + 16 * t) * 256, ro.ta[i], ro.tb[i]), pf, oacc[i]);
+        for (int i = 0; i < MT; ++i) oacc[i] = MFMA(frag_tr(Vt + (mt * 32 + 16 * t) * RB, ro.ta[i], ro.tb[i]), pf, oacc[i]);
       }
   };
   for (int kt = 0; kt < n_tiles; kt += 2) {
@@ -590,6 +614,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
     step(kt + 1, std::integral_constant<int, 1>());  // n_tiles is even
   }
   l += __shfl_xor(l, 32, 64);
+  if (q >= N) return;
   const float inv = masked ? 0.f : 1.f / l;
   uint16_t *op = o + ((int64_t)b * N + q) * HD + (int64_t)h * DH;
 #pragma unroll
@@ -606,31 +631,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
   if (g == 0) lse[((int64_t)b * Hs + h) * N + q] = masked ? 0.f : (m + log2f(l)) * kLn2;
 }
 
-// Backward of the rotary embedding on a lane's 64 gradient values of one row (acc[i][4 j + e] is head-dim column
-// 32 i + 8 j + 4 g + e): columns f and f + 64 form a pair rotated by the angle of (position, f); the backward pass turns
-// the gradient by the opposite angle.  tab holds (cos, sin) for f = 0..63 of every position, 128 floats per position.
-__device__ __forceinline__ void rope_grad(f32x16 (&acc)[MT], const float *tab, int pos, int g) {
+// Backward of the rotary embedding on a lane's gradient values of one row (acc[i][4 j + e] is head-dim column
+// 32 i + 8 j + 4 g + e): columns f and f + DH/2 form a pair rotated by the angle of (position, f); the backward pass turns
+// the gradient by the opposite angle.  tab holds (cos, sin) for f = 0 .. DH/2 - 1 of every position, DH floats per position.
+template <int DH>
+__device__ __forceinline__ void rope_grad(f32x16 (&acc)[Geo<DH>::MT], const float *tab, int pos, int g) {
   const f32x4 *row = reinterpret_cast<const f32x4 *>(tab + (int64_t)pos * DH);
 #pragma unroll
-  for (int i = 0; i < MT / 2; ++i)
+  for (int v = 0; v < DH / 16; ++v) {  // the lane's groups of four consecutive pair indices
+    const int f = 8 * v + 4 * g, v2 = v + DH / 16;  // group v of columns is registers 4 (v % 4) .. + 3 of block v / 4
+    const f32x4 w0 = row[f / 2], w1 = row[f / 2 + 1];
+    const float cs[4] = {w0[0], w0[2], w1[0], w1[2]}, sn[4] = {w0[1], w0[3], w1[1], w1[3]};
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int f = 32 * i + 8 * j + 4 * g;  // first of the lane's four consecutive pair indices
-      const f32x4 w0 = row[f / 2], w1 = row[f / 2 + 1];
-      const float cs[4] = {w0[0], w0[2], w1[0], w1[2]}, sn[4] = {w0[1], w0[3], w1[1], w1[3]};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float a = acc[i][4 * j + e], b = acc[i + MT / 2][4 * j + e];
-        acc[i][4 * j + e] = a * cs[e] + b * sn[e];
-        acc[i + MT / 2][4 * j + e] = b * cs[e] - a * sn[e];
-      }
+    for (int e = 0; e < 4; ++e) {
+      const float a = acc[v / 4][4 * (v % 4) + e], b = acc[v2 / 4][4 * (v2 % 4) + e];
+      acc[v / 4][4 * (v % 4) + e] = a * cs[e] + b * sn[e];
+      acc[v2 / 4][4 * (v2 % 4) + e] = b * cs[e] - a * sn[e];
     }
+  }
 }
 
+template <int DH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void flash_bwd_dq_dl_kernel(const uint16_t *qkv, const uint16_t *dout, const float *o32, const float *lse, float *delta,
                                                               uint16_t *dqkv, int N, int Hs, float scale, const float *rope, const int32_t *keep) {
+  using G = Geo<DH>;
+  constexpr int KS = G::KS, MT = G::MT, TILE_B = G::TILE_B, STAGE_B = G::STAGE_B, RB = G::RB;
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE_B];
-  const int nqb = N / 128, nbh = gridDim.x / nqb;
+  const int nqb = (N + 127) / 128, nbh = gridDim.x / nqb;
   const int rank = snake_rank(blockIdx.x, gridDim.x);
   const int qb = nqb - 1 - rank / nbh;
   const int bh = rank % nbh, b = bh / Hs, h = bh % Hs;
@@ -638,15 +665,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
   const int64_t HD = (int64_t)Hs * DH, ld = 3 * HD;
   const uint16_t *batch = qkv + (int64_t)b * N * ld;
   const uint16_t *qp = batch + (int64_t)h * DH;
-  const int q0 = qb * 128 + wave * 32, q = q0 + c;
+  const int q0 = qb * 128 + wave * 32, q = q0 + c, qr = min(q, N - 1);
   const float sc = scale * kLog2e;
-  const float L2 = lse[((int64_t)b * Hs + h) * N + q] * kLog2e;
+  const float L2 = lse[((int64_t)b * Hs + h) * N + qr] * kLog2e;
   const desc_t rs = make_desc(batch, (uint32_t)(N * ld * 2));
   const uint32_t tstep = (uint32_t)(64 * ld * 2);
-  TileLoader lk, lv;
+  TileLoader<DH> lk, lv;
   lk.init(ld, (uint32_t)((HD + h * DH) * 2), wave, lane);
   lv.init(ld, (uint32_t)((2 * HD + h * DH) * 2), wave, lane);
-  ReadOffsets ro;
+  ReadOffsets<DH> ro;
   ro.init(lane);
   const bool masked = keep && keep[h] < 0;  // masked head: the gradient is zero, nothing is loaded
   const int n_tiles = masked ? 0 : (qb + 1) * 2;
@@ -656,19 +683,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
   }
 
   bf16x8 qf[KS], gf[KS];
-  const uint16_t *gp = dout + ((int64_t)b * N + q) * HD + (int64_t)h * DH;
-  const float *op32 = o32 + ((int64_t)b * N + q) * HD + (int64_t)h * DH;
+  const uint16_t *gp = dout + ((int64_t)b * N + qr) * HD + (int64_t)h * DH;
+  const float *op32 = o32 + ((int64_t)b * N + qr) * HD + (int64_t)h * DH;
   float dl = 0.f;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + (int64_t)q * ld + ks * 16 + g * 8);
+    qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + (int64_t)qr * ld + ks * 16 + g * 8);
     gf[ks] = *reinterpret_cast<const bf16x8 *>(gp + ks * 16 + g * 8);
     const f32x4 oa = *reinterpret_cast<const f32x4 *>(op32 + ks * 16 + g * 8), ob = *reinterpret_cast<const f32x4 *>(op32 + ks * 16 + g * 8 + 4);
 #pragma unroll
     for (int e = 0; e < 4; ++e) dl += (float)gf[ks][e] * oa[e] + (float)gf[ks][e + 4] * ob[e];
   }
   dl += __shfl_xor(dl, 32, 64);
-  if (g == 0) delta[((int64_t)b * Hs + h) * N + q] = dl;
+  if (g == 0 && q < N) delta[((int64_t)b * Hs + h) * N + q] = dl;
   const float dls = dl * scale;
   f32x16 acc[MT];
 #pragma unroll
@@ -693,8 +720,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
       for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        s = MFMA(frag(Kt + mt * 8192, ro.fo[ks]), qf[ks], s);
-        dp = MFMA(frag(Vt + mt * 8192, ro.fo[ks]), gf[ks], dp);
+        s = MFMA(frag(Kt + mt * 32 * RB, ro.fo[ks]), qf[ks], s);
+        dp = MFMA(frag(Vt + mt * 32 * RB, ro.fo[ks]), gf[ks], dp);
       }
       if (diag) {  // tiles that straddle the diagonal: keys after the query get no weight
 #pragma unroll
@@ -709,7 +736,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
       for (int t = 0; t < 2; ++t) {
         const bf16x8 df = pack8(s, 8 * t);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) acc[i] = MFMA(frag_tr(Kt + (mt * 32 + 16 * t) * 256, ro.ta[i], ro.tb[i]), df, acc[i]);
+        for (int i = 0; i < MT; ++i) acc[i] = MFMA(frag_tr(Kt + (mt * 32 + 16 * t) * RB, ro.ta[i], ro.tb[i]), df, acc[i]);
       }
     }
   };
@@ -717,7 +744,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
     step(kt, std::integral_constant<int, 0>());
     step(kt + 1, std::integral_constant<int, 1>());
   }
-  if (rope) rope_grad(acc, rope, q, g);
+  if (q >= N) return;
+  if (rope) rope_grad<DH>(acc, rope, q, g);
   uint16_t *op = dqkv + ((int64_t)b * N + q) * ld + (int64_t)h * DH;
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -739,15 +767,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 // products on the same SIMD.  One workgroup barrier per phase.  The 64-query Q / dO tiles live in three LDS stages (the
 // tile being loaded, the producer's, and the consumer's, which is half a tile behind), the hand-over area in two.
 // A workgroup handles the key blocks p and nkb-1-p one after the other, so that all workgroups carry the same work.
-constexpr int DKV_LD_OFF = 3 * STAGE_B;             // per stage: 64 log-sum-exps, 64 deltas
-constexpr int DKV_XCH_OFF = DKV_LD_OFF + 3 * 512;   // [2 phases][4 key blocks][P lo, P hi, dS lo, dS hi][64 lanes] x 16 bytes
-constexpr int DKV_SMEM = DKV_XCH_OFF + 2 * 4 * 4096;
 #define DL_WAIT_LGKM0 __builtin_amdgcn_s_waitcnt(0xc07f)
 
+template <int DH>
 __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *qkv, const uint16_t *dout, const float *lse, const float *delta,
                                                                uint16_t *dqkv, int N, int Hs, float scale, const float *rope, const int32_t *keep) {
-  __shared__ __attribute__((aligned(1024))) char smem[DKV_SMEM];
-  const int nkb = N / 128, npair = (nkb + 1) / 2, nbh = gridDim.x / npair;
+  using G = Geo<DH>;
+  constexpr int KS = G::KS, MT = G::MT, TILE_B = G::TILE_B, STAGE_B = G::STAGE_B, RB = G::RB;
+  constexpr int DKV_LD_OFF = 3 * STAGE_B;             // per stage: 64 log-sum-exps, 64 deltas
+  constexpr int DKV_XCH_OFF = DKV_LD_OFF + 3 * 512;   // [2 phases][4 key blocks][P lo, P hi, dS lo, dS hi][64 lanes] x 16 bytes
+  __shared__ __attribute__((aligned(1024))) char smem[DKV_XCH_OFF + 2 * 4 * 4096];
+  const int nkb = (N + 127) / 128, npair = (nkb + 1) / 2, nbh = gridDim.x / npair;
   const int pr = (int)blockIdx.x / nbh;
   const int bh = blockIdx.x % nbh, b = bh / Hs, h = bh % Hs;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
@@ -762,10 +792,10 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
   const desc_t rq = make_desc(batch, (uint32_t)(N * ld * 2)), rg = make_desc(gbatch, (uint32_t)(N * HD * 2));
   const desc_t rl = make_desc(lse_b, (uint32_t)(N * 4)), rd = make_desc(del_b, (uint32_t)(N * 4));
   const uint32_t qstep = (uint32_t)(64 * ld * 2), gstep = (uint32_t)(64 * HD * 2);
-  TileLoader lt;  // the producers bring in the query tile and the log-sum-exps, the consumers the dO tile and the deltas
+  TileLoader<DH> lt;  // the producers bring in the query tile and the log-sum-exps, the consumers the dO tile and the deltas
   if (producer) lt.init(ld, (uint32_t)(h * DH * 2), wk, lane);
   else lt.init(HD, (uint32_t)(h * DH * 2), wk, lane);
-  ReadOffsets ro;
+  ReadOffsets<DH> ro;
   ro.init(lane);
   const bool masked = keep && keep[h] < 0;  // masked head: the gradients are zero, nothing is loaded
   auto issue = [&](int qt, int st) {
@@ -781,9 +811,9 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
   for (int item = 0; item < 2; ++item) {
     const int kb = item ? nkb - 1 - pr : pr;
     if (item && 2 * pr == nkb - 1) break;  // an odd number of key blocks: the middle one has no partner
-    const int k0 = kb * 128 + wk * 32, kv = k0 + c;
+    const int k0 = kb * 128 + wk * 32, kv = k0 + c, kr = min(kv, N - 1);
     const int qt0 = kb * 2;                          // first query tile at or below the diagonal
-    const int n_steps = masked ? 0 : N / 64 - qt0;   // query tiles qt0 .. N/64 - 1
+    const int n_steps = masked ? 0 : (N + 63) / 64 - qt0;   // query tiles at or below the diagonal
     const int n_ph = 2 * n_steps;                    // phases of 32 queries; the consumer runs one phase behind
     if (n_steps) issue(qt0, 0);
     // phase ph covers queries [q_lo, q_lo + 32) of tile ph / 2 (stage (ph / 2) % 3); it is skipped when all of them
@@ -793,8 +823,8 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
       bf16x8 kf[KS], vf[KS];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        kf[ks] = *reinterpret_cast<const bf16x8 *>(qp + HD + (int64_t)kv * ld + ks * 16 + g * 8);
-        vf[ks] = *reinterpret_cast<const bf16x8 *>(qp + 2 * HD + (int64_t)kv * ld + ks * 16 + g * 8);
+        kf[ks] = *reinterpret_cast<const bf16x8 *>(qp + HD + (int64_t)kr * ld + ks * 16 + g * 8);
+        vf[ks] = *reinterpret_cast<const bf16x8 *>(qp + 2 * HD + (int64_t)kr * ld + ks * 16 + g * 8);
       }
       DL_WAIT_VM0;  // the first tile, and the key / value fragments
 #pragma unroll
@@ -806,7 +836,7 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
         const int q_lo = q_lo_of(ph);
         if (ph < n_ph && q_lo + 31 >= k0) {
           const int st = t % 3;
-          const char *Qt = smem + st * STAGE_B + mt * 8192, *Gt = Qt + TILE_B;
+          const char *Qt = smem + st * STAGE_B + mt * 32 * RB, *Gt = Qt + TILE_B;
           const float *Ls = reinterpret_cast<const float *>(smem + DKV_LD_OFF + st * 512) + mt * 32, *Ds = Ls + 64;
           f32x16 sv, dp;
 #pragma unroll
@@ -861,15 +891,15 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
         const int pp = ph - 1;  // the phase the producer finished before the last barrier
         if (pp >= 0 && q_lo_of(pp) + 31 >= k0) {
           const int st = (pp >> 1) % 3, mp = pp & 1;
-          const char *Qt = smem + st * STAGE_B + mp * 8192, *Gt = Qt + TILE_B;
+          const char *Qt = smem + st * STAGE_B + mp * 32 * RB, *Gt = Qt + TILE_B;
           const u32x4 *X = reinterpret_cast<const u32x4 *>(smem + DKV_XCH_OFF + ((pp & 1) * 4 + wk) * 4096);
 #pragma unroll
           for (int t2 = 0; t2 < 2; ++t2) {
             const bf16x8 pf = __builtin_bit_cast(bf16x8, X[t2 * 64 + lane]), df = __builtin_bit_cast(bf16x8, X[128 + t2 * 64 + lane]);
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
-              dv[i] = MFMA(frag_tr(Gt + 16 * t2 * 256, ro.ta[i], ro.tb[i]), pf, dv[i]);
-              dk[i] = MFMA(frag_tr(Qt + 16 * t2 * 256, ro.ta[i], ro.tb[i]), df, dk[i]);
+              dv[i] = MFMA(frag_tr(Gt + 16 * t2 * RB, ro.ta[i], ro.tb[i]), pf, dv[i]);
+              dk[i] = MFMA(frag_tr(Qt + 16 * t2 * RB, ro.ta[i], ro.tb[i]), df, dk[i]);
             }
           }
         }
@@ -877,17 +907,19 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
         DL_WAIT_LGKM0;  // every LDS read of the phase has returned before the stage and the hand-over area are released
         __builtin_amdgcn_s_barrier();
       }
-      if (rope) rope_grad(dk, rope, kv, g);
-      uint16_t *op = dqkv + ((int64_t)b * N + kv) * ld + (int64_t)h * DH;
+      if (kv < N) {
+        if (rope) rope_grad<DH>(dk, rope, kv, g);
+        uint16_t *op = dqkv + ((int64_t)b * N + kv) * ld + (int64_t)h * DH;
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          u32x2 wkk = {pack2(dk[i][4 * j], dk[i][4 * j + 1]), pack2(dk[i][4 * j + 2], dk[i][4 * j + 3])};
-          u32x2 wv = {pack2(dv[i][4 * j], dv[i][4 * j + 1]), pack2(dv[i][4 * j + 2], dv[i][4 * j + 3])};
-          *reinterpret_cast<u32x2 *>(op + HD + i * 32 + 8 * j + 4 * g) = wkk;
-          *reinterpret_cast<u32x2 *>(op + 2 * HD + i * 32 + 8 * j + 4 * g) = wv;
-        }
+          for (int j = 0; j < 4; ++j) {
+            u32x2 wkk = {pack2(dk[i][4 * j], dk[i][4 * j + 1]), pack2(dk[i][4 * j + 2], dk[i][4 * j + 3])};
+            u32x2 wv = {pack2(dv[i][4 * j], dv[i][4 * j + 1]), pack2(dv[i][4 * j + 2], dv[i][4 * j + 3])};
+            *reinterpret_cast<u32x2 *>(op + HD + i * 32 + 8 * j + 4 * g) = wkk;
+            *reinterpret_cast<u32x2 *>(op + 2 * HD + i * 32 + 8 * j + 4 * g) = wv;
+          }
+      }
     }
     __builtin_amdgcn_s_barrier();  // the next item's first loads overwrite stage 0
   }
@@ -895,29 +927,37 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
 
 }  // namespace dl
 
-// the pipelined kernels address a whole batch element through one 32-bit buffer range
-bool dl_ok(const twist_ctx *ctx, int N, int Hs, int dh) {
-  return !ctx->staged_attention && (int64_t)N * 3 * Hs * dh * 2 < (1ll << 31);
-}
-
-bool shape_ok(const void *a, const void *b, int N, int Hs, int dh) {
-  (void)Hs;
-  return (dh == 64 || dh == 128) && N % 128 == 0 && (reinterpret_cast<uintptr_t>(a) % 16) == 0 && (reinterpret_cast<uintptr_t>(b) % 16) == 0;
+// The pipelined kernels cover d_head 32, 64 and 128 and any N; they address a whole batch element through one 32-bit buffer
+// range.  Longer ones (and the staged_attention test switch) run the register-staged kernels: d_head 64 or 128, N % 128 == 0.
+enum Family { FAM_NONE, FAM_STAGED, FAM_DL };
+Family family(const twist_ctx *ctx, const void *a, const void *b, int N, int Hs, int dh) {
+  if (ctx->plain_only || (reinterpret_cast<uintptr_t>(a) % 16) || (reinterpret_cast<uintptr_t>(b) % 16)) return FAM_NONE;
+  if (!ctx->staged_attention && (dh == 32 || dh == 64 || dh == 128) && (int64_t)N * 3 * Hs * dh * 2 < (1ll << 31)) return FAM_DL;
+  return (dh == 64 || dh == 128) && N % 128 == 0 ? FAM_STAGED : FAM_NONE;
 }
 
 }  // namespace
 
+// runs `expr` with DH standing for the head width
+#define TW_BY_DH(dh, expr)                                \
+  do {                                                    \
+    if ((dh) == 128) { constexpr int DH = 128; expr; }    \
+    else if ((dh) == 64) { constexpr int DH = 64; expr; } \
+    else { constexpr int DH = 32; expr; }                 \
+  } while (0)
+
 twist_status twist_attention_fwd_mfma(twist_ctx *ctx, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep,
                                       bool *done) {
-  const bool off = ctx->plain_only;
   *done = false;
-  if (off || !shape_ok(qkv, o, N, Hs, dh)) return TWIST_OK;
+  const Family fam = family(ctx, qkv, o, N, Hs, dh);
+  if (fam == FAM_NONE) return TWIST_OK;
   const float scale = 1.0f / sqrtf((float)dh);
-  dim3 grid((unsigned)((int64_t)(N / 128) * B * Hs)), block(256);
+  dim3 grid((unsigned)((int64_t)((N + 127) / 128) * B * Hs)), block(256);
   const uint16_t *x = static_cast<const uint16_t *>(qkv);
-  if (dh == 128 && dl_ok(ctx, N, Hs, dh)) hipLaunchKernelGGL(dl::flash_fwd_dl_kernel, grid, block, 0, ctx->stream, x, static_cast<uint16_t *>(o), o32, lse, N, Hs, scale, keep);
-  else if (dh == 128) hipLaunchKernelGGL(flash_fwd_kernel<128>, grid, block, 0, ctx->stream, x, static_cast<uint16_t *>(o), o32, lse, N, Hs, scale, keep);
-  else hipLaunchKernelGGL(flash_fwd_kernel<64>, grid, block, 0, ctx->stream, x, static_cast<uint16_t *>(o), o32, lse, N, Hs, scale, keep);
+  uint16_t *out = static_cast<uint16_t *>(o);
+  if (fam == FAM_DL) TW_BY_DH(dh, hipLaunchKernelGGL(dl::flash_fwd_dl_kernel<DH>, grid, block, 0, ctx->stream, x, out, o32, lse, N, Hs, scale, keep));
+  else if (dh == 128) hipLaunchKernelGGL(flash_fwd_kernel<128>, grid, block, 0, ctx->stream, x, out, o32, lse, N, Hs, scale, keep);
+  else hipLaunchKernelGGL(flash_fwd_kernel<64>, grid, block, 0, ctx->stream, x, out, o32, lse, N, Hs, scale, keep);
   TW_HIP(ctx, hipGetLastError());
   *done = true;
   return TWIST_OK;
@@ -925,19 +965,19 @@ twist_status twist_attention_fwd_mfma(twist_ctx *ctx, const void *qkv, void *o, 
 
 twist_status twist_attention_bwd_mfma(twist_ctx *ctx, const void *qkv, const float *o32, const void *dout, const float *lse, float *delta, void *dqkv,
                                       int B, int N, int Hs, int dh, const float *rope_tab, const int32_t *keep, bool *done, bool *rope_done) {
-  const bool off = ctx->plain_only;
   *done = false;
   *rope_done = false;
-  if (off || !o32 || !shape_ok(qkv, dout, N, Hs, dh) || (reinterpret_cast<uintptr_t>(dqkv) % 16) || (reinterpret_cast<uintptr_t>(o32) % 16)) return TWIST_OK;
+  const Family fam = family(ctx, qkv, dout, N, Hs, dh);
+  if (fam == FAM_NONE || !o32 || (reinterpret_cast<uintptr_t>(dqkv) % 16) || (reinterpret_cast<uintptr_t>(o32) % 16)) return TWIST_OK;
   const float scale = 1.0f / sqrtf((float)dh);
-  dim3 grid((unsigned)((int64_t)(N / 128) * B * Hs)), block(256);
+  dim3 grid((unsigned)((int64_t)((N + 127) / 128) * B * Hs)), block(256);
   const uint16_t *x = static_cast<const uint16_t *>(qkv), *gout = static_cast<const uint16_t *>(dout);
   uint16_t *dx = static_cast<uint16_t *>(dqkv);
-  if (dh == 128 && dl_ok(ctx, N, Hs, dh)) {
+  if (fam == FAM_DL) {
     const float *rt = rope_tab && (reinterpret_cast<uintptr_t>(rope_tab) % 16) == 0 ? rope_tab : nullptr;
-    hipLaunchKernelGGL(dl::flash_bwd_dq_dl_kernel, grid, block, 0, ctx->stream, x, gout, o32, lse, delta, dx, N, Hs, scale, rt, keep);
-    hipLaunchKernelGGL(dl::flash_bwd_dkv_dl_kernel, dim3((unsigned)((int64_t)((N / 128 + 1) / 2) * B * Hs)), dim3(512), 0, ctx->stream, x, gout, lse, delta, dx, N, Hs, scale, rt,
-                       keep);
+    const dim3 pairs((unsigned)((int64_t)((N + 255) / 256) * B * Hs));
+    TW_BY_DH(dh, hipLaunchKernelGGL(dl::flash_bwd_dq_dl_kernel<DH>, grid, block, 0, ctx->stream, x, gout, o32, lse, delta, dx, N, Hs, scale, rt, keep);
+             hipLaunchKernelGGL(dl::flash_bwd_dkv_dl_kernel<DH>, pairs, dim3(512), 0, ctx->stream, x, gout, lse, delta, dx, N, Hs, scale, rt, keep));
     *rope_done = rt != nullptr;
   } else if (dh == 128) {
     hipLaunchKernelGGL(flash_bwd_dq_kernel<128>, grid, block, 0, ctx->stream, x, gout, o32, lse, delta, dx, N, Hs, scale, keep);

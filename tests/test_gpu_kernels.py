@@ -206,3 +206,43 @@ def test_attention_backward_through_rotary_positions(lib, dh, N, choice):
     got = to_numpy(dqkv).reshape(B, N, 3, Hs, dh)
     for i in range(3):
         assert rel_fro(got[:, :, i], want[i]) <= 5e-3, (i, rel_fro(got[:, :, i], want[i]))
+
+
+# every edge of the tiled kernels: one row, a partial and a full 32-row wave block, 64-row tile and 128-row workgroup block, the
+# tiles after it, and an odd number of key blocks with a ragged last one
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("N", [1, 31, 33, 64, 65, 127, 129, 200, 321])
+def test_attention_of_any_length(lib, dh, N):
+    Hs, B = 3, 2
+    cfg = si.ModelCfg(arch="llama", d_model=64, n_heads=Hs, d_head=dh, d_ff=8, rope=True, dtype=BF, max_seq=N)
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    qkv = _dev(_snap(si.normal(dh + N, "qkv", (B * N, 3 * Hs * dh)), BF), BF)
+    dout = _dev(_snap(si.normal(N, "dout", (B * N, Hs * dh)), BF), BF)
+    o, lse, dqkv = ctx.twist_attention_raw(qkv, dout, B, N, Hs, rope_backward=True)
+    torch.cuda.synchronize()
+    q, k, v = (to_numpy(qkv).reshape(B, N, 3, Hs, dh)[:, :, i] for i in range(3))
+    g = to_numpy(dout).reshape(B, N, Hs, dh)
+    want_o, p = omodel.attention_fwd(q, k, v)
+    assert rel_fro(to_numpy(o).reshape(B, N, Hs, dh), want_o) <= 5e-3
+    dq, dk, dv = omodel.attention_bwd(p, q, k, v, g)
+    cos, sin = omodel.rope_tables(N, dh, cfg.rope_theta)
+    want = (omodel.rope_apply(dq, cos, sin, -1.0), omodel.rope_apply(dk, cos, sin, -1.0), dv)
+    got = to_numpy(dqkv).reshape(B, N, 3, Hs, dh)
+    for i in range(3):
+        # dq and dk of a sequence of one are zero in exact arithmetic (one probability of 1): fp32 rounding of dp - delta is left,
+        # 1e-7 of |dO| |v| |k|
+        assert np.linalg.norm(got[:, :, i] - want[i]) <= 5e-3 * np.linalg.norm(want[i]) + 1e-5 * np.linalg.norm(g) * dh, i
+
+
+def test_staged_attention_of_64_wide_heads(lib):
+    """The register-staged kernels still serve 64-wide heads of batch elements beyond the pipelined kernels' 2 GiB range."""
+    Hs, B, N, dh = 2, 2, 256, 64
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=Hs, d_head=dh, d_ff=8, dtype=BF, max_seq=N)))
+    qkv = _dev(_snap(si.normal(3, "qkv", (B * N, 3 * Hs * dh)), BF), BF)
+    dout = _dev(_snap(si.normal(4, "dout", (B * N, Hs * dh)), BF), BF)
+    a = ctx.twist_attention_raw(qkv, dout, B, N, Hs)
+    ctx.twist_set_kernel_choice(staged_attention=True)
+    b = ctx.twist_attention_raw(qkv, dout, B, N, Hs)
+    torch.cuda.synchronize()
+    for x, y in zip(a, b):
+        assert rel_fro(to_numpy(x), to_numpy(y)) <= 5e-3
