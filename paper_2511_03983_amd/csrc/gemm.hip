@@ -3,7 +3,8 @@
 //    loads for all but the smallest products, and a 128x128 register-staged kernel; operands stay in LDS in their
 //    memory orientation, and those whose contraction index is the slow axis in memory are read back with the
 //    transposing LDS load.
-//  - anything else (fp32 models, unaligned shapes): a plain tiled FMA kernel with arbitrary strides.
+//  - fp32 operands: the fp32 matrix instruction (gemm_f32.hip).
+//  - anything else (unaligned bf16 shapes): a plain tiled FMA kernel with arbitrary strides.
 #include <algorithm>
 
 #include "nn.h"
@@ -658,6 +659,13 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 
 }  // namespace
 
+twist_status twist_splitk_reduce(twist_ctx *ctx, hipStream_t st, const float *parts_ws, int parts, int M, int N, void *out, int64_t ldc, int out_f32, float alpha) {
+  const int64_t groups = ((int64_t)M * N + 3) / 4;
+  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, parts_ws, parts, M, N, out, ldc, out_f32, alpha);
+  TW_HIP(ctx, hipGetLastError());
+  return TWIST_OK;
+}
+
 twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, int K, const void *A, int64_t lda, const void *B, int64_t ldb,
                         int64_t ldc, const GemmEpilogue &e, hipStream_t st) {
   if (M <= 0 || N <= 0 || K <= 0) return TWIST_OK;
@@ -700,10 +708,7 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
         case GEMM_TN: hipLaunchKernelGGL((pp::gemm_pp_kernel<0, 0, true>), grid, block, 0, stream, M, N, K, a, lda, b, ldb, part, tm, tn, ks, kchunk); break;
       }
       TW_HIP(ctx, hipGetLastError());
-      const int64_t groups = ((int64_t)M * N + 3) / 4;
-      hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, stream, e.splitk_ws, ks, M, N, e.out, ldc, e.out_f32, e.alpha);
-      TW_HIP(ctx, hipGetLastError());
-      return TWIST_OK;
+      return twist_splitk_reduce(ctx, stream, e.splitk_ws, ks, M, N, e.out, ldc, e.out_f32, e.alpha);
     }
     switch (lay) {
       case GEMM_NT: launch_mfma<1, 1>(stream, ctx->gemm_tile, M, N, K, a, lda, b, ldb, ep); break;
@@ -713,6 +718,7 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
     TW_HIP(ctx, hipGetLastError());
     return TWIST_OK;
   }
+  if (!bf16 && !no_mfma) return twist_gemm_f32(ctx, stream, lay, M, N, K, static_cast<const float *>(A), lda, static_cast<const float *>(B), ldb, ldc, e);
   int64_t sam, sak, sbk, sbn;
   switch (lay) {
     case GEMM_NT: sam = lda; sak = 1; sbk = 1; sbn = ldb; break;

@@ -28,6 +28,13 @@ enum GemmLayout {
 twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, int K, const void *A, int64_t lda, const void *B,
                         int64_t ldb, int64_t ldc, const GemmEpilogue &ep, hipStream_t st = nullptr);
 
+// the fp32 form of twist_gemm, and the sum of the partial products [parts][M][N] of a product whose contraction was cut
+// (out = alpha * sum in ascending order)
+twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
+                            int64_t ldc, const GemmEpilogue &e);
+twist_status twist_splitk_reduce(twist_ctx *ctx, hipStream_t st, const float *parts_ws, int parts, int M, int N, void *out, int64_t ldc, int out_f32,
+                                 float alpha);
+
 // causal multi-head attention on a fused qkv buffer [T, 3*Hs*dh] (q | k | v); o [T, Hs*dh]; lse [B,Hs,N] fp32.
 // o32 (may be null): the same output unrounded, [T, Hs*dh] fp32, written by the tiled bf16 kernels only; the
 // tiled backward kernels need it (without it, or on shapes they do not cover, the plain kernels run).

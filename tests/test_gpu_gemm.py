@@ -52,6 +52,38 @@ def test_fp32_projection(lib):
         assert rel_fro(to_numpy(out), want) <= 1e-4
 
 
+# fp32 matrix-instruction kernel: 64- and 128-wide tiles (128 pinned, and by size at 3000 x 2900), ragged edges, contractions that end
+# inside a slice of 32, strides that allow 16-byte loads and strides that do not (odd K, M or N)
+@pytest.mark.parametrize("tile", [0, 128])
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (64, 64, 32), (65, 63, 33), (132, 260, 100), (300, 200, 136), (127, 129, 31), (40, 72, 1028)])
+def test_fp32_projection_edges(lib, tile, layout, M, N, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    ctx.twist_set_kernel_choice(gemm_tile=tile)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((K, M) if layout == 2 else (M, K), generator=gen, device="cuda")
+    B = torch.randn((N, K) if layout == 0 else (K, N), generator=gen, device="cuda")
+    want = (A.double().T if layout == 2 else A.double()) @ (B.double().T if layout == 0 else B.double())
+    buf = torch.full((M * N + 64,), float("nan"), device="cuda")            # what lies behind the result must stay
+    out = buf[:M * N].view(M, N)
+    ctx.twist_gemm_raw(layout, M, N, K, A, B, out, alpha=0.5)
+    torch.cuda.synchronize()
+    # K products of one rounding each and K additions: 2^-24 sqrt(2 K) at most about 3e-6 here
+    assert float((out.double() - 0.5 * want).norm() / (0.5 * want).norm()) <= 3e-6
+    assert torch.isnan(buf[M * N:]).all()
+
+
+def test_fp32_projection_by_size_takes_the_large_tiles(lib):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    M, N, K = 3000, 2900, 72
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    A, B = torch.randn((M, K), generator=gen, device="cuda"), torch.randn((N, K), generator=gen, device="cuda")
+    out = torch.full((M, N), float("nan"), device="cuda")
+    ctx.twist_gemm_raw(0, M, N, K, A, B, out)
+    want = A.double() @ B.double().T
+    assert float((out.double() - want).norm() / want.norm()) <= 3e-6
+
+
 def test_raw_rejects_bad_strides(lib):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
     A = torch.zeros(16, 8, dtype=torch.bfloat16, device="cuda")
