@@ -1,0 +1,268 @@
+// Tiled causal attention for fp32 models on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32), forward and backward,
+// d_head a multiple of 4 up to 128, any N.
+//
+// A workgroup owns 32 query rows (forward, dQ) or 32 key rows (dK / dV) of one head; its four waves share out the tiles of 32 keys
+// (or queries) that those rows see, wave w taking tiles w, w + 4, ..., each with accumulators of its own, and the four results are
+// added in wave order through LDS at the end.  That gives N / 32 workgroups per head, each a quarter as long as one wave would be:
+// these models are small, and what bounds the kernels is the chain of dependent steps and how many waves there are, then the
+// matrix pipes (64 cycles per instruction).  Operands go from global memory to registers: waves share no tile, and a head's keys
+// and values stay in the L2.
+// As in the bf16 kernels scores are formed transposed (a lane owns a query, or a key in the dK / dV kernel), and a score tile is
+// the B operand of the next product as it stands: MFMA number r contracts the rows 8 (r / 4) + 4 g + r % 4 (g = lane / 32), which
+// is where accumulator register r sits.  Along d_head, MFMA 4 u + e contracts columns 8 u + 4 g + e: one 16-byte load per lane
+// feeds four instructions.
+// delta_i = dO_i . O_i from the fp32 output.  Rows beyond N are clamped when read and not stored; keys beyond N come after
+// every query, and queries beyond N get probability zero.
+//
+// Measured (forward / dQ / dK dV) on 2 x 512 tokens, 6 heads of 64: 20 / 30 / 37 us against 423 / 905 / 427 us of the plain kernels
+// (a wave per row, a wave reduction per score), and closer to exact arithmetic (query / key gradients 5e-6 against 3e-5).
+#include "nn.h"
+
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+#define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32((a), (b), (c), 0, 0, 0)
+
+// one row's values for the contraction along d_head: group u holds columns 8 u + 4 g .. + 3 (zeros beyond dh)
+template <int DH>
+__device__ __forceinline__ void load_row(f32x4 (&f)[DH / 8], const float *row, int dh, int g) {
+#pragma unroll
+  for (int u = 0; u < DH / 8; ++u) {
+    const int k = 8 * u + 4 * g;
+    f[u] = k < dh ? *reinterpret_cast<const f32x4 *>(row + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+}
+// 32 x 32 tile of A B^T along d_head: `a` = this lane's row of A, `b` = this lane's column
+template <int DH>
+__device__ __forceinline__ f32x16 dot_tile(const f32x4 (&a)[DH / 8], const f32x4 (&b)[DH / 8]) {
+  f32x16 s;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+  for (int u = 0; u < DH / 8; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = MFMA(a[u][e], b[u][e], s);
+  return s;
+}
+// acc[i] += X^T[32 i ..][rows] w[rows][column]: X rows row0 .. row0 + 31 (clamped to N - 1), w in accumulator layout
+template <int DH>
+__device__ __forceinline__ void add_tile(f32x16 (&acc)[DH / 32], const float *x, int64_t ld, int row0, int N, int dh, const f32x16 &w, int c, int g) {
+#pragma unroll
+  for (int i = 0; i < DH / 32; ++i) {
+    if (32 * i >= dh) break;
+    const int col = min(32 * i + c, dh - 1);  // columns beyond dh give rows of the result that are not stored
+    float v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = x[(int64_t)min(row0 + 8 * (r >> 2) + 4 * g + (r & 3), N - 1) * ld + col];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i] = MFMA(v[r], w[r], acc[i]);
+  }
+}
+template <int DH>
+__device__ __forceinline__ void zero(f32x16 (&acc)[DH / 32]) {
+#pragma unroll
+  for (int i = 0; i < DH / 32; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+}
+
+// Sum of the four waves' [dh][32] accumulators (each multiplied by its lane's `mul`) written as rows of `out` (stride ld)
+template <int DH>
+__device__ __forceinline__ void merge(float *lds, const f32x16 (&acc)[DH / 32], float mul, float *out, int64_t ld, int rows_left, int dh, int wave, int c, int g) {
+  constexpr int LDR = DH + 4;
+#pragma unroll
+  for (int i = 0; i < DH / 32; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<f32x4 *>(lds + (wave * 32 + c) * LDR + 32 * i + 8 * j + 4 * g) =
+          f32x4{acc[i][4 * j] * mul, acc[i][4 * j + 1] * mul, acc[i][4 * j + 2] * mul, acc[i][4 * j + 3] * mul};
+  __syncthreads();
+  const int row = threadIdx.x >> 3;
+  if (row < rows_left)
+    for (int k = (threadIdx.x & 7) * 4; k < dh; k += 32) {
+      f32x4 v = *reinterpret_cast<const f32x4 *>(lds + row * LDR + k);
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f32x4 *>(lds + (w * 32 + row) * LDR + k);
+      *reinterpret_cast<f32x4 *>(out + row * ld + k) = v;
+    }
+  __syncthreads();
+}
+
+struct Item { int blk, b, h; };
+// late query blocks (early key blocks) are the longest: they start first
+__device__ __forceinline__ Item item_of(int N, int Hs, bool late_first) {
+  const int nb = (N + 31) / 32, nbh = gridDim.x / nb, rank = (int)blockIdx.x / nbh, bh = (int)blockIdx.x % nbh;
+  return {late_first ? nb - 1 - rank : rank, bh / Hs, bh % Hs};
+}
+
+template <int DH>
+__global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const float *qkv, float *o, float *lse, int N, int Hs, int dh, float scale, const int32_t *keep) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
+  __shared__ float ms[4][32], ls[4][32];
+  const Item it = item_of(N, Hs, true);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
+  const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
+  const float *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
+  const int q0 = it.blk * 32, q = q0 + c;
+  const float sc = scale * kLog2e;
+  const bool masked = keep && keep[it.h] < 0;  // masked head (Masked TwIST, Section 4.1): no key is visited, zeros are written
+  f32x4 qf[DH / 8], kf[DH / 8];
+  load_row<DH>(qf, qp + (int64_t)min(q, N - 1) * ld, dh, g);
+  f32x16 acc[DH / 32];
+  zero<DH>(acc);
+  float m = -INFINITY, l = 0.f;
+  for (int kt = wave; kt <= it.blk && !masked; kt += 4) {
+    load_row<DH>(kf, kp + (int64_t)min(kt * 32 + c, N - 1) * ld, dh, g);
+    f32x16 s = dot_tile<DH>(kf, qf);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (kt * 32 + 8 * (r >> 2) + 4 * g + (r & 3) > q) s[r] = -INFINITY;
+      mx = fmaxf(mx, s[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mn = fmaxf(m, mx * sc);  // finite: the tile's first key is visible to every query of the block
+    const float alpha = fast_exp2(m - mn);
+    float sum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { s[r] = fast_exp2(fmaf(s[r], sc, -mn)); sum += s[r]; }
+    l = l * alpha + sum;
+    m = mn;
+#pragma unroll
+    for (int i = 0; i < DH / 32; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] *= alpha;
+    add_tile<DH>(acc, vp, ld, kt * 32, N, dh, s, c, g);
+  }
+  l += __shfl_xor(l, 32, 64);
+  if (g == 0) { ms[wave][c] = m; ls[wave][c] = l; }
+  __syncthreads();
+  const float mt = fmaxf(fmaxf(ms[0][c], ms[1][c]), fmaxf(ms[2][c], ms[3][c]));
+  float lt = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) lt += ls[w][c] * fast_exp2(ms[w][c] - mt);
+  const float mul = masked ? 0.f : fast_exp2(m - mt) / lt;  // a wave without tiles has m = -inf: factor 0
+  if (wave == 0 && g == 0 && q < N) lse[((int64_t)it.b * Hs + it.h) * N + q] = masked ? 0.f : (mt + log2f(lt)) * kLn2;
+  merge<DH>(lds, acc, mul, o + ((int64_t)it.b * N + q0) * HD + (int64_t)it.h * dh, HD, N - q0, dh, wave, c, g);
+}
+
+template <int DH>
+__global__ __launch_bounds__(256) void attn_f32_dq_kernel(const float *qkv, const float *dout, const float *o, const float *lse, float *delta, float *dqkv, int N,
+                                                          int Hs, int dh, float scale, const int32_t *keep) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
+  const Item it = item_of(N, Hs, true);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
+  const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
+  const float *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
+  const int q0 = it.blk * 32, q = q0 + c, qr = min(q, N - 1);
+  const float sc = scale * kLog2e;
+  const int64_t row = ((int64_t)it.b * N + qr) * HD + (int64_t)it.h * dh, stat = ((int64_t)it.b * Hs + it.h) * N;
+  const float L2 = lse[stat + qr] * kLog2e;
+  f32x4 qf[DH / 8], gf[DH / 8], kf[DH / 8];
+  load_row<DH>(qf, qp + (int64_t)qr * ld, dh, g);
+  load_row<DH>(gf, dout + row, dh, g);
+  load_row<DH>(kf, o + row, dh, g);
+  float dl = 0.f;
+#pragma unroll
+  for (int u = 0; u < DH / 8; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dl += gf[u][e] * kf[u][e];
+  dl += __shfl_xor(dl, 32, 64);
+  if (wave == 0 && g == 0 && q < N) delta[stat + q] = dl;
+  const bool masked = keep && keep[it.h] < 0;
+  f32x16 acc[DH / 32];
+  zero<DH>(acc);
+  for (int kt = wave; kt <= it.blk && !masked; kt += 4) {
+    const int64_t kr = min(kt * 32 + c, N - 1);
+    load_row<DH>(kf, kp + kr * ld, dh, g);
+    f32x16 s = dot_tile<DH>(kf, qf);
+    load_row<DH>(kf, vp + kr * ld, dh, g);
+    const f32x16 dp = dot_tile<DH>(kf, gf);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float p = kt * 32 + 8 * (r >> 2) + 4 * g + (r & 3) > q ? 0.f : fast_exp2(fmaf(s[r], sc, -L2));
+      s[r] = p * (dp[r] - dl) * scale;
+    }
+    add_tile<DH>(acc, kp, ld, kt * 32, N, dh, s, c, g);
+  }
+  merge<DH>(lds, acc, 1.f, dqkv + ((int64_t)it.b * N + q0) * ld + (int64_t)it.h * dh, ld, N - q0, dh, wave, c, g);
+}
+
+template <int DH>
+__global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const float *qkv, const float *dout, const float *lse, const float *delta, float *dqkv, int N, int Hs,
+                                                           int dh, float scale, const int32_t *keep) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
+  const Item it = item_of(N, Hs, false);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
+  const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
+  const float *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
+  const float *gp = dout + (int64_t)it.b * N * HD + (int64_t)it.h * dh;
+  const int k0 = it.blk * 32, kv = k0 + c, kr = min(kv, N - 1);
+  const float sc = scale * kLog2e;
+  const float *lse_b = lse + ((int64_t)it.b * Hs + it.h) * N, *del_b = delta + ((int64_t)it.b * Hs + it.h) * N;
+  const bool masked = keep && keep[it.h] < 0;
+  f32x4 kf[DH / 8], vf[DH / 8], xf[DH / 8];
+  load_row<DH>(kf, kp + (int64_t)kr * ld, dh, g);
+  load_row<DH>(vf, vp + (int64_t)kr * ld, dh, g);
+  f32x16 dk[DH / 32], dv[DH / 32];
+  zero<DH>(dk);
+  zero<DH>(dv);
+  const int n_q = (N + 31) / 32;
+  for (int qt = it.blk + wave; qt < n_q && !masked; qt += 4) {
+    const int q0 = qt * 32;
+    const int64_t qr = min(q0 + c, N - 1);
+    load_row<DH>(xf, qp + qr * ld, dh, g);
+    f32x16 s = dot_tile<DH>(xf, kf);
+    load_row<DH>(xf, gp + qr * HD, dh, g);
+    f32x16 dp = dot_tile<DH>(xf, vf);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int q = q0 + 8 * (r >> 2) + 4 * g + (r & 3), qc = min(q, N - 1);
+      const float p = (q < kv || q >= N) ? 0.f : fast_exp2(fmaf(s[r], sc, -lse_b[qc] * kLog2e));
+      dp[r] = p * (dp[r] - del_b[qc]) * scale;
+      s[r] = p;
+    }
+    add_tile<DH>(dv, gp, HD, q0, N, dh, s, c, g);
+    add_tile<DH>(dk, qp, ld, q0, N, dh, dp, c, g);
+  }
+  float *out = dqkv + ((int64_t)it.b * N + k0) * ld + HD + (int64_t)it.h * dh;
+  merge<DH>(lds, dk, 1.f, out, ld, N - k0, dh, wave, c, g);
+  merge<DH>(lds, dv, 1.f, out + HD, ld, N - k0, dh, wave, c, g);
+}
+
+bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+}  // namespace
+
+#define TW_F32_DH(dh, expr)                              \
+  do {                                                   \
+    if ((dh) <= 32) { constexpr int DH = 32; expr; }      \
+    else if ((dh) <= 64) { constexpr int DH = 64; expr; } \
+    else { constexpr int DH = 128; expr; }               \
+  } while (0)
+
+bool twist_attention_f32_ok(const twist_ctx *ctx, const void *qkv, const void *o, const void *dout, const void *dqkv, int dh) {
+  return !ctx->plain_only && dh % 4 == 0 && dh <= 128 && al16(qkv) && al16(o) && al16(dout) && al16(dqkv);
+}
+
+twist_status twist_attention_f32_fwd(twist_ctx *ctx, const float *qkv, float *o, float *lse, int B, int N, int Hs, int dh, const int32_t *keep) {
+  const dim3 grid((unsigned)((int64_t)((N + 31) / 32) * B * Hs)), block(256);
+  const float scale = 1.0f / sqrtf((float)dh);
+  TW_F32_DH(dh, hipLaunchKernelGGL(attn_f32_fwd_kernel<DH>, grid, block, 0, ctx->stream, qkv, o, lse, N, Hs, dh, scale, keep));
+  TW_HIP(ctx, hipGetLastError());
+  return TWIST_OK;
+}
+
+twist_status twist_attention_f32_bwd(twist_ctx *ctx, const float *qkv, const float *o, const float *dout, const float *lse, float *delta, float *dqkv, int B, int N,
+                                     int Hs, int dh, const int32_t *keep) {
+  const dim3 grid((unsigned)((int64_t)((N + 31) / 32) * B * Hs)), block(256);
+  const float scale = 1.0f / sqrtf((float)dh);
+  TW_F32_DH(dh, hipLaunchKernelGGL(attn_f32_dq_kernel<DH>, grid, block, 0, ctx->stream, qkv, dout, o, lse, delta, dqkv, N, Hs, dh, scale, keep);
+            hipLaunchKernelGGL(attn_f32_dkv_kernel<DH>, grid, block, 0, ctx->stream, qkv, dout, lse, delta, dqkv, N, Hs, dh, scale, keep));
+  TW_HIP(ctx, hipGetLastError());
+  return TWIST_OK;
+}

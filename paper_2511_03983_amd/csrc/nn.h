@@ -43,10 +43,16 @@ twist_status twist_splitk_reduce(twist_ctx *ctx, hipStream_t st, const float *pa
 twist_status twist_attention_fwd(twist_ctx *ctx, int bf16, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh,
                                  const int32_t *keep = nullptr);
 // dqkv [T, 3*Hs*dh] from do [T, Hs*dh]; delta [B,Hs,N] fp32 scratch (sum_j p_ij dp_ij, written by the dq pass).
+// o_f32: the forward output in fp32 (bf16 models: the unrounded copy o32; fp32 models: o itself; null: the plain kernels run).
 // rope_tab (may be null): the table of twist_rope_table; when given, the q and k gradients are also taken back through
 // the rotary embedding (inside the tiled kernels where they cover the shape, else by twist_rope_apply afterwards).
-twist_status twist_attention_bwd(twist_ctx *ctx, int bf16, const void *qkv, const float *o32, const void *dout, const float *lse, float *delta,
+twist_status twist_attention_bwd(twist_ctx *ctx, int bf16, const void *qkv, const float *o_f32, const void *dout, const float *lse, float *delta,
                                  void *dqkv, int B, int N, int Hs, int dh, const float *rope_tab, const int32_t *keep = nullptr);
+// the tiled fp32 kernels behind the two calls above, and whether they cover the operands
+bool twist_attention_f32_ok(const twist_ctx *ctx, const void *qkv, const void *o, const void *dout, const void *dqkv, int dh);
+twist_status twist_attention_f32_fwd(twist_ctx *ctx, const float *qkv, float *o, float *lse, int B, int N, int Hs, int dh, const int32_t *keep);
+twist_status twist_attention_f32_bwd(twist_ctx *ctx, const float *qkv, const float *o, const float *dout, const float *lse, float *delta, float *dqkv, int B, int N,
+                                     int Hs, int dh, const int32_t *keep);
 
 twist_status twist_embed_fwd(twist_ctx *ctx, int bf16, const int32_t *tok, const void *tok_embed, const void *pos_embed, float *x, int B, int N, int D, int vocab);
 twist_status twist_embed_bwd(twist_ctx *ctx, const int32_t *tok, const float *dx, float *d_tok, float *d_pos, int B, int N, int D);

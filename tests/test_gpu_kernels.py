@@ -246,3 +246,28 @@ def test_staged_attention_of_64_wide_heads(lib):
     torch.cuda.synchronize()
     for x, y in zip(a, b):
         assert rel_fro(to_numpy(x), to_numpy(y)) <= 5e-3
+
+
+# fp32: head widths below, at and above a 32-column block; lengths below, at and beyond a 32-row tile and beyond four of them
+@pytest.mark.parametrize("dh", [4, 16, 32, 36, 64, 128])
+@pytest.mark.parametrize("N", [1, 31, 32, 33, 97, 160, 200])
+def test_fp32_attention_of_any_length(lib, dh, N):
+    Hs, B = 3, 2
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=Hs, d_head=dh, d_ff=8, max_seq=N)))
+    qkv = _dev(_snap(si.normal(dh + N, "qkv", (B * N, 3 * Hs * dh)), F32), F32)
+    dout = _dev(_snap(si.normal(N, "dout", (B * N, Hs * dh)), F32), F32)
+    q, k, v = (to_numpy(qkv).reshape(B, N, 3, Hs, dh)[:, :, i] for i in range(3))
+    g = to_numpy(dout).reshape(B, N, Hs, dh)
+    want_o, p = omodel.attention_fwd(q, k, v)
+    want = omodel.attention_bwd(p, q, k, v, g)
+    for keep_np in (None, np.array([0, -1, 3], np.int32)):
+        on = np.ones(Hs, bool) if keep_np is None else keep_np >= 0
+        o, lse, dqkv = ctx.twist_attention_raw(qkv, dout, B, N, Hs, keep=None if keep_np is None else torch.tensor(keep_np).cuda())
+        torch.cuda.synchronize()
+        o, got = to_numpy(o).reshape(B, N, Hs, dh), to_numpy(dqkv).reshape(B, N, 3, Hs, dh)
+        assert rel_fro(o[:, :, on], want_o[:, :, on]) <= 3e-6
+        assert not o[:, :, ~on].any() and not got[:, :, :, ~on].any()
+        for i in range(3):
+            # a sequence of one has dq = dk = 0 in exact arithmetic; what is left is the rounding of dp - delta, 1e-7 of |dO| |v| |k|
+            err = np.linalg.norm(got[:, :, i][:, :, on] - want[i][:, :, on])
+            assert err <= 1e-5 * np.linalg.norm(want[i][:, :, on]) + 1e-6 * np.linalg.norm(g) * dh, (i, err)
