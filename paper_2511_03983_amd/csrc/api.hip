@@ -441,6 +441,22 @@ bool make_job(const twist_ctx *ctx, const twist_plan *plan, int l, int t, const 
   return true;
 }
 
+}  // namespace
+
+int twist_tensor_kind(const twist_model_desc &d, int t) {
+  const Cut *c = cut_of(d, t);
+  return c ? c->kind : -1;
+}
+
+void twist_tensor_shape(const twist_model_desc &d, int t, int heads, int units, int &rows, int &cols) {
+  rows = cols = 0;
+  if (!layer_tensor_present(d, t)) return;
+  full_shape(d, t, rows, cols);
+  if (const Cut *c = cut_of(d, t)) (c->axis == 0 ? rows : cols) = c->kind == TWIST_KIND_HEAD ? heads * d.d_head : units * d.ffn_granule;
+}
+
+namespace {
+
 int job_blocks(const MoveJob &jb) { return jb.tiles_per_row * ((jb.rows + jb.tile_rows - 1) / jb.tile_rows); }
 
 twist_status check_full(twist_ctx *ctx, const twist_full_weights *full, const char *who) {
@@ -493,6 +509,48 @@ twist_status for_each_group(twist_ctx *ctx, const twist_plan *plan, const twist_
 }
 
 }  // namespace
+
+namespace {
+
+int64_t flat_blocks(const MoveJob &jb, int vn) { return ((int64_t)jb.rows * jb.n_full * (jb.vec ? jb.Q / vn : jb.Q) + kAccumPerBlock - 1) / kAccumPerBlock; }
+
+}  // namespace
+
+twist_status twist_gather_layer(twist_ctx *ctx, const twist_plan *plan, int l, int s, const void *const *full, const int64_t *dst_off, char *dst) {
+  MoveLaunch ml;
+  std::memset(&ml, 0, sizeof ml);
+  ml.sub_base[0] = dst;
+  int blocks = 0;
+  for (int t = 0; t < TWIST_N_LAYER_TENSORS; ++t) {
+    MoveJob &jb = ml.job[ml.n_jobs];
+    if (dst_off[t] < 0 || !make_job(ctx, plan, l, t, full[t], s, false, 0, jb)) continue;
+    jb.sub_off = dst_off[t];
+    jb.blk_begin = ml.blk_begin[ml.n_jobs] = blocks;
+    blocks += job_blocks(jb);
+    ++ml.n_jobs;
+  }
+  return twist_launch_extract(ctx, ml, blocks);
+}
+
+twist_status twist_expand_layer(twist_ctx *ctx, hipStream_t st, const twist_plan *plan, int l, int s, float *const *full, const int64_t *src_off, const float *src,
+                                uint32_t only) {
+  MoveLaunch ml;
+  std::memset(&ml, 0, sizeof ml);
+  ml.sub_base[0] = reinterpret_cast<const char *>(src);
+  ml.sub_row[0] = s;
+  int64_t blocks = 0;
+  for (int t = 0; t < TWIST_N_LAYER_TENSORS; ++t) {
+    MoveJob &jb = ml.job[ml.n_jobs];
+    if (!(only >> t & 1) || src_off[t] < 0 || !make_job(ctx, plan, l, t, full[t], s, true, 1, jb)) continue;
+    jb.sub_off = src_off[t];
+    jb.vec = jb.Q % 4 == 0 && src_off[t] % 4 == 0 && reinterpret_cast<uintptr_t>(full[t]) % 16 == 0 && reinterpret_cast<uintptr_t>(src) % 16 == 0;
+    jb.blk_begin = ml.blk_begin[ml.n_jobs] = (int32_t)blocks;
+    blocks += flat_blocks(jb, 4);
+    if (blocks * kAccumPerBlock >= (int64_t)1 << 31) TW_FAIL(ctx, TWIST_ESHAPE, "masked pass: a layer's gradients exceed the 32-bit index range");
+    ++ml.n_jobs;
+  }
+  return twist_launch_expand(ctx, st, ml, (int)blocks);
+}
 
 namespace {
 

@@ -805,6 +805,38 @@ __global__ __launch_bounds__(kThreads) void accumulate_kernel(const MoveLaunch m
   else accumulate_body<ES, 1, FINISH>(ml, jb, lb);
 }
 
+// ------------------------------------------------------------------------------------------- expand (masked pass)
+// fp32 values of the kept blocks back into full-width tensors, zeros in the other blocks: one pass over the full tensor, a lookup
+// in the inverse table per vector.  HBM-bound: reads the kept values, writes everything once.
+template <int VN>
+__device__ __forceinline__ void expand_body(const MoveLaunch &ml, const MoveJob &jb, uint32_t lb) {
+  const uint32_t q = jb.Q / VN, Wf = (uint32_t)jb.n_full * q, Ws = (uint32_t)jb.n_sub * q, total = (uint32_t)jb.rows * Wf;
+  const float *src = reinterpret_cast<const float *>(ml.sub_base[0]) + jb.sub_off;
+  float *out = reinterpret_cast<float *>(const_cast<void *>(jb.full));
+#pragma unroll
+  for (int u = 0; u < kAccumPerBlock / kThreads; ++u) {
+    const uint32_t f = lb * (uint32_t)kAccumPerBlock + u * kThreads + threadIdx.x;
+    if (f >= total) continue;
+    const uint32_t row = f / Wf, v = f - row * Wf, unit = v / q, j = v - unit * q;
+    const int p = jb.table[(int64_t)ml.sub_row[0] * jb.n_full + unit];
+    const int64_t from = (int64_t)row * Ws + (int64_t)p * q + j;
+    if (VN == 4) {
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+      if (p >= 0) x = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(src) + from);
+      __builtin_nontemporal_store(x, reinterpret_cast<f32x4 *>(out) + f);
+    } else {
+      out[f] = p >= 0 ? src[from] : 0.f;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void expand_kernel(const MoveLaunch ml) {
+  const MoveJob &jb = ml.job[find_job(ml, blockIdx.x)];
+  const uint32_t lb = blockIdx.x - jb.blk_begin;
+  if (jb.vec) expand_body<4>(ml, jb, lb);
+  else expand_body<1>(ml, jb, lb);
+}
+
 // ------------------------------------------------------------------------------------------- helpers
 template <int ES>
 __global__ __launch_bounds__(kThreads) void to_f32_kernel(const void *src, float *dst, int64_t n) {
@@ -876,6 +908,13 @@ twist_status twist_launch_accumulate(twist_ctx *ctx, const MoveLaunch &ml, int t
     if (finish) hipLaunchKernelGGL((accumulate_kernel<4, true>), g, b, 0, ctx->stream, ml);
     else hipLaunchKernelGGL((accumulate_kernel<4, false>), g, b, 0, ctx->stream, ml);
   }
+  TW_HIP(ctx, hipGetLastError());
+  return TWIST_OK;
+}
+
+twist_status twist_launch_expand(twist_ctx *ctx, hipStream_t st, const MoveLaunch &ml, int total_blocks) {
+  if (total_blocks <= 0) return TWIST_OK;
+  hipLaunchKernelGGL(expand_kernel, dim3(total_blocks), dim3(kThreads), 0, st ? st : ctx->stream, ml);
   TW_HIP(ctx, hipGetLastError());
   return TWIST_OK;
 }

@@ -28,7 +28,20 @@ struct LayerBufs {
   float *lse, *o32;  // o32: unrounded attention output (bf16 models), feeds the backward pass's delta
 };
 
+// Masked TwIST on the kept blocks only: the kept blocks of a layer's partitioned tensors are gathered into a scratch copy of one
+// layer, the layer runs dense at its kept width, and its gradients are spread back with zeros in the masked blocks.  The scratch
+// holds one layer at a time (weights again for the backward pass), so the whole fits the workspace that the full-width pass was
+// sized for as soon as the batch is a few hundred tokens: the activations shrink with the width.
+struct Compact {
+  bool on = false;
+  int64_t off[TWIST_N_LAYER_TENSORS];       // element offsets of one layer's matrices and (behind them) biases in the scratch
+  int64_t elems = 0, bias_off = 0;          // all of them; where the biases start
+};
+
 struct Workspace {
+  char *cw;                   // compact masked pass: weights of the layer at work,
+  float *cg, *cb;             // its matrix gradients, and the partitioned bias gradients of all layers (elems - bias_off each)
+  int64_t cb_stride;
   std::vector<float *> xs;    // residual stream before / inside / after every layer, fp32 [T,D]
   std::vector<float *> stats; // (mean, rstd) per row for each norm
   std::vector<LayerBufs> layer;
@@ -43,9 +56,31 @@ struct Workspace {
   size_t bytes;
 };
 
-void carve(const twist_ctx *ctx, const twist_subnet *sub, int B, int N, void *base, Workspace &w) {
+// offsets of layer l's kept blocks in the scratch (tensors whose blocks are all kept are used where they are: -1)
+void compact_layout(const twist_model_desc &d, const twist_plan *plan, int l, Compact &c) {
+  static const int order[] = {TWIST_WQ, TWIST_WK, TWIST_WV, -1, TWIST_WO, -1, TWIST_W_GATE, TWIST_W_UP, -1, TWIST_W_DOWN, -2, TWIST_BQ, TWIST_BK, TWIST_BV, -1, TWIST_B_UP, -1};
+  std::fill(c.off, c.off + TWIST_N_LAYER_TENSORS, (int64_t)-1);
+  int64_t n = 0;
+  for (int t : order) {
+    if (t < 0) {
+      n = (int64_t)align_up((size_t)n, 64);
+      if (t == -2) c.bias_off = n;
+      continue;
+    }
+    const PlanEntry &pe = plan->at(l, twist_tensor_kind(d, t));
+    if (pe.n_sub == pe.n_full) continue;
+    int r, cc;
+    twist_tensor_shape(d, t, pe.n_sub, pe.n_sub, r, cc);
+    if (!r) continue;
+    c.off[t] = n;
+    n += (int64_t)r * cc;
+  }
+  c.elems = n;
+}
+
+// heads / ffn: width of every layer in heads and FFN blocks; cplan: the plan whose row is compacted, or null
+void carve(const twist_ctx *ctx, const std::vector<int32_t> &heads, const std::vector<int32_t> &ffn, const twist_plan *cplan, int B, int N, void *base, Workspace &w) {
   const twist_model_desc &d = ctx->d;
-  const SubLayout &L = sub->plan->layout;
   const size_t es = ctx->esize();
   const size_t T = (size_t)B * N, D = d.d_model;
   const int nf = d.act == TWIST_ACT_SWIGLU ? 2 : 1;
@@ -57,14 +92,14 @@ void carve(const twist_ctx *ctx, const twist_subnet *sub, int B, int N, void *ba
   w.layer.resize(d.n_layers);
   size_t hd_max = 0, f_max = 0, h_max = 0;
   for (int l = 0; l < d.n_layers; ++l) {
-    const size_t HD = (size_t)L.heads_sub[l] * d.d_head, F = (size_t)L.ffn_sub[l] * d.ffn_granule;
-    hd_max = std::max(hd_max, HD); f_max = std::max(f_max, F); h_max = std::max(h_max, (size_t)L.heads_sub[l]);
+    const size_t HD = (size_t)heads[l] * d.d_head, F = (size_t)ffn[l] * d.ffn_granule;
+    hd_max = std::max(hd_max, HD); f_max = std::max(f_max, F); h_max = std::max(h_max, (size_t)heads[l]);
     LayerBufs &b = w.layer[l];
     b.h1 = c.take(T * D * es);
     b.qkv = c.take(T * 3 * HD * es);
     b.o = c.take(T * HD * es);
     b.o32 = es == 2 ? c.take<float>(T * HD * 4) : nullptr;
-    b.lse = c.take<float>((size_t)B * L.heads_sub[l] * N * 4);
+    b.lse = c.take<float>((size_t)B * heads[l] * N * 4);
     b.h2 = c.take(T * D * es);
     b.gu = c.take(T * nf * F * es);
     b.a = c.take(T * F * es);
@@ -88,6 +123,19 @@ void carve(const twist_ctx *ctx, const twist_subnet *sub, int B, int N, void *ba
   w.dh = c.take(T * D * es);
   w.dout = c.take(T * hd_max * es);
   w.dqkv = c.take(T * 3 * hd_max * es);
+  if (cplan) {
+    int64_t most = 0, bias = 0;
+    for (int l = 0; l < d.n_layers; ++l) {
+      Compact k;
+      compact_layout(d, cplan, l, k);
+      most = std::max(most, k.elems);
+      bias = std::max(bias, k.elems - k.bias_off);
+    }
+    w.cw = c.take<char>((size_t)most * es);
+    w.cg = c.take<float>((size_t)most * 4);
+    w.cb_stride = (int64_t)align_up((size_t)bias, 64);
+    w.cb = c.take<float>((size_t)w.cb_stride * d.n_layers * 4);
+  }
   w.bytes = align_up(c.off, 256);
 }
 
@@ -148,7 +196,7 @@ twist_status check_train_shape(twist_ctx *ctx, const twist_subnet *sub, int B, i
 twist_status twist_train_workspace_bytes(twist_ctx *ctx, const twist_subnet *sub, int B, int N, size_t *bytes) {
   TW_TRY(check_train_shape(ctx, sub, B, N));
   Workspace w;
-  carve(ctx, sub, B, N, nullptr, w);
+  carve(ctx, sub->plan->layout.heads_sub, sub->plan->layout.ffn_sub, nullptr, B, N, nullptr, w);
   *bytes = w.bytes;
   return TWIST_OK;
 }
@@ -159,11 +207,11 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
   if (!forward_only && !sub->grads) TW_FAIL(ctx, TWIST_ESHAPE, "fwd_bwd: subnet was extracted without gradient storage");
   if (reinterpret_cast<uintptr_t>(ws) % 256) TW_FAIL(ctx, TWIST_ESHAPE, "fwd_bwd: workspace must be 256-byte aligned");
   Workspace w;
-  carve(ctx, sub, B, N, ws, w);
+  const SubLayout &L = sub->plan->layout;
+  carve(ctx, L.heads_sub, L.ffn_sub, nullptr, B, N, ws, w);
   if (ws_bytes < w.bytes) TW_FAIL(ctx, TWIST_ESHAPE, "fwd_bwd: workspace of %zu bytes is smaller than the %zu needed", ws_bytes, w.bytes);
 
   const twist_model_desc &d = ctx->d;
-  const SubLayout &L = sub->plan->layout;
   const int bf = d.dtype == TWIST_BF16, es = ctx->esize();
   const int T = B * N, D = d.d_model, dh = d.d_head;
   const int rms = d.norm == TWIST_NORM_RMS;
@@ -171,19 +219,50 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
   const bool lm = d.vocab > 0;
   const bool um = d.out_unit_major != 0;  // output projections stored [in, out]: the three GEMM forms rotate
   // Masked variant (Section 4.1, "Masked TwIST"): `sub` is a full-width subnet and the blocks that row `mask_row` of
-  // `mask_plan` does not name are zeroed where they enter the output projections (attention output columns,
-  // FFN activations) and where the gradient comes back through the same places, inside the kernels that produce
-  // those tensors (attention forward / backward, activation forward / backward); the module scales are those of
-  // the masked widths.  Everything else is the ordinary pass, with the same number of launches.
+  // `mask_plan` does not name are masked; the module scales are those of the masked widths.  Two ways, same results:
+  //  - compact (struct Compact above): nothing is computed for masked blocks;
+  //  - in place: they are computed at full width and zeroed where they enter the output projections (attention output
+  //    columns, FFN activations) and where the gradient comes back through the same places, inside the kernels that produce
+  //    those tensors.  The ordinary pass, with the same number of launches.
+  // Compacting moves about 12 r + 4 bytes per layer parameter (bf16, r = kept share: gathered twice, gradients spread once) at
+  // 4.5 TB/s and saves 6 T (1 - r) flop of it at about 0.9 PFLOP/s (fp32 models: 20 r + 4 bytes, 0.1 PFLOP/s), which is where the
+  // line lies.  Llama-1B widths, 6 layers, 4 x 2048 tokens, half the blocks: 13.9 ms against 20.4 in place.
   if (mask_plan) {
     for (int l = 0; l < d.n_layers; ++l)
       if (L.heads_sub[l] != d.n_heads || L.ffn_sub[l] != ctx->n_ffn_units())
         TW_FAIL(ctx, TWIST_ESHAPE, "masked pass: the subnet must hold every block of layer %d", l);
   }
+  std::vector<int32_t> heads = L.heads_sub, ffn = L.ffn_sub;  // width of every layer as it is run
+  std::vector<Compact> compact(d.n_layers);
+  if (mask_plan && !forward_only) {
+    double full_p = 0, kept_p = 0;
+    for (int l = 0; l < d.n_layers; ++l)
+      for (int t = TWIST_WQ; t <= TWIST_W_DOWN; ++t) {
+        const PlanEntry &pe = mask_plan->at(l, twist_tensor_kind(d, t));
+        int r, c;
+        twist_tensor_shape(d, t, d.n_heads, ctx->n_ffn_units(), r, c);
+        full_p += (double)r * c;
+        kept_p += (double)r * c * pe.n_sub / pe.n_full;
+      }
+    const double r = kept_p / full_p, gain = T * (1.0 - r), cost = bf ? 33.0 * (12.0 * r + 4.0) : 4.0 * (20.0 * r + 4.0);
+    if (gain > cost) {
+      std::vector<int32_t> h2(d.n_layers), f2(d.n_layers);
+      for (int l = 0; l < d.n_layers; ++l) { h2[l] = mask_plan->at(l, TWIST_KIND_HEAD).n_sub; f2[l] = mask_plan->at(l, TWIST_KIND_FFN).n_sub; }
+      Workspace w2;
+      carve(ctx, h2, f2, mask_plan, B, N, ws, w2);
+      if (w2.bytes <= ws_bytes) {
+        w = w2;
+        heads = h2;
+        ffn = f2;
+        for (int l = 0; l < d.n_layers; ++l) { compact_layout(d, mask_plan, l, compact[l]); compact[l].on = true; }
+      }
+    }
+  }
+  const bool in_place = mask_plan && !compact[0].on;
   // per-block mask of layer l (device table: entry < 0 = block not kept), handed to the kernels that produce the attention
   // output, the FFN activation and their gradients; null in the ordinary pass
   auto keep_of = [&](int l, int kind) -> const int32_t * {
-    if (!mask_plan) return nullptr;
+    if (!in_place) return nullptr;
     const PlanEntry &pe = mask_plan->at(l, kind);
     return pe.d_inv + (size_t)mask_row * pe.n_full;
   };
@@ -191,6 +270,33 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
   const int scale_mode = mask_plan ? mask_plan->scale_mode : sub->plan->scale_mode;
   auto P = [&](const Slot &s) -> void * { return s.off < 0 ? nullptr : sub->params + s.off * es; };
   auto G = [&](const Slot &s) -> float * { return s.off < 0 ? nullptr : sub->grads + s.off; };
+  // weight and gradient of layer l's tensor t as the pass uses them: in the subnet, or in the compact scratch
+  auto PW = [&](int l, int t) -> void * {
+    const Compact &c = compact[l];
+    return c.on && c.off[t] >= 0 ? w.cw + c.off[t] * es : P(L.at(l, t));
+  };
+  auto GW = [&](int l, int t) -> float * {
+    const Compact &c = compact[l];
+    if (!c.on || c.off[t] < 0) return G(L.at(l, t));
+    return c.off[t] >= c.bias_off ? w.cb + l * w.cb_stride + (c.off[t] - c.bias_off) : w.cg + c.off[t];
+  };
+  int gathered = -1;  // layer whose kept blocks the scratch holds
+  auto gather_layer = [&](int l) -> twist_status {
+    if (!compact[l].on || compact[l].elems == 0 || gathered == l) return TWIST_OK;
+    const void *full[TWIST_N_LAYER_TENSORS];
+    for (int t = 0; t < TWIST_N_LAYER_TENSORS; ++t) full[t] = P(L.at(l, t));
+    gathered = l;
+    return twist_gather_layer(ctx, mask_plan, l, mask_row, full, compact[l].off, w.cw);
+  };
+  // gradients of the tensors in `only` from the scratch to their full-width places
+  auto expand = [&](hipStream_t st, int l, uint32_t only, const float *src, int64_t shift) -> twist_status {
+    const Compact &c = compact[l];
+    if (!c.on) return TWIST_OK;
+    float *full[TWIST_N_LAYER_TENSORS];
+    int64_t off[TWIST_N_LAYER_TENSORS];
+    for (int t = 0; t < TWIST_N_LAYER_TENSORS; ++t) { full[t] = G(L.at(l, t)); off[t] = c.off[t] < 0 ? -1 : c.off[t] - shift; }
+    return twist_expand_layer(ctx, st, mask_plan, l, mask_row, full, off, src, only);
+  };
   auto gemm = [&](GemmLayout lay, int M, int Nn, int K, const void *A, int64_t lda, const void *Bm, int64_t ldb, void *out, int64_t ldc, int out_f32,
                   float alpha = 1.f, const void *bias = nullptr, const float *residual = nullptr) {
     GemmEpilogue e;
@@ -218,22 +324,23 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
   if (d.use_rope) TW_TRY(twist_rope_table(ctx, w.rope_tab, N, dh, d.rope_theta));
 
   for (int l = 0; l < d.n_layers; ++l) {
-    const int Hs = L.heads_sub[l], HD = Hs * dh, F = L.ffn_sub[l] * d.ffn_granule;
+    const int Hs = heads[l], HD = Hs * dh, F = ffn[l] * d.ffn_granule;
     const float c_a = scale_mode ? sqrtf((float)d.n_heads / (float)kept(l, TWIST_KIND_HEAD, Hs)) : 1.f;
-    const float c_f = scale_mode ? sqrtf((float)ctx->n_ffn_units() / (float)kept(l, TWIST_KIND_FFN, L.ffn_sub[l])) : 1.f;
+    const float c_f = scale_mode ? sqrtf((float)ctx->n_ffn_units() / (float)kept(l, TWIST_KIND_FFN, ffn[l])) : 1.f;
     const LayerBufs &b = w.layer[l];
+    TW_TRY(gather_layer(l));
     TW_TRY(twist_norm_fwd(ctx, bf, rms, w.xs[2 * l], P(L.at(l, TWIST_NORM1_W)), P(L.at(l, TWIST_NORM1_B)), b.h1, w.stats[2 * l], T, D, d.norm_eps));
-    TW_TRY(gemm(GEMM_NT, T, 3 * HD, D, b.h1, D, P(L.at(l, TWIST_WQ)), D, b.qkv, 3 * HD, 0, 1.f, P(L.at(l, TWIST_BQ))));
+    TW_TRY(gemm(GEMM_NT, T, 3 * HD, D, b.h1, D, PW(l, TWIST_WQ), D, b.qkv, 3 * HD, 0, 1.f, PW(l, TWIST_BQ)));
     if (d.use_rope) TW_TRY(twist_rope_apply(ctx, bf, b.qkv, w.rope_tab, B, N, Hs, dh, 1.f));
     TW_TRY(twist_attention_fwd(ctx, bf, b.qkv, b.o, b.o32, b.lse, B, N, Hs, dh, keep_of(l, TWIST_KIND_HEAD)));
-    if (um) TW_TRY(gemm(GEMM_NN, T, D, HD, b.o, HD, P(L.at(l, TWIST_WO)), D, w.xs[2 * l + 1], D, 1, c_a, P(L.at(l, TWIST_BO)), w.xs[2 * l]));
-    else TW_TRY(gemm(GEMM_NT, T, D, HD, b.o, HD, P(L.at(l, TWIST_WO)), HD, w.xs[2 * l + 1], D, 1, c_a, P(L.at(l, TWIST_BO)), w.xs[2 * l]));
+    if (um) TW_TRY(gemm(GEMM_NN, T, D, HD, b.o, HD, PW(l, TWIST_WO), D, w.xs[2 * l + 1], D, 1, c_a, P(L.at(l, TWIST_BO)), w.xs[2 * l]));
+    else TW_TRY(gemm(GEMM_NT, T, D, HD, b.o, HD, PW(l, TWIST_WO), HD, w.xs[2 * l + 1], D, 1, c_a, P(L.at(l, TWIST_BO)), w.xs[2 * l]));
     TW_TRY(twist_norm_fwd(ctx, bf, rms, w.xs[2 * l + 1], P(L.at(l, TWIST_NORM2_W)), P(L.at(l, TWIST_NORM2_B)), b.h2, w.stats[2 * l + 1], T, D, d.norm_eps));
-    const Slot &w1 = nf == 2 ? L.at(l, TWIST_W_GATE) : L.at(l, TWIST_W_UP);
-    TW_TRY(gemm(GEMM_NT, T, nf * F, D, b.h2, D, P(w1), D, b.gu, nf * F, 0, 1.f, P(L.at(l, TWIST_B_UP))));
+    const int w1 = nf == 2 ? TWIST_W_GATE : TWIST_W_UP;
+    TW_TRY(gemm(GEMM_NT, T, nf * F, D, b.h2, D, PW(l, w1), D, b.gu, nf * F, 0, 1.f, PW(l, TWIST_B_UP)));
     TW_TRY(twist_act_fwd(ctx, bf, d.act, b.gu, b.a, T, F, keep_of(l, TWIST_KIND_FFN), d.ffn_granule));
-    if (um) TW_TRY(gemm(GEMM_NN, T, D, F, b.a, F, P(L.at(l, TWIST_W_DOWN)), D, w.xs[2 * l + 2], D, 1, c_f, P(L.at(l, TWIST_B_DOWN)), w.xs[2 * l + 1]));
-    else TW_TRY(gemm(GEMM_NT, T, D, F, b.a, F, P(L.at(l, TWIST_W_DOWN)), F, w.xs[2 * l + 2], D, 1, c_f, P(L.at(l, TWIST_B_DOWN)), w.xs[2 * l + 1]));
+    if (um) TW_TRY(gemm(GEMM_NN, T, D, F, b.a, F, PW(l, TWIST_W_DOWN), D, w.xs[2 * l + 2], D, 1, c_f, P(L.at(l, TWIST_B_DOWN)), w.xs[2 * l + 1]));
+    else TW_TRY(gemm(GEMM_NT, T, D, F, b.a, F, PW(l, TWIST_W_DOWN), F, w.xs[2 * l + 2], D, 1, c_f, P(L.at(l, TWIST_B_DOWN)), w.xs[2 * l + 1]));
   }
 
   // ------------------------------------------------------------------------------------ loss and its gradient
@@ -275,11 +382,12 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
   };
   void *gx = w.dxb, *gx_other = w.dxb2;  // gradient of the residual stream in activation type: current, spare
   for (int l = d.n_layers - 1; l >= 0; --l) {
-    const int Hs = L.heads_sub[l], HD = Hs * dh, F = L.ffn_sub[l] * d.ffn_granule;
+    const int Hs = heads[l], HD = Hs * dh, F = ffn[l] * d.ffn_granule;
     const float c_a = scale_mode ? sqrtf((float)d.n_heads / (float)kept(l, TWIST_KIND_HEAD, Hs)) : 1.f;
-    const float c_f = scale_mode ? sqrtf((float)ctx->n_ffn_units() / (float)kept(l, TWIST_KIND_FFN, L.ffn_sub[l])) : 1.f;
+    const float c_f = scale_mode ? sqrtf((float)ctx->n_ffn_units() / (float)kept(l, TWIST_KIND_FFN, ffn[l])) : 1.f;
     const LayerBufs &b = w.layer[l];
-    const Slot &w1 = nf == 2 ? L.at(l, TWIST_W_GATE) : L.at(l, TWIST_W_UP);
+    TW_TRY(gather_layer(l));
+    const int w1 = nf == 2 ? TWIST_W_GATE : TWIST_W_UP;
     // FFN branch: y = c_f (a W_down^T + b_down)
     // bias gradients: per-chunk column sums now (into this layer's block), reduced with everything else at the end
     float *bias_part = w.bias_partial + (size_t)l * w.bias_partial_stride;
@@ -291,40 +399,47 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     };
     if (L.at(l, TWIST_B_DOWN).off >= 0) TW_TRY(bias_grad(gx, D, c_f, G(L.at(l, TWIST_B_DOWN)), D));
     TW_TRY(side.fork(0));
-    if (um) TW_TRY(wgrad(F, D, b.a, F, gx, D, G(L.at(l, TWIST_W_DOWN)), c_f));
-    else TW_TRY(wgrad(D, F, gx, D, b.a, F, G(L.at(l, TWIST_W_DOWN)), c_f));
+    if (um) TW_TRY(wgrad(F, D, b.a, F, gx, D, GW(l, TWIST_W_DOWN), c_f));
+    else TW_TRY(wgrad(D, F, gx, D, b.a, F, GW(l, TWIST_W_DOWN), c_f));
+    TW_TRY(expand(side.stream(), l, 1u << TWIST_W_DOWN, w.cg, 0));
     TW_TRY(side.done(0));
-    if (um) TW_TRY(gemm(GEMM_NT, T, F, D, gx, D, P(L.at(l, TWIST_W_DOWN)), D, w.da, F, 0, c_f));
-    else TW_TRY(gemm(GEMM_NN, T, F, D, gx, D, P(L.at(l, TWIST_W_DOWN)), F, w.da, F, 0, c_f));
+    if (um) TW_TRY(gemm(GEMM_NT, T, F, D, gx, D, PW(l, TWIST_W_DOWN), D, w.da, F, 0, c_f));
+    else TW_TRY(gemm(GEMM_NN, T, F, D, gx, D, PW(l, TWIST_W_DOWN), F, w.da, F, 0, c_f));
     TW_TRY(side.wait_done(1));
     TW_TRY(twist_act_bwd(ctx, bf, d.act, b.gu, w.da, w.dgu, T, F, keep_of(l, TWIST_KIND_FFN), d.ffn_granule));
-    if (L.at(l, TWIST_B_UP).off >= 0) TW_TRY(bias_grad(w.dgu, nf * F, 1.f, G(L.at(l, TWIST_B_UP)), nf * F));
+    if (L.at(l, TWIST_B_UP).off >= 0) TW_TRY(bias_grad(w.dgu, nf * F, 1.f, GW(l, TWIST_B_UP), nf * F));
     TW_TRY(side.fork(1));
-    TW_TRY(wgrad(nf * F, D, w.dgu, nf * F, b.h2, D, G(w1), 1.f));
+    TW_TRY(wgrad(nf * F, D, w.dgu, nf * F, b.h2, D, GW(l, w1), 1.f));
+    TW_TRY(expand(side.stream(), l, 1u << TWIST_W_GATE | 1u << TWIST_W_UP, w.cg, 0));
     TW_TRY(side.done(1));
-    TW_TRY(gemm(GEMM_NN, T, D, nf * F, w.dgu, nf * F, P(w1), D, w.dh, D, 0));
+    TW_TRY(gemm(GEMM_NN, T, D, nf * F, w.dgu, nf * F, PW(l, w1), D, w.dh, D, 0));
     TW_TRY(side.wait_done(2));
     TW_TRY(norm_bwd(2 * l + 1, w.dh, w.xs[2 * l + 1], P(L.at(l, TWIST_NORM2_W)), 1, gx_other, G(L.at(l, TWIST_NORM2_W)), G(L.at(l, TWIST_NORM2_B))));
     // attention branch: y = c_a (o C_attn^T + b_o)
     if (L.at(l, TWIST_BO).off >= 0) TW_TRY(bias_grad(gx_other, D, c_a, G(L.at(l, TWIST_BO)), D));
     TW_TRY(side.fork(2));
-    if (um) TW_TRY(wgrad(HD, D, b.o, HD, gx_other, D, G(L.at(l, TWIST_WO)), c_a));
-    else TW_TRY(wgrad(D, HD, gx_other, D, b.o, HD, G(L.at(l, TWIST_WO)), c_a));
+    if (um) TW_TRY(wgrad(HD, D, b.o, HD, gx_other, D, GW(l, TWIST_WO), c_a));
+    else TW_TRY(wgrad(D, HD, gx_other, D, b.o, HD, GW(l, TWIST_WO), c_a));
+    TW_TRY(expand(side.stream(), l, 1u << TWIST_WO, w.cg, 0));
     TW_TRY(side.done(2));
-    if (um) TW_TRY(gemm(GEMM_NT, T, HD, D, gx_other, D, P(L.at(l, TWIST_WO)), D, w.dout, HD, 0, c_a));
-    else TW_TRY(gemm(GEMM_NN, T, HD, D, gx_other, D, P(L.at(l, TWIST_WO)), HD, w.dout, HD, 0, c_a));
+    if (um) TW_TRY(gemm(GEMM_NT, T, HD, D, gx_other, D, PW(l, TWIST_WO), D, w.dout, HD, 0, c_a));
+    else TW_TRY(gemm(GEMM_NN, T, HD, D, gx_other, D, PW(l, TWIST_WO), HD, w.dout, HD, 0, c_a));
     TW_TRY(side.wait_done(3));
     TW_TRY(twist_attention_bwd(ctx, bf, b.qkv, bf ? b.o32 : static_cast<const float *>(b.o), w.dout, b.lse, w.delta, w.dqkv, B, N, Hs, dh, d.use_rope ? w.rope_tab : nullptr,
                                keep_of(l, TWIST_KIND_HEAD)));
-    if (L.at(l, TWIST_BQ).off >= 0) TW_TRY(bias_grad(w.dqkv, 3 * HD, 1.f, G(L.at(l, TWIST_BQ)), 3 * HD));
+    if (L.at(l, TWIST_BQ).off >= 0) TW_TRY(bias_grad(w.dqkv, 3 * HD, 1.f, GW(l, TWIST_BQ), 3 * HD));
     TW_TRY(side.fork(3));
-    TW_TRY(wgrad(3 * HD, D, w.dqkv, 3 * HD, b.h1, D, G(L.at(l, TWIST_WQ)), 1.f));
+    TW_TRY(wgrad(3 * HD, D, w.dqkv, 3 * HD, b.h1, D, GW(l, TWIST_WQ), 1.f));
+    TW_TRY(expand(side.stream(), l, 1u << TWIST_WQ | 1u << TWIST_WK | 1u << TWIST_WV, w.cg, 0));
     TW_TRY(side.done(3));
-    TW_TRY(gemm(GEMM_NN, T, D, 3 * HD, w.dqkv, 3 * HD, P(L.at(l, TWIST_WQ)), D, w.dh, D, 0));
+    TW_TRY(gemm(GEMM_NN, T, D, 3 * HD, w.dqkv, 3 * HD, PW(l, TWIST_WQ), D, w.dh, D, 0));
     TW_TRY(side.wait_done(0));
     TW_TRY(norm_bwd(2 * l, w.dh, w.xs[2 * l], P(L.at(l, TWIST_NORM1_W)), 1, gx, G(L.at(l, TWIST_NORM1_W)), G(L.at(l, TWIST_NORM1_B))));
   }
   TW_TRY(twist_col_reduce_batch(ctx, reduce_items.data(), (int)reduce_items.size(), T));
+  if (d.has_bias)
+    for (int l = 0; l < d.n_layers; ++l)
+      TW_TRY(expand(nullptr, l, 1u << TWIST_BQ | 1u << TWIST_BK | 1u << TWIST_BV | 1u << TWIST_B_UP, w.cb + l * w.cb_stride, compact[l].bias_off));
   for (int i = 0; i < 4; ++i) TW_TRY(side.wait_done(i));  // join: the caller's stream sees the whole pass
   (void)gx_other;
 

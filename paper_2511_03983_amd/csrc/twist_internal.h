@@ -142,6 +142,18 @@ twist_status twist_launch_extract_all(twist_ctx *ctx, const MoveLaunch &ml, int 
 // into the fp32 image, or (finish) write image / owner count over all rows sub_row[0..n_subs) to the central tensors.
 constexpr int kAccumPerBlock = 256 * 4;  // vectors (or elements) of the central tensor one workgroup covers
 twist_status twist_launch_accumulate(twist_ctx *ctx, const MoveLaunch &ml, int total_blocks, bool finish);
+// The kept blocks of one layer as a dense layer, for the masked pass: gather copies them (row s of `plan`) from the layer's
+// full-width tensors full[t] into dst + dst_off[t] elements, for every tensor with dst_off[t] >= 0; expand is its inverse for fp32
+// gradients: the full-width tensors full[t] receive the values of src + src_off[t] in the kept blocks and zeros elsewhere
+// (`only`: bit t set for the tensors to write).
+twist_status twist_gather_layer(twist_ctx *ctx, const twist_plan *plan, int l, int s, const void *const *full, const int64_t *dst_off, char *dst);
+twist_status twist_expand_layer(twist_ctx *ctx, hipStream_t st, const twist_plan *plan, int l, int s, float *const *full, const int64_t *src_off, const float *src,
+                                uint32_t only);
+twist_status twist_launch_expand(twist_ctx *ctx, hipStream_t st, const MoveLaunch &ml, int total_blocks);
+// kind (TWIST_KIND_*) of the blocks that layer tensor t is cut into, or -1 if all subnets share it
+int twist_tensor_kind(const twist_model_desc &d, int t);
+// shape of layer tensor t with `heads` heads and `units` FFN blocks; rows = 0 if the model has no such tensor
+void twist_tensor_shape(const twist_model_desc &d, int t, int heads, int units, int &rows, int &cols);
 // fp32 master <- weights, zero-fill helpers
 twist_status twist_launch_to_f32(twist_ctx *ctx, const void *src, float *dst, int64_t n);
 twist_status twist_launch_zero(twist_ctx *ctx, void *dst, size_t bytes);

@@ -704,6 +704,62 @@ def test_masked_full_model_equals_the_extracted_subnet(lib, name):
         ctx.twist_subnet_fwd_bwd_masked(ctx.twist_extract(plan, fw, 0, store=lib.STORE_GRADS), plan, 0, x, y, ws, loss)
 
 
+# batches large enough that the masked pass runs on the kept blocks only: both storage orientations, biases, FFN blocks of one and of
+# eight neurons, a layer kept whole, one kind of block kept whole
+@pytest.mark.parametrize("name,cfg,hs,fs,shared,B,N", [
+    ("gpt_f32", si.ModelCfg(n_layers=3, d_model=72, n_heads=4, d_head=16, d_ff=160, ffn_granule=8, vocab=301, max_seq=100), 2, 7, [1, 0, 0], 3, 100),
+    ("llama_f32_um", si.ModelCfg(arch="llama", n_layers=2, d_model=64, n_heads=4, d_head=16, d_ff=176, vocab=259, max_seq=128, act="swiglu", norm="rms",
+                                 has_bias=False, tied_head=False, rope=True, out_unit_major=True), 2, 88, None, 3, 128),
+    ("gpt_bf16", replace(si.CFG2, n_layers=2, d_model=256, n_heads=4, d_ff=512, vocab=1003, max_seq=256), 1, 256, None, 8, 200),
+    ("llama_bf16_um", replace(si.CFG3, n_layers=2, d_model=256, n_heads=4, d_ff=704, vocab=517, max_seq=256, out_unit_major=True), 2, 352, None, 8, 256),
+    ("llama_bf16_heads_whole", replace(si.CFG3, n_layers=2, d_model=256, n_heads=4, d_ff=704, vocab=517, max_seq=256), 4, 176, None, 8, 256)])
+def test_masked_pass_on_the_kept_blocks_is_the_extracted_subnets_pass(lib, name, cfg, hs, fs, shared, B, N):
+    S = 4
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    dt = torch.bfloat16 if cfg.dtype == "bf16" else torch.float32
+    draw = lambda shp: (torch.randn(shp, generator=gen, device="cuda") * 0.05 + (1.0 if len(shp) == 1 else 0.0)).to(dt)
+    fw = lib.FullWeights([{k: draw(s) for k, s in si.stored_shapes(cfg).items()} for _ in range(cfg.n_layers)],
+                         {k: draw(s) for k, s in si.global_shapes(cfg).items()})
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    plan = ctx.twist_sample(S, hs, fs, seed=4, layer_shared=shared)
+    whole = ctx.twist_sample(1, cfg.n_heads, cfg.n_ffn_units, seed=0)
+    full_sub = ctx.twist_extract(whole, fw, 0, store=lib.STORE_GRADS)
+    full_sub.storage.view(torch.uint8)[-(full_sub.storage.numel() // 8):].fill_(0x7f)      # gradients must be overwritten, zeros included
+    sub = ctx.twist_extract(plan, fw, 1, store=lib.STORE_GRADS)
+    tok = torch.tensor(si.tokens_uniform(cfg.vocab, B, N, 9)).cuda()
+    x, y = tok[:, :-1].contiguous(), tok[:, 1:].contiguous()
+    loss, want = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    ws = torch.empty(ctx.twist_workspace_bytes(full_sub, B, N), dtype=torch.uint8, device="cuda")
+    ctx.twist_subnet_fwd_bwd(sub, x, y, ws, want)
+    for overlap in (True, False):
+        ctx.twist_set_overlap(overlap)
+        ctx.twist_subnet_fwd_bwd_masked(full_sub, plan, 1, x, y, ws, loss)
+        torch.cuda.synchronize()
+        assert loss.item() == want.item()
+        for l in range(cfg.n_layers):
+            for k in si.layer_shapes(cfg):
+                g, e = full_sub.twist_subnet_view(l, k, GRAD), sub.twist_subnet_view(l, k, GRAD)
+                ka = omove.PARTITIONED.get(k)
+                if ka is not None:
+                    kind, axis = ka
+                    if cfg.out_unit_major and k in si.STORED_TRANSPOSED:
+                        axis = 1 - axis
+                    q = cfg.d_head if kind == 0 else cfg.ffn_granule
+                    idx = plan.twist_plan_view(l, kind)[0][1].long()
+                    rows = (idx[:, None] * q + torch.arange(q)).reshape(-1).cuda()
+                    rest = torch.ones(g.shape[axis], dtype=torch.bool, device="cuda")
+                    rest[rows] = False
+                    assert not g.index_select(axis, rest.nonzero()[:, 0]).any(), (l, k)
+                    g = g.index_select(axis, rows)
+                assert torch.equal(g, e), (name, overlap, l, k)
+        for k in si.global_shapes(cfg):
+            g, e = full_sub.twist_subnet_view(-1, k, GRAD), sub.twist_subnet_view(-1, k, GRAD)
+            if k == "tok_embed":      # floating-point atomics: the order, hence the last bits, vary
+                assert float((g - e).norm() / e.norm()) <= 1e-6
+            else:
+                assert torch.equal(g, e), k
+
+
 def test_train_x_eval_y_grid_matches_checker(lib):
     """Section 5.1 ("Architectural Robustness"): a model trained for one round with subnets of X of 12 blocks (heads and
     FFN blocks alike, first and last layer shared) is evaluated, without retraining, through deployment subnets of Y of
