@@ -113,6 +113,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
 }
 
+// Elements from a panel's base to the end of its last 16-byte chunk.  A load that reaches beyond the buffer's range returns nothing at
+// all, so the range has to include the whole of a last row's partly used chunk (the chunk is aligned and holds at least one
+// element of the operand, so reading it is safe; what it holds beyond the operand meets zeros or is not stored).
+__device__ __forceinline__ int64_t panel_span(int km, int64_t ld, int rows, int rows_left, int K) {
+  const int64_t len = km ? K : rows_left, up = (len + 7) / 8 * 8;
+  return (km ? (int64_t)(rows - 1) : (int64_t)(K - 1)) * ld + (up < ld ? up : ld);
+}
+
 // Global accesses go through buffer instructions whose hardware range check returns zeros (loads) or drops the
 // access (stores) beyond the end, so tile edges need no branches: an out-of-range row or k chunk just gets an
 // offset outside the buffer.
@@ -129,7 +137,7 @@ struct TileLoader {
   uint32_t kstep;        // bytes to advance per k-tile
   // base = first row of this workgroup's panel (KMAJOR) or first column (otherwise)
   __device__ __forceinline__ void init(const uint16_t *base, int64_t ld, int rows_left, int K) {
-    const int64_t span = KMAJOR ? ((int64_t)(min(rows_left, ROWS) - 1) * ld + K) : ((int64_t)(K - 1) * ld + min(rows_left, (int)ld));
+    const int64_t span = panel_span(KMAJOR, ld, min(rows_left, ROWS), rows_left, K);
     rsrc = make_rsrc(base, (uint32_t)(span * 2));
     kstep = KMAJOR ? BK * 2 : (uint32_t)(BK * ld * 2);
 #pragma unroll
@@ -340,7 +348,7 @@ struct Loader {
   int kk[2];        // k of that chunk inside a sub-tile
   uint32_t kstep;   // bytes from one sub-tile to the next
   __device__ __forceinline__ void init(const uint16_t *base, int64_t ld, int rows_left, int K, int wave, int lane) {
-    const int64_t span = KM ? ((int64_t)(min(rows_left, 256) - 1) * ld + K) : ((int64_t)(K - 1) * ld + min(rows_left, (int)ld));
+    const int64_t span = panel_span(KM, ld, min(rows_left, 256), rows_left, K);
     rsrc = make_rsrc(base, (uint32_t)(span * 2));
     kstep = KM ? SK * 2 : (uint32_t)(SK * ld * 2);
 #pragma unroll

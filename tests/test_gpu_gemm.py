@@ -38,6 +38,27 @@ def test_bf16_projection_matches_fp64_product(lib, layout, tile):
             assert not guard.any()
 
 
+# rows padded to 16 bytes whose last chunk is partly used: the last k row (layout 2) or the last row (layout 1) of the operand ends in it
+@pytest.mark.parametrize("tile", [128, 256])
+@pytest.mark.parametrize("layout,M,N,K", [(2, 129, 64, 40), (2, 33, 257, 64), (1, 40, 64, 1003), (1, 257, 136, 129)])
+def test_bf16_projection_uses_a_partly_filled_last_chunk(lib, tile, layout, M, N, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
+    ctx.twist_set_kernel_choice(gemm_tile=tile)
+    up = lambda n: (n + 7) // 8 * 8
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a_rows, a_cols = (K, M) if layout == 2 else (M, K)
+    A, B = torch.zeros((a_rows, up(a_cols)), device="cuda").bfloat16()[:, :a_cols], torch.zeros((K, up(N)), device="cuda").bfloat16()[:, :N]
+    A.copy_(torch.randn(A.shape, generator=gen, device="cuda"))
+    B.copy_(torch.randn(B.shape, generator=gen, device="cuda"))
+    want = (A.double().T if layout == 2 else A.double()) @ B.double()
+    out = torch.full((M, N), float("nan"), device="cuda")
+    ctx.twist_gemm_raw(layout, M, N, K, A, B, out)
+    torch.cuda.synchronize()
+    # fp32 sums of exact products: an element that misses one of K products is off by 1 / sqrt(K)
+    rows = (out.double() - want).norm(dim=1) / want.norm(dim=1)
+    assert float(rows.max()) <= 1e-5 and float((out.double() - want).norm() / want.norm()) <= 1e-5
+
+
 def test_fp32_projection(lib):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
     for layout in (0, 1, 2):
