@@ -343,8 +343,8 @@ TWIST_API twist_status twist_profile_mfma_ceiling(twist_ctx *ctx, int32_t waves_
 TWIST_API twist_status twist_set_overlap(twist_ctx *ctx, int32_t enable);
 
 /* Kernel selection for tests (not part of the method): by default every launcher picks its kernel from the shape.
- *   gemm_tile        0 = by shape; 128 or 256 pins the tile of the matrix-core projection kernel and keeps the
- *                    contraction in one piece (TWIST_EINVAL for other values);
+ *   gemm_tile        0 = by shape; 256 or 128 pins the matrix-core projection kernel with tiles of 256x256 or 256x128
+ *                    (fp32 models: 64x64 or 128x128) and keeps the contraction in one piece (TWIST_EINVAL for other values);
  *   plain_only       non-zero: projections and attention never use the matrix-core kernels (the plain fp32-arithmetic
  *                    kernels that serve fp32 models and unaligned shapes run instead);
  *   staged_attention non-zero: d_head = 128 attention runs the register-staged tiled kernels instead of the ones fed by

@@ -1,48 +1,15 @@
 // Dense projections of the subnet: C = epilogue(op(A) op(B)) with fp32 accumulation.
-//  - bf16 operands: MFMA kernels (v_mfma_f32_32x32x16_bf16): a 256x256 ping-pong kernel fed by direct-to-LDS
-//    loads for all but the smallest products, and a 128x128 register-staged kernel; operands stay in LDS in their
-//    memory orientation, and those whose contraction index is the slow axis in memory are read back with the
-//    transposing LDS load.
+//  - bf16 operands: MFMA kernels (v_mfma_f32_32x32x16_bf16) fed by direct-to-LDS loads: ping-pong kernels with tiles of
+//    256x256 and 256x128 (here), and 64x64 and 32x32 tiles for products too small to fill the chip with those (gemm_dl.hip);
+//    operands stay in LDS in their memory orientation, and those whose contraction index is the slow axis in memory are
+//    read back with the transposing LDS load.
 //  - fp32 operands: the fp32 matrix instruction (gemm_f32.hip).
 //  - anything else (unaligned bf16 shapes): a plain tiled FMA kernel with arbitrary strides.
 #include <algorithm>
 
-#include "nn.h"
+#include "gemm_tile.h"
 
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-// two floats to a packed pair of bf16, round to nearest even, in one instruction (v_cvt_pk_bf16_f32): the same bits as f2bf for
-// every finite value and infinity (the software form costs about eight instructions and a branch per value, which showed in
-// the epilogue: 40.6 -> 39.9 ms per forward+backward pass)
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-  typedef float f32x2_t __attribute__((ext_vector_type(2)));
-  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-  const f32x2_t v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
-struct Ep {
-  float alpha;
-  const void *bias;
-  const float *residual;
-  void *out;
-  int out_f32;
-  int64_t ldc;
-  int vec_ok;  // out (and residual) rows allow 4-element vector accesses: ldc % 4 == 0, 16-byte aligned bases
-};
 
 template <int BF>
 __device__ __forceinline__ void store_out(const Ep &ep, int m, int n, float acc) {
@@ -93,231 +60,8 @@ __global__ __launch_bounds__(256) void gemm_plain_kernel(int M, int N, int K, co
     }
 }
 
-// ------------------------------------------------------------------------------------------- MFMA kernel
-// Workgroup tile BM x BN x 32, WM x WN waves, each wave (BM/WM) x (BN/WN) in 32x32 MFMA tiles.
-// An operand tile lives in LDS in the orientation of its memory:
-//   k contiguous in memory ("KMAJOR"):  LDS [rows][32 + 8]; a lane's 8 k values are one 16-byte LDS read;
-//   rows contiguous in memory:          LDS [32][rows + 16]; a lane's 8 k values are two transposing reads
-//                                       (ds_read_tr16_b64: 4 consecutive k rows of one column each).
-// Both paddings make the reads bank-conflict free.  Tiles are double-buffered: the next tile's global loads
-// are issued before the MFMAs of the current one and written to the other buffer after them, one barrier per
-// k-iteration.  Workgroups are renumbered so that each of the 8 XCDs (own L2) works on a contiguous range
-// of tiles.
-constexpr int BK = 64;
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-
-constexpr uint32_t kOob = 0x80000000u;  // byte offset beyond every buffer: loads return 0, stores are dropped
-
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
-}
-
-// Elements from a panel's base to the end of its last 16-byte chunk.  A load that reaches beyond the buffer's range returns nothing at
-// all, so the range has to include the whole of a last row's partly used chunk (the chunk is aligned and holds at least one
-// element of the operand, so reading it is safe; what it holds beyond the operand meets zeros or is not stored).
-__device__ __forceinline__ int64_t panel_span(int km, int64_t ld, int rows, int rows_left, int K) {
-  const int64_t len = km ? K : rows_left, up = (len + 7) / 8 * 8;
-  return (km ? (int64_t)(rows - 1) : (int64_t)(K - 1)) * ld + (up < ld ? up : ld);
-}
-
-// Global accesses go through buffer instructions whose hardware range check returns zeros (loads) or drops the
-// access (stores) beyond the end, so tile edges need no branches: an out-of-range row or k chunk just gets an
-// offset outside the buffer.
-template <int ROWS, int KMAJOR, int NT>
-struct TileLoader {
-  static constexpr int LD = KMAJOR ? BK + 8 : ROWS + 16;
-  static constexpr int ELEMS = KMAJOR ? ROWS * LD : BK * LD;
-  static constexpr int CHUNKS = ROWS * BK / 8 / NT;       // 16-byte chunks per thread
-  static constexpr int CPR = KMAJOR ? BK / 8 : ROWS / 8;  // chunks per stored row
-  u32x4 reg[CHUNKS];
-  __amdgpu_buffer_rsrc_t rsrc;
-  uint32_t off[CHUNKS];  // byte offset of each chunk at k0 = 0 (kOob if its row is outside the operand)
-  int kk[CHUNKS];        // k of the chunk inside a tile
-  uint32_t kstep;        // bytes to advance per k-tile
-  // base = first row of this workgroup's panel (KMAJOR) or first column (otherwise)
-  __device__ __forceinline__ void init(const uint16_t *base, int64_t ld, int rows_left, int K) {
-    const int64_t span = panel_span(KMAJOR, ld, min(rows_left, ROWS), rows_left, K);
-    rsrc = make_rsrc(base, (uint32_t)(span * 2));
-    kstep = KMAJOR ? BK * 2 : (uint32_t)(BK * ld * 2);
-#pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-      const int c = threadIdx.x + NT * i;
-      if (KMAJOR) {
-        const int r = c / CPR, kc = (c % CPR) * 8;
-        kk[i] = kc;
-        off[i] = r < rows_left ? (uint32_t)((r * ld + kc) * 2) : kOob;
-      } else {
-        const int k = c / CPR, rc = (c % CPR) * 8;
-        kk[i] = k;
-        off[i] = rc < rows_left ? (uint32_t)((k * ld + rc) * 2) : kOob;
-      }
-    }
-  }
-  __device__ __forceinline__ void load(int kt, int K) {
-#pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-      const uint32_t o = (kt * BK + kk[i] < K) ? off[i] + kt * kstep : kOob;
-      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0);
-    }
-  }
-  __device__ __forceinline__ void store(uint16_t *lds) const {
-#pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-      const int c = threadIdx.x + NT * i;
-      const int r = c / CPR, kc = (c % CPR) * 8;  // (row, k chunk) or (k row, row chunk): same arithmetic
-      *reinterpret_cast<u32x4 *>(lds + r * LD + kc) = reg[i];
-    }
-  }
-  // fragment for the 32 rows starting at row0 of the tile, k-step ks (16 wide)
-  static __device__ __forceinline__ bf16x8 frag(const uint16_t *lds, int row0, int ks) {
-    const int lane = threadIdx.x & 63;
-    if (KMAJOR) return *reinterpret_cast<const bf16x8 *>(lds + (row0 + (lane & 31)) * LD + ks * 16 + (lane >> 5) * 8);
-    const int s = lane & 15;
-    const uint16_t *p = lds + (ks * 16 + (lane >> 5) * 8 + (s >> 2)) * LD + row0 + 16 * ((lane >> 4) & 1) + 4 * (s & 3);
-    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-    s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
-    s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * LD));
-    s16x8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    return __builtin_bit_cast(bf16x8, v);
-  }
-};
-
-// A operand: rows = M index; B operand: rows = N index.  AKM / BKM say whether k is contiguous in memory.
-template <int AKM, int BKM, int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(WM *WN * 64) void gemm_mfma_kernel(int M, int N, int K, const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb,
-                                                                Ep ep, int tiles_m, int tiles_n) {
-  constexpr int NT = WM * WN * 64, TM = BM / WM / 32, TN = BN / WN / 32, KS = BK / 16;
-  using LA = TileLoader<BM, AKM, NT>;
-  using LB = TileLoader<BN, BKM, NT>;
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][LA::ELEMS];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][LB::ELEMS];
-  // XCD-aware renumbering: hardware deals workgroup ids round-robin over 8 XCDs
-  const int nb = tiles_m * tiles_n;
-  int bid = blockIdx.x;
-  if (nb % 8 == 0) bid = (bid % 8) * (nb / 8) + bid / 8;
-  // walk the tiles in column-panels of 8 tile rows so that concurrently running workgroups share operands
-  constexpr int GROUP = 8;
-  const int per_group = GROUP * tiles_n;
-  const int grp = bid / per_group, first_m = grp * GROUP;
-  const int gsize = min(GROUP, tiles_m - first_m);
-  const int tile_m = first_m + (bid % per_group) % gsize, tile_n = (bid % per_group) / gsize;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  LA la;
-  LB lb;
-  la.init(AKM ? A + (int64_t)m0 * lda : A + m0, lda, M - m0, K);
-  lb.init(BKM ? B + (int64_t)n0 * ldb : B + n0, ldb, N - n0, K);
-  // Pipeline: tile kt+2 travels from global memory to registers and tile kt+1 from registers to LDS while
-  // tile kt is multiplied; one barrier per k-iteration.
-  la.load(0, K);
-  lb.load(0, K);
-  la.store(As[0]);
-  lb.store(Bs[0]);
-  const int nk = (K + BK - 1) / BK;
-  if (nk > 1) {
-    la.load(1, K);
-    lb.load(1, K);
-  }
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) {
-      la.store(As[cur ^ 1]);
-      lb.store(Bs[cur ^ 1]);
-    }
-    if (kt + 2 < nk) {
-      la.load(kt + 2, K);
-      lb.load(kt + 2, K);
-    }
-    // fragments of k-step ks+1 are fetched while the MFMAs of k-step ks run
-    bf16x8 af[2][TM], bfr[2][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[0][i] = LA::frag(As[cur], wm + i * 32, 0);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bfr[0][j] = LB::frag(Bs[cur], wn + j * 32, 0);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (ks + 1 < KS) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) af[(ks + 1) & 1][i] = LA::frag(As[cur], wm + i * 32, ks + 1);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bfr[(ks + 1) & 1][j] = LB::frag(Bs[cur], wn + j * 32, ks + 1);
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks & 1][i], bfr[ks & 1][j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-
-  // Epilogue.  A 32x32 accumulator tile holds column lane % 32 and rows 8*(r/4) + 4*(lane/32) + r%4, which would store
-  // 2-byte pieces; each wave instead turns its results through LDS (the operand stages are free now), 32 rows at a time,
-  // so that a lane owns 4 consecutive columns and a store instruction writes four rows of 64 columns.
-  static_assert(TN == 2 && sizeof(As) >= WM * WN * 32 * 72 * 4, "staging of 32 x 64 results per wave fits the A stages");
-  constexpr int LDE = 72;  // floats per staged row: rows 4 apart (the two half-waves of a write) are 32 banks apart
-  float *stage = reinterpret_cast<float *>(&As[0][0]) + wave * (32 * LDE);
-  const int c = lane & 31, g = lane >> 5, c16 = lane & 15, rs = lane >> 4;
-  const int rows_left = M - m0;
-  const int ncol = n0 + wn + 4 * c16;  // first of this lane's 4 columns
-  float bias[4] = {0.f, 0.f, 0.f, 0.f};
-  if (ep.bias) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (ncol + e < N) bias[e] = bf2f(static_cast<const uint16_t *>(ep.bias)[ncol + e]);
-  }
-  const bool vec = ep.vec_ok && ncol + 3 < N;
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) stage[(8 * (r >> 2) + 4 * g + (r & 3)) * LDE + 32 * j + c] = acc[i][j][r];
-#pragma unroll 4
-    for (int p = 0; p < 8; ++p) {
-      const int row = 4 * p + rs, ml = wm + 32 * i + row;
-      const f32x4 v4 = *reinterpret_cast<const f32x4 *>(stage + row * LDE + 4 * c16);
-      if (ml >= rows_left || ncol >= N) continue;
-      const int64_t o = (int64_t)(m0 + ml) * ep.ldc + ncol;
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (v4[e] + bias[e]) * ep.alpha;
-      if (vec) {
-        if (ep.residual) {
-          const f32x4 rr = *reinterpret_cast<const f32x4 *>(ep.residual + o);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] += rr[e];
-        }
-        if (ep.out_f32) {
-          const f32x4 w = {v[0], v[1], v[2], v[3]};
-          *reinterpret_cast<f32x4 *>(static_cast<float *>(ep.out) + o) = w;
-        } else {
-          const u32x2 w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-          *reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(ep.out) + o) = w;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (ncol + e >= N) break;
-          float x = v[e];
-          if (ep.residual) x += ep.residual[o + e];
-          if (ep.out_f32) static_cast<float *>(ep.out)[o + e] = x;
-          else static_cast<uint16_t *>(ep.out)[o + e] = f2bf(x);
-        }
-      }
-    }
-  }
 }
 
 // ------------------------------------------------------------------------------- ping-pong MFMA kernel
@@ -333,33 +77,33 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_mfma_kernel(int M, int N, in
 namespace pp {
 
 constexpr int SK = 32;             // k extent of a sub-tile
-constexpr int OPB = 256 * SK * 2;  // bytes of one operand's sub-tile
-constexpr int STG = 2 * OPB;       // one stage: A sub-tile, then B sub-tile
 constexpr int NST = 4;
 typedef __attribute__((address_space(3))) void *lds_void;
 
-#define PP_WAIT_VM8_LGKM0 __builtin_amdgcn_s_waitcnt(0x0078)  // vmcnt(8) lgkmcnt(0)
+#define PP_WAIT_VM_LGKM0(vm) __builtin_amdgcn_s_waitcnt(0x0070 | (vm))  // vmcnt(vm < 16) lgkmcnt(0)
 #define PP_WAIT_VM0 __builtin_amdgcn_s_waitcnt(0x0f70)        // vmcnt(0)
 
-template <int KM>
+template <int KM, int ROWS>
 struct Loader {
+  static constexpr int NP = ROWS / 128;  // one-KB pieces per wave
+  static constexpr int CPR = ROWS / 8;   // rows contiguous: 16-byte chunks of a k row
   __amdgpu_buffer_rsrc_t rsrc;
-  uint32_t off[2];  // byte offset of the lane's chunk in sub-tile 0 (kOob: outside the operand)
-  int kk[2];        // k of that chunk inside a sub-tile
+  uint32_t off[NP];  // byte offset of the lane's chunk in sub-tile 0 (kOob: outside the operand)
+  int kk[NP];        // k of that chunk inside a sub-tile
   uint32_t kstep;   // bytes from one sub-tile to the next
   __device__ __forceinline__ void init(const uint16_t *base, int64_t ld, int rows_left, int K, int wave, int lane) {
-    const int64_t span = panel_span(KM, ld, min(rows_left, 256), rows_left, K);
+    const int64_t span = panel_span(KM, ld, min(rows_left, ROWS), rows_left, K);
     rsrc = make_rsrc(base, (uint32_t)(span * 2));
     kstep = KM ? SK * 2 : (uint32_t)(SK * ld * 2);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int j = wave + 8 * i;  // which of the 16 one-KB pieces of the sub-tile
+    for (int i = 0; i < NP; ++i) {
+      const int j = wave + 8 * i;  // which of the one-KB pieces of the sub-tile
       if (KM) {
         const int r = 16 * j + (lane >> 2), c = (lane & 3) ^ ((r >> 2) & 3);
         kk[i] = c * 8;
         off[i] = r < rows_left ? (uint32_t)((r * ld + c * 8) * 2) : kOob;
       } else {
-        const int k = 2 * j + (lane >> 5), c = (lane & 31) ^ (4 * (k & 3));
+        const int k = 64 / CPR * j + lane / CPR, c = (lane % CPR) ^ (4 * (k & 3));
         kk[i] = k;
         off[i] = c * 8 < rows_left ? (uint32_t)((k * ld + c * 8) * 2) : kOob;
       }
@@ -368,7 +112,7 @@ struct Loader {
   // start the loads of sub-tile u into the operand's 16 KB at dst (wave-uniform)
   __device__ __forceinline__ void issue(int u, int K, char *dst, int wave) const {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NP; ++i) {
       const uint32_t o = (u * SK + kk[i] < K) ? off[i] + u * kstep : kOob;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void)(dst + (wave + 8 * i) * 1024), 16, o, 0, 0, 0);
     }
@@ -376,8 +120,9 @@ struct Loader {
 };
 
 // Per-lane LDS byte offsets (inside an operand's sub-tile) of the fragment reads of a wave whose rows start at wb.
-template <int KM, int NTILE>
+template <int KM, int NTILE, int ROWS>
 struct Frags {
+  static constexpr int LEN = ROWS * 2;  // rows contiguous: bytes of a k row
   uint32_t a[KM ? 2 : NTILE];
   __device__ __forceinline__ void init(int wb, int lane) {
     const int c = lane & 31, g = lane >> 5, s = lane & 15, hi = (lane >> 4) & 1;
@@ -388,7 +133,7 @@ struct Frags {
 #pragma unroll
       for (int i = 0; i < NTILE; ++i) {
         const int chunk = (wb >> 3) + 4 * i + 2 * hi + ((s >> 1) & 1);
-        a[i] = (uint32_t)((g * 8 + (s >> 2)) * 512 + ((chunk ^ (4 * ((s >> 2) & 3))) * 16) + (s & 1) * 8);
+        a[i] = (uint32_t)((g * 8 + (s >> 2)) * LEN + ((chunk ^ (4 * ((s >> 2) & 3))) * 16) + (s & 1) * 8);
       }
     }
   }
@@ -396,9 +141,9 @@ struct Frags {
   __device__ __forceinline__ bf16x8 get(const char *p, int i, int ks) const {
     if (KM) return *reinterpret_cast<const bf16x8 *>(p + a[ks] + i * 2048);
     typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-    const char *q = p + a[i] + ks * 8192;
+    const char *q = p + a[i] + ks * 16 * LEN;
     s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q));
-    s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q + 2048));
+    s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q + 4 * LEN));
     s16x8 v = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
     return __builtin_bit_cast(bf16x8, v);
   }
@@ -407,20 +152,24 @@ struct Frags {
 // SPLIT: the k range is cut into `ksplit` parts of `kchunk` (a multiple of 32) and a work item is (part, tile); part p
 // writes its unscaled fp32 partial product to ep.out + p * M * ldc and splitk_reduce_kernel adds the parts.  Used for
 // products with few output tiles and a long k (weight gradients), which would otherwise occupy a fraction of the CUs.
-template <int AKM, int BKM, bool SPLIT>
+// BN = 256, or 128: half as wide, 64x64 per wave, for products with too few tiles of 256.
+template <int AKM, int BKM, bool SPLIT, int BN>
 __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, Ep ep,
                                                       int tiles_m, int tiles_n, int ksplit, int kchunk) {
-  constexpr int TM = 2, TN = 4;
-  constexpr int EPI_LD = 136;                    // floats per staged output row: 4 rows apart = 32 banks apart
-  constexpr int EPI_WAVE = 32 * EPI_LD * 4;      // one wave's 32 x 128 block of fp32 results
+  constexpr int TM = 2, TN = BN / 64, WN = BN / 2;
+  constexpr int OPA = 256 * SK * 2, OPB = BN * SK * 2, STG = OPA + OPB;  // bytes of the operands' sub-tiles; one stage: A, then B
+  constexpr int LPS = 2 + BN / 128;              // loads per sub-tile and wave
+  constexpr int EPI_LD = WN + 8;                 // floats per staged output row: 4 rows apart = 32 banks apart
+  constexpr int EPI_WAVE = 32 * EPI_LD * 4;      // one wave's 32 x WN block of fp32 results
+  constexpr int LPR = WN / 4, RPI = 64 / LPR;    // lanes per output row, rows per store instruction
   constexpr int SMEM = NST * STG > 8 * EPI_WAVE ? NST * STG : 8 * EPI_WAVE;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
   const int nb = tiles_m * tiles_n;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wpos = wave & 3, half = wave >> 2;  // waves w and w+4 share a SIMD and sit in different groups
-  const int wm = (wpos >> 1) * 128 + half * 64, wn = (wpos & 1) * 128;
-  Frags<AKM, TM> fa;
-  Frags<BKM, TN> fb;
+  const int wm = (wpos >> 1) * 128 + half * 64, wn = (wpos & 1) * WN;
+  Frags<AKM, TM, 256> fa;
+  Frags<BKM, TN, BN> fb;
   fa.init(wm, lane);
   fb.init(wn, lane);
   // Persistent workgroups: each walks the tiles vid, vid + gridDim.x, ...; the stores of one tile drain while the
@@ -438,7 +187,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
   const int grp = bid / per_group, first_m = grp * GROUP;
   const int gsize = min(GROUP, tiles_m - first_m);
   const int tile_m = first_m + (bid % per_group) % gsize, tile_n = (bid % per_group) / gsize;
-  const int m0 = tile_m * 256, n0 = tile_n * 256;
+  const int m0 = tile_m * 256, n0 = tile_n * BN;
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -448,8 +197,8 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  Loader<AKM> la;
-  Loader<BKM> lb;
+  Loader<AKM, 256> la;
+  Loader<BKM, BN> lb;
   la.init(AKM ? A + (int64_t)m0 * lda + kbeg : A + (int64_t)kbeg * lda + m0, lda, M - m0, Kl, wave, lane);
   lb.init(BKM ? B + (int64_t)n0 * ldb + kbeg : B + (int64_t)kbeg * ldb + n0, ldb, N - n0, Kl, wave, lane);
 
@@ -457,13 +206,13 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
 #pragma unroll
   for (int u = 0; u < NST - 1; ++u) {
     la.issue(u, Kl, smem + u * STG, wave);
-    lb.issue(u, Kl, smem + u * STG + OPB, wave);
+    lb.issue(u, Kl, smem + u * STG + OPA, wave);
   }
-  PP_WAIT_VM8_LGKM0;  // sub-tile 0 has landed (4 loads per sub-tile and wave)
+  PP_WAIT_VM_LGKM0(2 * LPS);  // sub-tile 0 has landed
   __builtin_amdgcn_s_barrier();
   if (half) __builtin_amdgcn_s_barrier();  // the second group runs one phase late
   for (int u = 0; u < nsub; ++u) {
-    const char *sa = smem + (u & (NST - 1)) * STG, *sb = sa + OPB;
+    const char *sa = smem + (u & (NST - 1)) * STG, *sb = sa + OPA;
     char *dn = smem + ((u + NST - 1) & (NST - 1)) * STG;
     __builtin_amdgcn_sched_barrier(0);
     // memory phase: fragments of sub-tile u; global loads of sub-tile u + 3 into the stage both groups left last
@@ -477,8 +226,8 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
       for (int j = 0; j < TN; ++j) bfr[ks][j] = fb.get(sb, j, ks);
     }
     la.issue(u + NST - 1, Kl, dn, wave);
-    lb.issue(u + NST - 1, Kl, dn + OPB, wave);
-    PP_WAIT_VM8_LGKM0;  // own fragments are in registers; own loads of sub-tile u + 1 have landed
+    lb.issue(u + NST - 1, Kl, dn + OPA, wave);
+    PP_WAIT_VM_LGKM0(2 * LPS);  // own fragments are in registers; own loads of sub-tile u + 1 have landed
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
@@ -498,12 +247,11 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
 
   // Epilogue.  A 32x32 accumulator tile holds column lane % 32 and rows 8*(r/4) + 4*(lane/32) + r%4, which
   // would store 2-byte pieces; each wave instead turns its results through LDS, 32 rows at a time, so that a
-  // lane owns 4 consecutive columns and a store instruction writes two full rows of 128 columns.
+  // lane owns 4 consecutive columns and a store instruction writes two full rows of 128 columns (four of 64).
   float *stage = reinterpret_cast<float *>(smem + wave * EPI_WAVE);
-  const int c = lane & 31, g = lane >> 5;
-  const int rows_left = M - m0;
+  const int c = lane & 31, g = lane >> 5, cq = lane % LPR, rq = lane / LPR;
   void *const outp = SPLIT ? static_cast<void *>(static_cast<float *>(ep.out) + (int64_t)part * M * ep.ldc) : ep.out;
-  const int ncol = n0 + wn + 4 * c;  // first of this lane's 4 columns
+  const int ncol = n0 + wn + 4 * cq;  // first of this lane's 4 columns
   float bias[4] = {0.f, 0.f, 0.f, 0.f};
   if (ep.bias) {
 #pragma unroll
@@ -512,7 +260,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
   }
   const bool vec = ep.vec_ok && ncol + 3 < N;
   // a tile that lies inside the output and needs nothing but the conversion (most projections): no edge tests, no arithmetic
-  const bool bare = ep.vec_ok && !ep.bias && !ep.residual && ep.alpha == 1.f && m0 + 256 <= M && n0 + 256 <= N;
+  const bool bare = ep.vec_ok && !ep.bias && !ep.residual && ep.alpha == 1.f && m0 + 256 <= M && n0 + BN <= N;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -520,11 +268,11 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
 #pragma unroll
       for (int r = 0; r < 16; ++r) stage[(8 * (r >> 2) + 4 * g + (r & 3)) * EPI_LD + 32 * j + c] = acc[i][j][r];
     if (bare) {
-      const int64_t o0 = (int64_t)(m0 + wm + 32 * i + g) * ep.ldc + ncol;
+      const int64_t o0 = (int64_t)(m0 + wm + 32 * i + rq) * ep.ldc + ncol;
 #pragma unroll
-      for (int p = 0; p < 16; ++p) {
-        const f32x4 v4 = *reinterpret_cast<const f32x4 *>(stage + (2 * p + g) * EPI_LD + 4 * c);
-        const int64_t o = o0 + 2 * p * ep.ldc;
+      for (int p = 0; p < 32 / RPI; ++p) {
+        const f32x4 v4 = *reinterpret_cast<const f32x4 *>(stage + (RPI * p + rq) * EPI_LD + 4 * cq);
+        const int64_t o = o0 + RPI * p * ep.ldc;
         if (ep.out_f32) {
           __builtin_nontemporal_store(v4, reinterpret_cast<f32x4 *>(static_cast<float *>(outp) + o));
         } else {
@@ -535,37 +283,10 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
       continue;
     }
 #pragma unroll 4
-    for (int p = 0; p < 16; ++p) {
-      const int row = 2 * p + g, ml = wm + 32 * i + row;
-      const f32x4 v4 = *reinterpret_cast<const f32x4 *>(stage + row * EPI_LD + 4 * c);
-      if (ml >= rows_left || ncol >= N) continue;
-      const int64_t o = (int64_t)(m0 + ml) * ep.ldc + ncol;
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (v4[e] + bias[e]) * ep.alpha;
-      if (vec) {
-        if (ep.residual) {
-          const f32x4 rr = *reinterpret_cast<const f32x4 *>(ep.residual + o);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] += rr[e];
-        }
-        if (ep.out_f32) {
-          const f32x4 w = {v[0], v[1], v[2], v[3]};
-          __builtin_nontemporal_store(w, reinterpret_cast<f32x4 *>(static_cast<float *>(outp) + o));
-        } else {
-          const u32x2 w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-          __builtin_nontemporal_store(w, reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(outp) + o));
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (ncol + e >= N) break;
-          float x = v[e];
-          if (ep.residual) x += ep.residual[o + e];
-          if (ep.out_f32) static_cast<float *>(outp)[o + e] = x;
-          else static_cast<uint16_t *>(outp)[o + e] = f2bf(x);
-        }
-      }
+    for (int p = 0; p < 32 / RPI; ++p) {
+      const int row = RPI * p + rq, m = m0 + wm + 32 * i + row;
+      const f32x4 v4 = *reinterpret_cast<const f32x4 *>(stage + row * EPI_LD + 4 * cq);
+      if (m < M && ncol < N) store_quad<true>(ep, outp, m, ncol, N, v4, bias, vec);
     }
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's staged results are in registers
@@ -636,31 +357,61 @@ __global__ __launch_bounds__(256) void mfma_only_kernel(int iters, float *sink, 
   sink[(size_t)blockIdx.x * 256 + threadIdx.x] = t;
 }
 
-// number of k parts for a product with few 256x256 output tiles and a long k (1 = do not split)
-int choose_ksplit(int M, int N, int K, int *kchunk) {
-  const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  *kchunk = K;
-  if (tiles >= 128 || K < 1024) return 1;
-  int ks = std::min({16, 256 / tiles, K / 512});
-  if (ks < 2) return 1;
-  *kchunk = ((K + ks - 1) / ks + 31) / 32 * 32;
-  return (K + *kchunk - 1) / *kchunk;
+// Which kernel a bf16 product runs on, and into how many parts its contraction is cut, by estimated time:
+//   fixed + rounds * slices * (s0 + s1 * share of the chip at work)   microseconds, slices of 32 along the contraction
+// with rounds = how many tiles the busiest of 256 CUs works through (the small tiles share a CU in pairs, so theirs need not be
+// whole).  fixed = launch, first loads, epilogue; s1 = how much slower a slice gets when the whole chip works (clock, memory).
+// Fitted to measurements (us), bf16 operands not in the caches, K-contiguous unless said:
+//   M x N x K             256x256  256x128   64x64   32x32   (register-staged 128x128, which these replace)
+//   128 x 2304 x 768         20.3     13.5     5.9     5.6    13.2
+//   128 x 768 x 1536         31.0              8.3     5.1    21.1
+//   2048 x 1536 x 768        19.2     14.6    12.8    23.3    14.3
+//   2048 x 768 x 2048        36.4     28.0    14.7    21.5    26.4
+//   8192 x 768 x 192         10.1      7.4    13.0    30.0    10.6
+//   8192 x 768 x 768         19.3     15.5    22.0    42.0    20.2
+//   3000 x 2688 x 2048       43.2     37.3    56.6    96.0    45.5
+//   8192 x 1024 x 2048       47.5     41.5    60.1            46.7
+//   8192 x 2048 x 1024 (NN)  34.6     40.3    68.4            49.0
+//   4096 x 4096 x 4096      110.9    134.7   232.0   348.0   163.0
+//   768 x 768 x 8192 (TN)   131.4    108.8    31.5    58.7    97.4   (uncut)
+// A cut contraction adds a launch and one pass over the fp32 partial products (5.5 TB/s).
+struct Kind { int bm, bn; double fixed, s0, s1; bool paired; };
+constexpr Kind kKinds[] = {{256, 256, 9.6, 0.40, 0.38, false}, {256, 128, 4.8, 0.33, 0.24, false}, {64, 64, 3.5, 0.10, 0.02, true}, {32, 32, 3.5, 0.05, 0.015, true}};
+struct Choice { int kind, parts; };
+Choice choose(int M, int N, int K, bool may_split, size_t split_floats) {
+  Choice best{0, 1};
+  double best_us = 1e30;
+  for (int k = 0; k < 4; ++k) {
+    const Kind &kd = kKinds[k];
+    const double tiles = (double)((M + kd.bm - 1) / kd.bm) * ((N + kd.bn - 1) / kd.bn);
+    for (int parts = 1; parts <= 16; ++parts) {
+      if (parts > 1 && (!may_split || K < 256 * parts || (double)parts * M * N > (double)split_floats)) break;
+      const double items = tiles * parts, share = std::min(1.0, items / 256), slices = (double)K / 32 / parts;
+      const double rounds = kd.paired ? std::max(1.0, items / 256) : (double)(((int64_t)items + 255) / 256);
+      double us = kd.fixed + rounds * slices * (kd.s0 + kd.s1 * share);
+      if (parts > 1) us += 2.5 + (parts + 1.0) * M * N * 4.0 / 5.5e6;
+      if (us < best_us) { best_us = us; best = {k, parts}; }
+    }
+  }
+  return best;
 }
 
-template <int AKM, int BKM>
-void launch_mfma(hipStream_t st, int force_tile, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const Ep &ep) {
-  // the 256x256 ping-pong kernel (one persistent workgroup per CU) from 128 tiles up (half the chip), else 128x128 tiles
-  // (4 waves of 64x64), four times as many, which fill the chip where the big tiles would occupy a third of it (the
-  // projections of narrow subnets: 96 big tiles at GPT-2-small quarter width, 5 to 10 % faster this way)
-  const int big = ((M + 255) / 256) * ((N + 255) / 256);
-  const bool use_big = force_tile ? force_tile == 256 : big >= 128;
-  if (use_big) {
-    const int tm = (M + 255) / 256, tn = (N + 255) / 256;
-    hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, BKM, false>), dim3(std::min(tm * tn, 256)), dim3(512), 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, 1, K);
-  } else {
-    const int tm = (M + 127) / 128, tn = (N + 127) / 128;
-    hipLaunchKernelGGL((gemm_mfma_kernel<AKM, BKM, 128, 128, 2, 2>), dim3(tm * tn), dim3(256), 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn);
+// one launch of gemm_pp_kernel: kchunk = K for an uncut contraction, else a multiple of 32
+template <int BN>
+void launch_pp(hipStream_t st, GemmLayout lay, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const Ep &ep, int parts, int kchunk) {
+  const int tm = (M + 255) / 256, tn = (N + BN - 1) / BN;
+  const dim3 grid(std::min(tm * tn * parts, 256)), block(512);
+#define TW_PP(AKM, BKM)                                                                                                                                             \
+  do {                                                                                                                                                              \
+    if (parts > 1) hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, BKM, true, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, parts, kchunk);            \
+    else hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, BKM, false, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, 1, K);                              \
+  } while (0)
+  switch (lay) {
+    case GEMM_NT: TW_PP(1, 1); break;
+    case GEMM_NN: TW_PP(1, 0); break;
+    case GEMM_TN: TW_PP(0, 0); break;
   }
+#undef TW_PP
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -704,27 +455,18 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
   const bool vec_ok = bf16 && !no_mfma && aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 && k_ok && span_ok;
   if (vec_ok) {
     const uint16_t *a = static_cast<const uint16_t *>(A), *b = static_cast<const uint16_t *>(B);
-    int kchunk = K;
-    const int ks = (e.splitk_ws && !e.bias && !e.residual && !ctx->gemm_tile) ? choose_ksplit(M, N, K, &kchunk) : 1;
-    if (ks > 1 && (size_t)ks * M * N <= e.splitk_floats && aligned16(e.splitk_ws)) {
-      const int tm = (M + 255) / 256, tn = (N + 255) / 256;
-      Ep part{1.f, nullptr, nullptr, e.splitk_ws, 1, N, N % 4 == 0};
-      const dim3 grid(std::min(tm * tn * ks, 256)), block(512);
-      switch (lay) {
-        case GEMM_NT: hipLaunchKernelGGL((pp::gemm_pp_kernel<1, 1, true>), grid, block, 0, stream, M, N, K, a, lda, b, ldb, part, tm, tn, ks, kchunk); break;
-        case GEMM_NN: hipLaunchKernelGGL((pp::gemm_pp_kernel<1, 0, true>), grid, block, 0, stream, M, N, K, a, lda, b, ldb, part, tm, tn, ks, kchunk); break;
-        case GEMM_TN: hipLaunchKernelGGL((pp::gemm_pp_kernel<0, 0, true>), grid, block, 0, stream, M, N, K, a, lda, b, ldb, part, tm, tn, ks, kchunk); break;
-      }
-      TW_HIP(ctx, hipGetLastError());
-      return twist_splitk_reduce(ctx, stream, e.splitk_ws, ks, M, N, e.out, ldc, e.out_f32, e.alpha);
-    }
-    switch (lay) {
-      case GEMM_NT: launch_mfma<1, 1>(stream, ctx->gemm_tile, M, N, K, a, lda, b, ldb, ep); break;
-      case GEMM_NN: launch_mfma<1, 0>(stream, ctx->gemm_tile, M, N, K, a, lda, b, ldb, ep); break;
-      case GEMM_TN: launch_mfma<0, 0>(stream, ctx->gemm_tile, M, N, K, a, lda, b, ldb, ep); break;
+    Choice ch = choose(M, N, K, e.splitk_ws && !e.bias && !e.residual && aligned16(e.splitk_ws), e.splitk_floats);
+    if (ctx->gemm_tile) ch = {ctx->gemm_tile == 256 ? 0 : 1, 1};
+    const int step = ch.kind < 2 ? 32 : 128, kchunk = ((K + ch.parts - 1) / ch.parts + step - 1) / step * step, parts = (K + kchunk - 1) / kchunk;
+    if (parts > 1) ep = Ep{1.f, nullptr, nullptr, e.splitk_ws, 1, N, N % 4 == 0};
+    switch (ch.kind) {
+      case 0: launch_pp<256>(stream, lay, M, N, K, a, lda, b, ldb, ep, parts, kchunk); break;
+      case 1: launch_pp<128>(stream, lay, M, N, K, a, lda, b, ldb, ep, parts, kchunk); break;
+      case 2: twist_launch_gemm_dl(stream, 64, lay, M, N, K, a, lda, b, ldb, &ep, parts, kchunk); break;
+      default: twist_launch_gemm_dl(stream, 32, lay, M, N, K, a, lda, b, ldb, &ep, parts, kchunk); break;
     }
     TW_HIP(ctx, hipGetLastError());
-    return TWIST_OK;
+    return parts > 1 ? twist_splitk_reduce(ctx, stream, e.splitk_ws, parts, M, N, e.out, ldc, e.out_f32, e.alpha) : TWIST_OK;
   }
   if (!bf16 && !no_mfma) return twist_gemm_f32(ctx, stream, lay, M, N, K, static_cast<const float *>(A), lda, static_cast<const float *>(B), ldb, ldc, e);
   int64_t sam, sak, sbk, sbn;

@@ -1,0 +1,88 @@
+// Device code shared by the bf16 projection kernels (gemm.hip, gemm_dl.hip): operand types, the epilogue's arguments, conversions.
+#pragma once
+#include "nn.h"
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+// two floats to a packed pair of bf16, round to nearest even, in one instruction (v_cvt_pk_bf16_f32): the same bits as f2bf for
+// every finite value and infinity (the software form costs about eight instructions and a branch per value, which showed in
+// the epilogue: 40.6 -> 39.9 ms per forward+backward pass)
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  const f32x2_t v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+__device__ __forceinline__ uint16_t f2bf(float f) {
+  uint32_t u = __float_as_uint(f);
+  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
+  u += 0x7fffu + ((u >> 16) & 1u);
+  return (uint16_t)(u >> 16);
+}
+
+struct Ep {
+  float alpha;
+  const void *bias;
+  const float *residual;
+  void *out;
+  int out_f32;
+  int64_t ldc;
+  int vec_ok;  // out (and residual) rows allow 4-element vector accesses: ldc % 4 == 0, 16-byte aligned bases
+};
+
+constexpr uint32_t kOob = 0x80000000u;  // byte offset beyond every buffer: loads return 0, stores are dropped
+
+// Elements from a panel's base to the end of its last 16-byte chunk.  A load that reaches beyond the buffer's range returns nothing at
+// all, so the range has to include the whole of a last row's partly used chunk (the chunk is aligned and holds at least one
+// element of the operand, so reading it is safe; what it holds beyond the operand meets zeros or is not stored).
+__device__ __forceinline__ int64_t panel_span(int km, int64_t ld, int rows, int rows_left, int K) {
+  const int64_t len = km ? K : rows_left, up = (len + 7) / 8 * 8;
+  return (km ? (int64_t)(rows - 1) : (int64_t)(K - 1)) * ld + (up < ld ? up : ld);
+}
+
+// Stores four consecutive columns ncol .. ncol + 3 of row m: out = (v4 + bias) alpha + residual (STREAM: past the caches)
+template <bool STREAM>
+__device__ __forceinline__ void store_quad(const Ep &ep, void *outp, int m, int ncol, int N, const f32x4 &v4, const float (&bias)[4], bool vec) {
+  const int64_t o = (int64_t)m * ep.ldc + ncol;
+  float v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = (v4[e] + bias[e]) * ep.alpha;
+  if (vec) {
+    if (ep.residual) {
+      const f32x4 rr = *reinterpret_cast<const f32x4 *>(ep.residual + o);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += rr[e];
+    }
+    if (ep.out_f32) {
+      const f32x4 w = {v[0], v[1], v[2], v[3]};
+      f32x4 *p = reinterpret_cast<f32x4 *>(static_cast<float *>(outp) + o);
+      if (STREAM) __builtin_nontemporal_store(w, p);
+      else *p = w;
+    } else {
+      const u32x2 w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+      u32x2 *p = reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(outp) + o);
+      if (STREAM) __builtin_nontemporal_store(w, p);
+      else *p = w;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (ncol + e >= N) break;
+      float x = v[e];
+      if (ep.residual) x += ep.residual[o + e];
+      if (ep.out_f32) static_cast<float *>(outp)[o + e] = x;
+      else static_cast<uint16_t *>(outp)[o + e] = f2bf(x);
+    }
+  }
+}
+
+}  // namespace

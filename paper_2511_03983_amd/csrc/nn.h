@@ -11,7 +11,7 @@ struct GemmEpilogue {
   int out_f32 = 0;               // 1: out is fp32, 0: out is the activation type
   // Optional scratch for products with few output tiles and a long contraction (weight gradients): when given (and no
   // bias/residual is asked for) the contraction may be cut into parts whose fp32 partial products go here and are then
-  // summed in a fixed order.  At most 256 tiles of 256 x 256 floats are ever needed.
+  // summed in a fixed order.
   float *splitk_ws = nullptr;
   size_t splitk_floats = 0;
 };
@@ -28,6 +28,9 @@ enum GemmLayout {
 twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, int K, const void *A, int64_t lda, const void *B,
                         int64_t ldb, int64_t ldc, const GemmEpilogue &ep, hipStream_t st = nullptr);
 
+// the bf16 kernels for tiles of 64 and 32 (ep: a gemm_tile.h Ep), the contraction cut into `parts` parts of kchunk (a multiple of 128)
+void twist_launch_gemm_dl(hipStream_t st, int tile, GemmLayout lay, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep,
+                          int parts, int kchunk);
 // the fp32 form of twist_gemm, and the sum of the partial products [parts][M][N] of a product whose contraction was cut
 // (out = alpha * sum in ascending order)
 twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,

@@ -73,6 +73,27 @@ def test_fp32_projection(lib):
         assert rel_fro(to_numpy(out), want) <= 1e-4
 
 
+# By size: the first shapes take the 32x32 tiles, the last four the 64x64 tiles; edges of both, contractions shorter than, ending in and
+# filling a slice (128 and 64 long) and fewer slices than the four stages
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (1, 40, 120), (31, 33, 136), (33, 64, 264), (128, 768, 1032), (65, 200, 3080),
+                                   (500, 2300, 136), (513, 2304, 8), (449, 2305, 56), (520, 2048, 648)])
+def test_small_bf16_projection_edges(lib, layout, M, N, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
+    up = lambda n: (n + 7) // 8 * 8
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, B = ((torch.randn((r, up(c)), generator=gen, device="cuda").bfloat16()[:, :c]) for r, c in
+            ((K, M) if layout == 2 else (M, K), (N, K) if layout == 0 else (K, N)))      # rows 16 bytes apart
+    want = (A.double().T if layout == 2 else A.double()) @ (B.double().T if layout == 0 else B.double())
+    for dt, tol in ((torch.bfloat16, 5e-3), (torch.float32, 1e-5)):
+        buf = torch.full((M * N + 64,), float("nan"), dtype=dt, device="cuda")            # what lies behind the result must stay
+        out = buf[:M * N].view(M, N)
+        ctx.twist_gemm_raw(layout, M, N, K, A, B, out, alpha=0.5)
+        torch.cuda.synchronize()
+        assert float((out.double() - 0.5 * want).norm() / (0.5 * want).norm()) <= tol
+        assert torch.isnan(buf[M * N:]).all()
+
+
 # fp32 matrix-instruction kernel: 64- and 128-wide tiles (128 pinned, and by size at 3000 x 2900), ragged edges, contractions that end
 # inside a slice of 32, strides that allow 16-byte loads and strides that do not (odd K, M or N)
 @pytest.mark.parametrize("tile", [0, 128])
