@@ -1,7 +1,7 @@
 // Dense projections of the subnet: C = epilogue(op(A) op(B)) with fp32 accumulation.
-//  - bf16 operands: MFMA kernels (v_mfma_f32_32x32x16_bf16) fed by direct-to-LDS loads: ping-pong kernels with tiles of
-//    256x256 and 256x128 (here), and 64x64 and 32x32 tiles for products too small to fill the chip with those (gemm_dl.hip);
-//    operands stay in LDS in their memory orientation, and those whose contraction index is the slow axis in memory are
+//  - bf16 operands: MFMA kernels fed by direct-to-LDS loads: ping-pong kernels with tiles of 256x256 and 256x128 (here; in
+//    gemm_nt.hip where both operands are contiguous along k), and 64x64 and 32x32 tiles for products too small to fill the
+//    chip with those (gemm_dl.hip); operands stay in LDS in their memory orientation, and those whose contraction index is the slow axis in memory are
 //    read back with the transposing LDS load.
 //  - fp32 operands: the fp32 matrix instruction (gemm_f32.hip).
 //  - anything else (unaligned bf16 shapes): a plain tiled FMA kernel with arbitrary strides.
@@ -78,8 +78,6 @@ namespace pp {
 
 constexpr int SK = 32;             // k extent of a sub-tile
 constexpr int NST = 4;
-typedef __attribute__((address_space(3))) void *lds_void;
-
 #define PP_WAIT_VM_LGKM0(vm) __builtin_amdgcn_s_waitcnt(0x0070 | (vm))  // vmcnt(vm < 16) lgkmcnt(0)
 #define PP_WAIT_VM0 __builtin_amdgcn_s_waitcnt(0x0f70)        // vmcnt(0)
 
@@ -153,7 +151,7 @@ struct Frags {
 // writes its unscaled fp32 partial product to ep.out + p * M * ldc and splitk_reduce_kernel adds the parts.  Used for
 // products with few output tiles and a long k (weight gradients), which would otherwise occupy a fraction of the CUs.
 // BN = 256, or 128: half as wide, 64x64 per wave, for products with too few tiles of 256.
-template <int AKM, int BKM, bool SPLIT, int BN>
+template <int AKM, bool SPLIT, int BN>
 __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, Ep ep,
                                                       int tiles_m, int tiles_n, int ksplit, int kchunk) {
   constexpr int TM = 2, TN = BN / 64, WN = BN / 2;
@@ -169,7 +167,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
   const int wpos = wave & 3, half = wave >> 2;  // waves w and w+4 share a SIMD and sit in different groups
   const int wm = (wpos >> 1) * 128 + half * 64, wn = (wpos & 1) * WN;
   Frags<AKM, TM, 256> fa;
-  Frags<BKM, TN, BN> fb;
+  Frags<0, TN, BN> fb;
   fa.init(wm, lane);
   fb.init(wn, lane);
   // Persistent workgroups: each walks the tiles vid, vid + gridDim.x, ...; the stores of one tile drain while the
@@ -198,9 +196,9 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   Loader<AKM, 256> la;
-  Loader<BKM, BN> lb;
+  Loader<0, BN> lb;
   la.init(AKM ? A + (int64_t)m0 * lda + kbeg : A + (int64_t)kbeg * lda + m0, lda, M - m0, Kl, wave, lane);
-  lb.init(BKM ? B + (int64_t)n0 * ldb + kbeg : B + (int64_t)kbeg * ldb + n0, ldb, N - n0, Kl, wave, lane);
+  lb.init(B + (int64_t)kbeg * ldb + n0, ldb, N - n0, Kl, wave, lane);
 
   const int nsub = (Kl + SK - 1) / SK;
 #pragma unroll
@@ -401,15 +399,15 @@ template <int BN>
 void launch_pp(hipStream_t st, GemmLayout lay, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const Ep &ep, int parts, int kchunk) {
   const int tm = (M + 255) / 256, tn = (N + BN - 1) / BN;
   const dim3 grid(std::min(tm * tn * parts, 256)), block(512);
-#define TW_PP(AKM, BKM)                                                                                                                                             \
+#define TW_PP(AKM)                                                                                                                                             \
   do {                                                                                                                                                              \
-    if (parts > 1) hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, BKM, true, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, parts, kchunk);            \
-    else hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, BKM, false, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, 1, K);                              \
+    if (parts > 1) hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, true, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, parts, kchunk);            \
+    else hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, false, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, 1, K);                              \
   } while (0)
   switch (lay) {
-    case GEMM_NT: TW_PP(1, 1); break;
-    case GEMM_NN: TW_PP(1, 0); break;
-    case GEMM_TN: TW_PP(0, 0); break;
+    case GEMM_NT: twist_launch_gemm_nt(st, BN, M, N, K, a, lda, b, ldb, &ep); break;  // never cut
+    case GEMM_NN: TW_PP(1); break;
+    case GEMM_TN: TW_PP(0); break;
   }
 #undef TW_PP
 }
@@ -455,7 +453,7 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
   const bool vec_ok = bf16 && !no_mfma && aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 && k_ok && span_ok;
   if (vec_ok) {
     const uint16_t *a = static_cast<const uint16_t *>(A), *b = static_cast<const uint16_t *>(B);
-    Choice ch = choose(M, N, K, e.splitk_ws && !e.bias && !e.residual && aligned16(e.splitk_ws), e.splitk_floats);
+    Choice ch = choose(M, N, K, e.splitk_ws && lay != GEMM_NT && !e.bias && !e.residual && aligned16(e.splitk_ws), e.splitk_floats);
     if (ctx->gemm_tile) ch = {ctx->gemm_tile == 256 ? 0 : 1, 1};
     const int step = ch.kind < 2 ? 32 : 128, kchunk = ((K + ch.parts - 1) / ch.parts + step - 1) / step * step, parts = (K + kchunk - 1) / kchunk;
     if (parts > 1) ep = Ep{1.f, nullptr, nullptr, e.splitk_ws, 1, N, N % 4 == 0};

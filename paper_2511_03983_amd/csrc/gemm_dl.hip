@@ -24,27 +24,6 @@
 
 namespace {
 
-typedef __attribute__((address_space(3))) void *lds_void;
-typedef uint32_t desc_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ desc_t make_desc(const void *p, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  desc_t d;
-  d.x = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  d.y = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
-  d.z = __builtin_amdgcn_readfirstlane(bytes);
-  d.w = 0x00020000u;
-  return d;
-}
-// 16 bytes per lane from global memory straight into LDS at lds + 16 lane (zeros where voff is outside the descriptor's range).  As
-// assembly because for the builtin form the compiler makes every later transposing LDS read wait for all such loads in flight.
-__device__ __forceinline__ void dma16(desc_t desc, const char *lds, uint32_t voff) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void)(lds));
-  uint32_t keep;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-               : "=&s"(keep) : "s"(l), "v"(voff), "s"(desc) : "memory");
-}
-
 // One operand: ROWS rows of the tile, slices of BK
 template <int KM, int ROWS, int BK>
 struct Operand {

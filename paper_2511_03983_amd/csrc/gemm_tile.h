@@ -49,6 +49,27 @@ __device__ __forceinline__ int64_t panel_span(int km, int64_t ld, int rows, int 
   return (km ? (int64_t)(rows - 1) : (int64_t)(K - 1)) * ld + (up < ld ? up : ld);
 }
 
+typedef __attribute__((address_space(3))) void *lds_void;
+typedef uint32_t desc_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ desc_t make_desc(const void *p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  desc_t d;
+  d.x = __builtin_amdgcn_readfirstlane((uint32_t)a);
+  d.y = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
+  d.z = __builtin_amdgcn_readfirstlane(bytes);
+  d.w = 0x00020000u;
+  return d;
+}
+// 16 bytes per lane from global memory straight into LDS at lds + 16 lane (zeros where voff is outside the descriptor's range).  As
+// assembly because for the builtin form the compiler makes every later transposing LDS read wait for all such loads in flight.
+__device__ __forceinline__ void dma16(desc_t desc, const char *lds, uint32_t voff) {
+  const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void)(lds));
+  uint32_t keep;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+               : "=&s"(keep) : "s"(l), "v"(voff), "s"(desc) : "memory");
+}
+
 // Stores four consecutive columns ncol .. ncol + 3 of row m: out = (v4 + bias) alpha + residual (STREAM: past the caches)
 template <bool STREAM>
 __device__ __forceinline__ void store_quad(const Ep &ep, void *outp, int m, int ncol, int N, const f32x4 &v4, const float (&bias)[4], bool vec) {

@@ -28,6 +28,8 @@ enum GemmLayout {
 twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, int K, const void *A, int64_t lda, const void *B,
                         int64_t ldb, int64_t ldc, const GemmEpilogue &ep, hipStream_t st = nullptr);
 
+// the bf16 ping-pong kernel for GEMM_NT (ep: a gemm_tile.h Ep), tiles of 256 x bn, bn = 256 or 128
+void twist_launch_gemm_nt(hipStream_t st, int bn, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep);
 // the bf16 kernels for tiles of 64 and 32 (ep: a gemm_tile.h Ep), the contraction cut into `parts` parts of kchunk (a multiple of 128)
 void twist_launch_gemm_dl(hipStream_t st, int tile, GemmLayout lay, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep,
                           int parts, int kchunk);

@@ -134,3 +134,23 @@ def test_raw_rejects_bad_strides(lib):
         ctx.twist_gemm_raw(0, 16, 16, 32, A, A, out)      # K larger than the row stride
     with pytest.raises(lib.TwistError):
         ctx.twist_set_kernel_choice(gemm_tile=64)         # only 0, 128 and 256 exist
+
+
+# y = x W^T on the ping-pong kernel: contractions around the length of its ring of five sub-tiles of 32, odd and even counts of them,
+# edges of a tile, and more tiles than workgroups (a second tile through the same stages)
+@pytest.mark.parametrize("tile", [128, 256])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 8), (255, 130, 32), (257, 260, 40), (300, 64, 64), (256, 256, 96), (31, 300, 136), (520, 136, 168), (256, 129, 328),
+                                   (4360, 4100, 72)])
+def test_bf16_nt_projection_edges(lib, tile, M, N, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
+    ctx.twist_set_kernel_choice(gemm_tile=tile)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, B = (torch.randn((r, K), generator=gen, device="cuda").bfloat16() for r in (M, N))
+    want = A.double() @ B.double().T
+    buf = torch.full((M * N + 64,), float("nan"), device="cuda")            # what lies behind the result must stay
+    out = buf[:M * N].view(M, N)
+    ctx.twist_gemm_raw(0, M, N, K, A, B, out)
+    torch.cuda.synchronize()
+    # fp32 sums of K exact products: 2^-24 sqrt(K) at most; a dropped or repeated chunk of 8 would show as sqrt(8 / K) >= 0.15
+    assert float((out.double() - want).norm() / want.norm()) <= 5e-6
+    assert torch.isnan(buf[M * N:]).all()
