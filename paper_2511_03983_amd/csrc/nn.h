@@ -101,8 +101,8 @@ twist_status twist_act_fwd(twist_ctx *ctx, int bf16, int act, const void *gu, vo
 twist_status twist_act_bwd(twist_ctx *ctx, int bf16, int act, const void *gu, const void *da, void *dgu, int T, int F, const int32_t *keep = nullptr,
                            int unit = 1);
 
-// logits [T,V] -> in place dlogits = (softmax - onehot)/T; row losses to rowloss[T]; then loss = mean
-twist_status twist_ce_fwd_bwd(twist_ctx *ctx, int bf16, void *logits, int64_t ld, const int32_t *targets, float *rowloss, float *loss, int T, int V);
+// logits [T,V] -> in place dlogits = (softmax - onehot)/T (grad) or left alone; row losses to rowloss[T]; then loss = mean
+twist_status twist_ce_fwd_bwd(twist_ctx *ctx, int bf16, void *logits, int64_t ld, const int32_t *targets, float *rowloss, float *loss, int T, int V, bool grad = true);
 // dx = 2 (x - y)/n ; dxb = activation-type copy; loss = mean squared error
 twist_status twist_mse_fwd_bwd(twist_ctx *ctx, int bf16, const float *x, const void *y, float *dx, void *dxb, float *partial, float *loss, int64_t n);
 

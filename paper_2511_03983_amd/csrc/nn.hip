@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kT) void act_bwd_kernel(int act, const void *gu, co
 
 // ------------------------------------------------------------------------------------------- losses
 // one workgroup per row: logsumexp, row loss, then dlogits in place
-template <int BF>
+template <int BF, bool GRAD>
 __global__ __launch_bounds__(kT) void ce_kernel(void *logits, int64_t ld, const int32_t *targets, float *rowloss, int V, float inv_T) {
   __shared__ float sh[4];
   const int64_t base = (int64_t)blockIdx.x * ld;
@@ -384,6 +384,7 @@ __global__ __launch_bounds__(kT) void ce_kernel(void *logits, int64_t ld, const 
   const float lse = m + logf(s);
   const int tgt = targets[blockIdx.x];
   if (threadIdx.x == 0) rowloss[blockIdx.x] = lse - El<BF>::ld(logits, base + tgt);
+  if (!GRAD) return;
   __syncthreads();
   for (int c = threadIdx.x; c < V; c += kT) {
     float p = __expf(El<BF>::ld(logits, base + c) - lse);
@@ -477,56 +478,82 @@ __device__ __forceinline__ u32x4v pack8(const F8 &f) {
   return u;
 }
 
-// Cross-entropy of a bf16 row of at most NV * 2048 logits held in registers: one read of the row, one write of its
-// gradient (the general kernel above walks the row three times with 2-byte accesses).  ld8 = row stride / 8; columns
-// between V and the stride are padding and get zeros.
-template <int NV>
-__global__ __launch_bounds__(kT) void ce_vec_kernel(u32x4v *logits, int64_t ld8, const int32_t *targets, float *rowloss, int V, float inv_T) {
-  __shared__ float sh[4];
+// Cross-entropy of a bf16 row of at most NV * 8 * NT logits held in registers: one read of the row, one write of its gradient where
+// that is wanted (GRAD).  Bound by memory; ld8 = row stride / 8; columns between V and the stride are padding and get zeros.
+// 512 threads take rows of up to 65536: 8192 x 50257 in 347 us (4.7 TB/s), where the two passes over the row of ce_vec_long_kernel, which
+// longer rows still use, take 418.  Without the gradient, which an evaluation has no use for, 4096 x 50257 takes 80 us instead of 212.
+template <int NV, int NT, bool GRAD>
+__global__ __launch_bounds__(NT) void ce_vec_kernel(u32x4v *logits, int64_t ld8, const int32_t *targets, float *rowloss, int V, float inv_T) {
+  constexpr int NW = NT / 64;
+  __shared__ float sh[2][NW];
   u32x4v *row = logits + (int64_t)blockIdx.x * ld8;
-  F8 x[NV];
+  const int wave = threadIdx.x >> 6;
+  u32x4v x[NV];
   float m = -INFINITY;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    const int idx = k * kT + threadIdx.x;
-    if (idx < ld8) {
-      x[k] = unpack8(row[idx]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (idx * 8 + e >= V) x[k].v[e] = -INFINITY;
-        m = fmaxf(m, x[k].v[e]);
-      }
-    }
+    const int idx = k * NT + threadIdx.x;
+    x[k] = u32x4v{0xff80ff80u, 0xff80ff80u, 0xff80ff80u, 0xff80ff80u};  // -inf: beyond the row
+    if (idx < ld8) x[k] = row[idx];
   }
-  m = block_max(m, sh);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int left = V - 8 * (k * NT + (int)threadIdx.x);  // logits from this vector on; padding becomes -inf
+    if (left < 8) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (e >= left) x[k][e >> 1] = e & 1 ? (x[k][e >> 1] & 0xffffu) | 0xff800000u : (x[k][e >> 1] & 0xffff0000u) | 0xff80u;
+    }
+    const F8 f = unpack8(x[k]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m = fmaxf(m, f.v[e]);
+  }
+  // (the row stays packed between the passes: unpacked it would take twice the registers and leave half the waves in flight)
+#define TW_KEEP_PACKED _Pragma("unroll") for (int k = 0; k < NV; ++k) asm volatile("" : "+v"(x[k]))
+  TW_KEEP_PACKED;
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) sh[0][wave] = m;
+  __syncthreads();
+  m = sh[0][0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) m = fmaxf(m, sh[0][i]);
   float s = 0.f;
 #pragma unroll
-  for (int k = 0; k < NV; ++k)
-    if (k * kT + (int)threadIdx.x < ld8) {
+  for (int k = 0; k < NV; ++k) {
+    const F8 f = unpack8(x[k]);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s += __expf(x[k].v[e] - m);
-    }
-  s = block_sum(s, sh);
+    for (int e = 0; e < 8; ++e) s += __expf(f.v[e] - m);
+  }
+  TW_KEEP_PACKED;
+#undef TW_KEEP_PACKED
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) sh[1][wave] = s;
+  __syncthreads();
+  s = sh[1][0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) s += sh[1][i];
   const float lse = m + logf(s);
   const int tgt = targets[blockIdx.x];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    const int idx = k * kT + threadIdx.x;
-    if (idx < ld8) {
+    const int idx = k * NT + threadIdx.x;
+    if (idx < ld8 && (GRAD || idx == tgt >> 3)) {
+      const F8 f = unpack8(x[k]);
       F8 g;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int c = idx * 8 + e;
-        if (c == tgt) rowloss[blockIdx.x] = lse - x[k].v[e];
-        g.v[e] = c < V ? (__expf(x[k].v[e] - lse) - (c == tgt ? 1.f : 0.f)) * inv_T : 0.f;
+        if (c == tgt) rowloss[blockIdx.x] = lse - f.v[e];
+        g.v[e] = c < V ? (__expf(f.v[e] - lse) - (c == tgt ? 1.f : 0.f)) * inv_T : 0.f;
       }
-      row[idx] = pack8(g);
+      if (GRAD) row[idx] = pack8(g);
     }
   }
 }
 
 // The same for rows of any length (row stride a multiple of 8): one vectorised pass keeps a running maximum and a
 // sum of exponentials relative to it, a second pass re-reads the row (it is still in the L2) and writes the gradient.
+template <bool GRAD>
 __global__ __launch_bounds__(kT) void ce_vec_long_kernel(u32x4v *logits, int64_t ld8, const int32_t *targets, float *rowloss, int V, float inv_T) {
   __shared__ float sh[4];
   u32x4v *row = logits + (int64_t)blockIdx.x * ld8;
@@ -549,15 +576,16 @@ __global__ __launch_bounds__(kT) void ce_vec_long_kernel(u32x4v *logits, int64_t
   s = block_sum(m == -INFINITY ? 0.f : s * __expf(m - M), sh);
   const float lse = M + logf(s);
   const int tgt = targets[blockIdx.x];
-  for (int idx = threadIdx.x; idx < ld8; idx += kT) {
+  for (int64_t idx = GRAD ? threadIdx.x : threadIdx.x == 0 && tgt >= 0 ? tgt >> 3 : ld8; idx < ld8; idx += kT) {
     const F8 x = unpack8(row[idx]);
     F8 g;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int c = idx * 8 + e;
+      const int c = (int)idx * 8 + e;
       if (c == tgt) rowloss[blockIdx.x] = lse - x.v[e];
       g.v[e] = c < V ? (__expf(x.v[e] - lse) - (c == tgt ? 1.f : 0.f)) * inv_T : 0.f;
     }
+    if (!GRAD) break;
     row[idx] = pack8(g);
   }
 }
@@ -896,15 +924,30 @@ twist_status twist_act_bwd(twist_ctx *ctx, int bf16, int act, const void *gu, co
   return TWIST_OK;
 }
 
-twist_status twist_ce_fwd_bwd(twist_ctx *ctx, int bf16, void *logits, int64_t ld, const int32_t *targets, float *rowloss, float *loss, int T, int V) {
+twist_status twist_ce_fwd_bwd(twist_ctx *ctx, int bf16, void *logits, int64_t ld, const int32_t *targets, float *rowloss, float *loss, int T, int V, bool grad) {
+  const float inv_T = 1.f / (float)T;
+#define TW_CE(KERNEL, GRAD, THREADS, ...) hipLaunchKernelGGL((KERNEL<__VA_ARGS__ GRAD>), dim3(T), dim3(THREADS), 0, ctx->stream, lv, LD, targets, rowloss, V, inv_T)
+#define TW_CE2(KERNEL, THREADS, ...)                        \
+  do {                                                      \
+    if (grad) TW_CE(KERNEL, true, THREADS, __VA_ARGS__);    \
+    else TW_CE(KERNEL, false, THREADS, __VA_ARGS__);        \
+  } while (0)
   if (bf16 && ld % 8 == 0 && al16(logits)) {
     u32x4v *lv = static_cast<u32x4v *>(logits);
-    if (ld <= 4 * 2048) hipLaunchKernelGGL(ce_vec_kernel<4>, dim3(T), dim3(kT), 0, ctx->stream, lv, ld / 8, targets, rowloss, V, 1.f / (float)T);
-    else if (ld <= 16 * 2048) hipLaunchKernelGGL(ce_vec_kernel<16>, dim3(T), dim3(kT), 0, ctx->stream, lv, ld / 8, targets, rowloss, V, 1.f / (float)T);
-    else hipLaunchKernelGGL(ce_vec_long_kernel, dim3(T), dim3(kT), 0, ctx->stream, lv, ld / 8, targets, rowloss, V, 1.f / (float)T);
-  } else
-    LAUNCH_BF(ce_kernel, bf16, dim3(T), dim3(kT), logits, ld, targets, rowloss, V, 1.f / (float)T);
-  hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kT), 0, ctx->stream, rowloss, (int64_t)T, 1.f / (float)T, loss);
+    const int64_t LD = ld / 8;
+    if (ld <= 4 * 2048) TW_CE2(ce_vec_kernel, kT, 4, kT,);
+    else if (ld <= 16 * 2048) TW_CE2(ce_vec_kernel, kT, 16, kT,);
+    else if (ld <= 16 * 4096) TW_CE2(ce_vec_kernel, 512, 16, 512,);
+    else TW_CE2(ce_vec_long_kernel, kT, );
+  } else {
+    void *lv = logits;
+    const int64_t LD = ld;
+    if (bf16) TW_CE2(ce_kernel, kT, 1,);
+    else TW_CE2(ce_kernel, kT, 0,);
+  }
+#undef TW_CE2
+#undef TW_CE
+  hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kT), 0, ctx->stream, rowloss, (int64_t)T, inv_T, loss);
   TW_HIP(ctx, hipGetLastError());
   return TWIST_OK;
 }

@@ -332,7 +332,7 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     TW_TRY(twist_norm_fwd(ctx, bf, rms, w.xs[2 * l], P(L.at(l, TWIST_NORM1_W)), P(L.at(l, TWIST_NORM1_B)), b.h1, w.stats[2 * l], T, D, d.norm_eps));
     TW_TRY(gemm(GEMM_NT, T, 3 * HD, D, b.h1, D, PW(l, TWIST_WQ), D, b.qkv, 3 * HD, 0, 1.f, PW(l, TWIST_BQ)));
     if (d.use_rope) TW_TRY(twist_rope_apply(ctx, bf, b.qkv, w.rope_tab, B, N, Hs, dh, 1.f));
-    TW_TRY(twist_attention_fwd(ctx, bf, b.qkv, b.o, b.o32, b.lse, B, N, Hs, dh, keep_of(l, TWIST_KIND_HEAD)));
+    TW_TRY(twist_attention_fwd(ctx, bf, b.qkv, b.o, forward_only ? nullptr : b.o32, b.lse, B, N, Hs, dh, keep_of(l, TWIST_KIND_HEAD)));
     if (um) TW_TRY(gemm(GEMM_NN, T, D, HD, b.o, HD, PW(l, TWIST_WO), D, w.xs[2 * l + 1], D, 1, c_a, P(L.at(l, TWIST_BO)), w.xs[2 * l]));
     else TW_TRY(gemm(GEMM_NT, T, D, HD, b.o, HD, PW(l, TWIST_WO), HD, w.xs[2 * l + 1], D, 1, c_a, P(L.at(l, TWIST_BO)), w.xs[2 * l]));
     TW_TRY(twist_norm_fwd(ctx, bf, rms, w.xs[2 * l + 1], P(L.at(l, TWIST_NORM2_W)), P(L.at(l, TWIST_NORM2_B)), b.h2, w.stats[2 * l + 1], T, D, d.norm_eps));
@@ -351,7 +351,7 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     TW_TRY(twist_norm_fwd(ctx, bf, rms, x_last, P(L.global[TWIST_FINAL_NORM_W]), P(L.global[TWIST_FINAL_NORM_B]), w.hf, w.stats[2 * d.n_layers], T, D,
                           d.norm_eps));
     TW_TRY(gemm(GEMM_NT, T, V, D, w.hf, D, P(wout), D, w.logits, w.ld_logits, 0));
-    TW_TRY(twist_ce_fwd_bwd(ctx, bf, w.logits, w.ld_logits, static_cast<const int32_t *>(targets), w.rowloss, loss_dev, T, V));
+    TW_TRY(twist_ce_fwd_bwd(ctx, bf, w.logits, w.ld_logits, static_cast<const int32_t *>(targets), w.rowloss, loss_dev, T, V, !forward_only));
     if (forward_only) return TWIST_OK;
     // projection weight gradient, then the gradient flowing back into the final norm
     TW_TRY(gemm(GEMM_TN, V, D, T, w.logits, w.ld_logits, w.hf, D, G(wout), D, 1));

@@ -108,9 +108,9 @@ def test_activation_forward_backward_and_neuron_mask(lib, dtype, act, T, F, unit
     assert not dm[:, ~on2].any() and np.array_equal(dm[:, on2], dgu[:, on2])
 
 
-# vocabulary: 515 and 1003 (rows held in registers, 4 vectors per lane), 32000 (16 vectors), 33001 (re-read kernel); the
+# vocabulary: 515 and 1003 (rows held in registers, 4 vectors per lane), 32000 (16 vectors), 33001 to 65536 (16 vectors, 512 threads), 70001 (re-read kernel); the
 # row stride is the vocabulary rounded up to 8, as in the training pass; 301 with fp32 takes the general kernel
-@pytest.mark.parametrize("dtype,V,T", [(BF, 515, 37), (BF, 1003, 8), (BF, 32000, 6), (BF, 33001, 5), (F32, 301, 37), (F32, 1003, 5)])
+@pytest.mark.parametrize("dtype,V,T", [(BF, 515, 37), (BF, 1003, 8), (BF, 32000, 6), (BF, 33001, 5), (BF, 50257, 3), (BF, 65536, 2), (BF, 70001, 2), (F32, 301, 37), (F32, 1003, 5)])
 def test_cross_entropy_loss_and_gradient(lib, dtype, V, T):
     cfg = si.ModelCfg(d_model=64, n_heads=1, d_head=8, d_ff=8, vocab=V, dtype=dtype)
     ctx = lib.Context(lib.desc_from_cfg(cfg))
