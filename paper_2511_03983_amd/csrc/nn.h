@@ -70,9 +70,10 @@ twist_status twist_norm_fwd(twist_ctx *ctx, int bf16, int rms, const float *x, c
 // dw, db (fp32, overwritten; db may be null); partial: scratch of at least norm_partial_floats(T, D).
 // With defer_reduce the per-chunk partial sums are left in `partial` and dw/db are not written: the caller later sums
 // many such buffers with one twist_col_reduce_batch launch (items {partial, dw, 2 D, D, 1} and {partial + D, db, 2 D, D, 1};
-// same summation order, hence the same bits).
+// same summation order, hence the same bits).  csum (may be null): per-chunk column sums of dxb, as twist_colsum defers them.
 twist_status twist_norm_bwd(twist_ctx *ctx, int bf16, int rms, const void *dy, const float *x, const void *w, const float *stats, float *dx,
-                            int accumulate, void *dxb, float *dw, float *db, float *partial, int T, int D, bool defer_reduce = false);
+                            int accumulate, void *dxb, float *dw, float *db, float *partial, int T, int D, bool defer_reduce = false,
+                            float *csum = nullptr);
 size_t twist_norm_partial_floats(int T, int D);
 // One deferred column reduction: out[c] = alpha * sum over the T/16-row chunks k of partial[k * stride + c], c < n.
 struct ColReduce {

@@ -307,11 +307,17 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
   // gradients are left as per-chunk partial sums in the layer's own block and summed for all layers by one launch at
   // the end of the pass, which takes 2 n_layers small kernels off the chain of dependent kernels.
   std::vector<ColReduce> reduce_items;
-  auto norm_bwd = [&](int idx, const void *dy, const float *x, const void *nw, int accumulate, void *dxb, float *dw, float *db) {
+  // Per-chunk column sums behind the bias gradients, reduced with everything else at the end; layer l's block: FFN down and attention
+  // output (the residual gradient's sums, formed by the norm backward that produces it), then FFN up, then q/k/v.
+  const size_t sum_d = twist_colsum_partial_floats(T, D);
+  auto down_sums = [&](int l) { return l >= 0 && L.at(l, TWIST_B_DOWN).off >= 0 ? w.bias_partial + (size_t)l * w.bias_partial_stride : nullptr; };
+  auto out_sums = [&](int l) { return L.at(l, TWIST_BO).off >= 0 ? w.bias_partial + (size_t)l * w.bias_partial_stride + sum_d : nullptr; };
+  // csum: where the column sums of the activation-type copy go (the next projection's bias gradient), or null.
+  auto norm_bwd = [&](int idx, const void *dy, const float *x, const void *nw, int accumulate, void *dxb, float *dw, float *db, float *csum) {
     float *part = w.norm_partial + (size_t)idx * w.norm_partial_stride;
     reduce_items.push_back({part, dw, 2 * (int64_t)D, D, 1.f});
     if (db) reduce_items.push_back({part + D, db, 2 * (int64_t)D, D, 1.f});
-    return twist_norm_bwd(ctx, bf, rms, dy, x, nw, w.stats[idx], w.dx, accumulate, dxb, dw, db, part, T, D, true);
+    return twist_norm_bwd(ctx, bf, rms, dy, x, nw, w.stats[idx], w.dx, accumulate, dxb, dw, db, part, T, D, true, csum);
   };
 
   // ------------------------------------------------------------------------------------ forward
@@ -365,10 +371,11 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
       TW_TRY(twist_gemm(ctx, bf, GEMM_NN, T, D, V, w.logits, w.ld_logits, P(wout), D, D, e));
     }
     TW_TRY(norm_bwd(2 * d.n_layers, w.dh, x_last, P(L.global[TWIST_FINAL_NORM_W]), 0, w.dxb, G(L.global[TWIST_FINAL_NORM_W]),
-                    G(L.global[TWIST_FINAL_NORM_B])));
+                    G(L.global[TWIST_FINAL_NORM_B]), down_sums(d.n_layers - 1)));
   } else {
     TW_TRY(twist_mse_fwd_bwd(ctx, bf, x_last, targets, w.dx, w.dxb, w.rowloss, loss_dev, (int64_t)T * D));
     if (forward_only) return TWIST_OK;
+    if (float *sums = down_sums(d.n_layers - 1)) TW_TRY(twist_colsum(ctx, bf, w.dxb, D, 1.f, nullptr, sums, T, D, true));
   }
 
   // ------------------------------------------------------------------------------------ backward through the layers
@@ -389,15 +396,15 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     TW_TRY(gather_layer(l));
     const int w1 = nf == 2 ? TWIST_W_GATE : TWIST_W_UP;
     // FFN branch: y = c_f (a W_down^T + b_down)
-    // bias gradients: per-chunk column sums now (into this layer's block), reduced with everything else at the end
-    float *bias_part = w.bias_partial + (size_t)l * w.bias_partial_stride;
-    auto bias_grad = [&](const void *src, int64_t ld, float alpha, float *out, int n) {
+    // bias gradients of the partitioned biases: per-chunk column sums now, reduced with everything else at the end
+    float *bias_part = w.bias_partial + (size_t)l * w.bias_partial_stride + 2 * sum_d;
+    auto bias_grad = [&](const void *src, int64_t ld, float *out, int n) {
       float *part = bias_part;
       bias_part += twist_colsum_partial_floats(T, n);
-      reduce_items.push_back({part, out, (int64_t)n, n, alpha});
-      return twist_colsum(ctx, bf, src, ld, alpha, out, part, T, n, true);
+      reduce_items.push_back({part, out, (int64_t)n, n, 1.f});
+      return twist_colsum(ctx, bf, src, ld, 1.f, out, part, T, n, true);
     };
-    if (L.at(l, TWIST_B_DOWN).off >= 0) TW_TRY(bias_grad(gx, D, c_f, G(L.at(l, TWIST_B_DOWN)), D));
+    if (float *sums = down_sums(l)) reduce_items.push_back({sums, G(L.at(l, TWIST_B_DOWN)), (int64_t)D, D, c_f});
     TW_TRY(side.fork(0));
     if (um) TW_TRY(wgrad(F, D, b.a, F, gx, D, GW(l, TWIST_W_DOWN), c_f));
     else TW_TRY(wgrad(D, F, gx, D, b.a, F, GW(l, TWIST_W_DOWN), c_f));
@@ -407,16 +414,16 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     else TW_TRY(gemm(GEMM_NN, T, F, D, gx, D, PW(l, TWIST_W_DOWN), F, w.da, F, 0, c_f));
     TW_TRY(side.wait_done(1));
     TW_TRY(twist_act_bwd(ctx, bf, d.act, b.gu, w.da, w.dgu, T, F, keep_of(l, TWIST_KIND_FFN), d.ffn_granule));
-    if (L.at(l, TWIST_B_UP).off >= 0) TW_TRY(bias_grad(w.dgu, nf * F, 1.f, GW(l, TWIST_B_UP), nf * F));
+    if (L.at(l, TWIST_B_UP).off >= 0) TW_TRY(bias_grad(w.dgu, nf * F, GW(l, TWIST_B_UP), nf * F));
     TW_TRY(side.fork(1));
     TW_TRY(wgrad(nf * F, D, w.dgu, nf * F, b.h2, D, GW(l, w1), 1.f));
     TW_TRY(expand(side.stream(), l, 1u << TWIST_W_GATE | 1u << TWIST_W_UP, w.cg, 0));
     TW_TRY(side.done(1));
     TW_TRY(gemm(GEMM_NN, T, D, nf * F, w.dgu, nf * F, PW(l, w1), D, w.dh, D, 0));
     TW_TRY(side.wait_done(2));
-    TW_TRY(norm_bwd(2 * l + 1, w.dh, w.xs[2 * l + 1], P(L.at(l, TWIST_NORM2_W)), 1, gx_other, G(L.at(l, TWIST_NORM2_W)), G(L.at(l, TWIST_NORM2_B))));
+    TW_TRY(norm_bwd(2 * l + 1, w.dh, w.xs[2 * l + 1], P(L.at(l, TWIST_NORM2_W)), 1, gx_other, G(L.at(l, TWIST_NORM2_W)), G(L.at(l, TWIST_NORM2_B)), out_sums(l)));
     // attention branch: y = c_a (o C_attn^T + b_o)
-    if (L.at(l, TWIST_BO).off >= 0) TW_TRY(bias_grad(gx_other, D, c_a, G(L.at(l, TWIST_BO)), D));
+    if (float *sums = out_sums(l)) reduce_items.push_back({sums, G(L.at(l, TWIST_BO)), (int64_t)D, D, c_a});
     TW_TRY(side.fork(2));
     if (um) TW_TRY(wgrad(HD, D, b.o, HD, gx_other, D, GW(l, TWIST_WO), c_a));
     else TW_TRY(wgrad(D, HD, gx_other, D, b.o, HD, GW(l, TWIST_WO), c_a));
@@ -427,14 +434,14 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     TW_TRY(side.wait_done(3));
     TW_TRY(twist_attention_bwd(ctx, bf, b.qkv, bf ? b.o32 : static_cast<const float *>(b.o), w.dout, b.lse, w.delta, w.dqkv, B, N, Hs, dh, d.use_rope ? w.rope_tab : nullptr,
                                keep_of(l, TWIST_KIND_HEAD)));
-    if (L.at(l, TWIST_BQ).off >= 0) TW_TRY(bias_grad(w.dqkv, 3 * HD, 1.f, GW(l, TWIST_BQ), 3 * HD));
+    if (L.at(l, TWIST_BQ).off >= 0) TW_TRY(bias_grad(w.dqkv, 3 * HD, GW(l, TWIST_BQ), 3 * HD));
     TW_TRY(side.fork(3));
     TW_TRY(wgrad(3 * HD, D, w.dqkv, 3 * HD, b.h1, D, GW(l, TWIST_WQ), 1.f));
     TW_TRY(expand(side.stream(), l, 1u << TWIST_WQ | 1u << TWIST_WK | 1u << TWIST_WV, w.cg, 0));
     TW_TRY(side.done(3));
     TW_TRY(gemm(GEMM_NN, T, D, 3 * HD, w.dqkv, 3 * HD, PW(l, TWIST_WQ), D, w.dh, D, 0));
     TW_TRY(side.wait_done(0));
-    TW_TRY(norm_bwd(2 * l, w.dh, w.xs[2 * l], P(L.at(l, TWIST_NORM1_W)), 1, gx, G(L.at(l, TWIST_NORM1_W)), G(L.at(l, TWIST_NORM1_B))));
+    TW_TRY(norm_bwd(2 * l, w.dh, w.xs[2 * l], P(L.at(l, TWIST_NORM1_W)), 1, gx, G(L.at(l, TWIST_NORM1_W)), G(L.at(l, TWIST_NORM1_B)), down_sums(l - 1)));
   }
   TW_TRY(twist_col_reduce_batch(ctx, reduce_items.data(), (int)reduce_items.size(), T));
   if (d.has_bias)

@@ -51,6 +51,10 @@ CASES = {
     # ReLU, the activation of the paper's analysis (Appendix A.1): scalar kernels (fp32, odd widths) and the 16-byte bf16 kernels
     "gpt_relu_f32": (si.ModelCfg(n_layers=2, d_model=96, n_heads=6, d_head=16, d_ff=200, vocab=301, max_seq=40, act="relu"), 3, 3, 100, 3, 37),
     "gpt_relu_bf16": (replace(si.CFG2, n_layers=2, d_model=256, n_heads=4, d_head=64, d_ff=1024, vocab=1003, max_seq=192, act="relu"), 2, 2, 512, 2, 192),
+    # rows of 3 x 256 and 8 x 256 elements, a last chunk of 5 rows: the bias gradients formed by the norm backward, and beside it
+    "block_gpt_bf16_d768": (si.ModelCfg(n_layers=2, d_model=768, n_heads=2, d_head=32, d_ff=64, vocab=0, max_seq=37, dtype="bf16"), 2, 1, 32, 1, 37),
+    "block_gpt_f32_d768": (si.ModelCfg(n_layers=2, d_model=768, n_heads=2, d_head=32, d_ff=64, vocab=0, max_seq=37), 2, 1, 32, 1, 37),
+    "block_gpt_f32_d2048": (si.ModelCfg(n_layers=2, d_model=2048, n_heads=2, d_head=32, d_ff=64, vocab=0, max_seq=21), 2, 1, 32, 1, 21),
     "block_relu_bf16_odd": (si.ModelCfg(n_layers=1, d_model=72, n_heads=3, d_head=8, d_ff=52, vocab=0, max_seq=24, act="relu", dtype="bf16"), 2, 2, 27, 3, 24),
 }
 # a seeded sweep of bf16 models with awkward widths (projection edges, attention with and without the tiled kernels)
