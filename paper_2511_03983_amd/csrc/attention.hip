@@ -190,8 +190,7 @@ twist_status twist_attention_fwd(twist_ctx *ctx, int bf16, const void *qkv, void
     TW_TRY(twist_attention_fwd_mfma(ctx, qkv, o, o32, lse, B, N, Hs, dh, keep, &done));
     if (done) return TWIST_OK;
   }
-  if (!bf16 && twist_attention_f32_ok(ctx, qkv, o, o, o, dh))
-    return twist_attention_f32_fwd(ctx, static_cast<const float *>(qkv), static_cast<float *>(o), lse, B, N, Hs, dh, keep);
+  if (twist_attention_f32_ok(ctx, qkv, o, bf16 ? o32 : o, o, dh)) return twist_attention_f32_fwd(ctx, bf16, qkv, o, bf16 ? o32 : nullptr, lse, B, N, Hs, dh, keep);
   dim3 grid((unsigned)(((int64_t)B * Hs * N + 3) / 4)), block(256);
   if (bf16) hipLaunchKernelGGL(attn_fwd_plain<1>, grid, block, 0, ctx->stream, qkv, o, lse, B, N, Hs, dh, scale, keep);
   else hipLaunchKernelGGL(attn_fwd_plain<0>, grid, block, 0, ctx->stream, qkv, o, lse, B, N, Hs, dh, scale, keep);
@@ -209,8 +208,8 @@ twist_status twist_attention_bwd(twist_ctx *ctx, int bf16, const void *qkv, cons
     TW_TRY(twist_attention_bwd_mfma(ctx, qkv, o_f32, dout, lse, delta, dqkv, B, N, Hs, dh, rope_tab, keep, &done, &rope_done));
     if (done) return (rope_tab && !rope_done) ? twist_rope_apply(ctx, bf16, dqkv, rope_tab, B, N, Hs, dh, -1.f) : TWIST_OK;
   }
-  if (!bf16 && o_f32 && twist_attention_f32_ok(ctx, qkv, o_f32, dout, dqkv, dh)) {
-    TW_TRY(twist_attention_f32_bwd(ctx, static_cast<const float *>(qkv), o_f32, static_cast<const float *>(dout), lse, delta, static_cast<float *>(dqkv), B, N, Hs, dh, keep));
+  if (o_f32 && twist_attention_f32_ok(ctx, qkv, o_f32, dout, dqkv, dh)) {
+    TW_TRY(twist_attention_f32_bwd(ctx, bf16, qkv, o_f32, dout, lse, delta, dqkv, B, N, Hs, dh, keep));
   } else if (bf16) {
     hipLaunchKernelGGL(attn_bwd_dq_plain<1>, grid, block, 0, ctx->stream, qkv, dout, lse, delta, dqkv, B, N, Hs, dh, scale, keep);
     hipLaunchKernelGGL(attn_bwd_dkv_plain<1>, grid, block, 0, ctx->stream, qkv, dout, lse, delta, dqkv, B, N, Hs, dh, scale, keep);
@@ -234,7 +233,9 @@ extern "C" twist_status twist_attention_raw(twist_ctx *ctx, const void *qkv, con
       if (ctx->d.d_head % 2) TW_FAIL(ctx, TWIST_ESHAPE, "twist_attention_raw: rotary positions need an even d_head");
       TW_TRY(twist_rope_table(ctx, rope_tab, N, ctx->d.d_head, ctx->d.rope_theta));
     }
-    TW_TRY(twist_attention_bwd(ctx, bf, qkv, bf ? o32 : static_cast<const float *>(o), dout, lse, delta, dqkv, B, N, Hs, ctx->d.d_head, rope_tab, keep));
+    // (a bf16 output that is not 16-byte aligned was computed by the plain kernel, which leaves o32 alone)
+    const float *o_f32 = !bf ? static_cast<const float *>(o) : reinterpret_cast<uintptr_t>(o) % 16 ? nullptr : o32;
+    TW_TRY(twist_attention_bwd(ctx, bf, qkv, o_f32, dout, lse, delta, dqkv, B, N, Hs, ctx->d.d_head, rope_tab, keep));
   }
   return TWIST_OK;
 }

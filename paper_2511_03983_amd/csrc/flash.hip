@@ -927,13 +927,13 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
 
 }  // namespace dl
 
-// The pipelined kernels cover d_head 32, 64 and 128 and any N; they address a whole batch element through one 32-bit buffer
-// range.  Longer ones (and the staged_attention test switch) run the register-staged kernels: d_head 64 or 128, N % 128 == 0.
+// The tiled kernels take d_head 64 or 128 and N % 128 == 0.  (They hand probabilities and score gradients to the matrix cores in bf16;
+// every other form has always been computed with those in fp32, and is by flash_f32.hip.)  The pipelined ones address a
+// whole batch element through one 32-bit buffer range; longer ones (and the staged_attention test switch) run the register-staged ones.
 enum Family { FAM_NONE, FAM_STAGED, FAM_DL };
 Family family(const twist_ctx *ctx, const void *a, const void *b, int N, int Hs, int dh) {
-  if (ctx->plain_only || (reinterpret_cast<uintptr_t>(a) % 16) || (reinterpret_cast<uintptr_t>(b) % 16)) return FAM_NONE;
-  if (!ctx->staged_attention && (dh == 32 || dh == 64 || dh == 128) && (int64_t)N * 3 * Hs * dh * 2 < (1ll << 31)) return FAM_DL;
-  return (dh == 64 || dh == 128) && N % 128 == 0 ? FAM_STAGED : FAM_NONE;
+  if (ctx->plain_only || !(dh == 64 || dh == 128) || N % 128 || (reinterpret_cast<uintptr_t>(a) % 16) || (reinterpret_cast<uintptr_t>(b) % 16)) return FAM_NONE;
+  return !ctx->staged_attention && (int64_t)N * 3 * Hs * dh * 2 < (1ll << 31) ? FAM_DL : FAM_STAGED;
 }
 
 }  // namespace
@@ -942,8 +942,7 @@ Family family(const twist_ctx *ctx, const void *a, const void *b, int N, int Hs,
 #define TW_BY_DH(dh, expr)                                \
   do {                                                    \
     if ((dh) == 128) { constexpr int DH = 128; expr; }    \
-    else if ((dh) == 64) { constexpr int DH = 64; expr; } \
-    else { constexpr int DH = 32; expr; }                 \
+    else { constexpr int DH = 64; expr; }                 \
   } while (0)
 
 twist_status twist_attention_fwd_mfma(twist_ctx *ctx, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep,

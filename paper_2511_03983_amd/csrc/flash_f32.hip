@@ -1,5 +1,6 @@
-// Tiled causal attention for fp32 models on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32), forward and backward,
-// d_head a multiple of 4 up to 128, any N.
+// Tiled causal attention in fp32 arithmetic on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32), forward and backward,
+// d_head a multiple of 4 up to 128, any N: for fp32 models, and (BF) for the bf16 models whose heads or sequence lengths the bf16 tiles
+// of flash.hip do not take: operands and results are bf16 there, probabilities and score gradients stay fp32.
 //
 // A workgroup owns 32 query rows (forward, dQ) or 32 key rows (dK / dV) of one head; its four waves share out the tiles of 32 keys
 // (or queries) that those rows see, wave w taking tiles w, w + 4, ..., each with accumulators of its own, and the four results are
@@ -15,25 +16,46 @@
 // every query, and queries beyond N get probability zero.
 //
 // Measured (forward / dQ / dK dV) on 2 x 512 tokens, 6 heads of 64: 20 / 30 / 37 us against 423 / 905 / 427 us of the plain kernels
-// (a wave per row, a wave reduction per score), and closer to exact arithmetic (query / key gradients 5e-6 against 3e-5).
+// (a wave per row, a wave reduction per score), and closer to exact arithmetic (query / key gradients 5e-6 against 3e-5).  bf16,
+// 3 x 1000 tokens, 7 heads of 128: 132 / 189 / 310 us against 2633 / 3596 / 1945, with the same error against 64 bits (1.6e-3, the rounding of the results; bf16
+// tiles, at 27 / 46 / 60 us, have 2.0e-3 and in the gradients 2.4e-3).
 #include "nn.h"
 
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32((a), (b), (c), 0, 0, 0)
 
+// element type of the operands and results
+template <int BF> struct El { using T = float; };
+template <> struct El<1> { using T = uint16_t; };
+__device__ __forceinline__ float get(const float *p) { return *p; }
+__device__ __forceinline__ float get(const uint16_t *p) { return __uint_as_float((uint32_t)*p << 16); }
+__device__ __forceinline__ f32x4 get4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+__device__ __forceinline__ f32x4 get4(const uint16_t *p) {
+  const u32x2 u = *reinterpret_cast<const u32x2 *>(p);
+  return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
+}
+__device__ __forceinline__ void put4(float *p, const f32x4 &v) { *reinterpret_cast<f32x4 *>(p) = v; }
+__device__ __forceinline__ void put4(uint16_t *p, const f32x4 &v) {  // round to nearest even
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const f32x2 a = {v[0], v[1]}, b = {v[2], v[3]};
+  *reinterpret_cast<u32x2 *>(p) = u32x2{__builtin_bit_cast(uint32_t, __builtin_convertvector(a, bf16x2)), __builtin_bit_cast(uint32_t, __builtin_convertvector(b, bf16x2))};
+}
+
 // one row's values for the contraction along d_head: group u holds columns 8 u + 4 g .. + 3 (zeros beyond dh)
-template <int DH>
-__device__ __forceinline__ void load_row(f32x4 (&f)[DH / 8], const float *row, int dh, int g) {
+template <int DH, class T>
+__device__ __forceinline__ void load_row(f32x4 (&f)[DH / 8], const T *row, int dh, int g) {
 #pragma unroll
   for (int u = 0; u < DH / 8; ++u) {
     const int k = 8 * u + 4 * g;
-    f[u] = k < dh ? *reinterpret_cast<const f32x4 *>(row + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+    f[u] = k < dh ? get4(row + k) : f32x4{0.f, 0.f, 0.f, 0.f};
   }
 }
 // 32 x 32 tile of A B^T along d_head: `a` = this lane's row of A, `b` = this lane's column
@@ -49,15 +71,15 @@ __device__ __forceinline__ f32x16 dot_tile(const f32x4 (&a)[DH / 8], const f32x4
   return s;
 }
 // acc[i] += X^T[32 i ..][rows] w[rows][column]: X rows row0 .. row0 + 31 (clamped to N - 1), w in accumulator layout
-template <int DH>
-__device__ __forceinline__ void add_tile(f32x16 (&acc)[DH / 32], const float *x, int64_t ld, int row0, int N, int dh, const f32x16 &w, int c, int g) {
+template <int DH, class T>
+__device__ __forceinline__ void add_tile(f32x16 (&acc)[DH / 32], const T *x, int64_t ld, int row0, int N, int dh, const f32x16 &w, int c, int g) {
 #pragma unroll
   for (int i = 0; i < DH / 32; ++i) {
     if (32 * i >= dh) break;
     const int col = min(32 * i + c, dh - 1);  // columns beyond dh give rows of the result that are not stored
     float v[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = x[(int64_t)min(row0 + 8 * (r >> 2) + 4 * g + (r & 3), N - 1) * ld + col];
+    for (int r = 0; r < 16; ++r) v[r] = get(x + (int64_t)min(row0 + 8 * (r >> 2) + 4 * g + (r & 3), N - 1) * ld + col);
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[i] = MFMA(v[r], w[r], acc[i]);
   }
@@ -70,9 +92,10 @@ __device__ __forceinline__ void zero(f32x16 (&acc)[DH / 32]) {
     for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
 }
 
-// Sum of the four waves' [dh][32] accumulators (each multiplied by its lane's `mul`) written as rows of `out` (stride ld)
-template <int DH>
-__device__ __forceinline__ void merge(float *lds, const f32x16 (&acc)[DH / 32], float mul, float *out, int64_t ld, int rows_left, int dh, int wave, int c, int g) {
+// Sum of the four waves' [dh][32] accumulators (each multiplied by its lane's `mul`) written as rows of `out` (stride ld) and, where it is
+// given, unrounded to out32
+template <int DH, class T>
+__device__ __forceinline__ void merge(float *lds, const f32x16 (&acc)[DH / 32], float mul, T *out, float *out32, int64_t ld, int rows_left, int dh, int wave, int c, int g) {
   constexpr int LDR = DH + 4;
 #pragma unroll
   for (int i = 0; i < DH / 32; ++i)
@@ -87,7 +110,8 @@ __device__ __forceinline__ void merge(float *lds, const f32x16 (&acc)[DH / 32], 
       f32x4 v = *reinterpret_cast<const f32x4 *>(lds + row * LDR + k);
 #pragma unroll
       for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f32x4 *>(lds + (w * 32 + row) * LDR + k);
-      *reinterpret_cast<f32x4 *>(out + row * ld + k) = v;
+      put4(out + row * ld + k, v);
+      if (out32) put4(out32 + row * ld + k, v);
     }
   __syncthreads();
 }
@@ -99,14 +123,14 @@ __device__ __forceinline__ Item item_of(int N, int Hs, bool late_first) {
   return {late_first ? nb - 1 - rank : rank, bh / Hs, bh % Hs};
 }
 
-template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const float *qkv, float *o, float *lse, int N, int Hs, int dh, float scale, const int32_t *keep) {
+template <int DH, int BF>
+__global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const typename El<BF>::T *qkv, typename El<BF>::T *o, float *o32, float *lse, int N, int Hs, int dh, float scale, const int32_t *keep) {
   __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
   __shared__ float ms[4][32], ls[4][32];
   const Item it = item_of(N, Hs, true);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
   const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
-  const float *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
+  const auto *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
   const int q0 = it.blk * 32, q = q0 + c;
   const float sc = scale * kLog2e;
   const bool masked = keep && keep[it.h] < 0;  // masked head (Masked TwIST, Section 4.1): no key is visited, zeros are written
@@ -147,17 +171,19 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const float *qkv, flo
   for (int w = 0; w < 4; ++w) lt += ls[w][c] * fast_exp2(ms[w][c] - mt);
   const float mul = masked ? 0.f : fast_exp2(m - mt) / lt;  // a wave without tiles has m = -inf: factor 0
   if (wave == 0 && g == 0 && q < N) lse[((int64_t)it.b * Hs + it.h) * N + q] = masked ? 0.f : (mt + log2f(lt)) * kLn2;
-  merge<DH>(lds, acc, mul, o + ((int64_t)it.b * N + q0) * HD + (int64_t)it.h * dh, HD, N - q0, dh, wave, c, g);
+  const int64_t at = ((int64_t)it.b * N + q0) * HD + (int64_t)it.h * dh;
+  merge<DH>(lds, acc, mul, o + at, o32 ? o32 + at : nullptr, HD, N - q0, dh, wave, c, g);
 }
 
-template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_dq_kernel(const float *qkv, const float *dout, const float *o, const float *lse, float *delta, float *dqkv, int N,
+template <int DH, int BF>
+__global__ __launch_bounds__(256) void attn_f32_dq_kernel(const typename El<BF>::T *qkv, const typename El<BF>::T *dout, const float *o, const float *lse, float *delta,
+                                                          typename El<BF>::T *dqkv, int N,
                                                           int Hs, int dh, float scale, const int32_t *keep) {
   __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
   const Item it = item_of(N, Hs, true);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
   const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
-  const float *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
+  const auto *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
   const int q0 = it.blk * 32, q = q0 + c, qr = min(q, N - 1);
   const float sc = scale * kLog2e;
   const int64_t row = ((int64_t)it.b * N + qr) * HD + (int64_t)it.h * dh, stat = ((int64_t)it.b * Hs + it.h) * N;
@@ -189,18 +215,19 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(const float *qkv, cons
     }
     add_tile<DH>(acc, kp, ld, kt * 32, N, dh, s, c, g);
   }
-  merge<DH>(lds, acc, 1.f, dqkv + ((int64_t)it.b * N + q0) * ld + (int64_t)it.h * dh, ld, N - q0, dh, wave, c, g);
+  merge<DH>(lds, acc, 1.f, dqkv + ((int64_t)it.b * N + q0) * ld + (int64_t)it.h * dh, nullptr, ld, N - q0, dh, wave, c, g);
 }
 
-template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const float *qkv, const float *dout, const float *lse, const float *delta, float *dqkv, int N, int Hs,
+template <int DH, int BF>
+__global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const typename El<BF>::T *qkv, const typename El<BF>::T *dout, const float *lse, const float *delta,
+                                                           typename El<BF>::T *dqkv, int N, int Hs,
                                                            int dh, float scale, const int32_t *keep) {
   __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
   const Item it = item_of(N, Hs, false);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
   const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
-  const float *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
-  const float *gp = dout + (int64_t)it.b * N * HD + (int64_t)it.h * dh;
+  const auto *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
+  const auto *gp = dout + (int64_t)it.b * N * HD + (int64_t)it.h * dh;
   const int k0 = it.blk * 32, kv = k0 + c, kr = min(kv, N - 1);
   const float sc = scale * kLog2e;
   const float *lse_b = lse + ((int64_t)it.b * Hs + it.h) * N, *del_b = delta + ((int64_t)it.b * Hs + it.h) * N;
@@ -229,9 +256,9 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const float *qkv, con
     add_tile<DH>(dv, gp, HD, q0, N, dh, s, c, g);
     add_tile<DH>(dk, qp, ld, q0, N, dh, dp, c, g);
   }
-  float *out = dqkv + ((int64_t)it.b * N + k0) * ld + HD + (int64_t)it.h * dh;
-  merge<DH>(lds, dk, 1.f, out, ld, N - k0, dh, wave, c, g);
-  merge<DH>(lds, dv, 1.f, out + HD, ld, N - k0, dh, wave, c, g);
+  auto *out = dqkv + ((int64_t)it.b * N + k0) * ld + HD + (int64_t)it.h * dh;
+  merge<DH>(lds, dk, 1.f, out, nullptr, ld, N - k0, dh, wave, c, g);
+  merge<DH>(lds, dv, 1.f, out + HD, nullptr, ld, N - k0, dh, wave, c, g);
 }
 
 bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -249,20 +276,35 @@ bool twist_attention_f32_ok(const twist_ctx *ctx, const void *qkv, const void *o
   return !ctx->plain_only && dh % 4 == 0 && dh <= 128 && al16(qkv) && al16(o) && al16(dout) && al16(dqkv);
 }
 
-twist_status twist_attention_f32_fwd(twist_ctx *ctx, const float *qkv, float *o, float *lse, int B, int N, int Hs, int dh, const int32_t *keep) {
+twist_status twist_attention_f32_fwd(twist_ctx *ctx, int bf16, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep) {
   const dim3 grid((unsigned)((int64_t)((N + 31) / 32) * B * Hs)), block(256);
   const float scale = 1.0f / sqrtf((float)dh);
-  TW_F32_DH(dh, hipLaunchKernelGGL(attn_f32_fwd_kernel<DH>, grid, block, 0, ctx->stream, qkv, o, lse, N, Hs, dh, scale, keep));
+  if (bf16)
+    TW_F32_DH(dh, hipLaunchKernelGGL((attn_f32_fwd_kernel<DH, 1>), grid, block, 0, ctx->stream, static_cast<const uint16_t *>(qkv), static_cast<uint16_t *>(o), o32, lse, N,
+                                     Hs, dh, scale, keep));
+  else
+    TW_F32_DH(dh, hipLaunchKernelGGL((attn_f32_fwd_kernel<DH, 0>), grid, block, 0, ctx->stream, static_cast<const float *>(qkv), static_cast<float *>(o), nullptr, lse, N, Hs,
+                                     dh, scale, keep));
   TW_HIP(ctx, hipGetLastError());
   return TWIST_OK;
 }
 
-twist_status twist_attention_f32_bwd(twist_ctx *ctx, const float *qkv, const float *o, const float *dout, const float *lse, float *delta, float *dqkv, int B, int N,
-                                     int Hs, int dh, const int32_t *keep) {
+template <int BF>
+static void launch_bwd(hipStream_t st, const void *qkv, const float *o, const void *dout, const float *lse, float *delta, void *dqkv, int B, int N, int Hs, int dh,
+                       const int32_t *keep) {
+  using T = typename El<BF>::T;
   const dim3 grid((unsigned)((int64_t)((N + 31) / 32) * B * Hs)), block(256);
   const float scale = 1.0f / sqrtf((float)dh);
-  TW_F32_DH(dh, hipLaunchKernelGGL(attn_f32_dq_kernel<DH>, grid, block, 0, ctx->stream, qkv, dout, o, lse, delta, dqkv, N, Hs, dh, scale, keep);
-            hipLaunchKernelGGL(attn_f32_dkv_kernel<DH>, grid, block, 0, ctx->stream, qkv, dout, lse, delta, dqkv, N, Hs, dh, scale, keep));
+  const T *x = static_cast<const T *>(qkv), *gout = static_cast<const T *>(dout);
+  T *dx = static_cast<T *>(dqkv);
+  TW_F32_DH(dh, hipLaunchKernelGGL((attn_f32_dq_kernel<DH, BF>), grid, block, 0, st, x, gout, o, lse, delta, dx, N, Hs, dh, scale, keep);
+            hipLaunchKernelGGL((attn_f32_dkv_kernel<DH, BF>), grid, block, 0, st, x, gout, lse, delta, dx, N, Hs, dh, scale, keep));
+}
+
+twist_status twist_attention_f32_bwd(twist_ctx *ctx, int bf16, const void *qkv, const float *o, const void *dout, const float *lse, float *delta, void *dqkv, int B, int N,
+                                     int Hs, int dh, const int32_t *keep) {
+  if (bf16) launch_bwd<1>(ctx->stream, qkv, o, dout, lse, delta, dqkv, B, N, Hs, dh, keep);
+  else launch_bwd<0>(ctx->stream, qkv, o, dout, lse, delta, dqkv, B, N, Hs, dh, keep);
   TW_HIP(ctx, hipGetLastError());
   return TWIST_OK;
 }

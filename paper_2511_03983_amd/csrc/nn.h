@@ -55,8 +55,8 @@ twist_status twist_attention_bwd(twist_ctx *ctx, int bf16, const void *qkv, cons
                                  void *dqkv, int B, int N, int Hs, int dh, const float *rope_tab, const int32_t *keep = nullptr);
 // the tiled fp32 kernels behind the two calls above, and whether they cover the operands
 bool twist_attention_f32_ok(const twist_ctx *ctx, const void *qkv, const void *o, const void *dout, const void *dqkv, int dh);
-twist_status twist_attention_f32_fwd(twist_ctx *ctx, const float *qkv, float *o, float *lse, int B, int N, int Hs, int dh, const int32_t *keep);
-twist_status twist_attention_f32_bwd(twist_ctx *ctx, const float *qkv, const float *o, const float *dout, const float *lse, float *delta, float *dqkv, int B, int N,
+twist_status twist_attention_f32_fwd(twist_ctx *ctx, int bf16, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep);
+twist_status twist_attention_f32_bwd(twist_ctx *ctx, int bf16, const void *qkv, const float *o, const void *dout, const float *lse, float *delta, void *dqkv, int B, int N,
                                      int Hs, int dh, const int32_t *keep);
 
 twist_status twist_embed_fwd(twist_ctx *ctx, int bf16, const int32_t *tok, const void *tok_embed, const void *pos_embed, float *x, int B, int N, int D, int vocab);
