@@ -388,7 +388,7 @@ __global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const uint16_t *qkv,
     }
 }
 
-// =========================================================================================== pipelined, any N
+// =========================================================================================== pipelined
 // Same decomposition, but the 64 x DH key / value (or query / dO) tiles of step t+1 travel from global memory
 // straight into LDS (buffer_load_dwordx4 ... lds, lane l of a wave writes 16 bytes at base + 16 l) while step t is
 // computed: two stages of two tiles, one barrier per step.  The fixed write pattern leaves no room for row
