@@ -13,7 +13,9 @@
 // is where accumulator register r sits.  Along d_head, MFMA 4 u + e contracts columns 8 u + 4 g + e: one 16-byte load per lane
 // feeds four instructions.
 // delta_i = dO_i . O_i from the fp32 output.  Rows beyond N are clamped when read and not stored; keys beyond N come after
-// every query, and queries beyond N get probability zero.
+// every query, and queries beyond N get probability zero.  An infinity or a NaN reaches what depends on it and nothing else: no
+// query sees a later key's, no key an earlier query's (add_tile).  That costs nothing that can be measured
+// (forward and backward of the first shape below: 80.3 us before, 78.6 since).
 //
 // Measured (forward / dQ / dK dV) on 2 x 512 tokens, 6 heads of 64: 20 / 30 / 37 us against 423 / 905 / 427 us of the plain kernels
 // (a wave per row, a wave reduction per score), and closer to exact arithmetic (query / key gradients 5e-6 against 3e-5).  bf16,
@@ -70,9 +72,13 @@ __device__ __forceinline__ f32x16 dot_tile(const f32x4 (&a)[DH / 8], const f32x4
     for (int e = 0; e < 4; ++e) s = MFMA(a[u][e], b[u][e], s);
   return s;
 }
-// acc[i] += X^T[32 i ..][rows] w[rows][column]: X rows row0 .. row0 + 31 (clamped to N - 1), w in accumulator layout
+// acc[i] += X^T[32 i ..][rows] w[rows][column]: X rows row0 .. row0 + 31 (those beyond N are taken as zero), w in accumulator layout.
+// `diag`: the tile lies on the diagonal, where a column does not see every row.  Hidden entries have weight zero, but zero times an
+// infinity or a NaN is a NaN, and it must not reach a column that never reads that row: such values are left out here, and if
+// there was one the weights are kept in `kept` (32 x 32 floats of LDS) and add_left_out() adds what the columns do see of them.
 template <int DH, class T>
-__device__ __forceinline__ void add_tile(f32x16 (&acc)[DH / 32], const T *x, int64_t ld, int row0, int N, int dh, const f32x16 &w, int c, int g) {
+__device__ __forceinline__ bool add_tile(f32x16 (&acc)[DH / 32], const T *x, int64_t ld, int row0, int N, int dh, const f32x16 &w, int c, int g, bool diag, float *kept) {
+  bool odd = false;
 #pragma unroll
   for (int i = 0; i < DH / 32; ++i) {
     if (32 * i >= dh) break;
@@ -80,8 +86,46 @@ __device__ __forceinline__ void add_tile(f32x16 (&acc)[DH / 32], const T *x, int
     float v[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[r] = get(x + (int64_t)min(row0 + 8 * (r >> 2) + 4 * g + (r & 3), N - 1) * ld + col);
+    if (row0 + 32 > N) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r] = row0 + 8 * (r >> 2) + 4 * g + (r & 3) < N ? v[r] : 0.f;
+    }
+    if (diag) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const bool ok = __builtin_isfinite(v[r]);
+        odd = odd || !ok;
+        v[r] = ok ? v[r] : 0.f;
+      }
+    }
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[i] = MFMA(v[r], w[r], acc[i]);
+  }
+  odd = __any(odd);
+  if (odd) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) kept[(8 * (r >> 2) + 4 * g + (r & 3)) * 32 + c] = w[r];
+  }
+  return odd;
+}
+// the infinities and NaNs of a diagonal tile (row0 = its first row), for the columns that see them
+template <int DH, class T, class Seen>
+__device__ __forceinline__ void add_left_out(f32x16 (&acc)[DH / 32], const T *x, int64_t ld, int row0, int N, int dh, int c, int g, const float *kept, Seen seen) {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // `kept` was written by this wave's other lanes
+#pragma unroll 1
+  for (int j = 0; j < 32 && row0 + j < N; ++j) {
+    if (!seen(row0 + j)) continue;
+    const float w = kept[j * 32 + c];
+#pragma unroll
+    for (int i = 0; i < DH / 32; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int col = 32 * i + 8 * k + 4 * g;
+        if (col >= dh) continue;
+        const f32x4 v = get4(x + (int64_t)(row0 + j) * ld + col);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][4 * k + e] += __builtin_isfinite(v[e]) ? 0.f : v[e] * w;
+      }
   }
 }
 template <int DH>
@@ -133,6 +177,8 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const typename El<BF>
   const auto *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
   const int q0 = it.blk * 32, q = q0 + c;
   const float sc = scale * kLog2e;
+  float *const kept = lds + wave * 32 * (DH + 4);  // the wave's part of the area that merge() uses afterwards
+  bool left_out = false;
   const bool masked = keep && keep[it.h] < 0;  // masked head (Masked TwIST, Section 4.1): no key is visited, zeros are written
   f32x4 qf[DH / 8], kf[DH / 8];
   load_row<DH>(qf, qp + (int64_t)min(q, N - 1) * ld, dh, g);
@@ -149,19 +195,20 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const typename El<BF>
       mx = fmaxf(mx, s[r]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m, mx * sc);  // finite: the tile's first key is visible to every query of the block
-    const float alpha = fast_exp2(m - mn);
+    const float mn = fmaxf(m, mx * sc), ref = mn == -INFINITY ? 0.f : mn;  // (all scores of the wave's tiles so far may be -inf: weights 0)
+    const float alpha = fast_exp2(m - ref);
     float sum = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { s[r] = fast_exp2(fmaf(s[r], sc, -mn)); sum += s[r]; }
+    for (int r = 0; r < 16; ++r) { s[r] = fast_exp2(fmaf(s[r], sc, -ref)); sum += s[r]; }
     l = l * alpha + sum;
     m = mn;
 #pragma unroll
     for (int i = 0; i < DH / 32; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][r] *= alpha;
-    add_tile<DH>(acc, vp, ld, kt * 32, N, dh, s, c, g);
+    left_out = add_tile<DH>(acc, vp, ld, kt * 32, N, dh, s, c, g, kt == it.blk, kept);
   }
+  if (left_out) add_left_out<DH>(acc, vp, ld, q0, N, dh, c, g, kept, [&](int key) { return key <= q; });  // (a wave's last tile: no rescaling since)
   l += __shfl_xor(l, 32, 64);
   if (g == 0) { ms[wave][c] = m; ls[wave][c] = l; }
   __syncthreads();
@@ -186,6 +233,8 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(const typename El<BF>:
   const auto *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
   const int q0 = it.blk * 32, q = q0 + c, qr = min(q, N - 1);
   const float sc = scale * kLog2e;
+  float *const kept = lds + wave * 32 * (DH + 4);  // the wave's part of the area that merge() uses afterwards
+  bool left_out = false;
   const int64_t row = ((int64_t)it.b * N + qr) * HD + (int64_t)it.h * dh, stat = ((int64_t)it.b * Hs + it.h) * N;
   const float L2 = lse[stat + qr] * kLog2e;
   f32x4 qf[DH / 8], gf[DH / 8], kf[DH / 8];
@@ -210,11 +259,12 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(const typename El<BF>:
     const f32x16 dp = dot_tile<DH>(kf, gf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float p = kt * 32 + 8 * (r >> 2) + 4 * g + (r & 3) > q ? 0.f : fast_exp2(fmaf(s[r], sc, -L2));
-      s[r] = p * (dp[r] - dl) * scale;
+      const float ds = fast_exp2(fmaf(s[r], sc, -L2)) * (dp[r] - dl) * scale;
+      s[r] = kt * 32 + 8 * (r >> 2) + 4 * g + (r & 3) > q ? 0.f : ds;
     }
-    add_tile<DH>(acc, kp, ld, kt * 32, N, dh, s, c, g);
+    left_out = add_tile<DH>(acc, kp, ld, kt * 32, N, dh, s, c, g, kt == it.blk, kept);
   }
+  if (left_out) add_left_out<DH>(acc, kp, ld, q0, N, dh, c, g, kept, [&](int key) { return key <= q; });
   merge<DH>(lds, acc, 1.f, dqkv + ((int64_t)it.b * N + q0) * ld + (int64_t)it.h * dh, nullptr, ld, N - q0, dh, wave, c, g);
 }
 
@@ -223,6 +273,7 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const typename El<BF>
                                                            typename El<BF>::T *dqkv, int N, int Hs,
                                                            int dh, float scale, const int32_t *keep) {
   __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
+  __shared__ float kept[2][32 * 32];  // wave 0's, which has the diagonal tile
   const Item it = item_of(N, Hs, false);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
   const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
@@ -230,6 +281,7 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const typename El<BF>
   const auto *gp = dout + (int64_t)it.b * N * HD + (int64_t)it.h * dh;
   const int k0 = it.blk * 32, kv = k0 + c, kr = min(kv, N - 1);
   const float sc = scale * kLog2e;
+  bool dv_left_out = false, dk_left_out = false;
   const float *lse_b = lse + ((int64_t)it.b * Hs + it.h) * N, *del_b = delta + ((int64_t)it.b * Hs + it.h) * N;
   const bool masked = keep && keep[it.h] < 0;
   f32x4 kf[DH / 8], vf[DH / 8], xf[DH / 8];
@@ -249,13 +301,17 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const typename El<BF>
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int q = q0 + 8 * (r >> 2) + 4 * g + (r & 3), qc = min(q, N - 1);
-      const float p = (q < kv || q >= N) ? 0.f : fast_exp2(fmaf(s[r], sc, -lse_b[qc] * kLog2e));
-      dp[r] = p * (dp[r] - del_b[qc]) * scale;
-      s[r] = p;
+      const float p = fast_exp2(fmaf(s[r], sc, -lse_b[qc] * kLog2e)), ds = p * (dp[r] - del_b[qc]) * scale;
+      const bool hidden = q < kv || q >= N;
+      dp[r] = hidden ? 0.f : ds;
+      s[r] = hidden ? 0.f : p;
     }
-    add_tile<DH>(dv, gp, HD, q0, N, dh, s, c, g);
-    add_tile<DH>(dk, qp, ld, q0, N, dh, dp, c, g);
+    dv_left_out = dv_left_out | add_tile<DH>(dv, gp, HD, q0, N, dh, s, c, g, qt == it.blk, kept[0]);
+    dk_left_out = dk_left_out | add_tile<DH>(dk, qp, ld, q0, N, dh, dp, c, g, qt == it.blk, kept[1]);
   }
+  auto seen = [&](int q) { return q >= kv; };
+  if (dv_left_out) add_left_out<DH>(dv, gp, HD, k0, N, dh, c, g, kept[0], seen);
+  if (dk_left_out) add_left_out<DH>(dk, qp, ld, k0, N, dh, c, g, kept[1], seen);
   auto *out = dqkv + ((int64_t)it.b * N + k0) * ld + HD + (int64_t)it.h * dh;
   merge<DH>(lds, dk, 1.f, out, nullptr, ld, N - k0, dh, wave, c, g);
   merge<DH>(lds, dv, 1.f, out + HD, nullptr, ld, N - k0, dh, wave, c, g);

@@ -289,3 +289,43 @@ def test_fp32_attention_of_any_length(lib, dh, N):
             # a sequence of one has dq = dk = 0 in exact arithmetic; what is left is the rounding of dp - delta, 1e-7 of |dO| |v| |k|
             err = np.linalg.norm(got[:, :, i][:, :, on] - want[i][:, :, on])
             assert err <= 1e-5 * np.linalg.norm(want[i][:, :, on]) + 1e-6 * np.linalg.norm(g) * dh, (i, err)
+
+
+# An infinity or a NaN in one token's value, key, query or output gradient: what does not depend on it keeps its bits (earlier queries'
+# outputs and gradients; for a query or an output gradient, later keys' too), and what the plain kernels, which visit visible pairs only,
+# compute as finite is finite.  Tokens inside a 32-row tile, at its edges and last of a ragged one.
+@pytest.mark.parametrize("dtype,dh", [(F32, 36), (F32, 64), (F32, 128), (BF, 32), (BF, 128)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_attention_keeps_a_non_finite_token_from_what_does_not_see_it(lib, dtype, dh, value):
+    Hs, B, N = 2, 2, 70
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=Hs, d_head=dh, d_ff=8, dtype=dtype, max_seq=N)))
+    qkv = _dev(_snap(si.normal(dh, "qkv", (B * N, 3 * Hs * dh)), dtype), dtype)
+    dout = _dev(_snap(si.normal(N, "dout", (B * N, Hs * dh)), dtype), dtype)
+
+    def run(x, g):
+        o, _, d = ctx.twist_attention_raw(x, g, B, N, Hs)
+        return [t.view(B, N, Hs, dh) for t in (o, *d.view(B, N, 3, Hs, dh).unbind(2))]
+
+    clean = run(qkv, dout)
+    for what in range(4):          # query, key, value, output gradient
+        for j in (5, 32, 47, 63, 69):
+            x, g = qkv.clone(), dout.clone()
+            if what < 3:
+                x.view(B, N, 3, Hs, dh)[0, j, what, 1, 3] = value
+            else:
+                g.view(B, N, Hs, dh)[0, j, 1, 3] = value
+            got = run(x, g)
+            ctx.twist_set_kernel_choice(plain_only=True)
+            plain = run(x, g)
+            ctx.twist_set_kernel_choice()
+            torch.cuda.synchronize()
+            for i, (a, b, c) in enumerate(zip(got, plain, clean)):
+                assert torch.equal(a[1], c[1]) and torch.equal(a[:, :, 0], c[:, :, 0]), (what, j, i)      # the other sequence, the other head
+                if i < 2:
+                    assert torch.equal(a[0, :j], c[0, :j]), (what, j, i)
+                elif what in (0, 3):
+                    assert torch.equal(a[0, j + 1:], c[0, j + 1:]), (what, j, i)
+                assert bool((torch.isfinite(a) | ~torch.isfinite(b)).all()), (what, j, i)
+            # and where it belongs it shows: in the token's own output, or its query's gradient (an infinite key may have weight zero)
+            if what != 1 or value != value:
+                assert not torch.isfinite(got[0 if what < 3 else 1][0, j, 1]).all(), (what, j)
