@@ -12,13 +12,18 @@
 // the B operand of the next product as it stands: MFMA number r contracts the rows 8 (r / 4) + 4 g + r % 4 (g = lane / 32), which
 // is where accumulator register r sits.  Along d_head, MFMA 4 u + e contracts columns 8 u + 4 g + e: one 16-byte load per lane
 // feeds four instructions.
+// Rounding (fp32 models; bf16 results are rounded a thousand times coarser): a score is added up in four chains and an exponent is
+// formed from the difference of a score and its reference, so that what is rounded is that and not the score, which may be large.
+// 2 x 200 tokens, 3 heads of 128, scores of about +-30, error of the output: 10.6e-7 with one chain and score * scale - reference,
+// 4.1e-7 like this, 3.5e-7 in the plain kernels, which add pairwise; 2 x 512 tokens, 6 heads of 64, normal operands: 2.3e-7, 1.6e-7
+// and 2.5e-7, for 2.5 us of 80 forward and backward.
 // delta_i = dO_i . O_i from the fp32 output.  Rows beyond N are clamped when read and not stored; keys beyond N come after
 // every query, and queries beyond N get probability zero.  An infinity or a NaN reaches what depends on it and nothing else: no
 // query sees a later key's, no key an earlier query's (add_tile).  That costs nothing that can be measured
 // (forward and backward of the first shape below: 80.3 us before, 78.6 since).
 //
 // Measured (forward / dQ / dK dV) on 2 x 512 tokens, 6 heads of 64: 20 / 30 / 37 us against 423 / 905 / 427 us of the plain kernels
-// (a wave per row, a wave reduction per score), and closer to exact arithmetic (query / key gradients 5e-6 against 3e-5).  bf16,
+// (a wave per row, a wave reduction per score), and closer to exact arithmetic where a value bias cancels (query / key gradients 1.3e-5 against 3.7e-5).  bf16,
 // 3 x 1000 tokens, 7 heads of 128: 132 / 189 / 310 us against 2633 / 3596 / 1945, with the same error against 64 bits (1.6e-3, the rounding of the results; bf16
 // tiles, at 27 / 46 / 60 us, have 2.0e-3 and in the gradients 2.4e-3).
 #include "nn.h"
@@ -29,7 +34,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
+constexpr float kLog2e = 1.4426950408889634f;
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32((a), (b), (c), 0, 0, 0)
 
@@ -60,17 +65,21 @@ __device__ __forceinline__ void load_row(f32x4 (&f)[DH / 8], const T *row, int d
     f[u] = k < dh ? get4(row + k) : f32x4{0.f, 0.f, 0.f, 0.f};
   }
 }
-// 32 x 32 tile of A B^T along d_head: `a` = this lane's row of A, `b` = this lane's column
-template <int DH>
+// chains of a score: the same in all kernels, so that the rounding of a score is the same where its probability is formed again
+template <int BF> constexpr int kChains = BF ? 1 : 4;
+// 32 x 32 tile of A B^T along d_head, summed in CH chains: `a` = this lane's row of A, `b` = this lane's column
+template <int DH, int CH>
 __device__ __forceinline__ f32x16 dot_tile(const f32x4 (&a)[DH / 8], const f32x4 (&b)[DH / 8]) {
-  f32x16 s;
+  f32x16 s[CH];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) s[r] = 0.f;
+  for (int h = 0; h < CH; ++h)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[h][r] = 0.f;
 #pragma unroll
   for (int u = 0; u < DH / 8; ++u)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s = MFMA(a[u][e], b[u][e], s);
-  return s;
+    for (int e = 0; e < 4; ++e) s[e % CH] = MFMA(a[u][e], b[u][e], s[e % CH]);
+  return CH == 4 ? (s[0] + s[1 % CH]) + (s[2 % CH] + s[3 % CH]) : CH == 2 ? s[0] + s[1 % CH] : s[0];
 }
 // acc[i] += X^T[32 i ..][rows] w[rows][column]: X rows row0 .. row0 + 31 (those beyond N are taken as zero), w in accumulator layout.
 // `diag`: the tile lies on the diagonal, where a column does not see every row.  Hidden entries have weight zero, but zero times an
@@ -187,7 +196,7 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const typename El<BF>
   float m = -INFINITY, l = 0.f;
   for (int kt = wave; kt <= it.blk && !masked; kt += 4) {
     load_row<DH>(kf, kp + (int64_t)min(kt * 32 + c, N - 1) * ld, dh, g);
-    f32x16 s = dot_tile<DH>(kf, qf);
+    f32x16 s = dot_tile<DH, kChains<BF>>(kf, qf);
     float mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -195,11 +204,11 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const typename El<BF>
       mx = fmaxf(mx, s[r]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m, mx * sc), ref = mn == -INFINITY ? 0.f : mn;  // (all scores of the wave's tiles so far may be -inf: weights 0)
-    const float alpha = fast_exp2(m - ref);
+    const float mn = fmaxf(m, mx), ref = mn == -INFINITY ? 0.f : mn;  // (all scores of the wave's tiles so far may be -inf: weights 0)
+    const float alpha = fast_exp2((m - ref) * sc);
     float sum = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { s[r] = fast_exp2(fmaf(s[r], sc, -ref)); sum += s[r]; }
+    for (int r = 0; r < 16; ++r) { s[r] = fast_exp2((s[r] - ref) * sc); sum += s[r]; }
     l = l * alpha + sum;
     m = mn;
 #pragma unroll
@@ -215,9 +224,9 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const typename El<BF>
   const float mt = fmaxf(fmaxf(ms[0][c], ms[1][c]), fmaxf(ms[2][c], ms[3][c]));
   float lt = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) lt += ls[w][c] * fast_exp2(ms[w][c] - mt);
-  const float mul = masked ? 0.f : fast_exp2(m - mt) / lt;  // a wave without tiles has m = -inf: factor 0
-  if (wave == 0 && g == 0 && q < N) lse[((int64_t)it.b * Hs + it.h) * N + q] = masked ? 0.f : (mt + log2f(lt)) * kLn2;
+  for (int w = 0; w < 4; ++w) lt += ls[w][c] * fast_exp2((ms[w][c] - mt) * sc);
+  const float mul = masked ? 0.f : fast_exp2((m - mt) * sc) / lt;  // a wave without tiles has m = -inf: factor 0
+  if (wave == 0 && g == 0 && q < N) lse[((int64_t)it.b * Hs + it.h) * N + q] = masked ? 0.f : fmaf(mt, scale, logf(lt));
   const int64_t at = ((int64_t)it.b * N + q0) * HD + (int64_t)it.h * dh;
   merge<DH>(lds, acc, mul, o + at, o32 ? o32 + at : nullptr, HD, N - q0, dh, wave, c, g);
 }
@@ -232,11 +241,10 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(const typename El<BF>:
   const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
   const auto *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
   const int q0 = it.blk * 32, q = q0 + c, qr = min(q, N - 1);
-  const float sc = scale * kLog2e;
   float *const kept = lds + wave * 32 * (DH + 4);  // the wave's part of the area that merge() uses afterwards
   bool left_out = false;
   const int64_t row = ((int64_t)it.b * N + qr) * HD + (int64_t)it.h * dh, stat = ((int64_t)it.b * Hs + it.h) * N;
-  const float L2 = lse[stat + qr] * kLog2e;
+  const float L = lse[stat + qr];
   f32x4 qf[DH / 8], gf[DH / 8], kf[DH / 8];
   load_row<DH>(qf, qp + (int64_t)qr * ld, dh, g);
   load_row<DH>(gf, dout + row, dh, g);
@@ -254,12 +262,12 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(const typename El<BF>:
   for (int kt = wave; kt <= it.blk && !masked; kt += 4) {
     const int64_t kr = min(kt * 32 + c, N - 1);
     load_row<DH>(kf, kp + kr * ld, dh, g);
-    f32x16 s = dot_tile<DH>(kf, qf);
+    f32x16 s = dot_tile<DH, kChains<BF>>(kf, qf);
     load_row<DH>(kf, vp + kr * ld, dh, g);
-    const f32x16 dp = dot_tile<DH>(kf, gf);
+    const f32x16 dp = dot_tile<DH, BF ? 1 : 2>(kf, gf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float ds = fast_exp2(fmaf(s[r], sc, -L2)) * (dp[r] - dl) * scale;
+      const float ds = fast_exp2(fmaf(s[r], scale, -L) * kLog2e) * (dp[r] - dl) * scale;
       s[r] = kt * 32 + 8 * (r >> 2) + 4 * g + (r & 3) > q ? 0.f : ds;
     }
     left_out = add_tile<DH>(acc, kp, ld, kt * 32, N, dh, s, c, g, kt == it.blk, kept);
@@ -280,7 +288,6 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const typename El<BF>
   const auto *qp = qkv + (int64_t)it.b * N * ld + (int64_t)it.h * dh, *kp = qp + HD, *vp = kp + HD;
   const auto *gp = dout + (int64_t)it.b * N * HD + (int64_t)it.h * dh;
   const int k0 = it.blk * 32, kv = k0 + c, kr = min(kv, N - 1);
-  const float sc = scale * kLog2e;
   bool dv_left_out = false, dk_left_out = false;
   const float *lse_b = lse + ((int64_t)it.b * Hs + it.h) * N, *del_b = delta + ((int64_t)it.b * Hs + it.h) * N;
   const bool masked = keep && keep[it.h] < 0;
@@ -295,13 +302,13 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const typename El<BF>
     const int q0 = qt * 32;
     const int64_t qr = min(q0 + c, N - 1);
     load_row<DH>(xf, qp + qr * ld, dh, g);
-    f32x16 s = dot_tile<DH>(xf, kf);
+    f32x16 s = dot_tile<DH, kChains<BF>>(xf, kf);
     load_row<DH>(xf, gp + qr * HD, dh, g);
-    f32x16 dp = dot_tile<DH>(xf, vf);
+    f32x16 dp = dot_tile<DH, BF ? 1 : 2>(xf, vf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int q = q0 + 8 * (r >> 2) + 4 * g + (r & 3), qc = min(q, N - 1);
-      const float p = fast_exp2(fmaf(s[r], sc, -lse_b[qc] * kLog2e)), ds = p * (dp[r] - del_b[qc]) * scale;
+      const float p = fast_exp2(fmaf(s[r], scale, -lse_b[qc]) * kLog2e), ds = p * (dp[r] - del_b[qc]) * scale;
       const bool hidden = q < kv || q >= N;
       dp[r] = hidden ? 0.f : ds;
       s[r] = hidden ? 0.f : p;

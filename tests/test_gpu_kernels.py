@@ -329,3 +329,31 @@ def test_attention_keeps_a_non_finite_token_from_what_does_not_see_it(lib, dtype
             # and where it belongs it shows: in the token's own output, or its query's gradient (an infinite key may have weight zero)
             if what != 1 or value != value:
                 assert not torch.isfinite(got[0 if what < 3 else 1][0, j, 1]).all(), (what, j)
+
+
+# fp32 attention keeps the precision of the plain kernels, which visit one key at a time and add pairwise: error against the fp64 checker
+# at most 1.35 times theirs (both are a few roundings of 2^-24; the order of sums alone moves it by up to 1.2), on plain normal operands,
+# on scores of about +-30 (what is rounded there must be score differences, not scores) and with a component common to all value rows
+@pytest.mark.parametrize("dh,N", [(32, 64), (64, 320), (128, 200)])
+@pytest.mark.parametrize("kind", ["normal", "sharp", "bias", "both"])
+def test_fp32_attention_is_as_precise_as_the_plain_kernels(lib, dh, N, kind):
+    Hs, B = 3, 2
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=Hs, d_head=dh, d_ff=8, max_seq=N)))
+    x = si.normal(dh + N, "qkv", (B * N, 3, Hs * dh))
+    if kind in ("sharp", "both"):
+        x[:, 0] *= 8
+    if kind in ("bias", "both"):
+        x[:, 2] += 20
+    qkv = _dev(_snap(x.reshape(B * N, -1), F32), F32)
+    dout = _dev(_snap(si.normal(N, "dout", (B * N, Hs * dh)), F32), F32)
+    q, k, v = (to_numpy(qkv).reshape(B, N, 3, Hs, dh)[:, :, i] for i in range(3))
+    want_o, p = omodel.attention_fwd(q, k, v)
+    want = (want_o, *omodel.attention_bwd(p, q, k, v, to_numpy(dout).reshape(B, N, Hs, dh)))
+    err = []
+    for plain in (False, True):
+        ctx.twist_set_kernel_choice(plain_only=plain)
+        o, _, d = ctx.twist_attention_raw(qkv, dout, B, N, Hs)
+        torch.cuda.synchronize()
+        got = (to_numpy(o).reshape(B, N, Hs, dh), *np.moveaxis(to_numpy(d).reshape(B, N, 3, Hs, dh), 2, 0))
+        err.append([rel_fro(a, b) for a, b in zip(got, want)])
+    assert all(a <= 1.35 * b for a, b in zip(*err)), err
