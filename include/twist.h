@@ -212,6 +212,10 @@ TWIST_API twist_status twist_subnet_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, c
 TWIST_API twist_status twist_subnet_fwd_bwd_masked(twist_ctx *ctx, twist_subnet *full_sub, const twist_plan *plan, int32_t s,
                                                    const void *inputs, const void *targets, int32_t B, int32_t N, void *workspace,
                                                    size_t workspace_bytes, float *loss_dev);
+/* Which of its two forms that pass takes for rows of `plan` and this batch, for tests and benchmarks: *kept_only = 1, only the
+ * kept blocks are computed (gathered layer by layer, their gradients spread back); 0, the full width is, with the masked
+ * blocks zeroed.  Results agree to rounding.  The form depends on the model, the blueprint's widths and the batch alone. */
+TWIST_API twist_status twist_masked_form(twist_ctx *ctx, const twist_plan *plan, int32_t B, int32_t N, int32_t *kept_only);
 
 /* Evaluation of an extracted subnet (Section 4.2, deployment: a pruned model is used as is): the forward half of
  * twist_subnet_fwd_bwd only; *loss_dev receives the same loss.  Works on subnets extracted with any storage mode

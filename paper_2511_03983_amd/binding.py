@@ -86,6 +86,7 @@ _SIGS = {
     "twist_subnet_fwd_bwd": ([_vp, _vp, _vp, _vp, _i32, _i32, _vp, _sz, _vp], _i32),
     "twist_subnet_forward": ([_vp, _vp, _vp, _vp, _i32, _i32, _vp, _sz, _vp], _i32),
     "twist_subnet_fwd_bwd_masked": ([_vp, _vp, _vp, _i32, _vp, _vp, _i32, _i32, _vp, _sz, _vp], _i32),
+    "twist_masked_form": ([_vp, _vp, _i32, _i32, _PI32], _i32),
     "twist_subnet_step": ([_vp, _vp, C.POINTER(OptDesc)], _i32),
     "twist_aggregate": ([_vp, _vp, C.POINTER(_vp), _i32, C.POINTER(FullWeightsC)], _i32),
     "twist_aggregate_image_bytes": ([_vp, C.POINTER(_sz)], _i32),
@@ -200,6 +201,12 @@ class Context:
         B, N = inputs.shape[0], inputs.shape[1]
         _check(lib.twist_subnet_fwd_bwd_masked(self.h, full_sub.h, plan.h, s, _vp(inputs.data_ptr()), _vp(targets.data_ptr()), B, N,
                                                _vp(workspace.data_ptr()), workspace.numel(), _vp(loss.data_ptr())), self.h)
+
+    def twist_masked_form(self, plan: "Plan", B: int, N: int) -> bool:
+        """Whether twist_subnet_fwd_bwd_masked under rows of `plan` computes the kept blocks only (see include/twist.h)."""
+        kept = _i32()
+        _check(lib.twist_masked_form(self.h, plan.h, B, N, C.byref(kept)), self.h)
+        return bool(kept.value)
 
     def twist_subnet_forward(self, sub: "Subnet", inputs: torch.Tensor, targets: torch.Tensor, workspace: torch.Tensor,
                              loss: torch.Tensor) -> None:

@@ -923,6 +923,14 @@ extern "C" twist_status twist_subnet_fwd_bwd_masked(twist_ctx *ctx, twist_subnet
   return twist_train_fwd_bwd(ctx, full_sub, inputs, targets, B, N, workspace, workspace_bytes, loss_dev, false, plan, s);
 }
 
+extern "C" twist_status twist_masked_form(twist_ctx *ctx, const twist_plan *plan, int32_t B, int32_t N, int32_t *kept_only) {
+  if (!ctx || !plan || !kept_only) TW_FAIL(ctx, TWIST_EINVAL, "twist_masked_form: null argument");
+  if (plan->ctx != ctx) TW_FAIL(ctx, TWIST_EINVAL, "twist_masked_form: plan belongs to another context");
+  if (B < 1 || N < 1) TW_FAIL(ctx, TWIST_ESHAPE, "twist_masked_form: batch %d x %d tokens is empty", B, N);
+  *kept_only = twist_train_masked_compact(ctx, plan, B, N);
+  return TWIST_OK;
+}
+
 extern "C" twist_status twist_subnet_forward(twist_ctx *ctx, twist_subnet *sub, const void *inputs, const void *targets, int32_t B, int32_t N,
                                              void *workspace, size_t workspace_bytes, float *loss_dev) {
   if (!ctx || !sub || !inputs || !targets || !workspace || !loss_dev) TW_FAIL(ctx, TWIST_EINVAL, "twist_subnet_forward: null argument");

@@ -30,8 +30,9 @@ struct LayerBufs {
 
 // Masked TwIST on the kept blocks only: the kept blocks of a layer's partitioned tensors are gathered into a scratch copy of one
 // layer, the layer runs dense at its kept width, and its gradients are spread back with zeros in the masked blocks.  The scratch
-// holds one layer at a time (weights again for the backward pass), so the whole fits the workspace that the full-width pass was
-// sized for as soon as the batch is a few hundred tokens: the activations shrink with the width.
+// holds one layer at a time (weights again for the backward pass), and the whole has to fit the workspace that the full-width pass is
+// sized for: the activations of every layer shrink with the width, the scratch is that of one layer.  (Llama-1B widths, half the
+// blocks: 150 MB of scratch against 54 KB per token and layer, i.e. 2800 tokens for one layer, 130 for 22.)
 struct Compact {
   bool on = false;
   int64_t off[TWIST_N_LAYER_TENSORS];       // element offsets of one layer's matrices and (behind them) biases in the scratch
@@ -201,6 +202,33 @@ twist_status twist_train_workspace_bytes(twist_ctx *ctx, const twist_subnet *sub
   return TWIST_OK;
 }
 
+// Whether the masked pass under a row of `plan` runs on the kept blocks only (struct Compact).  That depends on the model, the blueprint's
+// widths and the batch alone, not on the buffers of one call: equal calls take the same form and give the same bits.
+// Compacting moves about 12 r + 4 bytes per layer parameter (bf16, r = kept share: gathered twice, gradients spread once) at
+// 4.5 TB/s and saves 6 T (1 - r) flop of it at about 0.9 PFLOP/s (fp32 models: 20 r + 4 bytes, 0.1 PFLOP/s), which is where the
+// line lies.  Llama-1B widths, 6 layers, 4 x 2048 tokens, half the blocks: 13.9 ms against 20.4 in place.
+bool twist_train_masked_compact(const twist_ctx *ctx, const twist_plan *plan, int B, int N) {
+  const twist_model_desc &d = ctx->d;
+  const int L = d.n_layers, T = B * N;
+  double full_p = 0, kept_p = 0;
+  for (int l = 0; l < L; ++l)
+    for (int t = TWIST_WQ; t <= TWIST_W_DOWN; ++t) {
+      const PlanEntry &pe = plan->at(l, twist_tensor_kind(d, t));
+      int r, c;
+      twist_tensor_shape(d, t, d.n_heads, ctx->n_ffn_units(), r, c);
+      full_p += (double)r * c;
+      kept_p += (double)r * c * pe.n_sub / pe.n_full;
+    }
+  const double r = kept_p / full_p, gain = T * (1.0 - r), cost = d.dtype == TWIST_BF16 ? 33.0 * (12.0 * r + 4.0) : 4.0 * (20.0 * r + 4.0);
+  if (gain <= cost) return false;
+  std::vector<int32_t> h1(L, d.n_heads), f1(L, ctx->n_ffn_units()), h2(L), f2(L);
+  for (int l = 0; l < L; ++l) { h2[l] = plan->at(l, TWIST_KIND_HEAD).n_sub; f2[l] = plan->at(l, TWIST_KIND_FFN).n_sub; }
+  Workspace full, kept;
+  carve(ctx, h1, f1, nullptr, B, N, nullptr, full);
+  carve(ctx, h2, f2, plan, B, N, nullptr, kept);
+  return kept.bytes <= full.bytes;  // the caller's workspace is sized for the pass in place
+}
+
 twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *inputs, const void *targets, int B, int N, void *ws,
                                  size_t ws_bytes, float *loss_dev, bool forward_only, const twist_plan *mask_plan, int mask_row) {
   TW_TRY(check_train_shape(ctx, sub, B, N));
@@ -224,9 +252,7 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
   //  - in place: they are computed at full width and zeroed where they enter the output projections (attention output
   //    columns, FFN activations) and where the gradient comes back through the same places, inside the kernels that produce
   //    those tensors.  The ordinary pass, with the same number of launches.
-  // Compacting moves about 12 r + 4 bytes per layer parameter (bf16, r = kept share: gathered twice, gradients spread once) at
-  // 4.5 TB/s and saves 6 T (1 - r) flop of it at about 0.9 PFLOP/s (fp32 models: 20 r + 4 bytes, 0.1 PFLOP/s), which is where the
-  // line lies.  Llama-1B widths, 6 layers, 4 x 2048 tokens, half the blocks: 13.9 ms against 20.4 in place.
+  // (twist_train_masked_compact chooses.)
   if (mask_plan) {
     for (int l = 0; l < d.n_layers; ++l)
       if (L.heads_sub[l] != d.n_heads || L.ffn_sub[l] != ctx->n_ffn_units())
@@ -234,29 +260,14 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
   }
   std::vector<int32_t> heads = L.heads_sub, ffn = L.ffn_sub;  // width of every layer as it is run
   std::vector<Compact> compact(d.n_layers);
-  if (mask_plan && !forward_only) {
-    double full_p = 0, kept_p = 0;
-    for (int l = 0; l < d.n_layers; ++l)
-      for (int t = TWIST_WQ; t <= TWIST_W_DOWN; ++t) {
-        const PlanEntry &pe = mask_plan->at(l, twist_tensor_kind(d, t));
-        int r, c;
-        twist_tensor_shape(d, t, d.n_heads, ctx->n_ffn_units(), r, c);
-        full_p += (double)r * c;
-        kept_p += (double)r * c * pe.n_sub / pe.n_full;
-      }
-    const double r = kept_p / full_p, gain = T * (1.0 - r), cost = bf ? 33.0 * (12.0 * r + 4.0) : 4.0 * (20.0 * r + 4.0);
-    if (gain > cost) {
-      std::vector<int32_t> h2(d.n_layers), f2(d.n_layers);
-      for (int l = 0; l < d.n_layers; ++l) { h2[l] = mask_plan->at(l, TWIST_KIND_HEAD).n_sub; f2[l] = mask_plan->at(l, TWIST_KIND_FFN).n_sub; }
-      Workspace w2;
-      carve(ctx, h2, f2, mask_plan, B, N, ws, w2);
-      if (w2.bytes <= ws_bytes) {
-        w = w2;
-        heads = h2;
-        ffn = f2;
-        for (int l = 0; l < d.n_layers; ++l) { compact_layout(d, mask_plan, l, compact[l]); compact[l].on = true; }
-      }
+  if (mask_plan && !forward_only && twist_train_masked_compact(ctx, mask_plan, B, N)) {
+    for (int l = 0; l < d.n_layers; ++l) {
+      heads[l] = mask_plan->at(l, TWIST_KIND_HEAD).n_sub;
+      ffn[l] = mask_plan->at(l, TWIST_KIND_FFN).n_sub;
+      compact_layout(d, mask_plan, l, compact[l]);
+      compact[l].on = true;
     }
+    carve(ctx, heads, ffn, mask_plan, B, N, ws, w);
   }
   const bool in_place = mask_plan && !compact[0].on;
   // per-block mask of layer l (device table: entry < 0 = block not kept), handed to the kernels that produce the attention

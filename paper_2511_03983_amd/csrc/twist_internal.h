@@ -163,4 +163,5 @@ twist_status twist_train_workspace_bytes(twist_ctx *ctx, const twist_subnet *sub
 twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *inputs, const void *targets, int B,
                                  int N, void *ws, size_t ws_bytes, float *loss_dev, bool forward_only = false,
                                  const twist_plan *mask_plan = nullptr, int mask_row = 0);
+bool twist_train_masked_compact(const twist_ctx *ctx, const twist_plan *plan, int B, int N);
 twist_status twist_train_step(twist_ctx *ctx, twist_subnet *sub, const twist_opt_desc *opt);

@@ -764,6 +764,38 @@ def test_masked_pass_on_the_kept_blocks_is_the_extracted_subnets_pass(lib, name,
                 assert torch.equal(g, e), k
 
 
+def _masked_pass(lib, cfg, hs, fs, B, N, spare=0):
+    """Loss and gradient region of a masked pass under a blueprint of two rows, with `spare` bytes of workspace beyond what is asked for."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    dt = torch.bfloat16 if cfg.dtype == "bf16" else torch.float32
+    draw = lambda shp: (torch.randn(shp, generator=gen, device="cuda") * 0.05 + (1.0 if len(shp) == 1 else 0.0)).to(dt)
+    fw = lib.FullWeights([{k: draw(s) for k, s in si.stored_shapes(cfg).items()} for _ in range(cfg.n_layers)],
+                         {k: draw(s) for k, s in si.global_shapes(cfg).items()})
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    plan = ctx.twist_sample(2, hs, fs, seed=4)
+    sub = ctx.twist_extract(ctx.twist_sample(1, cfg.n_heads, cfg.n_ffn_units, seed=0), fw, 0, store=lib.STORE_GRADS)
+    tok = torch.tensor(si.tokens_uniform(cfg.vocab, B, N, 9)).cuda()
+    ws = torch.empty(ctx.twist_workspace_bytes(sub, B, N) + spare, dtype=torch.uint8, device="cuda")
+    loss = torch.zeros(1, device="cuda")
+    ctx.twist_profile_gemm(True)
+    ctx.twist_subnet_fwd_bwd_masked(sub, plan, 1, tok[:, :-1].contiguous(), tok[:, 1:].contiguous(), ws, loss)
+    flops = ctx.twist_profile_gemm_read()[2]
+    torch.cuda.synchronize()
+    grads = [sub.twist_subnet_view(l, k, GRAD).clone() for l in range(cfg.n_layers) for k in si.layer_shapes(cfg)]
+    return ctx, plan, loss.item(), grads, flops
+
+
+def test_masked_pass_takes_the_same_form_whatever_the_workspace(lib):
+    """A layer too large for its kept copy to fit beside the activations of few tokens: the pass in place, also with room to spare."""
+    cfg = replace(si.CFG3, n_layers=1, d_model=1024, n_heads=8, d_head=128, d_ff=2816, vocab=259, max_seq=512)
+    args = (lib, cfg, 4, 1408, 2, 512)
+    ctx, plan, loss, grads, flops = _masked_pass(*args)
+    _, _, loss2, grads2, flops2 = _masked_pass(*args, spare=1 << 30)
+    assert not ctx.twist_masked_form(plan, 2, 512)
+    assert flops == flops2 and loss == loss2
+    assert all(torch.equal(a, b) for a, b in zip(grads, grads2))
+
+
 def test_train_x_eval_y_grid_matches_checker(lib):
     """Section 5.1 ("Architectural Robustness"): a model trained for one round with subnets of X of 12 blocks (heads and
     FFN blocks alike, first and last layer shared) is evaluated, without retraining, through deployment subnets of Y of
