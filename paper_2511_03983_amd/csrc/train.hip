@@ -207,11 +207,18 @@ twist_status twist_train_workspace_bytes(twist_ctx *ctx, const twist_subnet *sub
 // Compacting moves about 12 r + 4 bytes per layer parameter (bf16, r = kept share: gathered twice, gradients spread once) at
 // 4.5 TB/s and saves 6 T (1 - r) flop of it at about 0.9 PFLOP/s (fp32 models: 20 r + 4 bytes, 0.1 PFLOP/s), which is where the
 // line lies.  Llama-1B widths, 6 layers, 4 x 2048 tokens, half the blocks: 13.9 ms against 20.4 in place.
+// Kept widths that break the 16-byte rows of a width that has them lose the matrix-core kernels in bf16 (2 such layers with 2501 of
+// 5632 neurons: 28.6 ms against 6.0 in place), so those models stay in place; in fp32 the projections go on with scalar loads, which
+// costs them up to 0.4 of their time (4 layers of 768, 1533 of 3072 neurons, 2 x 512 tokens: 2.6 ms; 1536 neurons 2.0; in place 2.8).
 bool twist_train_masked_compact(const twist_ctx *ctx, const twist_plan *plan, int B, int N) {
   const twist_model_desc &d = ctx->d;
   const int L = d.n_layers, T = B * N;
+  const int vec = 16 / ctx->esize();
   double full_p = 0, kept_p = 0;
-  for (int l = 0; l < L; ++l)
+  bool odd = false;  // some kept width breaks 16-byte rows
+  for (int l = 0; l < L; ++l) {
+    const int q[2] = {d.d_head, d.ffn_granule};
+    for (int k = 0; k < 2; ++k) odd |= plan->at(l, k).n_full * q[k] % vec == 0 && plan->at(l, k).n_sub * q[k] % vec != 0;
     for (int t = TWIST_WQ; t <= TWIST_W_DOWN; ++t) {
       const PlanEntry &pe = plan->at(l, twist_tensor_kind(d, t));
       int r, c;
@@ -219,7 +226,9 @@ bool twist_train_masked_compact(const twist_ctx *ctx, const twist_plan *plan, in
       full_p += (double)r * c;
       kept_p += (double)r * c * pe.n_sub / pe.n_full;
     }
-  const double r = kept_p / full_p, gain = T * (1.0 - r), cost = d.dtype == TWIST_BF16 ? 33.0 * (12.0 * r + 4.0) : 4.0 * (20.0 * r + 4.0);
+  }
+  if (odd && d.dtype == TWIST_BF16) return false;
+  const double r = kept_p / full_p, gain = T * (1.0 - (odd ? 1.4 : 1.0) * r), cost = d.dtype == TWIST_BF16 ? 33.0 * (12.0 * r + 4.0) : 4.0 * (20.0 * r + 4.0);
   if (gain <= cost) return false;
   std::vector<int32_t> h1(L, d.n_heads), f1(L, ctx->n_ffn_units()), h2(L), f2(L);
   for (int l = 0; l < L; ++l) { h2[l] = plan->at(l, TWIST_KIND_HEAD).n_sub; f2[l] = plan->at(l, TWIST_KIND_FFN).n_sub; }

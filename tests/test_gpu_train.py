@@ -796,6 +796,17 @@ def test_masked_pass_takes_the_same_form_whatever_the_workspace(lib):
     assert all(torch.equal(a, b) for a, b in zip(grads, grads2))
 
 
+@pytest.mark.parametrize("dtype,fs,kept_only", [("bf16", 1024, True), ("bf16", 1028, False), ("bf16", 1031, False), ("f32", 1024, True), ("f32", 1031, True),
+                                                ("f32", 1901, False)])
+def test_masked_pass_keeps_aligned_projections(lib, dtype, fs, kept_only):
+    """Kept widths that break 16-byte rows (bf16: no multiple of 8) stay at full width, where the matrix-core kernels run."""
+    cfg = replace(si.CFG2, n_layers=2, d_model=256, n_heads=4, d_head=64, d_ff=2048, vocab=259, max_seq=512, dtype=dtype)
+    ctx, plan, loss, grads, flops = _masked_pass(lib, cfg, 3, fs, 8, 512)
+    assert ctx.twist_masked_form(plan, 8, 512) == kept_only
+    width = lambda h, f: 2 * 8 * 512 * (cfg.n_layers * 256 * (4 * h * 64 + 2 * f) + 256 * 259) * 3.0
+    assert flops == (width(3, fs) if kept_only else width(4, 2048))
+
+
 def test_train_x_eval_y_grid_matches_checker(lib):
     """Section 5.1 ("Architectural Robustness"): a model trained for one round with subnets of X of 12 blocks (heads and
     FFN blocks alike, first and last layer shared) is evaluated, without retraining, through deployment subnets of Y of
