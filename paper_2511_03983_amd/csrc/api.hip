@@ -516,6 +516,22 @@ int64_t flat_blocks(const MoveJob &jb, int vn) { return ((int64_t)jb.rows * jb.n
 
 }  // namespace
 
+bool twist_expand_fits(const twist_ctx *ctx, const twist_plan *plan, int l) {
+  static const uint32_t launches[] = {1u << TWIST_WQ | 1u << TWIST_WK | 1u << TWIST_WV, 1u << TWIST_WO, 1u << TWIST_W_GATE | 1u << TWIST_W_UP, 1u << TWIST_W_DOWN,
+                                      1u << TWIST_BQ | 1u << TWIST_BK | 1u << TWIST_BV | 1u << TWIST_B_UP};
+  for (uint32_t only : launches) {
+    int64_t blocks = 0;
+    for (int t = 0; t < TWIST_N_LAYER_TENSORS; ++t) {
+      MoveJob jb;
+      if (!(only >> t & 1) || !make_job(ctx, plan, l, t, nullptr, 0, true, 1, jb)) continue;
+      jb.vec = jb.Q % 4 == 0;
+      blocks += flat_blocks(jb, 4);
+    }
+    if (blocks * kAccumPerBlock >= (int64_t)1 << 31) return false;
+  }
+  return true;
+}
+
 twist_status twist_gather_layer(twist_ctx *ctx, const twist_plan *plan, int l, int s, const void *const *full, const int64_t *dst_off, char *dst) {
   MoveLaunch ml;
   std::memset(&ml, 0, sizeof ml);

@@ -217,6 +217,7 @@ bool twist_train_masked_compact(const twist_ctx *ctx, const twist_plan *plan, in
   double full_p = 0, kept_p = 0;
   bool odd = false;  // some kept width breaks 16-byte rows
   for (int l = 0; l < L; ++l) {
+    if (!twist_expand_fits(ctx, plan, l)) return false;
     const int q[2] = {d.d_head, d.ffn_granule};
     for (int k = 0; k < 2; ++k) odd |= plan->at(l, k).n_full * q[k] % vec == 0 && plan->at(l, k).n_sub * q[k] % vec != 0;
     for (int t = TWIST_WQ; t <= TWIST_W_DOWN; ++t) {

@@ -149,6 +149,8 @@ twist_status twist_launch_accumulate(twist_ctx *ctx, const MoveLaunch &ml, int t
 twist_status twist_gather_layer(twist_ctx *ctx, const twist_plan *plan, int l, int s, const void *const *full, const int64_t *dst_off, char *dst);
 twist_status twist_expand_layer(twist_ctx *ctx, hipStream_t st, const twist_plan *plan, int l, int s, float *const *full, const int64_t *src_off, const float *src,
                                 uint32_t only);
+// whether every expand of layer l (one launch per projection, one for the biases) stays inside the kernel's 32-bit index range
+bool twist_expand_fits(const twist_ctx *ctx, const twist_plan *plan, int l);
 twist_status twist_launch_expand(twist_ctx *ctx, hipStream_t st, const MoveLaunch &ml, int total_blocks);
 // kind (TWIST_KIND_*) of the blocks that layer tensor t is cut into, or -1 if all subnets share it
 int twist_tensor_kind(const twist_model_desc &d, int t);

@@ -807,6 +807,16 @@ def test_masked_pass_keeps_aligned_projections(lib, dtype, fs, kept_only):
     assert flops == (width(3, fs) if kept_only else width(4, 2048))
 
 
+@pytest.mark.parametrize("granule,kept_only", [(4, True), (1, False)])
+def test_masked_pass_stays_in_place_beyond_the_index_range(lib, granule, kept_only):
+    """Gradients are spread back with 32-bit indexes, four elements at a time where blocks allow it: a layer beyond that (here one of
+    2^31 single columns) has to be known before the pass begins.  Nothing is run: the blueprint's tables are all that is allocated."""
+    cfg = si.ModelCfg(n_layers=1, d_model=16384, n_heads=128, d_head=128, d_ff=131072, ffn_granule=granule, vocab=259, max_seq=4096, dtype="bf16")
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    plan = ctx.twist_sample(2, 64, 65536 // granule, seed=1)
+    assert ctx.twist_masked_form(plan, 8, 4096) == kept_only
+
+
 def test_train_x_eval_y_grid_matches_checker(lib):
     """Section 5.1 ("Architectural Robustness"): a model trained for one round with subnets of X of 12 blocks (heads and
     FFN blocks alike, first and last layer shared) is evaluated, without retraining, through deployment subnets of Y of
