@@ -271,6 +271,17 @@ TWIST_API twist_status twist_round(twist_ctx *ctx, const twist_round_desc *rd, c
 TWIST_API twist_status twist_gemm_raw(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, const void *A, int64_t lda,
                                       const void *B, int64_t ldb, void *C, int64_t ldc, int32_t out_f32, float alpha);
 
+/* twist_gemm_raw with the scratch (dev, 16-byte aligned, may be NULL) that the training pass gives its weight gradients: with it the
+ * contraction may be cut into parts whose fp32 partial products go there and are summed in a fixed order. */
+TWIST_API twist_status twist_gemm_raw_cut(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, const void *A, int64_t lda,
+                                          const void *B, int64_t ldb, void *C, int64_t ldc, int32_t out_f32, float alpha, float *scratch,
+                                          size_t scratch_floats);
+/* Which matrix-core kernel a projection of this shape runs on where its operands are aligned (host only, for tests and benchmarks):
+ * chosen receives the rows and columns of the output tile and the number of parts of the contraction, given a scratch of
+ * scratch_floats (0: none). */
+TWIST_API twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32,
+                                         size_t scratch_floats, int32_t chosen[3]);
+
 /* Kernel-level entry point for tests: causal multi-head attention of Appendix A.1 in isolation, forward and (when
  * dout is not NULL) backward, on a fused activation buffer qkv [B*N, 3*Hs*d_head] (q | k | v, desc.dtype).
  * Outputs: o [B*N, Hs*d_head] (desc.dtype), lse [B, Hs, N] fp32 (log-sum-exp of the scaled scores), and dqkv

@@ -97,6 +97,8 @@ _SIGS = {
     "twist_round_bytes": ([_vp, C.POINTER(RoundDesc), C.POINTER(_sz), C.POINTER(_sz), C.POINTER(_sz)], _i32),
     "twist_round": ([_vp, C.POINTER(RoundDesc), C.POINTER(FullWeightsC), _vp, _vp, _vp, _sz, _vp, _sz, _vp, _sz, _vp], _i32),
     "twist_gemm_raw": ([_vp, _i32, _i32, _i32, _i32, _vp, C.c_int64, _vp, C.c_int64, _vp, C.c_int64, _i32, C.c_float], _i32),
+    "twist_gemm_raw_cut": ([_vp, _i32, _i32, _i32, _i32, _vp, C.c_int64, _vp, C.c_int64, _vp, C.c_int64, _i32, C.c_float, _vp, _sz], _i32),
+    "twist_gemm_kernel": ([_vp, _i32, _i32, _i32, _i32, _i32, _sz, _PI32], _i32),
     "twist_attention_raw": ([_vp, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp], _i32),
     "twist_norm_raw": ([_vp, _vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz], _i32),
     "twist_norm_raw_static": ([_vp, _vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp], _i32),
@@ -268,6 +270,18 @@ class Context:
         _check(lib.twist_gemm_raw(self.h, layout, M, N, K, _vp(A.data_ptr()), A.stride(0), _vp(B.data_ptr()), B.stride(0),
                                   _vp(out.data_ptr()), out.stride(0), int(out.dtype == torch.float32 and self.torch_dtype != torch.float32
                                                                           or out.dtype == torch.float32), alpha), self.h)
+
+    def twist_gemm_raw_cut(self, layout: int, M: int, N: int, K: int, A: torch.Tensor, B: torch.Tensor, out: torch.Tensor, scratch: torch.Tensor,
+                           alpha: float = 1.0) -> None:
+        """twist_gemm_raw whose contraction may be cut into parts, with fp32 partial products in `scratch`."""
+        _check(lib.twist_gemm_raw_cut(self.h, layout, M, N, K, _vp(A.data_ptr()), A.stride(0), _vp(B.data_ptr()), B.stride(0), _vp(out.data_ptr()),
+                                      out.stride(0), int(out.dtype == torch.float32), alpha, _vp(scratch.data_ptr()), scratch.numel()), self.h)
+
+    def twist_gemm_kernel(self, layout: int, M: int, N: int, K: int, out_f32: bool = False, scratch_floats: int = 0):
+        """(tile rows, tile columns, parts of the contraction) of a projection whose operands are aligned; host only."""
+        chosen = (_i32 * 3)()
+        _check(lib.twist_gemm_kernel(self.h, layout, M, N, K, int(out_f32), scratch_floats, chosen), self.h)
+        return tuple(chosen)
 
     def twist_attention_raw(self, qkv: torch.Tensor, dout, B: int, N: int, Hs: int, keep: torch.Tensor | None = None, rope_backward: bool = False):
         """Causal attention alone: returns (o, lse, dqkv or None) for qkv [B*N, 3*Hs*d_head] and dout [B*N, Hs*d_head] or None;

@@ -356,42 +356,55 @@ __global__ __launch_bounds__(256) void mfma_only_kernel(int iters, float *sink, 
 }
 
 // Which kernel a bf16 product runs on, and into how many parts its contraction is cut, by estimated time:
-//   fixed + rounds * slices * (s0 + s1 * share of the chip at work)   microseconds, slices of 32 along the contraction
-// with rounds = how many tiles the busiest of 256 CUs works through (the small tiles share a CU in pairs, so theirs need not be
-// whole).  fixed = launch, first loads, epilogue; s1 = how much slower a slice gets when the whole chip works (clock, memory).
-// Fitted to measurements (us), bf16 operands not in the caches, K-contiguous unless said:
-//   M x N x K             256x256  256x128   64x64   32x32   (register-staged 128x128, which these replace)
-//   128 x 2304 x 768         20.3     13.5     5.9     5.6    13.2
-//   128 x 768 x 1536         31.0              8.3     5.1    21.1
-//   2048 x 1536 x 768        19.2     14.6    12.8    23.3    14.3
-//   2048 x 768 x 2048        36.4     28.0    14.7    21.5    26.4
-//   8192 x 768 x 192         10.1      7.4    13.0    30.0    10.6
-//   8192 x 768 x 768         19.3     15.5    22.0    42.0    20.2
-//   3000 x 2688 x 2048       43.2     37.3    56.6    96.0    45.5
-//   8192 x 1024 x 2048       47.5     41.5    60.1            46.7
-//   8192 x 2048 x 1024 (NN)  34.6     40.3    68.4            49.0
-//   4096 x 4096 x 4096      110.9    134.7   232.0   348.0   163.0
-//   768 x 768 x 8192 (TN)   131.4    108.8    31.5    58.7    97.4   (uncut)
-// A cut contraction adds a launch and one pass over the fp32 partial products (5.5 TB/s).
-struct Kind { int bm, bn; double fixed, s0, s1; bool paired; };
-constexpr Kind kKinds[] = {{256, 256, 9.6, 0.40, 0.38, false}, {256, 128, 4.8, 0.33, 0.24, false}, {64, 64, 3.5, 0.10, 0.02, true}, {32, 32, 3.5, 0.05, 0.015, true}};
+//   fixed + rounds * (tile + tile32 * (fp32 output) + slices * (s0 + s1 * share of the chip at work))   microseconds
+// with slices of 32 along the contraction and rounds = how many tiles the busiest of 256 CUs works through.  fixed = launch; tile =
+// first loads and epilogue of every tile, which decide where the contraction is short and the rows are many; s1 = how much slower a
+// slice gets when the whole chip works (clock, memory); the 32x32 kernel's slices take nt of that where both operands are contiguous
+// along k.  A cut contraction adds a launch and one pass over the fp32 partial products.
+// Fitted to 530 products of every layout, sizes 33 to 8192, those of the TN layout cut in up to 16 parts (operands in rotation).  Over
+// 300 others the kernel taken is on average 0.8 % slower than the fastest (without the cost of a tile, and with the rounds of the small
+// tiles taken as items / 256, as the rule was: 2.7 %).  Some of them, us:
+//   M x N x K             256x256  256x128   64x64   32x32
+//   128 x 1536 x 2048        42.6     32.0     9.9     6.1
+//   2048 x 2048 x 128        10.0      7.6     9.1    21.7
+//   2048 x 1536 x 512        16.8     12.8    11.4    22.1   (fp32 output)
+//   4096 x 768 x 2560        57.1     41.9    29.9    50.4   (fp32 output)
+//   8192 x 768 x 64 (NN)      8.0      5.9    12.1    31.9
+//   8192 x 768 x 192 (NN)    11.4     10.0    15.0    35.6   (fp32 output; the rule took 64x64 here)
+//   8192 x 2048 x 256        15.6     17.4    32.9    81.8
+//   8192 x 3072 x 1024 (NN)  56.9     60.5   108.6   228.3
+//   1536 x 1536 x 2048 (TN)  39.5     33.8    25.3    47.5   (fp32 output)
+// and cut: 768 x 640 x 4096 (TN) 17.5 whole, 15.2 in two parts, 17.5 in three; 2048 x 1024 x 8192 56 in five, 63 in eight;
+// 256 x 128 x 2048 6.1 whole, 9.0 in eight.
+struct Kind { int bm, bn; double fixed, tile, tile32, s0, s1, nt; };
+constexpr Kind kKinds[] = {{256, 256, 1.0, 8.0, 0.2, 0.40, 0.35, 1.0}, {256, 128, 2.4, 3.4, 1.2, 0.35, 0.23, 1.0}, {64, 64, 3.0, 1.0, 0.1, 0.115, 0.01, 1.0},
+                           {32, 32, 2.8, 0.75, 0.05, 0.07, 0.01, 0.65}};
 struct Choice { int kind, parts; };
-Choice choose(int M, int N, int K, bool may_split, size_t split_floats) {
+Choice choose(GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split, size_t split_floats) {
   Choice best{0, 1};
   double best_us = 1e30;
   for (int k = 0; k < 4; ++k) {
     const Kind &kd = kKinds[k];
-    const double tiles = (double)((M + kd.bm - 1) / kd.bm) * ((N + kd.bn - 1) / kd.bn);
+    const int64_t tiles = (int64_t)((M + kd.bm - 1) / kd.bm) * ((N + kd.bn - 1) / kd.bn);
     for (int parts = 1; parts <= 16; ++parts) {
       if (parts > 1 && (!may_split || K < 256 * parts || (double)parts * M * N > (double)split_floats)) break;
-      const double items = tiles * parts, share = std::min(1.0, items / 256), slices = (double)K / 32 / parts;
-      const double rounds = kd.paired ? std::max(1.0, items / 256) : (double)(((int64_t)items + 255) / 256);
-      double us = kd.fixed + rounds * slices * (kd.s0 + kd.s1 * share);
-      if (parts > 1) us += 2.5 + (parts + 1.0) * M * N * 4.0 / 5.5e6;
+      const int64_t items = tiles * parts, rounds = (items + 255) / 256;
+      const double share = std::min(1.0, items / 256.0), slice = (kd.s0 + kd.s1 * share) * (lay == GEMM_NT ? kd.nt : 1.0);
+      double us = kd.fixed + rounds * (kd.tile + (f32_out || parts > 1 ? kd.tile32 : 0.0) + K / 32.0 / parts * slice);
+      if (parts > 1) us += 3.8 + (parts + 1.0) * M * N * 4.0 / 4.0e6;
       if (us < best_us) { best_us = us; best = {k, parts}; }
     }
   }
   return best;
+}
+
+// kernel, parts of the contraction and their length (a multiple of the kernel's slices) of a bf16 product whose operands are aligned
+struct Cut { int kind, parts, kchunk; };
+Cut cut_of(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split, size_t split_floats) {
+  Choice ch = choose(lay, M, N, K, f32_out, may_split && lay != GEMM_NT, split_floats);
+  if (ctx->gemm_tile) ch = {ctx->gemm_tile == 256 ? 0 : 1, 1};
+  const int step = ch.kind < 2 ? 32 : 128, kchunk = ((K + ch.parts - 1) / ch.parts + step - 1) / step * step;
+  return {ch.kind, (K + kchunk - 1) / kchunk, kchunk};
 }
 
 // one launch of gemm_pp_kernel: kchunk = K for an uncut contraction, else a multiple of 32
@@ -453,9 +466,8 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
   const bool vec_ok = bf16 && !no_mfma && aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 && k_ok && span_ok;
   if (vec_ok) {
     const uint16_t *a = static_cast<const uint16_t *>(A), *b = static_cast<const uint16_t *>(B);
-    Choice ch = choose(M, N, K, e.splitk_ws && lay != GEMM_NT && !e.bias && !e.residual && aligned16(e.splitk_ws), e.splitk_floats);
-    if (ctx->gemm_tile) ch = {ctx->gemm_tile == 256 ? 0 : 1, 1};
-    const int step = ch.kind < 2 ? 32 : 128, kchunk = ((K + ch.parts - 1) / ch.parts + step - 1) / step * step, parts = (K + kchunk - 1) / kchunk;
+    const Cut ch = cut_of(ctx, lay, M, N, K, e.out_f32, e.splitk_ws && !e.bias && !e.residual && aligned16(e.splitk_ws), e.splitk_floats);
+    const int parts = ch.parts, kchunk = ch.kchunk;
     if (parts > 1) ep = Ep{1.f, nullptr, nullptr, e.splitk_ws, 1, N, N % 4 == 0};
     switch (ch.kind) {
       case 0: launch_pp<256>(stream, lay, M, N, K, a, lda, b, ldb, ep, parts, kchunk); break;
@@ -482,15 +494,37 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
 
 extern "C" twist_status twist_gemm_raw(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, const void *A, int64_t lda, const void *B,
                                        int64_t ldb, void *C, int64_t ldc, int32_t out_f32, float alpha) {
+  return twist_gemm_raw_cut(ctx, layout, M, N, K, A, lda, B, ldb, C, ldc, out_f32, alpha, nullptr, 0);
+}
+
+extern "C" twist_status twist_gemm_raw_cut(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
+                                           void *C, int64_t ldc, int32_t out_f32, float alpha, float *scratch, size_t scratch_floats) {
   if (!ctx || !A || !B || !C) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_raw: null argument");
   if (layout < 0 || layout > 2 || M < 0 || N < 0 || K < 0) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_raw: bad layout or size");
   const int64_t need_a = layout == GEMM_TN ? M : K, need_b = layout == GEMM_NT ? K : N;
   if (lda < need_a || ldb < need_b || ldc < N) TW_FAIL(ctx, TWIST_ESHAPE, "twist_gemm_raw: a row stride is smaller than the row it strides");
+  if (!aligned16(scratch)) TW_FAIL(ctx, TWIST_ESHAPE, "twist_gemm_raw_cut: the scratch must be 16-byte aligned");
   GemmEpilogue e;
   e.alpha = alpha;
   e.out = C;
   e.out_f32 = out_f32;
+  e.splitk_ws = scratch;
+  e.splitk_floats = scratch_floats;
   return twist_gemm(ctx, ctx->d.dtype == TWIST_BF16, (GemmLayout)layout, M, N, K, A, lda, B, ldb, ldc, e);
+}
+
+extern "C" twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats, int32_t chosen[3]) {
+  if (!ctx || !chosen) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_kernel: null argument");
+  if (layout < 0 || layout > 2 || M < 1 || N < 1 || K < 1) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_kernel: bad layout or size");
+  if (ctx->d.dtype == TWIST_BF16) {
+    const Cut ch = cut_of(ctx, (GemmLayout)layout, M, N, K, out_f32, scratch_floats > 0, scratch_floats);
+    chosen[0] = kKinds[ch.kind].bm; chosen[1] = kKinds[ch.kind].bn; chosen[2] = ch.parts;
+  } else {
+    int kchunk;
+    twist_gemm_f32_choice(ctx, M, N, K, scratch_floats > 0, scratch_floats, chosen[0], chosen[2], kchunk);
+    chosen[1] = chosen[0];
+  }
+  return TWIST_OK;
 }
 
 extern "C" twist_status twist_set_overlap(twist_ctx *ctx, int32_t enable) {

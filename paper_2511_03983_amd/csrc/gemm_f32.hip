@@ -256,21 +256,26 @@ Choice choose(int M, int N, int K, bool may_split, size_t split_floats) {
 
 }  // namespace
 
+void twist_gemm_f32_choice(const twist_ctx *ctx, int M, int N, int K, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
+  Choice ch = choose(M, N, K, may_split && !ctx->gemm_tile, split_floats);
+  if (ctx->gemm_tile) ch = {ctx->gemm_tile == 128 ? 128 : 64, 1};
+  const int bk = ch.tile == 128 ? 32 : 64;
+  kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
+  tile = ch.tile;
+  parts = (K + kchunk - 1) / kchunk;
+}
+
 twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
                             int64_t ldc, const GemmEpilogue &e) {
   Ep32 ep{e.alpha, static_cast<const float *>(e.bias), e.residual, static_cast<float *>(e.out), ldc};
   const bool vec = aligned16(A) && aligned16(B) && lda % 4 == 0 && ldb % 4 == 0;
-  const bool may_split = e.splitk_ws && !e.bias && !e.residual && !ctx->gemm_tile;
-  Choice ch = choose(M, N, K, may_split, e.splitk_floats);
-  if (ctx->gemm_tile) ch = {ctx->gemm_tile == 128 ? 128 : 64, 1};
-  const int bk = ch.tile == 128 ? 32 : 64;
-  int kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
-  const int parts = (K + kchunk - 1) / kchunk;
+  int tile, parts, kchunk;
+  twist_gemm_f32_choice(ctx, M, N, K, e.splitk_ws && !e.bias && !e.residual, e.splitk_floats, tile, parts, kchunk);
   if (parts > 1) ep = Ep32{1.f, nullptr, nullptr, e.splitk_ws, N};
   switch (lay) {
-    case GEMM_NT: launch_tile<1, 1>(st, ch.tile, vec, M, N, K, A, lda, B, ldb, ep, parts, kchunk); break;
-    case GEMM_NN: launch_tile<1, 0>(st, ch.tile, vec, M, N, K, A, lda, B, ldb, ep, parts, kchunk); break;
-    case GEMM_TN: launch_tile<0, 0>(st, ch.tile, vec, M, N, K, A, lda, B, ldb, ep, parts, kchunk); break;
+    case GEMM_NT: launch_tile<1, 1>(st, tile, vec, M, N, K, A, lda, B, ldb, ep, parts, kchunk); break;
+    case GEMM_NN: launch_tile<1, 0>(st, tile, vec, M, N, K, A, lda, B, ldb, ep, parts, kchunk); break;
+    case GEMM_TN: launch_tile<0, 0>(st, tile, vec, M, N, K, A, lda, B, ldb, ep, parts, kchunk); break;
   }
   TW_HIP(ctx, hipGetLastError());
   if (parts > 1) return twist_splitk_reduce(ctx, st, e.splitk_ws, parts, M, N, e.out, ldc, 1, e.alpha);

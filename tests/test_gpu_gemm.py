@@ -154,3 +154,47 @@ def test_bf16_nt_projection_edges(lib, tile, M, N, K):
     # fp32 sums of K exact products: 2^-24 sqrt(K) at most; a dropped or repeated chunk of 8 would show as sqrt(8 / K) >= 0.15
     assert float((out.double() - want).norm() / want.norm()) <= 5e-6
     assert torch.isnan(buf[M * N:]).all()
+
+
+# Products whose contraction is cut (tile, then shape): parts of uneven length, a last one shorter than a slice, ragged edges; NN and TN
+@pytest.mark.parametrize("tile,layout,M,N,K", [(32, 2, 136, 200, 5000), (32, 2, 33, 40, 16000), (32, 1, 70, 72, 3000), (64, 2, 768, 192, 8100), (64, 2, 520, 776, 8100),
+                                               (64, 1, 200, 768, 4104), (128, 2, 1536, 776, 4000), (128, 1, 1100, 1032, 4000), (256, 2, 2816, 2048, 4100)])
+def test_cut_bf16_projection(lib, tile, layout, M, N, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
+    scratch = torch.full((1 << 24,), float("nan"), device="cuda")
+    cols, parts = ctx.twist_gemm_kernel(layout, M, N, K, True, scratch.numel())[1:]
+    assert cols == tile and parts > 1, (cols, parts)
+    up = lambda n: (n + 7) // 8 * 8
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, B = (torch.randn((r, up(c)), generator=gen, device="cuda").bfloat16()[:, :c] for r, c in (((K, M) if layout == 2 else (M, K)), (K, N)))
+    want = (A.double().T if layout == 2 else A.double()) @ B.double()
+    for dt in (torch.float32, torch.bfloat16):
+        buf = torch.full((M * N + 64,), float("nan"), dtype=dt, device="cuda")            # what lies behind the result must stay
+        out = buf[:M * N].view(M, N)
+        ctx.twist_gemm_raw_cut(layout, M, N, K, A, B, out, scratch, alpha=0.5)
+        torch.cuda.synchronize()
+        rows = (out.double() - 0.5 * want).norm(dim=1) / (0.5 * want).norm(dim=1)
+        # fp32 sums of K exact products: 2^-24 sqrt(K) at most; one left out or counted twice shows as 1 / sqrt(K), the rounding to bf16 as 2e-3
+        assert float(rows.max()) <= (2.0 ** -24 * K ** 0.5 if dt == torch.float32 else 5e-3)
+        assert torch.isnan(buf[M * N:]).all() and torch.isnan(scratch[parts * M * N:]).all()
+
+
+@pytest.mark.parametrize("tile,layout,M,N,K", [(32, 2, 132, 200, 1100), (32, 1, 131, 72, 2001), (64, 2, 1500, 1500, 2000), (64, 0, 1500, 1500, 1999), (128, 1, 1024, 768, 8003),
+                                               (128, 2, 1023, 769, 8003)])
+def test_cut_fp32_projection(lib, tile, layout, M, N, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    scratch = torch.full((1 << 24,), float("nan"), device="cuda")
+    rows, _, parts = ctx.twist_gemm_kernel(layout, M, N, K, True, scratch.numel())
+    assert rows == tile and parts > 1, (rows, parts)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((K, M) if layout == 2 else (M, K), generator=gen, device="cuda")
+    B = torch.randn((N, K) if layout == 0 else (K, N), generator=gen, device="cuda")
+    want = (A.double().T if layout == 2 else A.double()) @ (B.double().T if layout == 0 else B.double())
+    buf = torch.full((M * N + 64,), float("nan"), device="cuda")
+    out = buf[:M * N].view(M, N)
+    ctx.twist_gemm_raw_cut(layout, M, N, K, A, B, out, scratch, alpha=0.5)
+    torch.cuda.synchronize()
+    rows = (out.double() - 0.5 * want).norm(dim=1) / (0.5 * want).norm(dim=1)
+    # K products of one rounding each and K additions; a product left out shows as 1 / sqrt(K) >= 1e-2
+    assert float(rows.max()) <= 2.0 ** -24 * (2 * K) ** 0.5
+    assert torch.isnan(buf[M * N:]).all() and torch.isnan(scratch[parts * M * N:]).all()
