@@ -361,8 +361,8 @@ __global__ __launch_bounds__(256) void mfma_only_kernel(int iters, float *sink, 
 // first loads and epilogue of every tile, which decide where the contraction is short and the rows are many; s1 = how much slower a
 // slice gets when the whole chip works (clock, memory); the 32x32 kernel's slices take nt of that where both operands are contiguous
 // along k.  A cut contraction adds a launch and one pass over the fp32 partial products.
-// Fitted to 530 products of every layout, sizes 33 to 8192, those of the TN layout cut in up to 16 parts (operands in rotation).  Over
-// 300 others the kernel taken is on average 0.8 % slower than the fastest (without the cost of a tile, and with the rounds of the small
+// Fitted to 800 products of every layout, sizes 1 to 50257, those of the TN layout cut in up to 16 parts (operands in rotation).  Over
+// 300 others the kernel taken is on average 0.6 % slower than the fastest (without the cost of a tile, and with the rounds of the small
 // tiles taken as items / 256, as the rule was: 2.7 %).  Some of them, us:
 //   M x N x K             256x256  256x128   64x64   32x32
 //   128 x 1536 x 2048        42.6     32.0     9.9     6.1
@@ -373,12 +373,13 @@ __global__ __launch_bounds__(256) void mfma_only_kernel(int iters, float *sink, 
 //   8192 x 768 x 192 (NN)    11.4     10.0    15.0    35.6   (fp32 output; the rule took 64x64 here)
 //   8192 x 2048 x 256        15.6     17.4    32.9    81.8
 //   8192 x 3072 x 1024 (NN)  56.9     60.5   108.6   228.3
+//   8192 x 50257 x 64         340      465
 //   1536 x 1536 x 2048 (TN)  39.5     33.8    25.3    47.5   (fp32 output)
 // and cut: 768 x 640 x 4096 (TN) 17.5 whole, 15.2 in two parts, 17.5 in three; 2048 x 1024 x 8192 56 in five, 63 in eight;
 // 256 x 128 x 2048 6.1 whole, 9.0 in eight.
 struct Kind { int bm, bn; double fixed, tile, tile32, s0, s1, nt; };
-constexpr Kind kKinds[] = {{256, 256, 1.0, 8.0, 0.2, 0.40, 0.35, 1.0}, {256, 128, 2.4, 3.4, 1.2, 0.35, 0.23, 1.0}, {64, 64, 3.0, 1.0, 0.1, 0.115, 0.01, 1.0},
-                           {32, 32, 2.8, 0.75, 0.05, 0.07, 0.01, 0.65}};
+constexpr Kind kKinds[] = {{256, 256, 1.0, 9.1, 0.36, 0.434, 0.32, 1.0}, {256, 128, 1.7, 4.4, 1.0, 0.344, 0.23, 1.0}, {64, 64, 2.95, 0.875, 0.19, 0.12, 0.011, 1.0},
+                           {32, 32, 2.5, 0.81, 0.06, 0.068, 0.01, 0.71}};
 struct Choice { int kind, parts; };
 Choice choose(GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split, size_t split_floats) {
   Choice best{0, 1};
@@ -391,7 +392,7 @@ Choice choose(GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split,
       const int64_t items = tiles * parts, rounds = (items + 255) / 256;
       const double share = std::min(1.0, items / 256.0), slice = (kd.s0 + kd.s1 * share) * (lay == GEMM_NT ? kd.nt : 1.0);
       double us = kd.fixed + rounds * (kd.tile + (f32_out || parts > 1 ? kd.tile32 : 0.0) + K / 32.0 / parts * slice);
-      if (parts > 1) us += 3.8 + (parts + 1.0) * M * N * 4.0 / 4.0e6;
+      if (parts > 1) us += 4.4 + (parts + 1.0) * M * N * 4.0 / 2.8e6;
       if (us < best_us) { best_us = us; best = {k, parts}; }
     }
   }

@@ -158,7 +158,7 @@ def test_bf16_nt_projection_edges(lib, tile, M, N, K):
 
 # Products whose contraction is cut (tile, then shape): parts of uneven length, a last one shorter than a slice, ragged edges; NN and TN
 @pytest.mark.parametrize("tile,layout,M,N,K", [(32, 2, 136, 200, 5000), (32, 2, 33, 40, 16000), (32, 1, 70, 72, 3000), (64, 2, 768, 192, 8100), (64, 2, 520, 776, 8100),
-                                               (64, 1, 200, 768, 4104), (128, 2, 1536, 776, 4000), (128, 1, 1100, 1032, 4000), (256, 2, 2816, 2048, 4100)])
+                                               (64, 1, 264, 776, 12008), (128, 2, 1536, 776, 4000), (128, 1, 1100, 1032, 4000), (256, 2, 2816, 2048, 8200)])
 def test_cut_bf16_projection(lib, tile, layout, M, N, K):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
     scratch = torch.full((1 << 24,), float("nan"), device="cuda")
