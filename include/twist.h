@@ -277,8 +277,8 @@ TWIST_API twist_status twist_gemm_raw_cut(twist_ctx *ctx, int32_t layout, int32_
                                           const void *B, int64_t ldb, void *C, int64_t ldc, int32_t out_f32, float alpha, float *scratch,
                                           size_t scratch_floats);
 /* Which matrix-core kernel a projection of this shape runs on where its operands are aligned (host only, for tests and benchmarks):
- * chosen receives the rows and columns of the output tile and the number of parts of the contraction, given a scratch of
- * scratch_floats (0: none). */
+ * chosen receives the rows and columns of the output tile (0: the plain kernel) and the number of parts of the contraction,
+ * given a scratch of scratch_floats (0: none). */
 TWIST_API twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32,
                                          size_t scratch_floats, int32_t chosen[3]);
 

@@ -4,7 +4,7 @@
 //    chip with those (gemm_dl.hip); operands stay in LDS in their memory orientation, and those whose contraction index is the slow axis in memory are
 //    read back with the transposing LDS load.
 //  - fp32 operands: the fp32 matrix instruction (gemm_f32.hip).
-//  - anything else (unaligned bf16 shapes): a plain tiled FMA kernel with arbitrary strides.
+//  - anything else (unaligned bf16 shapes, fp32 contractions of a few elements): a plain tiled FMA kernel with arbitrary strides.
 #include <algorithm>
 
 #include "gemm_tile.h"
@@ -426,6 +426,16 @@ void launch_pp(hipStream_t st, GemmLayout lay, int M, int N, int K, const uint16
 #undef TW_PP
 }
 
+// fp32 contractions within one slice of the plain kernel, with an output too large for the 32x32 tiles: bound by the stores, of which the
+// plain kernel makes shorter work (us, plain / matrix instruction: 8192 x 2048 x 8 32 / 41, 512 x 50257 x 16 50 / 71, 3072 x 768 x 8 (TN)
+// 9.9 / 13.8; from there on the other way: 8192 x 2048 x 32 40 / 38, 4096 x 4096 x 16 (TN) 41 / 37, 768 x 768 x 8 6.2 / 5.2).
+bool short_f32(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K) {
+  if (K > (lay == GEMM_TN ? 8 : 16) || ctx->gemm_tile) return false;
+  int tile, parts, kchunk;
+  twist_gemm_f32_choice(ctx, M, N, K, false, 0, tile, parts, kchunk);
+  return tile > 32;
+}
+
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
@@ -479,7 +489,7 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
     TW_HIP(ctx, hipGetLastError());
     return parts > 1 ? twist_splitk_reduce(ctx, stream, e.splitk_ws, parts, M, N, e.out, ldc, e.out_f32, e.alpha) : TWIST_OK;
   }
-  if (!bf16 && !no_mfma) return twist_gemm_f32(ctx, stream, lay, M, N, K, static_cast<const float *>(A), lda, static_cast<const float *>(B), ldb, ldc, e);
+  if (!bf16 && !no_mfma && !short_f32(ctx, lay, M, N, K)) return twist_gemm_f32(ctx, stream, lay, M, N, K, static_cast<const float *>(A), lda, static_cast<const float *>(B), ldb, ldc, e);
   int64_t sam, sak, sbk, sbn;
   switch (lay) {
     case GEMM_NT: sam = lda; sak = 1; sbk = 1; sbn = ldb; break;
@@ -520,6 +530,8 @@ extern "C" twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_
   if (ctx->d.dtype == TWIST_BF16) {
     const Cut ch = cut_of(ctx, (GemmLayout)layout, M, N, K, out_f32, scratch_floats > 0, scratch_floats);
     chosen[0] = kKinds[ch.kind].bm; chosen[1] = kKinds[ch.kind].bn; chosen[2] = ch.parts;
+  } else if (short_f32(ctx, (GemmLayout)layout, M, N, K)) {
+    chosen[0] = chosen[1] = 0; chosen[2] = 1;
   } else {
     int kchunk;
     twist_gemm_f32_choice(ctx, M, N, K, scratch_floats > 0, scratch_floats, chosen[0], chosen[2], kchunk);

@@ -198,3 +198,21 @@ def test_cut_fp32_projection(lib, tile, layout, M, N, K):
     # K products of one rounding each and K additions; a product left out shows as 1 / sqrt(K) >= 1e-2
     assert float(rows.max()) <= 2.0 ** -24 * (2 * K) ** 0.5
     assert torch.isnan(buf[M * N:]).all() and torch.isnan(scratch[parts * M * N:]).all()
+
+
+# contractions of a few elements: the plain kernel up to 16 (TN: 8), the matrix instruction from there on
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("K", [1, 8, 9, 16, 17])
+def test_fp32_projection_of_a_short_contraction(lib, layout, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    M, N = 2050, 2101
+    assert (ctx.twist_gemm_kernel(layout, M, N, K, True)[0] == 0) == (K <= (8 if layout == 2 else 16))
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.randn((K, M) if layout == 2 else (M, K), generator=gen, device="cuda")
+    B = torch.randn((N, K) if layout == 0 else (K, N), generator=gen, device="cuda")
+    want = (A.double().T if layout == 2 else A.double()) @ (B.double().T if layout == 0 else B.double())
+    out = torch.full((M, N), float("nan"), device="cuda")
+    ctx.twist_gemm_raw(layout, M, N, K, A, B, out)
+    torch.cuda.synchronize()
+    # K products and K additions of one rounding each
+    assert float((out.double() - want).norm() / want.norm()) <= 2.0 ** -24 * (2 * K) ** 0.5
