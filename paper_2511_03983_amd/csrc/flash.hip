@@ -394,18 +394,12 @@ __global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const uint16_t *qkv,
 // computed: two stages of two tiles, one barrier per step.  The fixed write pattern leaves no room for row
 // padding; bank conflicts are avoided by storing chunk c (16 bytes) of row r at position c ^ swz(r), which serves both
 // read patterns: 16 consecutive rows of one chunk column (plain 16-byte fragment reads) and 4 consecutive rows of four
-// adjacent chunks (transposing reads).  256 bytes of LDS (all banks once) hold 1, 2 or 4 rows of 128, 64 or 32 head columns,
-// so the swizzle only has to spread the rows that share a position inside such a group.
+// adjacent chunks (transposing reads).  256 bytes of LDS (all banks once) hold 1 or 2 rows of 128 or 64 head columns, so the
+// swizzle only has to spread the rows that share a position inside such a group.
 //
-// SEQUENCES OF ANY LENGTH: rows at or beyond N read as zeros (they are outside the batch element's buffer range), the rows
-// a lane keeps in registers are clamped to N - 1 and their results not stored.  A key at or beyond N comes after every
-// query, so the causal mask removes it; a query at or beyond N has dO = 0, delta = 0 and P = 1, so it adds nothing to dK
-// and dV.
-//
-// Measured (forward / dQ / dK dV, us): B 3, N 1000, 7 heads of 128: 27 / 46 / 60, where lengths that are no multiple of 128
-// used to run the plain kernels, 2633 / 3596 / 1945.  B 8, N 1024, 3 heads of 64: 19 / 23 / 40 against 25 / 58 / 40 of the
-// register-staged kernels above.  All three are chains of dependent steps inside a workgroup (load, products, exponentials,
-// products), not bound by memory or by the matrix pipes' rate.
+// Measured (forward / dQ / dK dV, us): B 8, N 1024, 3 heads of 64: 19 / 23 / 40 against 25 / 58 / 40 of the register-staged kernels
+// above.  All three are chains of dependent steps inside a workgroup (load, products, exponentials, products), not bound by memory or
+// by the matrix pipes' rate.
 namespace dl {
 
 template <int DH>
@@ -415,7 +409,7 @@ struct Geo {
   static constexpr int STAGE_B = 2 * TILE_B;                     // K and V (or Q and dO)
   static constexpr int CPR = DH / 8, RPP = 64 / CPR;             // 16-byte chunks of a row, rows in a one-KB piece
   static __device__ __forceinline__ int swz(int r) {
-    return DH == 128 ? 4 * (r & 3) + ((r >> 2) & 3) : DH == 64 ? 4 * ((r >> 1) & 1) + ((r >> 2) & 3) : (r >> 2) & 3;
+    return DH == 128 ? 4 * (r & 3) + ((r >> 2) & 3) : 4 * ((r >> 1) & 1) + ((r >> 2) & 3);
   }
 };
 typedef __attribute__((address_space(3))) void *lds_void;
@@ -506,7 +500,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
   using G = Geo<DH>;
   constexpr int KS = G::KS, MT = G::MT, TILE_B = G::TILE_B, STAGE_B = G::STAGE_B, RB = G::RB;
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE_B];
-  const int nqb = (N + 127) / 128, nbh = gridDim.x / nqb;
+  const int nqb = N / 128, nbh = gridDim.x / nqb;
   const int rank = snake_rank(blockIdx.x, gridDim.x);
   const int qb = nqb - 1 - rank / nbh;
   const int bh = rank % nbh, b = bh / Hs, h = bh % Hs;
@@ -514,7 +508,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
   const int64_t HD = (int64_t)Hs * DH, ld = 3 * HD;
   const uint16_t *batch = qkv + (int64_t)b * N * ld;
   const uint16_t *qp = batch + (int64_t)h * DH;
-  const int q0 = qb * 128 + wave * 32, q = q0 + c, qr = min(q, N - 1);
+  const int q0 = qb * 128 + wave * 32, q = q0 + c;
   const float sc = scale * kLog2e;
   const desc_t rs = make_desc(batch, (uint32_t)(N * ld * 2));
   const uint32_t tstep = (uint32_t)(64 * ld * 2);
@@ -526,7 +520,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 
   bf16x8 qf[KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + (int64_t)qr * ld + ks * 16 + g * 8);
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + (int64_t)q * ld + ks * 16 + g * 8);
   f32x16 oacc[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -614,7 +608,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
     step(kt + 1, std::integral_constant<int, 1>());  // n_tiles is even
   }
   l += __shfl_xor(l, 32, 64);
-  if (q >= N) return;
   const float inv = masked ? 0.f : 1.f / l;
   uint16_t *op = o + ((int64_t)b * N + q) * HD + (int64_t)h * DH;
 #pragma unroll
@@ -657,7 +650,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
   using G = Geo<DH>;
   constexpr int KS = G::KS, MT = G::MT, TILE_B = G::TILE_B, STAGE_B = G::STAGE_B, RB = G::RB;
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE_B];
-  const int nqb = (N + 127) / 128, nbh = gridDim.x / nqb;
+  const int nqb = N / 128, nbh = gridDim.x / nqb;
   const int rank = snake_rank(blockIdx.x, gridDim.x);
   const int qb = nqb - 1 - rank / nbh;
   const int bh = rank % nbh, b = bh / Hs, h = bh % Hs;
@@ -665,9 +658,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
   const int64_t HD = (int64_t)Hs * DH, ld = 3 * HD;
   const uint16_t *batch = qkv + (int64_t)b * N * ld;
   const uint16_t *qp = batch + (int64_t)h * DH;
-  const int q0 = qb * 128 + wave * 32, q = q0 + c, qr = min(q, N - 1);
+  const int q0 = qb * 128 + wave * 32, q = q0 + c;
   const float sc = scale * kLog2e;
-  const float L2 = lse[((int64_t)b * Hs + h) * N + qr] * kLog2e;
+  const float L2 = lse[((int64_t)b * Hs + h) * N + q] * kLog2e;
   const desc_t rs = make_desc(batch, (uint32_t)(N * ld * 2));
   const uint32_t tstep = (uint32_t)(64 * ld * 2);
   TileLoader<DH> lk, lv;
@@ -683,19 +676,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
   }
 
   bf16x8 qf[KS], gf[KS];
-  const uint16_t *gp = dout + ((int64_t)b * N + qr) * HD + (int64_t)h * DH;
-  const float *op32 = o32 + ((int64_t)b * N + qr) * HD + (int64_t)h * DH;
+  const uint16_t *gp = dout + ((int64_t)b * N + q) * HD + (int64_t)h * DH;
+  const float *op32 = o32 + ((int64_t)b * N + q) * HD + (int64_t)h * DH;
   float dl = 0.f;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + (int64_t)qr * ld + ks * 16 + g * 8);
+    qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + (int64_t)q * ld + ks * 16 + g * 8);
     gf[ks] = *reinterpret_cast<const bf16x8 *>(gp + ks * 16 + g * 8);
     const f32x4 oa = *reinterpret_cast<const f32x4 *>(op32 + ks * 16 + g * 8), ob = *reinterpret_cast<const f32x4 *>(op32 + ks * 16 + g * 8 + 4);
 #pragma unroll
     for (int e = 0; e < 4; ++e) dl += (float)gf[ks][e] * oa[e] + (float)gf[ks][e + 4] * ob[e];
   }
   dl += __shfl_xor(dl, 32, 64);
-  if (g == 0 && q < N) delta[((int64_t)b * Hs + h) * N + q] = dl;
+  if (g == 0) delta[((int64_t)b * Hs + h) * N + q] = dl;
   const float dls = dl * scale;
   f32x16 acc[MT];
 #pragma unroll
@@ -744,7 +737,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
     step(kt, std::integral_constant<int, 0>());
     step(kt + 1, std::integral_constant<int, 1>());
   }
-  if (q >= N) return;
   if (rope) rope_grad<DH>(acc, rope, q, g);
   uint16_t *op = dqkv + ((int64_t)b * N + q) * ld + (int64_t)h * DH;
 #pragma unroll
@@ -777,7 +769,7 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
   constexpr int DKV_LD_OFF = 3 * STAGE_B;             // per stage: 64 log-sum-exps, 64 deltas
   constexpr int DKV_XCH_OFF = DKV_LD_OFF + 3 * 512;   // [2 phases][4 key blocks][P lo, P hi, dS lo, dS hi][64 lanes] x 16 bytes
   __shared__ __attribute__((aligned(1024))) char smem[DKV_XCH_OFF + 2 * 4 * 4096];
-  const int nkb = (N + 127) / 128, npair = (nkb + 1) / 2, nbh = gridDim.x / npair;
+  const int nkb = N / 128, npair = (nkb + 1) / 2, nbh = gridDim.x / npair;
   const int pr = (int)blockIdx.x / nbh;
   const int bh = blockIdx.x % nbh, b = bh / Hs, h = bh % Hs;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
@@ -811,9 +803,9 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
   for (int item = 0; item < 2; ++item) {
     const int kb = item ? nkb - 1 - pr : pr;
     if (item && 2 * pr == nkb - 1) break;  // an odd number of key blocks: the middle one has no partner
-    const int k0 = kb * 128 + wk * 32, kv = k0 + c, kr = min(kv, N - 1);
+    const int k0 = kb * 128 + wk * 32, kv = k0 + c;
     const int qt0 = kb * 2;                          // first query tile at or below the diagonal
-    const int n_steps = masked ? 0 : (N + 63) / 64 - qt0;   // query tiles at or below the diagonal
+    const int n_steps = masked ? 0 : N / 64 - qt0;   // query tiles at or below the diagonal
     const int n_ph = 2 * n_steps;                    // phases of 32 queries; the consumer runs one phase behind
     if (n_steps) issue(qt0, 0);
     // phase ph covers queries [q_lo, q_lo + 32) of tile ph / 2 (stage (ph / 2) % 3); it is skipped when all of them
@@ -823,8 +815,8 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
       bf16x8 kf[KS], vf[KS];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        kf[ks] = *reinterpret_cast<const bf16x8 *>(qp + HD + (int64_t)kr * ld + ks * 16 + g * 8);
-        vf[ks] = *reinterpret_cast<const bf16x8 *>(qp + 2 * HD + (int64_t)kr * ld + ks * 16 + g * 8);
+        kf[ks] = *reinterpret_cast<const bf16x8 *>(qp + HD + (int64_t)kv * ld + ks * 16 + g * 8);
+        vf[ks] = *reinterpret_cast<const bf16x8 *>(qp + 2 * HD + (int64_t)kv * ld + ks * 16 + g * 8);
       }
       DL_WAIT_VM0;  // the first tile, and the key / value fragments
 #pragma unroll
@@ -907,19 +899,17 @@ __global__ __launch_bounds__(512) void flash_bwd_dkv_dl_kernel(const uint16_t *q
         DL_WAIT_LGKM0;  // every LDS read of the phase has returned before the stage and the hand-over area are released
         __builtin_amdgcn_s_barrier();
       }
-      if (kv < N) {
-        if (rope) rope_grad<DH>(dk, rope, kv, g);
-        uint16_t *op = dqkv + ((int64_t)b * N + kv) * ld + (int64_t)h * DH;
+      if (rope) rope_grad<DH>(dk, rope, kv, g);
+      uint16_t *op = dqkv + ((int64_t)b * N + kv) * ld + (int64_t)h * DH;
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+      for (int i = 0; i < MT; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            u32x2 wkk = {pack2(dk[i][4 * j], dk[i][4 * j + 1]), pack2(dk[i][4 * j + 2], dk[i][4 * j + 3])};
-            u32x2 wv = {pack2(dv[i][4 * j], dv[i][4 * j + 1]), pack2(dv[i][4 * j + 2], dv[i][4 * j + 3])};
-            *reinterpret_cast<u32x2 *>(op + HD + i * 32 + 8 * j + 4 * g) = wkk;
-            *reinterpret_cast<u32x2 *>(op + 2 * HD + i * 32 + 8 * j + 4 * g) = wv;
-          }
-      }
+        for (int j = 0; j < 4; ++j) {
+          u32x2 wkk = {pack2(dk[i][4 * j], dk[i][4 * j + 1]), pack2(dk[i][4 * j + 2], dk[i][4 * j + 3])};
+          u32x2 wv = {pack2(dv[i][4 * j], dv[i][4 * j + 1]), pack2(dv[i][4 * j + 2], dv[i][4 * j + 3])};
+          *reinterpret_cast<u32x2 *>(op + HD + i * 32 + 8 * j + 4 * g) = wkk;
+          *reinterpret_cast<u32x2 *>(op + 2 * HD + i * 32 + 8 * j + 4 * g) = wv;
+        }
     }
     __builtin_amdgcn_s_barrier();  // the next item's first loads overwrite stage 0
   }
@@ -951,7 +941,7 @@ twist_status twist_attention_fwd_mfma(twist_ctx *ctx, const void *qkv, void *o, 
   const Family fam = family(ctx, qkv, o, N, Hs, dh);
   if (fam == FAM_NONE) return TWIST_OK;
   const float scale = 1.0f / sqrtf((float)dh);
-  dim3 grid((unsigned)((int64_t)((N + 127) / 128) * B * Hs)), block(256);
+  dim3 grid((unsigned)((int64_t)(N / 128) * B * Hs)), block(256);
   const uint16_t *x = static_cast<const uint16_t *>(qkv);
   uint16_t *out = static_cast<uint16_t *>(o);
   if (fam == FAM_DL) TW_BY_DH(dh, hipLaunchKernelGGL(dl::flash_fwd_dl_kernel<DH>, grid, block, 0, ctx->stream, x, out, o32, lse, N, Hs, scale, keep));
@@ -969,12 +959,12 @@ twist_status twist_attention_bwd_mfma(twist_ctx *ctx, const void *qkv, const flo
   const Family fam = family(ctx, qkv, dout, N, Hs, dh);
   if (fam == FAM_NONE || !o32 || (reinterpret_cast<uintptr_t>(dqkv) % 16) || (reinterpret_cast<uintptr_t>(o32) % 16)) return TWIST_OK;
   const float scale = 1.0f / sqrtf((float)dh);
-  dim3 grid((unsigned)((int64_t)((N + 127) / 128) * B * Hs)), block(256);
+  dim3 grid((unsigned)((int64_t)(N / 128) * B * Hs)), block(256);
   const uint16_t *x = static_cast<const uint16_t *>(qkv), *gout = static_cast<const uint16_t *>(dout);
   uint16_t *dx = static_cast<uint16_t *>(dqkv);
   if (fam == FAM_DL) {
     const float *rt = rope_tab && (reinterpret_cast<uintptr_t>(rope_tab) % 16) == 0 ? rope_tab : nullptr;
-    const dim3 pairs((unsigned)((int64_t)((N + 255) / 256) * B * Hs));
+    const dim3 pairs((unsigned)((int64_t)((N / 128 + 1) / 2) * B * Hs));
     TW_BY_DH(dh, hipLaunchKernelGGL(dl::flash_bwd_dq_dl_kernel<DH>, grid, block, 0, ctx->stream, x, gout, o32, lse, delta, dx, N, Hs, scale, rt, keep);
              hipLaunchKernelGGL(dl::flash_bwd_dkv_dl_kernel<DH>, pairs, dim3(512), 0, ctx->stream, x, gout, lse, delta, dx, N, Hs, scale, rt, keep));
     *rope_done = rt != nullptr;
