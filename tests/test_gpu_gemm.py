@@ -80,6 +80,7 @@ def test_fp32_projection(lib):
                                    (500, 2300, 136), (513, 2304, 8), (449, 2305, 56), (520, 2048, 648)])
 def test_small_bf16_projection_edges(lib, layout, M, N, K):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
+    assert {ctx.twist_gemm_kernel(layout, M, N, K, f32)[0] for f32 in (False, True)} == {64 if M >= 449 else 32}
     up = lambda n: (n + 7) // 8 * 8
     gen = torch.Generator(device="cuda").manual_seed(M + N + K)
     A, B = ((torch.randn((r, up(c)), generator=gen, device="cuda").bfloat16()[:, :c]) for r, c in
@@ -94,14 +95,15 @@ def test_small_bf16_projection_edges(lib, layout, M, N, K):
         assert torch.isnan(buf[M * N:]).all()
 
 
-# fp32 matrix-instruction kernel: 64- and 128-wide tiles (128 pinned, and by size at 3000 x 2900), ragged edges, contractions that end
-# inside a slice of 32, strides that allow 16-byte loads and strides that do not (odd K, M or N)
-@pytest.mark.parametrize("tile", [0, 128])
+# fp32 matrix-instruction kernel: tiles of 32 (by size), 64 (pinned by 256) and 128 (pinned), ragged edges, contractions that end
+# inside a slice of 32 or 64, strides that allow 16-byte loads and strides that do not (odd K, M or N)
+@pytest.mark.parametrize("tile", [0, 128, 256])
 @pytest.mark.parametrize("layout", [0, 1, 2])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (64, 64, 32), (65, 63, 33), (132, 260, 100), (300, 200, 136), (127, 129, 31), (40, 72, 1028)])
 def test_fp32_projection_edges(lib, tile, layout, M, N, K):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
     ctx.twist_set_kernel_choice(gemm_tile=tile)
+    assert ctx.twist_gemm_kernel(layout, M, N, K, True)[0] == {0: 32, 128: 128, 256: 64}[tile]
     gen = torch.Generator(device="cuda").manual_seed(M + N + K)
     A = torch.randn((K, M) if layout == 2 else (M, K), generator=gen, device="cuda")
     B = torch.randn((N, K) if layout == 0 else (K, N), generator=gen, device="cuda")
@@ -115,9 +117,10 @@ def test_fp32_projection_edges(lib, tile, layout, M, N, K):
     assert torch.isnan(buf[M * N:]).all()
 
 
-def test_fp32_projection_by_size_takes_the_large_tiles(lib):
+@pytest.mark.parametrize("M,N,K,tile", [(3000, 2900, 72, 64), (4000, 3900, 72, 128)])
+def test_fp32_projection_by_size_takes_the_larger_tiles(lib, M, N, K, tile):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
-    M, N, K = 3000, 2900, 72
+    assert ctx.twist_gemm_kernel(0, M, N, K, True)[0] == tile
     gen = torch.Generator(device="cuda").manual_seed(1)
     A, B = torch.randn((M, K), generator=gen, device="cuda"), torch.randn((N, K), generator=gen, device="cuda")
     out = torch.full((M, N), float("nan"), device="cuda")

@@ -43,9 +43,12 @@ CASES = {
     "gpt_bf16_1l": (replace(si.CFG2, n_layers=1, d_model=256, n_heads=4, d_head=64, d_ff=1024, vocab=1003, max_seq=192), 2, 2, 512, 2, 192),
     "llama_bf16_1l": (replace(si.CFG3, n_layers=1, d_model=256, n_heads=4, d_head=128, d_ff=704, vocab=517, max_seq=256), 2, 2, 352, 1, 256),
     "gpt_bf16_n384": (replace(si.CFG2, n_layers=1, d_model=192, n_heads=6, d_head=64, d_ff=768, vocab=515, max_seq=384), 2, 3, 384, 2, 384),
-    # 1024 tokens: the weight-gradient projections (contraction over the tokens) take the split-contraction path
+    # 1024 tokens: weight-gradient projections with a long contraction (over the tokens) and few tiles, still in one piece
     "llama_bf16_t1024": (replace(si.CFG3, n_layers=2, d_model=128, n_heads=2, d_head=64, d_ff=256, vocab=300, max_seq=256), 2, 1, 128, 4, 256),
-    # vocabulary above 32768: the cross-entropy kernel that re-reads the row instead of holding it in registers
+    # 4608 and 1110 tokens: their contraction is cut into parts (test_weight_gradients_of_many_tokens_are_cut)
+    "block_llama_bf16_t4608": (replace(si.CFG4, n_layers=1, d_model=256, n_heads=4, d_head=64, d_ff=1024, max_seq=512), 2, 2, 512, 9, 512),
+    "block_gpt_f32_t1110": (si.ModelCfg(n_layers=1, d_model=96, n_heads=4, d_head=32, d_ff=192, vocab=0, max_seq=370), 2, 2, 96, 3, 370),
+    # vocabulary above 32768: rows of more than 256 threads' registers
     "gpt_bf16_bigvocab": (replace(si.CFG2, n_layers=1, d_model=64, n_heads=2, d_head=32, d_ff=128, vocab=33001, max_seq=32), 2, 1, 64, 2, 32),
     "block_llama_bf16": (replace(si.CFG4, n_layers=1, d_model=256, n_heads=4, d_head=64, d_ff=512, max_seq=128), 2, 2, 256, 2, 128),
     # ReLU, the activation of the paper's analysis (Appendix A.1): scalar kernels (fp32, odd widths) and the 16-byte bf16 kernels
@@ -78,6 +81,18 @@ def _sweep_cases(n=int(os.environ.get("TWIST_SWEEP_CASES", "8"))):      # other 
 
 
 CASES.update(_sweep_cases())
+
+
+@pytest.mark.parametrize("name", ["block_llama_bf16_t4608", "block_gpt_f32_t1110"])
+def test_weight_gradients_of_many_tokens_are_cut(lib, name):
+    cfg, _, hs, fs, B, N = CASES[name]
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    D, HD, F = cfg.d_model, hs * cfg.d_head, fs * cfg.ffn_granule
+    products = ((3 * HD, D), (D, HD), ((2 if cfg.act == "swiglu" else 1) * F, D), (D, F))
+    parts = [ctx.twist_gemm_kernel(2, M, Nn, B * N, True, 1 << 24)[2] for M, Nn in products]
+    assert sum(p > 1 for p in parts) >= 3, parts
+
+
 # the same models with the output projections stored unit-major (their three projections change form)
 for _k in ("gpt_f32", "llama_f32", "gpt_bf16", "llama_bf16"):
     CASES[_k + "_um"] = (replace(CASES[_k][0], out_unit_major=True),) + CASES[_k][1:]
@@ -729,6 +744,7 @@ def test_masked_pass_on_the_kept_blocks_is_the_extracted_subnets_pass(lib, name,
     whole = ctx.twist_sample(1, cfg.n_heads, cfg.n_ffn_units, seed=0)
     full_sub = ctx.twist_extract(whole, fw, 0, store=lib.STORE_GRADS)
     full_sub.storage.view(torch.uint8)[-(full_sub.storage.numel() // 8):].fill_(0x7f)      # gradients must be overwritten, zeros included
+    assert ctx.twist_masked_form(plan, B, N)
     sub = ctx.twist_extract(plan, fw, 1, store=lib.STORE_GRADS)
     tok = torch.tensor(si.tokens_uniform(cfg.vocab, B, N, 9)).cuda()
     x, y = tok[:, :-1].contiguous(), tok[:, 1:].contiguous()
