@@ -61,7 +61,7 @@ def flops_fwd_bwd(cfg, hs, F, B, N):
 # HBM-side bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on this benchmark's own command and
 # calibrated against streaming kernels of known size in the same run (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0; the counter
 # sits behind the L2, so reads served by the Infinity Cache are included).  Source: profiles/bench_hbm_traffic_fetch_write.txt
-TRAFFIC_PROJECTION_LAUNCH = 316.7e6         # average over every projection launch of a forward+backward pass
+TRAFFIC_PROJECTION_LAUNCH = 311.0e6         # average over every projection launch of a forward+backward pass
 TRAFFIC_EXTRACT_LAYER_LAUNCH = 405.2e6      # one layer of one subnet at the 7B shape, unit-major layout
 TRAFFIC_AGGREGATE_LAYER_LAUNCH = 2029.6e6   # one layer, 8 subnets
 
@@ -289,7 +289,7 @@ def bench_movers(args, tw, si, torch, unit_major=True):
 
 
 def bench_golden_ticket(args, tw, si, torch):
-    """configs[4]: forward+backward of the Llama-7B-shaped stack pruned once to 16 of 32 heads and 5504 of 11008
+    """Forward+backward of the Llama-7B-shaped stack pruned once to 16 of 32 heads and 5504 of 11008
     neurons per layer (deployment extract, untimed), next to the unpruned stack at the same batch 2 x 4096."""
     cfg = replace(si.CFG5, out_unit_major=True)
     B, N = 2, 4096
@@ -324,8 +324,9 @@ def bench_golden_ticket(args, tw, si, torch):
 
 
 def bench_mfma_ceiling(tw, si, torch):
-    """The bf16 matrix instruction alone on the whole chip (no loads, about half a second per setting so that the clock
-    settles where the power limit puts it): the ceiling for any kernel built on it, next to the published 2.5 PFLOP/s."""
+    """The 32x32x16 bf16 matrix instruction alone on the whole chip (no loads, about half a second per setting so that the clock
+    settles where the power limit puts it): the ceiling for any kernel built on it (attention and the projections with a
+    rows-contiguous operand; the others use 16x16x32, whose ceiling is about a sixth higher), next to the published 2.5 PFLOP/s."""
     ctx = tw.Context(tw.desc_from_cfg(si.CFG3))
     out = {}
     for tag, rnd in (("constant_operands", False), ("random_operands", True)):
@@ -339,7 +340,7 @@ def bench_mfma_ceiling(tw, si, torch):
 
 
 def bench_gpt2_small(args, tw, si, torch):
-    """configs[1]: GPT-2-small-shaped model (12 layers, d 768, 12 heads, d_ff 3072, vocabulary 50257, tied head), S = 4
+    """GPT-2-small-shaped model (12 layers, d 768, 12 heads, d_ff 3072, vocabulary 50257, tied head), S = 4
     subnets of 3 heads and a disjoint quarter of the neurons each, batch 8 x 1024 uniform tokens: extract, one
     forward+backward per subnet back to back, aggregate."""
     cfg = replace(si.CFG2, out_unit_major=True)
@@ -379,7 +380,7 @@ def bench_gpt2_small(args, tw, si, torch):
            "fwd_bwd_tokens_per_s": B * N / (fb * 1e-3), "fwd_bwd_tflops": fl / (fb * 1e-3) / 1e12,
            "fwd_bwd_frac_mfma_peak": fl / (fb * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
            "whole_pass_tokens_per_s": S * B * N / ((med(t_ex) + med(t_fb) + med(t_ag)) * 1e-3), "loss": loss.item(),
-           "workload": "configs[1]: S=4 disjoint quarter-width subnets (3 of 12 heads, 768 of 3072 neurons), batch 8x1024, tied 50257-token head"}
+           "workload": "GPT-2-small shape, S=4 disjoint quarter-width subnets (3 of 12 heads, 768 of 3072 neurons), batch 8x1024, tied 50257-token head"}
     plan.close()
     del stor, ws, layers, globs, fw
     torch.cuda.empty_cache()
@@ -620,11 +621,11 @@ def main():
         "value": train["tokens_per_s"], "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": train["ms_per_step"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16", "data": "synthetic",
-        "config": {"workload": "llama1b_round: configs[2], 22 layers d=2048 16x128 heads SwiGLU 5632 vocab 32000, S=4 overlapping half-width "
+        "config": {"workload": "llama1b_round: 22 layers d=2048 16x128 heads SwiGLU 5632 vocab 32000, S=4 overlapping half-width "
                                f"subnets, batch 4x2048 Zipf(1.1) tokens, {args.local_steps} local AdamW steps per subnet, sample+extract+train+aggregate; "
                                "output projections stored unit-major",
                    "S": 4, "batch": 4, "seq_len": 2048, "local_steps": args.local_steps},
-        "roofline": {"bound": "mfma", "kernel": "gemm_pp_kernel / gemm_mfma_kernel: every projection launch of one forward+backward per subnet, "
+        "roofline": {"bound": "mfma", "kernel": "gemm_nt_kernel / gemm_pp_kernel / gemm_dl_kernel: every projection launch of one forward+backward per subnet, "
                                                  "kernels serialised on one stream",
                      "achieved": g["tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": g["tflops"] / PEAK_BF16_TFLOPS,
                      "traffic": TRAFFIC_PROJECTION_LAUNCH, "traffic_unit": "bytes per launch behind the L2 (rocprofv3 FETCH_SIZE/WRITE_SIZE, calibrated)",
@@ -640,7 +641,7 @@ def main():
     if movers:
         out["movers_llama7b_stack"] = movers
         out["roofline_movers"] = {
-            "bound": "hbm", "kernel": "extract_kernel / aggregate_rows_kernel at configs[3] (32 layers d=4096, S=8, 50%), output projections unit-major",
+            "bound": "hbm", "kernel": "extract_kernel / aggregate_rows_kernel at the Llama-7B layer stack (32 layers d=4096, S=8, 50%), output projections unit-major",
             "achieved": (movers["extract_alg_GB"] + movers["aggregate_alg_GB"]) / ((movers["extract_ms"] + movers["aggregate_ms"]) * 1e-3),
             "peak": PEAK_HBM_GBS, "unit": "GB/s",
             "frac": (movers["extract_alg_GB"] + movers["aggregate_alg_GB"]) / ((movers["extract_ms"] + movers["aggregate_ms"]) * 1e-3) / PEAK_HBM_GBS,

@@ -340,8 +340,10 @@ TWIST_API twist_status twist_embed_raw(twist_ctx *ctx, const int32_t *tok, int32
 TWIST_API twist_status twist_profile_gemm(twist_ctx *ctx, int32_t enable);
 TWIST_API twist_status twist_profile_gemm_read(twist_ctx *ctx, int64_t *launches, double *ms, double *flops);
 
-/* Measurement aid: the rate of the projection kernels' matrix instruction alone (v_mfma_f32_32x32x16_bf16, operands in
- * registers, no loads, four independent accumulator tiles per wave), with `waves_per_simd` waves on every SIMD of the
+/* Measurement aid: the rate of v_mfma_f32_32x32x16_bf16 alone (the instruction of the attention kernels and of the
+ * projections with a rows-contiguous operand; those with both operands contiguous along the contraction use
+ * v_mfma_f32_16x16x32_bf16, which draws less power and reaches 2.04 PFLOP/s on random operands where this one reaches 1.76).
+ * Operands in registers, no loads, four independent accumulator tiles per wave, with `waves_per_simd` waves on every SIMD of the
  * chip for `iters` iterations of four instructions: the ceiling any kernel built on that instruction has on this chip at
  * the clock it holds under that load.  random_operands = 0 feeds small constants, 1 pseudo-random values of magnitude
  * about one (the chip's power limit, hence its clock, depends on how many operand bits toggle).  sink (dev, at least
@@ -360,10 +362,10 @@ TWIST_API twist_status twist_set_overlap(twist_ctx *ctx, int32_t enable);
 /* Kernel selection for tests (not part of the method): by default every launcher picks its kernel from the shape.
  *   gemm_tile        0 = by shape; 256 or 128 pins the matrix-core projection kernel with tiles of 256x256 or 256x128
  *                    (fp32 models: 64x64 or 128x128) and keeps the contraction in one piece (TWIST_EINVAL for other values);
- *   plain_only       non-zero: projections and attention never use the matrix-core kernels (the plain fp32-arithmetic
- *                    kernels that serve fp32 models and unaligned shapes run instead);
- *   staged_attention non-zero: d_head = 128 attention runs the register-staged tiled kernels instead of the ones fed by
- *                    loads straight into LDS.
+ *   plain_only       non-zero: projections and attention never use the matrix-core kernels, neither the bf16 nor the fp32
+ *                    ones (the plain kernels that serve unaligned shapes run instead);
+ *   staged_attention non-zero: bf16 attention of 64- and 128-wide heads over multiples of 128 tokens runs the register-staged
+ *                    tiled kernels (which serve batch elements of 2 GiB and more) instead of the ones fed by loads straight into LDS.
  * Results stay within the same tolerances under every choice; only speed changes. */
 TWIST_API twist_status twist_set_kernel_choice(twist_ctx *ctx, int32_t gemm_tile, int32_t plain_only, int32_t staged_attention);
 

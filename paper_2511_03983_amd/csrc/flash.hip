@@ -1,6 +1,6 @@
 // Tiled causal attention for bf16 models on the matrix cores (v_mfma_f32_32x32x16_bf16), forward and backward.
 //
-// All kernels work on the fused [T, 3*Hs*dh] q|k|v buffer.
+// All kernels work on the fused [T, 3*Hs*dh] q|k|v buffer, d_head 64 or 128, N a multiple of 128.
 // Layout facts used throughout (32x32x16 MFMA, wave of 64 lanes, g = lane/32, c = lane%32):
 //   A operand (M x K): lane supplies row c, k = 8g .. 8g+7          B operand (K x N): lane supplies column c, same k
 //   D (32 x 32):       lane holds column c, register r holds row 8*(r/4) + 4g + r%4

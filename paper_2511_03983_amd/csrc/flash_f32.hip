@@ -22,10 +22,10 @@
 // query sees a later key's, no key an earlier query's (add_tile).  That costs nothing that can be measured
 // (forward and backward of the first shape below: 80.3 us before, 78.6 since).
 //
-// Measured (forward / dQ / dK dV) on 2 x 512 tokens, 6 heads of 64: 20 / 30 / 37 us against 423 / 905 / 427 us of the plain kernels
-// (a wave per row, a wave reduction per score), and closer to exact arithmetic where a value bias cancels (query / key gradients 1.3e-5 against 3.7e-5).  bf16,
-// 3 x 1000 tokens, 7 heads of 128: 132 / 189 / 310 us against 2633 / 3596 / 1945, with the same error against 64 bits (1.6e-3, the rounding of the results; bf16
-// tiles, at 27 / 46 / 60 us, have 2.0e-3 and in the gradients 2.4e-3).
+// Measured (forward / dQ / dK dV) on 2 x 512 tokens, 6 heads of 64: 20 / 29 / 36 us against 423 / 905 / 427 us of the plain kernels
+// (a wave per row, a wave reduction per score), and closer to exact arithmetic where a value bias cancels (query / key gradients 1.3e-5
+// against 3.7e-5).  bf16, 3 x 1000 tokens, 7 heads of 128: 125 / 182 / 271 us against 2633 / 3596 / 1945, with the same error against
+// 64 bits (1.6e-3, the rounding of the results; in the bf16 tiles it is 2.0e-3, in the gradients 2.4e-3).
 #include "nn.h"
 
 namespace {

@@ -1,8 +1,8 @@
 // Dense projections of the subnet: C = epilogue(op(A) op(B)) with fp32 accumulation.
 //  - bf16 operands: MFMA kernels fed by direct-to-LDS loads: ping-pong kernels with tiles of 256x256 and 256x128 (here; in
 //    gemm_nt.hip where both operands are contiguous along k), and 64x64 and 32x32 tiles for products too small to fill the
-//    chip with those (gemm_dl.hip); operands stay in LDS in their memory orientation, and those whose contraction index is the slow axis in memory are
-//    read back with the transposing LDS load.
+//    chip with those (gemm_dl.hip); operands stay in LDS in their memory orientation, and those whose contraction index is the slow
+//    axis in memory are read back with the transposing LDS load.
 //  - fp32 operands: the fp32 matrix instruction (gemm_f32.hip).
 //  - anything else (unaligned bf16 shapes, fp32 contractions of a few elements): a plain tiled FMA kernel with arbitrary strides.
 #include <algorithm>
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *ws, int
   }
 }
 
-// Measurement aid: nothing but the projection kernels' matrix instruction, four independent accumulator tiles per wave
+// Measurement aid: nothing but the 32x32x16 matrix instruction of the kernels here (gemm_nt.hip uses 16x16x32), four independent accumulator tiles per wave
 // (enough to issue back to back), operands in registers, no loads; the result is stored so that the loop stays.
 // random_operands = 0: small constants (few bits toggle between instructions); 1: four different operand pairs of
 // pseudo-random bf16 values of magnitude ~1 in rotation, which is what the multipliers see in a real projection and

@@ -7,7 +7,8 @@
 //  - the two 32-deep sub-tiles that share a row's 128-byte lines are fetched by consecutive instructions (400 ns per 32 KB), every
 //    second sub-tile, three and four sub-tiles ahead: a ring of five stages, all of the CU's 160 KB;
 //  - 16x16x32 products, B's fragment as first factor, so that a lane ends up with four adjacent columns of one row.
-// 8192^3 855 -> 802 us (1.37 PFLOP/s), 8192 x 6144 x 4096 334 -> 314, 8192 x 32000 x 2048 946 -> 906, 8192 x 5632 x 2048 186 -> 180.
+// Normally distributed operands, both kernels in one session: 8192^3 880 -> 810 us (1.36 PFLOP/s), 8192 x 6144 x 4096 333 -> 289,
+// 8192 x 32000 x 2048 950 -> 858, 8192 x 5632 x 2048 166 -> 147.
 // The same for an operand that is read back with the transposing LDS load gained nothing (its rows of 512 bytes are whole lines already
 // and its memory phase is the longer one): those orientations stay in gemm.hip.
 #include <algorithm>

@@ -43,8 +43,8 @@ twist_status twist_splitk_reduce(twist_ctx *ctx, hipStream_t st, const float *pa
                                  float alpha);
 
 // causal multi-head attention on a fused qkv buffer [T, 3*Hs*dh] (q | k | v); o [T, Hs*dh]; lse [B,Hs,N] fp32.
-// o32 (may be null): the same output unrounded, [T, Hs*dh] fp32, written by the tiled bf16 kernels only; the
-// tiled backward kernels need it (without it, or on shapes they do not cover, the plain kernels run).
+// o32 (may be null): the same output unrounded, [T, Hs*dh] fp32, written for bf16 models by every tiled kernel (in bf16 and in fp32
+// arithmetic), not by the plain ones; the tiled backward kernels need it (without it, or on shapes they do not cover, the plain kernels run).
 // keep (may be null; device, one entry per head): heads with keep[h] < 0 are masked (Masked TwIST, Section 4.1): the forward
 // kernels write zeros for them, the backward kernels zero gradients, and neither visits their keys.
 twist_status twist_attention_fwd(twist_ctx *ctx, int bf16, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh,
