@@ -189,6 +189,7 @@ twist_status twist_attention_fwd(twist_ctx *ctx, int bf16, const void *qkv, void
     bool done = false;
     TW_TRY(twist_attention_fwd_mfma(ctx, qkv, o, o32, lse, B, N, Hs, dh, keep, &done));
     if (done) return TWIST_OK;
+    if (twist_attention_64_ok(ctx, qkv, o, o32, nullptr, nullptr, N, Hs, dh)) return twist_attention_64_fwd(ctx, qkv, o, o32, lse, B, N, Hs, dh, keep);
   }
   if (twist_attention_f32_ok(ctx, qkv, o, bf16 ? o32 : o, o, dh)) return twist_attention_f32_fwd(ctx, bf16, qkv, o, bf16 ? o32 : nullptr, lse, B, N, Hs, dh, keep);
   dim3 grid((unsigned)(((int64_t)B * Hs * N + 3) / 4)), block(256);
@@ -206,6 +207,10 @@ twist_status twist_attention_bwd(twist_ctx *ctx, int bf16, const void *qkv, cons
   if (bf16) {
     bool done = false, rope_done = false;
     TW_TRY(twist_attention_bwd_mfma(ctx, qkv, o_f32, dout, lse, delta, dqkv, B, N, Hs, dh, rope_tab, keep, &done, &rope_done));
+    if (!done && o_f32 && twist_attention_64_ok(ctx, qkv, nullptr, o_f32, dout, dqkv, N, Hs, dh)) {
+      TW_TRY(twist_attention_64_bwd(ctx, qkv, o_f32, dout, lse, delta, dqkv, B, N, Hs, dh, rope_tab, keep, &rope_done));
+      done = true;
+    }
     if (done) return (rope_tab && !rope_done) ? twist_rope_apply(ctx, bf16, dqkv, rope_tab, B, N, Hs, dh, -1.f) : TWIST_OK;
   }
   if (o_f32 && twist_attention_f32_ok(ctx, qkv, o_f32, dout, dqkv, dh)) {

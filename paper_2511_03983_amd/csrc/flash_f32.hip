@@ -1,6 +1,6 @@
 // Tiled causal attention in fp32 arithmetic on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32), forward and backward,
-// d_head a multiple of 4 up to 128, any N: for fp32 models, and (BF) for the bf16 models whose heads or sequence lengths the bf16 tiles
-// of flash.hip do not take: operands and results are bf16 there, probabilities and score gradients stay fp32.
+// d_head a multiple of 4 up to 128, any N: for fp32 models, and (BF) for the bf16 models whose heads are not 32, 64 or 128 wide or whose batch
+// element exceeds 2 GiB (flash64.hip): operands and results are bf16 there, probabilities and score gradients stay fp32.
 //
 // A workgroup owns 32 query rows (forward, dQ) or 32 key rows (dK / dV) of one head; its four waves share out the tiles of 32 keys
 // (or queries) that those rows see, wave w taking tiles w, w + 4, ..., each with accumulators of its own, and the four results are
@@ -24,8 +24,7 @@
 //
 // Measured (forward / dQ / dK dV) on 2 x 512 tokens, 6 heads of 64: 20 / 29 / 36 us against 423 / 905 / 427 us of the plain kernels
 // (a wave per row, a wave reduction per score), and closer to exact arithmetic where a value bias cancels (query / key gradients 1.3e-5
-// against 3.7e-5).  bf16, 3 x 1000 tokens, 7 heads of 128: 125 / 182 / 271 us against 2633 / 3596 / 1945, with the same error against
-// 64 bits (1.6e-3, the rounding of the results; in the bf16 tiles it is 2.0e-3, in the gradients 2.4e-3).
+// against 3.7e-5).
 #include "nn.h"
 
 namespace {

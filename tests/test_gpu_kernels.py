@@ -252,6 +252,39 @@ def test_attention_outside_the_bf16_tiles_keeps_fp32_probabilities(lib, dh, N):
         assert rel_fro(to_numpy(dqkv).reshape(B, N, 3, Hs, dh)[:, :, i], want[i]) <= 1.8e-3, i
 
 
+# the 64-row workgroups with fp32 probabilities: lengths around their tiles, one to four of them; rounding of the results as above, the
+# log-sum-exp (below 10) within a dozen fp32 roundings; a masked head writes zeros and changes nothing for the others
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("N", [63, 66, 97, 191, 193, 255])
+def test_attention_in_64_row_workgroups(lib, dh, N):
+    Hs, B = 3, 2
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=Hs, d_head=dh, d_ff=8, dtype=BF, max_seq=N)))
+    qkv = _dev(_snap(si.normal(dh + N, "qkv", (B * N, 3 * Hs * dh)), BF), BF)
+    dout = _dev(_snap(si.normal(N, "dout", (B * N, Hs * dh)), BF), BF)
+    o, lse, dqkv = ctx.twist_attention_raw(qkv, dout, B, N, Hs)
+    om, _, dm = ctx.twist_attention_raw(qkv, dout, B, N, Hs, keep=torch.tensor([4, -1, 0], dtype=torch.int32).cuda())
+    torch.cuda.synchronize()
+    q, k, v = (to_numpy(qkv).reshape(B, N, 3, Hs, dh)[:, :, i] for i in range(3))
+    want_o, p = omodel.attention_fwd(q, k, v)
+    want = omodel.attention_bwd(p, q, k, v, to_numpy(dout).reshape(B, N, Hs, dh))
+    s = np.einsum("bqhd,bkhd->bhqk", q, k) / np.sqrt(dh)
+    s = np.where(np.tril(np.ones((N, N), bool)), s, -np.inf)
+    assert np.abs(to_numpy(lse).reshape(B, Hs, N) - np.logaddexp.reduce(s, axis=-1)).max() <= 1e-5
+    o, d = to_numpy(o).reshape(B, N, Hs, dh), to_numpy(dqkv).reshape(B, N, 3, Hs, dh)
+    om, dm = to_numpy(om).reshape(B, N, Hs, dh), to_numpy(dm).reshape(B, N, 3, Hs, dh)
+    assert rel_fro(o, want_o) <= 1.8e-3
+    for i in range(3):
+        assert rel_fro(d[:, :, i], want[i]) <= 1.8e-3, i
+    assert not om[:, :, 1].any() and not dm[:, :, :, 1].any()
+    assert np.array_equal(om[:, :, ::2], o[:, :, ::2]) and np.array_equal(dm[:, :, :, ::2], d[:, :, :, ::2])
+    for j in (0, N // 2, N - 1):                      # a token whose value row is infinite: earlier queries keep their bits, later ones see it
+        x = qkv.clone()
+        x.view(B, N, 3, Hs, dh)[0, j, 2, 0, 1] = float("inf")
+        oi = to_numpy(ctx.twist_attention_raw(x, None, B, N, Hs)[0]).reshape(B, N, Hs, dh)
+        assert np.array_equal(oi[0, :j], o[0, :j]) and np.array_equal(oi[1], o[1]), j
+        assert not np.isfinite(oi[0, j, 0, 1]) and np.isfinite(oi[0, :, 0, 2:]).all(), j
+
+
 def test_staged_attention_of_64_wide_heads(lib):
     """The register-staged kernels still serve 64-wide heads of batch elements beyond the pipelined kernels' 2 GiB range."""
     Hs, B, N, dh = 2, 2, 256, 64
