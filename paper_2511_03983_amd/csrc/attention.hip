@@ -181,15 +181,28 @@ twist_status twist_attention_fwd_mfma(twist_ctx *ctx, const void *qkv, void *o, 
 twist_status twist_attention_bwd_mfma(twist_ctx *ctx, const void *qkv, const float *o32, const void *dout, const float *lse, float *delta,
                                       void *dqkv, int B, int N, int Hs, int dh, const float *rope_tab, const int32_t *keep, bool *done, bool *rope_done);
 
+// Whether a form that flash.hip takes runs in the 64-row workgroups of flash64.hip instead: where its 128-row ones are at most one per CU,
+// the longest of them decides and half as much work in it is worth more than the second read of keys and values.
+// Forward / backward, us, 128-row -> 64-row workgroups (number of the former):
+//   (64)  2 x 512 tokens, 8 heads of 64     12.5 / 35.6 -> 11.7 / 20.8     (64)  2 x 512, 8 heads of 128    16.0 / 54.5 -> 14.6 / 36.6
+//   (192) 8 x 1024, 3 heads of 64           17.7 / 58.0 -> 17.2 / 39.1     (192) 2 x 1024, 12 of 128        26.4 / 83.2 -> 25.5 / 62
+//   (256) 1 x 4096, 8 heads of 64           54.8 / 180  -> 48.6 / 120      (256) 1 x 4096, 8 of 128         81 / 246 -> 70 / 183
+//   (320) 4 x 1024, 10 heads of 64          20.2 / 62.8 -> 19.3 / 58.3     (320) 4 x 1024, 10 of 128        30.0 / 88.0 -> 29.5 / 92.0
+//   (512) 4 x 2048, 8 heads of 64           34 / 106    -> 40 / 120        (512) 4 x 2048, 8 of 128         50 / 152 -> 62 / 195
+static bool few_rows(const twist_ctx *ctx, int B, int N, int Hs, int dh) {
+  return !ctx->plain_only && !ctx->staged_attention && N % 128 == 0 && (dh == 64 || dh == 128) && (int64_t)(N / 128) * B * Hs <= 256;
+}
+
 twist_status twist_attention_fwd(twist_ctx *ctx, int bf16, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh,
                                  const int32_t *keep) {
   if (dh > 64 * kE) TW_FAIL(ctx, TWIST_ESHAPE, "attention: d_head=%d above %d is not supported", dh, 64 * kE);
   const float scale = 1.0f / sqrtf((float)dh);
   if (bf16) {
     bool done = false;
-    TW_TRY(twist_attention_fwd_mfma(ctx, qkv, o, o32, lse, B, N, Hs, dh, keep, &done));
+    const bool rows64 = twist_attention_64_ok(ctx, qkv, o, o32, nullptr, nullptr, N, Hs, dh), few = rows64 && few_rows(ctx, B, N, Hs, dh);
+    if (!few) TW_TRY(twist_attention_fwd_mfma(ctx, qkv, o, o32, lse, B, N, Hs, dh, keep, &done));
     if (done) return TWIST_OK;
-    if (twist_attention_64_ok(ctx, qkv, o, o32, nullptr, nullptr, N, Hs, dh)) return twist_attention_64_fwd(ctx, qkv, o, o32, lse, B, N, Hs, dh, keep);
+    if (rows64) return twist_attention_64_fwd(ctx, qkv, o, o32, lse, B, N, Hs, dh, keep, few);
   }
   if (twist_attention_f32_ok(ctx, qkv, o, bf16 ? o32 : o, o, dh)) return twist_attention_f32_fwd(ctx, bf16, qkv, o, bf16 ? o32 : nullptr, lse, B, N, Hs, dh, keep);
   dim3 grid((unsigned)(((int64_t)B * Hs * N + 3) / 4)), block(256);
@@ -206,9 +219,10 @@ twist_status twist_attention_bwd(twist_ctx *ctx, int bf16, const void *qkv, cons
   dim3 grid((unsigned)(((int64_t)B * Hs * N + 3) / 4)), block(256);
   if (bf16) {
     bool done = false, rope_done = false;
-    TW_TRY(twist_attention_bwd_mfma(ctx, qkv, o_f32, dout, lse, delta, dqkv, B, N, Hs, dh, rope_tab, keep, &done, &rope_done));
-    if (!done && o_f32 && twist_attention_64_ok(ctx, qkv, nullptr, o_f32, dout, dqkv, N, Hs, dh)) {
-      TW_TRY(twist_attention_64_bwd(ctx, qkv, o_f32, dout, lse, delta, dqkv, B, N, Hs, dh, rope_tab, keep, &rope_done));
+    const bool rows64 = o_f32 && twist_attention_64_ok(ctx, qkv, nullptr, o_f32, dout, dqkv, N, Hs, dh), few = rows64 && few_rows(ctx, B, N, Hs, dh);
+    if (!few) TW_TRY(twist_attention_bwd_mfma(ctx, qkv, o_f32, dout, lse, delta, dqkv, B, N, Hs, dh, rope_tab, keep, &done, &rope_done));
+    if (!done && rows64) {
+      TW_TRY(twist_attention_64_bwd(ctx, qkv, o_f32, dout, lse, delta, dqkv, B, N, Hs, dh, rope_tab, keep, few, &rope_done));
       done = true;
     }
     if (done) return (rope_tab && !rope_done) ? twist_rope_apply(ctx, bf16, dqkv, rope_tab, B, N, Hs, dh, -1.f) : TWIST_OK;

@@ -1,7 +1,8 @@
-// Causal attention of bf16 models on the matrix cores (v_mfma_f32_32x32x16_bf16) with probabilities and score gradients in fp32, forward
-// and backward: d_head 32, 64 or 128, any N.
+// Causal attention of bf16 models on the matrix cores (v_mfma_f32_32x32x16_bf16) in workgroups of 64 queries or keys, forward and backward,
+// d_head 32, 64 or 128.  TERMS = 3: probabilities and score gradients in fp32, any N.  TERMS = 1: rounded to bf16, as in flash.hip, for the forms of
+// that file where 128-row workgroups are too few to fill the chip (few_rows in attention.hip).
 //
-// What bounded these forms (flash_f32.hip: every product on the fp32 matrix instruction, at a sixteenth of the bf16 rate): the matrix
+// What bounded the former (flash_f32.hip: every product on the fp32 matrix instruction, at a sixteenth of the bf16 rate): the matrix
 // pipes.  q, k, v and dO are bf16, so their products are exact in fp32 and S and dP belong on the bf16 instruction as they are.  A
 // probability or a score gradient is fp32 and is fed to it as three bf16 terms of 8 bits each, whose sum is exactly the fp32 value
 // (terms3); with a bf16 operand on the other side those products are exact as well, and only the order of sums differs from the fp32
@@ -13,7 +14,7 @@
 //
 // Layouts, swizzles and direct-to-LDS loads are those of flash.hip: S^T = K Q^T in the forward and dQ kernels (a lane owns a query), S = Q K^T
 // in the dK / dV kernel (a lane owns a key), two 64-row tiles a stage.  The dK / dV kernel has a producer and a consumer wave per SIMD as there;
-// P and dS are handed over in fp32 and split by the consumer.
+// P and dS are handed over in fp32 (TERMS = 3) and split by the consumer.
 // Rows beyond N: as keys or queries of a tile they read as zeros (outside the buffer's range), in registers they are clamped to N - 1
 // and their results not stored; a key beyond N comes after every query, a query beyond N gets probability zero.
 // An infinity or a NaN reaches what depends on it and nothing else: hidden entries have weight zero, but zero times an infinity or a NaN is a
@@ -21,9 +22,9 @@
 // adds what the columns do see of them.
 //
 // Measured (us, forward / forward and backward; before: the fp32 instruction):        error of the output in fp32, before in brackets
-//   3 x 1000 tokens,  7 heads of 128     35 / 119   (128 / 563)                        1.55e-7 (1.87e-7)
-//   2 x 500, 32 heads of 128             22 / 85    (104 / 461)                        1.36e-7 (1.66e-7)
-//   2 x 3001, 16 heads of 128           192 / 770  (1203 / 5642)
+//   3 x 1000 tokens,  7 heads of 128     32 / 111   (128 / 563)                        1.55e-7 (1.87e-7)
+//   2 x 500, 32 heads of 128             21 / 81    (104 / 461)                        1.36e-7 (1.66e-7)
+//   2 x 3001, 16 heads of 128           168 / 712  (1203 / 5642)
 //   8 x 1000, 3 heads of 64              22 / 76    (59 / 289)                         1.40e-7 (1.66e-7); scores of +-30 3.5e-7 (3.9e-7)
 //   4 x 1024, 8 heads of 32              17 / 61    (41 / 174)
 //   1 x 33, 4 heads of 64                11.5 / 19.5 (11.5 / 34)                       0.75e-7 (0.92e-7)
@@ -33,6 +34,9 @@
 #include "flash_tile.h"
 
 namespace {
+
+constexpr uint32_t kOob = 0x80000000u;  // byte offset beyond every buffer (at most 2 GiB): loads return 0
+#define WAIT_VM_LGKM0(vm) __builtin_amdgcn_s_waitcnt(0x0070 | ((vm) & 15) | ((vm) >> 4) << 14)  // vmcnt(vm < 64), lgkmcnt(0)
 
 // v[r0 .. r0 + 7] as three vectors of bf16 that add up to it exactly: 8 bits of the mantissa each, cut off, not rounded (so that no value
 // becomes infinite); an infinity is (infinity, 0, 0)
@@ -56,6 +60,12 @@ __device__ __forceinline__ void terms3(const f32x16 &v, int r0, bf16x8 (&t)[3]) 
   }
 #pragma unroll
   for (int k = 0; k < 3; ++k) t[k] = __builtin_bit_cast(bf16x8, w[k]);
+}
+// the weights v[r0 .. r0 + 7] as they are fed to the matrix instruction: exactly, in three terms, or rounded to bf16
+template <int TERMS>
+__device__ __forceinline__ void weights(const f32x16 &v, int r0, bf16x8 (&t)[TERMS]) {
+  if constexpr (TERMS == 3) terms3(v, r0, t);
+  else t[0] = pack8(v, r0);
 }
 
 // An operand fragment without its infinities and NaNs (`odd` becomes nonzero if there were any): exponents of all ones carry into the sign
@@ -145,13 +155,13 @@ __device__ __forceinline__ void keep_weights(float *kept, const f32x16 &w, int c
 // add up to the same (snake order); beyond that the longest start first.
 __device__ __forceinline__ int rank_of(int b, int nwg) { return nwg <= 512 ? snake_rank(b, nwg) : b; }
 
-template <int DH>
+template <int DH, int TERMS, int NST>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn64_fwd_kernel(const uint16_t *qkv, uint16_t *o, float *o32, float *lse, int N, int Hs,
                                                                                                float scale, const int32_t *keep) {
   using G = Geo<DH>;
   constexpr int KS = G::KS, MT = G::MT, TILE_B = G::TILE_B, STAGE_B = G::STAGE_B, RB = G::RB, LDR = DH + 4;
-  __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE_B + 4 * 4096];
-  static_assert(2 * 32 * LDR * 4 <= 2 * STAGE_B, "the halves are merged in the stages");
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE_B];
+  static_assert(2 * 32 * LDR * 4 + 1024 <= NST * STAGE_B, "the halves are merged in the stages");
   const int nqb = (N + 63) / 64, nbh = gridDim.x / nqb;
   const int rank = rank_of(blockIdx.x, gridDim.x);
   const int qb = nqb - 1 - rank / nbh, bh = rank % nbh, b = bh / Hs, h = bh % Hs;
@@ -170,12 +180,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
   ro.init(lane);
   const bool masked = keep && keep[h] < 0;  // masked head (Masked TwIST, Section 4.1): no key is visited, zeros are written
   const int n_tiles = masked ? 0 : qb + 1;
-  auto issue = [&](int kt) {
-    char *st = smem + (kt & 1) * STAGE_B;
-    lk.issue(rs, st, (uint32_t)kt * tstep, wave);
-    lv.issue(rs, st + TILE_B, (uint32_t)kt * tstep, wave);
+  auto issue = [&](int kt) {  // (beyond the last tile nothing is fetched, zeros are filled in)
+    char *st = smem + kt % NST * STAGE_B;
+    const uint32_t o = kt < n_tiles ? (uint32_t)kt * tstep : kOob;
+    lk.issue(rs, st, o, wave);
+    lv.issue(rs, st + TILE_B, o, wave);
   };
-  if (n_tiles) issue(0);
+#pragma unroll
+  for (int kt = 0; kt < NST - 1; ++kt) issue(kt);
 
   bf16x8 qf[KS];
   load_row<KS>(qf, qp + (int64_t)min(q, N - 1) * ld, g);
@@ -204,7 +216,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       s[r] = fast_exp2((s[r] - ref) * sc);
-      sum += s[r];
+      if (TERMS == 1 && r % 2) {  // the sum is that of the rounded weights, so that the output is an exact convex combination of the value rows
+        const uint32_t u = pack2(s[r - 1], s[r]);
+        sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, u), __builtin_bit_cast(bf16x2, 0x3f803f80u), sum, false);
+      }
+      if (TERMS == 3) sum += s[r];
     }
     if (__any(mn > m)) {
       const float alpha = mn > m ? fast_exp2((m - ref) * sc) : 1.f;
@@ -219,43 +235,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     uint32_t odd = 0u;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      bf16x8 p[3];
-      terms3(s, 8 * t, p);
+      bf16x8 p[TERMS];
+      weights<TERMS>(s, 8 * t, p);
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         bf16x8 v = frag_tr(Vt + 16 * t * RB, ro.ta[i], ro.tb[i]);
         if (DIAG) v = clean(v, odd);
 #pragma unroll
-        for (int k = 2; k >= 0; --k) acc[i] = MFMA(v, p[k], acc[i]);
+        for (int k = TERMS - 1; k >= 0; --k) acc[i] = MFMA(v, p[k], acc[i]);
       }
     }
     if (DIAG && __any(odd != 0u)) {
-      float *kept = reinterpret_cast<float *>(smem + 2 * STAGE_B + wave * 4096);
+      const int after = (k0 >> 6) + 1 + wave * 4096 / STAGE_B;  // (the stages behind the last tile's are free)
+      float *kept = reinterpret_cast<float *>(smem + after % NST * STAGE_B + wave * 4096 % STAGE_B);
       keep_weights(kept, s, c, g);
       add_left_out<MT>(acc, vp + (int64_t)k0 * ld, ld, min(32, N - k0), g, [&](int j) { return k0 + j <= q; }, [&](int j) { return kept[j * 32 + c]; });
     }
   };
-  auto step = [&](int kt, auto stage_c) {
-    DL_WAIT_VM0;                   // this wave's pieces of tile kt have landed
-    __builtin_amdgcn_s_barrier();  // everybody's have, and everybody is done with the other stage
-    issue(kt + 1);
-    const char *Kt = smem + decltype(stage_c)::value * STAGE_B + kg * 32 * RB;
+  int kt = 0;
+  for (; kt + 1 < n_tiles; ++kt) {
+    WAIT_VM_LGKM0((NST - 2) * 2 * TileLoader<DH>::NP);  // this wave's pieces of tile kt have landed, its reads of the tile before have returned
+    __builtin_amdgcn_s_barrier();                       // everybody's: tile kt can be read, the stage of the one before be overwritten
+    issue(kt + NST - 1);
+    const char *Kt = smem + kt % NST * STAGE_B + kg * 32 * RB;
     body(Kt, Kt + TILE_B, kt * 64 + 32 * kg, std::false_type());
-  };
-  for (int kt = 0; kt + 1 < n_tiles; ++kt) {
-    if (kt & 1) step(kt, std::integral_constant<int, 1>());
-    else step(kt, std::integral_constant<int, 0>());
   }
-  DL_WAIT_VM0;
+  WAIT_VM_LGKM0(0);
   __builtin_amdgcn_s_barrier();
   if (n_tiles && kg <= qg) {  // the last tile: keys 32 .. 63 of it are in the future of queries 0 .. 31
-    const char *Kt = smem + ((n_tiles - 1) & 1) * STAGE_B + kg * 32 * RB;
-    body(Kt, Kt + TILE_B, (n_tiles - 1) * 64 + 32 * kg, std::true_type());
+    const char *Kt = smem + kt % NST * STAGE_B + kg * 32 * RB;
+    body(Kt, Kt + TILE_B, kt * 64 + 32 * kg, std::true_type());
   }
   DL_WAIT_LGKM0;
   __builtin_amdgcn_s_barrier();  // the stages are free
   l += __shfl_xor(l, 32, 64);
-  float *ms = reinterpret_cast<float *>(smem + 2 * STAGE_B), *ls = ms + 128;
+  float *ms = reinterpret_cast<float *>(smem + NST * STAGE_B - 1024), *ls = ms + 128;
   if (g == 0) { ms[wave * 32 + c] = m; ls[wave * 32 + c] = l; }
   __syncthreads();
   const float mo = ms[(wave ^ 2) * 32 + c], lo = ls[(wave ^ 2) * 32 + c];
@@ -277,13 +291,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 }
 
 // delta_q = dO_q . O_q from the unrounded forward output, dS^T = p (dp - delta) scale, dQ^T[dh][q] += K^T[dh][kv] dS^T[kv][q]
-template <int DH>
+template <int DH, int TERMS, int NST>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn64_dq_kernel(const uint16_t *qkv, const uint16_t *dout, const float *o32, const float *lse, float *delta,
                                                                                               uint16_t *dqkv, int N, int Hs, float scale, const float *rope, const int32_t *keep) {
   using G = Geo<DH>;
   constexpr int KS = G::KS, MT = G::MT, TILE_B = G::TILE_B, STAGE_B = G::STAGE_B, RB = G::RB, LDR = DH + 4;
-  __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE_B + 4 * 4096];
-  static_assert(2 * 32 * LDR * 4 <= 2 * STAGE_B, "the halves are merged in the stages");
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE_B];
+  static_assert(2 * 32 * LDR * 4 + 1024 <= NST * STAGE_B, "the halves are merged in the stages");
   const int nqb = (N + 63) / 64, nbh = gridDim.x / nqb;
   const int rank = rank_of(blockIdx.x, gridDim.x);
   const int qb = nqb - 1 - rank / nbh, bh = rank % nbh, b = bh / Hs, h = bh % Hs;
@@ -301,12 +315,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
   ro.init(lane);
   const bool masked = keep && keep[h] < 0;  // masked head: the gradient is zero, nothing is loaded
   const int n_tiles = masked ? 0 : qb + 1;
-  auto issue = [&](int kt) {
-    char *st = smem + (kt & 1) * STAGE_B;
-    lk.issue(rs, st, (uint32_t)kt * tstep, wave);
-    lv.issue(rs, st + TILE_B, (uint32_t)kt * tstep, wave);
+  auto issue = [&](int kt) {  // (beyond the last tile nothing is fetched, zeros are filled in)
+    char *st = smem + kt % NST * STAGE_B;
+    const uint32_t o = kt < n_tiles ? (uint32_t)kt * tstep : kOob;
+    lk.issue(rs, st, o, wave);
+    lv.issue(rs, st + TILE_B, o, wave);
   };
-  if (n_tiles) issue(0);
+#pragma unroll
+  for (int kt = 0; kt < NST - 1; ++kt) issue(kt);
 
   const int64_t at = ((int64_t)b * N + qr) * HD + (int64_t)h * DH, stat = ((int64_t)b * Hs + h) * N + qr;
   const float L = lse[stat];
@@ -343,38 +359,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     uint32_t odd = 0u;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      bf16x8 d[3];
-      terms3(s, 8 * t, d);
+      bf16x8 d[TERMS];
+      weights<TERMS>(s, 8 * t, d);
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         bf16x8 k = frag_tr(Kt + 16 * t * RB, ro.ta[i], ro.tb[i]);
         if (DIAG) k = clean(k, odd);
 #pragma unroll
-        for (int e = 2; e >= 0; --e) acc[i] = MFMA(k, d[e], acc[i]);
+        for (int e = TERMS - 1; e >= 0; --e) acc[i] = MFMA(k, d[e], acc[i]);
       }
     }
     if (DIAG && __any(odd != 0u)) {
-      float *kept = reinterpret_cast<float *>(smem + 2 * STAGE_B + wave * 4096);
+      const int after = (k0 >> 6) + 1 + wave * 4096 / STAGE_B;  // (the stages behind the last tile's are free)
+      float *kept = reinterpret_cast<float *>(smem + after % NST * STAGE_B + wave * 4096 % STAGE_B);
       keep_weights(kept, s, c, g);
       add_left_out<MT>(acc, kp + (int64_t)k0 * ld, ld, min(32, N - k0), g, [&](int j) { return k0 + j <= q; }, [&](int j) { return kept[j * 32 + c]; });
     }
   };
-  auto step = [&](int kt, auto stage_c) {
-    DL_WAIT_VM0;
-    __builtin_amdgcn_s_barrier();
-    issue(kt + 1);
-    const char *Kt = smem + decltype(stage_c)::value * STAGE_B + kg * 32 * RB;
+  int kt = 0;
+  for (; kt + 1 < n_tiles; ++kt) {
+    WAIT_VM_LGKM0((NST - 2) * 2 * TileLoader<DH>::NP);  // this wave's pieces of tile kt have landed, its reads of the tile before have returned
+    __builtin_amdgcn_s_barrier();                       // everybody's: tile kt can be read, the stage of the one before be overwritten
+    issue(kt + NST - 1);
+    const char *Kt = smem + kt % NST * STAGE_B + kg * 32 * RB;
     body(Kt, Kt + TILE_B, kt * 64 + 32 * kg, std::false_type());
-  };
-  for (int kt = 0; kt + 1 < n_tiles; ++kt) {
-    if (kt & 1) step(kt, std::integral_constant<int, 1>());
-    else step(kt, std::integral_constant<int, 0>());
   }
-  DL_WAIT_VM0;
+  WAIT_VM_LGKM0(0);
   __builtin_amdgcn_s_barrier();
-  if (n_tiles && kg <= qg) {
-    const char *Kt = smem + ((n_tiles - 1) & 1) * STAGE_B + kg * 32 * RB;
-    body(Kt, Kt + TILE_B, (n_tiles - 1) * 64 + 32 * kg, std::true_type());
+  if (n_tiles && kg <= qg) {  // the last tile: keys 32 .. 63 of it are in the future of queries 0 .. 31
+    const char *Kt = smem + kt % NST * STAGE_B + kg * 32 * RB;
+    body(Kt, Kt + TILE_B, kt * 64 + 32 * kg, std::true_type());
   }
   DL_WAIT_LGKM0;
   __builtin_amdgcn_s_barrier();
@@ -390,14 +404,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // dV^T[dh][kv] += dO^T[dh][q] P[q][kv], dK^T[dh][kv] += Q^T[dh][q] dS[q][kv].  Wave w (producer) and w + 4 (consumer) share SIMD w: 32 keys
 // (w & 1) and 32 queries (w >> 1) of every 64-query tile.  Three stages (the tile being loaded, the producer's, the consumer's, which is one
 // behind), two hand-over areas; all of the CU's 160 KB at d_head 128, so the log-sum-exps and deltas travel in registers, a tile ahead.
-template <int DH>
+template <int DH, int TERMS, int NST>
 __global__ __launch_bounds__(512) void attn64_dkv_kernel(const uint16_t *qkv, const uint16_t *dout, const float *lse, const float *delta, uint16_t *dqkv, int N, int Hs,
                                                          float scale, const float *rope, const int32_t *keep) {
   using G = Geo<DH>;
   constexpr int KS = G::KS, MT = G::MT, TILE_B = G::TILE_B, STAGE_B = G::STAGE_B, RB = G::RB, LDR = DH + 4;
-  constexpr int XCH = 3 * STAGE_B;  // [2 tiles][4 SIMDs][P, dS][4 register quads][64 lanes] x 16 bytes
-  __shared__ __attribute__((aligned(1024))) char smem[XCH + 2 * 4 * 8192];
-  static_assert(4 * 32 * LDR * 4 <= XCH + 65536, "the halves are merged in the stages");
+  constexpr int XCH = NST * STAGE_B;           // [2 tiles][4 SIMDs][P, dS][4 register quads, or 2 octets in bf16][64 lanes] x 16 bytes
+  constexpr int XB = TERMS == 3 ? 8192 : 4096;
+  constexpr bool LDS_STATS = NST > 3;          // the log-sum-exps and deltas of a tile, 512 bytes a stage
+  constexpr int STATS = XCH + 2 * 4 * XB;
+  __shared__ __attribute__((aligned(1024))) char smem[STATS + (LDS_STATS ? NST * 512 : 0)];
+  static_assert(4 * 32 * LDR * 4 <= XCH + 2 * 4 * XB, "the halves are merged in the stages");
   const int nkb = (N + 63) / 64, nbh = gridDim.x / nkb;
   const int kb = (int)blockIdx.x / nbh, bh = (int)blockIdx.x % nbh, b = bh / Hs, h = bh % Hs;  // early key blocks are the longest: they start first
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
@@ -417,13 +434,24 @@ __global__ __launch_bounds__(512) void attn64_dkv_kernel(const uint16_t *qkv, co
   const bool masked = keep && keep[h] < 0;  // masked head: the gradients are zero, nothing is loaded
   const int k0 = kb * 64 + 32 * kg, kv = k0 + c, kr = min(kv, N - 1);
   const int n_ph = masked ? 0 : nkb - kb;   // query tiles at or below the diagonal
-  auto issue = [&](int ph) {
-    if (producer) lt.issue(rq, smem + (ph % 3) * STAGE_B, (uint32_t)(kb + ph) * qstep, simd);
-    else lt.issue(rg, smem + (ph % 3) * STAGE_B + TILE_B, (uint32_t)(kb + ph) * gstep, simd);
+  const desc_t rst = make_desc(producer ? lse_b : del_b, (uint32_t)(N * 4));
+  auto issue = [&](int ph) {  // (beyond the last tile nothing is fetched, zeros are filled in)
+    char *st = smem + ph % NST * STAGE_B;
+    const bool in = ph < n_ph;
+    if (producer) lt.issue(rq, st, in ? (uint32_t)(kb + ph) * qstep : kOob, simd);
+    else lt.issue(rg, st + TILE_B, in ? (uint32_t)(kb + ph) * gstep : kOob, simd);
+    if (LDS_STATS && simd == 0) dma<4>(rst, smem + STATS + ph % NST * 512 + (producer ? 0 : 256), in ? (uint32_t)((kb + ph) * 256 + lane * 4) : kOob);
+  };
+  // all but the loads of the newest PF - 1 tiles have landed; LDS reads have returned, writes are done
+  constexpr int PF = NST - 2, NP = TileLoader<DH>::NP;
+  auto wait = [&] {
+    if (LDS_STATS && simd == 0) WAIT_VM_LGKM0((PF - 1) * (NP + 1));
+    else WAIT_VM_LGKM0((PF - 1) * NP);
   };
   // tile 0 is on the diagonal: there SIMD (kg 1, qg 0) has nothing, (0, 1) everything, the others a triangle
   const bool idle = kg > qg;
-  if (n_ph) issue(0);
+#pragma unroll
+  for (int ph = 0; ph < PF; ++ph) issue(ph);
   if (producer) {
     bf16x8 kf[KS], vf[KS];
     load_row<KS>(kf, qp + HD + (int64_t)kr * ld, g);
@@ -445,20 +473,27 @@ __global__ __launch_bounds__(512) void attn64_dkv_kernel(const uint16_t *qkv, co
         }
       }
     };
-    if (n_ph) stats(0);
-    DL_WAIT_VM0;  // the first tile, and the key / value fragments
+    if (!LDS_STATS && n_ph) stats(0);
+    DL_WAIT_VM0;  // the first tiles, and the key / value fragments
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(kf[ks]), "+v"(vf[ks]));  // (used here: the compiler may not sink the loads, and its waits for them, into the loop)
     __builtin_amdgcn_s_barrier();
     for (int ph = 0; ph <= n_ph; ++ph) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { L[k] = Ln[k]; D[k] = Dn[k]; }
-      if (ph + 1 < n_ph) {
-        stats(ph + 1);
-        issue(ph + 1);
+      for (int k = 0; k < 4; ++k) {
+        if (LDS_STATS) {
+          const char *st = smem + STATS + ph % NST * 512 + (32 * qg + 8 * k + 4 * g) * 4;
+          L[k] = *reinterpret_cast<const f32x4 *>(st);
+          D[k] = *reinterpret_cast<const f32x4 *>(st + 256);
+        } else {
+          L[k] = Ln[k];
+          D[k] = Dn[k];
+        }
       }
+      if (!LDS_STATS && ph + 1 < n_ph) stats(ph + 1);
+      issue(ph + PF);
       if (ph < n_ph && !(idle && ph == 0)) {
-        const char *Qt = smem + (ph % 3) * STAGE_B + qg * 32 * RB, *Gt = Qt + TILE_B;
+        const char *Qt = smem + ph % NST * STAGE_B + qg * 32 * RB, *Gt = Qt + TILE_B;
         f32x16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
@@ -477,17 +512,26 @@ __global__ __launch_bounds__(512) void attn64_dkv_kernel(const uint16_t *qkv, co
           dp[r] = hidden ? 0.f : ds;
           s[r] = hidden ? 0.f : p;
         }
-        f32x4 *X = reinterpret_cast<f32x4 *>(smem + XCH + ((ph & 1) * 4 + simd) * 8192);
+        char *X = smem + XCH + ((ph & 1) * 4 + simd) * XB + 16 * lane;
+        if (TERMS == 3) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          X[64 * k + lane] = f32x4{s[4 * k], s[4 * k + 1], s[4 * k + 2], s[4 * k + 3]};
-          X[256 + 64 * k + lane] = f32x4{dp[4 * k], dp[4 * k + 1], dp[4 * k + 2], dp[4 * k + 3]};
+          for (int k = 0; k < 4; ++k) {
+            *reinterpret_cast<f32x4 *>(X + 1024 * k) = f32x4{s[4 * k], s[4 * k + 1], s[4 * k + 2], s[4 * k + 3]};
+            *reinterpret_cast<f32x4 *>(X + 4096 + 1024 * k) = f32x4{dp[4 * k], dp[4 * k + 1], dp[4 * k + 2], dp[4 * k + 3]};
+          }
+        } else {
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            *reinterpret_cast<bf16x8 *>(X + 1024 * k) = pack8(s, 8 * k);
+            *reinterpret_cast<bf16x8 *>(X + 2048 + 1024 * k) = pack8(dp, 8 * k);
+          }
         }
       }
-      DL_WAIT_VM0;    // this wave's pieces of the next tile have landed
-      DL_WAIT_LGKM0;  // the hand-over is written
+      wait();  // this wave's pieces of the next tile have landed, the hand-over is written
       __builtin_amdgcn_s_barrier();
     }
+    DL_WAIT_VM0;
+    __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_s_barrier();  // (the consumers' exchange below)
   } else {
     f32x16 dk[MT], dv[MT];
@@ -497,21 +541,26 @@ __global__ __launch_bounds__(512) void attn64_dkv_kernel(const uint16_t *qkv, co
     __builtin_amdgcn_s_barrier();
     auto body = [&](int pp, auto diag_c) {
       constexpr bool DIAG = decltype(diag_c)::value;
-      const char *Qt = smem + (pp % 3) * STAGE_B + qg * 32 * RB, *Gt = Qt + TILE_B;
-      const float *X = reinterpret_cast<const float *>(smem + XCH + ((pp & 1) * 4 + simd) * 8192);
+      const char *Qt = smem + pp % NST * STAGE_B + qg * 32 * RB, *Gt = Qt + TILE_B;
+      const char *X = smem + XCH + ((pp & 1) * 4 + simd) * XB;
       uint32_t odd_v = 0u, odd_k = 0u;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        f32x16 w;  // P, dS of the lane's 8 rows of this half
+        bf16x8 pt[TERMS], dt[TERMS];
+        if constexpr (TERMS == 3) {
+          f32x16 w;  // P, dS of the lane's 8 rows of this half
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const f32x4 x = *reinterpret_cast<const f32x4 *>(X + (k >> 1) * 1024 + (2 * t + (k & 1)) * 256 + 4 * lane);
+          for (int k = 0; k < 4; ++k) {
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(X + (k >> 1) * 4096 + (2 * t + (k & 1)) * 1024 + 16 * lane);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) w[4 * k + e] = x[e];
+            for (int e = 0; e < 4; ++e) w[4 * k + e] = x[e];
+          }
+          terms3(w, 0, pt);
+          terms3(w, 8, dt);
+        } else {
+          pt[0] = *reinterpret_cast<const bf16x8 *>(X + t * 1024 + 16 * lane);
+          dt[0] = *reinterpret_cast<const bf16x8 *>(X + 2048 + t * 1024 + 16 * lane);
         }
-        bf16x8 pt[3], dt[3];
-        terms3(w, 0, pt);
-        terms3(w, 8, dt);
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
           bf16x8 x = frag_tr(Gt + 16 * t * RB, ro.ta[i], ro.tb[i]), y = frag_tr(Qt + 16 * t * RB, ro.ta[i], ro.tb[i]);
@@ -520,7 +569,7 @@ __global__ __launch_bounds__(512) void attn64_dkv_kernel(const uint16_t *qkv, co
             y = clean(y, odd_k);
           }
 #pragma unroll
-          for (int k = 2; k >= 0; --k) {
+          for (int k = TERMS - 1; k >= 0; --k) {
             dv[i] = MFMA(x, pt[k], dv[i]);
             dk[i] = MFMA(y, dt[k], dk[i]);
           }
@@ -529,21 +578,26 @@ __global__ __launch_bounds__(512) void attn64_dkv_kernel(const uint16_t *qkv, co
       if (DIAG) {
         const int q0 = (kb + pp) * 64 + 32 * qg, rows = min(32, N - q0);
         auto seen = [&](int j) { return q0 + j >= kv; };
-        auto at = [&](const float *x, int j) { return x[(j >> 3) * 256 + (((j >> 2) & 1) * 32 + c) * 4 + (j & 3)]; };
-        if (__any(odd_v != 0u)) add_left_out<MT>(dv, gp + (int64_t)q0 * HD, HD, rows, g, seen, [&](int j) { return at(X, j); });
-        if (__any(odd_k != 0u)) add_left_out<MT>(dk, qp + (int64_t)q0 * ld, ld, rows, g, seen, [&](int j) { return at(X + 1024, j); });
+        auto at = [&](int part, int j) {  // P or dS of row j, register 4 (j / 8) + j % 4 of half j / 4 % 2, and the lane's column
+          const int r = 4 * (j >> 3) + (j & 3), l = ((j >> 2) & 1) * 32 + c;
+          if (TERMS == 3) return *reinterpret_cast<const float *>(X + part * 4096 + (r >> 2) * 1024 + 16 * l + 4 * (r & 3));
+          return __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t *>(X + part * 2048 + (r >> 3) * 1024 + 16 * l + 2 * (r & 7)) << 16);
+        };
+        if (__any(odd_v != 0u)) add_left_out<MT>(dv, gp + (int64_t)q0 * HD, HD, rows, g, seen, [&](int j) { return at(0, j); });
+        if (__any(odd_k != 0u)) add_left_out<MT>(dk, qp + (int64_t)q0 * ld, ld, rows, g, seen, [&](int j) { return at(1, j); });
       }
     };
     auto phase = [&](int ph, auto work) {
-      if (ph + 1 < n_ph) issue(ph + 1);
+      issue(ph + PF);
       work();
-      DL_WAIT_VM0;
-      DL_WAIT_LGKM0;  // every LDS read of the tile has returned before the stage and the hand-over area are released
+      wait();  // ... and every LDS read of the tile has returned before the stage and the hand-over area are released
       __builtin_amdgcn_s_barrier();
     };
     phase(0, [] {});
     if (n_ph) phase(1, [&] { if (!idle) body(0, std::true_type()); });
     for (int ph = 2; ph <= n_ph; ++ph) phase(ph, [&] { body(ph - 1, std::false_type()); });
+    DL_WAIT_VM0;                   // the zero fills beyond the last tile
+    __builtin_amdgcn_s_barrier();  // everybody's
     // the two query halves are added: the consumers of the first finish dK, those of the second dV
     float *rows = reinterpret_cast<float *>(smem) + (kg * 32 + c) * LDR;  // dV of the first half; 64 rows further: dK of the second
     if (qg == 0) put_rows<MT>(rows, dv, g);
@@ -567,11 +621,17 @@ bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
 
-#define TW_DH64(dh, expr)                                 \
-  do {                                                    \
-    if ((dh) == 32) { constexpr int DH = 32; expr; }      \
-    else if ((dh) == 64) { constexpr int DH = 64; expr; } \
-    else { constexpr int DH = 128; expr; }                \
+// runs `expr` with DH standing for the head width, TERMS for the terms of a weight, NSQ and NSK for the stages of the forward and dQ kernels
+// and of the dK / dV kernel.  64- and 32-wide heads: a few more stages than two and three are free and save the backward kernels up to 14 %
+// (1 x 2048 tokens, 8 heads of 64: 66.8 -> 57.7 us); 128-wide ones: four stages leave one forward or dQ workgroup on a CU
+// (1 x 4096, 4 heads: 74 -> 91 us).
+#define TW_DH64(dh, rounded, expr)                                                                       \
+  do {                                                                                                   \
+    if ((dh) == 32) { constexpr int DH = 32, TERMS = 3, NSQ = 4, NSK = 5; expr; }                        \
+    else if ((dh) == 64 && !(rounded)) { constexpr int DH = 64, TERMS = 3, NSQ = 4, NSK = 5; expr; }     \
+    else if ((dh) == 64) { constexpr int DH = 64, TERMS = 1, NSQ = 4, NSK = 5; expr; }                   \
+    else if (!(rounded)) { constexpr int DH = 128, TERMS = 3, NSQ = 2, NSK = 3; expr; }                  \
+    else { constexpr int DH = 128, TERMS = 1, NSQ = 2, NSK = 3; expr; }                                  \
   } while (0)
 
 // Everything in bf16 with these head widths that flash.hip does not take; faster than flash_f32.hip at every size tried (figures above).
@@ -580,23 +640,23 @@ bool twist_attention_64_ok(const twist_ctx *ctx, const void *qkv, const void *o,
   return !ctx->plain_only && (dh == 32 || dh == 64 || dh == 128) && (int64_t)N * 3 * Hs * dh * 2 < (1ll << 31) && al16(qkv) && al16(o) && al16(o32) && al16(dout) && al16(dqkv);
 }
 
-twist_status twist_attention_64_fwd(twist_ctx *ctx, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep) {
+twist_status twist_attention_64_fwd(twist_ctx *ctx, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep, bool rounded) {
   const dim3 grid((unsigned)((int64_t)((N + 63) / 64) * B * Hs)), block(256);
-  TW_DH64(dh, hipLaunchKernelGGL(attn64_fwd_kernel<DH>, grid, block, 0, ctx->stream, static_cast<const uint16_t *>(qkv), static_cast<uint16_t *>(o), o32, lse, N, Hs,
+  TW_DH64(dh, rounded, hipLaunchKernelGGL((attn64_fwd_kernel<DH, TERMS, NSQ>), grid, block, 0, ctx->stream, static_cast<const uint16_t *>(qkv), static_cast<uint16_t *>(o), o32, lse, N, Hs,
                                  1.0f / sqrtf((float)dh), keep));
   TW_HIP(ctx, hipGetLastError());
   return TWIST_OK;
 }
 
 twist_status twist_attention_64_bwd(twist_ctx *ctx, const void *qkv, const float *o32, const void *dout, const float *lse, float *delta, void *dqkv, int B, int N, int Hs, int dh,
-                                    const float *rope_tab, const int32_t *keep, bool *rope_done) {
+                                    const float *rope_tab, const int32_t *keep, bool rounded, bool *rope_done) {
   const dim3 grid((unsigned)((int64_t)((N + 63) / 64) * B * Hs));
   const float scale = 1.0f / sqrtf((float)dh);
   const uint16_t *x = static_cast<const uint16_t *>(qkv), *gout = static_cast<const uint16_t *>(dout);
   uint16_t *dx = static_cast<uint16_t *>(dqkv);
   const float *rt = rope_tab && al16(rope_tab) && dh >= 64 ? rope_tab : nullptr;
-  TW_DH64(dh, hipLaunchKernelGGL(attn64_dq_kernel<DH>, grid, dim3(256), 0, ctx->stream, x, gout, o32, lse, delta, dx, N, Hs, scale, rt, keep);
-          hipLaunchKernelGGL(attn64_dkv_kernel<DH>, grid, dim3(512), 0, ctx->stream, x, gout, lse, delta, dx, N, Hs, scale, rt, keep));
+  TW_DH64(dh, rounded, hipLaunchKernelGGL((attn64_dq_kernel<DH, TERMS, NSQ>), grid, dim3(256), 0, ctx->stream, x, gout, o32, lse, delta, dx, N, Hs, scale, rt, keep);
+          hipLaunchKernelGGL((attn64_dkv_kernel<DH, TERMS, NSK>), grid, dim3(512), 0, ctx->stream, x, gout, lse, delta, dx, N, Hs, scale, rt, keep));
   TW_HIP(ctx, hipGetLastError());
   *rope_done = rt != nullptr;
   return TWIST_OK;

@@ -58,9 +58,10 @@ twist_status twist_attention_bwd(twist_ctx *ctx, int bf16, const void *qkv, cons
 // bf16 models outside flash.hip's tiles: the kernels with fp32 probabilities on the bf16 instruction, and whether they cover the operands
 // (null: not asked about)
 bool twist_attention_64_ok(const twist_ctx *ctx, const void *qkv, const void *o, const void *o32, const void *dout, const void *dqkv, int N, int Hs, int dh);
-twist_status twist_attention_64_fwd(twist_ctx *ctx, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep);
+twist_status twist_attention_64_fwd(twist_ctx *ctx, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep,
+                                    bool rounded);
 twist_status twist_attention_64_bwd(twist_ctx *ctx, const void *qkv, const float *o32, const void *dout, const float *lse, float *delta, void *dqkv, int B, int N, int Hs, int dh,
-                                    const float *rope_tab, const int32_t *keep, bool *rope_done);
+                                    const float *rope_tab, const int32_t *keep, bool rounded, bool *rope_done);
 // the tiled fp32 kernels behind the two calls above, and whether they cover the operands
 bool twist_attention_f32_ok(const twist_ctx *ctx, const void *qkv, const void *o, const void *dout, const void *dqkv, int dh);
 twist_status twist_attention_f32_fwd(twist_ctx *ctx, int bf16, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep);

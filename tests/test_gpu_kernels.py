@@ -285,6 +285,31 @@ def test_attention_in_64_row_workgroups(lib, dh, N):
         assert not np.isfinite(oi[0, j, 0, 1]) and np.isfinite(oi[0, :, 0, 2:]).all(), j
 
 
+# more 128-row workgroups than CUs (3 to 1 blocks of a sequence times many heads): the kernels of 128 rows; the same heads one sequence at a time
+# are few enough for the 64-row ones.  Both against the checker, with a head mask, through the rotary backward
+@pytest.mark.parametrize("dh,N,Hs,B", [(64, 128, 129, 2), (128, 384, 43, 2), (64, 640, 26, 2)])
+def test_attention_with_many_and_with_few_workgroups(lib, dh, N, Hs, B):
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(arch="llama", d_model=64, n_heads=Hs, d_head=dh, d_ff=8, rope=True, dtype=BF, max_seq=N)))
+    qkv = _dev(_snap(si.normal(dh + N, "qkv", (B * N, 3 * Hs * dh)), BF), BF)
+    dout = _dev(_snap(si.normal(N, "dout", (B * N, Hs * dh)), BF), BF)
+    keep_np = np.where(np.arange(Hs) % 5 == 1, -1, 2).astype(np.int32)
+    keep, on = torch.tensor(keep_np).cuda(), keep_np >= 0
+    many = ctx.twist_attention_raw(qkv, dout, B, N, Hs, keep=keep, rope_backward=True)
+    few = ctx.twist_attention_raw(qkv[:N], dout[:N], 1, N, Hs, keep=keep, rope_backward=True)
+    torch.cuda.synchronize()
+    q, k, v = (to_numpy(qkv[:N]).reshape(1, N, 3, Hs, dh)[:, :, i] for i in range(3))
+    want_o, p = omodel.attention_fwd(q, k, v)
+    dq, dk, dv = omodel.attention_bwd(p, q, k, v, to_numpy(dout[:N]).reshape(1, N, Hs, dh))
+    cos, sin = omodel.rope_tables(N, dh, 1e4)
+    want = (omodel.rope_apply(dq, cos, sin, -1.0), omodel.rope_apply(dk, cos, sin, -1.0), dv)
+    for o, _, d in (many, few):
+        o, d = to_numpy(o[:N]).reshape(1, N, Hs, dh), to_numpy(d[:N]).reshape(1, N, 3, Hs, dh)
+        assert not o[:, :, ~on].any() and not d[:, :, :, ~on].any()
+        assert rel_fro(o[:, :, on], want_o[:, :, on]) <= 5e-3
+        for i in range(3):
+            assert rel_fro(d[:, :, i][:, :, on], want[i][:, :, on]) <= 5e-3, i
+
+
 def test_staged_attention_of_64_wide_heads(lib):
     """The register-staged kernels still serve 64-wide heads of batch elements beyond the pipelined kernels' 2 GiB range."""
     Hs, B, N, dh = 2, 2, 256, 64
