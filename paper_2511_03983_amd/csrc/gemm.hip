@@ -432,7 +432,7 @@ void launch_pp(hipStream_t st, GemmLayout lay, int M, int N, int K, const uint16
 bool short_f32(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K) {
   if (K > (lay == GEMM_TN ? 8 : 16) || ctx->gemm_tile) return false;
   int tile, parts, kchunk;
-  twist_gemm_f32_choice(ctx, M, N, K, false, 0, tile, parts, kchunk);
+  twist_gemm_f32_choice(ctx, lay, M, N, K, false, 0, tile, parts, kchunk);
   return tile > 32;
 }
 
@@ -534,7 +534,7 @@ extern "C" twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_
     chosen[0] = chosen[1] = 0; chosen[2] = 1;
   } else {
     int kchunk;
-    twist_gemm_f32_choice(ctx, M, N, K, scratch_floats > 0, scratch_floats, chosen[0], chosen[2], kchunk);
+    twist_gemm_f32_choice(ctx, (GemmLayout)layout, M, N, K, scratch_floats > 0, scratch_floats, chosen[0], chosen[2], kchunk);
     chosen[1] = chosen[0];
   }
   return TWIST_OK;

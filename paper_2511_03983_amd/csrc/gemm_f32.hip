@@ -1,21 +1,25 @@
-// Dense projections of fp32 models on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: exact fp32 products, fp32
-// accumulation, the same precision as the vector units at the matrix pipes' issue rate).
+// Dense projections of fp32 models on the matrix cores.
 //
-// Workgroup tile BM x BN, four waves, the contraction walked in slices of BK that are double-buffered in LDS (the next slice's
-// global loads are in flight while the current one is multiplied, one barrier per slice).  The waves divide the tile (WK = 1), or
-// the slice (WK = 4: every wave forms the whole 32x32 tile over a quarter of each slice, and the four results are added in wave
-// order at the end).
-// An operand tile lies in LDS in the orientation of its memory:
-//   k contiguous ("KM"): LDS [rows][BK + 4]; a lane reads 4 consecutive k at once (16 bytes), good for four MFMAs;
-//   rows contiguous:     LDS [BK][rows + 8]; a lane reads one k row's element per MFMA, consecutive lanes consecutive banks.
-// MFMA number 4 u + j of a slice contracts k = 8 u + j (lanes 0-31) and 8 u + 4 + j (lanes 32-63): the order of k inside a slice
-// is free as long as both operands agree.  Both paddings make the reads conflict-free (16 rows of BK + 4 floats start in 16
-// different bank groups; the two halves of a wave read k rows that are 4 (rows + 8) floats, i.e. 32 banks, apart).
-// Bound by the matrix pipes (256 flop per cycle and CU: 157 TFLOP/s at 2.4 GHz) and by how evenly the tiles fill 256 CUs; see
-// choose() for which tile is taken.
-// Measured: 4096^3 1.11 ms (124 TFLOP/s) with 128 tiles; 1024 x 1152 x 768 28-31 us with 32 tiles, 34-37 with 64, 69 with 128;
-// 8192 x 768 x 768 103 us with 64 tiles, 115 with 128; 256 x 192 x 128 5 us with 32 tiles, 8 with 64.  The plain fp32-arithmetic
-// kernel that ran before reached 10-12 TFLOP/s (307 us on average where these take 40).
+// Tiles of 128 and 64: gemm_f32_kernel, on the bf16 instruction (v_mfma_f32_32x32x16_bf16, sixteen times the rate of the fp32 one).  An fp32
+// value is the sum of three bf16 values (8 bits each, rounded to nearest, the last one exactly what is left), a product of two bf16 values is exact in
+// fp32, and of the nine products of two such sums the six largest are formed: what is left out is below 2^-26 of the product, against 2^-24 for
+// one rounding of fp32.  The sums run in fp32 as before, in fewer steps (one per 16 products), the small products in a sum of their own.  Error
+// against 64 bits on normal operands, the fp32 instruction in brackets: K = 384 0.8e-7 (1.8e-7), 768 1.1e-7 (2.5e-7 to 5.0e-7), 4096 2.7e-7 (11.5e-7),
+// 50257 in 16 parts 2.5e-7 (10e-7); one sum for all six products: K = 768 3.0e-7.
+// Tiles of 32, for few rows: gemm_f32_small_kernel, on the fp32 instruction (v_mfma_f32_32x32x2_f32): there every value would be split into
+// its terms for 32 products only.
+//
+// Both: four or eight waves, the contraction walked in slices of BK that are double-buffered in LDS, one barrier per slice.  The waves
+// divide the tile, and (WK) the slice: their results are added in wave order at the end.
+// gemm_f32_kernel: three slices are in flight to registers; their terms are formed on the way to LDS, in the orientation of the memory:
+//   k contiguous ("KM"): [rows][BK + 8], plain 16-byte fragment reads;      rows contiguous: [BK][rows + 16], transposing reads.
+// gemm_f32_small_kernel: one slice in flight;
+//   k contiguous: LDS [rows][BK + 4], a lane reads 4 consecutive k at once, good for four MFMAs;      rows contiguous: [BK][rows + 8].
+//   MFMA number 4 u + j of a slice contracts k = 8 u + j (lanes 0-31) and 8 u + 4 + j (lanes 32-63): the order of k inside a slice
+//   is free as long as both operands agree.  Both paddings make the reads conflict-free.
+// Measured, us (before: the fp32 instruction in all tiles): 4096^3 805 (1107), 4096 x 2048 x 2048 222 (286), 1024 x 50257 x 768 595 (741) and its
+// gradients 580 (735) and 555 (699), 8192 x 768 x 768 89 (103), 1024 x 1536 x 768 30 (37), 1152 x 768 x 1024 (TN) 25 (30).  What bounds the large
+// ones is the rate of the bf16 instruction at the power limit (six of them per product: 1.04 PFLOP/s in 4096^3), the small ones the chain of slices.
 // Strides and bases that do not allow 16-byte loads go through the scalar loader (VEC = 0).
 #include <algorithm>
 
@@ -23,11 +27,113 @@
 
 namespace {
 
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {  // round to nearest even
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+// four floats as three vectors of bf16 that add up to them exactly (an infinity, a NaN or what rounds to infinity gives a NaN)
+__device__ __forceinline__ void split(f32x4 v, u32x2 (&t)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    t[k] = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    if (k == 2) break;
+    v[0] -= __uint_as_float(t[k].x << 16);
+    v[1] -= __uint_as_float(t[k].x & 0xffff0000u);
+    v[2] -= __uint_as_float(t[k].y << 16);
+    v[3] -= __uint_as_float(t[k].y & 0xffff0000u);
+  }
+}
+
+constexpr int kAhead = 3;  // slices in flight between memory and registers
+
+// One operand's slice: fp32 from memory to registers, its three terms to LDS, fragments of 32 rows x 16 k back
+template <int ROWS, int KM, int VEC, int BK, int NT>
+struct Loader {
+  static constexpr int LD = KM ? BK + 8 : ROWS + 16;            // elements of a stored row
+  static constexpr int PLANE = KM ? ROWS * LD : BK * LD;        // elements of one term
+  static constexpr int ELEMS = 3 * PLANE;
+  static constexpr int CHUNKS = ROWS * BK / 4 / NT;             // groups of 4 floats per thread (NT threads)
+  static constexpr int CPR = KM ? BK / 4 : ROWS / 4;            // groups per stored row
+  f32x4 reg[kAhead][CHUNKS];  // slices on their way
+  const float *base;
+  uint32_t off[CHUNKS];    // byte offset of this thread's groups from the slice's first element (32 bits: the caller checks the range)
+  int64_t step;            // floats from one slice to the next
+  int rows_left;
+  // base = first row of the panel (KM) or first column (otherwise) at the first k
+  __device__ __forceinline__ void init(const float *base_, int64_t ld, int rows_left_) {
+    base = base_;
+    step = KM ? BK : BK * ld;
+    rows_left = rows_left_;
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) {
+      const int c = threadIdx.x + NT * i, major = c / CPR, minor = (c % CPR) * 4;
+      // rows beyond the last give results that are not stored: they are read from the last (KM) or from the last group that holds a row
+      const int r = KM ? min(major, rows_left - 1) : min(minor, (rows_left - 1) / 4 * 4);
+      off[i] = (uint32_t)((KM ? r * ld + minor : major * ld + r) * 4);
+    }
+  }
+  // the next slice's groups into register set `set`; k_left = k from the slice's first to the end of the contraction
+  __device__ __forceinline__ void load(int set, int k_left) {
+    if (VEC && k_left >= BK && (KM || rows_left >= ROWS)) {
+#pragma unroll
+      for (int i = 0; i < CHUNKS; ++i) reg[set][i] = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(base) + off[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < CHUNKS; ++i) {
+        const int c = threadIdx.x + NT * i, k = KM ? c % CPR * 4 : c / CPR, r = KM ? 0 : min(c % CPR * 4, (rows_left - 1) / 4 * 4);
+        const float *p = reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + off[i]);
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        // what lies beyond the last k is zero; (an aligned group that straddles an edge holds at least one element of the operand, so reading it is safe)
+        if (VEC && k < k_left) v = *reinterpret_cast<const f32x4 *>(p);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool in = KM ? k + e < k_left : (k < k_left && r + e < rows_left);
+          if (VEC) v[e] = in ? v[e] : 0.f;
+          else if (in) v[e] = p[e];
+        }
+        reg[set][i] = v;
+      }
+    }
+    base += step;
+  }
+  __device__ __forceinline__ void store(int set, uint16_t *lds) const {
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) {
+      const int c = threadIdx.x + NT * i;
+      u32x2 t[3];
+      split(reg[set][i], t);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2 *>(lds + k * PLANE + (c / CPR) * LD + (c % CPR) * 4) = t[k];
+    }
+  }
+  // the wave's fragments of the 32 rows from row0 on and the 16 k from k0 on, all three terms
+  static __device__ __forceinline__ void frag(const uint16_t *lds, int row0, int k0, bf16x8 (&f)[3]) {
+    const int lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5, s = lane & 15, hi = (lane >> 4) & 1;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (KM) {
+        f[k] = *reinterpret_cast<const bf16x8 *>(lds + k * PLANE + (row0 + c) * LD + k0 + 8 * g);
+      } else {
+        typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
+        const uint16_t *q = lds + k * PLANE + (k0 + 8 * g + (s >> 2)) * LD + row0 + 16 * hi + 4 * (s & 3);
+        const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q)), y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q + 4 * LD));
+        f[k] = __builtin_bit_cast(bf16x8, s16x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]});
+      }
+    }
+  }
+};
 
 template <int ROWS, int KM, int VEC, int BK>
-struct Loader {
+struct SmallLoader {
   static constexpr int LD = KM ? BK + 4 : ROWS + 8;
   static constexpr int ELEMS = KM ? ROWS * LD : BK * LD;
   static constexpr int CHUNKS = ROWS * BK / 4 / 256;  // groups of 4 floats per thread
@@ -99,15 +205,166 @@ struct Ep32 {
   int64_t ldc;
 };
 
+// Waves: 2 x 2 over the tile (W2 = 2) or one (W2 = 1), times WK shares of a slice's k; where two waves share a SIMD (8 waves) the first four
+// form the next slice's terms before their products, the others after, so that a SIMD's matrix and vector pipes are busy together.
 // Grid: x = tiles (dealt so that each of the 8 XCDs walks a contiguous range, in columns of 8 tile rows), y = parts of the
 // contraction (kchunk long, a multiple of BK; part p writes its partial product to out + p M ldc).
-template <int AKM, int BKM, int BM, int BN, int WK, int BK, int VEC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, Ep32 ep, int tiles_m,
+template <int AKM, int BKM, int BM, int W2, int WK, int BK, int VEC>
+__global__ __launch_bounds__(64 * W2 * W2 * WK) void gemm_f32_kernel(int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, Ep32 ep, int tiles_m,
+                                                                     int tiles_n, int kchunk) {
+  constexpr int BN = BM, NT = 64 * W2 * W2 * WK, TM = BM / W2 / 32, KS = BK / 16 / WK;  // TM: 32x32 tiles of a wave each way; KS: its steps of 16 k per slice
+  using LA = Loader<BM, AKM, VEC, BK, NT>;
+  using LB = Loader<BN, BKM, VEC, BK, NT>;
+  constexpr int STAGE = LA::ELEMS + LB::ELEMS;
+  __shared__ __attribute__((aligned(16))) uint16_t lds[2 * STAGE];
+  const int nb = tiles_m * tiles_n;
+  int bid = blockIdx.x;
+  if (nb % 8 == 0) bid = (bid % 8) * (nb / 8) + bid / 8;
+  constexpr int GROUP = 8;
+  const int per_group = GROUP * tiles_n;
+  const int grp = bid / per_group, first_m = grp * GROUP;
+  const int gsize = min(GROUP, tiles_m - first_m);
+  const int m0 = (first_m + (bid % per_group) % gsize) * BM, n0 = ((bid % per_group) / gsize) * BN;
+  const int kbeg = blockIdx.y * kchunk, kend = min(K, kbeg + kchunk);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wk = wave / (W2 * W2), wpos = wave % (W2 * W2);
+  const int wm = wpos / W2 * (BM / W2), wn = wpos % W2 * (BN / W2), kw = wk * (BK / WK);
+  const bool late = W2 * W2 * WK == 8 && wave >= 4;
+  const float *pa = AKM ? A + (int64_t)m0 * lda : A + m0, *pb = BKM ? B + (int64_t)n0 * ldb : B + n0;
+
+  f32x16 acc[TM][TM], low[TM][TM];  // the sums of the largest products, and of the others: fewer roundings at the size of the result
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.f; low[i][j][r] = 0.f; }
+  LA la;
+  LB lb;
+  la.init(AKM ? pa + kbeg : pa + (int64_t)kbeg * lda, lda, M - m0);
+  lb.init(BKM ? pb + kbeg : pb + (int64_t)kbeg * ldb, ldb, N - n0);
+  la.load(0, kend - kbeg);
+  lb.load(0, kend - kbeg);
+  la.store(0, lds);
+  lb.store(0, lds + LA::ELEMS);
+#pragma unroll
+  for (int u = 1; u <= kAhead; ++u)
+    if (kbeg + u * BK < kend) {
+      la.load(u % kAhead, kend - kbeg - u * BK);
+      lb.load(u % kAhead, kend - kbeg - u * BK);
+    }
+  __syncthreads();
+  int cur = 0;
+  for (int k1 = kbeg; k1 < kend; k1 += kAhead * BK) {
+#pragma unroll
+  for (int d = 0; d < kAhead; ++d, cur ^= 1) {
+    const int k0 = k1 + d * BK;
+    if (k0 >= kend) break;
+    // slice k0 is in LDS, the next ones in registers or on their way there
+    auto next = [&] {
+      const int set = (d + 1) % kAhead;
+      if (k0 + BK < kend) {
+        la.store(set, lds + (cur ^ 1) * STAGE);
+        lb.store(set, lds + (cur ^ 1) * STAGE + LA::ELEMS);
+      }
+      if (k0 + (kAhead + 1) * BK < kend) {
+        la.load(set, kend - k0 - (kAhead + 1) * BK);
+        lb.load(set, kend - k0 - (kAhead + 1) * BK);
+      }
+    };
+    if (!late) next();
+    const uint16_t *st = lds + cur * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      bf16x8 af[TM][3], bf[TM][3];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        LA::frag(st, wm + i * 32, kw + 16 * ks, af[i]);
+        LB::frag(st + LA::ELEMS, wn + i * 32, kw + 16 * ks, bf[i]);
+      }
+      // the six largest of the nine products, small ones first
+#pragma unroll
+      for (int p = 0; p < 6; ++p) {
+        constexpr int pa_[6] = {2, 0, 1, 1, 0, 0}, pb_[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TM; ++j) {
+            f32x16 &to = p == 5 ? acc[i][j] : low[i][j];
+            to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i][pa_[p]], bf[j][pb_[p]], to, 0, 0, 0);
+          }
+      }
+    }
+    if (late) next();
+    __syncthreads();
+  }
+  }
+  // accumulator register r of lane (g = lane / 32, c = lane % 32): row 8 (r / 4) + 4 g + r % 4, column c: a store instruction writes
+  // two rows of 128 consecutive bytes
+  float *out = ep.out + (int64_t)blockIdx.y * M * ep.ldc;
+  auto put = [&](int m, int n, float x, float bias) {
+    if (m >= M) return;
+    float v = (x + bias) * ep.alpha;
+    const int64_t o = (int64_t)m * ep.ldc + n;
+    if (ep.residual) v += ep.residual[o];
+    out[o] = v;
+  };
+  bool finite = true;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc[i][j][r] += low[i][j][r];
+        finite = finite && __builtin_isfinite(acc[i][j][r]);
+      }
+  if (__syncthreads_or(!finite)) {
+    // an infinity or a NaN among the operands (or a value that rounds to infinity): its terms do not behave like it, so this tile is formed plainly
+#pragma unroll 1
+    for (int i = threadIdx.x; i < BM * BN; i += NT) {
+      const int m = m0 + i / BN, n = n0 + i % BN;
+      if (m >= M || n >= N) continue;
+      float x = 0.f;
+      for (int k = kbeg; k < kend; ++k) x = fmaf(AKM ? A[m * lda + k] : A[k * lda + m], BKM ? B[n * ldb + k] : B[k * ldb + n], x);
+      put(m, n, x, ep.bias ? ep.bias[n] : 0.f);
+    }
+    return;
+  }
+  // the WK shares are added in order; each of their waves finishes 16 / WK of a 32x32 tile's registers
+  float *part = reinterpret_cast<float *>(lds);
+  constexpr int TILE_F = W2 * W2 * WK * 1024;
+  static_assert(sizeof(lds) >= (TM > 1 ? 2 : 1) * TILE_F * sizeof(float), "the results of one 32x32 tile of every wave fit the stages, and of the next");
+#pragma unroll
+  for (int j = 0; j < TM; ++j) {
+    const int n = n0 + wn + 32 * j + (lane & 31);
+    const float bias = ep.bias && n < N ? ep.bias[n] : 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      float *p = part + (j * TM + i & 1) * TILE_F + lane;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p[wave * 1024 + r * 64] = acc[i][j][r];
+      __syncthreads();
+#pragma unroll
+      for (int rr = 0; rr < 16 / WK; ++rr) {
+        const int r = wk * (16 / WK) + rr;
+        float x = 0.f;
+#pragma unroll
+        for (int w = 0; w < WK; ++w) x += p[(w * W2 * W2 + wpos) * 1024 + r * 64];
+        if (n < N) put(m0 + wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), n, x, bias);
+      }
+    }
+  }
+}
+
+// Grid: x = tiles (dealt so that each of the 8 XCDs walks a contiguous range, in columns of 8 tile rows), y = parts of the
+// contraction (kchunk long, a multiple of BK; part p writes its partial product to out + p M ldc).
+template <int AKM, int BKM, int VEC>
+__global__ __launch_bounds__(256) void gemm_f32_small_kernel(int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, Ep32 ep, int tiles_m,
                                                        int tiles_n, int kchunk) {
-  constexpr int WM = WK == 1 ? 2 : 1, WN = WM, TM = BM / WM / 32, TN = BN / WN / 32, US = BK / 8 / WK;  // US: groups of 4 MFMAs per slice and wave
-  static_assert(WM * WN * WK == 4 && (WK == 1 || (TM == 1 && TN == 1)), "four waves divide the tile or the slice");
-  using LA = Loader<BM, AKM, VEC, BK>;
-  using LB = Loader<BN, BKM, VEC, BK>;
+  constexpr int BM = 32, BN = 32, BK = 64, US = BK / 8 / 4;  // US: groups of 4 MFMAs per slice and wave
+  using LA = SmallLoader<BM, AKM, VEC, BK>;
+  using LB = SmallLoader<BN, BKM, VEC, BK>;
   __shared__ __attribute__((aligned(16))) float As[2][LA::ELEMS];
   __shared__ __attribute__((aligned(16))) float Bs[2][LB::ELEMS];
   const int nb = tiles_m * tiles_n;
@@ -120,16 +377,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, cons
   const int m0 = (first_m + (bid % per_group) % gsize) * BM, n0 = ((bid % per_group) / gsize) * BN;
   const int kbeg = blockIdx.y * kchunk, kend = min(K, kbeg + kchunk);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wm = WK == 1 ? (wave >> 1) * (BM / 2) : 0, wn = WK == 1 ? (wave & 1) * (BN / 2) : 0, u0 = WK == 1 ? 0 : wave * US;
+  const int u0 = wave * US;
   const float *pa = AKM ? A + (int64_t)m0 * lda : A + m0, *pb = BKM ? B + (int64_t)n0 * ldb : B + n0;
 
-  f32x16 acc[TM][TN];
+  f32x16 acc;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   LA la;
   LB lb;
   la.init(pa, lda, M - m0, kbeg);
@@ -147,25 +400,17 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, cons
       lb.load(kend - k0 - BK);
     }
     // fragments of group u + 1 are fetched while the MFMAs of group u run
-    f32x4 af[2][TM], bf[2][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[0][i] = LA::frag(As[cur], wm + i * 32, u0);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bf[0][j] = LB::frag(Bs[cur], wn + j * 32, u0);
+    f32x4 af[2], bf[2];
+    af[0] = LA::frag(As[cur], 0, u0);
+    bf[0] = LB::frag(Bs[cur], 0, u0);
 #pragma unroll
     for (int u = 0; u < US; ++u) {
       if (u + 1 < US) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) af[(u + 1) & 1][i] = LA::frag(As[cur], wm + i * 32, u0 + u + 1);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bf[(u + 1) & 1][j] = LB::frag(Bs[cur], wn + j * 32, u0 + u + 1);
+        af[(u + 1) & 1] = LA::frag(As[cur], 0, u0 + u + 1);
+        bf[(u + 1) & 1] = LB::frag(Bs[cur], 0, u0 + u + 1);
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[u & 1][i][e], bf[u & 1][j][e], acc[i][j], 0, 0, 0);
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[u & 1][e], bf[u & 1][e], acc, 0, 0, 0);
     }
     if (more) {
       la.store(As[cur ^ 1]);
@@ -183,72 +428,76 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, cons
     if (ep.residual) v += ep.residual[o];
     out[o] = v;
   };
-  if (WK == 1) {
+  // every wave finishes a quarter of the rows: registers 4 w .. 4 w + 3 of all four waves
+  float *part = &As[0][0];
+  static_assert(sizeof(As) >= 4 * 1024 * sizeof(float), "four 32x32 results fit the A stages");
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int n = n0 + wn + 32 * j + (lane & 31);
-      if (n >= N) continue;
-      const float bias = ep.bias ? ep.bias[n] : 0.f;
+  for (int r = 0; r < 16; ++r) part[wave * 1024 + r * 64 + lane] = acc[r];
+  __syncthreads();
+  const int n = n0 + (lane & 31);
+  const float bias = ep.bias && n < N ? ep.bias[n] : 0.f;
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+  for (int rr = 0; rr < 4; ++rr) {
+    const int r = 4 * wave + rr;
+    float x = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) put(m0 + wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), n, acc[i][j][r], bias);
-    }
-  } else {
-    // every wave finishes a quarter of the rows: registers 4 w .. 4 w + 3 of all four waves
-    float *part = &As[0][0];
-    static_assert(sizeof(As) >= 4 * 1024 * sizeof(float), "four 32x32 results fit the A stages");
-#pragma unroll
-    for (int r = 0; r < 16; ++r) part[wave * 1024 + r * 64 + lane] = acc[0][0][r];
-    __syncthreads();
-    const int n = n0 + (lane & 31);
-    const float bias = ep.bias && n < N ? ep.bias[n] : 0.f;
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int r = 4 * wave + rr;
-      float x = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) x += part[w * 1024 + r * 64 + lane];
-      if (n < N) put(m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), n, x, bias);
-    }
+    for (int w = 0; w < 4; ++w) x += part[w * 1024 + r * 64 + lane];
+    if (n < N) put(m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), n, x, bias);
   }
 }
 
-template <int AKM, int BKM, int BM, int WK, int BK, int VEC>
+template <int AKM, int BKM, int BM, int W2, int WK, int BK, int VEC>
 void launch(hipStream_t st, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, const Ep32 &ep, int parts, int kchunk) {
   const int tm = (M + BM - 1) / BM, tn = (N + BM - 1) / BM;
-  hipLaunchKernelGGL((gemm_f32_kernel<AKM, BKM, BM, BM, WK, BK, VEC>), dim3(tm * tn, parts), dim3(256), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk);
+  hipLaunchKernelGGL((gemm_f32_kernel<AKM, BKM, BM, W2, WK, BK, VEC>), dim3(tm * tn, parts), dim3(64 * W2 * W2 * WK), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk);
 }
 
-template <int AKM, int BKM>
-void launch_tile(hipStream_t st, int tile, bool vec, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, const Ep32 &ep, int parts,
-                 int kchunk) {
-  if (tile == 128 && vec) launch<AKM, BKM, 128, 1, 32, 1>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
-  else if (tile == 128) launch<AKM, BKM, 128, 1, 32, 0>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
-  else if (tile == 64 && vec) launch<AKM, BKM, 64, 1, 64, 1>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
-  else if (tile == 64) launch<AKM, BKM, 64, 1, 64, 0>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
-  else if (vec) launch<AKM, BKM, 32, 4, 64, 1>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
-  else launch<AKM, BKM, 32, 4, 64, 0>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
+template <int AKM, int BKM, int VEC>
+void launch_tile(hipStream_t st, int tile, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, const Ep32 &ep, int parts, int kchunk) {
+  if (tile == 128) return launch<AKM, BKM, 128, 2, 2, 32, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
+  if (tile == 64) {
+    // one tile per CU: slices of 64 (1024 x 768 x 1536 32 us, 44 in slices of 32); more: two workgroups to a CU (1024 x 1536 x 768 34 us, 30)
+    if ((int64_t)((M + 63) / 64) * ((N + 63) / 64) * parts <= 256) launch<AKM, BKM, 64, 2, 2, 64, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
+    else launch<AKM, BKM, 64, 2, 2, 32, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
+    return;
+  }
+  const int tm = (M + 31) / 32, tn = (N + 31) / 32;
+  hipLaunchKernelGGL((gemm_f32_small_kernel<AKM, BKM, VEC>), dim3(tm * tn, parts), dim3(256), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk);
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// Tile and number of parts of the contraction, by estimated time: the busiest of 256 CUs works through ceil(tiles parts / 256)
-// tiles at the share of the matrix peak that the tile reaches (measured over many rounds: 128 0.78, 64 0.6, 32 0.45; a quarter less
-// where a CU holds one workgroup and nothing hides its waits); a cut contraction adds the pass over the partial products.
+// Tile and number of parts of the contraction, by estimated time of the kernels above (us).  128: n = tiles on the busiest of 256 CUs,
+// 3 + n (6 + 1.47 per slice of 32).  64: one tile a CU 4.3 + 1.2 per slice of 64; more run in pairs, 2 (1.9 + 0.48 per slice of 32), a single one
+// left over in the second round 1.9 + 0.85 per slice, and from then on the rounds run into each other.  32: 4 + 1.4 (n - 4, if more) + (0.2 + 0.36 n) per
+// slice of 64.  Rows contiguous in both operands (TN): an eighth more for tiles of 128, a sixth for single ones of 64.
+// Fitted to (measured; 128 / 64 / 32): 1024 x 768 x 384 25.6 / 11.4 / 11.9, 1024 x 1536 x 768 43 / 29.7 / -, 1152 x 768 x 1024 (TN) 56 / 25 / 38,
+// 1024 x 768 x 1536 76 / 32 / 33, 512 x 1536 x 768 - / 18.7 / 19.3, 256 x 1024 x 1024 - / 22 / 13, 4096^3 790 / 1083 / -, 1024 x 50257 x 768 586 / 713 / -,
+// 8192 x 2048 x 24 43 / 40 / 98; 1500 x 1500 x 2000 (TN) 118 / 129 / 112, in two parts 131 / 105 / 119, in four 109 / 104 / 122;
+// 1024 x 768 x 8003 (TN) 414 / 178 / 143, in four parts 120 / 140 / 147, in eight 131 / 124 / 150.
 struct Choice { int tile, parts; };
-Choice choose(int M, int N, int K, bool may_split, size_t split_floats) {
-  static const struct { int tile; double rate; } kinds[] = {{128, 0.78}, {64, 0.6}, {32, 0.45}};
+Choice choose(GemmLayout lay, int M, int N, int K, bool may_split, size_t split_floats) {
   Choice best{64, 1};
   double best_us = 1e30;
-  for (const auto &k : kinds) {
-    const double tiles = (double)((M + k.tile - 1) / k.tile) * ((N + k.tile - 1) / k.tile);
+  for (int tile = 128; tile >= 32; tile /= 2) {
+    const int64_t tiles = (int64_t)((M + tile - 1) / tile) * ((N + tile - 1) / tile);
     for (int parts = 1; parts <= 16; parts *= 2) {
       if (parts > 1 && (!may_split || K / parts < 256 || (double)parts * M * N > (double)split_floats)) break;
-      const double rounds = (double)(((int64_t)(tiles * parts) + 255) / 256);
-      double us = rounds * 2.0 * k.tile * k.tile * K / parts / (0.61e6 * k.rate * (rounds == 1 ? 0.75 : 1.0));  // 0.61 TFLOP/s per CU
-      if (parts > 1) us += 4.0 + (parts + 1.0) * M * N * 8.0 / 4e6;
-      if (us < best_us) { best_us = us; best = {k.tile, parts}; }
+      const int64_t items = tiles * parts;
+      const double n = (double)((items + 255) / 256), k = (double)K / parts;
+      double us;
+      if (tile == 128) {
+        us = 3.0 + n * (6.0 + (lay == GEMM_TN ? 1.65 : 1.47) * k / 32);
+      } else if (tile == 32) {
+        us = 4.0 + 1.4 * std::max(n - 4.0, 0.0) + (0.2 + 0.36 * n) * k / 64;
+      } else if (n == 1) {
+        us = 4.3 + (lay == GEMM_TN ? 1.38 : 1.2) * k / 64;
+      } else {
+        const double pair = 2 * (1.9 + 0.48 * k / 32), rounds = items / 512.0;
+        us = 3.0 + (rounds <= 1 ? pair : rounds <= 1.5 ? pair + 1.9 + 0.85 * k / 32 : rounds <= 2 ? 2 * pair : pair * (rounds + 0.25));
+      }
+      if (parts > 1) us += 3.5 + (parts + 1.0) * M * N * 8.0 / 6e6;
+      if (us < best_us) { best_us = us; best = {tile, parts}; }
     }
   }
   return best;
@@ -256,8 +505,8 @@ Choice choose(int M, int N, int K, bool may_split, size_t split_floats) {
 
 }  // namespace
 
-void twist_gemm_f32_choice(const twist_ctx *ctx, int M, int N, int K, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
-  Choice ch = choose(M, N, K, may_split && !ctx->gemm_tile, split_floats);
+void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
+  Choice ch = choose(lay, M, N, K, may_split && !ctx->gemm_tile, split_floats);
   if (ctx->gemm_tile) ch = {ctx->gemm_tile == 128 ? 128 : 64, 1};
   const int bk = ch.tile == 128 ? 32 : 64;
   kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
@@ -270,13 +519,24 @@ twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int 
   Ep32 ep{e.alpha, static_cast<const float *>(e.bias), e.residual, static_cast<float *>(e.out), ldc};
   const bool vec = aligned16(A) && aligned16(B) && lda % 4 == 0 && ldb % 4 == 0;
   int tile, parts, kchunk;
-  twist_gemm_f32_choice(ctx, M, N, K, e.splitk_ws && !e.bias && !e.residual, e.splitk_floats, tile, parts, kchunk);
-  if (parts > 1) ep = Ep32{1.f, nullptr, nullptr, e.splitk_ws, N};
-  switch (lay) {
-    case GEMM_NT: launch_tile<1, 1>(st, tile, vec, M, N, K, A, lda, B, ldb, ep, parts, kchunk); break;
-    case GEMM_NN: launch_tile<1, 0>(st, tile, vec, M, N, K, A, lda, B, ldb, ep, parts, kchunk); break;
-    case GEMM_TN: launch_tile<0, 0>(st, tile, vec, M, N, K, A, lda, B, ldb, ep, parts, kchunk); break;
+  twist_gemm_f32_choice(ctx, lay, M, N, K, e.splitk_ws && !e.bias && !e.residual, e.splitk_floats, tile, parts, kchunk);
+  if (tile != 32 && std::max(lda, ldb) >= 1 << 23) {  // a slice of such rows exceeds the larger tiles' 32-bit offsets
+    tile = 32;
+    kchunk = (kchunk + 63) / 64 * 64;
+    parts = (K + kchunk - 1) / kchunk;
   }
+  if (parts > 1) ep = Ep32{1.f, nullptr, nullptr, e.splitk_ws, N};
+#define TW_F32(AKM, BKM)                                                                                \
+  do {                                                                                                    \
+    if (vec) launch_tile<AKM, BKM, 1>(st, tile, M, N, K, A, lda, B, ldb, ep, parts, kchunk);              \
+    else launch_tile<AKM, BKM, 0>(st, tile, M, N, K, A, lda, B, ldb, ep, parts, kchunk);                  \
+  } while (0)
+  switch (lay) {
+    case GEMM_NT: TW_F32(1, 1); break;
+    case GEMM_NN: TW_F32(1, 0); break;
+    case GEMM_TN: TW_F32(0, 0); break;
+  }
+#undef TW_F32
   TW_HIP(ctx, hipGetLastError());
   if (parts > 1) return twist_splitk_reduce(ctx, st, e.splitk_ws, parts, M, N, e.out, ldc, 1, e.alpha);
   return TWIST_OK;

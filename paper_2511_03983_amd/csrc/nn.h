@@ -38,7 +38,7 @@ void twist_launch_gemm_dl(hipStream_t st, int tile, GemmLayout lay, int M, int N
 twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
                             int64_t ldc, const GemmEpilogue &e);
 // its tile, number of parts of the contraction and length of a part
-void twist_gemm_f32_choice(const twist_ctx *ctx, int M, int N, int K, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk);
+void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk);
 twist_status twist_splitk_reduce(twist_ctx *ctx, hipStream_t st, const float *parts_ws, int parts, int M, int N, void *out, int64_t ldc, int out_f32,
                                  float alpha);
 

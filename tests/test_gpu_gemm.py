@@ -95,7 +95,7 @@ def test_small_bf16_projection_edges(lib, layout, M, N, K):
         assert torch.isnan(buf[M * N:]).all()
 
 
-# fp32 matrix-instruction kernel: tiles of 32 (by size), 64 (pinned by 256) and 128 (pinned), ragged edges, contractions that end
+# fp32 kernels: tiles of 32 (by size), 64 (pinned by 256) and 128 (pinned), ragged edges, contractions that end
 # inside a slice of 32 or 64, strides that allow 16-byte loads and strides that do not (odd K, M or N)
 @pytest.mark.parametrize("tile", [0, 128, 256])
 @pytest.mark.parametrize("layout", [0, 1, 2])
@@ -115,6 +115,35 @@ def test_fp32_projection_edges(lib, tile, layout, M, N, K):
     # K products of one rounding each and K additions: 2^-24 sqrt(2 K) at most about 3e-6 here
     assert float((out.double() - 0.5 * want).norm() / (0.5 * want).norm()) <= 3e-6
     assert torch.isnan(buf[M * N:]).all()
+
+
+# the tiles on the bf16 instruction: operands of very different sizes, and values that their three terms cannot stand for (infinities, NaNs, the largest
+# floats, which round to infinity in bf16) give what the plain kernel gives; rows and columns without such a value stay finite and exact
+@pytest.mark.parametrize("tile", [128, 256])
+@pytest.mark.parametrize("layout", [0, 1, 2])
+def test_fp32_projection_with_values_beyond_the_terms(lib, tile, layout):
+    M, N, K = 260, 140, 200
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    gen = torch.Generator(device="cuda").manual_seed(layout)
+    A, B = torch.randn((M, K), generator=gen, device="cuda"), torch.randn((N, K), generator=gen, device="cuda")
+    A *= 10.0 ** torch.randint(-12, 12, (M, 1), generator=gen, device="cuda")
+    for special in (None, float("inf"), float("-inf"), float("nan"), 3.4e38):
+        a, b = A.clone(), B.clone()
+        if special is not None:
+            a[70, 50], b[100, 7] = special, special
+            a[70, 51:] = 0.0
+        want = (a.double() @ b.double().T).float()                        # 64 bits: overflows where fp32 does
+        a_, b_ = (a.T.contiguous() if layout == 2 else a), (b if layout == 0 else b.T.contiguous())
+        out = torch.empty((M, N), device="cuda")
+        ctx.twist_set_kernel_choice(gemm_tile=tile)
+        ctx.twist_gemm_raw(layout, M, N, K, a_, b_, out)
+        torch.cuda.synchronize()
+        ok = torch.isfinite(want)
+        assert torch.equal(torch.isfinite(out), ok) and torch.equal(torch.isnan(out), torch.isnan(want)), special
+        err = torch.where(ok, (out.double() - want.double()).abs(), 0.0)
+        # 2^-24 sqrt(2 K) of the row's and column's norms, three times that for the largest of 36000 entries; terms near 3.4e38 leave nothing of others
+        bound = 4e-6 * a.double().nan_to_num(0, 0, 0).norm(dim=1)[:, None] * b.double().nan_to_num(0, 0, 0).norm(dim=1)[None, :]
+        assert bool((err <= bound).all()), special
 
 
 @pytest.mark.parametrize("M,N,K,tile", [(3000, 2900, 72, 64), (4000, 3900, 72, 128)])
