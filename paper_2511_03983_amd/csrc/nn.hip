@@ -6,6 +6,9 @@
 namespace {
 
 constexpr int kT = 256;
+typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 template <int BF> struct El;
 template <> struct El<0> {
@@ -159,48 +162,74 @@ __global__ __launch_bounds__(64) void norm_bwd_dw_kernel(const void *dy, const f
   partial[((int64_t)chunk * 2 + 1) * D + c] = sb;
 }
 
-// Fused norm backward for rows of NV * 256 elements: one pass over dy and x yields dx (+= when accumulating), its
+// four consecutive values of an operand
+template <int BF>
+__device__ __forceinline__ f32x4v ld4(const void *p, int64_t vec) {
+  if (BF) {
+    const u32x2v u = static_cast<const u32x2v *>(p)[vec];
+    return f32x4v{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
+  }
+  return static_cast<const f32x4v *>(p)[vec];
+}
+// ... stored (bf16: round to nearest even); returns what was stored
+template <int BF>
+__device__ __forceinline__ f32x4v st4(void *p, int64_t vec, const f32x4v &o) {
+  if (BF) {
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 lo = {o[0], o[1]}, hi = {o[2], o[3]};
+    const u32x2v pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, b2)), __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, b2))};
+    static_cast<u32x2v *>(p)[vec] = pk;
+    return f32x4v{__uint_as_float(pk.x << 16), __uint_as_float(pk.x & 0xffff0000u), __uint_as_float(pk.y << 16), __uint_as_float(pk.y & 0xffff0000u)};
+  }
+  static_cast<f32x4v *>(p)[vec] = o;
+  return o;
+}
+
+// Fused norm backward for rows of D <= NV * 256 elements, D a multiple of 4: one pass over dy and x yields dx (+= when accumulating), its
 // activation-type copy, and this chunk's partial sums for the gain / bias gradients.  A wave owns a row at a time and
-// a lane the same 4 NV columns of every row (vector v = lane + 64 k holds columns 4v .. 4v+3), so the parameter sums
-// stay in registers across the chunk's rows; the four waves' sums are combined through LDS.
+// a lane the same 4 NV columns of every row (vector v = lane + 64 k holds columns 4v .. 4v+3; those beyond D are read from the last one and
+// count as zero), so the parameter sums stay in registers across the chunk's rows; the W waves' sums are combined through LDS.
 // CS: the copy's column sums are formed as well (csum[chunk][D]): the bias gradients of the projection that the copy goes back into,
 // which otherwise cost a launch and another pass over it (8192 x 768 bf16: 7.8 us beside this kernel's 20).
-template <int BF, int RMS, int NV, bool CS>
-__global__ __launch_bounds__(kT) void norm_bwd_fused_kernel(const void *dy, const float *x, const void *w, const float *stats, float *dx, int accumulate,
-                                                             void *dxb, float *partial, float *csum, int T) {
-  constexpr int D = NV * 256;
-  typedef float f4 __attribute__((ext_vector_type(4)));
-  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-  __shared__ float red[(RMS ? 1 : 2) * 4 * D];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// W = 8 instead of 4 where the chunks are fewer than the CUs, so that a wave has two rows after one another, not four.
+// Bound by memory where the chunks fill the chip (8192 x 2048 bf16: 54 us, 5 TB/s).  Widths that are no multiple of 256 ran two kernels
+// with 2- and 4-byte loads (forward and backward, us): 4000 x 1304 bf16 52 -> 28, 4096 x 520 38 -> 26; fp32 2000 x 3400 95 -> 38.
+template <int BF, int RMS, int NV, bool CS, int W, bool FULL>
+__global__ __launch_bounds__(64 * W) void norm_bwd_fused_kernel(const void *dy, const float *x, const void *w, const float *stats, float *dx, int accumulate,
+                                                                void *dxb, float *partial, float *csum, int T, int Dn) {
+  const int D = FULL ? NV * 256 : Dn;
+  __shared__ float red[(RMS ? 1 : 2) * W * NV * 256];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, d4 = D >> 2;
   const int r0 = blockIdx.x * kChunkRows, r1 = min(r0 + kChunkRows, T);
-  auto load4 = [](const void *p, int64_t vec) -> f4 {
-    if (BF) {
-      const u2 u = static_cast<const u2 *>(p)[vec];
-      return f4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
-    }
-    return static_cast<const f4 *>(p)[vec];
-  };
-  f4 wv[NV], aw[NV], ab[NV], ac[CS ? NV : 1];
+  auto on = [&](int k) { return FULL || lane + 64 * k < d4; };
+  auto at = [&](int k) { return FULL ? lane + 64 * k : min(lane + 64 * k, d4 - 1); };
+  f32x4v wv[NV], aw[NV], ab[NV], ac[CS ? NV : 1];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    wv[k] = load4(w, lane + 64 * k);
-    aw[k] = f4{0.f, 0.f, 0.f, 0.f};
-    ab[k] = f4{0.f, 0.f, 0.f, 0.f};
-    if (CS) ac[CS ? k : 0] = f4{0.f, 0.f, 0.f, 0.f};
+    wv[k] = ld4<BF>(w, at(k));
+    aw[k] = f32x4v{0.f, 0.f, 0.f, 0.f};
+    ab[k] = f32x4v{0.f, 0.f, 0.f, 0.f};
+    if (CS) ac[CS ? k : 0] = f32x4v{0.f, 0.f, 0.f, 0.f};
   }
-  for (int r = r0 + wave; r < r1; r += 4) {
+  for (int r = r0 + wave; r < r1; r += W) {
     const float mean = stats[2 * r], rstd = stats[2 * r + 1];
-    const int64_t rv = (int64_t)r * (D / 4);
-    f4 g[NV], z[NV];
+    const int64_t rv = (int64_t)r * d4;
+    f32x4v g[NV], z[NV];
     float c1 = 0.f, c2 = 0.f;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      g[k] = load4(dy, rv + lane + 64 * k);
-      z[k] = (reinterpret_cast<const f4 *>(x)[rv + lane + 64 * k] - mean) * rstd;
+      const int v = at(k);
+      g[k] = ld4<BF>(dy, rv + v);
+      z[k] = (reinterpret_cast<const f32x4v *>(x)[rv + v] - mean) * rstd;
     }
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        g[k][e] = on(k) ? g[k][e] : 0.f;
+        z[k][e] = on(k) ? z[k][e] : 0.f;
+      }
       aw[k] += g[k] * z[k];
       if (!RMS) ab[k] += g[k];
       g[k] *= wv[k];  // dz
@@ -211,41 +240,120 @@ __global__ __launch_bounds__(kT) void norm_bwd_fused_kernel(const void *dy, cons
     c2 = wave_sum(c2) / D;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      f4 o = rstd * (g[k] - c1 - z[k] * c2);
-      f4 *dp = reinterpret_cast<f4 *>(dx) + rv + lane + 64 * k;
+      if (!on(k)) continue;
+      f32x4v o = rstd * (g[k] - c1 - z[k] * c2);
+      f32x4v *dp = reinterpret_cast<f32x4v *>(dx) + rv + lane + 64 * k;
       if (accumulate) o += *dp;
       *dp = o;
       if (dxb) {
-        if (BF) {
-          typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-          typedef float f2 __attribute__((ext_vector_type(2)));
-          const f2 lo = {o[0], o[1]}, hi = {o[2], o[3]};
-          const u2 pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, b2)), __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, b2))};
-          static_cast<u2 *>(dxb)[rv + lane + 64 * k] = pk;
-          if (CS) ac[CS ? k : 0] += f4{__uint_as_float(pk.x << 16), __uint_as_float(pk.x & 0xffff0000u), __uint_as_float(pk.y << 16), __uint_as_float(pk.y & 0xffff0000u)};
-        } else {
-          static_cast<f4 *>(dxb)[rv + lane + 64 * k] = o;
-          if (CS) ac[CS ? k : 0] += o;
-        }
+        const f32x4v kept = st4<BF>(dxb, rv + lane + 64 * k, o);
+        if (CS) ac[CS ? k : 0] += kept;
       }
     }
   }
+  constexpr int LD = NV * 256;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    *reinterpret_cast<f4 *>(&red[wave * D + 4 * (lane + 64 * k)]) = aw[k];
-    if (!RMS) *reinterpret_cast<f4 *>(&red[(4 + wave) * D + 4 * (lane + 64 * k)]) = ab[k];
+    *reinterpret_cast<f32x4v *>(&red[wave * LD + 4 * (lane + 64 * k)]) = aw[k];
+    if (!RMS) *reinterpret_cast<f32x4v *>(&red[(W + wave) * LD + 4 * (lane + 64 * k)]) = ab[k];
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < D; c += kT) {
-    partial[((int64_t)blockIdx.x * 2) * D + c] = red[c] + red[D + c] + red[2 * D + c] + red[3 * D + c];
-    if (!RMS) partial[((int64_t)blockIdx.x * 2 + 1) * D + c] = red[4 * D + c] + red[5 * D + c] + red[6 * D + c] + red[7 * D + c];
+  auto sum = [&](int first, int c) {
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < W; ++i) t += red[(first + i) * LD + c];
+    return t;
+  };
+  for (int c = threadIdx.x; c < D; c += 64 * W) {
+    partial[((int64_t)blockIdx.x * 2) * D + c] = sum(0, c);
+    if (!RMS) partial[((int64_t)blockIdx.x * 2 + 1) * D + c] = sum(W, c);
   }
   if (CS) {
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < NV; ++k) *reinterpret_cast<f4 *>(&red[wave * D + 4 * (lane + 64 * k)]) = ac[CS ? k : 0];
+    for (int k = 0; k < NV; ++k) *reinterpret_cast<f32x4v *>(&red[wave * LD + 4 * (lane + 64 * k)]) = ac[CS ? k : 0];
     __syncthreads();
-    for (int c = threadIdx.x; c < D; c += kT) csum[(int64_t)blockIdx.x * D + c] = red[c] + red[D + c] + red[2 * D + c] + red[3 * D + c];
+    for (int c = threadIdx.x; c < D; c += 64 * W) csum[(int64_t)blockIdx.x * D + c] = sum(0, c);
+  }
+}
+
+// The same for rows of up to NV * 1024 elements: four waves share a row and a thread holds vectors t + 256 k of it, so that the registers still allow
+// three waves per SIMD (one wave a row: 256 registers, one wave; 8192 x 4096 bf16 210 us, 112); the next row's loads run under this row's
+// sums, and the parameter sums are whole where they are formed.
+template <int BF, int RMS, int NV, bool CS>
+__global__ __launch_bounds__(kT) void norm_bwd_wide_kernel(const void *dy, const float *x, const void *w, const float *stats, float *dx, int accumulate,
+                                                           void *dxb, float *partial, float *csum, int T, int D) {
+  __shared__ float sh[2][2][4];
+  const int wave = threadIdx.x >> 6, d4 = D >> 2;
+  const int r0 = blockIdx.x * kChunkRows, r1 = min(r0 + kChunkRows, T);
+  f32x4v wv[NV], aw[NV], ab[NV], ac[CS ? NV : 1];
+  int at[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    at[k] = min((int)threadIdx.x + kT * k, d4 - 1);
+    wv[k] = ld4<BF>(w, at[k]);
+    aw[k] = f32x4v{0.f, 0.f, 0.f, 0.f};
+    ab[k] = f32x4v{0.f, 0.f, 0.f, 0.f};
+    if (CS) ac[CS ? k : 0] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  }
+  struct Row { f32x4v g[NV], x[NV], d[NV]; float mean, rstd; };
+  auto load = [&](Row &q, int r) {
+    const int64_t rv = (int64_t)r * d4;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      q.g[k] = ld4<BF>(dy, rv + at[k]);
+      q.x[k] = reinterpret_cast<const f32x4v *>(x)[rv + at[k]];
+      q.d[k] = accumulate ? reinterpret_cast<const f32x4v *>(dx)[rv + at[k]] : f32x4v{0.f, 0.f, 0.f, 0.f};
+    }
+    q.mean = stats[2 * r];
+    q.rstd = stats[2 * r + 1];
+  };
+  Row q;
+  load(q, r0);
+  for (int r = r0; r < r1; ++r) {
+    Row next = q;
+    if (r + 1 < r1) load(next, r + 1);
+    float c1 = 0.f, c2 = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const bool on = (int)threadIdx.x + kT * k < d4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float g = on ? q.g[k][e] : 0.f, z = on ? (q.x[k][e] - q.mean) * q.rstd : 0.f;
+        aw[k][e] += g * z;
+        if (!RMS) ab[k][e] += g;
+        q.g[k][e] = g * wv[k][e];  // dz
+        q.x[k][e] = z;
+        c1 += q.g[k][e];
+        c2 += q.g[k][e] * z;
+      }
+    }
+    c1 = RMS ? 0.f : wave_sum(c1);
+    c2 = wave_sum(c2);
+    if ((threadIdx.x & 63) == 0) { sh[r & 1][0][wave] = c1; sh[r & 1][1][wave] = c2; }
+    __syncthreads();  // (two sets: the next row's writes do not meet this row's reads)
+    c1 = RMS ? 0.f : (sh[r & 1][0][0] + sh[r & 1][0][1] + sh[r & 1][0][2] + sh[r & 1][0][3]) / D;
+    c2 = (sh[r & 1][1][0] + sh[r & 1][1][1] + sh[r & 1][1][2] + sh[r & 1][1][3]) / D;
+    const int64_t rv = (int64_t)r * d4;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      if ((int)threadIdx.x + kT * k >= d4) continue;
+      const f32x4v o = q.rstd * (q.g[k] - c1 - q.x[k] * c2) + q.d[k];
+      reinterpret_cast<f32x4v *>(dx)[rv + at[k]] = o;
+      if (dxb) {
+        const f32x4v kept = st4<BF>(dxb, rv + at[k], o);
+        if (CS) ac[CS ? k : 0] += kept;
+      }
+    }
+    q = next;
+  }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    if ((int)threadIdx.x + kT * k >= d4) continue;
+    f32x4v *p = reinterpret_cast<f32x4v *>(partial + (int64_t)blockIdx.x * 2 * D);
+    p[at[k]] = aw[k];
+    if (!RMS) p[d4 + at[k]] = ab[k];
+    if (CS) reinterpret_cast<f32x4v *>(csum + (int64_t)blockIdx.x * D)[at[k]] = ac[CS ? k : 0];
   }
 }
 
@@ -497,8 +605,6 @@ __global__ __launch_bounds__(kT) void zero_f32_kernel(float *p, int64_t n) {
 
 // ------------------------------------------------------------------------------------------- 16-byte paths (bf16)
 // Eight bf16 values per thread and access, used when rows are multiples of 8 elements and bases 16-byte aligned.
-typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-typedef float f32x4v __attribute__((ext_vector_type(4)));
 struct F8 { float v[8]; };
 __device__ __forceinline__ F8 unpack8(const u32x4v &u) {
   F8 r;
@@ -730,42 +836,46 @@ __global__ __launch_bounds__(kT) void rope_vec_kernel(u32x4v *qkv, const float *
   qkv[base + h8] = pack8(ob);
 }
 
-// norm forward for bf16 outputs and rows of NV * 256 elements: a wave per row, the row held in registers
-template <int RMS, int NV>
-__global__ __launch_bounds__(kT) void norm_fwd_vec_kernel(const float *x, const void *w, const void *b, void *y, float *stats, int T, float eps) {
-  constexpr int D = NV * 256;
-  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+// norm forward for rows of D <= NV * 256 elements, D a multiple of 4: a wave per row, the row held in registers (vectors beyond D as in the
+// backward kernel).  fp32 8192 x 2048 32 -> 20 us, bf16 4000 x 1304 16 -> 8.7 (one value a lane and three passes over the row
+// before); FULL: D = NV * 256.
+template <int BF, int RMS, int NV, bool FULL>
+__global__ __launch_bounds__(kT) void norm_fwd_vec_kernel(const float *x, const void *w, const void *b, void *y, float *stats, int T, int Dn, float eps) {
+  const int D = FULL ? NV * 256 : Dn;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, d4 = D >> 2;
   if (row >= T) return;
-  const int64_t rv = (int64_t)row * (D / 4);
-  auto load4b = [](const void *p, int64_t vec) -> f32x4v {
-    const u2 u = static_cast<const u2 *>(p)[vec];
-    return f32x4v{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
+  const int64_t rv = (int64_t)row * d4;
+  auto on = [&](int k) { return FULL || lane + 64 * k < d4; };
+  auto at = [&](int k) { return FULL ? lane + 64 * k : min(lane + 64 * k, d4 - 1); };
+  f32x4v xv[NV], wv[NV], bv[NV];
+  auto gains = [&](int k) {
+    const int v = at(k);
+    wv[k] = ld4<BF>(w, v);
+    bv[k] = b ? ld4<BF>(b, v) : f32x4v{0.f, 0.f, 0.f, 0.f};
   };
-  f32x4v xv[NV];
   float s = 0.f;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    xv[k] = reinterpret_cast<const f32x4v *>(x)[rv + lane + 64 * k];
-    s += xv[k][0] + xv[k][1] + xv[k][2] + xv[k][3];
+    xv[k] = reinterpret_cast<const f32x4v *>(x)[rv + at(k)];
+    if (NV <= 4) gains(k);  // (longer rows: in time enough, and in fewer registers, behind the sums)
   }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) s += on(k) ? xv[k][0] + xv[k][1] + xv[k][2] + xv[k][3] : 0.f;
   const float mean = RMS ? 0.f : wave_sum(s) / D;
   float s2 = 0.f;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     xv[k] -= mean;
-    s2 += xv[k][0] * xv[k][0] + xv[k][1] * xv[k][1] + xv[k][2] * xv[k][2] + xv[k][3] * xv[k][3];
+    s2 += on(k) ? xv[k][0] * xv[k][0] + xv[k][1] * xv[k][1] + xv[k][2] * xv[k][2] + xv[k][3] * xv[k][3] : 0.f;
   }
   const float rstd = 1.0f / sqrtf(wave_sum(s2) / D + eps);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    f32x4v o = xv[k] * rstd * load4b(w, lane + 64 * k);
-    if (b) o += load4b(b, lane + 64 * k);
-    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 lo = {o[0], o[1]}, hi = {o[2], o[3]};
-    const u2 pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, b2)), __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, b2))};
-    static_cast<u2 *>(y)[rv + lane + 64 * k] = pk;
+    if (NV > 4) gains(k);
+    if (!on(k)) continue;
+    f32x4v o = xv[k] * rstd * wv[k];
+    if (b) o += bv[k];
+    st4<BF>(y, rv + lane + 64 * k, o);
   }
   if (lane == 0) { stats[2 * row] = mean; stats[2 * row + 1] = rstd; }
 }
@@ -821,22 +931,39 @@ twist_status twist_cast_in(twist_ctx *ctx, int bf16, const void *src, float *dst
 
 static bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+// vectors of 256 columns that the register-held norm kernels are built for, enough for rows of D (0: too long, or not a multiple of 4)
+static int norm_vectors(int D) {
+  if (D % 4 || D > 4096) return 0;
+  const int n = (D + 255) / 256;
+  return n <= 4 ? n : n <= 6 ? 6 : n <= 8 ? 8 : n <= 12 ? 12 : 16;
+}
+
 twist_status twist_norm_fwd(twist_ctx *ctx, int bf16, int rms, const float *x, const void *w, const void *b, void *y, float *stats, int T, int D, float eps) {
-  const int nv = D % 256 == 0 ? D / 256 : 0;
-  if (bf16 && al16(x) && al16(w) && al16(y) && (!b || al16(b)) && (nv == 1 || nv == 2 || nv == 3 || nv == 4 || nv == 8 || nv == 16)) {
-#define TW_NORM_FWD(NV)                                                                                                                          \
-  do {                                                                                                                                           \
-    if (rms) hipLaunchKernelGGL((norm_fwd_vec_kernel<1, NV>), dim3((T + 3) / 4), dim3(kT), 0, ctx->stream, x, w, b, y, stats, T, eps);           \
-    else hipLaunchKernelGGL((norm_fwd_vec_kernel<0, NV>), dim3((T + 3) / 4), dim3(kT), 0, ctx->stream, x, w, b, y, stats, T, eps);              \
+  const int nv = norm_vectors(D);
+  if (nv && al16(x) && al16(w) && al16(y) && (!b || al16(b))) {
+#define TW_NORM_FWD(BF, RMS, NV)                                                                                                                                          \
+  do {                                                                                                                                                                   \
+    if (D == NV * 256) hipLaunchKernelGGL((norm_fwd_vec_kernel<BF, RMS, NV, true>), dim3((T + 3) / 4), dim3(kT), 0, ctx->stream, x, w, b, y, stats, T, D, eps);            \
+    else hipLaunchKernelGGL((norm_fwd_vec_kernel<BF, RMS, NV, false>), dim3((T + 3) / 4), dim3(kT), 0, ctx->stream, x, w, b, y, stats, T, D, eps);                        \
+  } while (0)
+#define TW_NORM_FWD4(NV)                     \
+  do {                                       \
+    if (bf16 && rms) TW_NORM_FWD(1, 1, NV);  \
+    else if (bf16) TW_NORM_FWD(1, 0, NV);    \
+    else if (rms) TW_NORM_FWD(0, 1, NV);     \
+    else TW_NORM_FWD(0, 0, NV);              \
   } while (0)
     switch (nv) {
-      case 1: TW_NORM_FWD(1); break;
-      case 2: TW_NORM_FWD(2); break;
-      case 3: TW_NORM_FWD(3); break;
-      case 4: TW_NORM_FWD(4); break;
-      case 8: TW_NORM_FWD(8); break;
-      default: TW_NORM_FWD(16); break;
+      case 1: TW_NORM_FWD4(1); break;
+      case 2: TW_NORM_FWD4(2); break;
+      case 3: TW_NORM_FWD4(3); break;
+      case 4: TW_NORM_FWD4(4); break;
+      case 6: TW_NORM_FWD4(6); break;
+      case 8: TW_NORM_FWD4(8); break;
+      case 12: TW_NORM_FWD4(12); break;
+      default: TW_NORM_FWD4(16); break;
     }
+#undef TW_NORM_FWD4
 #undef TW_NORM_FWD
     TW_HIP(ctx, hipGetLastError());
     return TWIST_OK;
@@ -852,32 +979,54 @@ size_t twist_colsum_partial_floats(int T, int n) { return (size_t)n_chunks(T) * 
 twist_status twist_norm_bwd(twist_ctx *ctx, int bf16, int rms, const void *dy, const float *x, const void *w, const float *stats, float *dx,
                             int accumulate, void *dxb, float *dw, float *db, float *partial, int T, int D, bool defer_reduce, float *csum) {
   const int nc = n_chunks(T);
-  const int nv = D % 256 == 0 ? D / 256 : 0;
-  const bool fused_ok = al16(dy) && al16(x) && al16(w) && al16(dx) && (!dxb || al16(dxb)) && (nv == 1 || nv == 2 || nv == 3 || nv == 4 || nv == 8 || (nv == 16 && rms && bf16));
-  if (fused_ok) {
-    float *fcs = nv <= 4 ? csum : nullptr;  // longer rows: the third set of sums costs the kernel half its waves
-#define TW_NORM_CS(BF, RMS, NV)                                                                                                                        \
-  do {                                                                                                                                                 \
-    if (fcs) hipLaunchKernelGGL((norm_bwd_fused_kernel<BF, RMS, NV, (NV <= 4)>), dim3(nc), dim3(kT), 0, ctx->stream, dy, x, w, stats, dx, accumulate, dxb, partial, fcs, T);  \
-    else hipLaunchKernelGGL((norm_bwd_fused_kernel<BF, RMS, NV, false>), dim3(nc), dim3(kT), 0, ctx->stream, dy, x, w, stats, dx, accumulate, dxb, partial, fcs, T);      \
+  const int nv = norm_vectors(D);
+  const bool cs_ok = csum && al16(csum) && dxb;
+  if (nv && al16(dy) && al16(x) && al16(w) && al16(dx) && al16(partial) && (!dxb || al16(dxb))) {
+    float *fcs = cs_ok && (nv <= 4 || nv >= 12) ? csum : nullptr;  // rows of 6 and 8 vectors: the third set of sums costs the kernel half its waves
+    const bool few = nc < 256;
+#define TW_NORM_BWD2(BF, RMS, NV, CS, W, FULL) \
+  hipLaunchKernelGGL((norm_bwd_fused_kernel<BF, RMS, NV, CS, W, FULL>), dim3(nc), dim3(64 * (W)), 0, ctx->stream, dy, x, w, stats, dx, accumulate, dxb, partial, fcs, T, D)
+#define TW_NORM_BWD(BF, RMS, NV, CS, W)                              \
+  do {                                                               \
+    if (D == NV * 256) TW_NORM_BWD2(BF, RMS, NV, CS, W, true);       \
+    else TW_NORM_BWD2(BF, RMS, NV, CS, W, false);                    \
   } while (0)
-#define TW_NORM_FUSED(NV)                     \
-  do {                                        \
-    if (bf16 && rms) TW_NORM_CS(1, 1, NV);    \
-    else if (bf16) TW_NORM_CS(1, 0, NV);      \
-    else if (rms) TW_NORM_CS(0, 1, NV);       \
-    else TW_NORM_CS(0, 0, NV);                \
+#define TW_NORM_SHORT(BF, RMS, NV)                          \
+  do {                                                      \
+    if (fcs && few) TW_NORM_BWD(BF, RMS, NV, true, 8);      \
+    else if (fcs) TW_NORM_BWD(BF, RMS, NV, true, 4);        \
+    else if (few) TW_NORM_BWD(BF, RMS, NV, false, 8);       \
+    else TW_NORM_BWD(BF, RMS, NV, false, 4);                \
+  } while (0)
+#define TW_NORM_LONG(BF, RMS, NV) TW_NORM_BWD(BF, RMS, NV, false, 4)
+#define TW_NORM_WIDE(BF, RMS, NV)                                                                                                                             \
+  do {                                                                                                                                                         \
+    if (fcs) hipLaunchKernelGGL((norm_bwd_wide_kernel<BF, RMS, NV, true>), dim3(nc), dim3(kT), 0, ctx->stream, dy, x, w, stats, dx, accumulate, dxb, partial, fcs, T, D);  \
+    else hipLaunchKernelGGL((norm_bwd_wide_kernel<BF, RMS, NV, false>), dim3(nc), dim3(kT), 0, ctx->stream, dy, x, w, stats, dx, accumulate, dxb, partial, fcs, T, D);      \
+  } while (0)
+#define TW_NORM_FUSED(KIND, NV)                \
+  do {                                         \
+    if (bf16 && rms) KIND(1, 1, NV);           \
+    else if (bf16) KIND(1, 0, NV);             \
+    else if (rms) KIND(0, 1, NV);              \
+    else KIND(0, 0, NV);                       \
   } while (0)
     switch (nv) {
-      case 1: TW_NORM_FUSED(1); break;
-      case 2: TW_NORM_FUSED(2); break;
-      case 3: TW_NORM_FUSED(3); break;
-      case 4: TW_NORM_FUSED(4); break;
-      case 8: TW_NORM_FUSED(8); break;
-      default: TW_NORM_CS(1, 1, 16); break;
+      case 1: TW_NORM_FUSED(TW_NORM_SHORT, 1); break;
+      case 2: TW_NORM_FUSED(TW_NORM_SHORT, 2); break;
+      case 3: TW_NORM_FUSED(TW_NORM_SHORT, 3); break;
+      case 4: TW_NORM_FUSED(TW_NORM_SHORT, 4); break;
+      case 6: TW_NORM_FUSED(TW_NORM_LONG, 6); break;
+      case 8: TW_NORM_FUSED(TW_NORM_LONG, 8); break;
+      case 12: TW_NORM_FUSED(TW_NORM_WIDE, 3); break;
+      default: TW_NORM_FUSED(TW_NORM_WIDE, 4); break;
     }
-#undef TW_NORM_CS
+#undef TW_NORM_WIDE
 #undef TW_NORM_FUSED
+#undef TW_NORM_LONG
+#undef TW_NORM_SHORT
+#undef TW_NORM_BWD
+#undef TW_NORM_BWD2
     TW_HIP(ctx, hipGetLastError());
     if (csum && !fcs) TW_TRY(twist_colsum(ctx, bf16, dxb, D, 1.f, nullptr, csum, T, D, true));
     if (defer_reduce) return TWIST_OK;

@@ -54,6 +54,15 @@ def test_norm_forward_and_backward(lib, dtype, kind, D, T):
         assert rel_fro(to_numpy(db), want_db) <= 1e-4
 
 
+# widths that fill the last vector of 256 columns, have one lane in it or leave most of it empty, in every kernel: a wave per row (1 to 4 vectors, with
+# four and with eight waves to a chunk of 16 rows; 6 and 8 vectors) and four waves per row (beyond 2048); ragged last chunks
+@pytest.mark.parametrize("dtype", [BF, F32])
+@pytest.mark.parametrize("kind,D,T", [("ln", 4, 5), ("rms", 12, 4097), ("ln", 252, 4100), ("ln", 260, 40), ("rms", 516, 33), ("ln", 1020, 4099), ("ln", 1284, 50), ("rms", 1536, 20),
+                                       ("ln", 1928, 35), ("ln", 2052, 18), ("rms", 3072, 33), ("ln", 3076, 19), ("ln", 4096, 33), ("rms", 4100, 17), ("ln", 70, 20)])
+def test_norm_of_any_width(lib, dtype, kind, D, T):
+    test_norm_forward_and_backward(lib, dtype, kind, D, T)
+
+
 @pytest.mark.parametrize("dtype", [BF, F32])
 @pytest.mark.parametrize("dh,Hs,B,N", [(128, 2, 2, 48), (64, 3, 1, 40), (6, 5, 2, 9)])
 def test_rotary_positions(lib, dtype, dh, Hs, B, N):
