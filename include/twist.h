@@ -353,7 +353,8 @@ TWIST_API twist_status twist_profile_mfma_ceiling(twist_ctx *ctx, int32_t waves_
                                                   size_t sink_floats, double *tflops);
 
 /* The weight-gradient projections of twist_subnet_fwd_bwd run on a second stream that the library creates
- * (default priority), next to the input-gradient kernels on the context's stream; the call still returns with
+ * (default priority), next to the input-gradient kernels on the context's stream, where a layer's are large enough
+ * to gain from it (the results are the same bits either way); the call still returns with
  * all of its work ordered before anything enqueued on the context's stream afterwards.  enable = 0 puts every
  * kernel on the context's stream (needed when per-kernel durations are to be measured one at a time).
  * Default: enabled. */

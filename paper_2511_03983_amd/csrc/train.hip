@@ -149,8 +149,12 @@ void carve(const twist_ctx *ctx, const std::vector<int32_t> &heads, const std::v
 struct SideStream {
   twist_ctx *ctx;
   bool on = false, recorded[4] = {false, false, false, false};
-  twist_status init() {
-    on = ctx->overlap;
+  // `flop`: of an average layer's weight gradients.  Where they are few the events and waits, about 12 us of host time per layer and
+  // gaps of a few us each on the device, cost more than the overlap gives.  Forward and backward of 6 layers, us, second stream / one stream:
+  //   bf16, 0.05 GFLOP 974 / 596    0.8 983 / 744    3.2 1012 / 897    7.2 1131 / 1101    12.9 1338 / 1316    14.5 1614 / 1643    26 1792 / 1866
+  //   fp32, 0.05 GFLOP 1020 / 861   0.8 1318 / 1294  1.6 1834 / 1884   3.2 1796 / 1799     3.6 1767 / 1819     7.2 2516 / 2796
+  twist_status init(double flop) {
+    on = ctx->overlap && flop >= (ctx->d.dtype == TWIST_BF16 ? 13e9 : 3e9);
     if (!on) return TWIST_OK;
     if (!ctx->side) {
       TW_HIP(ctx, hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
@@ -401,7 +405,9 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
 
   // ------------------------------------------------------------------------------------ backward through the layers
   SideStream side{ctx};
-  TW_TRY(side.init());
+  double wgrad_flop = 0.0;
+  for (int l = 0; l < d.n_layers; ++l) wgrad_flop += 2.0 * T * D * (4.0 * heads[l] * dh + (nf + 1.0) * ffn[l] * d.ffn_granule) / d.n_layers;
+  TW_TRY(side.init(wgrad_flop));
   auto wgrad = [&](int M, int Nn, const void *A, int64_t lda, const void *Bm, int64_t ldb, float *out, float alpha) {
     GemmEpilogue e;
     e.alpha = alpha; e.out = out; e.out_f32 = 1;

@@ -723,6 +723,39 @@ def test_masked_full_model_equals_the_extracted_subnet(lib, name):
         ctx.twist_subnet_fwd_bwd_masked(ctx.twist_extract(plan, fw, 0, store=lib.STORE_GRADS), plan, 0, x, y, ws, loss)
 
 
+# layers whose weight gradients go to the second stream (26 GFLOP a layer) and layers whose stay on the caller's: one stream, both and a captured pass
+# replayed between eager work all give the same bits
+@pytest.mark.parametrize("d,B,N", [(1024, 2, 1024), (1024, 1, 256)])
+def test_schedules_agree_eagerly_and_in_a_graph(lib, d, B, N):
+    cfg = replace(si.CFG3, n_layers=2, d_model=d, n_heads=8, d_head=128, d_ff=2816, vocab=0, out_unit_major=True, max_seq=N)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    draw = lambda s: (torch.randn(s, generator=gen, device="cuda") * 0.02 + (1.0 if len(s) == 1 else 0.0)).bfloat16()
+    fw = lib.FullWeights([{k: draw(s) for k, s in si.stored_shapes(cfg).items()} for _ in range(2)], {})
+    x, y = (torch.randn((B, N, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        ctx = lib.Context(lib.desc_from_cfg(cfg))
+        sub = ctx.twist_extract(ctx.twist_sample(2, 4, 1408, seed=1), fw, 0, store=lib.STORE_GRADS)
+        ws = torch.empty(ctx.twist_workspace_bytes(sub, B, N), dtype=torch.uint8, device="cuda")
+        loss = torch.zeros(1, device="cuda")
+        run = lambda: ctx.twist_subnet_fwd_bwd(sub, x, y, ws, loss)
+        grads = lambda: [sub.twist_subnet_view(l, k, GRAD).clone() for l in range(2) for k in si.layer_shapes(cfg)]
+        run()
+        want, want_loss = grads(), loss.item()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            run()
+        for mode in ("graph", "one", "graph", "both", "graph"):
+            sub.storage.view(torch.uint8)[-(sub.storage.numel() // 3):].fill_(0x7f)    # (gradients are the last region)
+            loss.fill_(-1.0)
+            ctx.twist_set_overlap(mode != "one")
+            g.replay() if mode == "graph" else run()
+            stream.synchronize()
+            assert loss.item() == want_loss, mode
+            assert all(torch.equal(a, b) for a, b in zip(grads(), want)), mode
+
+
 # batches large enough that the masked pass runs on the kept blocks only: both storage orientations, biases, FFN blocks of one and of
 # eight neurons, a layer kept whole, one kind of block kept whole
 @pytest.mark.parametrize("name,cfg,hs,fs,shared,B,N", [
