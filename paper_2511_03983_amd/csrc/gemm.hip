@@ -284,7 +284,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
     for (int p = 0; p < 32 / RPI; ++p) {
       const int row = RPI * p + rq, m = m0 + wm + 32 * i + row;
       const f32x4 v4 = *reinterpret_cast<const f32x4 *>(stage + row * EPI_LD + 4 * cq);
-      if (m < M && ncol < N) store_quad<true>(ep, outp, m, ncol, N, v4, bias, vec);
+      if (m < M && ncol < N) store_quad<true, false>(ep, outp, m, ncol, N, v4, bias, vec);
     }
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's staged results are in registers
@@ -465,8 +465,8 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
     hipStream_t s; hipEvent_t e;
     ~StopRecorder() { if (e) (void)hipEventRecord(e, s); }
   } stop_recorder{stream, ev_stop};
-  Ep ep{e.alpha, e.bias, e.residual, e.out, e.out_f32, ldc, 0};
-  ep.vec_ok = ldc % 4 == 0 && aligned16(e.out) && (!e.residual || aligned16(e.residual));
+  Ep ep{e.alpha, e.bias, e.residual, e.out, e.out_f32, ldc, nullptr, 0, 0};
+  ep.vec_ok = ldc % 4 == 0 && aligned16(e.out) && (!e.residual || aligned16(e.residual)) && aligned16(e.act_out);
   const bool no_mfma = ctx->plain_only;
   // 16-byte chunks along k must not straddle the end of an operand row.  For y = x W with a ragged K the
   // caller pads x's rows (lda >= K rounded up to 8) with zeros; W's rows beyond K are never touched.
@@ -479,7 +479,12 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
     const uint16_t *a = static_cast<const uint16_t *>(A), *b = static_cast<const uint16_t *>(B);
     const Cut ch = cut_of(ctx, lay, M, N, K, e.out_f32, e.splitk_ws && !e.bias && !e.residual && aligned16(e.splitk_ws), e.splitk_floats);
     const int parts = ch.parts, kchunk = ch.kchunk;
-    if (parts > 1) ep = Ep{1.f, nullptr, nullptr, e.splitk_ws, 1, N, N % 4 == 0};
+    if (e.act_out) {
+      ep.act_out = e.act_out;
+      ep.act = e.act;
+      if (e.act_only) ep.out = nullptr;
+    }
+    if (parts > 1) ep = Ep{1.f, nullptr, nullptr, e.splitk_ws, 1, N, nullptr, 0, N % 4 == 0};
     switch (ch.kind) {
       case 0: launch_pp<256>(stream, lay, M, N, K, a, lda, b, ldb, ep, parts, kchunk); break;
       case 1: launch_pp<128>(stream, lay, M, N, K, a, lda, b, ldb, ep, parts, kchunk); break;
@@ -489,7 +494,11 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
     TW_HIP(ctx, hipGetLastError());
     return parts > 1 ? twist_splitk_reduce(ctx, stream, e.splitk_ws, parts, M, N, e.out, ldc, e.out_f32, e.alpha) : TWIST_OK;
   }
-  if (!bf16 && !no_mfma && !short_f32(ctx, lay, M, N, K)) return twist_gemm_f32(ctx, stream, lay, M, N, K, static_cast<const float *>(A), lda, static_cast<const float *>(B), ldb, ldc, e);
+  auto activate = [&]() -> twist_status { return e.act_out ? twist_act_fwd(ctx, bf16, e.act, e.out, e.act_out, M, N) : TWIST_OK; };  // the kernels below do not
+  if (!bf16 && !no_mfma && !short_f32(ctx, lay, M, N, K)) {
+    TW_TRY(twist_gemm_f32(ctx, stream, lay, M, N, K, static_cast<const float *>(A), lda, static_cast<const float *>(B), ldb, ldc, e));
+    return activate();
+  }
   int64_t sam, sak, sbk, sbn;
   switch (lay) {
     case GEMM_NT: sam = lda; sak = 1; sbk = 1; sbn = ldb; break;
@@ -500,7 +509,7 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
   if (bf16) hipLaunchKernelGGL(gemm_plain_kernel<1>, grid, block, 0, stream, M, N, K, A, sam, sak, B, sbk, sbn, ep);
   else hipLaunchKernelGGL(gemm_plain_kernel<0>, grid, block, 0, stream, M, N, K, A, sam, sak, B, sbk, sbn, ep);
   TW_HIP(ctx, hipGetLastError());
-  return TWIST_OK;
+  return activate();
 }
 
 extern "C" twist_status twist_gemm_raw(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, const void *A, int64_t lda, const void *B,

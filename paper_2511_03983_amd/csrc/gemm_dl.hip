@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256) void gemm_dl_kernel(int M, int N, int K, const
       for (int p = 0; p < 32 / RPI; ++p) {
         const int row = RPI * p + rq, m = m0 + wm + 32 * i + row;
         const f32x4 v4 = *reinterpret_cast<const f32x4 *>(stage + row * LDE + 4 * cq);
-        if (m < M && ncol < N) store_quad<false>(ep, outp, m, ncol, N, v4, bias, vec);
+        if (m < M && ncol < N) store_quad<false, AKM && BKM>(ep, outp, m, ncol, N, v4, bias, vec);
       }
     }
   } else {
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void gemm_dl_kernel(int M, int N, int K, const
       f32x4 v4 = *reinterpret_cast<const f32x4 *>(stage + row * LDE + 4 * cq);
 #pragma unroll
       for (int w = 1; w < 4; ++w) v4 += *reinterpret_cast<const f32x4 *>(stage + (w * BM + row) * LDE + 4 * cq);
-      if (m < M && ncol < N) store_quad<false>(ep, outp, m, ncol, N, v4, bias, vec);
+      if (m < M && ncol < N) store_quad<false, AKM && BKM>(ep, outp, m, ncol, N, v4, bias, vec);
     }
   }
 }

@@ -151,7 +151,7 @@ __global__ __launch_bounds__(512) void gemm_nt_kernel(int M, int N, int K, const
   }
   const bool vec = ep.vec_ok && ncol + 3 < N;
   // a tile that lies inside the output and needs nothing but the conversion (most projections): no edge tests, no arithmetic
-  const bool bare = ep.vec_ok && !ep.bias && !ep.residual && ep.alpha == 1.f && m0 + 256 <= M && n0 + BN <= N;
+  const bool bare = ep.vec_ok && !ep.act_out && !ep.bias && !ep.residual && ep.alpha == 1.f && m0 + 256 <= M && n0 + BN <= N;
 #pragma unroll
   for (int i = 0; i < TM / 2; ++i) {
 #pragma unroll
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(512) void gemm_nt_kernel(int M, int N, int K, const
     for (int p = 0; p < 32 / RPI; ++p) {
       const int row = RPI * p + rq, m = m0 + wm + 32 * i + row;
       const f32x4 v4 = *reinterpret_cast<const f32x4 *>(stage + row * EPI_LD + 4 * cq);
-      if (m < M && ncol < N) store_quad<true>(ep, ep.out, m, ncol, N, v4, bias, vec);
+      if (m < M && ncol < N) store_quad<true, true>(ep, ep.out, m, ncol, N, v4, bias, vec);
     }
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's staged results are in registers

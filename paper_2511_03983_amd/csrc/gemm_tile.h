@@ -1,5 +1,6 @@
 // Device code shared by the bf16 projection kernels (gemm.hip, gemm_dl.hip): operand types, the epilogue's arguments, conversions.
 #pragma once
+#include "act.h"
 #include "nn.h"
 
 namespace {
@@ -36,7 +37,9 @@ struct Ep {
   void *out;
   int out_f32;
   int64_t ldc;
-  int vec_ok;  // out (and residual) rows allow 4-element vector accesses: ldc % 4 == 0, 16-byte aligned bases
+  void *act_out;  // f(out as stored) of an ungated activation, laid out like out, bf16 (or null); out may then be null
+  int act;
+  int vec_ok;  // out (and residual, act_out) rows allow 4-element vector accesses: ldc % 4 == 0, 16-byte aligned bases
 };
 
 constexpr uint32_t kOob = 0x80000000u;  // byte offset beyond every buffer: loads return 0, stores are dropped
@@ -70,8 +73,8 @@ __device__ __forceinline__ void dma16(desc_t desc, const char *lds, uint32_t vof
                : "=&s"(keep) : "s"(l), "v"(voff), "s"(desc) : "memory");
 }
 
-// Stores four consecutive columns ncol .. ncol + 3 of row m: out = (v4 + bias) alpha + residual (STREAM: past the caches)
-template <bool STREAM>
+// Stores four consecutive columns ncol .. ncol + 3 of row m: out = (v4 + bias) alpha + residual (STREAM: past the caches), and (ACT) its activation
+template <bool STREAM, bool ACT>
 __device__ __forceinline__ void store_quad(const Ep &ep, void *outp, int m, int ncol, int N, const f32x4 &v4, const float (&bias)[4], bool vec) {
   const int64_t o = (int64_t)m * ep.ldc + ncol;
   float v[4];
@@ -91,8 +94,20 @@ __device__ __forceinline__ void store_quad(const Ep &ep, void *outp, int m, int 
     } else {
       const u32x2 w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
       u32x2 *p = reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(outp) + o);
-      if (STREAM) __builtin_nontemporal_store(w, p);
-      else *p = w;
+      if (ACT && !outp) {
+      } else if (STREAM) {
+        __builtin_nontemporal_store(w, p);
+      } else {
+        *p = w;
+      }
+      if (ACT && ep.act_out) {
+        const float f[4] = {act_value<false>(ep.act, bf2f((uint16_t)w.x)), act_value<false>(ep.act, bf2f((uint16_t)(w.x >> 16))),
+                            act_value<false>(ep.act, bf2f((uint16_t)w.y)), act_value<false>(ep.act, bf2f((uint16_t)(w.y >> 16)))};
+        const u32x2 a = {pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3])};
+        u32x2 *q = reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(ep.act_out) + o);
+        if (STREAM) __builtin_nontemporal_store(a, q);
+        else *q = a;
+      }
     }
   } else {
 #pragma unroll
@@ -100,8 +115,13 @@ __device__ __forceinline__ void store_quad(const Ep &ep, void *outp, int m, int 
       if (ncol + e >= N) break;
       float x = v[e];
       if (ep.residual) x += ep.residual[o + e];
-      if (ep.out_f32) static_cast<float *>(outp)[o + e] = x;
-      else static_cast<uint16_t *>(outp)[o + e] = f2bf(x);
+      if (ep.out_f32) {
+        static_cast<float *>(outp)[o + e] = x;
+      } else {
+        const uint16_t w = f2bf(x);
+        if (!ACT || outp) static_cast<uint16_t *>(outp)[o + e] = w;
+        if (ACT && ep.act_out) static_cast<uint16_t *>(ep.act_out)[o + e] = f2bf(act_value<false>(ep.act, bf2f(w)));
+      }
     }
   }
 }

@@ -1,6 +1,7 @@
 // Memory-bound kernels of the subnet training path: embedding, norms (Appendix A.1), rotary positions,
 // activations, losses, reductions for bias / gain gradients, and the local optimizer steps.
 // Activations and weights are fp32 or bf16 (template flag BF); all arithmetic is fp32.
+#include "act.h"
 #include "nn.h"
 
 namespace {
@@ -468,15 +469,6 @@ __global__ __launch_bounds__(kT) void rope_kernel(void *qkv, const float *tab, i
 }
 
 // ------------------------------------------------------------------------------------------- activations
-__device__ __forceinline__ float gelu_tanh(float u) {
-  const float k0 = 0.7978845608028654f, k1 = 0.044715f;
-  return 0.5f * u * (1.f + tanhf(k0 * (u + k1 * u * u * u)));
-}
-__device__ __forceinline__ float gelu_tanh_grad(float u) {
-  const float k0 = 0.7978845608028654f, k1 = 0.044715f;
-  float t = tanhf(k0 * (u + k1 * u * u * u));
-  return 0.5f * (1.f + t) + 0.5f * u * (1.f - t * t) * k0 * (1.f + 3.f * k1 * u * u);
-}
 __device__ __forceinline__ float sigmoidf(float x) { return 1.f / (1.f + __expf(-x)); }
 
 // `keep` (may be null): the Masked-TwIST neuron mask of Section 4.1, y = M * f(x).  keep[b] < 0 marks FFN block b (of
@@ -492,8 +484,7 @@ __global__ __launch_bounds__(kT) void act_fwd_kernel(int act, const void *gu, vo
     float g = El<BF>::ld(gu, t * 2 * F + c), u = El<BF>::ld(gu, t * 2 * F + F + c);
     o = g * sigmoidf(g) * u;
   } else {
-    float u = El<BF>::ld(gu, i);
-    o = act == TWIST_ACT_RELU ? fmaxf(u, 0.f) : gelu_tanh(u);
+    o = act_value<BF == 0>(act, El<BF>::ld(gu, i));
   }
   if (keep && keep[c / unit] < 0) o = 0.f;
   El<BF>::st(a, i, o);
@@ -513,7 +504,7 @@ __global__ __launch_bounds__(kT) void act_bwd_kernel(int act, const void *gu, co
     El<BF>::st(dgu, t * 2 * F + c, d * u * (sg + g * sg * (1.f - sg)));
   } else {
     float u = El<BF>::ld(gu, i);
-    El<BF>::st(dgu, i, d * (act == TWIST_ACT_RELU ? (u > 0.f ? 1.f : 0.f) : gelu_tanh_grad(u)));
+    El<BF>::st(dgu, i, d * (act == TWIST_ACT_RELU ? (u > 0.f ? 1.f : 0.f) : gelu_tanh_grad<BF == 0>(u)));
   }
 }
 
@@ -772,7 +763,7 @@ __global__ __launch_bounds__(kT) void act_fwd_vec_kernel(int act, const u32x4v *
   const F8 x = unpack8(u[i]);
   F8 o;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o.v[e] = act == TWIST_ACT_RELU ? fmaxf(x.v[e], 0.f) : gelu_tanh(x.v[e]);
+  for (int e = 0; e < 8; ++e) o.v[e] = act_value<false>(act, x.v[e]);
   if (keep) mask8(o, keep, unit, 8 * (int)(i % F8n));
   a[i] = pack8(o);
 }
@@ -786,7 +777,7 @@ __global__ __launch_bounds__(kT) void act_bwd_vec_kernel(int act, const u32x4v *
   if (keep) mask8(d, keep, unit, 8 * (int)(i % F8n));
   F8 o;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o.v[e] = d.v[e] * (act == TWIST_ACT_RELU ? (x.v[e] > 0.f ? 1.f : 0.f) : gelu_tanh_grad(x.v[e]));
+  for (int e = 0; e < 8; ++e) o.v[e] = d.v[e] * (act == TWIST_ACT_RELU ? (x.v[e] > 0.f ? 1.f : 0.f) : gelu_tanh_grad<false>(x.v[e]));
   du[i] = pack8(o);
 }
 

@@ -368,8 +368,14 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     else TW_TRY(gemm(GEMM_NT, T, D, HD, b.o, HD, PW(l, TWIST_WO), HD, w.xs[2 * l + 1], D, 1, c_a, P(L.at(l, TWIST_BO)), w.xs[2 * l]));
     TW_TRY(twist_norm_fwd(ctx, bf, rms, w.xs[2 * l + 1], P(L.at(l, TWIST_NORM2_W)), P(L.at(l, TWIST_NORM2_B)), b.h2, w.stats[2 * l + 1], T, D, d.norm_eps));
     const int w1 = nf == 2 ? TWIST_W_GATE : TWIST_W_UP;
-    TW_TRY(gemm(GEMM_NT, T, nf * F, D, b.h2, D, PW(l, w1), D, b.gu, nf * F, 0, 1.f, PW(l, TWIST_B_UP)));
-    TW_TRY(twist_act_fwd(ctx, bf, d.act, b.gu, b.a, T, F, keep_of(l, TWIST_KIND_FFN), d.ffn_granule));
+    if (nf == 1 && !in_place) {  // ungated: the projection applies it
+      GemmEpilogue e;
+      e.bias = PW(l, TWIST_B_UP); e.out = b.gu; e.act_out = b.a; e.act = d.act; e.act_only = forward_only;
+      TW_TRY(twist_gemm(ctx, bf, GEMM_NT, T, F, D, b.h2, D, PW(l, w1), D, F, e));
+    } else {
+      TW_TRY(gemm(GEMM_NT, T, nf * F, D, b.h2, D, PW(l, w1), D, b.gu, nf * F, 0, 1.f, PW(l, TWIST_B_UP)));
+      TW_TRY(twist_act_fwd(ctx, bf, d.act, b.gu, b.a, T, F, keep_of(l, TWIST_KIND_FFN), d.ffn_granule));
+    }
     if (um) TW_TRY(gemm(GEMM_NN, T, D, F, b.a, F, PW(l, TWIST_W_DOWN), D, w.xs[2 * l + 2], D, 1, c_f, P(L.at(l, TWIST_B_DOWN)), w.xs[2 * l + 1]));
     else TW_TRY(gemm(GEMM_NT, T, D, F, b.a, F, PW(l, TWIST_W_DOWN), F, w.xs[2 * l + 2], D, 1, c_f, P(L.at(l, TWIST_B_DOWN)), w.xs[2 * l + 1]));
   }

@@ -723,6 +723,40 @@ def test_masked_full_model_equals_the_extracted_subnet(lib, name):
         ctx.twist_subnet_fwd_bwd_masked(ctx.twist_extract(plan, fw, 0, store=lib.STORE_GRADS), plan, 0, x, y, ws, loss)
 
 
+# The up projection applies the activation to what it stores; the masked pass in place runs it in a kernel of its own.  With nothing masked both are
+# the same pass: same loss, same gradients, bit for bit, and evaluation (which does not store the pre-activation) gives the same loss.  Sizes reach every projection
+# kernel: tiles of 32 and 64, 256 rows by 128 and 256 columns with ragged edges, the plain one (odd widths, fp32)
+@pytest.mark.parametrize("act", ["gelu_tanh", "relu"])
+@pytest.mark.parametrize("dtype,d,ff,B,N,tile", [("bf16", 72, 136, 1, 33, 32), ("bf16", 200, 1000, 3, 333, 64), ("bf16", 264, 1544, 3, 700, 128), ("bf16", 264, 3080, 4, 1000, 256),
+                                                 ("bf16", 66, 130, 2, 40, 0), ("f32", 72, 136, 2, 40, 0)])
+def test_activation_in_the_projection_and_behind_it_agree(lib, act, dtype, d, ff, B, N, tile):
+    cfg = si.ModelCfg(n_layers=2, d_model=d, n_heads=2, d_head=32, d_ff=ff, act=act, vocab=0, max_seq=N, dtype=dtype)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    draw = lambda s: (torch.randn(s, generator=gen, device="cuda") * 0.05 + (1.0 if len(s) == 1 else 0.0)).to(dt)
+    fw = lib.FullWeights([{k: draw(s) for k, s in si.stored_shapes(cfg).items()} for _ in range(2)], {})
+    x, y = (torch.randn((B, N, d), generator=gen, device="cuda").to(dt) for _ in range(2))
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    if tile:
+        assert ctx.twist_gemm_kernel(0, B * N, ff, d)[1] == tile
+    plan = ctx.twist_sample(1, 2, ff, seed=0)
+    sub = ctx.twist_extract(plan, fw, 0, store=lib.STORE_GRADS)
+    ws = torch.empty(ctx.twist_workspace_bytes(sub, B, N), dtype=torch.uint8, device="cuda")
+    loss = torch.zeros(3, device="cuda")
+    grads = lambda: [sub.twist_subnet_view(l, k, GRAD).clone() for l in range(2) for k in si.layer_shapes(cfg)]
+    assert not ctx.twist_masked_form(plan, B, N)
+    ctx.twist_subnet_fwd_bwd_masked(sub, plan, 0, x, y, ws, loss[:1])
+    want = grads()
+    ws.fill_(0x7f)
+    ctx.twist_subnet_fwd_bwd(sub, x, y, ws, loss[1:2])
+    got = grads()
+    ws.fill_(0x7f)
+    ctx.twist_subnet_forward(sub, x, y, ws, loss[2:])
+    torch.cuda.synchronize()
+    assert torch.isfinite(loss).all() and loss[0] == loss[1] == loss[2]
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
 # layers whose weight gradients go to the second stream (26 GFLOP a layer) and layers whose stay on the caller's: one stream, both and a captured pass
 # replayed between eager work all give the same bits
 @pytest.mark.parametrize("d,B,N", [(1024, 2, 1024), (1024, 1, 256)])
