@@ -485,6 +485,12 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
       if (e.act_only) ep.out = nullptr;
     }
     if (parts > 1) ep = Ep{1.f, nullptr, nullptr, e.splitk_ws, 1, N, nullptr, 0, N % 4 == 0};
+    if (e.targets && lay == GEMM_NT && ch.kind < 2 && !e.out_f32 && !e.bias && !e.residual && e.alpha == 1.f) {
+      twist_launch_gemm_nt(stream, ch.kind ? 128 : 256, M, N, K, a, lda, b, ldb, &ep, e.targets, e.loss_parts, e.target_logit);
+      TW_HIP(ctx, hipGetLastError());
+      *e.loss_blocks = 2 * ((N + kKinds[ch.kind].bn - 1) / kKinds[ch.kind].bn);
+      return TWIST_OK;
+    }
     switch (ch.kind) {
       case 0: launch_pp<256>(stream, lay, M, N, K, a, lda, b, ldb, ep, parts, kchunk); break;
       case 1: launch_pp<128>(stream, lay, M, N, K, a, lda, b, ldb, ep, parts, kchunk); break;

@@ -11,6 +11,9 @@
 // 8192 x 32000 x 2048 950 -> 858, 8192 x 5632 x 2048 166 -> 147.
 // The same for an operand that is read back with the transposing LDS load gained nothing (its rows of 512 bytes are whole lines already
 // and its memory phase is the longer one): those orientations stay in gemm.hip.
+// LOSS: a vocabulary projection whose caller only wants the cross-entropy (evaluation).  A lane holds 4 columns of every 16 of a row, so
+// a row's maximum and sum of exponentials over a wave's columns take two exchanges between lanes, and nothing but those two numbers is
+// written: no burst of stores, no second pass.  4096 x 50257 x 768 with its loss: 397 + 76 us (logits written, read again) -> 337 + 6.
 #include <algorithm>
 
 #include "gemm_tile.h"
@@ -50,9 +53,9 @@ struct Loader {
   }
 };
 
-template <int BN>
+template <int BN, bool LOSS>
 __global__ __launch_bounds__(512) void gemm_nt_kernel(int M, int N, int K, const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, Ep ep, int tiles_m,
-                                                      int tiles_n) {
+                                                      int tiles_n, const int32_t *targets, float *loss_parts, float *target_logit) {
   constexpr int TM = 4, TN = BN / 32, WN = BN / 2;  // 16x16 tiles of a wave, its columns
   constexpr int OPA = 256 * SK * 2, STG = OPA + BN * SK * 2;  // bytes of A's sub-tile; of a stage: A, then B
   constexpr int LPP = 4 + BN / 64;               // loads per pair of sub-tiles and wave
@@ -137,6 +140,41 @@ __global__ __launch_bounds__(512) void gemm_nt_kernel(int M, int N, int K, const
   NT_WAIT(0);                    // own zero-filling loads beyond the last sub-tile
   __builtin_amdgcn_s_barrier();  // ... and everybody else's: LDS is reused below
 
+  if constexpr (LOSS) {
+    const int col0 = n0 + wn + 4 * q, blocks = 2 * tiles_n, block = col0 / WN;
+    const bool edge = n0 + BN > N;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int row = m0 + wm + 16 * i + s;
+      const int at = (row < M ? targets[row] : -1) - col0;  // the target's distance from the lane's first column
+      float mx = -INFINITY, target = 0.f;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const uint32_t lo = pack_bf16(acc[i][j][0], acc[i][j][1]), hi = pack_bf16(acc[i][j][2], acc[i][j][3]);  // the logits as they would be stored
+        acc[i][j] = f32x4{bf2f((uint16_t)lo), bf2f((uint16_t)(lo >> 16)), bf2f((uint16_t)hi), bf2f((uint16_t)(hi >> 16))};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (at == 16 * j + e) target = acc[i][j][e];
+          if (edge && col0 + 16 * j + e >= N) acc[i][j][e] = -INFINITY;
+          mx = fmaxf(mx, acc[i][j][e]);
+        }
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float ref = mx == -INFINITY ? 0.f : mx;
+      float sum = 0.f;
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum += __expf(acc[i][j][e] - ref);
+      sum += __shfl_xor(sum, 16, 64);
+      sum += __shfl_xor(sum, 32, 64);
+      if (row >= M) continue;
+      if (q == 0) *reinterpret_cast<f32x2 *>(loss_parts + ((int64_t)row * blocks + block) * 2) = f32x2{mx, sum};
+      if (at >= 0 && at < WN && (at & 15) < 4) target_logit[row] = target;
+    }
+    continue;
+  }
   // Epilogue.  Of a 16x16 accumulator tile a lane holds columns 4 (lane / 16) .. + 3 of row lane % 16; each wave turns its results
   // through LDS, 32 rows at a time, so that a store instruction writes two full rows of 128 columns (four of 64).
   float *stage = reinterpret_cast<float *>(smem + wave * (32 * EPI_LD * 4));
@@ -187,10 +225,15 @@ __global__ __launch_bounds__(512) void gemm_nt_kernel(int M, int N, int K, const
 
 }  // namespace
 
-void twist_launch_gemm_nt(hipStream_t st, int bn, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep) {
+void twist_launch_gemm_nt(hipStream_t st, int bn, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep,
+                          const int32_t *targets, float *loss_parts, float *target_logit) {
   const Ep &e = *static_cast<const Ep *>(ep);
   const int tm = (M + 255) / 256, tn = (N + bn - 1) / bn;
   const dim3 grid(std::min(tm * tn, 256)), block(512);
-  if (bn == 256) hipLaunchKernelGGL(gemm_nt_kernel<256>, grid, block, 0, st, M, N, K, a, lda, b, ldb, e, tm, tn);
-  else hipLaunchKernelGGL(gemm_nt_kernel<128>, grid, block, 0, st, M, N, K, a, lda, b, ldb, e, tm, tn);
+#define TW_NT(BN, LOSS) hipLaunchKernelGGL((gemm_nt_kernel<BN, LOSS>), grid, block, 0, st, M, N, K, a, lda, b, ldb, e, tm, tn, targets, loss_parts, target_logit)
+  if (targets && bn == 256) TW_NT(256, true);
+  else if (targets) TW_NT(128, true);
+  else if (bn == 256) TW_NT(256, false);
+  else TW_NT(128, false);
+#undef TW_NT
 }

@@ -19,6 +19,12 @@ struct GemmEpilogue {
   void *act_out = nullptr;
   int act = 0;
   bool act_only = false;
+  // Evaluation of a vocabulary projection: with `targets` the kernels of 256-row tiles may reduce each row of the (rounded) output to what its cross-entropy
+  // needs instead of writing it: loss_parts[row][*loss_blocks][2] = (maximum, sum of exponentials against it) of a block of columns, and
+  // target_logit[row].  *loss_blocks stays 0 where the output was written as usual; loss_parts may share its memory.
+  const int32_t *targets = nullptr;
+  float *loss_parts = nullptr, *target_logit = nullptr;
+  int *loss_blocks = nullptr;
 };
 constexpr size_t kSplitkFloats = (size_t)256 * 256 * 256;
 
@@ -33,8 +39,9 @@ enum GemmLayout {
 twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, int K, const void *A, int64_t lda, const void *B,
                         int64_t ldb, int64_t ldc, const GemmEpilogue &ep, hipStream_t st = nullptr);
 
-// the bf16 ping-pong kernel for GEMM_NT (ep: a gemm_tile.h Ep), tiles of 256 x bn, bn = 256 or 128
-void twist_launch_gemm_nt(hipStream_t st, int bn, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep);
+// the bf16 ping-pong kernel for GEMM_NT (ep: a gemm_tile.h Ep), tiles of 256 x bn, bn = 256 or 128; with `targets` the rows' loss parts instead of an output
+void twist_launch_gemm_nt(hipStream_t st, int bn, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep,
+                          const int32_t *targets = nullptr, float *loss_parts = nullptr, float *target_logit = nullptr);
 // the bf16 kernels for tiles of 64 and 32 (ep: a gemm_tile.h Ep), the contraction cut into `parts` parts of kchunk (a multiple of 128)
 void twist_launch_gemm_dl(hipStream_t st, int tile, GemmLayout lay, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep,
                           int parts, int kchunk);
@@ -118,6 +125,8 @@ twist_status twist_act_bwd(twist_ctx *ctx, int bf16, int act, const void *gu, co
 
 // logits [T,V] -> in place dlogits = (softmax - onehot)/T (grad) or left alone; row losses to rowloss[T]; then loss = mean
 twist_status twist_ce_fwd_bwd(twist_ctx *ctx, int bf16, void *logits, int64_t ld, const int32_t *targets, float *rowloss, float *loss, int T, int V, bool grad = true);
+// the same loss from the parts that a projection left (GemmEpilogue::targets); rowloss holds the target logits and receives the row losses
+twist_status twist_ce_parts(twist_ctx *ctx, const float *parts, int blocks, float *rowloss, float *loss, int T);
 // dx = 2 (x - y)/n ; dxb = activation-type copy; loss = mean squared error
 twist_status twist_mse_fwd_bwd(twist_ctx *ctx, int bf16, const float *x, const void *y, float *dx, void *dxb, float *partial, float *loss, int64_t n);
 

@@ -10,6 +10,7 @@ constexpr int kT = 256;
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef float f32x2v __attribute__((ext_vector_type(2)));
 
 template <int BF> struct El;
 template <> struct El<0> {
@@ -531,6 +532,21 @@ __global__ __launch_bounds__(kT) void ce_kernel(void *logits, int64_t ld, const 
   }
   // columns between V and the padded row stride are read (times zero weights) by the next projection
   for (int c = V + threadIdx.x; c < ld; c += kT) El<BF>::st(logits, base + c, 0.f);
+}
+
+// row loss from (maximum, sum of exponentials) pairs of its blocks of columns; a wave per row
+__global__ __launch_bounds__(kT) void ce_parts_kernel(const f32x2v *parts, int blocks, float *rowloss, int T) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= T) return;
+  const f32x2v *p = parts + (int64_t)row * blocks;
+  float m = -INFINITY;
+  for (int k = lane; k < blocks; k += 64) m = fmaxf(m, p[k].x);
+  m = wave_max(m);
+  const float ref = m == -INFINITY ? 0.f : m;
+  float s = 0.f;
+  for (int k = lane; k < blocks; k += 64) s += p[k].y * __expf(p[k].x - ref);
+  s = wave_sum(s);
+  if (lane == 0) rowloss[row] = m + logf(s) - rowloss[row];
 }
 
 __global__ __launch_bounds__(kT) void mean_kernel(const float *v, int64_t n, float scale, float *out) {
@@ -1146,6 +1162,13 @@ twist_status twist_ce_fwd_bwd(twist_ctx *ctx, int bf16, void *logits, int64_t ld
 #undef TW_CE2
 #undef TW_CE
   hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kT), 0, ctx->stream, rowloss, (int64_t)T, inv_T, loss);
+  TW_HIP(ctx, hipGetLastError());
+  return TWIST_OK;
+}
+
+twist_status twist_ce_parts(twist_ctx *ctx, const float *parts, int blocks, float *rowloss, float *loss, int T) {
+  hipLaunchKernelGGL(ce_parts_kernel, dim3((T + 3) / 4), dim3(kT), 0, ctx->stream, reinterpret_cast<const f32x2v *>(parts), blocks, rowloss, T);
+  hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kT), 0, ctx->stream, rowloss, (int64_t)T, 1.f / (float)T, loss);
   TW_HIP(ctx, hipGetLastError());
   return TWIST_OK;
 }

@@ -387,7 +387,19 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     const Slot &wout = d.tied_head ? L.global[TWIST_TOK_EMBED] : L.global[TWIST_LM_HEAD];
     TW_TRY(twist_norm_fwd(ctx, bf, rms, x_last, P(L.global[TWIST_FINAL_NORM_W]), P(L.global[TWIST_FINAL_NORM_B]), w.hf, w.stats[2 * d.n_layers], T, D,
                           d.norm_eps));
-    TW_TRY(gemm(GEMM_NT, T, V, D, w.hf, D, P(wout), D, w.logits, w.ld_logits, 0));
+    int blocks = 0;  // of the loss parts that the projection leaves instead of the logits
+    {
+      GemmEpilogue e;
+      e.out = w.logits;
+      if (forward_only) {
+        e.targets = static_cast<const int32_t *>(targets);
+        e.loss_parts = static_cast<float *>(w.logits);  // (8 bytes for 64 columns or more: they fit the logits' place)
+        e.target_logit = w.rowloss;
+        e.loss_blocks = &blocks;
+      }
+      TW_TRY(twist_gemm(ctx, bf, GEMM_NT, T, V, D, w.hf, D, P(wout), D, w.ld_logits, e));
+    }
+    if (blocks) return twist_ce_parts(ctx, static_cast<const float *>(w.logits), blocks, w.rowloss, loss_dev, T);
     TW_TRY(twist_ce_fwd_bwd(ctx, bf, w.logits, w.ld_logits, static_cast<const int32_t *>(targets), w.rowloss, loss_dev, T, V, !forward_only));
     if (forward_only) return TWIST_OK;
     // projection weight gradient, then the gradient flowing back into the final norm

@@ -757,6 +757,34 @@ def test_activation_in_the_projection_and_behind_it_agree(lib, act, dtype, d, ff
     assert all(torch.equal(a, b) for a, b in zip(got, want))
 
 
+# evaluation reduces the rows of wide vocabulary projections to their loss in the projection itself: the loss of the training pass, which writes the
+# logits (both sum the same rounded logits in fp32: a few roundings apart), for tiles of 256 and 128 columns, ragged rows and columns, targets in every tile
+@pytest.mark.parametrize("V,B,N,tile", [(32001, 3, 333, 256), (50257, 2, 700, 256), (33000, 2, 256, 128), (4001, 2, 700, 128), (1003, 2, 40, 32)])
+def test_evaluation_loss_is_the_training_pass_loss(lib, V, B, N, tile):
+    cfg = si.ModelCfg(n_layers=1, d_model=64, n_heads=2, d_head=32, d_ff=64, vocab=V, max_seq=N, dtype="bf16")
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    draw = lambda s: (torch.randn(s, generator=gen, device="cuda") * 0.3 + (1.0 if len(s) == 1 else 0.0)).bfloat16()
+    fw = lib.FullWeights([{k: draw(s) for k, s in si.stored_shapes(cfg).items()}], {k: draw(s) for k, s in si.global_shapes(cfg).items()})
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    assert ctx.twist_gemm_kernel(0, B * N, V, 64)[1] == tile
+    sub = ctx.twist_extract(ctx.twist_sample(1, 2, 64, seed=0), fw, 0, store=lib.STORE_GRADS)
+    x = torch.randint(0, V, (B, N), generator=gen, device="cuda", dtype=torch.int32)
+    y = torch.randint(0, V, (B, N), generator=gen, device="cuda", dtype=torch.int32)
+    y[0, 0], y[0, -1] = 0, V - 1
+    ws = torch.empty(ctx.twist_workspace_bytes(sub, B, N), dtype=torch.uint8, device="cuda")
+    loss = torch.zeros(2, device="cuda")
+    ctx.twist_subnet_fwd_bwd(sub, x, y, ws, loss[:1])
+    ws.fill_(0x7f)
+    ctx.twist_subnet_forward(sub, x, y, ws, loss[1:])
+    torch.cuda.synchronize()
+    a, b = loss.tolist()
+    assert abs(a - b) <= 1e-6 * abs(a), (a, b)
+    head = sub.twist_subnet_view(-1, "tok_embed", 0)
+    head[V - 2, 5] = float("nan")                      # a logit that is no number
+    ctx.twist_subnet_forward(sub, x, y, ws, loss[1:])
+    assert not bool(torch.isfinite(loss[1]))
+
+
 # layers whose weight gradients go to the second stream (26 GFLOP a layer) and layers whose stay on the caller's: one stream, both and a captured pass
 # replayed between eager work all give the same bits
 @pytest.mark.parametrize("d,B,N", [(1024, 2, 1024), (1024, 1, 256)])
