@@ -276,6 +276,22 @@ TWIST_API twist_status twist_gemm_raw(twist_ctx *ctx, int32_t layout, int32_t M,
 TWIST_API twist_status twist_gemm_raw_cut(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, const void *A, int64_t lda,
                                           const void *B, int64_t ldb, void *C, int64_t ldc, int32_t out_f32, float alpha, float *scratch,
                                           size_t scratch_floats);
+
+/* Weight gradients alone, as the training pass forms a layer's: out[i][M][N] = alpha a^T b over the same K rows, n <= 4 products in one
+ * launch where their kernels allow it (bf16, 16-byte aligned rows), otherwise one by one.  Rows of a and b may be padded, those of out
+ * (fp32) are not.  scratch (device, or NULL) may receive fp32 partial products.  chosen (host, or NULL) receives tile rows, tile
+ * columns and parts of the contraction of a common launch, or zeros. */
+typedef struct {
+  int32_t M, N;
+  const void *a;
+  int64_t lda;
+  const void *b;
+  int64_t ldb;
+  float *out;
+  float alpha;
+} twist_weight_grad;
+TWIST_API twist_status twist_weight_grads_raw(twist_ctx *ctx, int32_t n, const twist_weight_grad *products, int32_t K, float *scratch, size_t scratch_floats,
+                                              int32_t chosen[3]);
 /* Which matrix-core kernel a projection of this shape runs on where its operands are aligned (host only, for tests and benchmarks):
  * chosen receives the rows and columns of the output tile (0: the plain kernel) and the number of parts of the contraction,
  * given a scratch of scratch_floats (0: none). */

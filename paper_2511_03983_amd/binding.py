@@ -67,6 +67,11 @@ class RoundDesc(C.Structure):
     _fields_ = [("sample", SampleDesc), ("opt", OptDesc), ("local_steps", C.c_int32), ("B", C.c_int32), ("N", C.c_int32)]
 
 
+class WeightGrad(C.Structure):
+    _fields_ = [("M", C.c_int32), ("N", C.c_int32), ("a", C.c_void_p), ("lda", C.c_int64), ("b", C.c_void_p), ("ldb", C.c_int64),
+                ("out", C.c_void_p), ("alpha", C.c_float)]
+
+
 _vp, _i32, _sz = C.c_void_p, C.c_int32, C.c_size_t
 _PI32 = C.POINTER(C.c_int32)
 _SIGS = {
@@ -98,6 +103,7 @@ _SIGS = {
     "twist_round": ([_vp, C.POINTER(RoundDesc), C.POINTER(FullWeightsC), _vp, _vp, _vp, _sz, _vp, _sz, _vp, _sz, _vp], _i32),
     "twist_gemm_raw": ([_vp, _i32, _i32, _i32, _i32, _vp, C.c_int64, _vp, C.c_int64, _vp, C.c_int64, _i32, C.c_float], _i32),
     "twist_gemm_raw_cut": ([_vp, _i32, _i32, _i32, _i32, _vp, C.c_int64, _vp, C.c_int64, _vp, C.c_int64, _i32, C.c_float, _vp, _sz], _i32),
+    "twist_weight_grads_raw": ([_vp, _i32, C.POINTER(WeightGrad), _i32, _vp, _sz, _PI32], _i32),
     "twist_gemm_kernel": ([_vp, _i32, _i32, _i32, _i32, _i32, _sz, _PI32], _i32),
     "twist_attention_raw": ([_vp, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp], _i32),
     "twist_norm_raw": ([_vp, _vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz], _i32),
@@ -276,6 +282,16 @@ class Context:
         """twist_gemm_raw whose contraction may be cut into parts, with fp32 partial products in `scratch`."""
         _check(lib.twist_gemm_raw_cut(self.h, layout, M, N, K, _vp(A.data_ptr()), A.stride(0), _vp(B.data_ptr()), B.stride(0), _vp(out.data_ptr()),
                                       out.stride(0), int(out.dtype == torch.float32), alpha, _vp(scratch.data_ptr()), scratch.numel()), self.h)
+
+    def twist_weight_grads_raw(self, K: int, products, scratch: torch.Tensor | None, alphas):
+        """products: up to 4 triples (a [K, M], b [K, N], out [M, N] fp32); returns (tile rows, tile columns, parts) of their common
+        launch, zeros if they ran one by one."""
+        items, chosen = (WeightGrad * len(products))(), (_i32 * 3)()
+        for it, (a, b, out), alpha in zip(items, products, alphas):
+            it.M, it.N, it.a, it.lda, it.b, it.ldb, it.out, it.alpha = a.shape[1], b.shape[1], a.data_ptr(), a.stride(0), b.data_ptr(), b.stride(0), out.data_ptr(), alpha
+        _check(lib.twist_weight_grads_raw(self.h, len(products), items, K, _vp(scratch.data_ptr() if scratch is not None else None),
+                                          scratch.numel() if scratch is not None else 0, chosen), self.h)
+        return tuple(chosen)
 
     def twist_gemm_kernel(self, layout: int, M: int, N: int, K: int, out_f32: bool = False, scratch_floats: int = 0):
         """(tile rows, tile columns, parts of the contraction) of a projection whose operands are aligned; host only."""

@@ -6,6 +6,7 @@
 //  - fp32 operands: the fp32 matrix instruction (gemm_f32.hip).
 //  - anything else (unaligned bf16 shapes, fp32 contractions of a few elements): a plain tiled FMA kernel with arbitrary strides.
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm_tile.h"
 
@@ -151,9 +152,12 @@ struct Frags {
 // writes its unscaled fp32 partial product to ep.out + p * M * ldc and splitk_reduce_kernel adds the parts.  Used for
 // products with few output tiles and a long k (weight gradients), which would otherwise occupy a fraction of the CUs.
 // BN = 256, or 128: half as wide, 64x64 per wave, for products with too few tiles of 256.
-template <int AKM, bool SPLIT, int BN>
+// GROUP: the tiles of several weight gradients in one launch (with SPLIT; ksplit may be 1), nb tiles in all; their own sizes, operands
+// and output replace the arguments'.
+template <int AKM, bool SPLIT, int BN, class G = NoGroup>
 __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, Ep ep,
-                                                      int tiles_m, int tiles_n, int ksplit, int kchunk) {
+                                                      int tiles_m, int tiles_n, int ksplit, int kchunk, G group) {
+  constexpr bool GROUP_OF = std::is_same<G, TnGroup>::value;
   constexpr int TM = 2, TN = BN / 64, WN = BN / 2;
   constexpr int OPA = 256 * SK * 2, OPB = BN * SK * 2, STG = OPA + OPB;  // bytes of the operands' sub-tiles; one stage: A, then B
   constexpr int LPS = 2 + BN / 128;              // loads per sub-tile and wave
@@ -162,7 +166,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
   constexpr int LPR = WN / 4, RPI = 64 / LPR;    // lanes per output row, rows per store instruction
   constexpr int SMEM = NST * STG > 8 * EPI_WAVE ? NST * STG : 8 * EPI_WAVE;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-  const int nb = tiles_m * tiles_n;
+  const int nb = GROUP_OF ? tiles_m : tiles_m * tiles_n;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wpos = wave & 3, half = wave >> 2;  // waves w and w+4 share a SIMD and sit in different groups
   const int wm = (wpos >> 1) * 128 + half * 64, wn = (wpos & 1) * WN;
@@ -175,9 +179,17 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(int M, int N, int K, const
   // b runs on XCD b % 8) works on a contiguous range of tiles.
   const int n_items = SPLIT ? nb * ksplit : nb;
   for (int vid = blockIdx.x; vid < n_items; vid += gridDim.x) {
-  const int part = SPLIT ? vid / nb : 0;
-  int bid = SPLIT ? vid - part * nb : vid;
-  if (nb % 8 == 0) bid = (bid % 8) * (nb / 8) + bid / 8;
+  int item = vid;
+  if constexpr (GROUP_OF) item = (vid & 7) * (n_items >> 3) + min(vid & 7, n_items & 7) + (vid >> 3);  // an XCD's range stays within a part's k
+  const int part = SPLIT ? item / nb : 0;
+  int bid = SPLIT ? item - part * nb : item;
+  if constexpr (GROUP_OF) {
+    const TnProduct &p = group.p[product_of(group, bid)];
+    M = p.M; N = p.N; A = p.a; B = p.b; lda = p.lda; ldb = p.ldb; tiles_m = p.tiles_m; tiles_n = p.tiles_n;
+    ep.out = p.out; ep.ldc = N; ep.alpha = p.alpha; ep.vec_ok = p.vec_ok;
+  } else if (nb % 8 == 0) {
+    bid = (bid % 8) * (nb / 8) + bid / 8;
+  }
   const int kbeg = SPLIT ? part * kchunk : 0;
   const int Kl = SPLIT ? min(kchunk, K - kbeg) : K;  // this item's k extent
   constexpr int GROUP = 8;
@@ -316,6 +328,32 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *ws, int
   }
 }
 
+// the same for the products of a group, whose parts lie at p[].out; out[]: their gradients.  Blocks of 1024 elements, those of product i
+// from first[i] on.
+struct GroupOut { float *out[kGroupProducts]; int first[kGroupProducts]; };
+__global__ __launch_bounds__(256) void group_reduce_kernel(TnGroup g, GroupOut o, int parts) {
+  int q = 0;
+#pragma unroll
+  for (int i = 1; i < kGroupProducts; ++i)
+    if (i < g.n && (int)blockIdx.x >= o.first[i]) q = i;
+  const int64_t total = (int64_t)g.p[q].M * g.p[q].N, i = ((int64_t)(blockIdx.x - o.first[q]) * 256 + threadIdx.x) * 4;
+  if (i >= total) return;
+  const float *src = g.p[q].out + i;
+  float *out = o.out[q] + i;
+  if (total % 4 == 0 && ((reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(src)) & 15) == 0) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int p = 0; p < parts; ++p) v += *reinterpret_cast<const f32x4 *>(src + p * total);
+    *reinterpret_cast<f32x4 *>(out) = v * g.p[q].alpha;
+  } else {
+    for (int e = 0; e < 4 && i + e < total; ++e) {
+      float v = 0.f;
+      for (int p = 0; p < parts; ++p) v += src[p * total + e];
+      out[e] = v * g.p[q].alpha;
+    }
+  }
+}
+
 // Measurement aid: nothing but the 32x32x16 matrix instruction of the kernels here (gemm_nt.hip uses 16x16x32), four independent accumulator tiles per wave
 // (enough to issue back to back), operands in registers, no loads; the result is stored so that the loop stays.
 // random_operands = 0: small constants (few bits toggle between instructions); 1: four different operand pairs of
@@ -380,20 +418,23 @@ __global__ __launch_bounds__(256) void mfma_only_kernel(int iters, float *sink, 
 struct Kind { int bm, bn; double fixed, tile, tile32, s0, s1, nt; };
 constexpr Kind kKinds[] = {{256, 256, 1.0, 9.1, 0.36, 0.434, 0.32, 1.0}, {256, 128, 1.7, 4.4, 1.0, 0.344, 0.23, 1.0}, {64, 64, 2.95, 0.875, 0.19, 0.12, 0.011, 1.0},
                            {32, 32, 2.5, 0.81, 0.06, 0.068, 0.01, 0.71}};
-struct Choice { int kind, parts; };
-Choice choose(GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split, size_t split_floats) {
+struct Choice { int kind, parts; double us = 0.0, idle = 0.0; };  // idle: of the microseconds, those of CUs without a tile
+// (several products over the same K that share a launch: their tiles and outputs together)
+Choice choose(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, bool may_split, size_t split_floats) {
   Choice best{0, 1};
-  double best_us = 1e30;
+  double best_us = 1e30, outputs = 0.0;
+  for (int i = 0; i < n; ++i) outputs += (double)Ms[i] * Ns[i];
   for (int k = 0; k < 4; ++k) {
     const Kind &kd = kKinds[k];
-    const int64_t tiles = (int64_t)((M + kd.bm - 1) / kd.bm) * ((N + kd.bn - 1) / kd.bn);
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += (int64_t)((Ms[i] + kd.bm - 1) / kd.bm) * ((Ns[i] + kd.bn - 1) / kd.bn);
     for (int parts = 1; parts <= 16; ++parts) {
-      if (parts > 1 && (!may_split || K < 256 * parts || (double)parts * M * N > (double)split_floats)) break;
+      if (parts > 1 && (!may_split || K < 256 * parts || parts * outputs > (double)split_floats)) break;
       const int64_t items = tiles * parts, rounds = (items + 255) / 256;
       const double share = std::min(1.0, items / 256.0), slice = (kd.s0 + kd.s1 * share) * (lay == GEMM_NT ? kd.nt : 1.0);
       double us = kd.fixed + rounds * (kd.tile + (f32_out || parts > 1 ? kd.tile32 : 0.0) + K / 32.0 / parts * slice);
-      if (parts > 1) us += 4.4 + (parts + 1.0) * M * N * 4.0 / 2.8e6;
-      if (us < best_us) { best_us = us; best = {k, parts}; }
+      if (parts > 1) us += 4.4 + (parts + 1.0) * outputs * 4.0 / 2.8e6;
+      if (us < best_us) { best_us = us; best = {k, parts, us, us * (1.0 - (k < 2 ? items / (256.0 * rounds) : share))}; }
     }
   }
   return best;
@@ -401,11 +442,14 @@ Choice choose(GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split,
 
 // kernel, parts of the contraction and their length (a multiple of the kernel's slices) of a bf16 product whose operands are aligned
 struct Cut { int kind, parts, kchunk; };
-Cut cut_of(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split, size_t split_floats) {
-  Choice ch = choose(lay, M, N, K, f32_out, may_split && lay != GEMM_NT, split_floats);
-  if (ctx->gemm_tile) ch = {ctx->gemm_tile == 256 ? 0 : 1, 1};
+Cut cut_into(Choice ch, int K) {
   const int step = ch.kind < 2 ? 32 : 128, kchunk = ((K + ch.parts - 1) / ch.parts + step - 1) / step * step;
   return {ch.kind, (K + kchunk - 1) / kchunk, kchunk};
+}
+Cut cut_of(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split, size_t split_floats) {
+  Choice ch = choose(lay, 1, &M, &N, K, f32_out, may_split && lay != GEMM_NT, split_floats);
+  if (ctx->gemm_tile) ch = {ctx->gemm_tile == 256 ? 0 : 1, 1};
+  return cut_into(ch, K);
 }
 
 // one launch of gemm_pp_kernel: kchunk = K for an uncut contraction, else a multiple of 32
@@ -415,8 +459,8 @@ void launch_pp(hipStream_t st, GemmLayout lay, int M, int N, int K, const uint16
   const dim3 grid(std::min(tm * tn * parts, 256)), block(512);
 #define TW_PP(AKM)                                                                                                                                             \
   do {                                                                                                                                                              \
-    if (parts > 1) hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, true, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, parts, kchunk);            \
-    else hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, false, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, 1, K);                              \
+    if (parts > 1) hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, true, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, parts, kchunk, NoGroup()); \
+    else hipLaunchKernelGGL((pp::gemm_pp_kernel<AKM, false, BN>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, 1, K, NoGroup());                   \
   } while (0)
   switch (lay) {
     case GEMM_NT: twist_launch_gemm_nt(st, BN, M, N, K, a, lda, b, ldb, &ep); break;  // never cut
@@ -436,6 +480,26 @@ bool short_f32(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K) {
   return tile > 32;
 }
 
+// twist_set_gemm_profile: events around a launch (the closing one on every return path) and its operations
+struct GemmTimer {
+  twist_ctx *ctx;
+  hipStream_t st;
+  hipEvent_t stop = nullptr;
+  twist_status start(double flops) {
+    if (!ctx->prof_gemm) return TWIST_OK;
+    hipEvent_t begin, end;
+    TW_HIP(ctx, hipEventCreate(&begin));
+    TW_HIP(ctx, hipEventCreate(&end));
+    ctx->prof_events.push_back(begin);
+    ctx->prof_events.push_back(end);
+    ctx->prof_flops += flops;
+    TW_HIP(ctx, hipEventRecord(begin, st));
+    stop = end;
+    return TWIST_OK;
+  }
+  ~GemmTimer() { if (stop) (void)hipEventRecord(stop, st); }
+};
+
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
@@ -451,20 +515,8 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
                         int64_t ldc, const GemmEpilogue &e, hipStream_t st) {
   if (M <= 0 || N <= 0 || K <= 0) return TWIST_OK;
   const hipStream_t stream = st ? st : ctx->stream;
-  hipEvent_t ev_stop = nullptr;
-  if (ctx->prof_gemm) {
-    hipEvent_t ev_start;
-    TW_HIP(ctx, hipEventCreate(&ev_start));
-    TW_HIP(ctx, hipEventCreate(&ev_stop));
-    ctx->prof_events.push_back(ev_start);
-    ctx->prof_events.push_back(ev_stop);
-    ctx->prof_flops += 2.0 * M * N * K;
-    TW_HIP(ctx, hipEventRecord(ev_start, stream));
-  }
-  struct StopRecorder {  // records the closing event on every return path
-    hipStream_t s; hipEvent_t e;
-    ~StopRecorder() { if (e) (void)hipEventRecord(e, s); }
-  } stop_recorder{stream, ev_stop};
+  GemmTimer timer{ctx, stream};
+  TW_TRY(timer.start(2.0 * M * N * K));
   Ep ep{e.alpha, e.bias, e.residual, e.out, e.out_f32, ldc, nullptr, 0, 0};
   ep.vec_ok = ldc % 4 == 0 && aligned16(e.out) && (!e.residual || aligned16(e.residual)) && aligned16(e.act_out);
   const bool no_mfma = ctx->plain_only;
@@ -518,6 +570,81 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
   return activate();
 }
 
+// What bound them: the weight gradients of one layer of a small model are too few tiles each to fill the chip, cut into many parts with
+// a pass over the partial products behind each.  Together they fill it in fewer parts: 8192 x 768 x (192 heads, 768 hidden) in bf16 four
+// launches and four sums, 109 us, against 49 + 8; 2048 x 768 x (512, 2048) 77 us against 44.
+twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGrad *items, int K, float *scratch, size_t scratch_floats, hipStream_t st,
+                                int32_t *chosen) {
+  TnGroup g{};
+  GroupOut o{};
+  int Ms[kGroupProducts], Ns[kGroupProducts];
+  bool one = bf16 && !ctx->plain_only && !ctx->gemm_tile && n <= kGroupProducts;
+  for (int i = 0; i < n && one; ++i) {
+    const WeightGrad &w = items[i];
+    if (w.M <= 0 || w.N <= 0) continue;
+    Ms[g.n] = w.M; Ns[g.n] = w.N;
+    o.out[g.n] = w.out;
+    g.p[g.n++] = {static_cast<const uint16_t *>(w.a), static_cast<const uint16_t *>(w.b), w.out, w.lda, w.ldb, w.M, w.N, 0, 0, 0, w.alpha, w.N % 4 == 0 && aligned16(w.out)};
+    one = aligned16(w.a) && aligned16(w.b) && w.lda % 8 == 0 && w.ldb % 8 == 0 && K * w.lda * 2 < (1ll << 31) && K * w.ldb * 2 < (1ll << 31) &&
+          256ll * w.N * 4 < (1ll << 31);
+  }
+  if (!one || g.n < 2 || K <= 0) {
+    for (int i = 0; i < n; ++i) {
+      GemmEpilogue e;
+      e.alpha = items[i].alpha; e.out = items[i].out; e.out_f32 = 1;
+      e.splitk_ws = scratch; e.splitk_floats = scratch_floats;
+      TW_TRY(twist_gemm(ctx, bf16, GEMM_TN, items[i].M, items[i].N, K, items[i].a, items[i].lda, items[i].b, items[i].ldb, items[i].N, e, st));
+    }
+    return TWIST_OK;
+  }
+  const hipStream_t stream = st ? st : ctx->stream;
+  GemmTimer timer{ctx, stream};
+  double outputs = 0.0;
+  for (int i = 0; i < g.n; ++i) outputs += (double)Ms[i] * Ns[i];
+  TW_TRY(timer.start(2.0 * outputs * K));
+  const Cut ch = cut_into(choose(GEMM_TN, g.n, Ms, Ns, K, true, scratch && aligned16(scratch), scratch_floats), K);
+  if (chosen) { chosen[0] = kKinds[ch.kind].bm; chosen[1] = kKinds[ch.kind].bn; chosen[2] = ch.parts; }
+  int tiles = 0, blocks = 0;
+  float *part0 = scratch;
+  for (int i = 0; i < g.n; ++i) {
+    TnProduct &p = g.p[i];
+    p.tiles_m = (p.M + kKinds[ch.kind].bm - 1) / kKinds[ch.kind].bm;
+    p.tiles_n = (p.N + kKinds[ch.kind].bn - 1) / kKinds[ch.kind].bn;
+    p.first = tiles;
+    tiles += p.tiles_m * p.tiles_n;
+    o.first[i] = blocks;
+    blocks += (int)(((int64_t)p.M * p.N + 1023) / 1024);
+    if (ch.parts > 1) {
+      p.out = part0;
+      p.vec_ok = p.N % 4 == 0 && aligned16(part0);
+      part0 += (int64_t)ch.parts * p.M * p.N;
+    }
+  }
+  TnGroup run = g;
+  if (ch.parts > 1)
+    for (int i = 0; i < g.n; ++i) run.p[i].alpha = 1.f;
+  Ep ep{1.f, nullptr, nullptr, nullptr, 1, 0, nullptr, 0, 0};
+  if (ch.kind < 2) {
+    const dim3 grid(std::min(tiles * ch.parts, 256)), block(512);
+    if (ch.kind == 0) hipLaunchKernelGGL((pp::gemm_pp_kernel<0, true, 256, TnGroup>), grid, block, 0, stream, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, ch.parts, ch.kchunk, run);
+    else hipLaunchKernelGGL((pp::gemm_pp_kernel<0, true, 128, TnGroup>), grid, block, 0, stream, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, ch.parts, ch.kchunk, run);
+  } else {
+    twist_launch_gemm_dl_group(stream, ch.kind == 2 ? 64 : 32, &run, tiles, K, &ep, ch.parts, ch.kchunk);
+  }
+  TW_HIP(ctx, hipGetLastError());
+  if (ch.parts > 1) {
+    hipLaunchKernelGGL(group_reduce_kernel, dim3(blocks), dim3(256), 0, stream, g, o, ch.parts);
+    TW_HIP(ctx, hipGetLastError());
+  }
+  return TWIST_OK;
+}
+
+void twist_gemm_estimate(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, size_t split_floats, GemmEstimate &sum) {
+  const Choice ch = choose(lay, n, Ms, Ns, K, f32_out, split_floats > 0, split_floats);
+  sum.us += ch.us;
+  sum.idle += ch.idle;
+}
+
 extern "C" twist_status twist_gemm_raw(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, const void *A, int64_t lda, const void *B,
                                        int64_t ldb, void *C, int64_t ldc, int32_t out_f32, float alpha) {
   return twist_gemm_raw_cut(ctx, layout, M, N, K, A, lda, B, ldb, C, ldc, out_f32, alpha, nullptr, 0);
@@ -537,6 +664,20 @@ extern "C" twist_status twist_gemm_raw_cut(twist_ctx *ctx, int32_t layout, int32
   e.splitk_ws = scratch;
   e.splitk_floats = scratch_floats;
   return twist_gemm(ctx, ctx->d.dtype == TWIST_BF16, (GemmLayout)layout, M, N, K, A, lda, B, ldb, ldc, e);
+}
+
+extern "C" twist_status twist_weight_grads_raw(twist_ctx *ctx, int32_t n, const twist_weight_grad *products, int32_t K, float *scratch, size_t scratch_floats,
+                                               int32_t chosen[3]) {
+  if (!ctx || !products) TW_FAIL(ctx, TWIST_EINVAL, "twist_weight_grads_raw: null argument");
+  if (n < 1 || n > kGroupProducts || K < 0) TW_FAIL(ctx, TWIST_EINVAL, "twist_weight_grads_raw: bad number of products or rows");
+  for (int i = 0; i < n; ++i) {
+    const twist_weight_grad &p = products[i];
+    if (p.M < 0 || p.N < 0 || (p.M > 0 && p.N > 0 && (!p.a || !p.b || !p.out))) TW_FAIL(ctx, TWIST_EINVAL, "twist_weight_grads_raw: bad product %d", i);
+    if (p.lda < p.M || p.ldb < p.N) TW_FAIL(ctx, TWIST_ESHAPE, "twist_weight_grads_raw: a row stride is smaller than the row it strides");
+  }
+  if (!aligned16(scratch)) TW_FAIL(ctx, TWIST_ESHAPE, "twist_weight_grads_raw: the scratch must be 16-byte aligned");
+  if (chosen) chosen[0] = chosen[1] = chosen[2] = 0;
+  return twist_weight_grads(ctx, ctx->d.dtype == TWIST_BF16, n, products, K, scratch, scratch_floats, nullptr, chosen);
 }
 
 extern "C" twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats, int32_t chosen[3]) {

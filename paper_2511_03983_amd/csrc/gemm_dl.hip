@@ -93,9 +93,10 @@ struct Frags {
 
 #define DL_WAIT(vm) __builtin_amdgcn_s_waitcnt(0x0070 | ((vm) & 15) | ((vm) >> 4) << 14)  // vmcnt(vm < 64), lgkmcnt(0)
 
-template <int AKM, int BKM, int BM, int BN, int BK, int WK, int NST>
+// G: TnGroup for the tiles of several weight gradients in one launch, tiles_m in all (tiles_n = 1)
+template <int AKM, int BKM, int BM, int BN, int BK, int WK, int NST, class G = NoGroup>
 __global__ __launch_bounds__(256) void gemm_dl_kernel(int M, int N, int K, const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, Ep ep, int tiles_m,
-                                                      int tiles_n, int kchunk) {
+                                                      int tiles_n, int kchunk, G group) {
   constexpr int WM = WK == 1 ? 2 : 1, TM = BM / WM / 32, TN = BN / WM / 32, KS = BK / 16 / WK;  // KS: k-steps per slice and wave
   using OA = Operand<AKM, BM, BK>;
   using OB = Operand<BKM, BN, BK>;
@@ -105,7 +106,12 @@ __global__ __launch_bounds__(256) void gemm_dl_kernel(int M, int N, int K, const
   __shared__ __attribute__((aligned(1024))) char smem[NST * STG > EPI ? NST * STG : EPI];
   // workgroup b runs on XCD b % 8: every XCD (own L2) gets a contiguous range of tiles, walked in columns of 8 tile rows
   const int nb = tiles_m * tiles_n, xcd = blockIdx.x & 7, q8 = nb >> 3, r8 = nb & 7;
-  const int bid = xcd * q8 + min(xcd, r8) + (int)(blockIdx.x >> 3);
+  int bid = xcd * q8 + min(xcd, r8) + (int)(blockIdx.x >> 3);
+  if constexpr (std::is_same<G, TnGroup>::value) {
+    const TnProduct &p = group.p[product_of(group, bid)];
+    M = p.M; N = p.N; A = p.a; B = p.b; lda = p.lda; ldb = p.ldb; tiles_m = p.tiles_m; tiles_n = p.tiles_n;
+    ep.out = p.out; ep.ldc = N; ep.alpha = p.alpha; ep.vec_ok = p.vec_ok;
+  }
   constexpr int GROUP = 8;
   const int per_group = GROUP * tiles_n;
   const int grp = bid / per_group, first_m = grp * GROUP;
@@ -230,9 +236,9 @@ void launch(hipStream_t st, GemmLayout lay, int M, int N, int K, const uint16_t 
   const int tm = (M + BM - 1) / BM, tn = (N + BM - 1) / BM;
   const dim3 grid(tm * tn, parts), block(256);
   switch (lay) {
-    case GEMM_NT: hipLaunchKernelGGL((gemm_dl_kernel<1, 1, BM, BM, BK, WK, NST>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, kchunk); break;
-    case GEMM_NN: hipLaunchKernelGGL((gemm_dl_kernel<1, 0, BM, BM, BK, WK, NST>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, kchunk); break;
-    case GEMM_TN: hipLaunchKernelGGL((gemm_dl_kernel<0, 0, BM, BM, BK, WK, NST>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, kchunk); break;
+    case GEMM_NT: hipLaunchKernelGGL((gemm_dl_kernel<1, 1, BM, BM, BK, WK, NST>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, kchunk, NoGroup()); break;
+    case GEMM_NN: hipLaunchKernelGGL((gemm_dl_kernel<1, 0, BM, BM, BK, WK, NST>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, kchunk, NoGroup()); break;
+    case GEMM_TN: hipLaunchKernelGGL((gemm_dl_kernel<0, 0, BM, BM, BK, WK, NST>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep, tm, tn, kchunk, NoGroup()); break;
   }
 }
 
@@ -243,4 +249,12 @@ void twist_launch_gemm_dl(hipStream_t st, int tile, GemmLayout lay, int M, int N
   const Ep &e = *static_cast<const Ep *>(ep);
   if (tile == 32) launch<32, 128, 4, 4>(st, lay, M, N, K, a, lda, b, ldb, e, parts, kchunk);
   else launch<64, 64, 1, 4>(st, lay, M, N, K, a, lda, b, ldb, e, parts, kchunk);
+}
+
+void twist_launch_gemm_dl_group(hipStream_t st, int tile, const void *group, int tiles, int K, const void *ep, int parts, int kchunk) {
+  const Ep &e = *static_cast<const Ep *>(ep);
+  const TnGroup &g = *static_cast<const TnGroup *>(group);
+  const dim3 grid(tiles, parts), block(256);
+  if (tile == 32) hipLaunchKernelGGL((gemm_dl_kernel<0, 0, 32, 32, 128, 4, 4, TnGroup>), grid, block, 0, st, 0, 0, K, nullptr, 0, nullptr, 0, e, tiles, 1, kchunk, g);
+  else hipLaunchKernelGGL((gemm_dl_kernel<0, 0, 64, 64, 64, 1, 4, TnGroup>), grid, block, 0, st, 0, 0, K, nullptr, 0, nullptr, 0, e, tiles, 1, kchunk, g);
 }

@@ -43,6 +43,30 @@ struct Ep {
   int vec_ok;  // out (and residual, act_out) rows allow 4-element vector accesses: ldc % 4 == 0, 16-byte aligned bases
 };
 
+// Weight gradients (TN products over the same contraction) that share a launch; tiles are numbered through all of them.
+struct TnProduct {
+  const uint16_t *a, *b;
+  float *out;      // with a cut contraction: the product's part 0 in the scratch
+  int64_t lda, ldb;
+  int M, N, first, tiles_m, tiles_n;  // first: number of its first tile
+  float alpha;
+  int vec_ok;
+};
+struct TnGroup {
+  int n;
+  TnProduct p[kGroupProducts];
+};
+struct NoGroup {};
+// the product that tile `bid` belongs to; bid becomes the tile's number within it
+__device__ __forceinline__ int product_of(const TnGroup &g, int &bid) {
+  int q = 0;
+#pragma unroll
+  for (int i = 1; i < kGroupProducts; ++i)
+    if (i < g.n && bid >= g.p[i].first) q = i;
+  bid -= g.p[q].first;
+  return q;
+}
+
 constexpr uint32_t kOob = 0x80000000u;  // byte offset beyond every buffer: loads return 0, stores are dropped
 
 // Elements from a panel's base to the end of its last 16-byte chunk.  A load that reaches beyond the buffer's range returns nothing at

@@ -39,12 +39,26 @@ enum GemmLayout {
 twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, int K, const void *A, int64_t lda, const void *B,
                         int64_t ldb, int64_t ldc, const GemmEpilogue &ep, hipStream_t st = nullptr);
 
+// Weight gradients over the same K rows, up to kGroupProducts of them: one launch where their kernels allow it.  `scratch` (or null) as in
+// GemmEpilogue; chosen as in twist_weight_grads_raw.
+using WeightGrad = twist_weight_grad;
+constexpr int kGroupProducts = 4;
+twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGrad *items, int K, float *scratch, size_t scratch_floats, hipStream_t st = nullptr,
+                                int32_t *chosen = nullptr);
+
+// What the rule that chooses bf16 kernels expects (host only), added up: microseconds, and those that CUs without a tile stand idle.  Several
+// M, N: weight gradients in one launch.
+struct GemmEstimate { double us = 0.0, idle = 0.0; };
+void twist_gemm_estimate(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, size_t split_floats, GemmEstimate &sum);
+
 // the bf16 ping-pong kernel for GEMM_NT (ep: a gemm_tile.h Ep), tiles of 256 x bn, bn = 256 or 128; with `targets` the rows' loss parts instead of an output
 void twist_launch_gemm_nt(hipStream_t st, int bn, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep,
                           const int32_t *targets = nullptr, float *loss_parts = nullptr, float *target_logit = nullptr);
 // the bf16 kernels for tiles of 64 and 32 (ep: a gemm_tile.h Ep), the contraction cut into `parts` parts of kchunk (a multiple of 128)
 void twist_launch_gemm_dl(hipStream_t st, int tile, GemmLayout lay, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb, const void *ep,
                           int parts, int kchunk);
+// the same for the weight gradients of a group (a gemm_tile.h TnGroup), `tiles` in all
+void twist_launch_gemm_dl_group(hipStream_t st, int tile, const void *group, int tiles, int K, const void *ep, int parts, int kchunk);
 // the fp32 form of twist_gemm, and the sum of the partial products [parts][M][N] of a product whose contraction was cut
 // (out = alpha * sum in ascending order)
 twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,

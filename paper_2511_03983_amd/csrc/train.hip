@@ -140,21 +140,46 @@ void carve(const twist_ctx *ctx, const std::vector<int32_t> &heads, const std::v
   w.bytes = align_up(c.off, 256);
 }
 
-// The weight-gradient projections of the backward pass only write parameter gradients, nothing downstream in
-// the pass reads them, and on their own most of them have too few output tiles to fill the chip.  They are
-// therefore enqueued on a second stream, where they run next to the chain of input-gradient kernels.  Slot i
-// (0 = FFN down, 1 = FFN up/gate, 2 = attention output, 3 = q/k/v) has a "ready" event (the main stream has
-// produced the operands) and a "done" event (the side stream has consumed them; the main stream waits for it
-// before it overwrites those operands one layer later).
+// The weight-gradient projections of the backward pass only write parameter gradients, and nothing downstream in the pass reads them.
+// They are either enqueued on a second stream, where they run next to the chain of input-gradient kernels and fill the CUs that the
+// chain leaves idle, each by itself or the FFN's two and the attention's two together; or in one launch at the layer's end.  Slot i
+// (0 = FFN down, 1 = FFN up/gate or both, 2 = attention output, 3 = q/k/v or both) has a "ready" event (the main stream has produced
+// the operands) and a "done" event (the side stream has consumed them; the main stream waits for it before it overwrites them).
 struct SideStream {
   twist_ctx *ctx;
-  bool on = false, recorded[4] = {false, false, false, false};
-  // `flop`: of an average layer's weight gradients.  Where they are few the events and waits, about 12 us of host time per layer and
-  // gaps of a few us each on the device, cost more than the overlap gives.  Forward and backward of 6 layers, us, second stream / one stream:
-  //   bf16, 0.05 GFLOP 974 / 596    0.8 983 / 744    3.2 1012 / 897    7.2 1131 / 1101    12.9 1338 / 1316    14.5 1614 / 1643    26 1792 / 1866
-  //   fp32, 0.05 GFLOP 1020 / 861   0.8 1318 / 1294  1.6 1834 / 1884   3.2 1796 / 1799     3.6 1767 / 1819     7.2 2516 / 2796
-  twist_status init(double flop) {
-    on = ctx->overlap && flop >= (ctx->d.dtype == TWIST_BF16 ? 13e9 : 3e9);
+  bool whole = true;  // a layer's gradients in one launch; otherwise:
+  bool ffn_pair = false, attn_pair = false;
+  bool on = false, recorded[4] = {false, false, false, false};  // on the second stream (same launches, so the same results, without it)
+  // T tokens, `heads` columns of heads and F of the FFN's hidden layer in an average layer.
+  // Where the gradients are few the events and waits, about 12 us of host time per layer and gaps of a few us each on the device, cost
+  // more than the overlap gives.  Forward and backward of 6 layers, us, second stream / one stream:
+  //   bf16 (apart), 0.05 GFLOP 974 / 596    0.8 983 / 744    3.2 1012 / 897    12.9 1338 / 1316   (pairs / one launch) 14.5 1490 / 1522    21 2013 / 2079
+  //   fp32          0.05 GFLOP 1020 / 861   0.8 1318 / 1294  1.6 1834 / 1884   3.2 1796 / 1799    7.2 2496 / 2784
+  // Where the chain and one launch of all gradients leave few CUs idle, and that launch is well shorter than the others, the streams only
+  // contend; of 95 bf16 models of 13 to 3400 GFLOP a layer the rule takes the slower form at most 1.4 % to its cost, but for one (768 x 4096,
+  // 4 %).  d x tokens, us, pairs on the second stream / one launch: 768 x 8192 2149 / 2093, 1024 x 8192 4271 / 4123, 1024 x 2048 2479 / 2346;
+  // and on the other side of the line 768 x 6144 2701 / 2951, 2048 x 3000 3376 / 3530, 1600 x 8192 3891 / 4152.
+  twist_status init(int T, int D, int heads, int F, int nf) {
+    const double flop = 2.0 * T * D * (4.0 * heads + (nf + 1.0) * F);
+    whole = flop < (ctx->d.dtype == TWIST_BF16 ? 13e9 : 3e9);
+    if (!whole && ctx->d.dtype == TWIST_BF16) {
+      // a launch for two where it is expected to take a tenth less than two launches: 2048 x 768 x (512, 2048) 31 / 44 and 22 / 34 us; not the
+      // FFN's of 8192 x 2048 x 2816, whose 264 tiles would take two rounds: 406 / 301
+      const int f = nf * F, q = 3 * heads, Ms[4] = {D, f, D, q}, Ns[4] = {F, D, heads, D};
+      GemmEstimate chain, one[4], two[2], all;
+      twist_gemm_estimate(GEMM_NN, 1, &T, &F, D, false, 0, chain);
+      twist_gemm_estimate(GEMM_NN, 1, &T, &D, f, false, 0, chain);
+      twist_gemm_estimate(GEMM_NN, 1, &T, &heads, D, false, 0, chain);
+      twist_gemm_estimate(GEMM_NN, 1, &T, &D, q, false, 0, chain);
+      for (int i = 0; i < 4; ++i) twist_gemm_estimate(GEMM_TN, 1, Ms + i, Ns + i, T, true, kSplitkFloats, one[i]);
+      for (int i = 0; i < 2; ++i) twist_gemm_estimate(GEMM_TN, 2, Ms + 2 * i, Ns + 2 * i, T, true, kSplitkFloats, two[i]);
+      twist_gemm_estimate(GEMM_TN, 4, Ms, Ns, T, true, kSplitkFloats, all);
+      ffn_pair = two[0].us < 0.9 * (one[0].us + one[1].us);
+      attn_pair = two[1].us < 0.9 * (one[2].us + one[3].us);
+      const double halves = std::min(two[0].us, one[0].us + one[1].us) + std::min(two[1].us, one[2].us + one[3].us);
+      whole = chain.idle + all.idle <= 0.18 * (chain.us + all.us) && all.us <= 0.85 * halves;
+    }
+    on = !whole && ctx->overlap;
     if (!on) return TWIST_OK;
     if (!ctx->side) {
       TW_HIP(ctx, hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
@@ -423,14 +448,24 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
 
   // ------------------------------------------------------------------------------------ backward through the layers
   SideStream side{ctx};
-  double wgrad_flop = 0.0;
-  for (int l = 0; l < d.n_layers; ++l) wgrad_flop += 2.0 * T * D * (4.0 * heads[l] * dh + (nf + 1.0) * ffn[l] * d.ffn_granule) / d.n_layers;
-  TW_TRY(side.init(wgrad_flop));
-  auto wgrad = [&](int M, int Nn, const void *A, int64_t lda, const void *Bm, int64_t ldb, float *out, float alpha) {
-    GemmEpilogue e;
-    e.alpha = alpha; e.out = out; e.out_f32 = 1;
-    e.splitk_ws = w.splitk; e.splitk_floats = kSplitkFloats;  // one scratch: these projections are serialised on their stream
-    return twist_gemm(ctx, bf, GEMM_TN, M, Nn, T, A, lda, Bm, ldb, Nn, e, side.stream());
+  int64_t sum_heads = 0, sum_ffn = 0;
+  for (int l = 0; l < d.n_layers; ++l) { sum_heads += heads[l]; sum_ffn += ffn[l]; }
+  TW_TRY(side.init(T, D, (int)(sum_heads * dh / d.n_layers), (int)(sum_ffn * d.ffn_granule / d.n_layers), nf));
+  // Weight gradients wait in `grads` and run together
+  std::vector<WeightGrad> grads;
+  uint32_t grads_of = 0;
+  auto wgrad = [&](int M, int Nn, const void *A, int64_t lda, const void *Bm, int64_t ldb, float *out, float alpha, uint32_t tensors) {
+    grads.push_back({M, Nn, A, lda, Bm, ldb, out, alpha});
+    grads_of |= tensors;
+  };
+  auto run_wgrads = [&](int l, int slot) -> twist_status {
+    TW_TRY(side.fork(slot));
+    TW_TRY(twist_weight_grads(ctx, bf, (int)grads.size(), grads.data(), T, w.splitk, kSplitkFloats, side.stream()));  // (one scratch: one stream)
+    TW_TRY(expand(side.stream(), l, grads_of, w.cg, 0));
+    TW_TRY(side.done(slot));
+    grads.clear();
+    grads_of = 0;
+    return TWIST_OK;
   };
   void *gx = w.dxb, *gx_other = w.dxb2;  // gradient of the residual stream in activation type: current, spare
   for (int l = d.n_layers - 1; l >= 0; --l) {
@@ -450,42 +485,34 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
       return twist_colsum(ctx, bf, src, ld, 1.f, out, part, T, n, true);
     };
     if (float *sums = down_sums(l)) reduce_items.push_back({sums, G(L.at(l, TWIST_B_DOWN)), (int64_t)D, D, c_f});
-    TW_TRY(side.fork(0));
-    if (um) TW_TRY(wgrad(F, D, b.a, F, gx, D, GW(l, TWIST_W_DOWN), c_f));
-    else TW_TRY(wgrad(D, F, gx, D, b.a, F, GW(l, TWIST_W_DOWN), c_f));
-    TW_TRY(expand(side.stream(), l, 1u << TWIST_W_DOWN, w.cg, 0));
-    TW_TRY(side.done(0));
+    if (um) wgrad(F, D, b.a, F, gx, D, GW(l, TWIST_W_DOWN), c_f, 1u << TWIST_W_DOWN);
+    else wgrad(D, F, gx, D, b.a, F, GW(l, TWIST_W_DOWN), c_f, 1u << TWIST_W_DOWN);
+    if (!side.whole && !side.ffn_pair) TW_TRY(run_wgrads(l, 0));
     if (um) TW_TRY(gemm(GEMM_NT, T, F, D, gx, D, PW(l, TWIST_W_DOWN), D, w.da, F, 0, c_f));
     else TW_TRY(gemm(GEMM_NN, T, F, D, gx, D, PW(l, TWIST_W_DOWN), F, w.da, F, 0, c_f));
     TW_TRY(side.wait_done(1));
     TW_TRY(twist_act_bwd(ctx, bf, d.act, b.gu, w.da, w.dgu, T, F, keep_of(l, TWIST_KIND_FFN), d.ffn_granule));
     if (L.at(l, TWIST_B_UP).off >= 0) TW_TRY(bias_grad(w.dgu, nf * F, GW(l, TWIST_B_UP), nf * F));
-    TW_TRY(side.fork(1));
-    TW_TRY(wgrad(nf * F, D, w.dgu, nf * F, b.h2, D, GW(l, w1), 1.f));
-    TW_TRY(expand(side.stream(), l, 1u << TWIST_W_GATE | 1u << TWIST_W_UP, w.cg, 0));
-    TW_TRY(side.done(1));
+    wgrad(nf * F, D, w.dgu, nf * F, b.h2, D, GW(l, w1), 1.f, 1u << TWIST_W_GATE | 1u << TWIST_W_UP);
+    if (!side.whole) TW_TRY(run_wgrads(l, 1));
     TW_TRY(gemm(GEMM_NN, T, D, nf * F, w.dgu, nf * F, PW(l, w1), D, w.dh, D, 0));
-    TW_TRY(side.wait_done(2));
+    TW_TRY(side.wait_done(side.attn_pair ? 3 : 2));
     TW_TRY(norm_bwd(2 * l + 1, w.dh, w.xs[2 * l + 1], P(L.at(l, TWIST_NORM2_W)), 1, gx_other, G(L.at(l, TWIST_NORM2_W)), G(L.at(l, TWIST_NORM2_B)), out_sums(l)));
     // attention branch: y = c_a (o C_attn^T + b_o)
     if (float *sums = out_sums(l)) reduce_items.push_back({sums, G(L.at(l, TWIST_BO)), (int64_t)D, D, c_a});
-    TW_TRY(side.fork(2));
-    if (um) TW_TRY(wgrad(HD, D, b.o, HD, gx_other, D, GW(l, TWIST_WO), c_a));
-    else TW_TRY(wgrad(D, HD, gx_other, D, b.o, HD, GW(l, TWIST_WO), c_a));
-    TW_TRY(expand(side.stream(), l, 1u << TWIST_WO, w.cg, 0));
-    TW_TRY(side.done(2));
+    if (um) wgrad(HD, D, b.o, HD, gx_other, D, GW(l, TWIST_WO), c_a, 1u << TWIST_WO);
+    else wgrad(D, HD, gx_other, D, b.o, HD, GW(l, TWIST_WO), c_a, 1u << TWIST_WO);
+    if (!side.whole && !side.attn_pair) TW_TRY(run_wgrads(l, 2));
     if (um) TW_TRY(gemm(GEMM_NT, T, HD, D, gx_other, D, PW(l, TWIST_WO), D, w.dout, HD, 0, c_a));
     else TW_TRY(gemm(GEMM_NN, T, HD, D, gx_other, D, PW(l, TWIST_WO), HD, w.dout, HD, 0, c_a));
     TW_TRY(side.wait_done(3));
     TW_TRY(twist_attention_bwd(ctx, bf, b.qkv, bf ? b.o32 : static_cast<const float *>(b.o), w.dout, b.lse, w.delta, w.dqkv, B, N, Hs, dh, d.use_rope ? w.rope_tab : nullptr,
                                keep_of(l, TWIST_KIND_HEAD)));
     if (L.at(l, TWIST_BQ).off >= 0) TW_TRY(bias_grad(w.dqkv, 3 * HD, GW(l, TWIST_BQ), 3 * HD));
-    TW_TRY(side.fork(3));
-    TW_TRY(wgrad(3 * HD, D, w.dqkv, 3 * HD, b.h1, D, GW(l, TWIST_WQ), 1.f));
-    TW_TRY(expand(side.stream(), l, 1u << TWIST_WQ | 1u << TWIST_WK | 1u << TWIST_WV, w.cg, 0));
-    TW_TRY(side.done(3));
+    wgrad(3 * HD, D, w.dqkv, 3 * HD, b.h1, D, GW(l, TWIST_WQ), 1.f, 1u << TWIST_WQ | 1u << TWIST_WK | 1u << TWIST_WV);
+    TW_TRY(run_wgrads(l, 3));
     TW_TRY(gemm(GEMM_NN, T, D, 3 * HD, w.dqkv, 3 * HD, PW(l, TWIST_WQ), D, w.dh, D, 0));
-    TW_TRY(side.wait_done(0));
+    TW_TRY(side.wait_done(side.ffn_pair ? 1 : 0));
     TW_TRY(norm_bwd(2 * l, w.dh, w.xs[2 * l], P(L.at(l, TWIST_NORM1_W)), 1, gx, G(L.at(l, TWIST_NORM1_W)), G(L.at(l, TWIST_NORM1_B)), down_sums(l - 1)));
   }
   TW_TRY(twist_col_reduce_batch(ctx, reduce_items.data(), (int)reduce_items.size(), T));

@@ -211,6 +211,38 @@ def test_cut_bf16_projection(lib, tile, layout, M, N, K):
         assert torch.isnan(buf[M * N:]).all() and torch.isnan(scratch[parts * M * N:]).all()
 
 
+# Weight gradients that share a launch, on every tile, whole and cut: edges of tiles in both directions, products of odd sizes (whose partial
+# products leave the next product's unaligned), an empty one, a last part shorter than the others
+@pytest.mark.parametrize("tile,cut,K,shapes", [
+    (32, False, 100, [(33, 41), (70, 36), (131, 40), (8, 33)]), (32, True, 9000, [(33, 41), (70, 36), (131, 41), (8, 40)]),
+    (64, False, 1100, [(520, 776), (776, 515), (264, 520), (515, 776)]), (64, True, 8100, [(260, 390), (264, 201), (100, 100)]),
+    (128, False, 2000, [(2100, 1024), (0, 8), (1024, 2100), (3000, 1001)]), (128, True, 8200, [(768, 768), (768, 769), (576, 768), (768, 192)]),
+    (256, False, 1500, [(2816, 2048), (5000, 2048), (3072, 2048), (2048, 1001)]), (256, True, 8200, [(768, 3072), (3000, 769), (2304, 768), (768, 775)])])
+def test_weight_gradients_in_one_launch(lib, tile, cut, K, shapes):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    up = lambda n: (n + 7) // 8 * 8
+    rows = lambda n: torch.randn((K, up(n)), generator=gen, device="cuda").bfloat16()[:, :n]
+    alphas = (0.5, 1.0, 2.0, 1.0)
+    scratch = torch.full((1 << 24,), float("nan"), device="cuda")
+    bufs = [torch.full((M * N + 64,), float("nan"), device="cuda") for M, N in shapes]
+    products = [(rows(M), rows(N), buf[:M * N].view(M, N)) for (M, N), buf in zip(shapes, bufs)]
+    _, cols, parts = ctx.twist_weight_grads_raw(K, products, scratch, alphas)
+    torch.cuda.synchronize()
+    assert cols == tile and (parts > 1) == cut, (cols, parts)
+    for (a, b, out), buf, alpha in zip(products, bufs, alphas):
+        want = alpha * (a.double().T @ b.double())
+        # fp32 sums of K exact products: 2^-24 sqrt(K) at most; one left out or counted twice shows as 1 / sqrt(K)
+        assert out.numel() == 0 or float(((out.double() - want).norm(dim=1) / want.norm(dim=1)).max()) <= 2.0 ** -24 * K ** 0.5
+        assert torch.isnan(buf[out.numel():]).all()
+    assert torch.isnan(scratch[parts * sum(M * N for M, N in shapes) if cut else 0:]).all()
+    a, b, out = products[0]
+    one_by_one = [(a[:, 1:], b, torch.empty((a.shape[1] - 1, b.shape[1]), device="cuda")), products[1]]     # rows that are not 16-byte aligned
+    assert ctx.twist_weight_grads_raw(K, one_by_one, scratch, alphas) == (0, 0, 0)
+    torch.cuda.synchronize()
+    assert float((one_by_one[0][2].double() - 0.5 * a[:, 1:].double().T @ b.double()).norm() / out.double().norm()) <= 2.0 ** -24 * K ** 0.5
+
+
 @pytest.mark.parametrize("tile,layout,M,N,K", [(32, 2, 132, 200, 1100), (32, 1, 131, 72, 2001), (64, 2, 1500, 1500, 2000), (64, 0, 1500, 1500, 1999), (128, 1, 1024, 768, 8003),
                                                (128, 2, 1023, 769, 8003)])
 def test_cut_fp32_projection(lib, tile, layout, M, N, K):
