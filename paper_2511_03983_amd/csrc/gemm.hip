@@ -3,7 +3,7 @@
 //    gemm_nt.hip where both operands are contiguous along k), and 64x64 and 32x32 tiles for products too small to fill the
 //    chip with those (gemm_dl.hip); operands stay in LDS in their memory orientation, and those whose contraction index is the slow
 //    axis in memory are read back with the transposing LDS load.
-//  - fp32 operands: the fp32 matrix instruction (gemm_f32.hip).
+//  - fp32 operands: gemm_f32.hip.
 //  - anything else (unaligned bf16 shapes, fp32 contractions of a few elements): a plain tiled FMA kernel with arbitrary strides.
 #include <algorithm>
 #include <type_traits>

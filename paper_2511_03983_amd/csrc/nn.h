@@ -133,9 +133,10 @@ twist_status twist_rope_apply(twist_ctx *ctx, int bf16, void *qkv, const float *
 // act: a = f(u) (gu = [T,F]) or a = silu(g) * u (gu = [T,2F], gate first).
 // keep (may be null; device, one entry per FFN block of `unit` neurons): blocks with keep[b] < 0 are masked (Masked TwIST,
 // Section 4.1): their activations are written as zero and, in the backward kernel, da is taken as zero there.
+// sums (may be null): also the column sums of dgu per chunk of rows, twist_colsum_partial_floats(T, columns of dgu) of them.
 twist_status twist_act_fwd(twist_ctx *ctx, int bf16, int act, const void *gu, void *a, int T, int F, const int32_t *keep = nullptr, int unit = 1);
 twist_status twist_act_bwd(twist_ctx *ctx, int bf16, int act, const void *gu, const void *da, void *dgu, int T, int F, const int32_t *keep = nullptr,
-                           int unit = 1);
+                           int unit = 1, float *sums = nullptr);
 
 // logits [T,V] -> in place dlogits = (softmax - onehot)/T (grad) or left alone; row losses to rowloss[T]; then loss = mean
 twist_status twist_ce_fwd_bwd(twist_ctx *ctx, int bf16, void *logits, int64_t ld, const int32_t *targets, float *rowloss, float *loss, int T, int V, bool grad = true);

@@ -822,6 +822,50 @@ __global__ __launch_bounds__(kT) void act_bwd_vec_kernel(int act, const u32x4v *
   du[i] = pack8(o);
 }
 
+// The same, and the column sums of du over chunks of kChunkRows rows (the up projection's bias gradient), which a kernel of its own would read
+// du again for.  A workgroup owns 64 (chunk, 8 columns) pairs, a wave a quarter of their rows: 8192 x 768
+// 8.7 + 4.9 us -> 10.6, bound by the arithmetic of the gradient as much as by its 38 MB.
+__global__ __launch_bounds__(kT) void act_bwd_sum_kernel(int act, const u32x4v *u, const u32x4v *da, u32x4v *du, float *partial, int T, int n8, int64_t pairs,
+                                                          const int32_t *keep, int unit) {
+  constexpr int R = kChunkRows / 4;
+  __shared__ f32x4v sh[3][2][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const bool mine = i < pairs;
+  const int chunk = mine ? (int)(i / n8) : 0, v = mine ? (int)(i - (int64_t)chunk * n8) : 0, r0 = chunk * kChunkRows + R * wave;
+  u32x4v x[R], y[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t at = (int64_t)min(r0 + r, T - 1) * n8 + v;
+    x[r] = u[at];
+    y[r] = da[at];
+  }
+  f32x4v lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const F8 a = unpack8(x[r]);
+    F8 d = unpack8(y[r]), o;
+    if (keep) mask8(d, keep, unit, 8 * v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o.v[e] = d.v[e] * (act == TWIST_ACT_RELU ? (a.v[e] > 0.f ? 1.f : 0.f) : gelu_tanh_grad<false>(a.v[e]));
+    const u32x4v p = pack8(o);
+    if (mine && r0 + r < T) {
+      du[(int64_t)(r0 + r) * n8 + v] = p;
+      const F8 s = unpack8(p);  // as stored
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { lo[e] += s.v[e]; hi[e] += s.v[4 + e]; }
+    }
+  }
+  if (wave) { sh[wave - 1][0][lane] = lo; sh[wave - 1][1][lane] = hi; }
+  __syncthreads();
+  if (wave || !mine) return;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) { lo += sh[k][0][lane]; hi += sh[k][1][lane]; }
+  f32x4v *o = reinterpret_cast<f32x4v *>(partial) + 2 * i;
+  o[0] = lo;
+  o[1] = hi;
+}
+
 __global__ __launch_bounds__(kT) void swiglu_bwd_vec_kernel(const u32x4v *gu, const u32x4v *da, u32x4v *dgu, int F8n, int64_t total, const int32_t *keep,
                                                              int unit) {
   const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
@@ -1151,22 +1195,30 @@ twist_status twist_act_fwd(twist_ctx *ctx, int bf16, int act, const void *gu, vo
   return TWIST_OK;
 }
 
-twist_status twist_act_bwd(twist_ctx *ctx, int bf16, int act, const void *gu, const void *da, void *dgu, int T, int F, const int32_t *keep, int unit) {
+twist_status twist_act_bwd(twist_ctx *ctx, int bf16, int act, const void *gu, const void *da, void *dgu, int T, int F, const int32_t *keep, int unit,
+                           float *sums) {
   const int64_t total = (int64_t)T * F;
-  if (bf16 && act == TWIST_ACT_SWIGLU && F % 8 == 0 && al16(gu) && al16(da) && al16(dgu)) {
+  const bool vec = bf16 && al16(gu) && al16(da) && al16(dgu);
+  if (vec && sums && act != TWIST_ACT_SWIGLU && F % 8 == 0 && total > 0 && al16(sums)) {
+    const int64_t pairs = (int64_t)n_chunks(T) * (F / 8);
+    hipLaunchKernelGGL(act_bwd_sum_kernel, dim3((unsigned)((pairs + 63) / 64)), dim3(kT), 0, ctx->stream, act, static_cast<const u32x4v *>(gu),
+                       static_cast<const u32x4v *>(da), static_cast<u32x4v *>(dgu), sums, T, F / 8, pairs, keep, unit);
+    TW_HIP(ctx, hipGetLastError());
+    return TWIST_OK;
+  }
+  if (vec && act == TWIST_ACT_SWIGLU && F % 8 == 0) {
     hipLaunchKernelGGL(swiglu_bwd_vec_kernel, grid1(total / 8), dim3(kT), 0, ctx->stream, static_cast<const u32x4v *>(gu), static_cast<const u32x4v *>(da),
                        static_cast<u32x4v *>(dgu), F / 8, total / 8, keep, unit);
     TW_HIP(ctx, hipGetLastError());
-    return TWIST_OK;
-  }
-  if (bf16 && act != TWIST_ACT_SWIGLU && (keep ? F % 8 == 0 : total % 8 == 0) && al16(gu) && al16(da) && al16(dgu)) {
+  } else if (vec && act != TWIST_ACT_SWIGLU && (keep ? F % 8 == 0 : total % 8 == 0)) {
     hipLaunchKernelGGL(act_bwd_vec_kernel, grid1(total / 8), dim3(kT), 0, ctx->stream, act, static_cast<const u32x4v *>(gu), static_cast<const u32x4v *>(da),
                        static_cast<u32x4v *>(dgu), total / 8, keep, unit, F / 8);
     TW_HIP(ctx, hipGetLastError());
-    return TWIST_OK;
+  } else {
+    LAUNCH_BF(act_bwd_kernel, bf16, grid1(total), dim3(kT), act, gu, da, dgu, F, total, keep, unit);
   }
-  LAUNCH_BF(act_bwd_kernel, bf16, grid1(total), dim3(kT), act, gu, da, dgu, F, total, keep, unit);
-  return TWIST_OK;
+  const int n = act == TWIST_ACT_SWIGLU ? 2 * F : F;
+  return sums ? twist_colsum(ctx, bf16, dgu, n, 1.f, nullptr, sums, T, n, true) : TWIST_OK;
 }
 
 twist_status twist_ce_fwd_bwd(twist_ctx *ctx, int bf16, void *logits, int64_t ld, const int32_t *targets, float *rowloss, float *loss, int T, int V, bool grad) {

@@ -478,11 +478,11 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     // FFN branch: y = c_f (a W_down^T + b_down)
     // bias gradients of the partitioned biases: per-chunk column sums now, reduced with everything else at the end
     float *bias_part = w.bias_partial + (size_t)l * w.bias_partial_stride + 2 * sum_d;
-    auto bias_grad = [&](const void *src, int64_t ld, float *out, int n) {
+    auto bias_sums = [&](float *out, int n) {
       float *part = bias_part;
       bias_part += twist_colsum_partial_floats(T, n);
       reduce_items.push_back({part, out, (int64_t)n, n, 1.f});
-      return twist_colsum(ctx, bf, src, ld, 1.f, out, part, T, n, true);
+      return part;
     };
     if (float *sums = down_sums(l)) reduce_items.push_back({sums, G(L.at(l, TWIST_B_DOWN)), (int64_t)D, D, c_f});
     if (um) wgrad(F, D, b.a, F, gx, D, GW(l, TWIST_W_DOWN), c_f, 1u << TWIST_W_DOWN);
@@ -491,8 +491,8 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     if (um) TW_TRY(gemm(GEMM_NT, T, F, D, gx, D, PW(l, TWIST_W_DOWN), D, w.da, F, 0, c_f));
     else TW_TRY(gemm(GEMM_NN, T, F, D, gx, D, PW(l, TWIST_W_DOWN), F, w.da, F, 0, c_f));
     TW_TRY(side.wait_done(1));
-    TW_TRY(twist_act_bwd(ctx, bf, d.act, b.gu, w.da, w.dgu, T, F, keep_of(l, TWIST_KIND_FFN), d.ffn_granule));
-    if (L.at(l, TWIST_B_UP).off >= 0) TW_TRY(bias_grad(w.dgu, nf * F, GW(l, TWIST_B_UP), nf * F));
+    TW_TRY(twist_act_bwd(ctx, bf, d.act, b.gu, w.da, w.dgu, T, F, keep_of(l, TWIST_KIND_FFN), d.ffn_granule,
+                         L.at(l, TWIST_B_UP).off >= 0 ? bias_sums(GW(l, TWIST_B_UP), nf * F) : nullptr));
     wgrad(nf * F, D, w.dgu, nf * F, b.h2, D, GW(l, w1), 1.f, 1u << TWIST_W_GATE | 1u << TWIST_W_UP);
     if (!side.whole) TW_TRY(run_wgrads(l, 1));
     TW_TRY(gemm(GEMM_NN, T, D, nf * F, w.dgu, nf * F, PW(l, w1), D, w.dh, D, 0));
@@ -508,7 +508,7 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     TW_TRY(side.wait_done(3));
     TW_TRY(twist_attention_bwd(ctx, bf, b.qkv, bf ? b.o32 : static_cast<const float *>(b.o), w.dout, b.lse, w.delta, w.dqkv, B, N, Hs, dh, d.use_rope ? w.rope_tab : nullptr,
                                keep_of(l, TWIST_KIND_HEAD)));
-    if (L.at(l, TWIST_BQ).off >= 0) TW_TRY(bias_grad(w.dqkv, 3 * HD, GW(l, TWIST_BQ), 3 * HD));
+    if (L.at(l, TWIST_BQ).off >= 0) TW_TRY(twist_colsum(ctx, bf, w.dqkv, 3 * HD, 1.f, nullptr, bias_sums(GW(l, TWIST_BQ), 3 * HD), T, 3 * HD, true));
     wgrad(3 * HD, D, w.dqkv, 3 * HD, b.h1, D, GW(l, TWIST_WQ), 1.f, 1u << TWIST_WQ | 1u << TWIST_WK | 1u << TWIST_WV);
     TW_TRY(run_wgrads(l, 3));
     TW_TRY(gemm(GEMM_NN, T, D, 3 * HD, w.dqkv, 3 * HD, PW(l, TWIST_WQ), D, w.dh, D, 0));
