@@ -421,6 +421,38 @@ __global__ __launch_bounds__(kT) void reduce_partial_batch_kernel(const ColReduc
   }
 }
 
+// ... where n and the stride are multiples of 4 and the partial sums 16-byte aligned: 4 columns a thread, 64 a workgroup, the same order of
+// additions and eight loads in flight.  What bounded it: half lines of 64 bytes, one load of a thread at a time; 64 sums
+// of 768 columns over 512 chunks 38 -> 23 us.
+__global__ __launch_bounds__(kT) void reduce_partial_batch_vec_kernel(const ColReduceArgs a, int n_chunks) {
+  __shared__ f32x4v sh[16][16];
+  const ColReduce it = a.item[blockIdx.y];
+  const int lane = threadIdx.x & 15, slice = threadIdx.x >> 4, c = 64 * blockIdx.x + 4 * lane;
+  if (64 * (int)blockIdx.x >= it.n) return;  // uniform over the workgroup
+  f32x4v s = {0.f, 0.f, 0.f, 0.f};
+  if (c < it.n) {
+    const float *p = it.partial + c;
+    int k = slice;
+    for (; k + 7 * 16 < n_chunks; k += 8 * 16) {
+      f32x4v v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4v *>(p + (int64_t)(k + 16 * j) * it.stride);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s += v[j];
+    }
+    for (; k < n_chunks; k += 16) s += *reinterpret_cast<const f32x4v *>(p + (int64_t)k * it.stride);
+  }
+  sh[slice][lane] = s;
+  __syncthreads();
+  if (slice == 0 && c < it.n) {
+    f32x4v t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t += sh[i][lane];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) it.out[c + e] = it.alpha * t[e];
+  }
+}
+
 template <int BF>
 __global__ __launch_bounds__(64) void colsum_kernel(const void *src, int64_t ld, float *partial, int T, int n) {
   const int c = blockIdx.x * 64 + threadIdx.x;
@@ -1136,8 +1168,14 @@ twist_status twist_col_reduce_batch(twist_ctx *ctx, const ColReduce *items, int 
     ColReduceArgs a;
     const int m = std::min(kReduceBatch, n_items - i0);
     int widest = 1;
-    for (int i = 0; i < m; ++i) { a.item[i] = items[i0 + i]; widest = std::max(widest, items[i0 + i].n); }
-    hipLaunchKernelGGL(reduce_partial_batch_kernel, dim3((widest + 15) / 16, m), dim3(kT), 0, ctx->stream, a, nc);
+    bool vec = true;
+    for (int i = 0; i < m; ++i) {
+      const ColReduce &it = a.item[i] = items[i0 + i];
+      widest = std::max(widest, it.n);
+      vec = vec && it.n % 4 == 0 && it.stride % 4 == 0 && al16(it.partial);
+    }
+    if (vec) hipLaunchKernelGGL(reduce_partial_batch_vec_kernel, dim3((widest + 63) / 64, m), dim3(kT), 0, ctx->stream, a, nc);
+    else hipLaunchKernelGGL(reduce_partial_batch_kernel, dim3((widest + 15) / 16, m), dim3(kT), 0, ctx->stream, a, nc);
     TW_HIP(ctx, hipGetLastError());
   }
   return TWIST_OK;
