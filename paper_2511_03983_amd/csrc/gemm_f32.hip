@@ -2,10 +2,14 @@
 //
 // Tiles of 128 and 64: gemm_f32_kernel, on the bf16 instruction (v_mfma_f32_32x32x16_bf16, sixteen times the rate of the fp32 one).  An fp32
 // value is the sum of three bf16 values (8 bits each, rounded to nearest, the last one exactly what is left), a product of two bf16 values is exact in
-// fp32, and of the nine products of two such sums the six largest are formed: what is left out is below 2^-26 of the product, against 2^-24 for
-// one rounding of fp32.  The sums run in fp32 as before, in fewer steps (one per 16 products), the small products in a sum of their own.  Error
-// against 64 bits on normal operands, the fp32 instruction in brackets: K = 384 0.8e-7 (1.8e-7), 768 1.1e-7 (2.5e-7 to 5.0e-7), 4096 2.7e-7 (11.5e-7),
-// 50257 in 16 parts 2.5e-7 (10e-7); one sum for all six products: K = 768 3.0e-7.
+// fp32, and of the nine products of two such sums the six largest are formed.  What is left out of a product is 2^-28 of it on average over
+// operands of random bits and at most about 2^-24 (0.99 of that for the square of 1 + 2^-8 - 2^-17), one rounding of fp32.  The sums run in fp32 as
+// before, in fewer steps (one per 16 products), the small products in a sum of their own.  Error against 64 bits on normal operands, the fp32
+// instruction in brackets: K = 17 0.4e-7 (0.8e-7), 33 0.4e-7 (1.0e-7), 100 0.5e-7 (1.8e-7), 384 0.8e-7 (1.8e-7), 768 1.1e-7 (2.5e-7 to 5.0e-7),
+// 4096 2.7e-7 (11.5e-7), 50257 in 16 parts 2.5e-7 (10e-7); one sum for all six products: K = 768 3.0e-7.
+// The third term of a value below 2^-110 would need bits below the smallest bf16 (2^-133; the instruction takes subnormal operands), so the terms
+// are those of 2^16 times the value, which holds down to the smallest fp32 (2^-149), and 2^32 is taken out of the sums: operands of 1e-36 0.7e-7
+// (without the factor 270e-7).
 // Tiles of 32, for few rows: gemm_f32_small_kernel, on the fp32 instruction (v_mfma_f32_32x32x2_f32): there every value would be split into
 // its terms for 32 products only.
 //
@@ -40,8 +44,10 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {  // round to n
   const f32x2 v = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
-// four floats as three vectors of bf16 that add up to them exactly (an infinity, a NaN or what rounds to infinity gives a NaN)
+constexpr float kUp = 65536.f, kDown = 1.f / (kUp * kUp);  // factor of the terms, and what takes it out of a sum of their products
+// four floats as three vectors of bf16 that add up to kUp times them exactly (an infinity, a NaN or what overflows gives a NaN)
 __device__ __forceinline__ void split(f32x4 v, u32x2 (&t)[3]) {
+  v *= kUp;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     t[k] = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
@@ -318,9 +324,11 @@ __global__ __launch_bounds__(64 * W2 * W2 * WK) void gemm_f32_kernel(int M, int 
       for (int r = 0; r < 16; ++r) {
         acc[i][j][r] += low[i][j][r];
         finite = finite && __builtin_isfinite(acc[i][j][r]);
+        acc[i][j][r] *= kDown;
       }
   if (__syncthreads_or(!finite)) {
-    // an infinity or a NaN among the operands (or a value that rounds to infinity): its terms do not behave like it, so this tile is formed plainly
+    // an infinity or a NaN among the operands (or a value beyond 2^111 or a sum beyond 2^95, where the factor overflows): its terms do not behave
+    // like it, so this tile is formed plainly
 #pragma unroll 1
     for (int i = threadIdx.x; i < BM * BN; i += NT) {
       const int m = m0 + i / BN, n = n0 + i % BN;

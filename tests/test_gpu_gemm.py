@@ -146,6 +146,27 @@ def test_fp32_projection_with_values_beyond_the_terms(lib, tile, layout):
         assert bool((err <= bound).all()), special
 
 
+# ... and operands down to the smallest float, whose lower terms would be below the smallest bf16, against as large ones on the other side (the largest
+# overflow as terms).  Bound: K products summed in fp32 in any order, 2^-24 sqrt(K) of the result's norm
+@pytest.mark.parametrize("tile", [128, 256])
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("up,down", [(90, -100), (90, -112), (90, -120), (90, -126), (95, -135), (118, -135), (-20, -100)])
+def test_fp32_projection_of_tiny_operands(lib, tile, layout, up, down):
+    M, N, K = 260, 140, 200
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    gen = torch.Generator(device="cuda").manual_seed(layout)
+    A, B = torch.randn((M, K), generator=gen, device="cuda"), torch.randn((N, K), generator=gen, device="cuda")
+    for ea, eb in ((up, down), (down, up)):
+        a, b = (A.double() * 2.0 ** ea).float(), (B.double() * 2.0 ** eb).float()
+        want = a.double() @ b.double().T
+        a_, b_ = (a.T.contiguous() if layout == 2 else a), (b if layout == 0 else b.T.contiguous())
+        out = torch.empty((M, N), device="cuda")
+        ctx.twist_set_kernel_choice(gemm_tile=tile)
+        ctx.twist_gemm_raw(layout, M, N, K, a_, b_, out)
+        torch.cuda.synchronize()
+        assert float((out.double() - want).norm() / want.norm()) <= 2.0 ** -24 * K ** 0.5
+
+
 @pytest.mark.parametrize("M,N,K,tile", [(3000, 2900, 72, 64), (4000, 3900, 72, 128)])
 def test_fp32_projection_by_size_takes_the_larger_tiles(lib, M, N, K, tile):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
