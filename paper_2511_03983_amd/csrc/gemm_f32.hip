@@ -59,6 +59,14 @@ __device__ __forceinline__ void split(f32x4 v, u32x2 (&t)[3]) {
   }
 }
 
+// for the fp32 instruction: four consecutive k of one row, from a slice in LDS stored by rows (KM) or by k
+template <int KM, int LD>
+__device__ __forceinline__ f32x4 four_k(const float *lds, int row, int k) {
+  if (KM) return *reinterpret_cast<const f32x4 *>(lds + row * LD + k);
+  const float *p = lds + k * LD + row;
+  return f32x4{p[0], p[LD], p[2 * LD], p[3 * LD]};
+}
+
 constexpr int kAhead = 3;  // slices in flight between memory and registers
 
 // One operand's slice: fp32 from memory to registers, its three terms to LDS, fragments of 32 rows x 16 k back
@@ -119,6 +127,15 @@ struct Loader {
       split(reg[set][i], t);
 #pragma unroll
       for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2 *>(lds + k * PLANE + (c / CPR) * LD + (c % CPR) * 4) = t[k];
+    }
+  }
+  // register set 0 as it is, for the fp32 instruction
+  static constexpr int LD32 = KM ? BK + 4 : ROWS + 8, ELEMS32 = KM ? ROWS * LD32 : BK * LD32;
+  __device__ __forceinline__ void store_f32(float *lds) const {
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) {
+      const int c = threadIdx.x + NT * i;
+      *reinterpret_cast<f32x4 *>(lds + (c / CPR) * LD32 + (c % CPR) * 4) = reg[0][i];
     }
   }
   // the wave's fragments of the 32 rows from row0 on and the 16 k from k0 on, all three terms
@@ -197,10 +214,7 @@ struct SmallLoader {
   }
   // the lane's values for MFMAs 4 u .. 4 u + 3 of the 32 rows starting at row0
   static __device__ __forceinline__ f32x4 frag(const float *lds, int row0, int u) {
-    const int c = threadIdx.x & 31, k = 8 * u + 4 * ((threadIdx.x >> 5) & 1);
-    if (KM) return *reinterpret_cast<const f32x4 *>(lds + (row0 + c) * LD + k);
-    const float *p = lds + k * LD + row0 + c;
-    return f32x4{p[0], p[LD], p[2 * LD], p[3 * LD]};
+    return four_k<KM, LD>(lds, row0 + (threadIdx.x & 31), 8 * u + 4 * ((threadIdx.x >> 5) & 1));
   }
 };
 
@@ -328,16 +342,47 @@ __global__ __launch_bounds__(64 * W2 * W2 * WK) void gemm_f32_kernel(int M, int 
       }
   if (__syncthreads_or(!finite)) {
     // an infinity or a NaN among the operands (or a value beyond 2^111 or a sum beyond 2^95, where the factor overflows): its terms do not behave
-    // like it, so this tile is formed plainly
+    // like it, so this tile is formed again on the fp32 instruction (1024 x 50257 x 768, us: 667, with one NaN in one row of 1024,
+    // i.e. in an eighth of the tiles, 934, with nothing but NaNs 1301; 1024 x 1536 x 768 30, 56, 56)
+    float *sa = reinterpret_cast<float *>(lds), *sb = sa + LA::ELEMS32;
+    static_assert((LA::ELEMS32 + LB::ELEMS32) * sizeof(float) <= sizeof(lds), "one slice in fp32 fits the stages");
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    la.init(AKM ? pa + kbeg : pa + (int64_t)kbeg * lda, lda, M - m0);
+    lb.init(BKM ? pb + kbeg : pb + (int64_t)kbeg * ldb, ldb, N - n0);
+    la.load(0, kend - kbeg);
+    lb.load(0, kend - kbeg);
 #pragma unroll 1
-    for (int i = threadIdx.x; i < BM * BN; i += NT) {
-      const int m = m0 + i / BN, n = n0 + i % BN;
-      if (m >= M || n >= N) continue;
-      float x = 0.f;
-      for (int k = kbeg; k < kend; ++k) x = fmaf(AKM ? A[m * lda + k] : A[k * lda + m], BKM ? B[n * ldb + k] : B[k * ldb + n], x);
-      put(m, n, x, ep.bias ? ep.bias[n] : 0.f);
+    for (int k0 = kbeg; k0 < kend; k0 += BK) {
+      la.store_f32(sa);
+      lb.store_f32(sb);
+      __syncthreads();
+      if (k0 + BK < kend) {
+        la.load(0, kend - k0 - BK);
+        lb.load(0, kend - k0 - BK);
+      }
+#pragma unroll
+      for (int u = 0; u < BK / WK / 8; ++u) {
+        const int k = kw + 8 * u + 4 * (lane >> 5);
+        f32x4 af[TM], bf[TM];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          af[i] = four_k<AKM, LA::LD32>(sa, wm + 32 * i + (lane & 31), k);
+          bf[i] = four_k<BKM, LB::LD32>(sb, wn + 32 * i + (lane & 31), k);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][e], bf[j][e], acc[i][j], 0, 0, 0);
+      }
+      __syncthreads();
     }
-    return;
   }
   // the WK shares are added in order; each of their waves finishes 16 / WK of a 32x32 tile's registers
   float *part = reinterpret_cast<float *>(lds);

@@ -167,6 +167,32 @@ def test_fp32_projection_of_tiny_operands(lib, tile, layout, up, down):
         assert float((out.double() - want).norm() / want.norm()) <= 2.0 ** -24 * K ** 0.5
 
 
+# a tile that an infinity or a NaN reaches is formed a second time, on the fp32 instruction (measured: twice as long in all).  A loop over k
+# per output in its place took 34 to 115 times as long
+@pytest.mark.parametrize("layout,M,N,K", [(0, 1024, 20000, 768), (0, 1024, 1536, 768), (1, 1024, 768, 1536), (2, 2048, 2048, 768)])
+def test_fp32_projection_of_nans_keeps_its_speed(lib, layout, M, N, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    assert ctx.twist_gemm_kernel(layout, M, N, K)[0] >= 64
+    A, B = torch.randn((K, M) if layout == 2 else (M, K), device="cuda"), torch.randn((N, K) if layout == 0 else (K, N), device="cuda")
+    out = torch.empty((M, N), device="cuda")
+
+    def fastest(passes):
+        times = []
+        for _ in range(passes):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                ctx.twist_gemm_raw(layout, M, N, K, A, B, out)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    plain = fastest(6)
+    A.fill_(float("nan"))
+    assert fastest(3) <= 8 * plain and bool(torch.isnan(out).all())
+
+
 @pytest.mark.parametrize("M,N,K,tile", [(3000, 2900, 72, 64), (4000, 3900, 72, 128)])
 def test_fp32_projection_by_size_takes_the_larger_tiles(lib, M, N, K, tile):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
