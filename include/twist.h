@@ -277,6 +277,12 @@ TWIST_API twist_status twist_gemm_raw_cut(twist_ctx *ctx, int32_t layout, int32_
                                           const void *B, int64_t ldb, void *C, int64_t ldc, int32_t out_f32, float alpha, float *scratch,
                                           size_t scratch_floats);
 
+/* The up projection of an ungated FFN alone, as the training pass runs it: C = A B^T (+ bias [N]), rounded to desc.dtype, and act_out = f(C),
+ * f = act (TWIST_ACT_GELU_TANH or TWIST_ACT_RELU) of the rounded values.  A [M,K], B [N,K], C and act_out [M,N] (ldc = N), desc.dtype; bias may
+ * be NULL; with act_only C is scratch whose contents are undefined afterwards (evaluation).  Any other layout, ldc or activation: TWIST_EINVAL. */
+TWIST_API twist_status twist_gemm_act_raw(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, const void *A, int64_t lda, const void *B,
+                                          int64_t ldb, void *C, int64_t ldc, const void *bias, int32_t act, void *act_out, int32_t act_only);
+
 /* Weight gradients alone, as the training pass forms a layer's: out[i][M][N] = alpha a^T b over the same K rows, n <= 4 products in one
  * launch where their kernels allow it (bf16, 16-byte aligned rows), otherwise one by one.  Rows of a and b may be padded, those of out
  * (fp32) are not.  scratch (device, or NULL) may receive fp32 partial products.  chosen (host, or NULL) receives tile rows, tile

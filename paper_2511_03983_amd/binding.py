@@ -103,6 +103,7 @@ _SIGS = {
     "twist_round": ([_vp, C.POINTER(RoundDesc), C.POINTER(FullWeightsC), _vp, _vp, _vp, _sz, _vp, _sz, _vp, _sz, _vp], _i32),
     "twist_gemm_raw": ([_vp, _i32, _i32, _i32, _i32, _vp, C.c_int64, _vp, C.c_int64, _vp, C.c_int64, _i32, C.c_float], _i32),
     "twist_gemm_raw_cut": ([_vp, _i32, _i32, _i32, _i32, _vp, C.c_int64, _vp, C.c_int64, _vp, C.c_int64, _i32, C.c_float, _vp, _sz], _i32),
+    "twist_gemm_act_raw": ([_vp, _i32, _i32, _i32, _i32, _vp, C.c_int64, _vp, C.c_int64, _vp, C.c_int64, _vp, _i32, _vp, _i32], _i32),
     "twist_weight_grads_raw": ([_vp, _i32, C.POINTER(WeightGrad), _i32, _vp, _sz, _PI32], _i32),
     "twist_gemm_kernel": ([_vp, _i32, _i32, _i32, _i32, _i32, _sz, _PI32], _i32),
     "twist_attention_raw": ([_vp, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp], _i32),
@@ -282,6 +283,13 @@ class Context:
         """twist_gemm_raw whose contraction may be cut into parts, with fp32 partial products in `scratch`."""
         _check(lib.twist_gemm_raw_cut(self.h, layout, M, N, K, _vp(A.data_ptr()), A.stride(0), _vp(B.data_ptr()), B.stride(0), _vp(out.data_ptr()),
                                       out.stride(0), int(out.dtype == torch.float32), alpha, _vp(scratch.data_ptr()), scratch.numel()), self.h)
+
+    def twist_gemm_act_raw(self, A: torch.Tensor, B: torch.Tensor, bias: torch.Tensor | None, act: int, act_only: bool = False):
+        """(C, f(C)) with C = A B^T (+ bias) rounded to the model's type; act_only: C is not defined."""
+        C_, a = (torch.empty((A.shape[0], B.shape[0]), dtype=self.torch_dtype, device=A.device) for _ in range(2))
+        _check(lib.twist_gemm_act_raw(self.h, 0, A.shape[0], B.shape[0], A.shape[1], _ptr(A), A.stride(0), _ptr(B), B.stride(0), _ptr(C_), C_.stride(0), _ptr(bias),
+                                      act, _ptr(a), int(act_only)), self.h)
+        return C_, a
 
     def twist_weight_grads_raw(self, K: int, products, scratch: torch.Tensor | None, alphas):
         """products: up to 4 triples (a [K, M], b [K, N], out [M, N] fp32); returns (tile rows, tile columns, parts) of their common

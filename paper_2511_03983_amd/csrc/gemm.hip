@@ -515,6 +515,8 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
                         int64_t ldc, const GemmEpilogue &e, hipStream_t st) {
   if (M <= 0 || N <= 0 || K <= 0) return TWIST_OK;
   const hipStream_t stream = st ? st : ctx->stream;
+  if (e.act_out && (lay != GEMM_NT || ldc != N || stream != ctx->stream || (bf16 && e.out_f32) || (e.act != TWIST_ACT_GELU_TANH && e.act != TWIST_ACT_RELU)))
+    TW_FAIL(ctx, TWIST_EINVAL, "projection: an ungated activation is applied to y = x W^T with unpadded rows in the model's type, on the context's stream only");
   GemmTimer timer{ctx, stream};
   TW_TRY(timer.start(2.0 * M * N * K));
   Ep ep{e.alpha, e.bias, e.residual, e.out, e.out_f32, ldc, nullptr, 0, 0};
@@ -663,6 +665,21 @@ extern "C" twist_status twist_gemm_raw_cut(twist_ctx *ctx, int32_t layout, int32
   e.out_f32 = out_f32;
   e.splitk_ws = scratch;
   e.splitk_floats = scratch_floats;
+  return twist_gemm(ctx, ctx->d.dtype == TWIST_BF16, (GemmLayout)layout, M, N, K, A, lda, B, ldb, ldc, e);
+}
+
+extern "C" twist_status twist_gemm_act_raw(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
+                                           void *C, int64_t ldc, const void *bias, int32_t act, void *act_out, int32_t act_only) {
+  if (!ctx || !A || !B || !C || !act_out) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_act_raw: null argument");
+  if (layout < 0 || layout > 2 || M < 0 || N < 0 || K < 0) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_act_raw: bad layout or size");
+  const int64_t need_a = layout == GEMM_TN ? M : K, need_b = layout == GEMM_NT ? K : N;
+  if (lda < need_a || ldb < need_b || ldc < N) TW_FAIL(ctx, TWIST_ESHAPE, "twist_gemm_act_raw: a row stride is smaller than the row it strides");
+  GemmEpilogue e;
+  e.bias = bias;
+  e.out = C;
+  e.act_out = act_out;
+  e.act = act;
+  e.act_only = act_only != 0;
   return twist_gemm(ctx, ctx->d.dtype == TWIST_BF16, (GemmLayout)layout, M, N, K, A, lda, B, ldb, ldc, e);
 }
 

@@ -14,8 +14,8 @@ struct GemmEpilogue {
   // summed in a fixed order.
   float *splitk_ws = nullptr;
   size_t splitk_floats = 0;
-  // Ungated activation of the output, as twist_act_fwd forms it from the stored one ([M,N] with ldc = N): act_out = f(out).  With act_only the output itself
-  // need not be written (out is then scratch).
+  // Ungated activation of the output, as twist_act_fwd forms it from the stored one: act_out = f(out).  GEMM_NT with ldc = N on the context's stream and an
+  // output of the model's type; anything else is refused.  With act_only the output itself need not be written (out is then scratch).
   void *act_out = nullptr;
   int act = 0;
   bool act_only = false;

@@ -47,3 +47,16 @@ def test_host_only_error_paths():
     bad = tw.desc_from_cfg(si.CFG1)
     bad.ffn_granule = 7
     assert tw.lib.twist_create(ctypes.byref(bad), None, ctypes.byref(h)) == 3
+
+
+def test_a_projection_applies_an_activation_in_its_own_form_only():
+    """y = x W^T with unpadded rows and an ungated activation; nothing else (refused before any device work: the pointers are no memory)."""
+    import paper_2511_03983_amd as tw
+    import synth_inputs as si
+    for cfg in (si.CFG1, si.CFG3):
+        d, h = tw.desc_from_cfg(cfg), ctypes.c_void_p()
+        assert tw.lib.twist_create(ctypes.byref(d), None, ctypes.byref(h)) == 0
+        for layout, ldc, act in ((1, 64, 0), (2, 64, 0), (0, 72, 1), (0, 64, 2), (0, 64, 7)):
+            assert tw.lib.twist_gemm_act_raw(h, layout, 64, 64, 64, 4096, 64, 4096, 64, 4096, ldc, None, act, 4096, 1) == 1, (layout, ldc, act)
+            assert b"activation" in tw.lib.twist_last_error(h)
+        tw.lib.twist_destroy(h)

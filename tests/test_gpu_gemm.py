@@ -258,6 +258,28 @@ def test_cut_bf16_projection(lib, tile, layout, M, N, K):
         assert torch.isnan(buf[M * N:]).all() and torch.isnan(scratch[parts * M * N:]).all()
 
 
+# the up projection with its activation: the projection's bits and the activation kernel's of them, on every tile and on the plain kernel, with and without the
+# projection itself
+@pytest.mark.parametrize("act", ["gelu_tanh", "relu"])
+@pytest.mark.parametrize("bf16,M,N,K,tile", [(True, 33, 136, 72, 32), (True, 999, 1000, 200, 64), (True, 2100, 1544, 264, 128), (True, 4000, 3080, 264, 256), (True, 80, 130, 66, 0),
+                                             (False, 80, 136, 72, 0), (False, 1000, 1543, 200, 0)])
+def test_projection_with_its_activation(lib, act, bf16, M, N, K, tile):
+    cfg = si.ModelCfg(d_model=64, n_heads=1, d_head=8, d_ff=N, act=act, dtype="bf16" if bf16 else "f32")
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    assert not tile or ctx.twist_gemm_kernel(0, M, N, K)[1] == tile
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    A, B = (torch.randn(s, generator=gen, device="cuda").to(dt) * 0.2 for s in ((M, K), (N, K)))
+    want = torch.empty((M, N), dtype=dt, device="cuda")
+    ctx.twist_gemm_raw(0, M, N, K, A, B, want)
+    want_a, _ = ctx.twist_act_raw(want, N)
+    kind = ctx.desc.act
+    got, a = ctx.twist_gemm_act_raw(A, B, None, kind)
+    _, only = ctx.twist_gemm_act_raw(A, B, None, kind, act_only=True)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and torch.equal(a, want_a) and torch.equal(only, want_a)
+
+
 # Weight gradients that share a launch, on every tile, whole and cut: edges of tiles in both directions, products of odd sizes (whose partial
 # products leave the next product's unaligned), an empty one, a last part shorter than the others
 @pytest.mark.parametrize("tile,cut,K,shapes", [
