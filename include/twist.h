@@ -382,6 +382,11 @@ TWIST_API twist_status twist_profile_mfma_ceiling(twist_ctx *ctx, int32_t waves_
  * Default: enabled. */
 TWIST_API twist_status twist_set_overlap(twist_ctx *ctx, int32_t enable);
 
+/* How twist_subnet_fwd_bwd runs the weight gradients of a model whose average layer has head_columns columns of heads and ffn_columns of the FFN's
+ * hidden layer, for a batch of `tokens` (host only, for tests and benchmarks).  chosen: [0] 1 = a layer's in one launch, on the context's
+ * stream; otherwise [1] 1 = the FFN's two share a launch, [2] 1 = the attention's two do; [3] 1 = on the second stream. */
+TWIST_API twist_status twist_backward_schedule(twist_ctx *ctx, int32_t tokens, int32_t head_columns, int32_t ffn_columns, int32_t chosen[4]);
+
 /* Kernel selection for tests (not part of the method): by default every launcher picks its kernel from the shape.
  *   gemm_tile        0 = by shape; 256 or 128 pins the matrix-core projection kernel with tiles of 256x256 or 256x128
  *                    (fp32 models: 64x64 or 128x128) and keeps the contraction in one piece (TWIST_EINVAL for other values);

@@ -116,6 +116,7 @@ _SIGS = {
     "twist_set_kernel_choice": ([_vp, _i32, _i32, _i32], _i32),
     "twist_profile_gemm": ([_vp, _i32], _i32),
     "twist_set_overlap": ([_vp, _i32], _i32),
+    "twist_backward_schedule": ([_vp, _i32, _i32, _i32, _PI32], _i32),
     "twist_profile_mfma_ceiling": ([_vp, _i32, _i32, _i32, _vp, _sz, C.POINTER(C.c_double)], _i32),
     "twist_profile_gemm_read": ([_vp, C.POINTER(C.c_int64), C.POINTER(C.c_double), C.POINTER(C.c_double)], _i32),
 }
@@ -306,6 +307,12 @@ class Context:
         chosen = (_i32 * 3)()
         _check(lib.twist_gemm_kernel(self.h, layout, M, N, K, int(out_f32), scratch_floats, chosen), self.h)
         return tuple(chosen)
+
+    def twist_backward_schedule(self, tokens: int, head_columns: int, ffn_columns: int):
+        """(one launch per layer on the context's stream, FFN gradients paired, attention gradients paired, second stream in use); host only."""
+        chosen = (_i32 * 4)()
+        _check(lib.twist_backward_schedule(self.h, tokens, head_columns, ffn_columns, chosen), self.h)
+        return tuple(bool(c) for c in chosen)
 
     def twist_attention_raw(self, qkv: torch.Tensor, dout, B: int, N: int, Hs: int, keep: torch.Tensor | None = None, rope_backward: bool = False):
         """Causal attention alone: returns (o, lse, dqkv or None) for qkv [B*N, 3*Hs*d_head] and dout [B*N, Hs*d_head] or None;

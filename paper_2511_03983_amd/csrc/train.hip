@@ -145,11 +145,9 @@ void carve(const twist_ctx *ctx, const std::vector<int32_t> &heads, const std::v
 // chain leaves idle, each by itself or the FFN's two and the attention's two together; or in one launch at the layer's end.  Slot i
 // (0 = FFN down, 1 = FFN up/gate or both, 2 = attention output, 3 = q/k/v or both) has a "ready" event (the main stream has produced
 // the operands) and a "done" event (the side stream has consumed them; the main stream waits for it before it overwrites them).
-struct SideStream {
-  twist_ctx *ctx;
-  bool whole = true;  // a layer's gradients in one launch; otherwise:
+struct Schedule {
+  bool whole = true;  // a layer's gradients in one launch on the caller's stream; otherwise on the second stream, and:
   bool ffn_pair = false, attn_pair = false;
-  bool on = false, recorded[4] = {false, false, false, false};  // on the second stream (same launches, so the same results, without it)
   // T tokens, `heads` columns of heads and F of the FFN's hidden layer in an average layer.
   // Where the gradients are few the events and waits, about 12 us of host time per layer and gaps of a few us each on the device, cost
   // more than the overlap gives.  Forward and backward of 6 layers, us, second stream / one stream:
@@ -159,10 +157,10 @@ struct SideStream {
   // contend; of 95 bf16 models of 13 to 3400 GFLOP a layer the rule takes the slower form at most 1.4 % to its cost, but for one (768 x 4096,
   // 4 %).  d x tokens, us, pairs on the second stream / one launch: 768 x 8192 2149 / 2093, 1024 x 8192 4271 / 4123, 1024 x 2048 2479 / 2346;
   // and on the other side of the line 768 x 6144 2701 / 2951, 2048 x 3000 3376 / 3530, 1600 x 8192 3891 / 4152.
-  twist_status init(int T, int D, int heads, int F, int nf) {
+  void choose(bool bf16, int T, int D, int heads, int F, int nf) {
     const double flop = 2.0 * T * D * (4.0 * heads + (nf + 1.0) * F);
-    whole = flop < (ctx->d.dtype == TWIST_BF16 ? 13e9 : 3e9);
-    if (!whole && ctx->d.dtype == TWIST_BF16) {
+    whole = flop < (bf16 ? 13e9 : 3e9);
+    if (!whole && bf16) {
       // a launch for two where it is expected to take a tenth less than two launches: 2048 x 768 x (512, 2048) 31 / 44 and 22 / 34 us; not the
       // FFN's of 8192 x 2048 x 2816, whose 264 tiles would take two rounds: 406 / 301
       const int f = nf * F, q = 3 * heads, Ms[4] = {D, f, D, q}, Ns[4] = {F, D, heads, D};
@@ -179,6 +177,15 @@ struct SideStream {
       const double halves = std::min(two[0].us, one[0].us + one[1].us) + std::min(two[1].us, one[2].us + one[3].us);
       whole = chain.idle + all.idle <= 0.18 * (chain.us + all.us) && all.us <= 0.85 * halves;
     }
+  }
+};
+
+struct SideStream : Schedule {
+  twist_ctx *ctx;
+  bool on = false, recorded[4] = {false, false, false, false};  // on the second stream (same launches, so the same results, without it)
+  explicit SideStream(twist_ctx *c) : ctx(c) {}
+  twist_status init(int T, int D, int heads, int F, int nf) {
+    choose(ctx->d.dtype == TWIST_BF16, T, D, heads, F, nf);
     on = !whole && ctx->overlap;
     if (!on) return TWIST_OK;
     if (!ctx->side) {
@@ -447,7 +454,7 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
   }
 
   // ------------------------------------------------------------------------------------ backward through the layers
-  SideStream side{ctx};
+  SideStream side(ctx);
   int64_t sum_heads = 0, sum_ffn = 0;
   for (int l = 0; l < d.n_layers; ++l) { sum_heads += heads[l]; sum_ffn += ffn[l]; }
   TW_TRY(side.init(T, D, (int)(sum_heads * dh / d.n_layers), (int)(sum_ffn * d.ffn_granule / d.n_layers), nf));
@@ -530,6 +537,15 @@ twist_status twist_train_fwd_bwd(twist_ctx *ctx, twist_subnet *sub, const void *
     const Slot &pe = L.global[TWIST_POS_EMBED];
     if (pe.off >= 0 && N < pe.rows) TW_TRY(twist_zero_f32(ctx, G(pe) + (size_t)N * D, (int64_t)(pe.rows - N) * D));
   }
+  return TWIST_OK;
+}
+
+extern "C" twist_status twist_backward_schedule(twist_ctx *ctx, int32_t tokens, int32_t head_columns, int32_t ffn_columns, int32_t chosen[4]) {
+  if (!ctx || !chosen) TW_FAIL(ctx, TWIST_EINVAL, "twist_backward_schedule: null argument");
+  if (tokens < 1 || head_columns < 1 || ffn_columns < 1) TW_FAIL(ctx, TWIST_EINVAL, "twist_backward_schedule: bad size");
+  Schedule s;
+  s.choose(ctx->d.dtype == TWIST_BF16, tokens, ctx->d.d_model, head_columns, ffn_columns, ctx->d.act == TWIST_ACT_SWIGLU ? 2 : 1);
+  chosen[0] = s.whole; chosen[1] = s.ffn_pair; chosen[2] = s.attn_pair; chosen[3] = !s.whole && ctx->overlap;
   return TWIST_OK;
 }
 

@@ -1,6 +1,7 @@
 """The rule that chooses a projection's kernel (twist_gemm_kernel, host only): never far from the fastest of the kernels as they were
 measured on a MI355X."""
 import ctypes
+from dataclasses import replace
 
 import pytest
 
@@ -114,3 +115,19 @@ def test_fp32_rule_leaves_short_contractions_of_large_outputs_to_the_plain_kerne
     assert _chosen(lib, si.CFG1, 0, 8192, 2048, 8, 1, 0)[0] == 0 and _chosen(lib, si.CFG1, 0, 512, 50257, 16, 1, 0)[0] == 0
     assert _chosen(lib, si.CFG1, 2, 3072, 768, 8, 1, 0)[0] == 0 and _chosen(lib, si.CFG1, 2, 4096, 4096, 16, 1, 0)[0] == 128
     assert _chosen(lib, si.CFG1, 0, 8192, 2048, 17, 1, 0)[0] == 128 and _chosen(lib, si.CFG1, 2, 768, 768, 8, 1, 0)[0] == 32
+
+
+# cfg, tokens, columns of heads and of the FFN's hidden layer in an average layer -> (one launch on the caller's stream, FFN paired, attention paired)
+@pytest.mark.parametrize("cfg,tokens,heads,ffn,want", [
+    (si.CFG3, 8192, 1024, 2816, (0, 0, 1)), (si.CFG3, 3000, 896, 2488, (0, 1, 1)), (si.CFG2, 2048, 384, 1536, (0, 1, 0)), (si.CFG2, 2048, 768, 704, (0, 0, 0)),
+    (si.CFG2, 8192, 192, 768, (1, 1, 1)), (replace(si.CFG3, d_model=1024), 2048, 512, 1408, (1, 1, 1)), (replace(si.CFG3, d_model=1024), 256, 512, 1408, (1, 0, 0)),
+    (replace(si.CFG2, dtype="f32"), 1024, 384, 1536, (0, 0, 0)), (si.CFG1, 256, 64, 256, (1, 0, 0))])
+def test_schedule_of_the_weight_gradients(lib, cfg, tokens, heads, ffn, want):
+    h, out = ctypes.c_void_p(), (ctypes.c_int32 * 4)()
+    d = lib.desc_from_cfg(cfg)
+    assert lib.lib.twist_create(ctypes.byref(d), None, ctypes.byref(h)) == 0
+    assert lib.lib.twist_backward_schedule(h, tokens, heads, ffn, out) == 0
+    assert tuple(out)[:3] == want and out[3] == (not want[0])
+    assert lib.lib.twist_set_overlap(h, 0) == 0 and lib.lib.twist_backward_schedule(h, tokens, heads, ffn, out) == 0 and out[3] == 0
+    assert lib.lib.twist_backward_schedule(h, 0, heads, ffn, out) == 1
+    lib.lib.twist_destroy(h)

@@ -105,6 +105,7 @@ def test_second_stream_weight_gradients_are_bit_identical_to_serial_schedule(lib
     globs = {k: draw(s) for k, s in si.global_shapes(cfg).items()}
     fw = lib.FullWeights(layers, globs)
     ctx = lib.Context(lib.desc_from_cfg(cfg))
+    assert ctx.twist_backward_schedule(B * N, hs * cfg.d_head, fs)[3]
     plan = ctx.twist_sample(S, hs, fs, seed=3)
     sub = ctx.twist_extract(plan, fw, 1, store=lib.STORE_GRADS)
     ws = torch.empty(ctx.twist_workspace_bytes(sub, B, N), dtype=torch.uint8, device="cuda")

@@ -91,6 +91,36 @@ def test_weight_gradients_of_many_tokens_are_cut(lib, name):
     products = ((3 * HD, D), (D, HD), ((2 if cfg.act == "swiglu" else 1) * F, D), (D, F))
     parts = [ctx.twist_gemm_kernel(2, M, Nn, B * N, True, 1 << 24)[2] for M, Nn in products]
     assert sum(p > 1 for p in parts) >= 3, parts
+    if cfg.dtype == "bf16":                                  # a layer's run in one launch: cut as well
+        assert ctx.twist_backward_schedule(B * N, HD, F)[0]
+        zeros = lambda n: torch.zeros((B * N, n), dtype=torch.bfloat16, device="cuda")
+        grads = [(zeros(M), zeros(Nn), torch.empty((M, Nn), device="cuda")) for M, Nn in products]
+        assert ctx.twist_weight_grads_raw(B * N, grads, torch.empty(1 << 24, device="cuda"), (1.0,) * 4)[2] > 1
+
+
+# models whose weight gradients go to the second stream, by how they share launches there; (cfg, S, heads_sub, ffn_sub, B, N), two disjoint halves each.
+# (So many token ids that hardly one occurs three times in a batch: two atomic additions to a cleared row give the same bits in either order.)
+TWO_STREAMS = {
+    "attention_paired": (replace(si.CFG3, n_layers=2, d_model=1024, n_heads=4, d_ff=1408, vocab=8009, max_seq=1024), 2, 2, 704, 2, 1024),
+    "ffn_and_attention_paired": (replace(si.CFG3, n_layers=2, d_model=2048, n_heads=14, d_ff=4976, vocab=8009, max_seq=1000), 2, 7, 2488, 1, 1000),
+    "ffn_paired": (replace(si.CFG2, n_layers=2, n_heads=12, d_ff=3072, vocab=8009, max_seq=1024), 2, 6, 1536, 2, 1024),
+    "apart": (replace(si.CFG2, n_layers=2, n_heads=24, d_ff=1408, vocab=8009, max_seq=1024, out_unit_major=True), 2, 12, 704, 2, 1024),
+    "apart_f32": (replace(si.CFG2, n_layers=2, n_heads=12, d_ff=3072, vocab=8009, max_seq=512, dtype="f32"), 2, 6, 1536, 2, 512),
+}
+
+
+def _schedule(ctx, cfg, hs, fs, B, N):
+    return ctx.twist_backward_schedule(B * N, hs * cfg.d_head, fs * cfg.ffn_granule)
+
+
+@pytest.mark.parametrize("name,ffn,attn", [("attention_paired", False, True), ("ffn_and_attention_paired", True, True), ("ffn_paired", True, False), ("apart", False, False),
+                                           ("apart_f32", False, False)])
+def test_two_stream_models_are_what_their_names_say(lib, name, ffn, attn):
+    cfg, _, hs, fs, B, N = TWO_STREAMS[name]
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    assert _schedule(ctx, cfg, hs, fs, B, N) == (False, ffn, attn, True)
+    ctx.twist_set_overlap(False)
+    assert _schedule(ctx, cfg, hs, fs, B, N) == (False, ffn, attn, False)
 
 
 # the same models with the output projections stored unit-major (their three projections change form)
@@ -540,11 +570,12 @@ def test_round_and_running_aggregate_reject_bad_arguments(lib):
     acc.close()
 
 
-def test_forward_backward_can_be_captured_in_a_graph_and_replayed(lib):
-    """twist_subnet_fwd_bwd + an SGD step recorded once into a HIP graph (both of the library's streams, no allocation,
+@pytest.mark.parametrize("case", ["llama_bf16", "attention_paired", "ffn_and_attention_paired"])
+def test_forward_backward_can_be_captured_in_a_graph_and_replayed(lib, case):
+    """twist_subnet_fwd_bwd + an SGD step recorded once into a HIP graph (one stream, and both of the library's; no allocation,
     no synchronisation inside) and replayed three times with eager work in between: every replay gives the loss and the
     weights of the same steps run eagerly."""
-    cfg, S, hs, fs, B, N = CASES["llama_bf16"]
+    cfg, S, hs, fs, B, N = CASES.get(case) or TWO_STREAMS[case]
     full_np = si.make_weights(cfg, 3, std=0.02, generic=True)
     x_np, y_np, x, y = _data(cfg, B, N, 5)
     stream = torch.cuda.Stream()
@@ -553,6 +584,7 @@ def test_forward_backward_can_be_captured_in_a_graph_and_replayed(lib):
         full_t = to_device(full_np, cfg)
         with torch.cuda.stream(stream):
             ctx = lib.Context(lib.desc_from_cfg(cfg))            # its work goes to `stream`
+            assert _schedule(ctx, cfg, hs, fs, B, N)[3] == (case in TWO_STREAMS)
             plan = ctx.twist_sample(S, hs, fs, seed=4)
             fw = lib.FullWeights(full_t["layers"], full_t["globals"])
             sub = ctx.twist_extract(plan, fw, 0, store=lib.STORE_GRADS)
@@ -593,10 +625,11 @@ def test_forward_backward_can_be_captured_in_a_graph_and_replayed(lib):
             assert np.array_equal(w, results["graph"][1]["globals"][k]), k
 
 
-def test_work_is_enqueued_on_the_contexts_stream(lib):
+@pytest.mark.parametrize("case", ["llama_bf16", "attention_paired", "ffn_and_attention_paired", "apart_f32"])
+def test_work_is_enqueued_on_the_contexts_stream(lib, case):
     """A context created on a non-default stream gives the same bits as one on the default stream (every kernel,
     the second stream's included, is ordered on the stream the caller handed over)."""
-    cfg, S, hs, fs, B, N = CASES["llama_bf16"]
+    cfg, S, hs, fs, B, N = CASES.get(case) or TWO_STREAMS[case]
     full_np = si.make_weights(cfg, 2, std=0.02, generic=True)
     full_t = to_device(full_np, cfg)
     x_np, y_np, x, y = _data(cfg, B, N, 5)
@@ -604,6 +637,7 @@ def test_work_is_enqueued_on_the_contexts_stream(lib):
     results = []
     for stream in (None, torch.cuda.Stream(), torch.cuda.Stream()):
         ctx = lib.Context(lib.desc_from_cfg(cfg), stream=stream)
+        assert _schedule(ctx, cfg, hs, fs, B, N)[3] == (case in TWO_STREAMS)
         plan = ctx.twist_sample(S, hs, fs, seed=3)
         fw = lib.FullWeights(full_t["layers"], full_t["globals"])
         sub = ctx.twist_extract(plan, fw, 0, store=lib.STORE_GRADS)
@@ -613,7 +647,7 @@ def test_work_is_enqueued_on_the_contexts_stream(lib):
         for _ in range(2):
             ctx.twist_subnet_fwd_bwd(sub, x, y, ws, loss)
         torch.cuda.synchronize()
-        results.append((loss.item(), {k: sub.twist_subnet_view(1, k, GRAD).clone() for k in ("wq", "wo", "w_gate", "w_down", "norm1_w")}))
+        results.append((loss.item(), {k: sub.twist_subnet_view(1, k, GRAD).clone() for k in ("wq", "wo", "w_up", "w_down", "norm1_w") + (("w_gate",) if cfg.act == "swiglu" else ())}))
     for other in results[1:]:
         assert other[0] == results[0][0]
         for k, g in results[0][1].items():
@@ -785,20 +819,27 @@ def test_evaluation_loss_is_the_training_pass_loss(lib, V, B, N, tile):
     assert not bool(torch.isfinite(loss[1]))
 
 
-# layers whose weight gradients go to the second stream (26 GFLOP a layer) and layers whose stay on the caller's: one stream, both and a captured pass
-# replayed between eager work all give the same bits
-@pytest.mark.parametrize("d,B,N", [(1024, 2, 1024), (1024, 1, 256)])
-def test_schedules_agree_eagerly_and_in_a_graph(lib, d, B, N):
-    cfg = replace(si.CFG3, n_layers=2, d_model=d, n_heads=8, d_head=128, d_ff=2816, vocab=0, out_unit_major=True, max_seq=N)
+# weight gradients on the second stream in every form, and on the caller's stream (26 GFLOP a layer, which fill the chip, and 3): one stream, both and a
+# captured pass replayed between eager work all give the same bits
+ONE_STREAM = {f"block_{d}_{B}_{N}": (replace(si.CFG3, n_layers=2, d_model=d, n_heads=8, d_head=128, d_ff=2816, out_unit_major=True, max_seq=N), 2, 4, 1408, B, N)
+              for d, B, N in ((1024, 2, 1024), (1024, 1, 256))}
+
+
+@pytest.mark.parametrize("case", [*ONE_STREAM, *TWO_STREAMS])
+def test_schedules_agree_eagerly_and_in_a_graph(lib, case):
+    cfg, S, hs, fs, B, N = ONE_STREAM.get(case) or TWO_STREAMS[case]
+    cfg, d = replace(cfg, vocab=0), cfg.d_model
     gen = torch.Generator(device="cuda").manual_seed(2)
-    draw = lambda s: (torch.randn(s, generator=gen, device="cuda") * 0.02 + (1.0 if len(s) == 1 else 0.0)).bfloat16()
+    dt = torch.bfloat16 if cfg.dtype == "bf16" else torch.float32
+    draw = lambda s: (torch.randn(s, generator=gen, device="cuda") * 0.02 + (1.0 if len(s) == 1 else 0.0)).to(dt)
     fw = lib.FullWeights([{k: draw(s) for k, s in si.stored_shapes(cfg).items()} for _ in range(2)], {})
-    x, y = (torch.randn((B, N, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    x, y = (torch.randn((B, N, d), generator=gen, device="cuda").to(dt) for _ in range(2))
     stream = torch.cuda.Stream()
     stream.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(stream):
         ctx = lib.Context(lib.desc_from_cfg(cfg))
-        sub = ctx.twist_extract(ctx.twist_sample(2, 4, 1408, seed=1), fw, 0, store=lib.STORE_GRADS)
+        assert _schedule(ctx, cfg, hs, fs, B, N)[3] == (case in TWO_STREAMS)
+        sub = ctx.twist_extract(ctx.twist_sample(S, hs, fs, seed=1), fw, 0, store=lib.STORE_GRADS)
         ws = torch.empty(ctx.twist_workspace_bytes(sub, B, N), dtype=torch.uint8, device="cuda")
         loss = torch.zeros(1, device="cuda")
         run = lambda: ctx.twist_subnet_fwd_bwd(sub, x, y, ws, loss)
@@ -819,14 +860,16 @@ def test_schedules_agree_eagerly_and_in_a_graph(lib, d, B, N):
 
 
 # batches large enough that the masked pass runs on the kept blocks only: both storage orientations, biases, FFN blocks of one and of
-# eight neurons, a layer kept whole, one kind of block kept whole
+# eight neurons, a layer kept whole, one kind of block kept whole; the last two with weight gradients on the second stream (the others on the caller's)
 @pytest.mark.parametrize("name,cfg,hs,fs,shared,B,N", [
     ("gpt_f32", si.ModelCfg(n_layers=3, d_model=72, n_heads=4, d_head=16, d_ff=160, ffn_granule=8, vocab=301, max_seq=100), 2, 7, [1, 0, 0], 3, 100),
     ("llama_f32_um", si.ModelCfg(arch="llama", n_layers=2, d_model=64, n_heads=4, d_head=16, d_ff=176, vocab=259, max_seq=128, act="swiglu", norm="rms",
                                  has_bias=False, tied_head=False, rope=True, out_unit_major=True), 2, 88, None, 3, 128),
     ("gpt_bf16", replace(si.CFG2, n_layers=2, d_model=256, n_heads=4, d_ff=512, vocab=1003, max_seq=256), 1, 256, None, 8, 200),
     ("llama_bf16_um", replace(si.CFG3, n_layers=2, d_model=256, n_heads=4, d_ff=704, vocab=517, max_seq=256, out_unit_major=True), 2, 352, None, 8, 256),
-    ("llama_bf16_heads_whole", replace(si.CFG3, n_layers=2, d_model=256, n_heads=4, d_ff=704, vocab=517, max_seq=256), 4, 176, None, 8, 256)])
+    ("llama_bf16_heads_whole", replace(si.CFG3, n_layers=2, d_model=256, n_heads=4, d_ff=704, vocab=517, max_seq=256), 4, 176, None, 8, 256),
+    ("two_streams", replace(si.CFG3, n_layers=2, d_model=1024, n_heads=4, d_ff=1408, vocab=517, max_seq=1024), 2, 704, None, 2, 1024),
+    ("two_streams_in_pairs", replace(si.CFG3, n_layers=2, d_model=256, n_heads=16, d_ff=1408, vocab=517, max_seq=2048), 8, 704, None, 2, 2048)])
 def test_masked_pass_on_the_kept_blocks_is_the_extracted_subnets_pass(lib, name, cfg, hs, fs, shared, B, N):
     S = 4
     gen = torch.Generator(device="cuda").manual_seed(7)
@@ -840,6 +883,7 @@ def test_masked_pass_on_the_kept_blocks_is_the_extracted_subnets_pass(lib, name,
     full_sub = ctx.twist_extract(whole, fw, 0, store=lib.STORE_GRADS)
     full_sub.storage.view(torch.uint8)[-(full_sub.storage.numel() // 8):].fill_(0x7f)      # gradients must be overwritten, zeros included
     assert ctx.twist_masked_form(plan, B, N)
+    assert _schedule(ctx, cfg, hs, fs, B, N)[1:] == {"two_streams": (False, True, True), "two_streams_in_pairs": (True, True, True)}.get(name, (False, False, False))
     sub = ctx.twist_extract(plan, fw, 1, store=lib.STORE_GRADS)
     tok = torch.tensor(si.tokens_uniform(cfg.vocab, B, N, 9)).cuda()
     x, y = tok[:, :-1].contiguous(), tok[:, 1:].contiguous()
