@@ -360,11 +360,12 @@ def test_fp32_attention_of_any_length(lib, dh, N):
 
 # An infinity or a NaN in one token's value, key, query or output gradient: what does not depend on it keeps its bits (earlier queries'
 # outputs and gradients; for a query or an output gradient, later keys' too), and what the plain kernels, which visit visible pairs only,
-# compute as finite is finite.  Tokens inside a 32-row tile, at its edges and last of a ragged one.
-@pytest.mark.parametrize("dtype,dh", [(F32, 36), (F32, 64), (F32, 128), (BF, 32), (BF, 128)])
+# compute as finite is finite.  Tokens inside a 32-row tile, at its edges and last of a ragged one.  (bf16 at 128 and 256 tokens: the 64-row workgroups with
+# probabilities rounded to bf16.)
+@pytest.mark.parametrize("dtype,dh,N", [(F32, 36, 70), (F32, 64, 70), (F32, 128, 70), (BF, 32, 70), (BF, 128, 70), (BF, 64, 128), (BF, 128, 128), (BF, 64, 256)])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
-def test_attention_keeps_a_non_finite_token_from_what_does_not_see_it(lib, dtype, dh, value):
-    Hs, B, N = 2, 2, 70
+def test_attention_keeps_a_non_finite_token_from_what_does_not_see_it(lib, dtype, dh, N, value):
+    Hs, B = 2, 2
     ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=Hs, d_head=dh, d_ff=8, dtype=dtype, max_seq=N)))
     qkv = _dev(_snap(si.normal(dh, "qkv", (B * N, 3 * Hs * dh)), dtype), dtype)
     dout = _dev(_snap(si.normal(N, "dout", (B * N, Hs * dh)), dtype), dtype)
@@ -375,7 +376,7 @@ def test_attention_keeps_a_non_finite_token_from_what_does_not_see_it(lib, dtype
 
     clean = run(qkv, dout)
     for what in range(4):          # query, key, value, output gradient
-        for j in (5, 32, 47, 63, 69):
+        for j in (5, 32, 47, 63, 69, N - 1):
             x, g = qkv.clone(), dout.clone()
             if what < 3:
                 x.view(B, N, 3, Hs, dh)[0, j, what, 1, 3] = value
