@@ -61,14 +61,14 @@ def flops_fwd_bwd(cfg, hs, F, B, N):
 # HBM-side bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on this benchmark's own command and
 # calibrated against streaming kernels of known size in the same run (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0; the counter
 # sits behind the L2, so reads served by the Infinity Cache are included).  Source: profiles/bench_hbm_traffic_fetch_write.txt
-TRAFFIC_PROJECTION_LAUNCH = 311.0e6         # average over every projection launch of a forward+backward pass
+TRAFFIC_PROJECTION_LAUNCH = 310.8e6         # average over every projection launch of a forward+backward pass
 TRAFFIC_EXTRACT_LAYER_LAUNCH = 405.2e6      # one layer of one subnet at the 7B shape, unit-major layout
 TRAFFIC_AGGREGATE_LAYER_LAUNCH = 2029.6e6   # one layer, 8 subnets
 
 
 def bytes_fwd_bwd_projections(cfg, hs, F, B, N):
-    """Algorithmic bytes of the projection launches of one forward+backward: each operand read once, the output
-    written once (fp32 residual read and written where the epilogue adds it), and their number."""
+    """Algorithmic bytes of the projections of one forward+backward: each operand read once, the output
+    written once (fp32 residual read and written where the epilogue adds it)."""
     T, d, hd, V = B * N, cfg.d_model, hs * cfg.d_head, cfg.vocab
     nf = 2 if cfg.act == "swiglu" else 1
     def g(m, n, k, out_b, resid=False):
@@ -77,7 +77,7 @@ def bytes_fwd_bwd_projections(cfg, hs, F, B, N):
                  + g(T, d, 3 * hd, 2) + g(T, hd, d, 2) + g(T, d, nf * F, 2) + g(T, F, d, 2)                    # input gradients
                  + g(3 * hd, d, T, 4) + g(hd, d, T, 4) + g(nf * F, d, T, 4) + g(F, d, T, 4))                  # weight gradients
     head = g(T, V, d, 2) + g(T, d, V, 2) + g(V, d, T, 4)
-    return cfg.n_layers * per_layer + head, cfg.n_layers * 12 + 3
+    return cfg.n_layers * per_layer + head
 
 
 def bench_train(args, tw, si, torch):
@@ -179,8 +179,7 @@ def bench_train(args, tw, si, torch):
                  "flops_per_launch": gemm_flops / max(n_gemm, 1)},
         "loss": loss.item(),
     }
-    pb, pn = bytes_fwd_bwd_projections(cfg, hs, fs, B, N)
-    res["gemm"]["algorithmic_bytes_per_launch"] = pb / pn
+    res["gemm"]["algorithmic_bytes_per_launch"] = S * bytes_fwd_bwd_projections(cfg, hs, fs, B, N) / max(n_gemm, 1)   # (a launch may hold two weight gradients)
     if args.native_round:
         # the same round through twist_round: the loop runs inside the library, ONE subnet is resident at a time and the
         # aggregation is the running fp32 sum (Section 3's round with the repartition interval of Section 5)
