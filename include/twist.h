@@ -300,9 +300,12 @@ TWIST_API twist_status twist_weight_grads_raw(twist_ctx *ctx, int32_t n, const t
                                               int32_t chosen[3]);
 /* Which matrix-core kernel a projection of this shape runs on where its operands are aligned (host only, for tests and benchmarks):
  * chosen receives the rows and columns of the output tile (0: the plain kernel) and the number of parts of the contraction,
- * given a scratch of scratch_floats (0: none). */
+ * given a scratch of scratch_floats (0: none).  twist_gemm_tile: among all kernels; twist_gemm_kernel: without the bf16 ones whose two
+ * groups of waves share the contraction, which twist_gemm_tile names where they take the product over. */
 TWIST_API twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32,
                                          size_t scratch_floats, int32_t chosen[3]);
+TWIST_API twist_status twist_gemm_tile(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32,
+                                       size_t scratch_floats, int32_t chosen[3]);
 
 /* Kernel-level entry point for tests: causal multi-head attention of Appendix A.1 in isolation, forward and (when
  * dout is not NULL) backward, on a fused activation buffer qkv [B*N, 3*Hs*d_head] (q | k | v, desc.dtype).

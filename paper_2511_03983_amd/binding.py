@@ -106,6 +106,7 @@ _SIGS = {
     "twist_gemm_act_raw": ([_vp, _i32, _i32, _i32, _i32, _vp, C.c_int64, _vp, C.c_int64, _vp, C.c_int64, _vp, _i32, _vp, _i32], _i32),
     "twist_weight_grads_raw": ([_vp, _i32, C.POINTER(WeightGrad), _i32, _vp, _sz, _PI32], _i32),
     "twist_gemm_kernel": ([_vp, _i32, _i32, _i32, _i32, _i32, _sz, _PI32], _i32),
+    "twist_gemm_tile": ([_vp, _i32, _i32, _i32, _i32, _i32, _sz, _PI32], _i32),
     "twist_attention_raw": ([_vp, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp], _i32),
     "twist_norm_raw": ([_vp, _vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz], _i32),
     "twist_norm_raw_static": ([_vp, _vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp], _i32),
@@ -303,9 +304,16 @@ class Context:
         return tuple(chosen)
 
     def twist_gemm_kernel(self, layout: int, M: int, N: int, K: int, out_f32: bool = False, scratch_floats: int = 0):
-        """(tile rows, tile columns, parts of the contraction) of a projection whose operands are aligned; host only."""
+        """(tile rows, tile columns, parts of the contraction) of a projection whose operands are aligned, among the kernels whose waves
+        share every slice; host only."""
         chosen = (_i32 * 3)()
         _check(lib.twist_gemm_kernel(self.h, layout, M, N, K, int(out_f32), scratch_floats, chosen), self.h)
+        return tuple(chosen)
+
+    def twist_gemm_tile(self, layout: int, M: int, N: int, K: int, out_f32: bool = False, scratch_floats: int = 0):
+        """The same among all kernels: what the product runs on; host only."""
+        chosen = (_i32 * 3)()
+        _check(lib.twist_gemm_tile(self.h, layout, M, N, K, int(out_f32), scratch_floats, chosen), self.h)
         return tuple(chosen)
 
     def twist_backward_schedule(self, tokens: int, head_columns: int, ffn_columns: int):

@@ -3,6 +3,7 @@
 //    gemm_nt.hip where both operands are contiguous along k), and 64x64 and 32x32 tiles for products too small to fill the
 //    chip with those (gemm_dl.hip); operands stay in LDS in their memory orientation, and those whose contraction index is the slow
 //    axis in memory are read back with the transposing LDS load.
+//    Products between the two run on tiles of 64 to 192 rows and columns (gemm_kp.hip).
 //  - fp32 operands: gemm_f32.hip.
 //  - anything else (unaligned bf16 shapes, fp32 contractions of a few elements): a plain tiled FMA kernel with arbitrary strides.
 #include <algorithm>
@@ -415,29 +416,60 @@ __global__ __launch_bounds__(256) void mfma_only_kernel(int iters, float *sink, 
 //   1536 x 1536 x 2048 (TN)  39.5     33.8    25.3    47.5   (fp32 output)
 // and cut: 768 x 640 x 4096 (TN) 17.5 whole, 15.2 in two parts, 17.5 in three; 2048 x 1024 x 8192 56 in five, 63 in eight;
 // 256 x 128 x 2048 6.1 whole, 9.0 in eight.
-struct Kind { int bm, bn; double fixed, tile, tile32, s0, s1, nt; };
-constexpr Kind kKinds[] = {{256, 256, 1.0, 9.1, 0.36, 0.434, 0.32, 1.0}, {256, 128, 1.7, 4.4, 1.0, 0.344, 0.23, 1.0}, {64, 64, 2.95, 0.875, 0.19, 0.12, 0.011, 1.0},
-                           {32, 32, 2.5, 0.81, 0.06, 0.068, 0.01, 0.71}};
-struct Choice { int kind, parts; double us = 0.0, idle = 0.0; };  // idle: of the microseconds, those of CUs without a tile
-// (several products over the same K that share a launch: their tiles and outputs together)
-Choice choose(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, bool may_split, size_t split_floats) {
-  Choice best{0, 1};
+struct Kind { int bm, bn; double fixed, tile, tile32, s0, s1, lay[3]; };  // lay: factors of a slice's time for GEMM_NT, NN, TN
+constexpr Kind kKinds[] = {{256, 256, 1.0, 9.1, 0.36, 0.434, 0.32, {1, 1, 1}}, {256, 128, 1.7, 4.4, 1.0, 0.344, 0.23, {1, 1, 1}},
+                           {64, 64, 2.95, 0.875, 0.19, 0.12, 0.011, {1, 1, 1}}, {32, 32, 2.5, 0.81, 0.06, 0.068, 0.01, {0.71, 1, 1}},
+// Two groups that share the contraction (gemm_kp.hip).  Fitted to 600 products of their own, sizes 64 to 50257 (half of the estimates within
+// 4 %, 8 % for 64x96; nine tenths within 13 and 18 %).  They are taken where they are expected to be a twelfth faster than the others: of 200
+// products not fitted to, 33 then went to them, 20 % faster on average and one slower, by 4.6 %; with the bare estimates 43, one of them
+// 23 % slower.  Launches of fewer than 128 tiles (2048 x 896 x 3000, TN, 112 of 128x128: 22.8 us, 64x64 20.8) and of more than four rounds
+// (50257 x 280 x 7007, TN: 383, 256x256 329) are left out, and contractions beyond 8192 (choose_any).  us, the others' fastest / these:
+//   8192 x 768 x 768            16.2 / 15.2 (128x192)      2048 x 768 x 2048 (f32)       15.3 / 11.8 (64x96)
+//   4096 x 768 x 2560 (f32)     30.4 / 21.1 (128x96)       2048 x 1536 x 768             13.0 /  9.9 (128x96)
+//   2048 x 2048 x 768           16.0 / 11.4 (128x128)      3000 x 2048 x 2488 (f32)      48.3 / 39.2 (192x128)
+//   3000 x 2048 x 4976 (NN)     74.5 / 59.5 (192x128)      1024 x 2048 x 8192 (TN)       50.1 / 51.1 (128x128; 46 in two parts)
+//   2816 x 2048 x 8192 (TN)      119 / 95   (128x192)      3072 x 2048 x 8192 (TN)        121 / 94   (192x128)
+// and on the other side of the line 8192 x 768 x 192 (NN, f32) 9.6 / 13.1, 4096 x 1920 x 768 16.5 / 19.1, 8192 x 1024 x 2048 33.2 / 35.0,
+// 8192 x 5632 x 2048 144 / 200, 1024^3 7.2 / 7.9, 50257 x 768 x 8192 (TN) 594 / 732.
+                           {128, 192, 1.62, 6.98, 0.31, 0.252, 0.118, {1, 1.045, 1.08}}, {192, 128, 1.09, 6.73, 0.33, 0.262, 0.1, {1, 1.005, 1.075}},
+                           {128, 128, 1.98, 4.75, 0.34, 0.16, 0.09, {1, 1.01, 0.975}}, {128, 96, 2.66, 3.92, 0.35, 0.143, 0.058, {1, 1.105, 1.17}},
+                           {64, 96, 5.52, 0.97, 0.3, 0.0865, 0.0335, {1, 1.085, 1.12}}};
+constexpr int kOneGroup = 4, kAllKinds = sizeof(kKinds) / sizeof(kKinds[0]);  // kinds from kOneGroup on are those of gemm_kp.hip
+struct Choice { int kind, parts; double us = 0.0, idle = 0.0; int64_t items = 0; };  // idle: of the microseconds, those of CUs without a tile
+// (several products over the same K that share a launch: their tiles and outputs together; among kinds first .. last - 1)
+Choice choose_of(int first, int last, GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, int most_parts, size_t split_floats) {
+  Choice best{first, 1, 1e30};
   double best_us = 1e30, outputs = 0.0;
   for (int i = 0; i < n; ++i) outputs += (double)Ms[i] * Ns[i];
-  for (int k = 0; k < 4; ++k) {
+  for (int k = first; k < last; ++k) {
     const Kind &kd = kKinds[k];
     int64_t tiles = 0;
     for (int i = 0; i < n; ++i) tiles += (int64_t)((Ms[i] + kd.bm - 1) / kd.bm) * ((Ns[i] + kd.bn - 1) / kd.bn);
-    for (int parts = 1; parts <= 16; ++parts) {
-      if (parts > 1 && (!may_split || K < 256 * parts || parts * outputs > (double)split_floats)) break;
+    for (int parts = 1; parts <= most_parts; ++parts) {
+      if (parts > 1 && (K < 256 * parts || parts * outputs > (double)split_floats)) break;
       const int64_t items = tiles * parts, rounds = (items + 255) / 256;
-      const double share = std::min(1.0, items / 256.0), slice = (kd.s0 + kd.s1 * share) * (lay == GEMM_NT ? kd.nt : 1.0);
+      if (k >= kOneGroup && (items < 128 || items > 1024)) continue;
+      const double share = std::min(1.0, items / 256.0), slice = (kd.s0 + kd.s1 * share) * kd.lay[lay];
       double us = kd.fixed + rounds * (kd.tile + (f32_out || parts > 1 ? kd.tile32 : 0.0) + K / 32.0 / parts * slice);
       if (parts > 1) us += 4.4 + (parts + 1.0) * outputs * 4.0 / 2.8e6;
-      if (us < best_us) { best_us = us; best = {k, parts, us, us * (1.0 - (k < 2 ? items / (256.0 * rounds) : share))}; }
+      if (us < best_us) { best_us = us; best = {k, parts, us, us * (1.0 - (k < 2 || k >= kOneGroup ? items / (256.0 * rounds) : share)), items}; }
     }
   }
   return best;
+}
+// the kernels whose waves share every slice
+Choice choose(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, bool may_split, size_t split_floats) {
+  return choose_of(0, kOneGroup, lay, n, Ms, Ns, K, f32_out, may_split ? 16 : 1, split_floats);
+}
+// all kernels.  Those of gemm_kp.hip cut a contraction no further than the others would.  Where it is longer than any batch (the vocabulary's input
+// gradient) they wait for memory: a CU has 120 KB in flight, and operands that come from beyond the caches take 2 us and more to arrive; us, the others /
+// these: 8192 x 768 x 50257 778 / 741, 4096 x 512 x 50257 241 / 305, 1500 x 1024 x 32000 116 / 137, 8192 x 2048 x 32000 817 / 1074.
+// Of the small tiles two share a CU, and their second round is shorter than the estimate has it (a tenth of the whole time): 0.82 there.
+Choice choose_any(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, bool may_split, size_t split_floats) {
+  const Choice one = choose(lay, n, Ms, Ns, K, f32_out, may_split, split_floats);
+  if (K > 8192) return one;
+  const Choice two = choose_of(kOneGroup, kAllKinds, lay, n, Ms, Ns, K, f32_out, one.parts, split_floats);
+  return two.us < (one.kind >= 2 && one.items > 256 ? 0.82 : 0.92) * one.us ? two : one;
 }
 
 // kernel, parts of the contraction and their length (a multiple of the kernel's slices) of a bf16 product whose operands are aligned
@@ -446,8 +478,9 @@ Cut cut_into(Choice ch, int K) {
   const int step = ch.kind < 2 ? 32 : 128, kchunk = ((K + ch.parts - 1) / ch.parts + step - 1) / step * step;
   return {ch.kind, (K + kchunk - 1) / kchunk, kchunk};
 }
-Cut cut_of(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split, size_t split_floats) {
-  Choice ch = choose(lay, 1, &M, &N, K, f32_out, may_split && lay != GEMM_NT, split_floats);
+// `any`: among all kernels
+Cut cut_of(const twist_ctx *ctx, bool any, GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split, size_t split_floats) {
+  Choice ch = (any ? choose_any : choose)(lay, 1, &M, &N, K, f32_out, may_split && lay != GEMM_NT, split_floats);
   if (ctx->gemm_tile) ch = {ctx->gemm_tile == 256 ? 0 : 1, 1};
   return cut_into(ch, K);
 }
@@ -531,7 +564,7 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
   const bool vec_ok = bf16 && !no_mfma && aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 && k_ok && span_ok;
   if (vec_ok) {
     const uint16_t *a = static_cast<const uint16_t *>(A), *b = static_cast<const uint16_t *>(B);
-    const Cut ch = cut_of(ctx, lay, M, N, K, e.out_f32, e.splitk_ws && !e.bias && !e.residual && aligned16(e.splitk_ws), e.splitk_floats);
+    const Cut ch = cut_of(ctx, !e.targets, lay, M, N, K, e.out_f32, e.splitk_ws && !e.bias && !e.residual && aligned16(e.splitk_ws), e.splitk_floats);
     const int parts = ch.parts, kchunk = ch.kchunk;
     if (e.act_out) {
       ep.act_out = e.act_out;
@@ -549,7 +582,8 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
       case 0: launch_pp<256>(stream, lay, M, N, K, a, lda, b, ldb, ep, parts, kchunk); break;
       case 1: launch_pp<128>(stream, lay, M, N, K, a, lda, b, ldb, ep, parts, kchunk); break;
       case 2: twist_launch_gemm_dl(stream, 64, lay, M, N, K, a, lda, b, ldb, &ep, parts, kchunk); break;
-      default: twist_launch_gemm_dl(stream, 32, lay, M, N, K, a, lda, b, ldb, &ep, parts, kchunk); break;
+      case 3: twist_launch_gemm_dl(stream, 32, lay, M, N, K, a, lda, b, ldb, &ep, parts, kchunk); break;
+      default: twist_launch_gemm_kp(stream, kKinds[ch.kind].bm, kKinds[ch.kind].bn, lay, M, N, K, a, lda, b, ldb, &ep, parts, kchunk); break;
     }
     TW_HIP(ctx, hipGetLastError());
     return parts > 1 ? twist_splitk_reduce(ctx, stream, e.splitk_ws, parts, M, N, e.out, ldc, e.out_f32, e.alpha) : TWIST_OK;
@@ -604,7 +638,7 @@ twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGra
   double outputs = 0.0;
   for (int i = 0; i < g.n; ++i) outputs += (double)Ms[i] * Ns[i];
   TW_TRY(timer.start(2.0 * outputs * K));
-  const Cut ch = cut_into(choose(GEMM_TN, g.n, Ms, Ns, K, true, scratch && aligned16(scratch), scratch_floats), K);
+  const Cut ch = cut_into(choose_any(GEMM_TN, g.n, Ms, Ns, K, true, scratch && aligned16(scratch), scratch_floats), K);
   if (chosen) { chosen[0] = kKinds[ch.kind].bm; chosen[1] = kKinds[ch.kind].bn; chosen[2] = ch.parts; }
   int tiles = 0, blocks = 0;
   float *part0 = scratch;
@@ -630,8 +664,10 @@ twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGra
     const dim3 grid(std::min(tiles * ch.parts, 256)), block(512);
     if (ch.kind == 0) hipLaunchKernelGGL((pp::gemm_pp_kernel<0, true, 256, TnGroup>), grid, block, 0, stream, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, ch.parts, ch.kchunk, run);
     else hipLaunchKernelGGL((pp::gemm_pp_kernel<0, true, 128, TnGroup>), grid, block, 0, stream, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, ch.parts, ch.kchunk, run);
-  } else {
+  } else if (ch.kind < kOneGroup) {
     twist_launch_gemm_dl_group(stream, ch.kind == 2 ? 64 : 32, &run, tiles, K, &ep, ch.parts, ch.kchunk);
+  } else {
+    twist_launch_gemm_kp_group(stream, kKinds[ch.kind].bm, kKinds[ch.kind].bn, &run, tiles, K, &ep, ch.parts, ch.kchunk);
   }
   TW_HIP(ctx, hipGetLastError());
   if (ch.parts > 1) {
@@ -697,11 +733,12 @@ extern "C" twist_status twist_weight_grads_raw(twist_ctx *ctx, int32_t n, const 
   return twist_weight_grads(ctx, ctx->d.dtype == TWIST_BF16, n, products, K, scratch, scratch_floats, nullptr, chosen);
 }
 
-extern "C" twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats, int32_t chosen[3]) {
-  if (!ctx || !chosen) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_kernel: null argument");
-  if (layout < 0 || layout > 2 || M < 1 || N < 1 || K < 1) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_kernel: bad layout or size");
+static twist_status tile_query(const char *who, bool any, twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats,
+                               int32_t chosen[3]) {
+  if (!ctx || !chosen) TW_FAIL(ctx, TWIST_EINVAL, "%s: null argument", who);
+  if (layout < 0 || layout > 2 || M < 1 || N < 1 || K < 1) TW_FAIL(ctx, TWIST_EINVAL, "%s: bad layout or size", who);
   if (ctx->d.dtype == TWIST_BF16) {
-    const Cut ch = cut_of(ctx, (GemmLayout)layout, M, N, K, out_f32, scratch_floats > 0, scratch_floats);
+    const Cut ch = cut_of(ctx, any, (GemmLayout)layout, M, N, K, out_f32, scratch_floats > 0, scratch_floats);
     chosen[0] = kKinds[ch.kind].bm; chosen[1] = kKinds[ch.kind].bn; chosen[2] = ch.parts;
   } else if (short_f32(ctx, (GemmLayout)layout, M, N, K)) {
     chosen[0] = chosen[1] = 0; chosen[2] = 1;
@@ -711,6 +748,12 @@ extern "C" twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_
     chosen[1] = chosen[0];
   }
   return TWIST_OK;
+}
+extern "C" twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats, int32_t chosen[3]) {
+  return tile_query("twist_gemm_kernel", false, ctx, layout, M, N, K, out_f32, scratch_floats, chosen);
+}
+extern "C" twist_status twist_gemm_tile(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats, int32_t chosen[3]) {
+  return tile_query("twist_gemm_tile", true, ctx, layout, M, N, K, out_f32, scratch_floats, chosen);
 }
 
 extern "C" twist_status twist_set_overlap(twist_ctx *ctx, int32_t enable) {

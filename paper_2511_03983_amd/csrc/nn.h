@@ -59,6 +59,10 @@ void twist_launch_gemm_dl(hipStream_t st, int tile, GemmLayout lay, int M, int N
                           int parts, int kchunk);
 // the same for the weight gradients of a group (a gemm_tile.h TnGroup), `tiles` in all
 void twist_launch_gemm_dl_group(hipStream_t st, int tile, const void *group, int tiles, int K, const void *ep, int parts, int kchunk);
+// the bf16 kernels whose two groups of waves share the contraction: tiles of 128x192, 192x128, 128x128, 128x96 and 64x96; otherwise as the two above
+void twist_launch_gemm_kp(hipStream_t st, int bm, int bn, GemmLayout lay, int M, int N, int K, const uint16_t *a, int64_t lda, const uint16_t *b, int64_t ldb,
+                          const void *ep, int parts, int kchunk);
+void twist_launch_gemm_kp_group(hipStream_t st, int bm, int bn, const void *group, int tiles, int K, const void *ep, int parts, int kchunk);
 // the fp32 form of twist_gemm, and the sum of the partial products [parts][M][N] of a product whose contraction was cut
 // (out = alpha * sum in ascending order)
 twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,

@@ -258,6 +258,65 @@ def test_cut_bf16_projection(lib, tile, layout, M, N, K):
         assert torch.isnan(buf[M * N:]).all() and torch.isnan(scratch[parts * M * N:]).all()
 
 
+# Tiles whose two groups of waves share the contraction: every tile in every layout, ragged rows and columns, contractions that end within a
+# slice, on an odd and on an even one; cut; with alpha, and with the activation of the up projection
+@pytest.mark.parametrize("tile,layout,M,N,K", [
+    ((64, 96), 0, 262, 3330, 856), ((128, 96), 0, 3527, 844, 208), ((128, 128), 0, 787, 3836, 200), ((128, 192), 0, 1619, 3636, 808), ((192, 128), 0, 1309, 3077, 648),
+    ((64, 96), 1, 3417, 267, 887), ((128, 96), 1, 1374, 2178, 219), ((128, 128), 1, 1647, 1881, 209), ((128, 192), 1, 1578, 3605, 976), ((192, 128), 1, 1038, 3635, 730),
+    ((64, 96), 2, 2729, 323, 943), ((128, 96), 2, 2942, 1040, 210), ((128, 128), 2, 1932, 1571, 203), ((128, 192), 2, 2306, 2462, 890), ((192, 128), 2, 1035, 3598, 637),
+    ((128, 128), 2, 1020, 2045, 8190)])
+def test_bf16_projection_in_two_groups(lib, tile, layout, M, N, K):
+    cut = K > 8000
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=1, d_head=8, d_ff=N, act="relu", dtype="bf16")))
+    scratch = torch.full((1 << 24,), float("nan"), device="cuda")
+    rows, cols, parts = ctx.twist_gemm_tile(layout, M, N, K, True, scratch.numel() if cut else 0)
+    assert (rows, cols) == tile and (parts > 1) == cut, (rows, cols, parts)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    up = lambda n: (n + 7) // 8 * 8
+    def operand(r, c):                                                   # rows padded to whole chunks: with zeros along k, with NaNs otherwise
+        x = torch.full((r, up(c)), 0.0 if c == K else float("nan"), device="cuda").bfloat16()
+        x[:, :c] = torch.randn((r, c), generator=gen, device="cuda").bfloat16()
+        return x[:, :c]
+    A = operand(K, M) if layout == 2 else operand(M, K)
+    B = operand(N, K) if layout == 0 else operand(K, N)
+    want = (A.double().T if layout == 2 else A.double()) @ (B.double().T if layout == 0 else B.double())
+    for dt, alpha in ((torch.float32, 0.5), (torch.float32, 1.0), (torch.bfloat16, 1.0)):
+        buf = torch.full((M * N + 64,), float("nan"), dtype=dt, device="cuda")             # what lies behind the result must stay
+        out = buf[:M * N].view(M, N)
+        if dt == torch.float32 and cut: ctx.twist_gemm_raw_cut(layout, M, N, K, A, B, out, scratch, alpha=alpha)
+        else: ctx.twist_gemm_raw(layout, M, N, K, A, B, out, alpha=alpha)
+        torch.cuda.synchronize()
+        err = (out.double() - alpha * want).norm(dim=1) / (alpha * want).norm(dim=1)
+        # fp32 sums of K exact products: 2^-24 sqrt(K) at most; one left out or counted twice shows as 1 / sqrt(K), the rounding to bf16 as 2e-3
+        assert float(err.max()) <= (2.0 ** -24 * K ** 0.5 if dt == torch.float32 else 5e-3)
+        assert torch.isnan(buf[M * N:]).all()
+    if layout == 0:
+        got, act = ctx.twist_gemm_act_raw(A.contiguous(), B.contiguous(), None, ctx.desc.act)
+        torch.cuda.synchronize()
+        assert torch.equal(got, out) and torch.equal(act, out.relu())
+
+
+# ... and as weight gradients in one launch, whole and cut
+@pytest.mark.parametrize("tile,cut,K,shapes", [((64, 96), False, 1000, [(264, 1541), (520, 768), (0, 8), (768, 264)]),
+                                               ((192, 128), False, 1000, [(2000, 2048), (1032, 520)]), ((128, 128), True, 8190, [(1032, 1100), (520, 1032)])])
+def test_weight_gradients_in_two_groups(lib, tile, cut, K, shapes):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    up = lambda n: (n + 7) // 8 * 8
+    rows = lambda n: torch.randn((K, up(n)), generator=gen, device="cuda").bfloat16()[:, :n]
+    scratch = torch.full((1 << 24,), float("nan"), device="cuda")
+    bufs = [torch.full((M * N + 64,), float("nan"), device="cuda") for M, N in shapes]
+    products = [(rows(M), rows(N), buf[:M * N].view(M, N)) for (M, N), buf in zip(shapes, bufs)]
+    alphas = (0.5, 1.0, 2.0, 1.0)[:len(shapes)]
+    r, c, parts = ctx.twist_weight_grads_raw(K, products, scratch, alphas)
+    torch.cuda.synchronize()
+    assert (r, c) == tile and (parts > 1) == cut, (r, c, parts)
+    for (a, b, out), buf, alpha in zip(products, bufs, alphas):
+        want = alpha * (a.double().T @ b.double())
+        assert out.numel() == 0 or float(((out.double() - want).norm(dim=1) / want.norm(dim=1)).max()) <= 2.0 ** -24 * K ** 0.5
+        assert torch.isnan(buf[out.numel():]).all()
+
+
 # the up projection with its activation: the projection's bits and the activation kernel's of them, on every tile and on the plain kernel, with and without the
 # projection itself
 @pytest.mark.parametrize("act", ["gelu_tanh", "relu"])
