@@ -284,7 +284,7 @@ TWIST_API twist_status twist_gemm_act_raw(twist_ctx *ctx, int32_t layout, int32_
                                           int64_t ldb, void *C, int64_t ldc, const void *bias, int32_t act, void *act_out, int32_t act_only);
 
 /* Weight gradients alone, as the training pass forms a layer's: out[i][M][N] = alpha a^T b over the same K rows, n <= 4 products in one
- * launch where their kernels allow it (bf16, 16-byte aligned rows), otherwise one by one.  Rows of a and b may be padded, those of out
+ * launch where their kernels allow it (16-byte aligned rows), otherwise one by one.  Rows of a and b may be padded, those of out
  * (fp32) are not.  scratch (device, or NULL) may receive fp32 partial products.  chosen (host, or NULL) receives tile rows, tile
  * columns and parts of the contraction of a common launch, or zeros. */
 typedef struct {

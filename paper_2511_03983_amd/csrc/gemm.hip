@@ -608,23 +608,33 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
 
 // What bound them: the weight gradients of one layer of a small model are too few tiles each to fill the chip, cut into many parts with
 // a pass over the partial products behind each.  Together they fill it in fewer parts: 8192 x 768 x (192 heads, 768 hidden) in bf16 four
-// launches and four sums, 109 us, against 49 + 8; 2048 x 768 x (512, 2048) 77 us against 44.
+// launches and four sums, 109 us, against 49 + 8; 2048 x 768 x (512, 2048) 77 us against 44.  In fp32 (one stream, so where they are
+// fewest): 256 x 128 x (64, 256) 20 us against 8, 1248 x 88 x (832, 344) 46 / 20, 1024 x 768 x (384, 1536) 109 / 59; of 156 such groups and pairs the
+// mean is two thirds.
 twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGrad *items, int K, float *scratch, size_t scratch_floats, hipStream_t st,
                                 int32_t *chosen) {
   TnGroup g{};
   GroupOut o{};
   int Ms[kGroupProducts], Ns[kGroupProducts];
-  bool one = bf16 && !ctx->plain_only && !ctx->gemm_tile && n <= kGroupProducts;
+  // (fp32 contractions of a few elements: short_f32)
+  bool one = !ctx->plain_only && !ctx->gemm_tile && n <= kGroupProducts && (bf16 || K > 8);
   for (int i = 0; i < n && one; ++i) {
     const WeightGrad &w = items[i];
     if (w.M <= 0 || w.N <= 0) continue;
     Ms[g.n] = w.M; Ns[g.n] = w.N;
     o.out[g.n] = w.out;
     g.p[g.n++] = {static_cast<const uint16_t *>(w.a), static_cast<const uint16_t *>(w.b), w.out, w.lda, w.ldb, w.M, w.N, 0, 0, 0, w.alpha, w.N % 4 == 0 && aligned16(w.out)};
-    one = aligned16(w.a) && aligned16(w.b) && w.lda % 8 == 0 && w.ldb % 8 == 0 && K * w.lda * 2 < (1ll << 31) && K * w.ldb * 2 < (1ll << 31) &&
-          256ll * w.N * 4 < (1ll << 31);
+    const int row = bf16 ? 8 : 4;  // elements that a row's stride is a multiple of
+    one = aligned16(w.a) && aligned16(w.b) && w.lda % row == 0 && w.ldb % row == 0;
+    if (bf16) one = one && K * w.lda * 2 < (1ll << 31) && K * w.ldb * 2 < (1ll << 31) && 256ll * w.N * 4 < (1ll << 31);
+    else one = one && std::max(w.lda, w.ldb) < 1 << 23;
   }
-  if (!one || g.n < 2 || K <= 0) {
+  const bool may_split = scratch && aligned16(scratch);
+  Cut ch{0, 1, K};
+  int bm = 0, bn;
+  one = one && g.n > 1 && K > 0;
+  if (one && !bf16) one = twist_gemm_f32_group_choice(g.n, Ms, Ns, K, may_split ? scratch_floats : 0, bm, ch.parts, ch.kchunk);
+  if (!one) {
     for (int i = 0; i < n; ++i) {
       GemmEpilogue e;
       e.alpha = items[i].alpha; e.out = items[i].out; e.out_f32 = 1;
@@ -638,14 +648,20 @@ twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGra
   double outputs = 0.0;
   for (int i = 0; i < g.n; ++i) outputs += (double)Ms[i] * Ns[i];
   TW_TRY(timer.start(2.0 * outputs * K));
-  const Cut ch = cut_into(choose_any(GEMM_TN, g.n, Ms, Ns, K, true, scratch && aligned16(scratch), scratch_floats), K);
-  if (chosen) { chosen[0] = kKinds[ch.kind].bm; chosen[1] = kKinds[ch.kind].bn; chosen[2] = ch.parts; }
+  if (bf16) {
+    ch = cut_into(choose_any(GEMM_TN, g.n, Ms, Ns, K, true, may_split, scratch_floats), K);
+    bm = kKinds[ch.kind].bm;
+    bn = kKinds[ch.kind].bn;
+  } else {
+    bn = bm;
+  }
+  if (chosen) { chosen[0] = bm; chosen[1] = bn; chosen[2] = ch.parts; }
   int tiles = 0, blocks = 0;
   float *part0 = scratch;
   for (int i = 0; i < g.n; ++i) {
     TnProduct &p = g.p[i];
-    p.tiles_m = (p.M + kKinds[ch.kind].bm - 1) / kKinds[ch.kind].bm;
-    p.tiles_n = (p.N + kKinds[ch.kind].bn - 1) / kKinds[ch.kind].bn;
+    p.tiles_m = (p.M + bm - 1) / bm;
+    p.tiles_n = (p.N + bn - 1) / bn;
     p.first = tiles;
     tiles += p.tiles_m * p.tiles_n;
     o.first[i] = blocks;
@@ -660,14 +676,21 @@ twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGra
   if (ch.parts > 1)
     for (int i = 0; i < g.n; ++i) run.p[i].alpha = 1.f;
   Ep ep{1.f, nullptr, nullptr, nullptr, 1, 0, nullptr, 0, 0};
-  if (ch.kind < 2) {
+  if (!bf16) {
+    F32Product fp[kGroupProducts];
+    for (int i = 0; i < g.n; ++i) {
+      const TnProduct &p = run.p[i];
+      fp[i] = {reinterpret_cast<const float *>(p.a), reinterpret_cast<const float *>(p.b), p.out, p.lda, p.ldb, p.M, p.N, p.first, p.tiles_m, p.tiles_n, p.alpha};
+    }
+    twist_launch_gemm_f32_group(stream, bm, g.n, fp, tiles, K, ch.parts, ch.kchunk);
+  } else if (ch.kind < 2) {
     const dim3 grid(std::min(tiles * ch.parts, 256)), block(512);
     if (ch.kind == 0) hipLaunchKernelGGL((pp::gemm_pp_kernel<0, true, 256, TnGroup>), grid, block, 0, stream, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, ch.parts, ch.kchunk, run);
     else hipLaunchKernelGGL((pp::gemm_pp_kernel<0, true, 128, TnGroup>), grid, block, 0, stream, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, ch.parts, ch.kchunk, run);
   } else if (ch.kind < kOneGroup) {
     twist_launch_gemm_dl_group(stream, ch.kind == 2 ? 64 : 32, &run, tiles, K, &ep, ch.parts, ch.kchunk);
   } else {
-    twist_launch_gemm_kp_group(stream, kKinds[ch.kind].bm, kKinds[ch.kind].bn, &run, tiles, K, &ep, ch.parts, ch.kchunk);
+    twist_launch_gemm_kp_group(stream, bm, bn, &run, tiles, K, &ep, ch.parts, ch.kchunk);
   }
   TW_HIP(ctx, hipGetLastError());
   if (ch.parts > 1) {

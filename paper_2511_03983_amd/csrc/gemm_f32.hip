@@ -26,6 +26,7 @@
 // ones is the rate of the bf16 instruction at the power limit (six of them per product: 1.04 PFLOP/s in 4096^3), the small ones the chain of slices.
 // Strides and bases that do not allow 16-byte loads go through the scalar loader (VEC = 0).
 #include <algorithm>
+#include <type_traits>
 
 #include "nn.h"
 
@@ -225,13 +226,35 @@ struct Ep32 {
   int64_t ldc;
 };
 
+// Weight gradients that share a launch: with G = F32Group their sizes, operands and outputs replace the kernels' arguments, and tiles_m is the
+// number of tiles of all of them.
+struct F32Group {
+  int n;
+  F32Product p[kGroupProducts];
+};
+struct NoGroup {};
+template <class G>
+__device__ __forceinline__ void take_product(const G &group, int &bid, int &M, int &N, const float *&A, int64_t &lda, const float *&B, int64_t &ldb, Ep32 &ep,
+                                             int &tiles_m, int &tiles_n) {
+  if constexpr (std::is_same<G, F32Group>::value) {
+    int q = 0;
+#pragma unroll
+    for (int i = 1; i < kGroupProducts; ++i)
+      if (i < group.n && bid >= group.p[i].first) q = i;
+    const F32Product &p = group.p[q];
+    bid -= p.first;
+    M = p.M; N = p.N; A = p.a; lda = p.lda; B = p.b; ldb = p.ldb; tiles_m = p.tiles_m; tiles_n = p.tiles_n;
+    ep.alpha = p.alpha; ep.out = p.out; ep.ldc = N;
+  }
+}
+
 // Waves: 2 x 2 over the tile (W2 = 2) or one (W2 = 1), times WK shares of a slice's k; where two waves share a SIMD (8 waves) the first four
 // form the next slice's terms before their products, the others after, so that a SIMD's matrix and vector pipes are busy together.
 // Grid: x = tiles (dealt so that each of the 8 XCDs walks a contiguous range, in columns of 8 tile rows), y = parts of the
 // contraction (kchunk long, a multiple of BK; part p writes its partial product to out + p M ldc).
-template <int AKM, int BKM, int BM, int W2, int WK, int BK, int VEC>
+template <int AKM, int BKM, int BM, int W2, int WK, int BK, int VEC, class G = NoGroup>
 __global__ __launch_bounds__(64 * W2 * W2 * WK) void gemm_f32_kernel(int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, Ep32 ep, int tiles_m,
-                                                                     int tiles_n, int kchunk) {
+                                                                     int tiles_n, int kchunk, G group) {
   constexpr int BN = BM, NT = 64 * W2 * W2 * WK, TM = BM / W2 / 32, KS = BK / 16 / WK;  // TM: 32x32 tiles of a wave each way; KS: its steps of 16 k per slice
   using LA = Loader<BM, AKM, VEC, BK, NT>;
   using LB = Loader<BN, BKM, VEC, BK, NT>;
@@ -240,6 +263,7 @@ __global__ __launch_bounds__(64 * W2 * W2 * WK) void gemm_f32_kernel(int M, int 
   const int nb = tiles_m * tiles_n;
   int bid = blockIdx.x;
   if (nb % 8 == 0) bid = (bid % 8) * (nb / 8) + bid / 8;
+  take_product(group, bid, M, N, A, lda, B, ldb, ep, tiles_m, tiles_n);
   constexpr int GROUP = 8;
   const int per_group = GROUP * tiles_n;
   const int grp = bid / per_group, first_m = grp * GROUP;
@@ -412,9 +436,9 @@ __global__ __launch_bounds__(64 * W2 * W2 * WK) void gemm_f32_kernel(int M, int 
 
 // Grid: x = tiles (dealt so that each of the 8 XCDs walks a contiguous range, in columns of 8 tile rows), y = parts of the
 // contraction (kchunk long, a multiple of BK; part p writes its partial product to out + p M ldc).
-template <int AKM, int BKM, int VEC>
+template <int AKM, int BKM, int VEC, class G = NoGroup>
 __global__ __launch_bounds__(256) void gemm_f32_small_kernel(int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, Ep32 ep, int tiles_m,
-                                                       int tiles_n, int kchunk) {
+                                                       int tiles_n, int kchunk, G group) {
   constexpr int BM = 32, BN = 32, BK = 64, US = BK / 8 / 4;  // US: groups of 4 MFMAs per slice and wave
   using LA = SmallLoader<BM, AKM, VEC, BK>;
   using LB = SmallLoader<BN, BKM, VEC, BK>;
@@ -423,6 +447,7 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(int M, int N, int K
   const int nb = tiles_m * tiles_n;
   int bid = blockIdx.x;
   if (nb % 8 == 0) bid = (bid % 8) * (nb / 8) + bid / 8;
+  take_product(group, bid, M, N, A, lda, B, ldb, ep, tiles_m, tiles_n);
   constexpr int GROUP = 8;
   const int per_group = GROUP * tiles_n;
   const int grp = bid / per_group, first_m = grp * GROUP;
@@ -502,7 +527,7 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(int M, int N, int K
 template <int AKM, int BKM, int BM, int W2, int WK, int BK, int VEC>
 void launch(hipStream_t st, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, const Ep32 &ep, int parts, int kchunk) {
   const int tm = (M + BM - 1) / BM, tn = (N + BM - 1) / BM;
-  hipLaunchKernelGGL((gemm_f32_kernel<AKM, BKM, BM, W2, WK, BK, VEC>), dim3(tm * tn, parts), dim3(64 * W2 * W2 * WK), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk);
+  hipLaunchKernelGGL((gemm_f32_kernel<AKM, BKM, BM, W2, WK, BK, VEC>), dim3(tm * tn, parts), dim3(64 * W2 * W2 * WK), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
 }
 
 template <int AKM, int BKM, int VEC>
@@ -515,7 +540,7 @@ void launch_tile(hipStream_t st, int tile, int M, int N, int K, const float *A, 
     return;
   }
   const int tm = (M + 31) / 32, tn = (N + 31) / 32;
-  hipLaunchKernelGGL((gemm_f32_small_kernel<AKM, BKM, VEC>), dim3(tm * tn, parts), dim3(256), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk);
+  hipLaunchKernelGGL((gemm_f32_small_kernel<AKM, BKM, VEC>), dim3(tm * tn, parts), dim3(256), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -528,14 +553,18 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 // 1024 x 768 x 1536 76 / 32 / 33, 512 x 1536 x 768 - / 18.7 / 19.3, 256 x 1024 x 1024 - / 22 / 13, 4096^3 790 / 1083 / -, 1024 x 50257 x 768 586 / 713 / -,
 // 8192 x 2048 x 24 43 / 40 / 98; 1500 x 1500 x 2000 (TN) 118 / 129 / 112, in two parts 131 / 105 / 119, in four 109 / 104 / 122;
 // 1024 x 768 x 8003 (TN) 414 / 178 / 143, in four parts 120 / 140 / 147, in eight 131 / 124 / 150.
+// Several products over the same K that share a launch: their tiles and outputs together.
 struct Choice { int tile, parts; };
-Choice choose(GemmLayout lay, int M, int N, int K, bool may_split, size_t split_floats) {
-  Choice best{64, 1};
-  double best_us = 1e30;
-  for (int tile = 128; tile >= 32; tile /= 2) {
-    const int64_t tiles = (int64_t)((M + tile - 1) / tile) * ((N + tile - 1) / tile);
+Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bool may_split, size_t split_floats, int least_tile = 32, int least_parts = 1) {
+  Choice best{0, 1};
+  double best_us = 1e30, outputs = 0.0;
+  for (int i = 0; i < count; ++i) outputs += (double)Ms[i] * Ns[i];
+  for (int tile = 128; tile >= least_tile; tile /= 2) {
+    int64_t tiles = 0;
+    for (int i = 0; i < count; ++i) tiles += (int64_t)((Ms[i] + tile - 1) / tile) * ((Ns[i] + tile - 1) / tile);
     for (int parts = 1; parts <= 16; parts *= 2) {
-      if (parts > 1 && (!may_split || K / parts < 256 || (double)parts * M * N > (double)split_floats)) break;
+      if (parts > 1 && (!may_split || K / parts < 256 || parts * outputs > (double)split_floats)) break;
+      if (parts < least_parts) continue;
       const int64_t items = tiles * parts;
       const double n = (double)((items + 255) / 256), k = (double)K / parts;
       double us;
@@ -549,7 +578,7 @@ Choice choose(GemmLayout lay, int M, int N, int K, bool may_split, size_t split_
         const double pair = 2 * (1.9 + 0.48 * k / 32), rounds = items / 512.0;
         us = 3.0 + (rounds <= 1 ? pair : rounds <= 1.5 ? pair + 1.9 + 0.85 * k / 32 : rounds <= 2 ? 2 * pair : pair * (rounds + 0.25));
       }
-      if (parts > 1) us += 3.5 + (parts + 1.0) * M * N * 8.0 / 6e6;
+      if (parts > 1) us += 3.5 + (parts + 1.0) * outputs * 8.0 / 6e6;
       if (us < best_us) { best_us = us; best = {tile, parts}; }
     }
   }
@@ -559,7 +588,7 @@ Choice choose(GemmLayout lay, int M, int N, int K, bool may_split, size_t split_
 }  // namespace
 
 void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
-  Choice ch = choose(lay, M, N, K, may_split && !ctx->gemm_tile, split_floats);
+  Choice ch = choose(lay, 1, &M, &N, K, may_split && !ctx->gemm_tile, split_floats);
   if (ctx->gemm_tile) ch = {ctx->gemm_tile == 128 ? 128 : 64, 1};
   const int bk = ch.tile == 128 ? 32 : 64;
   kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
@@ -593,4 +622,36 @@ twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int 
   TW_HIP(ctx, hipGetLastError());
   if (parts > 1) return twist_splitk_reduce(ctx, st, e.splitk_ws, parts, M, N, e.out, ldc, 1, e.alpha);
   return TWIST_OK;
+}
+
+// A common launch is no coarser in its sums than the launches it replaces: a part of the contraction is no longer than the shortest of
+// theirs, and tiles are of 32 (on the fp32 instruction, whose error is the greater one) only where all of theirs are.  280 x 1120 and
+// 1120 x 280 over 1636 rows on tiles of 32: error 3.7e-7 instead of 1.9e-7.  False where the scratch does not hold that many parts.
+bool twist_gemm_f32_group_choice(int n, const int *Ms, const int *Ns, int K, size_t split_floats, int &tile, int &parts, int &kchunk) {
+  int least_tile = 32, least_parts = 1;
+  for (int i = 0; i < n; ++i) {
+    const Choice c = choose(GEMM_TN, 1, Ms + i, Ns + i, K, split_floats > 0, split_floats);
+    least_tile = std::max(least_tile, std::min(c.tile, 64));
+    least_parts = std::max(least_parts, c.parts);
+  }
+  const Choice ch = choose(GEMM_TN, n, Ms, Ns, K, split_floats > 0, split_floats, least_tile, least_parts);
+  if (!ch.tile) return false;
+  const int bk = ch.tile == 128 ? 32 : 64;
+  kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
+  tile = ch.tile;
+  parts = (K + kchunk - 1) / kchunk;
+  return true;
+}
+
+void twist_launch_gemm_f32_group(hipStream_t st, int tile, int n, const F32Product *products, int tiles, int K, int parts, int kchunk) {
+  F32Group g{};
+  g.n = n;
+  for (int i = 0; i < n; ++i) g.p[i] = products[i];
+  const Ep32 ep{1.f, nullptr, nullptr, nullptr, 0};
+#define TW_F32G(BM, BK) hipLaunchKernelGGL((gemm_f32_kernel<0, 0, BM, 2, 2, BK, 1, F32Group>), dim3(tiles, parts), dim3(512), 0, st, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, kchunk, g)
+  if (tile == 128) TW_F32G(128, 32);
+  else if (tile == 64 && (int64_t)tiles * parts <= 256) TW_F32G(64, 64);
+  else if (tile == 64) TW_F32G(64, 32);
+  else hipLaunchKernelGGL((gemm_f32_small_kernel<0, 0, 1, F32Group>), dim3(tiles, parts), dim3(256), 0, st, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, kchunk, g);
+#undef TW_F32G
 }

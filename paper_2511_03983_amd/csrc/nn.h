@@ -69,6 +69,17 @@ twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int 
                             int64_t ldc, const GemmEpilogue &e);
 // its tile, number of parts of the contraction and length of a part
 void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk);
+// weight gradients in fp32 that share a launch (aligned operands; `first`: number of a product's first tile; out: part 0 of a cut contraction): the choice
+// as above (false: none that sums as finely as separate launches), and the launch
+struct F32Product {
+  const float *a, *b;
+  float *out;
+  int64_t lda, ldb;
+  int M, N, first, tiles_m, tiles_n;
+  float alpha;
+};
+bool twist_gemm_f32_group_choice(int n, const int *Ms, const int *Ns, int K, size_t split_floats, int &tile, int &parts, int &kchunk);
+void twist_launch_gemm_f32_group(hipStream_t st, int tile, int n, const F32Product *products, int tiles, int K, int parts, int kchunk);
 twist_status twist_splitk_reduce(twist_ctx *ctx, hipStream_t st, const float *parts_ws, int parts, int M, int N, void *out, int64_t ldc, int out_f32,
                                  float alpha);
 

@@ -317,6 +317,37 @@ def test_weight_gradients_in_two_groups(lib, tile, cut, K, shapes):
         assert torch.isnan(buf[out.numel():]).all()
 
 
+# fp32 weight gradients in one launch, on every tile, whole and cut: odd sizes (partial products that leave the next product's unaligned), an empty one; then
+# rows that are not 16-byte aligned, and contractions of a few elements: one by one
+@pytest.mark.parametrize("tile,cut,K,shapes", [(32, False, 100, [(33, 41), (70, 36), (131, 40), (8, 33)]), (32, True, 1249, [(88, 345), (344, 87), (88, 833), (0, 8)]),
+                                               (64, False, 1100, [(360, 1127), (1128, 360)]), (64, True, 3337, [(176, 351), (353, 176), (176, 320), (961, 176)]),
+                                               (128, False, 321, [(752, 2400), (2401, 751)])])
+def test_fp32_weight_gradients_in_one_launch(lib, tile, cut, K, shapes):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    rows = lambda n: torch.randn((K, (n + 3) // 4 * 4), generator=gen, device="cuda")[:, :n]
+    alphas = (0.5, 1.0, 2.0, 1.0)[:len(shapes)]
+    scratch = torch.full((1 << 24,), float("nan"), device="cuda")
+    bufs = [torch.full((M * N + 64,), float("nan"), device="cuda") for M, N in shapes]
+    products = [(rows(M), rows(N), buf[:M * N].view(M, N)) for (M, N), buf in zip(shapes, bufs)]
+    r, _, parts = ctx.twist_weight_grads_raw(K, products, scratch, alphas)
+    torch.cuda.synchronize()
+    assert r == tile and (parts > 1) == cut, (r, parts)
+    for (a, b, out), buf, alpha in zip(products, bufs, alphas):
+        want = alpha * (a.double().T @ b.double())
+        # fp32 sums of K products, 2^-24 sqrt(K) at most; one left out or counted twice shows as 1 / sqrt(K)
+        assert out.numel() == 0 or float(((out.double() - want).norm(dim=1) / want.norm(dim=1)).max()) <= 2.0 ** -24 * K ** 0.5
+        assert torch.isnan(buf[out.numel():]).all()
+    assert torch.isnan(scratch[parts * sum(M * N for M, N in shapes) if cut else 0:]).all()
+    a, b, out = products[0]
+    for x, y in ((a[:, 1:], b), (a[:5], b[:5])):
+        one = torch.empty((x.shape[1], y.shape[1]), device="cuda"), torch.empty((x.shape[1], y.shape[1]), device="cuda")
+        assert ctx.twist_weight_grads_raw(x.shape[0], [(x, y, one[0]), (x, y, one[1])], scratch, (1.0, 0.5)) == (0, 0, 0)
+        torch.cuda.synchronize()
+        want = x.double().T @ y.double()
+        assert torch.equal(one[0] * 0.5, one[1]) and float((one[0].double() - want).norm() / want.norm()) <= 2.0 ** -24 * K ** 0.5
+
+
 # the up projection with its activation: the projection's bits and the activation kernel's of them, on every tile and on the plain kernel, with and without the
 # projection itself
 @pytest.mark.parametrize("act", ["gelu_tanh", "relu"])
