@@ -503,13 +503,16 @@ void launch_pp(hipStream_t st, GemmLayout lay, int M, int N, int K, const uint16
 #undef TW_PP
 }
 
+// fp32 operands without padding have rows of whole 16-byte chunks
+bool dense_rows_of_16(GemmLayout lay, int M, int N, int K) { return (lay == GEMM_TN ? M : K) % 4 == 0 && (lay == GEMM_NT ? K : N) % 4 == 0; }
+
 // fp32 contractions within one slice of the plain kernel, with an output too large for the 32x32 tiles: bound by the stores, of which the
 // plain kernel makes shorter work (us, plain / matrix instruction: 8192 x 2048 x 8 32 / 41, 512 x 50257 x 16 50 / 71, 3072 x 768 x 8 (TN)
 // 9.9 / 13.8; from there on the other way: 8192 x 2048 x 32 40 / 38, 4096 x 4096 x 16 (TN) 41 / 37, 768 x 768 x 8 6.2 / 5.2).
 bool short_f32(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K) {
   if (K > (lay == GEMM_TN ? 8 : 16) || ctx->gemm_tile) return false;
   int tile, parts, kchunk;
-  twist_gemm_f32_choice(ctx, lay, M, N, K, false, 0, tile, parts, kchunk);
+  twist_gemm_f32_choice(ctx, lay, M, N, K, dense_rows_of_16(lay, M, N, K), false, 0, tile, parts, kchunk);
   return tile > 32;
 }
 
@@ -767,7 +770,7 @@ static twist_status tile_query(const char *who, bool any, twist_ctx *ctx, int32_
     chosen[0] = chosen[1] = 0; chosen[2] = 1;
   } else {
     int kchunk;
-    twist_gemm_f32_choice(ctx, (GemmLayout)layout, M, N, K, scratch_floats > 0, scratch_floats, chosen[0], chosen[2], kchunk);
+    twist_gemm_f32_choice(ctx, (GemmLayout)layout, M, N, K, dense_rows_of_16((GemmLayout)layout, M, N, K), scratch_floats > 0, scratch_floats, chosen[0], chosen[2], kchunk);
     chosen[1] = chosen[0];
   }
   return TWIST_OK;

@@ -1,6 +1,6 @@
 // Dense projections of fp32 models on the matrix cores.
 //
-// Tiles of 128 and 64: gemm_f32_kernel, on the bf16 instruction (v_mfma_f32_32x32x16_bf16, sixteen times the rate of the fp32 one).  An fp32
+// Tiles of 128 and 64: gemm_f32_kernel and gemm_f32_wave_kernel, on the bf16 instruction (v_mfma_f32_32x32x16_bf16, sixteen times the rate of the fp32 one).  An fp32
 // value is the sum of three bf16 values (8 bits each, rounded to nearest, the last one exactly what is left), a product of two bf16 values is exact in
 // fp32, and of the nine products of two such sums the six largest are formed.  What is left out of a product is 2^-28 of it on average over
 // operands of random bits and at most about 2^-24 (0.99 of that for the square of 1 + 2^-8 - 2^-17), one rounding of fp32.  The sums run in fp32 as
@@ -13,38 +13,38 @@
 // Tiles of 32, for few rows: gemm_f32_small_kernel, on the fp32 instruction (v_mfma_f32_32x32x2_f32): there every value would be split into
 // its terms for 32 products only.
 //
-// Both: four or eight waves, the contraction walked in slices of BK that are double-buffered in LDS, one barrier per slice.  The waves
-// divide the tile, and (WK) the slice: their results are added in wave order at the end.
+// gemm_f32_wave_kernel, tiles of 64 whose operands allow 16-byte loads.  What bounded such tiles in gemm_f32_kernel was neither the matrix
+// pipes nor the loads but LDS and what it is fed with: three terms of 2 bytes written and, by waves of 32x32, read twice, a barrier for every
+// slice, and two waves a SIMD in step (1.2 us per slice of 64 where the instructions take 0.35 and forming the terms 0.47).  Here every wave forms
+// the whole tile over steps of 16 k of its own, so that
+//  - no two waves need the same element: it crosses LDS once, as fp32, and its terms are formed in the registers that multiply it;
+//  - there is no barrier before the waves' sums are added at the end: while one wave of a SIMD forms terms the other multiplies;
+//  - a wave's next two steps are in flight, loaded straight to LDS in whole pieces of rows (a first form that loaded the fragments into
+//    registers spent its time on the addresses of 32 rows per load: 1024 x 768 x 1536 48 us).
+// Its chains are an eighth (a quarter) of the contraction long, and the error is smaller: K = 768 0.9e-7 (gemm_f32_kernel 1.1e-7), 4096 (TN) 1.9e-7
+// (2.7e-7), 50257 whole 5.0e-7 (10e-7).  us, before / now: 1024 x 768 x 1536 32.1 / 23.6, its NN form 35.3 / 23.8, 1152 x 768 x 1024 (TN) 25.2 / 18.8,
+// 1024 x 1536 x 768 31.6 / 25.5, 1536 x 768 x 1024 (TN) 37.7 / 27.5, 8192 x 768 x 768 89 / 78, 3072 x 768 x 8192 (TN) 330 / 262, 1024 x 768 x 50257 (NN, cut)
+// 580 / 490.  What bounds it: small products the fixed 6 us (launch 2, first loads 2, sums and stores 2), large ones the power limit: 4096^3 797 us
+// against 830 in tiles of 128 on the same card.
+//
+// gemm_f32_kernel and gemm_f32_small_kernel: four or eight waves, the contraction walked in slices of BK that are double-buffered in LDS, one
+// barrier per slice.  The waves divide the tile, and (WK) the slice: their results are added in wave order at the end.
 // gemm_f32_kernel: three slices are in flight to registers; their terms are formed on the way to LDS, in the orientation of the memory:
 //   k contiguous ("KM"): [rows][BK + 8], plain 16-byte fragment reads;      rows contiguous: [BK][rows + 16], transposing reads.
 // gemm_f32_small_kernel: one slice in flight;
 //   k contiguous: LDS [rows][BK + 4], a lane reads 4 consecutive k at once, good for four MFMAs;      rows contiguous: [BK][rows + 8].
 //   MFMA number 4 u + j of a slice contracts k = 8 u + j (lanes 0-31) and 8 u + 4 + j (lanes 32-63): the order of k inside a slice
 //   is free as long as both operands agree.  Both paddings make the reads conflict-free.
-// Measured, us (before: the fp32 instruction in all tiles): 4096^3 805 (1107), 4096 x 2048 x 2048 222 (286), 1024 x 50257 x 768 595 (741) and its
-// gradients 580 (735) and 555 (699), 8192 x 768 x 768 89 (103), 1024 x 1536 x 768 30 (37), 1152 x 768 x 1024 (TN) 25 (30).  What bounds the large
-// ones is the rate of the bf16 instruction at the power limit (six of them per product: 1.04 PFLOP/s in 4096^3), the small ones the chain of slices.
-// Strides and bases that do not allow 16-byte loads go through the scalar loader (VEC = 0).
+// Measured, us (before: the fp32 instruction in all tiles), tiles of 128: 4096^3 805 (1107), 4096 x 2048 x 2048 222 (286), 1024 x 50257 x 768 595 (741): the rate
+// of the bf16 instruction at the power limit (six of them per product: 1.04 PFLOP/s in 4096^3).
+// Strides and bases that do not allow 16-byte loads go through the scalar loader (VEC = 0), in tiles of 64 too.
 #include <algorithm>
 #include <type_traits>
 
-#include "nn.h"
+#include "gemm_tile.h"
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {  // round to nearest even
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const f32x2 v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
 constexpr float kUp = 65536.f, kDown = 1.f / (kUp * kUp);  // factor of the terms, and what takes it out of a sum of their products
 // four floats as three vectors of bf16 that add up to kUp times them exactly (an infinity, a NaN or what overflows gives a NaN)
 __device__ __forceinline__ void split(f32x4 v, u32x2 (&t)[3]) {
@@ -232,7 +232,6 @@ struct F32Group {
   int n;
   F32Product p[kGroupProducts];
 };
-struct NoGroup {};
 template <class G>
 __device__ __forceinline__ void take_product(const G &group, int &bid, int &M, int &N, const float *&A, int64_t &lda, const float *&B, int64_t &ldb, Ep32 &ep,
                                              int &tiles_m, int &tiles_n) {
@@ -434,6 +433,205 @@ __global__ __launch_bounds__(64 * W2 * W2 * WK) void gemm_f32_kernel(int M, int 
   }
 }
 
+// One operand's 64 rows x 16 k of a wave's step: brought into the wave's own part of LDS as they lie in memory, and read back as fragments.
+//   k contiguous: [64 rows][4 chunks of 16 bytes], position p of row r holds chunk p ^ (r / 4) % 4;      rows contiguous: [16 k][64]
+template <int KM>
+struct Step {
+  static constexpr int BYTES = 4096, NP = BYTES / 1024;  // loads of a step
+  const float *base;  // the wave's next step: first row of the panel (KM) or first column (otherwise) at its first k
+  int64_t ld, step;   // floats from one step of the wave to its next
+  int rows;
+  f32x4 v[2][2];      // lane (g = lane / 32, c = lane % 32): rows c and 32 + c, k = 8 g .. 8 g + 7
+  __device__ __forceinline__ void init(const float *base_, int64_t ld_, int rows_left, int waves) {
+    base = base_;
+    ld = ld_;
+    rows = min(rows_left, 64);
+    step = (KM ? 1 : ld) * 16 * waves;
+  }
+  // start the loads of the next step into st (wave-uniform); k_left > 0: k from its first to the end of the contraction.  Rows (and k, where
+  // rows are contiguous) beyond the last lie beyond the buffer's range and come as zeros.  The range ends with a whole chunk: it is aligned
+  // and holds at least one element of the operand.
+  __device__ __forceinline__ void issue(char *st, int k_left) {
+    const int lane = threadIdx.x & 63, up = ((KM ? k_left : rows) + 3) / 4 * 4;
+    const desc_t d = make_desc(base, (uint32_t)((((KM ? rows : min(k_left, 16)) - 1) * ld + up) * 4));
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int major = KM ? 16 * i + (lane >> 2) : 4 * i + (lane >> 4), minor = KM ? ((lane & 3) ^ (lane >> 4 & 3)) * 4 : (lane & 15) * 4;
+      dma16(d, st + i * 1024, (uint32_t)((major * ld + minor) * 4));
+    }
+    base += step;
+  }
+  __device__ __forceinline__ void read(const char *st, int k_left) {
+    const int lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (KM) {
+          v[i][h] = *reinterpret_cast<const f32x4 *>(st + (32 * i + c) * 64 + (((2 * g + h) ^ (c >> 2 & 3)) << 4));
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[i][h][e] = *reinterpret_cast<const float *>(st + ((8 * g + 4 * h + e) * 64 + 32 * i + c) * 4);
+        }
+      }
+    // what a load brought in beside the operand's own
+    if (KM ? k_left < 16 : rows < 64) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[i][h][e] = (KM ? 8 * g + 4 * h + e < k_left : 32 * i + c < rows) ? v[i][h][e] : 0.f;
+    }
+  }
+  // the three terms of the 32 rows i
+  __device__ __forceinline__ void terms(int i, bf16x8 (&t)[3]) const {
+    u32x2 a[3], b[3];
+    split(v[i][0], a);
+    split(v[i][1], b);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t[k] = __builtin_bit_cast(bf16x8, u32x4{a[k].x, a[k].y, b[k].x, b[k].y});
+  }
+};
+
+// Tiles of 64 x 64: every wave forms the whole tile over steps of 16 k of its own (w, w + NW, ...).  One tile per CU: eight waves; more: four,
+// two workgroups to a CU.  Grid as in gemm_f32_kernel.
+template <int AKM, int BKM, int NW, class G = NoGroup>
+__global__ __launch_bounds__(64 * NW, 2) void gemm_f32_wave_kernel(int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, Ep32 ep, int tiles_m,
+                                                                   int tiles_n, int kchunk, G group) {
+  __shared__ __attribute__((aligned(1024))) f32x4 part[NW][16][64];  // a wave's two steps on their way, and its sums at the end
+  const int nb = tiles_m * tiles_n;
+  int bid = blockIdx.x;
+  if (nb % 8 == 0) bid = (bid % 8) * (nb / 8) + bid / 8;
+  take_product(group, bid, M, N, A, lda, B, ldb, ep, tiles_m, tiles_n);
+  constexpr int GROUP = 8;
+  const int per_group = GROUP * tiles_n;
+  const int grp = bid / per_group, first_m = grp * GROUP;
+  const int gsize = min(GROUP, tiles_m - first_m);
+  const int m0 = (first_m + (bid % per_group) % gsize) * 64, n0 = ((bid % per_group) / gsize) * 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int kend = min(K, (int)(blockIdx.y + 1) * kchunk), kfirst = blockIdx.y * kchunk + 16 * wave;
+  const float *pa = AKM ? A + (int64_t)m0 * lda + kfirst : A + (int64_t)kfirst * lda + m0, *pb = BKM ? B + (int64_t)n0 * ldb + kfirst : B + (int64_t)kfirst * ldb + n0;
+  Step<AKM> a;
+  Step<BKM> b;
+  constexpr int STAGE = a.BYTES + b.BYTES, LPS = a.NP + b.NP;
+  static_assert(2 * STAGE == sizeof(part[0]), "two steps in flight");
+  char *const own = reinterpret_cast<char *>(part[wave]);
+  a.init(pa, lda, M - m0, NW);
+  b.init(pb, ldb, N - n0, NW);
+  auto issue = [&](int slot, int k) {
+    a.issue(own + slot * STAGE, kend - k);
+    b.issue(own + slot * STAGE + a.BYTES, kend - k);
+  };
+  auto read = [&](int slot, int k) {
+    a.read(own + slot * STAGE, kend - k);
+    b.read(own + slot * STAGE + a.BYTES, kend - k);
+  };
+
+  f32x16 acc[2][2], low[2][2];  // the sums of the largest products, and of the others: fewer roundings at the size of the result
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.f; low[i][j][r] = 0.f; }
+  if (kfirst < kend) issue(0, kfirst);
+  if (kfirst + 16 * NW < kend) issue(1, kfirst + 16 * NW);
+  int slot = 0;
+#pragma unroll 1
+  for (int k = kfirst; k < kend; k += 16 * NW, slot ^= 1) {
+    if (k + 16 * NW < kend) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    read(slot, k);
+    bf16x8 ta[2][3], tb[2][3];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      a.terms(i, ta[i]);
+      b.terms(i, tb[i]);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the step is in registers: its place is free
+    if (k + 32 * NW < kend) issue(slot, k + 32 * NW);
+    __builtin_amdgcn_sched_barrier(0);
+    // the six largest of the nine products, small ones first
+#pragma unroll
+    for (int p = 0; p < 6; ++p) {
+      constexpr int pa_[6] = {2, 0, 1, 1, 0, 0}, pb_[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          f32x16 &to = p == 5 ? acc[i][j] : low[i][j];
+          to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ta[i][pa_[p]], tb[j][pb_[p]], to, 0, 0, 0);
+        }
+    }
+  }
+  bool finite = true;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc[i][j][r] += low[i][j][r];
+        finite = finite && __builtin_isfinite(acc[i][j][r]);
+        acc[i][j][r] *= kDown;
+      }
+  if (__syncthreads_or(!finite)) {
+    // as in gemm_f32_kernel: the tile is formed again on the fp32 instruction, whose product number 4 h + e of a step contracts k = 4 h + e
+    // (lanes 0-31) and 8 + 4 h + e (lanes 32-63)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    a.base = pa;
+    b.base = pb;
+#pragma unroll 1
+    for (int k = kfirst; k < kend; k += 16 * NW) {
+      issue(0, k);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      read(0, k);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[i][h][e], b.v[j][h][e], acc[i][j], 0, 0, 0);
+    }
+  }
+  // the waves' sums are added in wave order; each wave finishes 16 / NW of the groups of four registers.  Registers 4 q .. 4 q + 3 of tile
+  // (i, j): rows 32 i + 8 q + 4 g .. + 3, column 32 j + c
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) part[wave][(2 * i + j) * 4 + q][lane] = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+  __syncthreads();
+  float *out = ep.out + (int64_t)blockIdx.y * M * ep.ldc;
+#pragma unroll
+  for (int t = 0; t < 16 / NW; ++t) {
+    const int at = wave * (16 / NW) + t, m = m0 + 32 * (at >> 3) + 8 * (at & 3) + 4 * (lane >> 5), n = n0 + 32 * ((at >> 2) & 1) + (lane & 31);
+    f32x4 x = part[0][at][lane];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) x += part[w][at][lane];
+    if (n >= N) continue;
+    const float bias = ep.bias ? ep.bias[n] : 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (m + e >= M) break;
+      float v = (x[e] + bias) * ep.alpha;
+      const int64_t o = (int64_t)(m + e) * ep.ldc + n;
+      if (ep.residual) v += ep.residual[o];
+      out[o] = v;
+    }
+  }
+}
+
 // Grid: x = tiles (dealt so that each of the 8 XCDs walks a contiguous range, in columns of 8 tile rows), y = parts of the
 // contraction (kchunk long, a multiple of BK; part p writes its partial product to out + p M ldc).
 template <int AKM, int BKM, int VEC, class G = NoGroup>
@@ -534,9 +732,16 @@ template <int AKM, int BKM, int VEC>
 void launch_tile(hipStream_t st, int tile, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, const Ep32 &ep, int parts, int kchunk) {
   if (tile == 128) return launch<AKM, BKM, 128, 2, 2, 32, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
   if (tile == 64) {
-    // one tile per CU: slices of 64 (1024 x 768 x 1536 32 us, 44 in slices of 32); more: two workgroups to a CU (1024 x 1536 x 768 34 us, 30)
-    if ((int64_t)((M + 63) / 64) * ((N + 63) / 64) * parts <= 256) launch<AKM, BKM, 64, 2, 2, 64, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
-    else launch<AKM, BKM, 64, 2, 2, 32, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
+    const int tm = (M + 63) / 64, tn = (N + 63) / 64;
+    const bool one = (int64_t)tm * tn * parts <= 256;
+    if constexpr (VEC) {
+      if (one) hipLaunchKernelGGL((gemm_f32_wave_kernel<AKM, BKM, 8>), dim3(tm * tn, parts), dim3(512), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
+      else hipLaunchKernelGGL((gemm_f32_wave_kernel<AKM, BKM, 4>), dim3(tm * tn, parts), dim3(256), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
+    } else if (one) {  // slices of 64; more than one tile per CU: of 32, two workgroups to a CU
+      launch<AKM, BKM, 64, 2, 2, 64, 0>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
+    } else {
+      launch<AKM, BKM, 64, 2, 2, 32, 0>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
+    }
     return;
   }
   const int tm = (M + 31) / 32, tn = (N + 31) / 32;
@@ -545,17 +750,23 @@ void launch_tile(hipStream_t st, int tile, int M, int N, int K, const float *A, 
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// Tile and number of parts of the contraction, by estimated time of the kernels above (us).  128: n = tiles on the busiest of 256 CUs,
-// 3 + n (6 + 1.47 per slice of 32).  64: one tile a CU 4.3 + 1.2 per slice of 64; more run in pairs, 2 (1.9 + 0.48 per slice of 32), a single one
-// left over in the second round 1.9 + 0.85 per slice, and from then on the rounds run into each other.  32: 4 + 1.4 (n - 4, if more) + (0.2 + 0.36 n) per
-// slice of 64.  Rows contiguous in both operands (TN): an eighth more for tiles of 128, a sixth for single ones of 64.
-// Fitted to (measured; 128 / 64 / 32): 1024 x 768 x 384 25.6 / 11.4 / 11.9, 1024 x 1536 x 768 43 / 29.7 / -, 1152 x 768 x 1024 (TN) 56 / 25 / 38,
-// 1024 x 768 x 1536 76 / 32 / 33, 512 x 1536 x 768 - / 18.7 / 19.3, 256 x 1024 x 1024 - / 22 / 13, 4096^3 790 / 1083 / -, 1024 x 50257 x 768 586 / 713 / -,
-// 8192 x 2048 x 24 43 / 40 / 98; 1500 x 1500 x 2000 (TN) 118 / 129 / 112, in two parts 131 / 105 / 119, in four 109 / 104 / 122;
-// 1024 x 768 x 8003 (TN) 414 / 178 / 143, in four parts 120 / 140 / 147, in eight 131 / 124 / 150.
+// Tile and number of parts of the contraction, by estimated time of the kernels above (us); n = items (tiles, times parts) on the busiest of
+// 256 CUs.  Operands that allow 16-byte loads:
+//   128: 3 + n (8.4 + 1.55 per slice of 32)
+//   64: one a CU 6.3 + (0.55 to 0.77, the whole chip at work) per 64 of the contraction, two 7.4 + (1.2 to 1.55), from then on 4.5 + 2.05 n + 0.745 n,
+//   and 0.25 for an odd n, per 64
+//   32: 3.4 + 1.4 (n - 4, if more) + (0.2 + 0.355 n) per slice of 64
+//   sum of a cut one 4 + its bytes at 4.5 TB/s.
+// Fitted to 180 products of 48 to 8000 tiles of 64, K = 64 to 4096 (measured; 128 / 64 / 32): 1024 x 768 x 768 43.4 / 15.4 / -, 1024 x 1024 x 4096 186 / 61 / -,
+// 1024 x 1152 x 768 43.6 / 22.6 / 30.4, 2048 x 1024 x 1536 80 / 45 / -, 1536 x 1408 x 768 44.5 / 39.4 / -, 2048 x 2048 x 768 48.5 / 49.6 / -,
+// 4096 x 1536 x 768 90 / 70 / -, 4096 x 4096 x 64 48.9 / 47.6 / -, 4096^3 824 / 797 / -, 512 x 384 x 768 40 / 14 / 10.4; 1500 x 1500 x 2000 (TN) 117 / 93 / -, in two
+// parts 133 / 88 / 137, in four 113 / 92 / -; 1024 x 768 x 8000 - / 83 / -, in four parts 111 / 93 / -; 3072 x 768 x 8192 (TN) 396 / 332 / 417, in four 332 / 260 / -.
+// Others (64 in gemm_f32_kernel): 128 3 + n (6 + 1.47 per slice of 32); 64 one a CU 4.3 + 1.2 per slice of 64, more in pairs, 2 (1.9 + 0.48 per slice of 32),
+// a single one left over in the second round 1.9 + 0.85 per slice, and from then on the rounds run into each other; 32 as above.  Rows contiguous in
+// both operands (TN): an eighth more for tiles of 128, a sixth for single ones of 64.
 // Several products over the same K that share a launch: their tiles and outputs together.
 struct Choice { int tile, parts; };
-Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bool may_split, size_t split_floats, int least_tile = 32, int least_parts = 1) {
+Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bool vec, bool may_split, size_t split_floats, int least_tile = 32, int least_parts = 1) {
   Choice best{0, 1};
   double best_us = 1e30, outputs = 0.0;
   for (int i = 0; i < count; ++i) outputs += (double)Ms[i] * Ns[i];
@@ -568,17 +779,22 @@ Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bo
       const int64_t items = tiles * parts;
       const double n = (double)((items + 255) / 256), k = (double)K / parts;
       double us;
-      if (tile == 128) {
+      if (tile == 128 && vec) {
+        us = 3.0 + n * (8.4 + 1.55 * k / 32);
+      } else if (tile == 128) {
         us = 3.0 + n * (6.0 + (lay == GEMM_TN ? 1.65 : 1.47) * k / 32);
       } else if (tile == 32) {
-        us = 4.0 + 1.4 * std::max(n - 4.0, 0.0) + (0.2 + 0.36 * n) * k / 64;
+        us = (vec ? 3.4 : 4.0) + 1.4 * std::max(n - 4.0, 0.0) + (0.2 + (vec ? 0.355 : 0.36) * n) * k / 64;
+      } else if (vec) {
+        us = n == 1 ? 6.3 + (0.55 + 0.22 * items / 256) * k / 64 : n == 2 ? 7.4 + (0.9 + 0.65 * items / 512) * k / 64
+                    : 4.5 + 2.05 * n + (0.745 * n + ((int64_t)n % 2 ? 0.25 : 0.0)) * k / 64;
       } else if (n == 1) {
         us = 4.3 + (lay == GEMM_TN ? 1.38 : 1.2) * k / 64;
       } else {
         const double pair = 2 * (1.9 + 0.48 * k / 32), rounds = items / 512.0;
         us = 3.0 + (rounds <= 1 ? pair : rounds <= 1.5 ? pair + 1.9 + 0.85 * k / 32 : rounds <= 2 ? 2 * pair : pair * (rounds + 0.25));
       }
-      if (parts > 1) us += 3.5 + (parts + 1.0) * outputs * 8.0 / 6e6;
+      if (parts > 1) us += vec ? 4.0 + (parts + 1.0) * outputs * 4.0 / 4.5e6 : 3.5 + (parts + 1.0) * outputs * 8.0 / 6e6;
       if (us < best_us) { best_us = us; best = {tile, parts}; }
     }
   }
@@ -587,8 +803,8 @@ Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bo
 
 }  // namespace
 
-void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
-  Choice ch = choose(lay, 1, &M, &N, K, may_split && !ctx->gemm_tile, split_floats);
+void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool vec, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
+  Choice ch = choose(lay, 1, &M, &N, K, vec, may_split && !ctx->gemm_tile, split_floats);
   if (ctx->gemm_tile) ch = {ctx->gemm_tile == 128 ? 128 : 64, 1};
   const int bk = ch.tile == 128 ? 32 : 64;
   kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
@@ -601,7 +817,7 @@ twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int 
   Ep32 ep{e.alpha, static_cast<const float *>(e.bias), e.residual, static_cast<float *>(e.out), ldc};
   const bool vec = aligned16(A) && aligned16(B) && lda % 4 == 0 && ldb % 4 == 0;
   int tile, parts, kchunk;
-  twist_gemm_f32_choice(ctx, lay, M, N, K, e.splitk_ws && !e.bias && !e.residual, e.splitk_floats, tile, parts, kchunk);
+  twist_gemm_f32_choice(ctx, lay, M, N, K, vec, e.splitk_ws && !e.bias && !e.residual, e.splitk_floats, tile, parts, kchunk);
   if (tile != 32 && std::max(lda, ldb) >= 1 << 23) {  // a slice of such rows exceeds the larger tiles' 32-bit offsets
     tile = 32;
     kchunk = (kchunk + 63) / 64 * 64;
@@ -630,11 +846,11 @@ twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int 
 bool twist_gemm_f32_group_choice(int n, const int *Ms, const int *Ns, int K, size_t split_floats, int &tile, int &parts, int &kchunk) {
   int least_tile = 32, least_parts = 1;
   for (int i = 0; i < n; ++i) {
-    const Choice c = choose(GEMM_TN, 1, Ms + i, Ns + i, K, split_floats > 0, split_floats);
+    const Choice c = choose(GEMM_TN, 1, Ms + i, Ns + i, K, true, split_floats > 0, split_floats);
     least_tile = std::max(least_tile, std::min(c.tile, 64));
     least_parts = std::max(least_parts, c.parts);
   }
-  const Choice ch = choose(GEMM_TN, n, Ms, Ns, K, split_floats > 0, split_floats, least_tile, least_parts);
+  const Choice ch = choose(GEMM_TN, n, Ms, Ns, K, true, split_floats > 0, split_floats, least_tile, least_parts);
   if (!ch.tile) return false;
   const int bk = ch.tile == 128 ? 32 : 64;
   kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
@@ -649,9 +865,11 @@ void twist_launch_gemm_f32_group(hipStream_t st, int tile, int n, const F32Produ
   for (int i = 0; i < n; ++i) g.p[i] = products[i];
   const Ep32 ep{1.f, nullptr, nullptr, nullptr, 0};
 #define TW_F32G(BM, BK) hipLaunchKernelGGL((gemm_f32_kernel<0, 0, BM, 2, 2, BK, 1, F32Group>), dim3(tiles, parts), dim3(512), 0, st, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, kchunk, g)
+#define TW_F32W(NW) hipLaunchKernelGGL((gemm_f32_wave_kernel<0, 0, NW, F32Group>), dim3(tiles, parts), dim3(64 * NW), 0, st, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, kchunk, g)
   if (tile == 128) TW_F32G(128, 32);
-  else if (tile == 64 && (int64_t)tiles * parts <= 256) TW_F32G(64, 64);
-  else if (tile == 64) TW_F32G(64, 32);
+  else if (tile == 64 && (int64_t)tiles * parts <= 256) TW_F32W(8);
+  else if (tile == 64) TW_F32W(4);
   else hipLaunchKernelGGL((gemm_f32_small_kernel<0, 0, 1, F32Group>), dim3(tiles, parts), dim3(256), 0, st, 0, 0, K, nullptr, 0, nullptr, 0, ep, tiles, 1, kchunk, g);
+#undef TW_F32W
 #undef TW_F32G
 }

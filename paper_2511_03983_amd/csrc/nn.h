@@ -67,8 +67,8 @@ void twist_launch_gemm_kp_group(hipStream_t st, int bm, int bn, const void *grou
 // (out = alpha * sum in ascending order)
 twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
                             int64_t ldc, const GemmEpilogue &e);
-// its tile, number of parts of the contraction and length of a part
-void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk);
+// its tile, number of parts of the contraction and length of a part (vec: bases and strides allow 16-byte loads)
+void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool vec, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk);
 // weight gradients in fp32 that share a launch (aligned operands; `first`: number of a product's first tile; out: part 0 of a cut contraction): the choice
 // as above (false: none that sums as finely as separate launches), and the launch
 struct F32Product {

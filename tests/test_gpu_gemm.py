@@ -167,6 +167,33 @@ def test_fp32_projection_of_tiny_operands(lib, tile, layout, up, down):
         assert float((out.double() - want).norm() / want.norm()) <= 2.0 ** -24 * K ** 0.5
 
 
+# tiles of 64 whose rows are padded to 16 bytes, NaNs in the padding: contractions that end at and beside a wave's step of 16 and the waves' round of
+# 64 or 128, rows and columns that end inside a tile; one tile per CU (eight waves) and more (four)
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 1), (1, 3, 17), (65, 63, 15), (127, 130, 16), (193, 62, 127), (66, 64, 128), (64, 129, 131), (61, 190, 525),
+                                   (1089, 1027, 50), (1100, 1026, 64), (1027, 1089, 67), (1030, 1091, 243)])
+def test_fp32_projection_leaves_padding_out(lib, layout, M, N, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    ctx.twist_set_kernel_choice(gemm_tile=256)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+
+    def padded(rows, cols):
+        x = torch.full((rows, (cols + 3) // 4 * 4), float("nan"), device="cuda")
+        x[:, :cols] = torch.randn((rows, cols), generator=gen, device="cuda")
+        return x[:, :cols]
+    A, B = padded(*((K, M) if layout == 2 else (M, K))), padded(*((N, K) if layout == 0 else (K, N)))
+    want = (A.double().T if layout == 2 else A.double()) @ (B.double().T if layout == 0 else B.double())
+    buf = torch.full((M * N + 64,), float("nan"), device="cuda")
+    out = buf[:M * N].view(M, N)
+    ctx.twist_gemm_raw(layout, M, N, K, A, B, out, alpha=0.5)
+    torch.cuda.synchronize()
+    # K products of one rounding each and K additions against the sum of the products' sizes; a product left out or counted twice is 1 / K of that on
+    # average, and more than 10 times the bound
+    size = (A.double().abs().T if layout == 2 else A.double().abs()) @ (B.double().abs().T if layout == 0 else B.double().abs())
+    assert float(((out.double() - 0.5 * want).abs() / (0.5 * size)).max()) <= 2.0 ** -24 * (K + 2)
+    assert torch.isnan(buf[M * N:]).all()
+
+
 # a tile that an infinity or a NaN reaches is formed a second time, on the fp32 instruction (measured: twice as long in all).  A loop over k
 # per output in its place took 34 to 115 times as long
 @pytest.mark.parametrize("layout,M,N,K", [(0, 1024, 20000, 768), (0, 1024, 1536, 768), (1, 1024, 768, 1536), (2, 2048, 2048, 768)])
