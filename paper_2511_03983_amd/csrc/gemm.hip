@@ -512,7 +512,7 @@ bool dense_rows_of_16(GemmLayout lay, int M, int N, int K) { return (lay == GEMM
 bool short_f32(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K) {
   if (K > (lay == GEMM_TN ? 8 : 16) || ctx->gemm_tile) return false;
   int tile, parts, kchunk;
-  twist_gemm_f32_choice(ctx, lay, M, N, K, dense_rows_of_16(lay, M, N, K), false, 0, tile, parts, kchunk);
+  twist_gemm_f32_choice(ctx, lay, M, N, K, false, false, 0, tile, parts, kchunk);  // (measured against those kernels; K is a step of any)
   return tile > 32;
 }
 
