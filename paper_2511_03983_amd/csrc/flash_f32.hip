@@ -2,9 +2,9 @@
 // d_head a multiple of 4 up to 128, any N: for fp32 models, and (BF) for the bf16 models whose heads are not 32, 64 or 128 wide or whose batch
 // element exceeds 2 GiB (flash64.hip): operands and results are bf16 there, probabilities and score gradients stay fp32.
 //
-// A workgroup owns 32 query rows (forward, dQ) or 32 key rows (dK / dV) of one head; its four waves share out the tiles of 32 keys
-// (or queries) that those rows see, wave w taking tiles w, w + 4, ..., each with accumulators of its own, and the four results are
-// added in wave order through LDS at the end.  That gives N / 32 workgroups per head, each a quarter as long as one wave would be:
+// A workgroup owns 32 query rows (forward, dQ) or 32 key rows (dK / dV) of one head; its four or eight (NW) waves share out the tiles of 32 keys
+// (or queries) that those rows see, wave w taking tiles w, w + NW, ..., each with accumulators of its own, and the results are
+// added in wave order through LDS at the end.  That gives N / 32 workgroups per head, each a quarter or less as long as one wave would be:
 // these models are small, and what bounds the kernels is the chain of dependent steps and how many waves there are, then the
 // matrix pipes (64 cycles per instruction).  Operands go from global memory to registers: waves share no tile, and a head's keys
 // and values stay in the L2.
@@ -80,6 +80,14 @@ __device__ __forceinline__ f32x16 dot_tile(const f32x4 (&a)[DH / 8], const f32x4
     for (int e = 0; e < 4; ++e) s[e % CH] = MFMA(a[u][e], b[u][e], s[e % CH]);
   return CH == 4 ? (s[0] + s[1 % CH]) + (s[2 % CH] + s[3 % CH]) : CH == 2 ? s[0] + s[1 % CH] : s[0];
 }
+// the same with this lane's column in LDS (its group u at b + 8 u)
+template <int DH, int CH>
+__device__ __forceinline__ f32x16 dot_tile(const f32x4 (&a)[DH / 8], const float *b) {
+  f32x4 f[DH / 8];
+#pragma unroll
+  for (int u = 0; u < DH / 8; ++u) f[u] = get4(b + 8 * u);
+  return dot_tile<DH, CH>(a, f);
+}
 // acc[i] += X^T[32 i ..][rows] w[rows][column]: X rows row0 .. row0 + 31 (those beyond N are taken as zero), w in accumulator layout.
 // `diag`: the tile lies on the diagonal, where a column does not see every row.  Hidden entries have weight zero, but zero times an
 // infinity or a NaN is a NaN, and it must not reach a column that never reads that row: such values are left out here, and if
@@ -144,9 +152,9 @@ __device__ __forceinline__ void zero(f32x16 (&acc)[DH / 32]) {
     for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
 }
 
-// Sum of the four waves' [dh][32] accumulators (each multiplied by its lane's `mul`) written as rows of `out` (stride ld) and, where it is
+// Sum of the NW waves' [dh][32] accumulators (each multiplied by its lane's `mul`) written as rows of `out` (stride ld) and, where it is
 // given, unrounded to out32
-template <int DH, class T>
+template <int DH, int NW, class T>
 __device__ __forceinline__ void merge(float *lds, const f32x16 (&acc)[DH / 32], float mul, T *out, float *out32, int64_t ld, int rows_left, int dh, int wave, int c, int g) {
   constexpr int LDR = DH + 4;
 #pragma unroll
@@ -156,12 +164,13 @@ __device__ __forceinline__ void merge(float *lds, const f32x16 (&acc)[DH / 32], 
       *reinterpret_cast<f32x4 *>(lds + (wave * 32 + c) * LDR + 32 * i + 8 * j + 4 * g) =
           f32x4{acc[i][4 * j] * mul, acc[i][4 * j + 1] * mul, acc[i][4 * j + 2] * mul, acc[i][4 * j + 3] * mul};
   __syncthreads();
-  const int row = threadIdx.x >> 3;
+  constexpr int TPR = 2 * NW;  // threads per row
+  const int row = threadIdx.x / TPR;
   if (row < rows_left)
-    for (int k = (threadIdx.x & 7) * 4; k < dh; k += 32) {
+    for (int k = threadIdx.x % TPR * 4; k < dh; k += 4 * TPR) {
       f32x4 v = *reinterpret_cast<const f32x4 *>(lds + row * LDR + k);
 #pragma unroll
-      for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f32x4 *>(lds + (w * 32 + row) * LDR + k);
+      for (int w = 1; w < NW; ++w) v += *reinterpret_cast<const f32x4 *>(lds + (w * 32 + row) * LDR + k);
       put4(out + row * ld + k, v);
       if (out32) put4(out32 + row * ld + k, v);
     }
@@ -175,10 +184,10 @@ __device__ __forceinline__ Item item_of(int N, int Hs, bool late_first) {
   return {late_first ? nb - 1 - rank : rank, bh / Hs, bh % Hs};
 }
 
-template <int DH, int BF>
-__global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const typename El<BF>::T *qkv, typename El<BF>::T *o, float *o32, float *lse, int N, int Hs, int dh, float scale, const int32_t *keep) {
-  __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
-  __shared__ float ms[4][32], ls[4][32];
+template <int DH, int BF, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_f32_fwd_kernel(const typename El<BF>::T *qkv, typename El<BF>::T *o, float *o32, float *lse, int N, int Hs, int dh, float scale, const int32_t *keep) {
+  __shared__ __attribute__((aligned(16))) float lds[NW * 32 * (DH + 4)];
+  __shared__ float ms[NW][32], ls[NW][32];
   const Item it = item_of(N, Hs, true);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
   const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
@@ -193,7 +202,7 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const typename El<BF>
   f32x16 acc[DH / 32];
   zero<DH>(acc);
   float m = -INFINITY, l = 0.f;
-  for (int kt = wave; kt <= it.blk && !masked; kt += 4) {
+  for (int kt = wave; kt <= it.blk && !masked; kt += NW) {
     load_row<DH>(kf, kp + (int64_t)min(kt * 32 + c, N - 1) * ld, dh, g);
     f32x16 s = dot_tile<DH, kChains<BF>>(kf, qf);
     float mx = -INFINITY;
@@ -220,21 +229,22 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(const typename El<BF>
   l += __shfl_xor(l, 32, 64);
   if (g == 0) { ms[wave][c] = m; ls[wave][c] = l; }
   __syncthreads();
-  const float mt = fmaxf(fmaxf(ms[0][c], ms[1][c]), fmaxf(ms[2][c], ms[3][c]));
-  float lt = 0.f;
+  float mt = ms[0][c], lt = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) lt += ls[w][c] * fast_exp2((ms[w][c] - mt) * sc);
+  for (int w = 1; w < NW; ++w) mt = fmaxf(mt, ms[w][c]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) lt += ls[w][c] * fast_exp2((ms[w][c] - mt) * sc);
   const float mul = masked ? 0.f : fast_exp2((m - mt) * sc) / lt;  // a wave without tiles has m = -inf: factor 0
   if (wave == 0 && g == 0 && q < N) lse[((int64_t)it.b * Hs + it.h) * N + q] = masked ? 0.f : fmaf(mt, scale, logf(lt));
   const int64_t at = ((int64_t)it.b * N + q0) * HD + (int64_t)it.h * dh;
-  merge<DH>(lds, acc, mul, o + at, o32 ? o32 + at : nullptr, HD, N - q0, dh, wave, c, g);
+  merge<DH, NW>(lds, acc, mul, o + at, o32 ? o32 + at : nullptr, HD, N - q0, dh, wave, c, g);
 }
 
-template <int DH, int BF>
-__global__ __launch_bounds__(256) void attn_f32_dq_kernel(const typename El<BF>::T *qkv, const typename El<BF>::T *dout, const float *o, const float *lse, float *delta,
+template <int DH, int BF, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(const typename El<BF>::T *qkv, const typename El<BF>::T *dout, const float *o, const float *lse, float *delta,
                                                           typename El<BF>::T *dqkv, int N,
                                                           int Hs, int dh, float scale, const int32_t *keep) {
-  __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
+  __shared__ __attribute__((aligned(16))) float lds[NW * 32 * (DH + 4)];
   const Item it = item_of(N, Hs, true);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
   const int64_t HD = (int64_t)Hs * dh, ld = 3 * HD;
@@ -258,7 +268,7 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(const typename El<BF>:
   const bool masked = keep && keep[it.h] < 0;
   f32x16 acc[DH / 32];
   zero<DH>(acc);
-  for (int kt = wave; kt <= it.blk && !masked; kt += 4) {
+  for (int kt = wave; kt <= it.blk && !masked; kt += NW) {
     const int64_t kr = min(kt * 32 + c, N - 1);
     load_row<DH>(kf, kp + kr * ld, dh, g);
     f32x16 s = dot_tile<DH, kChains<BF>>(kf, qf);
@@ -272,14 +282,18 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(const typename El<BF>:
     left_out = add_tile<DH>(acc, kp, ld, kt * 32, N, dh, s, c, g, kt == it.blk, kept);
   }
   if (left_out) add_left_out<DH>(acc, kp, ld, q0, N, dh, c, g, kept, [&](int key) { return key <= q; });
-  merge<DH>(lds, acc, 1.f, dqkv + ((int64_t)it.b * N + q0) * ld + (int64_t)it.h * dh, nullptr, ld, N - q0, dh, wave, c, g);
+  merge<DH, NW>(lds, acc, 1.f, dqkv + ((int64_t)it.b * N + q0) * ld + (int64_t)it.h * dh, nullptr, ld, N - q0, dh, wave, c, g);
 }
 
-template <int DH, int BF>
-__global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const typename El<BF>::T *qkv, const typename El<BF>::T *dout, const float *lse, const float *delta,
+template <int DH, int BF, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(const typename El<BF>::T *qkv, const typename El<BF>::T *dout, const float *lse, const float *delta,
                                                            typename El<BF>::T *dqkv, int N, int Hs,
                                                            int dh, float scale, const int32_t *keep) {
-  __shared__ __attribute__((aligned(16))) float lds[4 * 32 * (DH + 4)];
+  __shared__ __attribute__((aligned(16))) float lds[NW * 32 * (DH + 4)];
+  // Eight waves have half the registers each: the key and value rows, the same for all, lie in LDS
+  constexpr bool SHARED = NW == 8;
+  constexpr int LDR = DH + 4;
+  __shared__ __attribute__((aligned(16))) float rows[SHARED ? 2 * 32 * LDR : 4];
   __shared__ float kept[2][32 * 32];  // wave 0's, which has the diagonal tile
   const Item it = item_of(N, Hs, false);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
@@ -291,19 +305,34 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const typename El<BF>
   const float *lse_b = lse + ((int64_t)it.b * Hs + it.h) * N, *del_b = delta + ((int64_t)it.b * Hs + it.h) * N;
   const bool masked = keep && keep[it.h] < 0;
   f32x4 kf[DH / 8], vf[DH / 8], xf[DH / 8];
-  load_row<DH>(kf, kp + (int64_t)kr * ld, dh, g);
-  load_row<DH>(vf, vp + (int64_t)kr * ld, dh, g);
+  const float *const ks = rows + c * LDR + 4 * g, *const vs = ks + 32 * LDR;
+  if constexpr (SHARED) {
+    if (wave < 2) {
+      load_row<DH>(xf, (wave ? vp : kp) + (int64_t)kr * ld, dh, g);
+#pragma unroll
+      for (int u = 0; u < DH / 8; ++u) *reinterpret_cast<f32x4 *>(rows + (32 * wave + c) * LDR + 8 * u + 4 * g) = xf[u];
+    }
+    __syncthreads();
+  } else {
+    load_row<DH>(kf, kp + (int64_t)kr * ld, dh, g);
+    load_row<DH>(vf, vp + (int64_t)kr * ld, dh, g);
+  }
   f32x16 dk[DH / 32], dv[DH / 32];
   zero<DH>(dk);
   zero<DH>(dv);
   const int n_q = (N + 31) / 32;
-  for (int qt = it.blk + wave; qt < n_q && !masked; qt += 4) {
+  for (int qt = it.blk + wave; qt < n_q && !masked; qt += NW) {
     const int q0 = qt * 32;
     const int64_t qr = min(q0 + c, N - 1);
     load_row<DH>(xf, qp + qr * ld, dh, g);
-    f32x16 s = dot_tile<DH, kChains<BF>>(xf, kf);
+    if constexpr (SHARED) asm volatile("" ::: "memory");  // (the rows in LDS are not to be kept in registers)
+    f32x16 s;
+    if constexpr (SHARED) s = dot_tile<DH, kChains<BF>>(xf, ks);
+    else s = dot_tile<DH, kChains<BF>>(xf, kf);
     load_row<DH>(xf, gp + qr * HD, dh, g);
-    f32x16 dp = dot_tile<DH, BF ? 1 : 2>(xf, vf);
+    f32x16 dp;
+    if constexpr (SHARED) dp = dot_tile<DH, BF ? 1 : 2>(xf, vs);
+    else dp = dot_tile<DH, BF ? 1 : 2>(xf, vf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int q = q0 + 8 * (r >> 2) + 4 * g + (r & 3), qc = min(q, N - 1);
@@ -319,34 +348,44 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(const typename El<BF>
   if (dv_left_out) add_left_out<DH>(dv, gp, HD, k0, N, dh, c, g, kept[0], seen);
   if (dk_left_out) add_left_out<DH>(dk, qp, ld, k0, N, dh, c, g, kept[1], seen);
   auto *out = dqkv + ((int64_t)it.b * N + k0) * ld + HD + (int64_t)it.h * dh;
-  merge<DH>(lds, dk, 1.f, out, nullptr, ld, N - k0, dh, wave, c, g);
-  merge<DH>(lds, dv, 1.f, out + HD, nullptr, ld, N - k0, dh, wave, c, g);
+  merge<DH, NW>(lds, dk, 1.f, out, nullptr, ld, N - k0, dh, wave, c, g);
+  merge<DH, NW>(lds, dv, 1.f, out + HD, nullptr, ld, N - k0, dh, wave, c, g);
 }
 
 bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
 
-#define TW_F32_DH(dh, expr)                              \
-  do {                                                   \
-    if ((dh) <= 32) { constexpr int DH = 32; expr; }      \
-    else if ((dh) <= 64) { constexpr int DH = 64; expr; } \
-    else { constexpr int DH = 128; expr; }               \
+// WG(DH, NW) for heads of up to DH columns and workgroups of NW waves
+#define TW_F32_DH(dh, wide, WG)               \
+  do {                                        \
+    if ((dh) <= 32 && (wide)) WG(32, 8);      \
+    else if ((dh) <= 32) WG(32, 4);           \
+    else if ((dh) <= 64 && (wide)) WG(64, 8); \
+    else if ((dh) <= 64) WG(64, 4);           \
+    else WG(128, 4);                          \
   } while (0)
+
+// Eight waves to a workgroup where there are few workgroups to a CU and more tiles of 32 in a sequence than four waves: the chain of a wave is half as
+// long, and a second wave a SIMD works while the first waits for operands.  Forward / forward and backward, fp32, us, four waves and eight: 2 x 512
+// tokens, 6 heads of 64 19.5 / 81.8 and 18.4 / 77.6; 1 x 2048, 6 of 64 (384 workgroups) 73 / 283 and 55 / 241; 1 x 4096, 4 of 32 (512) 86 / 346 and
+// 63 / 275; 4 x 1024, 8 of 64 (1024) 69 / 332 and 72 / 312.  Heads of 128 do not fit the registers of a wave among eight.
+static bool wide_of(int64_t workgroups, int N) { return workgroups <= 512 && N > 128; }
 
 bool twist_attention_f32_ok(const twist_ctx *ctx, const void *qkv, const void *o, const void *dout, const void *dqkv, int dh) {
   return !ctx->plain_only && dh % 4 == 0 && dh <= 128 && al16(qkv) && al16(o) && al16(dout) && al16(dqkv);
 }
 
 twist_status twist_attention_f32_fwd(twist_ctx *ctx, int bf16, const void *qkv, void *o, float *o32, float *lse, int B, int N, int Hs, int dh, const int32_t *keep) {
-  const dim3 grid((unsigned)((int64_t)((N + 31) / 32) * B * Hs)), block(256);
+  const dim3 grid((unsigned)((int64_t)((N + 31) / 32) * B * Hs));
   const float scale = 1.0f / sqrtf((float)dh);
-  if (bf16)
-    TW_F32_DH(dh, hipLaunchKernelGGL((attn_f32_fwd_kernel<DH, 1>), grid, block, 0, ctx->stream, static_cast<const uint16_t *>(qkv), static_cast<uint16_t *>(o), o32, lse, N,
-                                     Hs, dh, scale, keep));
-  else
-    TW_F32_DH(dh, hipLaunchKernelGGL((attn_f32_fwd_kernel<DH, 0>), grid, block, 0, ctx->stream, static_cast<const float *>(qkv), static_cast<float *>(o), nullptr, lse, N, Hs,
-                                     dh, scale, keep));
+  const bool wide = wide_of(grid.x, N);
+#define TW_FWD_BF(DH, NW) hipLaunchKernelGGL((attn_f32_fwd_kernel<DH, 1, NW>), grid, dim3(64 * NW), 0, ctx->stream, static_cast<const uint16_t *>(qkv), static_cast<uint16_t *>(o), o32, lse, N, Hs, dh, scale, keep)
+#define TW_FWD(DH, NW) hipLaunchKernelGGL((attn_f32_fwd_kernel<DH, 0, NW>), grid, dim3(64 * NW), 0, ctx->stream, static_cast<const float *>(qkv), static_cast<float *>(o), nullptr, lse, N, Hs, dh, scale, keep)
+  if (bf16) TW_F32_DH(dh, wide, TW_FWD_BF);
+  else TW_F32_DH(dh, wide, TW_FWD);
+#undef TW_FWD_BF
+#undef TW_FWD
   TW_HIP(ctx, hipGetLastError());
   return TWIST_OK;
 }
@@ -355,12 +394,18 @@ template <int BF>
 static void launch_bwd(hipStream_t st, const void *qkv, const float *o, const void *dout, const float *lse, float *delta, void *dqkv, int B, int N, int Hs, int dh,
                        const int32_t *keep) {
   using T = typename El<BF>::T;
-  const dim3 grid((unsigned)((int64_t)((N + 31) / 32) * B * Hs)), block(256);
+  const dim3 grid((unsigned)((int64_t)((N + 31) / 32) * B * Hs));
   const float scale = 1.0f / sqrtf((float)dh);
+  const bool wide = wide_of(grid.x, N);
   const T *x = static_cast<const T *>(qkv), *gout = static_cast<const T *>(dout);
   T *dx = static_cast<T *>(dqkv);
-  TW_F32_DH(dh, hipLaunchKernelGGL((attn_f32_dq_kernel<DH, BF>), grid, block, 0, st, x, gout, o, lse, delta, dx, N, Hs, dh, scale, keep);
-            hipLaunchKernelGGL((attn_f32_dkv_kernel<DH, BF>), grid, block, 0, st, x, gout, lse, delta, dx, N, Hs, dh, scale, keep));
+#define TW_BWD(DH, NW)                                                                                                                                            \
+  do {                                                                                                                                                               \
+    hipLaunchKernelGGL((attn_f32_dq_kernel<DH, BF, NW>), grid, dim3(64 * NW), 0, st, x, gout, o, lse, delta, dx, N, Hs, dh, scale, keep);  \
+    hipLaunchKernelGGL((attn_f32_dkv_kernel<DH, BF, NW>), grid, dim3(64 * NW), 0, st, x, gout, lse, delta, dx, N, Hs, dh, scale, keep);    \
+  } while (0)
+  TW_F32_DH(dh, wide, TW_BWD);
+#undef TW_BWD
 }
 
 twist_status twist_attention_f32_bwd(twist_ctx *ctx, int bf16, const void *qkv, const float *o, const void *dout, const float *lse, float *delta, void *dqkv, int B, int N,
