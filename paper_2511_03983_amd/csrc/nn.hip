@@ -768,6 +768,72 @@ __global__ __launch_bounds__(NT) void ce_vec_kernel(u32x4v *logits, int64_t ld8,
   }
 }
 
+// The same for fp32 rows of at most NV * 4 * NT logits: bound by memory as well, where ce_kernel reads a row three times, four bytes to a lane and
+// load: 1024 x 50257 229 -> 85 us, 4.8 TB/s.
+template <int NV, int NT, bool GRAD>
+__global__ __launch_bounds__(NT) void ce_vec_f32_kernel(f32x4v *logits, int64_t ld4, const int32_t *targets, float *rowloss, int V, float inv_T) {
+  constexpr int NW = NT / 64;
+  __shared__ float sh[2][NW];
+  f32x4v *row = logits + (int64_t)blockIdx.x * ld4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int mine = (int)ld4 - 64 * wave;  // k NT >= mine: all of the wave's vector k lies beyond the row, and is skipped
+  f32x4v x[NV];
+  float m = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int idx = k * NT + threadIdx.x;
+    x[k] = f32x4v{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    if (idx < ld4) x[k] = row[idx];
+  }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    if (k * NT < mine) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (4 * (k * NT + (int)threadIdx.x) + e >= V) x[k][e] = -INFINITY;  // padding
+        m = fmaxf(m, x[k][e]);
+      }
+    }
+  }
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) sh[0][wave] = m;
+  __syncthreads();
+  m = sh[0][0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) m = fmaxf(m, sh[0][i]);
+  float s = 0.f;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    if (k * NT < mine) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s += __expf(x[k][e] - m);
+    }
+  }
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) sh[1][wave] = s;
+  __syncthreads();
+  s = sh[1][0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) s += sh[1][i];
+  const float lse = m + logf(s);
+  const int tgt = targets[blockIdx.x];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int idx = k * NT + threadIdx.x;
+    if (idx < ld4 && (GRAD || idx == tgt >> 2)) {
+      f32x4v g;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = 4 * idx + e;
+        if (c == tgt) rowloss[blockIdx.x] = lse - x[k][e];
+        // columns between V and the row stride are read (times zero weights) by the next projection
+        g[e] = c < V ? (__expf(x[k][e] - lse) - (c == tgt ? 1.f : 0.f)) * inv_T : 0.f;
+      }
+      if (GRAD) row[idx] = g;
+    }
+  }
+}
+
 // The same for rows of any length (row stride a multiple of 8): one vectorised pass keeps a running maximum and a
 // sum of exponentials relative to it, a second pass re-reads the row (it is still in the L2) and writes the gradient.
 template <bool GRAD>
@@ -1274,6 +1340,13 @@ twist_status twist_ce_fwd_bwd(twist_ctx *ctx, int bf16, void *logits, int64_t ld
     else if (ld <= 16 * 2048) TW_CE2(ce_vec_kernel, kT, 16, kT,);
     else if (ld <= 16 * 4096) TW_CE2(ce_vec_kernel, 512, 16, 512,);
     else TW_CE2(ce_vec_long_kernel, kT, );
+  } else if (!bf16 && ld % 4 == 0 && ld <= 65536 && al16(logits)) {
+    f32x4v *lv = static_cast<f32x4v *>(logits);
+    const int64_t LD = ld / 4;
+    if (ld <= 4 * 1024) TW_CE2(ce_vec_f32_kernel, kT, 4, kT,);
+    else if (ld <= 16 * 1024) TW_CE2(ce_vec_f32_kernel, kT, 16, kT,);
+    else if (ld <= 16 * 2048) TW_CE2(ce_vec_f32_kernel, 512, 16, 512,);
+    else TW_CE2(ce_vec_f32_kernel, 1024, 16, 1024,);
   } else {
     void *lv = logits;
     const int64_t LD = ld;

@@ -141,6 +141,33 @@ def test_cross_entropy_loss_and_gradient(lib, dtype, V, T):
     np.testing.assert_allclose(to_numpy(rowloss).mean(), want_loss, rtol=1e-5)
 
 
+# fp32 rows held in registers: 4 vectors per lane of 256 threads, 16 of 256, of 512 and of 1024, and the re-read kernel beyond 65536; strides of the
+# vocabulary rounded up to 8, vocabularies that end in a vector, at it and before it
+@pytest.mark.parametrize("V,T", [(1, 2), (4, 3), (4093, 5), (4097, 4), (16383, 3), (16385, 3), (32768, 2), (32775, 2), (50257, 3), (65534, 2), (65537, 2)])
+@pytest.mark.parametrize("odd", [None, float("inf"), float("nan"), torch.finfo(torch.float32).min])
+def test_fp32_cross_entropy_at_the_edges_of_its_kernels(lib, V, T, odd):
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=1, d_head=8, d_ff=8, vocab=V, dtype=F32)))
+    x = torch.randn(T, (V + 7) // 8 * 8, generator=torch.Generator().manual_seed(V)) * 3
+    x[:, V:] = float("nan")                                               # the padding must not enter the sums
+    if odd is not None:
+        x[0, V // 2] = odd
+    tgt = torch.tensor([V - 1] + [(7919 * i) % V for i in range(1, T)], dtype=torch.int32)
+    t = x.cuda()
+    loss, rowloss = ctx.twist_ce_raw(t, tgt.cuda())
+    torch.cuda.synchronize()
+    z = x[:, :V].double()
+    rows = torch.arange(T)
+    want_loss, want = torch.logsumexp(z, 1) - z[rows, tgt.long()], torch.softmax(z, 1)
+    want[rows, tgt.long()] -= 1
+    sound = torch.isfinite(want).all(1)
+    rowloss, got = rowloss.cpu().double(), t.cpu().double() * T
+    assert not torch.isfinite(rowloss[~sound]).any()
+    # exponentials of relative error 2^-22 and 2^-24 |x - lse| (at most 30) of their argument; loss: an fp32 sum and difference of values below 32
+    torch.testing.assert_close(rowloss[sound], want_loss[sound], rtol=2e-6, atol=4e-6)
+    torch.testing.assert_close(got[sound][:, :V], want[sound], rtol=1e-5, atol=1e-6)
+    assert not got[sound][:, V:].any()
+
+
 @pytest.mark.parametrize("dtype", [BF, F32])
 @pytest.mark.parametrize("positions", [True, False])
 def test_embedding_forward_and_backward(lib, dtype, positions):
@@ -356,6 +383,25 @@ def test_fp32_attention_of_any_length(lib, dh, N):
             # a sequence of one has dq = dk = 0 in exact arithmetic; what is left is the rounding of dp - delta, 1e-7 of |dO| |v| |k|
             err = np.linalg.norm(got[:, :, i][:, :, on] - want[i][:, :, on])
             assert err <= 1e-5 * np.linalg.norm(want[i][:, :, on]) + 1e-6 * np.linalg.norm(g) * dh, (i, err)
+
+
+# fp32: more tiles of 32 than four waves, in few workgroups (eight waves each) and many (four): the same sequences give the same results
+@pytest.mark.parametrize("dh", [32, 36, 64])
+@pytest.mark.parametrize("N", [129, 160, 289])
+def test_fp32_attention_of_few_and_many_workgroups(lib, dh, N):
+    Hs, many = 3, 40
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=Hs, d_head=dh, d_ff=8, max_seq=N)))
+    assert (N + 31) // 32 * Hs <= 512 < (N + 31) // 32 * Hs * many
+    qkv = _dev(_snap(si.normal(dh + N, "qkv", (N, 3 * Hs * dh)), F32), F32)
+    dout = _dev(_snap(si.normal(N, "dout", (N, Hs * dh)), F32), F32)
+    few = ctx.twist_attention_raw(qkv, dout, 1, N, Hs)
+    more = ctx.twist_attention_raw(qkv.repeat(many, 1), dout.repeat(many, 1), many, N, Hs)
+    torch.cuda.synchronize()
+    for i, (a, b) in enumerate(zip(few, more)):
+        b = b.view(many, *a.shape)
+        assert torch.equal(b, b[:1].expand_as(b))
+        # both as far from exact arithmetic as the oracle comparison above allows, 3e-6 forward and 1e-5 backward
+        assert rel_fro(to_numpy(b[0]), to_numpy(a)) <= (6e-6 if i < 2 else 2e-5), i
 
 
 # An infinity or a NaN in one token's value, key, query or output gradient: what does not depend on it keeps its bits (earlier queries'
