@@ -298,7 +298,8 @@ typedef struct {
 } twist_weight_grad;
 TWIST_API twist_status twist_weight_grads_raw(twist_ctx *ctx, int32_t n, const twist_weight_grad *products, int32_t K, float *scratch, size_t scratch_floats,
                                               int32_t chosen[3]);
-/* Which matrix-core kernel a projection of this shape runs on where its operands are aligned (host only, for tests and benchmarks):
+/* Which matrix-core kernel a projection of this shape runs on where its operands are aligned, their rows without padding (host only, for tests and
+ * benchmarks):
  * chosen receives the rows and columns of the output tile (0: the plain kernel) and the number of parts of the contraction,
  * given a scratch of scratch_floats (0: none).  twist_gemm_tile: among all kernels; twist_gemm_kernel: without the bf16 ones whose two
  * groups of waves share the contraction, which twist_gemm_tile names where they take the product over. */

@@ -152,7 +152,7 @@ struct Schedule {
   // Where the gradients are few the events and waits, about 12 us of host time per layer and gaps of a few us each on the device, cost
   // more than the overlap gives.  Forward and backward of 6 layers, us, second stream / one stream:
   //   bf16 (apart), 0.05 GFLOP 974 / 596    0.8 983 / 744    3.2 1012 / 897    12.9 1338 / 1316   (pairs / one launch) 14.5 1490 / 1522    21 2013 / 2079
-  //   fp32          0.05 GFLOP 1020 / 861   0.8 1318 / 1294  1.6 1834 / 1884   3.2 1796 / 1799    7.2 2496 / 2784
+  //   fp32          0.9 GFLOP 1263 / 1048   1.1 1454 / 1222   2.1 1598 / 1433   3.2 1604 / 1571   6.4 2013 / 1991   7.2 2034 / 2083   14.5 2964 / 3097
   // Where the chain and one launch of all gradients leave few CUs idle, and that launch is well shorter than the others, the streams only
   // contend; of 95 bf16 models of 13 to 3400 GFLOP a layer the rule takes the slower form at most 1.4 % to its cost, but for one (768 x 4096,
   // 4 %).  d x tokens, us, pairs on the second stream / one launch: 768 x 8192 2149 / 2093, 1024 x 8192 4271 / 4123, 1024 x 2048 2479 / 2346;
