@@ -612,7 +612,7 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
 // What bound them: the weight gradients of one layer of a small model are too few tiles each to fill the chip, cut into many parts with
 // a pass over the partial products behind each.  Together they fill it in fewer parts: 8192 x 768 x (192 heads, 768 hidden) in bf16 four
 // launches and four sums, 109 us, against 49 + 8; 2048 x 768 x (512, 2048) 77 us against 44.  In fp32 (one stream, so where they are
-// fewest): 256 x 128 x (64, 256) 20 us against 8, 1248 x 88 x (832, 344) 46 / 20, 1024 x 768 x (384, 1536) 109 / 59; of 156 such groups and pairs the
+// fewest): 256 x 128 x (64, 256) 20 us against 8, 1248 x 88 x (832, 344) 46 / 20, 1024 x 768 x (384, 1536) 98 / 63; of 156 such groups and pairs the
 // mean is two thirds.
 twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGrad *items, int K, float *scratch, size_t scratch_floats, hipStream_t st,
                                 int32_t *chosen) {
