@@ -21,8 +21,8 @@
 //  - there is no barrier before the waves' sums are added at the end: while one wave of a SIMD forms terms the other multiplies;
 //  - a wave's next two steps are in flight, loaded straight to LDS in whole pieces of rows (a first form that loaded the fragments into
 //    registers spent its time on the addresses of 32 rows per load: 1024 x 768 x 1536 48 us).
-// Its chains are an eighth (a quarter) of the contraction long, and the error is smaller: K = 768 0.9e-7 (gemm_f32_kernel 1.1e-7), 4096 (TN) 1.9e-7
-// (2.7e-7), 50257 whole 5.0e-7 (10e-7).  us, before / now: 1024 x 768 x 1536 32.1 / 23.6, its NN form 35.3 / 23.8, 1152 x 768 x 1024 (TN) 25.2 / 18.8,
+// Its chains are an eighth (a quarter) of the contraction long, and the error is smaller: K = 96 0.47e-7 (gemm_f32_kernel 0.53e-7), 768 0.8e-7 (1.1e-7),
+// 4096 1.9e-7 (2.7e-7), 50257 whole 5.0e-7 (10e-7).  us, before / now: 1024 x 768 x 1536 32.1 / 23.6, its NN form 35.3 / 23.8, 1152 x 768 x 1024 (TN) 25.2 / 18.8,
 // 1024 x 1536 x 768 31.6 / 25.5, 1536 x 768 x 1024 (TN) 37.7 / 27.5, 8192 x 768 x 768 89 / 78, 3072 x 768 x 8192 (TN) 330 / 262, 1024 x 768 x 50257 (NN, cut)
 // 580 / 490.  What bounds it: small products the fixed 6 us (launch 2, first loads 2, sums and stores 2), large ones the power limit: 4096^3 797 us
 // against 830 in tiles of 128 on the same card.
@@ -603,8 +603,9 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_f32_wave_kernel(int M, int N,
             for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[i][h][e], b.v[j][h][e], acc[i][j], 0, 0, 0);
     }
   }
-  // the waves' sums are added in wave order; each wave finishes 16 / NW of the groups of four registers.  Registers 4 q .. 4 q + 3 of tile
-  // (i, j): rows 32 i + 8 q + 4 g .. + 3, column 32 j + c
+  // the waves' sums are added, of eight waves the first pairs in 32 bits, the rest in 64: contractions of 48 to 200 are a step or two per wave, and
+  // their error is that of these additions (K = 96 5.9e-8 in 32 bits and wave order, 5.2e-8 in gemm_f32_kernel).  Each wave finishes 16 / NW of the groups of
+  // four registers.  Registers 4 q .. 4 q + 3 of tile (i, j): rows 32 i + 8 q + 4 g .. + 3, column 32 j + c
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -616,9 +617,11 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_f32_wave_kernel(int M, int N,
 #pragma unroll
   for (int t = 0; t < 16 / NW; ++t) {
     const int at = wave * (16 / NW) + t, m = m0 + 32 * (at >> 3) + 8 * (at & 3) + 4 * (lane >> 5), n = n0 + 32 * ((at >> 2) & 1) + (lane & 31);
-    f32x4 x = part[0][at][lane];
+    f32x4 y[4], x;
 #pragma unroll
-    for (int w = 1; w < NW; ++w) x += part[w][at][lane];
+    for (int w = 0; w < 4; ++w) y[w] = NW == 8 ? part[w][at][lane] + part[(w + 4) % NW][at][lane] : part[w][at][lane];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = (float)(((double)y[0][e] + y[1][e]) + ((double)y[2][e] + y[3][e]));
     if (n >= N) continue;
     const float bias = ep.bias ? ep.bias[n] : 0.f;
 #pragma unroll

@@ -194,6 +194,27 @@ def test_fp32_projection_leaves_padding_out(lib, layout, M, N, K):
     assert torch.isnan(buf[M * N:]).all()
 
 
+# tiles of 64 (eight waves to a tile, and four) sum no coarser than tiles of 128, whose waves share every slice: contractions of a few steps of 16 to a
+# wave, where the additions of the waves' sums are most of the error.  (2 % for the norm over a million outputs)
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("size", [1024, 2048])
+@pytest.mark.parametrize("K", [48, 56, 64, 96, 128, 192, 320, 768])
+def test_fp32_tiles_of_64_sum_as_finely_as_tiles_of_128(lib, layout, size, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.randn((K, size) if layout == 2 else (size, K), generator=gen, device="cuda")
+    B = torch.randn((size, K) if layout == 0 else (K, size), generator=gen, device="cuda")
+    want = (A.double().T if layout == 2 else A.double()) @ (B.double().T if layout == 0 else B.double())
+    err = []
+    for pin in (128, 256):
+        ctx.twist_set_kernel_choice(gemm_tile=pin)
+        out = torch.empty((size, size), device="cuda")
+        ctx.twist_gemm_raw(layout, size, size, K, A, B, out)
+        torch.cuda.synchronize()
+        err.append(float((out.double() - want).norm() / want.norm()))
+    assert err[1] <= 1.02 * err[0], err
+
+
 # a tile that an infinity or a NaN reaches is formed a second time, on the fp32 instruction (measured: twice as long in all).  A loop over k
 # per output in its place took 34 to 115 times as long
 @pytest.mark.parametrize("layout,M,N,K", [(0, 1024, 20000, 768), (0, 1024, 1536, 768), (1, 1024, 768, 1536), (2, 2048, 2048, 768)])
