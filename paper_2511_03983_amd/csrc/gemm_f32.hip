@@ -753,6 +753,10 @@ void launch_tile(hipStream_t st, int tile, int M, int N, int K, const float *A, 
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+// Of the k of a part those that one accumulator of a wave sums up; the error of a product grows with the root of that number.  In tiles of 32, on the fp32
+// instruction, it is a quarter of k; their error is 1.8 to 2.2 times that of gemm_f32_kernel, as if it were 2.4 k.
+double chain_of(int tile, bool vec, int64_t items, double k) { return tile == 32 ? 2.4 * k : tile == 64 && vec ? k / (items <= 256 ? 8 : 4) : k / 2; }
+
 // Tile and number of parts of the contraction, by estimated time of the kernels above (us); n = items (tiles, times parts) on the busiest of
 // 256 CUs.  Operands that allow 16-byte loads:
 //   128: 3 + n (8.4 + 1.55 per slice of 32)
@@ -768,8 +772,13 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 // a single one left over in the second round 1.9 + 0.85 per slice, and from then on the rounds run into each other; 32 as above.  Rows contiguous in
 // both operands (TN): an eighth more for tiles of 128, a sixth for single ones of 64.
 // Several products over the same K that share a launch: their tiles and outputs together.
+//
+// `longest`: how coarse the sums may be (chain_of).  Operands that allow 16-byte loads are summed no more coarsely than the same product without them: by
+// time alone 276 x 500 x 1272 (NN) takes tiles of 32 for 0.5 us less and leaves 1.7e-7 where 64 in four parts leaves 0.8e-7; 740 x 848 x 8704 (NN) 64 whole
+// for 128 in 16 parts, 2.0e-7 for 1.25e-7.
 struct Choice { int tile, parts; };
-Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bool vec, bool may_split, size_t split_floats, int least_tile = 32, int least_parts = 1) {
+Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bool vec, bool may_split, size_t split_floats, double longest = 1e30, int least_tile = 32,
+              int least_parts = 1) {
   Choice best{0, 1};
   double best_us = 1e30, outputs = 0.0;
   for (int i = 0; i < count; ++i) outputs += (double)Ms[i] * Ns[i];
@@ -780,6 +789,7 @@ Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bo
       if (parts > 1 && (!may_split || K / parts < 256 || parts * outputs > (double)split_floats)) break;
       if (parts < least_parts) continue;
       const int64_t items = tiles * parts;
+      if (chain_of(tile, vec, items, (double)K / parts) > longest) continue;
       const double n = (double)((items + 255) / 256), k = (double)K / parts;
       double us;
       if (tile == 128 && vec) {
@@ -807,7 +817,9 @@ Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bo
 }  // namespace
 
 void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool vec, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
-  Choice ch = choose(lay, 1, &M, &N, K, vec, may_split && !ctx->gemm_tile, split_floats);
+  const bool split = may_split && !ctx->gemm_tile;
+  Choice ch = choose(lay, 1, &M, &N, K, false, split, split_floats);
+  if (vec) ch = choose(lay, 1, &M, &N, K, true, split, split_floats, chain_of(ch.tile, false, 0, (double)K / ch.parts));
   if (ctx->gemm_tile) ch = {ctx->gemm_tile == 128 ? 128 : 64, 1};
   const int bk = ch.tile == 128 ? 32 : 64;
   kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
@@ -853,7 +865,7 @@ bool twist_gemm_f32_group_choice(int n, const int *Ms, const int *Ns, int K, siz
     least_tile = std::max(least_tile, std::min(c.tile, 64));
     least_parts = std::max(least_parts, c.parts);
   }
-  const Choice ch = choose(GEMM_TN, n, Ms, Ns, K, true, split_floats > 0, split_floats, least_tile, least_parts);
+  const Choice ch = choose(GEMM_TN, n, Ms, Ns, K, true, split_floats > 0, split_floats, 1e30, least_tile, least_parts);
   if (!ch.tile) return false;
   const int bk = ch.tile == 128 ? 32 : 64;
   kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
