@@ -777,17 +777,15 @@ double chain_of(int tile, bool vec, int64_t items, double k) { return tile == 32
 // time alone 276 x 500 x 1272 (NN) takes tiles of 32 for 0.5 us less and leaves 1.7e-7 where 64 in four parts leaves 0.8e-7; 740 x 848 x 8704 (NN) 64 whole
 // for 128 in 16 parts, 2.0e-7 for 1.25e-7.
 struct Choice { int tile, parts; };
-Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bool vec, bool may_split, size_t split_floats, double longest = 1e30, int least_tile = 32,
-              int least_parts = 1) {
+Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bool vec, bool may_split, size_t split_floats, double longest = 1e30) {
   Choice best{0, 1};
   double best_us = 1e30, outputs = 0.0;
   for (int i = 0; i < count; ++i) outputs += (double)Ms[i] * Ns[i];
-  for (int tile = 128; tile >= least_tile; tile /= 2) {
+  for (int tile = 128; tile >= 32; tile /= 2) {
     int64_t tiles = 0;
     for (int i = 0; i < count; ++i) tiles += (int64_t)((Ms[i] + tile - 1) / tile) * ((Ns[i] + tile - 1) / tile);
     for (int parts = 1; parts <= 16; parts *= 2) {
       if (parts > 1 && (!may_split || K / parts < 256 || parts * outputs > (double)split_floats)) break;
-      if (parts < least_parts) continue;
       const int64_t items = tiles * parts;
       if (chain_of(tile, vec, items, (double)K / parts) > longest) continue;
       const double n = (double)((items + 255) / 256), k = (double)K / parts;
@@ -855,17 +853,15 @@ twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int 
   return TWIST_OK;
 }
 
-// A common launch is no coarser in its sums than the launches it replaces: a part of the contraction is no longer than the shortest of
-// theirs, and tiles are of 32 (on the fp32 instruction, whose error is the greater one) only where all of theirs are.  280 x 1120 and
-// 1120 x 280 over 1636 rows on tiles of 32: error 3.7e-7 instead of 1.9e-7.  False where the scratch does not hold that many parts.
+// As with a single product, a common launch is no coarser in its sums than every product by itself on unaligned rows: 280 x 1120 and 1120 x 280 over 1636
+// rows on tiles of 32 would have an error of 3.7e-7 instead of 1.9e-7.  False where the scratch does not hold that many parts.
 bool twist_gemm_f32_group_choice(int n, const int *Ms, const int *Ns, int K, size_t split_floats, int &tile, int &parts, int &kchunk) {
-  int least_tile = 32, least_parts = 1;
+  double longest = 1e30;
   for (int i = 0; i < n; ++i) {
-    const Choice c = choose(GEMM_TN, 1, Ms + i, Ns + i, K, true, split_floats > 0, split_floats);
-    least_tile = std::max(least_tile, std::min(c.tile, 64));
-    least_parts = std::max(least_parts, c.parts);
+    const Choice c = choose(GEMM_TN, 1, Ms + i, Ns + i, K, false, split_floats > 0, split_floats);
+    longest = std::min(longest, chain_of(c.tile, false, 0, (double)K / c.parts));
   }
-  const Choice ch = choose(GEMM_TN, n, Ms, Ns, K, true, split_floats > 0, split_floats, 1e30, least_tile, least_parts);
+  const Choice ch = choose(GEMM_TN, n, Ms, Ns, K, true, split_floats > 0, split_floats, longest);
   if (!ch.tile) return false;
   const int bk = ch.tile == 128 ? 32 : 64;
   kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
