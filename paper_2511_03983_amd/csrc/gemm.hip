@@ -436,8 +436,21 @@ constexpr Kind kKinds[] = {{256, 256, 1.0, 9.1, 0.36, 0.434, 0.32, {1, 1, 1}}, {
                            {64, 96, 5.52, 0.97, 0.3, 0.0865, 0.0335, {1, 1.085, 1.12}}};
 constexpr int kOneGroup = 4, kAllKinds = sizeof(kKinds) / sizeof(kKinds[0]);  // kinds from kOneGroup on are those of gemm_kp.hip
 struct Choice { int kind, parts; double us = 0.0, idle = 0.0; int64_t items = 0; };  // idle: of the microseconds, those of CUs without a tile
-// (several products over the same K that share a launch: their tiles and outputs together; among kinds first .. last - 1)
-Choice choose_of(int first, int last, GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, int most_parts, size_t split_floats) {
+// parts of the contraction and their length, a multiple of the kernel's slices
+struct Cut { int kind, parts, kchunk; };
+Cut cut_into(int kind, int parts, int K) {
+  const int step = kind < 2 ? 32 : 128, kchunk = ((K + parts - 1) / parts + step - 1) / step * step;
+  return {kind, (K + kchunk - 1) / kchunk, kchunk};
+}
+// Of the k of a part those that one fp32 accumulator of a wave sums up.  The error of a product grows with the root of that number, whatever the
+// instruction: 6728 x 136 x 7984 (TN) on 256x256 in nine parts 1.8e-7, on 64x96 whole 3.9e-7; uncut products of gemm_kp.hip are at 0.69 of the others.
+double chain_of(int kind, int parts, int K) {
+  const int k = std::min(K, cut_into(kind, parts, K).kchunk);
+  return kind >= kOneGroup ? k / 2.0 : kind == 3 ? k / 4.0 : k;
+}
+// (several products over the same K that share a launch: their tiles and outputs together; among kinds first .. last - 1; sums no longer than `longest`)
+Choice choose_of(int first, int last, GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, int most_parts, size_t split_floats,
+                 double longest = 1e30) {
   Choice best{first, 1, 1e30};
   double best_us = 1e30, outputs = 0.0;
   for (int i = 0; i < n; ++i) outputs += (double)Ms[i] * Ns[i];
@@ -448,7 +461,7 @@ Choice choose_of(int first, int last, GemmLayout lay, int n, const int *Ms, cons
     for (int parts = 1; parts <= most_parts; ++parts) {
       if (parts > 1 && (K < 256 * parts || parts * outputs > (double)split_floats)) break;
       const int64_t items = tiles * parts, rounds = (items + 255) / 256;
-      if (k >= kOneGroup && (items < 128 || items > 1024)) continue;
+      if (k >= kOneGroup && (items < 128 || items > 1024 || chain_of(k, parts, K) > longest)) continue;
       const double share = std::min(1.0, items / 256.0), slice = (kd.s0 + kd.s1 * share) * kd.lay[lay];
       double us = kd.fixed + rounds * (kd.tile + (f32_out || parts > 1 ? kd.tile32 : 0.0) + K / 32.0 / parts * slice);
       if (parts > 1) us += 4.4 + (parts + 1.0) * outputs * 4.0 / 2.8e6;
@@ -461,28 +474,22 @@ Choice choose_of(int first, int last, GemmLayout lay, int n, const int *Ms, cons
 Choice choose(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, bool may_split, size_t split_floats) {
   return choose_of(0, kOneGroup, lay, n, Ms, Ns, K, f32_out, may_split ? 16 : 1, split_floats);
 }
-// all kernels.  Those of gemm_kp.hip cut a contraction no further than the others would.  Where it is longer than any batch (the vocabulary's input
+// all kernels.  Those of gemm_kp.hip cut a contraction no further than the others would, and sum no more coarsely.  Where it is longer than any batch (the vocabulary's input
 // gradient) they wait for memory: a CU has 120 KB in flight, and operands that come from beyond the caches take 2 us and more to arrive; us, the others /
 // these: 8192 x 768 x 50257 778 / 741, 4096 x 512 x 50257 241 / 305, 1500 x 1024 x 32000 116 / 137, 8192 x 2048 x 32000 817 / 1074.
 // Of the small tiles two share a CU, and their second round is shorter than the estimate has it (a tenth of the whole time): 0.82 there.
 Choice choose_any(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, bool may_split, size_t split_floats) {
   const Choice one = choose(lay, n, Ms, Ns, K, f32_out, may_split, split_floats);
   if (K > 8192) return one;
-  const Choice two = choose_of(kOneGroup, kAllKinds, lay, n, Ms, Ns, K, f32_out, one.parts, split_floats);
+  const Choice two = choose_of(kOneGroup, kAllKinds, lay, n, Ms, Ns, K, f32_out, one.parts, split_floats, chain_of(one.kind, one.parts, K));
   return two.us < (one.kind >= 2 && one.items > 256 ? 0.82 : 0.92) * one.us ? two : one;
 }
 
-// kernel, parts of the contraction and their length (a multiple of the kernel's slices) of a bf16 product whose operands are aligned
-struct Cut { int kind, parts, kchunk; };
-Cut cut_into(Choice ch, int K) {
-  const int step = ch.kind < 2 ? 32 : 128, kchunk = ((K + ch.parts - 1) / ch.parts + step - 1) / step * step;
-  return {ch.kind, (K + kchunk - 1) / kchunk, kchunk};
-}
-// `any`: among all kernels
+// kernel, parts of the contraction and their length of a bf16 product whose operands are aligned; `any`: among all kernels
 Cut cut_of(const twist_ctx *ctx, bool any, GemmLayout lay, int M, int N, int K, bool f32_out, bool may_split, size_t split_floats) {
   Choice ch = (any ? choose_any : choose)(lay, 1, &M, &N, K, f32_out, may_split && lay != GEMM_NT, split_floats);
   if (ctx->gemm_tile) ch = {ctx->gemm_tile == 256 ? 0 : 1, 1};
-  return cut_into(ch, K);
+  return cut_into(ch.kind, ch.parts, K);
 }
 
 // one launch of gemm_pp_kernel: kchunk = K for an uncut contraction, else a multiple of 32
@@ -652,7 +659,8 @@ twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGra
   for (int i = 0; i < g.n; ++i) outputs += (double)Ms[i] * Ns[i];
   TW_TRY(timer.start(2.0 * outputs * K));
   if (bf16) {
-    ch = cut_into(choose_any(GEMM_TN, g.n, Ms, Ns, K, true, may_split, scratch_floats), K);
+    const Choice c = choose_any(GEMM_TN, g.n, Ms, Ns, K, true, may_split, scratch_floats);
+    ch = cut_into(c.kind, c.parts, K);
     bm = kKinds[ch.kind].bm;
     bn = kKinds[ch.kind].bn;
   } else {
