@@ -301,8 +301,8 @@ TWIST_API twist_status twist_weight_grads_raw(twist_ctx *ctx, int32_t n, const t
 /* Which matrix-core kernel a projection of this shape runs on where its operands are aligned, their rows without padding (host only, for tests and
  * benchmarks):
  * chosen receives the rows and columns of the output tile (0: the plain kernel) and the number of parts of the contraction,
- * given a scratch of scratch_floats (0: none).  twist_gemm_tile: among all kernels; twist_gemm_kernel: without the bf16 ones whose two
- * groups of waves share the contraction, which twist_gemm_tile names where they take the product over. */
+ * given a scratch of scratch_floats (0: none).  (The vocabulary's projection in twist_subnet_forward, which forms the loss as well, never runs on
+ * the bf16 tiles of 128x192, 192x128, 128x128, 128x96 and 64x96.)  twist_gemm_tile is another name of it. */
 TWIST_API twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32,
                                          size_t scratch_floats, int32_t chosen[3]);
 TWIST_API twist_status twist_gemm_tile(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32,

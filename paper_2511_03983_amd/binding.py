@@ -304,17 +304,14 @@ class Context:
         return tuple(chosen)
 
     def twist_gemm_kernel(self, layout: int, M: int, N: int, K: int, out_f32: bool = False, scratch_floats: int = 0):
-        """(tile rows, tile columns, parts of the contraction) of a projection whose operands are aligned, among the kernels whose waves
-        share every slice; host only."""
+        """(tile rows, tile columns, parts of the contraction) of a projection whose operands are aligned; host only."""
         chosen = (_i32 * 3)()
         _check(lib.twist_gemm_kernel(self.h, layout, M, N, K, int(out_f32), scratch_floats, chosen), self.h)
         return tuple(chosen)
 
     def twist_gemm_tile(self, layout: int, M: int, N: int, K: int, out_f32: bool = False, scratch_floats: int = 0):
-        """The same among all kernels: what the product runs on; host only."""
-        chosen = (_i32 * 3)()
-        _check(lib.twist_gemm_tile(self.h, layout, M, N, K, int(out_f32), scratch_floats, chosen), self.h)
-        return tuple(chosen)
+        """Another name of twist_gemm_kernel."""
+        return self.twist_gemm_kernel(layout, M, N, K, out_f32, scratch_floats)
 
     def twist_backward_schedule(self, tokens: int, head_columns: int, ffn_columns: int):
         """(one launch per layer on the context's stream, FFN gradients paired, attention gradients paired, second stream in use); host only."""

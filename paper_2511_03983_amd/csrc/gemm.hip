@@ -767,12 +767,11 @@ extern "C" twist_status twist_weight_grads_raw(twist_ctx *ctx, int32_t n, const 
   return twist_weight_grads(ctx, ctx->d.dtype == TWIST_BF16, n, products, K, scratch, scratch_floats, nullptr, chosen);
 }
 
-static twist_status tile_query(const char *who, bool any, twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats,
-                               int32_t chosen[3]) {
-  if (!ctx || !chosen) TW_FAIL(ctx, TWIST_EINVAL, "%s: null argument", who);
-  if (layout < 0 || layout > 2 || M < 1 || N < 1 || K < 1) TW_FAIL(ctx, TWIST_EINVAL, "%s: bad layout or size", who);
+extern "C" twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats, int32_t chosen[3]) {
+  if (!ctx || !chosen) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_kernel: null argument");
+  if (layout < 0 || layout > 2 || M < 1 || N < 1 || K < 1) TW_FAIL(ctx, TWIST_EINVAL, "twist_gemm_kernel: bad layout or size");
   if (ctx->d.dtype == TWIST_BF16) {
-    const Cut ch = cut_of(ctx, any, (GemmLayout)layout, M, N, K, out_f32, scratch_floats > 0, scratch_floats);
+    const Cut ch = cut_of(ctx, true, (GemmLayout)layout, M, N, K, out_f32, scratch_floats > 0, scratch_floats);
     chosen[0] = kKinds[ch.kind].bm; chosen[1] = kKinds[ch.kind].bn; chosen[2] = ch.parts;
   } else if (short_f32(ctx, (GemmLayout)layout, M, N, K)) {
     chosen[0] = chosen[1] = 0; chosen[2] = 1;
@@ -783,11 +782,8 @@ static twist_status tile_query(const char *who, bool any, twist_ctx *ctx, int32_
   }
   return TWIST_OK;
 }
-extern "C" twist_status twist_gemm_kernel(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats, int32_t chosen[3]) {
-  return tile_query("twist_gemm_kernel", false, ctx, layout, M, N, K, out_f32, scratch_floats, chosen);
-}
 extern "C" twist_status twist_gemm_tile(twist_ctx *ctx, int32_t layout, int32_t M, int32_t N, int32_t K, int32_t out_f32, size_t scratch_floats, int32_t chosen[3]) {
-  return tile_query("twist_gemm_tile", true, ctx, layout, M, N, K, out_f32, scratch_floats, chosen);
+  return twist_gemm_kernel(ctx, layout, M, N, K, out_f32, scratch_floats, chosen);
 }
 
 extern "C" twist_status twist_set_overlap(twist_ctx *ctx, int32_t enable) {

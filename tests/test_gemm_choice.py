@@ -65,6 +65,20 @@ UNCUT = [
     (1, 1024, 256, 1024, 0, (NEVER, NEVER, 8.0, 5.3)),
     (0, 8192, 2304, 768, 0, (45.0, 46.0, 60.0, NEVER)),
 ]
+# those of them, and of the products below, that run on tiles whose two groups of waves share the contraction: tile, microseconds there and on the fastest of the
+# other kernels, cut where that pays, in one session
+IN_GROUPS = {
+    (0, 4096, 768, 2560, 1): ((128, 96), 24.2, 34.3),
+    (0, 4096, 768, 640, 1): ((128, 96), 11.0, 12.7),
+    (0, 2048, 1536, 512, 1): ((128, 96), 9.9, 11.1),
+    (0, 1000, 2048, 4096, 1): ((128, 96), 26.5, 27.7),
+    (2, 1536, 1536, 2048, 1): ((128, 128), 18.2, 22.9),
+    (2, 768, 4096, 1000, 1): ((128, 128), 13.7, 15.2),
+    (0, 8192, 2304, 768, 0): ((128, 192), 40.1, 43.5),
+    (2, 2816, 2048, 8192, 1): ((192, 128), 93.7, 105.3),
+    (2, 3072, 2048, 8192, 1): ((192, 128), 94.1, 106.2),
+    (2, 2048, 768, 2048, 1): ((64, 96), 13.6, 15.4),
+}
 # TN products with scratch: those of (tile columns, parts of the contraction) within a quarter of the fastest, microseconds
 CUT = [
     (768, 192, 8192, {(64, 6): 15.2, (64, 5): 15.2, (64, 4): 15.3, (64, 7): 15.4, (64, 3): 17.2, (64, 11): 17.9, (64, 14): 18.1, (64, 8): 18.2}),
@@ -94,12 +108,20 @@ def _chosen(lib, cfg, *shape):
 @pytest.mark.parametrize("layout,M,N,K,f32,us", UNCUT)
 def test_bf16_rule_is_near_the_fastest_kernel(lib, layout, M, N, K, f32, us):
     rows, cols, parts = _chosen(lib, si.CFG3, layout, M, N, K, f32, 0)
+    if (layout, M, N, K, f32) in IN_GROUPS:
+        tile, here, others = IN_GROUPS[layout, M, N, K, f32]
+        assert (rows, cols, parts) == (*tile, 1) and here <= 1.2 * others
+        return
     assert parts == 1 and us[((256, 256), (256, 128), (64, 64), (32, 32)).index((rows, cols))] <= 1.2 * min(us)
 
 
 @pytest.mark.parametrize("M,N,K,us", CUT)
 def test_bf16_rule_cuts_a_contraction_where_it_pays(lib, M, N, K, us):
-    _, cols, parts = _chosen(lib, si.CFG3, 2, M, N, K, 1, 1 << 24)
+    rows, cols, parts = _chosen(lib, si.CFG3, 2, M, N, K, 1, 1 << 24)
+    if (2, M, N, K, 1) in IN_GROUPS:
+        tile, here, others = IN_GROUPS[2, M, N, K, 1]
+        assert (rows, cols, parts) == (*tile, 1) and here <= 1.2 * others
+        return
     assert (cols, parts) in us, (cols, parts)
 
 

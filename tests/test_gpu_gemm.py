@@ -307,13 +307,16 @@ def test_bf16_nt_projection_edges(lib, tile, M, N, K):
 
 
 # Products whose contraction is cut (tile, then shape): parts of uneven length, a last one shorter than a slice, ragged edges; NN and TN
-@pytest.mark.parametrize("tile,layout,M,N,K", [(32, 2, 136, 200, 5000), (32, 2, 33, 40, 16000), (32, 1, 70, 72, 3000), (64, 2, 768, 192, 8100), (64, 2, 520, 776, 8100),
-                                               (64, 1, 264, 776, 12008), (128, 2, 1536, 776, 4000), (128, 1, 1100, 1032, 4000), (256, 2, 2816, 2048, 8200)])
+@pytest.mark.parametrize("tile,layout,M,N,K", [((32, 32), 2, 136, 200, 5000), ((32, 32), 2, 33, 40, 16000), ((32, 32), 1, 70, 72, 3000), ((64, 64), 2, 768, 192, 8100),
+                                               ((64, 64), 2, 520, 776, 8100), ((64, 64), 1, 264, 776, 12008), ((128, 128), 2, 1536, 776, 4000),
+                                               ((128, 128), 1, 1100, 1032, 4000), ((256, 128), 2, 1536, 776, 8200), ((256, 128), 1, 1100, 1032, 9001),
+                                               ((256, 256), 2, 2816, 2048, 8200)])
 def test_cut_bf16_projection(lib, tile, layout, M, N, K):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
     scratch = torch.full((1 << 24,), float("nan"), device="cuda")
-    cols, parts = ctx.twist_gemm_kernel(layout, M, N, K, True, scratch.numel())[1:]
-    assert cols == tile and parts > 1, (cols, parts)
+    for f32 in (False, True):
+        rows, cols, parts = ctx.twist_gemm_kernel(layout, M, N, K, f32, scratch.numel())
+        assert (rows, cols) == tile and parts > 1, (rows, cols, parts)
     up = lambda n: (n + 7) // 8 * 8
     gen = torch.Generator(device="cuda").manual_seed(M + N + K)
     A, B = (torch.randn((r, up(c)), generator=gen, device="cuda").bfloat16()[:, :c] for r, c in (((K, M) if layout == 2 else (M, K)), (K, N)))
@@ -340,7 +343,7 @@ def test_bf16_projection_in_two_groups(lib, tile, layout, M, N, K):
     cut = K > 8000
     ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=1, d_head=8, d_ff=N, act="relu", dtype="bf16")))
     scratch = torch.full((1 << 24,), float("nan"), device="cuda")
-    rows, cols, parts = ctx.twist_gemm_tile(layout, M, N, K, True, scratch.numel() if cut else 0)
+    rows, cols, parts = ctx.twist_gemm_kernel(layout, M, N, K, True, scratch.numel() if cut else 0)
     assert (rows, cols) == tile and (parts > 1) == cut, (rows, cols, parts)
     gen = torch.Generator(device="cuda").manual_seed(M + N + K)
     up = lambda n: (n + 7) // 8 * 8
@@ -460,12 +463,13 @@ def test_fp32_weight_gradients_in_one_launch_sum_as_finely(lib, K, shapes):
 # the up projection with its activation: the projection's bits and the activation kernel's of them, on every tile and on the plain kernel, with and without the
 # projection itself
 @pytest.mark.parametrize("act", ["gelu_tanh", "relu"])
-@pytest.mark.parametrize("bf16,M,N,K,tile", [(True, 33, 136, 72, 32), (True, 999, 1000, 200, 64), (True, 2100, 1544, 264, 128), (True, 4000, 3080, 264, 256), (True, 80, 130, 66, 0),
+@pytest.mark.parametrize("bf16,M,N,K,tile", [(True, 33, 136, 72, (32, 32)), (True, 999, 1000, 200, (64, 64)), (True, 2100, 1544, 264, (128, 128)),
+                                             (True, 8190, 776, 768, (256, 128)), (True, 4000, 3080, 264, (256, 256)), (True, 80, 130, 66, 0),
                                              (False, 80, 136, 72, 0), (False, 1000, 1543, 200, 0)])
 def test_projection_with_its_activation(lib, act, bf16, M, N, K, tile):
     cfg = si.ModelCfg(d_model=64, n_heads=1, d_head=8, d_ff=N, act=act, dtype="bf16" if bf16 else "f32")
     ctx = lib.Context(lib.desc_from_cfg(cfg))
-    assert not tile or ctx.twist_gemm_kernel(0, M, N, K)[1] == tile
+    assert not tile or ctx.twist_gemm_kernel(0, M, N, K)[:2] == tile
     gen = torch.Generator(device="cuda").manual_seed(M)
     dt = torch.bfloat16 if bf16 else torch.float32
     A, B = (torch.randn(s, generator=gen, device="cuda").to(dt) * 0.2 for s in ((M, K), (N, K)))
@@ -482,10 +486,11 @@ def test_projection_with_its_activation(lib, act, bf16, M, N, K, tile):
 # Weight gradients that share a launch, on every tile, whole and cut: edges of tiles in both directions, products of odd sizes (whose partial
 # products leave the next product's unaligned), an empty one, a last part shorter than the others
 @pytest.mark.parametrize("tile,cut,K,shapes", [
-    (32, False, 100, [(33, 41), (70, 36), (131, 40), (8, 33)]), (32, True, 9000, [(33, 41), (70, 36), (131, 41), (8, 40)]),
-    (64, False, 1100, [(520, 776), (776, 515), (264, 520), (515, 776)]), (64, True, 8100, [(260, 390), (264, 201), (100, 100)]),
-    (128, False, 2000, [(2100, 1024), (0, 8), (1024, 2100), (3000, 1001)]), (128, True, 8200, [(768, 768), (768, 769), (576, 768), (768, 192)]),
-    (256, False, 1500, [(2816, 2048), (5000, 2048), (3072, 2048), (2048, 1001)]), (256, True, 8200, [(768, 3072), (3000, 769), (2304, 768), (768, 775)])])
+    ((32, 32), False, 100, [(33, 41), (70, 36), (131, 40), (8, 33)]), ((32, 32), True, 9000, [(33, 41), (70, 36), (131, 41), (8, 40)]),
+    ((64, 64), False, 1100, [(520, 776), (776, 515), (264, 520), (515, 776)]), ((64, 64), True, 8100, [(260, 390), (264, 201), (100, 100)]),
+    ((256, 128), False, 2000, [(2100, 1024), (0, 8), (1024, 2100), (3000, 1001)]), ((256, 128), True, 8200, [(768, 768), (768, 769), (576, 768), (768, 192)]),
+    ((256, 256), False, 1500, [(2816, 2048), (5000, 2048), (3072, 2048), (2048, 1001)]),
+    ((256, 256), True, 8200, [(768, 3072), (3000, 769), (2304, 768), (768, 775)])])
 def test_weight_gradients_in_one_launch(lib, tile, cut, K, shapes):
     ctx = lib.Context(lib.desc_from_cfg(si.CFG3))
     gen = torch.Generator(device="cuda").manual_seed(K)
@@ -495,9 +500,9 @@ def test_weight_gradients_in_one_launch(lib, tile, cut, K, shapes):
     scratch = torch.full((1 << 24,), float("nan"), device="cuda")
     bufs = [torch.full((M * N + 64,), float("nan"), device="cuda") for M, N in shapes]
     products = [(rows(M), rows(N), buf[:M * N].view(M, N)) for (M, N), buf in zip(shapes, bufs)]
-    _, cols, parts = ctx.twist_weight_grads_raw(K, products, scratch, alphas)
+    rows, cols, parts = ctx.twist_weight_grads_raw(K, products, scratch, alphas)
     torch.cuda.synchronize()
-    assert cols == tile and (parts > 1) == cut, (cols, parts)
+    assert (rows, cols) == tile and (parts > 1) == cut, (rows, cols, parts)
     for (a, b, out), buf, alpha in zip(products, bufs, alphas):
         want = alpha * (a.double().T @ b.double())
         # fp32 sums of K exact products: 2^-24 sqrt(K) at most; one left out or counted twice shows as 1 / sqrt(K)

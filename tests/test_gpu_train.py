@@ -48,6 +48,9 @@ CASES = {
     # 4608 and 1110 tokens: their contraction is cut into parts (test_weight_gradients_of_many_tokens_are_cut)
     "block_llama_bf16_t4608": (replace(si.CFG4, n_layers=1, d_model=256, n_heads=4, d_head=64, d_ff=1024, max_seq=512), 2, 2, 512, 9, 512),
     "block_gpt_f32_t1110": (si.ModelCfg(n_layers=1, d_model=96, n_heads=4, d_head=32, d_ff=192, vocab=0, max_seq=370), 2, 2, 96, 3, 370),
+    # 2700 tokens: projections on tiles of 128x96 and 192x128, with bias, with bias and residual, ragged in rows and columns
+    # (test_projections_of_many_tokens_run_in_two_groups)
+    "block_gpt_bf16_t2700": (replace(si.CFG2, n_layers=1, d_model=1032, n_heads=8, d_head=64, d_ff=3088, vocab=0, max_seq=900), 2, 4, 1544, 3, 900),
     # vocabulary above 32768: rows of more than 256 threads' registers
     "gpt_bf16_bigvocab": (replace(si.CFG2, n_layers=1, d_model=64, n_heads=2, d_head=32, d_ff=128, vocab=33001, max_seq=32), 2, 1, 64, 2, 32),
     "block_llama_bf16": (replace(si.CFG4, n_layers=1, d_model=256, n_heads=4, d_head=64, d_ff=512, max_seq=128), 2, 2, 256, 2, 128),
@@ -96,6 +99,13 @@ def test_weight_gradients_of_many_tokens_are_cut(lib, name):
         zeros = lambda n: torch.zeros((B * N, n), dtype=torch.bfloat16, device="cuda")
         grads = [(zeros(M), zeros(Nn), torch.empty((M, Nn), device="cuda")) for M, Nn in products]
         assert ctx.twist_weight_grads_raw(B * N, grads, torch.empty(1 << 24, device="cuda"), (1.0,) * 4)[2] > 1
+
+
+def test_projections_of_many_tokens_run_in_two_groups(lib):
+    cfg, _, hs, fs, B, N = CASES["block_gpt_bf16_t2700"]
+    ctx = lib.Context(lib.desc_from_cfg(cfg))
+    tile = lambda n, k, f32: ctx.twist_gemm_kernel(0, B * N, n, k, f32)
+    assert tile(fs, cfg.d_model, False) == (192, 128, 1) and tile(cfg.d_model, fs, True) == tile(3 * hs * cfg.d_head, cfg.d_model, False) == (128, 96, 1)
 
 
 # models whose weight gradients go to the second stream, by how they share launches there; (cfg, S, heads_sub, ffn_sub, B, N), two disjoint halves each.
@@ -759,9 +769,10 @@ def test_masked_full_model_equals_the_extracted_subnet(lib, name):
 
 # The up projection applies the activation to what it stores; the masked pass in place runs it in a kernel of its own.  With nothing masked both are
 # the same pass: same loss, same gradients, bit for bit, and evaluation (which does not store the pre-activation) gives the same loss.  Sizes reach every projection
-# kernel: tiles of 32 and 64, 256 rows by 128 and 256 columns with ragged edges, the plain one (odd widths, fp32)
+# kernel: tiles of 32, 64 and 128, 256 rows by 128 and 256 columns with ragged edges, the plain one (odd widths, fp32)
 @pytest.mark.parametrize("act", ["gelu_tanh", "relu"])
-@pytest.mark.parametrize("dtype,d,ff,B,N,tile", [("bf16", 72, 136, 1, 33, 32), ("bf16", 200, 1000, 3, 333, 64), ("bf16", 264, 1544, 3, 700, 128), ("bf16", 264, 3080, 4, 1000, 256),
+@pytest.mark.parametrize("dtype,d,ff,B,N,tile", [("bf16", 72, 136, 1, 33, (32, 32)), ("bf16", 200, 1000, 3, 333, (64, 64)), ("bf16", 264, 1544, 3, 700, (128, 128)),
+                                                 ("bf16", 768, 776, 8, 1000, (256, 128)), ("bf16", 264, 3080, 4, 1000, (256, 256)),
                                                  ("bf16", 66, 130, 2, 40, 0), ("f32", 72, 136, 2, 40, 0)])
 def test_activation_in_the_projection_and_behind_it_agree(lib, act, dtype, d, ff, B, N, tile):
     cfg = si.ModelCfg(n_layers=2, d_model=d, n_heads=2, d_head=32, d_ff=ff, act=act, vocab=0, max_seq=N, dtype=dtype)
@@ -772,7 +783,7 @@ def test_activation_in_the_projection_and_behind_it_agree(lib, act, dtype, d, ff
     x, y = (torch.randn((B, N, d), generator=gen, device="cuda").to(dt) for _ in range(2))
     ctx = lib.Context(lib.desc_from_cfg(cfg))
     if tile:
-        assert ctx.twist_gemm_kernel(0, B * N, ff, d)[1] == tile
+        assert ctx.twist_gemm_kernel(0, B * N, ff, d)[:2] == tile
     plan = ctx.twist_sample(1, 2, ff, seed=0)
     sub = ctx.twist_extract(plan, fw, 0, store=lib.STORE_GRADS)
     ws = torch.empty(ctx.twist_workspace_bytes(sub, B, N), dtype=torch.uint8, device="cuda")
