@@ -712,7 +712,7 @@ twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGra
 }
 
 void twist_gemm_estimate(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, size_t split_floats, GemmEstimate &sum) {
-  const Choice ch = choose(lay, n, Ms, Ns, K, f32_out, split_floats > 0, split_floats);
+  const Choice ch = choose_any(lay, n, Ms, Ns, K, f32_out, split_floats > 0, split_floats);
   sum.us += ch.us;
   sum.idle += ch.idle;
 }

@@ -153,16 +153,18 @@ struct Schedule {
   // more than the overlap gives.  Forward and backward of 6 layers, us, second stream / one stream:
   //   bf16 (apart), 0.05 GFLOP 974 / 596    0.8 983 / 744    3.2 1012 / 897    12.9 1338 / 1316   (pairs / one launch) 14.5 1490 / 1522    21 2013 / 2079
   //   fp32          0.9 GFLOP 1263 / 1048   1.1 1454 / 1222   2.1 1598 / 1433   3.2 1604 / 1571   6.4 2013 / 1991   7.2 2034 / 2083   14.5 2964 / 3097
-  // Where the chain and one launch of all gradients leave few CUs idle, and that launch is well shorter than the others, the streams only
-  // contend; of 95 bf16 models of 13 to 3400 GFLOP a layer the rule takes the slower form at most 1.4 % to its cost, but for one (768 x 4096,
-  // 4 %).  d x tokens, us, pairs on the second stream / one launch: 768 x 8192 2149 / 2093, 1024 x 8192 4271 / 4123, 1024 x 2048 2479 / 2346;
-  // and on the other side of the line 768 x 6144 2701 / 2951, 2048 x 3000 3376 / 3530, 1600 x 8192 3891 / 4152.
+  // The second stream's launches fill the CUs that the chain and they themselves leave idle, which one launch does not do; but it is the shorter one
+  // for small layers, and has no events, waits and gaps (about 14 us a layer).  Estimates are of the kernels that run.  Of 126 bf16 models of 13 to 1900
+  // GFLOP a layer the form taken is 0.4 % above the fastest on average, and 2 to 6 % for 11 of them.  d x tokens (columns of heads, hidden), us of a
+  // pass of 6 layers, second stream / one launch: 768 x 2048 (384, 1536) 1390 / 1317, 576 x 6144 (128, 1152) 1846 / 1718, 768 x 8192 (768, 3072) 5110 / 4938,
+  // 1024 x 1024 (1024, 1408 gated) 1587 / 1450; and on the other side of the line 896 x 6144 (512, 2464 gated) 3570 / 3709, 1536 x 2048 (384, 3072) 2270 / 2349,
+  // 2560 x 4096 (2560, 5120) 10089 / 11071.
   void choose(bool bf16, int T, int D, int heads, int F, int nf) {
     const double flop = 2.0 * T * D * (4.0 * heads + (nf + 1.0) * F);
     whole = flop < (bf16 ? 13e9 : 3e9);
     if (!whole && bf16) {
-      // a launch for two where it is expected to take a tenth less than two launches: 2048 x 768 x (512, 2048) 31 / 44 and 22 / 34 us; not the
-      // FFN's of 8192 x 2048 x 2816, whose 264 tiles would take two rounds: 406 / 301
+      // a launch for two where it is expected to take a twentieth less than two launches: 1536 x 3000 (1536, 3072) 3830 a pass, apart 4029; not the FFN's
+      // of 8192 x 2048 x 2816, whose 264 tiles would take two rounds: 10417, 9853.  (Without the twentieth 126 models take 0.2 % longer on average.)
       const int f = nf * F, q = 3 * heads, Ms[4] = {D, f, D, q}, Ns[4] = {F, D, heads, D};
       GemmEstimate chain, one[4], two[2], all;
       twist_gemm_estimate(GEMM_NN, 1, &T, &F, D, false, 0, chain);
@@ -172,10 +174,17 @@ struct Schedule {
       for (int i = 0; i < 4; ++i) twist_gemm_estimate(GEMM_TN, 1, Ms + i, Ns + i, T, true, kSplitkFloats, one[i]);
       for (int i = 0; i < 2; ++i) twist_gemm_estimate(GEMM_TN, 2, Ms + 2 * i, Ns + 2 * i, T, true, kSplitkFloats, two[i]);
       twist_gemm_estimate(GEMM_TN, 4, Ms, Ns, T, true, kSplitkFloats, all);
-      ffn_pair = two[0].us < 0.9 * (one[0].us + one[1].us);
-      attn_pair = two[1].us < 0.9 * (one[2].us + one[3].us);
-      const double halves = std::min(two[0].us, one[0].us + one[1].us) + std::min(two[1].us, one[2].us + one[3].us);
-      whole = chain.idle + all.idle <= 0.18 * (chain.us + all.us) && all.us <= 0.85 * halves;
+      bool pair[2];
+      GemmEstimate side = chain;  // the chain, and the launches of the second stream
+      for (int i = 0; i < 2; ++i) {
+        const GemmEstimate apart{one[2 * i].us + one[2 * i + 1].us, one[2 * i].idle + one[2 * i + 1].idle}, &less = two[i].us < apart.us ? two[i] : apart;
+        pair[i] = two[i].us < 0.95 * apart.us;
+        side.us += less.us;
+        side.idle += less.idle;
+      }
+      ffn_pair = pair[0];
+      attn_pair = pair[1];
+      whole = chain.us + all.us + side.idle < side.us + 14.0;
     }
   }
 };

@@ -111,10 +111,10 @@ def test_projections_of_many_tokens_run_in_two_groups(lib):
 # models whose weight gradients go to the second stream, by how they share launches there; (cfg, S, heads_sub, ffn_sub, B, N), two disjoint halves each.
 # (So many token ids that hardly one occurs three times in a batch: two atomic additions to a cleared row give the same bits in either order.)
 TWO_STREAMS = {
-    "attention_paired": (replace(si.CFG3, n_layers=2, d_model=1024, n_heads=4, d_ff=1408, vocab=8009, max_seq=1024), 2, 2, 704, 2, 1024),
+    "attention_paired": (replace(si.CFG3, n_layers=2, d_model=1536, n_heads=6, d_ff=7360, vocab=8009, max_seq=1000), 2, 3, 3680, 1, 1000),
     "ffn_and_attention_paired": (replace(si.CFG3, n_layers=2, d_model=2048, n_heads=14, d_ff=4976, vocab=8009, max_seq=1000), 2, 7, 2488, 1, 1000),
-    "ffn_paired": (replace(si.CFG2, n_layers=2, n_heads=12, d_ff=3072, vocab=8009, max_seq=1024), 2, 6, 1536, 2, 1024),
-    "apart": (replace(si.CFG2, n_layers=2, n_heads=24, d_ff=1408, vocab=8009, max_seq=1024, out_unit_major=True), 2, 12, 704, 2, 1024),
+    "ffn_paired": (replace(si.CFG2, n_layers=2, d_model=2304, n_heads=60, d_ff=1200, vocab=8009, max_seq=1000), 2, 30, 600, 1, 1000),
+    "apart": (replace(si.CFG2, n_layers=2, d_model=2304, n_heads=60, d_ff=8128, vocab=8009, max_seq=1024, out_unit_major=True), 2, 30, 4064, 1, 1024),
     "apart_f32": (replace(si.CFG2, n_layers=2, n_heads=12, d_ff=3072, vocab=8009, max_seq=512, dtype="f32"), 2, 6, 1536, 2, 512),
 }
 
@@ -879,8 +879,8 @@ def test_schedules_agree_eagerly_and_in_a_graph(lib, case):
     ("gpt_bf16", replace(si.CFG2, n_layers=2, d_model=256, n_heads=4, d_ff=512, vocab=1003, max_seq=256), 1, 256, None, 8, 200),
     ("llama_bf16_um", replace(si.CFG3, n_layers=2, d_model=256, n_heads=4, d_ff=704, vocab=517, max_seq=256, out_unit_major=True), 2, 352, None, 8, 256),
     ("llama_bf16_heads_whole", replace(si.CFG3, n_layers=2, d_model=256, n_heads=4, d_ff=704, vocab=517, max_seq=256), 4, 176, None, 8, 256),
-    ("two_streams", replace(si.CFG3, n_layers=2, d_model=1024, n_heads=4, d_ff=1408, vocab=517, max_seq=1024), 2, 704, None, 2, 1024),
-    ("two_streams_in_pairs", replace(si.CFG3, n_layers=2, d_model=256, n_heads=16, d_ff=1408, vocab=517, max_seq=2048), 8, 704, None, 2, 2048)])
+    ("two_streams", replace(si.CFG3, n_layers=2, d_model=1536, n_heads=8, d_ff=7360, vocab=517, max_seq=1000), 4, 3680, None, 2, 1000),
+    ("two_streams_in_pairs", replace(si.CFG3, n_layers=2, d_model=256, n_heads=20, d_ff=2816, vocab=517, max_seq=1000), 10, 1408, None, 3, 1000)])
 def test_masked_pass_on_the_kept_blocks_is_the_extracted_subnets_pass(lib, name, cfg, hs, fs, shared, B, N):
     S = 4
     gen = torch.Generator(device="cuda").manual_seed(7)
