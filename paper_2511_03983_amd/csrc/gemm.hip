@@ -422,8 +422,10 @@ constexpr Kind kKinds[] = {{256, 256, 1.0, 9.1, 0.36, 0.434, 0.32, {1, 1, 1}}, {
 // Two groups that share the contraction (gemm_kp.hip).  Fitted to 600 products of their own, sizes 64 to 50257 (half of the estimates within
 // 4 %, 8 % for 64x96; nine tenths within 13 and 18 %).  They are taken where they are expected to be a twelfth faster than the others: of 200
 // products not fitted to, 33 then went to them, 20 % faster on average and one slower, by 4.6 %; with the bare estimates 43, one of them
-// 23 % slower.  Launches of fewer than 128 tiles (2048 x 896 x 3000, TN, 112 of 128x128: 22.8 us, 64x64 20.8) and of more than four rounds
-// (50257 x 280 x 7007, TN: 383, 256x256 329) are left out, and contractions beyond 8192 (choose_any).  us, the others' fastest / these:
+// 23 % slower.  Launches of fewer than 128 tiles (2048 x 896 x 3000, TN, 112 of 128x128: 22.8 us, 64x64 20.8), of fewer than 170 tiles of 96 columns, whose
+// CUs have too little in flight where operands come from memory (37 products 4 % faster with operands in the caches, 8 % slower otherwise; 1536 x 1024 x
+// 4096, NN, 132 tiles 26.2 / 28.0 and 29.9 / 36.4; 51 of 170 to 192 tiles 24 and 13 % faster), and of more than four rounds (50257 x 280 x 7007, TN: 383,
+// 256x256 329) are left out, and contractions beyond 8192 (choose_any).  us, the others' fastest / these:
 //   8192 x 768 x 768            16.2 / 15.2 (128x192)      2048 x 768 x 2048 (f32)       15.3 / 11.8 (64x96)
 //   4096 x 768 x 2560 (f32)     30.4 / 21.1 (128x96)       2048 x 1536 x 768             13.0 /  9.9 (128x96)
 //   2048 x 2048 x 768           16.0 / 11.4 (128x128)      3000 x 2048 x 2488 (f32)      48.3 / 39.2 (192x128)
@@ -461,7 +463,7 @@ Choice choose_of(int first, int last, GemmLayout lay, int n, const int *Ms, cons
     for (int parts = 1; parts <= most_parts; ++parts) {
       if (parts > 1 && (K < 256 * parts || parts * outputs > (double)split_floats)) break;
       const int64_t items = tiles * parts, rounds = (items + 255) / 256;
-      if (k >= kOneGroup && (items < 128 || items > 1024 || chain_of(k, parts, K) > longest)) continue;
+      if (k >= kOneGroup && (items < (kd.bn == 96 ? 170 : 128) || items > 1024 || chain_of(k, parts, K) > longest)) continue;
       const double share = std::min(1.0, items / 256.0), slice = (kd.s0 + kd.s1 * share) * kd.lay[lay];
       double us = kd.fixed + rounds * (kd.tile + (f32_out || parts > 1 ? kd.tile32 : 0.0) + K / 32.0 / parts * slice);
       if (parts > 1) us += 4.4 + (parts + 1.0) * outputs * 4.0 / 2.8e6;
@@ -474,15 +476,18 @@ Choice choose_of(int first, int last, GemmLayout lay, int n, const int *Ms, cons
 Choice choose(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, bool may_split, size_t split_floats) {
   return choose_of(0, kOneGroup, lay, n, Ms, Ns, K, f32_out, may_split ? 16 : 1, split_floats);
 }
-// all kernels.  Those of gemm_kp.hip cut a contraction no further than the others would, and sum no more coarsely.  Where it is longer than any batch (the vocabulary's input
-// gradient) they wait for memory: a CU has 120 KB in flight, and operands that come from beyond the caches take 2 us and more to arrive; us, the others /
-// these: 8192 x 768 x 50257 778 / 741, 4096 x 512 x 50257 241 / 305, 1500 x 1024 x 32000 116 / 137, 8192 x 2048 x 32000 817 / 1074.
-// Of the small tiles two share a CU, and their second round is shorter than the estimate has it (a tenth of the whole time): 0.82 there.
+// all kernels.  Those of gemm_kp.hip cut a contraction no further than the others would, and sum no more coarsely.  Where it is as long as a vocabulary (its
+// input gradient) they wait for memory: a CU has 120 KB in flight, and operands that come from beyond the caches take 2 us and more to arrive; us, the
+// others / these: 8192 x 768 x 50257 778 / 741, 4096 x 512 x 50257 241 / 305, 1500 x 1024 x 32000 116 / 137, 8192 x 2048 x 32000 817 / 1074.  8192 is the longest
+// they were fitted to, not where they cross: of longer ones some are faster (2816 x 2048 x 8200, TN, 121 / 108, 768 x 768 x 32768 78 / 66).
+// Of the small tiles two share a CU, and their second round is shorter than the estimate has it (a tenth of the whole time): 0.82 there.  Tiles of 256x256
+// suffer less from operands in memory: 11 products expected at 0.88 to 0.92 of their time took 0.99 with operands in the caches and 1.14 otherwise (8192 x 2304 x
+// 768 43.5 / 40.1 and 42.9 / 49.8); 105 of 256x128 0.96 and 1.01.
 Choice choose_any(GemmLayout lay, int n, const int *Ms, const int *Ns, int K, bool f32_out, bool may_split, size_t split_floats) {
   const Choice one = choose(lay, n, Ms, Ns, K, f32_out, may_split, split_floats);
   if (K > 8192) return one;
   const Choice two = choose_of(kOneGroup, kAllKinds, lay, n, Ms, Ns, K, f32_out, one.parts, split_floats, chain_of(one.kind, one.parts, K));
-  return two.us < (one.kind >= 2 && one.items > 256 ? 0.82 : 0.92) * one.us ? two : one;
+  return two.us < (one.kind >= 2 && one.items > 256 ? 0.82 : one.kind == 0 ? 0.88 : 0.92) * one.us ? two : one;
 }
 
 // kernel, parts of the contraction and their length of a bf16 product whose operands are aligned; `any`: among all kernels

@@ -74,7 +74,6 @@ IN_GROUPS = {
     (0, 1000, 2048, 4096, 1): ((128, 96), 26.5, 27.7),
     (2, 1536, 1536, 2048, 1): ((128, 128), 18.2, 22.9),
     (2, 768, 4096, 1000, 1): ((128, 128), 13.7, 15.2),
-    (0, 8192, 2304, 768, 0): ((128, 192), 40.1, 43.5),
     (2, 2816, 2048, 8192, 1): ((192, 128), 93.7, 105.3),
     (2, 3072, 2048, 8192, 1): ((192, 128), 94.1, 106.2),
     (2, 2048, 768, 2048, 1): ((64, 96), 13.6, 15.4),
@@ -113,6 +112,22 @@ def test_bf16_rule_is_near_the_fastest_kernel(lib, layout, M, N, K, f32, us):
         assert (rows, cols, parts) == (*tile, 1) and here <= 1.2 * others
         return
     assert parts == 1 and us[((256, 256), (256, 128), (64, 64), (32, 32)).index((rows, cols))] <= 1.2 * min(us)
+
+
+# products that tiles whose two groups of waves share the contraction make slower where their operands come from memory, and hardly faster otherwise: layout, M, N, K,
+# fp32 output, tile, microseconds (operands in the caches, in memory) there and on those tiles
+OTHERWISE = [
+    (1, 1536, 1024, 4096, 0, (64, 64), (26.2, 29.9), (28.0, 36.4)),
+    (1, 1504, 1088, 4480, 0, (64, 64), (29.2, 30.5), (30.2, 39.1)),
+    (1, 3008, 576, 7744, 0, (64, 64), (49.2, 51.3), (48.6, 71.6)),
+    (0, 1424, 576, 8128, 1, (64, 64), (30.2, 38.9), (33.1, 43.9)),
+    (0, 8192, 2304, 768, 0, (256, 256), (43.5, 42.9), (40.1, 49.8)),
+]
+
+
+@pytest.mark.parametrize("layout,M,N,K,f32,tile,here,others", OTHERWISE)
+def test_bf16_rule_minds_operands_in_memory(lib, layout, M, N, K, f32, tile, here, others):
+    assert sum(here) < sum(others) and _chosen(lib, si.CFG3, layout, M, N, K, f32, 0) == (*tile, 1)
 
 
 @pytest.mark.parametrize("M,N,K,us", CUT)

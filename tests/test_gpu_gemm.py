@@ -336,7 +336,7 @@ def test_cut_bf16_projection(lib, tile, layout, M, N, K):
 # slice, on an odd and on an even one; cut; with alpha, and with the activation of the up projection
 @pytest.mark.parametrize("tile,layout,M,N,K", [
     ((64, 96), 0, 326, 3333, 856), ((128, 96), 0, 3527, 844, 208), ((128, 128), 0, 787, 3836, 200), ((128, 192), 0, 1619, 3636, 808), ((192, 128), 0, 1309, 3077, 648),
-    ((64, 96), 1, 3417, 267, 887), ((128, 96), 1, 1374, 2178, 219), ((128, 128), 1, 1647, 1881, 209), ((128, 192), 1, 1578, 3605, 976), ((192, 128), 1, 1038, 3635, 730),
+    ((64, 96), 1, 3611, 267, 887), ((128, 96), 1, 1374, 2178, 219), ((128, 128), 1, 1647, 1881, 209), ((128, 192), 1, 1578, 3605, 976), ((192, 128), 1, 1038, 3635, 730),
     ((64, 96), 2, 2729, 323, 943), ((128, 96), 2, 2942, 1040, 210), ((128, 128), 2, 1932, 1571, 203), ((128, 192), 2, 2306, 2462, 890), ((192, 128), 2, 1035, 3598, 637),
     ((128, 128), 2, 1020, 2045, 8190)])
 def test_bf16_projection_in_two_groups(lib, tile, layout, M, N, K):
