@@ -13,7 +13,7 @@
 // Tiles of 32, for few rows: gemm_f32_small_kernel, on the fp32 instruction (v_mfma_f32_32x32x2_f32): there every value would be split into
 // its terms for 32 products only.
 //
-// gemm_f32_wave_kernel, tiles of 64 whose operands allow 16-byte loads.  What bounded such tiles in gemm_f32_kernel was neither the matrix
+// gemm_f32_wave_kernel, tiles of 64 whose operands allow 16-byte loads, contractions from 320 on (launch_tile).  What bounded such tiles in gemm_f32_kernel was neither the matrix
 // pipes nor the loads but LDS and what it is fed with: three terms of 2 bytes written and, by waves of 32x32, read twice, a barrier for every
 // slice, and two waves a SIMD in step (1.2 us per slice of 64 where the instructions take 0.35 and forming the terms 0.47).  Here every wave forms
 // the whole tile over steps of 16 k of its own, so that
@@ -731,6 +731,7 @@ void launch(hipStream_t st, int M, int N, int K, const float *A, int64_t lda, co
   hipLaunchKernelGGL((gemm_f32_kernel<AKM, BKM, BM, W2, WK, BK, VEC>), dim3(tm * tn, parts), dim3(64 * W2 * W2 * WK), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
 }
 
+constexpr int kWaveK = 320;  // shortest contraction for which tiles of 64 are gemm_f32_wave_kernel's
 template <int AKM, int BKM, int VEC>
 void launch_tile(hipStream_t st, int tile, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, const Ep32 &ep, int parts, int kchunk) {
   if (tile == 128) return launch<AKM, BKM, 128, 2, 2, 32, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
@@ -738,13 +739,18 @@ void launch_tile(hipStream_t st, int tile, int M, int N, int K, const float *A, 
     const int tm = (M + 63) / 64, tn = (N + 63) / 64;
     const bool one = (int64_t)tm * tn * parts <= 256;
     if constexpr (VEC) {
-      if (one) hipLaunchKernelGGL((gemm_f32_wave_kernel<AKM, BKM, 8>), dim3(tm * tn, parts), dim3(512), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
-      else hipLaunchKernelGGL((gemm_f32_wave_kernel<AKM, BKM, 4>), dim3(tm * tn, parts), dim3(256), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
-    } else if (one) {  // slices of 64; more than one tile per CU: of 32, two workgroups to a CU
-      launch<AKM, BKM, 64, 2, 2, 64, 0>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
-    } else {
-      launch<AKM, BKM, 64, 2, 2, 32, 0>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
+      // shorter contractions are a few steps to a wave, and the addition of the waves' sums and the fixed time weigh more than what the steps save (us,
+      // gemm_f32_kernel / waves: 1024 x 768 x 64 5.8 / 6.7, 3000 x 3072 x 64 28.1 / 30.8, 4096 x 512 x 128 9.5 / 10.3, 192 11.7 / 12.0, 256 13.6 / 14.1; 1024 x 768
+      // x 320 10.1 / 9.9, x 384 11.6 / 11.3), but where the last slice of 64 would be half empty (1024 x 768 x 96 7.2 / 7.1, 160, NN, 8.5 / 8.0)
+      if (K >= kWaveK || (one && K > 64 && (K + 31) / 32 % 2 == 1)) {
+        if (one) hipLaunchKernelGGL((gemm_f32_wave_kernel<AKM, BKM, 8>), dim3(tm * tn, parts), dim3(512), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
+        else hipLaunchKernelGGL((gemm_f32_wave_kernel<AKM, BKM, 4>), dim3(tm * tn, parts), dim3(256), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
+        return;
+      }
     }
+    // slices of 64; more than one tile per CU: of 32, two workgroups to a CU
+    if (one) launch<AKM, BKM, 64, 2, 2, 64, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
+    else launch<AKM, BKM, 64, 2, 2, 32, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
     return;
   }
   const int tm = (M + 31) / 32, tn = (N + 31) / 32;
@@ -758,7 +764,7 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 double chain_of(int tile, bool vec, int64_t items, double k) { return tile == 32 ? 2.4 * k : tile == 64 && vec ? k / (items <= 256 ? 8 : 4) : k / 2; }
 
 // Tile and number of parts of the contraction, by estimated time of the kernels above (us); n = items (tiles, times parts) on the busiest of
-// 256 CUs.  Operands that allow 16-byte loads:
+// 256 CUs.  Operands that allow 16-byte loads, K >= 320 or several products:
 //   128: 3 + n (8.4 + 1.55 per slice of 32)
 //   64: one a CU 6.3 + (0.55 to 0.77, the whole chip at work) per 64 of the contraction, two 7.4 + (1.2 to 1.55), from then on 4.5 + 2.05 n + 0.745 n,
 //   and 0.25 for an odd n, per 64
@@ -766,7 +772,7 @@ double chain_of(int tile, bool vec, int64_t items, double k) { return tile == 32
 //   sum of a cut one 4 + its bytes at 4.5 TB/s.
 // Fitted to 180 products of 48 to 8000 tiles of 64, K = 64 to 4096 (measured; 128 / 64 / 32): 1024 x 768 x 768 43.4 / 15.4 / -, 1024 x 1024 x 4096 186 / 61 / -,
 // 1024 x 1152 x 768 43.6 / 22.6 / 30.4, 2048 x 1024 x 1536 80 / 45 / -, 1536 x 1408 x 768 44.5 / 39.4 / -, 2048 x 2048 x 768 48.5 / 49.6 / -,
-// 4096 x 1536 x 768 90 / 70 / -, 4096 x 4096 x 64 48.9 / 47.6 / -, 4096^3 824 / 797 / -, 512 x 384 x 768 40 / 14 / 10.4; 1500 x 1500 x 2000 (TN) 117 / 93 / -, in two
+// 4096 x 1536 x 768 90 / 70 / -, 4096^3 824 / 797 / -, 512 x 384 x 768 40 / 14 / 10.4; 1500 x 1500 x 2000 (TN) 117 / 93 / -, in two
 // parts 133 / 88 / 137, in four 113 / 92 / -; 1024 x 768 x 8000 - / 83 / -, in four parts 111 / 93 / -; 3072 x 768 x 8192 (TN) 396 / 332 / 417, in four 332 / 260 / -.
 // Others (64 in gemm_f32_kernel): 128 3 + n (6 + 1.47 per slice of 32); 64 one a CU 4.3 + 1.2 per slice of 64, more in pairs, 2 (1.9 + 0.48 per slice of 32),
 // a single one left over in the second round 1.9 + 0.85 per slice, and from then on the rounds run into each other; 32 as above.  Rows contiguous in
@@ -817,7 +823,7 @@ Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bo
 void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool vec, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
   const bool split = may_split && !ctx->gemm_tile;
   Choice ch = choose(lay, 1, &M, &N, K, false, split, split_floats);
-  if (vec) ch = choose(lay, 1, &M, &N, K, true, split, split_floats, chain_of(ch.tile, false, 0, (double)K / ch.parts));
+  if (vec && K >= kWaveK) ch = choose(lay, 1, &M, &N, K, true, split, split_floats, chain_of(ch.tile, false, 0, (double)K / ch.parts));
   if (ctx->gemm_tile) ch = {ctx->gemm_tile == 128 ? 128 : 64, 1};
   const int bk = ch.tile == 128 ? 32 : 64;
   kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;

@@ -215,6 +215,29 @@ def test_fp32_tiles_of_64_sum_as_finely_as_tiles_of_128(lib, layout, size, K):
     assert err[1] <= 1.02 * err[0], err
 
 
+# contractions below 320 in tiles of 64 keep the kernel whose waves share every slice, the one of rows that are not aligned: the same bits.  (Not where one
+# tile a CU has a last slice of 64 that is half empty, and not from 320 on)
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K,same", [(264, 328, 64, True), (1000, 772, 48, True), (1024, 768, 128, True), (1028, 772, 244, True), (2048, 1028, 96, True), (1500, 1540, 316, True),
+                                        (1024, 768, 96, False), (1028, 772, 320, False), (1500, 1540, 320, False)])
+def test_fp32_short_contractions_in_tiles_of_64(lib, layout, M, N, K, same):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    ctx.twist_set_kernel_choice(gemm_tile=256)
+    assert ctx.twist_gemm_kernel(layout, M, N, K, True)[0] == 64
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.randn((K, M) if layout == 2 else (M, K), generator=gen, device="cuda")
+    B = torch.randn((N, K) if layout == 0 else (K, N), generator=gen, device="cuda")
+    odd = lambda x: torch.cat((x[:, :1], x), 1)[:, 1:]
+    bufs = [torch.full((M * N + 64,), float("nan"), device="cuda") for _ in range(2)]
+    outs = [buf[:M * N].view(M, N) for buf in bufs]
+    ctx.twist_gemm_raw(layout, M, N, K, odd(A), odd(B), outs[0])
+    ctx.twist_gemm_raw(layout, M, N, K, A, B, outs[1])
+    torch.cuda.synchronize()
+    want = (A.double().T if layout == 2 else A.double()) @ (B.double().T if layout == 0 else B.double())
+    assert torch.equal(*outs) == same and all(torch.isnan(buf[M * N:]).all() for buf in bufs)
+    assert float((outs[1].double() - want).norm() / want.norm()) <= 1e-6
+
+
 # aligned operands take kernels of their own: their sums are no coarser than those of the same product on rows that are not aligned.  Products that the
 # fp32 instruction, a shorter cut of the contraction or fewer waves to a tile would give a larger error for (1.3 to 3.7 times), and some where the
 # kernels agree.  (3 % for the norm over 1e5 outputs and more)
