@@ -369,8 +369,10 @@ bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 // Eight waves to a workgroup where there are few workgroups to a CU and more tiles of 32 in a sequence than four waves: the chain of a wave is half as
 // long, and a second wave a SIMD works while the first waits for operands.  Forward / forward and backward, fp32, us, four waves and eight: 2 x 512
 // tokens, 6 heads of 64 19.5 / 81.8 and 18.4 / 77.6; 1 x 2048, 6 of 64 (384 workgroups) 73 / 283 and 55 / 241; 1 x 4096, 4 of 32 (512) 86 / 346 and
-// 63 / 275; 4 x 1024, 8 of 64 (1024) 69 / 332 and 72 / 312.  Heads of 128 do not fit the registers of a wave among eight.
-static bool wide_of(int64_t workgroups, int N) { return workgroups <= 512 && N > 128; }
+// 63 / 275; 4 x 1024, 8 of 64 (1024) 69 / 332 and 72 / 312.  Of a short sequence's rows few see tiles for eight waves, and the others' wait in
+// workgroups that share a CU: 160 tokens, 40 workgroups 11.9 / 48 and 11.8 / 43, 320 13 / 57 and 16 / 62, 480 14 / 71 and 19 / 73; 256 tokens, 192 12.6 / 50 and 13 / 50, 512
+// 16 / 76 and 20 / 79; 288 tokens, 288 16.5 / 65 and 16 / 64, 504 20 / 90 and 22 / 89.  Heads of 128 do not fit the registers of a wave among eight.
+static bool wide_of(int64_t workgroups, int N) { return N > 128 && workgroups <= (N <= 256 ? 256 : N <= 320 ? 384 : 512); }
 
 bool twist_attention_f32_ok(const twist_ctx *ctx, const void *qkv, const void *o, const void *dout, const void *dqkv, int dh) {
   return !ctx->plain_only && dh % 4 == 0 && dh <= 128 && al16(qkv) && al16(o) && al16(dout) && al16(dqkv);

@@ -404,6 +404,20 @@ def test_fp32_attention_of_few_and_many_workgroups(lib, dh, N):
         assert rel_fro(to_numpy(b[0]), to_numpy(a)) <= (6e-6 if i < 2 else 2e-5), i
 
 
+# ... and sequences of a few tiles more than four waves have four to a workgroup as soon as there are more workgroups than CUs: the bits of the same ones among many
+@pytest.mark.parametrize("dh", [32, 64])
+@pytest.mark.parametrize("N,B", [(129, 18), (160, 18), (256, 11), (257, 15), (320, 13)])
+def test_fp32_attention_of_short_sequences_on_full_cus(lib, dh, N, B):
+    Hs, many = 3, 40
+    ctx = lib.Context(lib.desc_from_cfg(si.ModelCfg(d_model=64, n_heads=Hs, d_head=dh, d_ff=8, max_seq=N)))
+    assert (256 if N <= 256 else 384) < (N + 31) // 32 * Hs * B <= 512 < (N + 31) // 32 * Hs * many
+    qkv = _dev(_snap(si.normal(dh + N, "qkv", (N, 3 * Hs * dh)), F32), F32)
+    dout = _dev(_snap(si.normal(N, "dout", (N, Hs * dh)), F32), F32)
+    some, more = (ctx.twist_attention_raw(qkv.repeat(n, 1), dout.repeat(n, 1), n, N, Hs) for n in (B, many))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b[:len(a)]) for a, b in zip(some, more))
+
+
 # An infinity or a NaN in one token's value, key, query or output gradient: what does not depend on it keeps its bits (earlier queries'
 # outputs and gradients; for a query or an output gradient, later keys' too), and what the plain kernels, which visit visible pairs only,
 # compute as finite is finite.  Tokens inside a 32-row tile, at its edges and last of a ragged one.  (bf16 at 128 and 256 tokens: the 64-row workgroups with
