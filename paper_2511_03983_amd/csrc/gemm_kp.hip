@@ -1,8 +1,8 @@
 // bf16 projections of middling size: workgroup tiles of 64 to 192 rows and columns, one for (almost) every CU, where tiles of 256 rows would
 // leave CUs idle and tiles of 64x64 fetch everything many times.
 //
-// What bounds such a product is the path from the L2 into LDS (about 100 B/ns and CU, loads alone: 4096 x 768 x 2560 in 128x96 tiles 19.2 of
-// 20.7 us, products alone 11.1, fragment reads alone 11.0), then LDS itself.  Hence
+// What bounds such a product is the path from the L2 into LDS (4096 x 768 x 2560 in 128x96 tiles, 1.15 MB to a CU: loads alone 19.2 of 20.7 us, products
+// alone 11.1, fragment reads alone 11.0; 60 B/ns and CU over the whole launch, 71 from slice to slice), then LDS itself.  Hence
 //  - the largest tile that still gives the CUs one each, and slices 64 deep, so that a row of a k-contiguous operand comes in whole lines;
 //  - the two groups of four waves (one of each per SIMD) take every second slice of the whole tile instead of half the tile each: a
 //    wave's part of the tile stays large (64x48 of 128x96), and a slice's fragments are read from LDS by four waves, not eight.  The
@@ -217,6 +217,10 @@ __global__ __launch_bounds__(512) void gemm_kp_kernel(int M, int N, int K, const
   __syncthreads();
   void *const outp = gridDim.y > 1 ? static_cast<void *>(static_cast<float *>(ep.out) + (int64_t)blockIdx.y * M * ep.ldc) : ep.out;
   constexpr int QPR = BN / 4;  // groups of four columns in a row
+  // A weight gradient goes past the caches, as from the 256-row tiles: nothing reads it before the optimizer, and what the following kernels read stays
+  // (us of a pass, 256x128 tiles / these, kept in the caches / past them: 708 tokens, 176 wide, vocabulary 32000 341.5 / 349.9 / 336.9; 512 tokens, 616 wide, ten
+  // layers 2265 / 2284 / 2239).  Partial products are read next.
+  const bool stream = !AKM && gridDim.y == 1;
   // a tile that lies inside the output and needs nothing but the conversion: no edge tests, no arithmetic
   if (ep.vec_ok && !ep.act_out && !ep.bias && !ep.residual && ep.alpha == 1.f && m0 + BM <= M && n0 + BN <= N) {
 #pragma unroll
@@ -224,7 +228,8 @@ __global__ __launch_bounds__(512) void gemm_kp_kernel(int M, int N, int K, const
       const int id = id0 + threadIdx.x, row = id / QPR, c4 = id % QPR * 4;
       const f32x4 v = *reinterpret_cast<const f32x4 *>(tile + row * LDE + c4);
       const int64_t o = (int64_t)(m0 + row) * ep.ldc + n0 + c4;
-      if (ep.out_f32) *reinterpret_cast<f32x4 *>(static_cast<float *>(outp) + o) = v;
+      if (!AKM && stream && ep.out_f32) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(static_cast<float *>(outp) + o));
+      else if (ep.out_f32) *reinterpret_cast<f32x4 *>(static_cast<float *>(outp) + o) = v;
       else *reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(outp) + o) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
     }
     return;
@@ -239,7 +244,10 @@ __global__ __launch_bounds__(512) void gemm_kp_kernel(int M, int N, int K, const
       for (int e = 0; e < 4; ++e)
         if (ncol + e < N) bias[e] = bf2f(static_cast<const uint16_t *>(ep.bias)[ncol + e]);
     }
-    store_quad<false, AKM && BKM>(ep, outp, m, ncol, N, *reinterpret_cast<const f32x4 *>(tile + row * LDE + c4), bias, ep.vec_ok && ncol + 3 < N);
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(tile + row * LDE + c4);
+    const bool vec = ep.vec_ok && ncol + 3 < N;
+    if (!AKM && stream) store_quad<true, false>(ep, outp, m, ncol, N, v, bias, vec);
+    else store_quad<false, AKM && BKM>(ep, outp, m, ncol, N, v, bias, vec);
   }
 }
 
