@@ -13,7 +13,7 @@
 // Tiles of 32, for few rows: gemm_f32_small_kernel, on the fp32 instruction (v_mfma_f32_32x32x2_f32): there every value would be split into
 // its terms for 32 products only.
 //
-// gemm_f32_wave_kernel, tiles of 64 whose operands allow 16-byte loads, contractions from 320 on (launch_tile).  What bounded such tiles in gemm_f32_kernel was neither the matrix
+// gemm_f32_wave_kernel, tiles of 64 whose operands allow 16-byte loads, contractions from 320 on and some shorter ones (launch_tile).  What bounded such tiles in gemm_f32_kernel was neither the matrix
 // pipes nor the loads but LDS and what it is fed with: three terms of 2 bytes written and, by waves of 32x32, read twice, a barrier for every
 // slice, and two waves a SIMD in step (1.2 us per slice of 64 where the instructions take 0.35 and forming the terms 0.47).  Here every wave forms
 // the whole tile over steps of 16 k of its own, so that
@@ -24,8 +24,8 @@
 // Its chains are an eighth (a quarter) of the contraction long, and the error is smaller: K = 96 0.47e-7 (gemm_f32_kernel 0.53e-7), 768 0.8e-7 (1.1e-7),
 // 4096 1.9e-7 (2.7e-7), 50257 whole 5.0e-7 (10e-7).  us, before / now: 1024 x 768 x 1536 32.1 / 23.6, its NN form 35.3 / 23.8, 1152 x 768 x 1024 (TN) 25.2 / 18.8,
 // 1024 x 1536 x 768 31.6 / 25.5, 1536 x 768 x 1024 (TN) 37.7 / 27.5, 8192 x 768 x 768 89 / 78, 3072 x 768 x 8192 (TN) 330 / 262, 1024 x 768 x 50257 (NN, cut)
-// 580 / 490.  What bounds it: small products the fixed 6 us (launch 2, first loads 2, sums and stores 2), large ones the power limit: 4096^3 797 us
-// against 830 in tiles of 128 on the same card.
+// 580 / 490 (in eight parts; it runs on tiles of 128 in sixteen, whose sums are shorter: choose).  What bounds it: small products the fixed 6 us
+// (launch 2, first loads 2, sums and stores 2), large ones the power limit: 4096^3 797 us, in tiles of 128 824 to 830 on the same card.
 //
 // gemm_f32_kernel and gemm_f32_small_kernel: four or eight waves, the contraction walked in slices of BK that are double-buffered in LDS, one
 // barrier per slice.  The waves divide the tile, and (WK) the slice: their results are added in wave order at the end.
@@ -35,8 +35,9 @@
 //   k contiguous: LDS [rows][BK + 4], a lane reads 4 consecutive k at once, good for four MFMAs;      rows contiguous: [BK][rows + 8].
 //   MFMA number 4 u + j of a slice contracts k = 8 u + j (lanes 0-31) and 8 u + 4 + j (lanes 32-63): the order of k inside a slice
 //   is free as long as both operands agree.  Both paddings make the reads conflict-free.
-// Measured, us (before: the fp32 instruction in all tiles), tiles of 128: 4096^3 805 (1107), 4096 x 2048 x 2048 222 (286), 1024 x 50257 x 768 595 (741): the rate
-// of the bf16 instruction at the power limit (six of them per product: 1.04 PFLOP/s in 4096^3).
+// Measured, us (before: the fp32 instruction in all tiles), tiles of 128, on another card than the figures above: 4096^3 805 (1107), 4096 x 2048 x 2048 222
+// (286), 1024 x 50257 x 768 595 (741): the rate of the bf16 instruction at the power limit (six of them per product: 1.04 PFLOP/s in 4096^3).  All three run on
+// tiles of 64 now (1024 x 50257 x 768 560).
 // Strides and bases that do not allow 16-byte loads go through the scalar loader (VEC = 0), in tiles of 64 too.
 #include <algorithm>
 #include <type_traits>
@@ -733,7 +734,8 @@ void launch(hipStream_t st, int M, int N, int K, const float *A, int64_t lda, co
 
 constexpr int kWaveK = 320;  // shortest contraction for which tiles of 64 are gemm_f32_wave_kernel's
 template <int AKM, int BKM, int VEC>
-void launch_tile(hipStream_t st, int tile, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, const Ep32 &ep, int parts, int kchunk) {
+void launch_tile(hipStream_t st, int tile, bool waves, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb, const Ep32 &ep, int parts,
+                 int kchunk) {
   if (tile == 128) return launch<AKM, BKM, 128, 2, 2, 32, VEC>(st, M, N, K, A, lda, B, ldb, ep, parts, kchunk);
   if (tile == 64) {
     const int tm = (M + 63) / 64, tn = (N + 63) / 64;
@@ -741,8 +743,9 @@ void launch_tile(hipStream_t st, int tile, int M, int N, int K, const float *A, 
     if constexpr (VEC) {
       // shorter contractions are a few steps to a wave, and the addition of the waves' sums and the fixed time weigh more than what the steps save (us,
       // gemm_f32_kernel / waves: 1024 x 768 x 64 5.8 / 6.7, 3000 x 3072 x 64 28.1 / 30.8, 4096 x 512 x 128 9.5 / 10.3, 192 11.7 / 12.0, 256 13.6 / 14.1; 1024 x 768
-      // x 320 10.1 / 9.9, x 384 11.6 / 11.3), but where the last slice of 64 would be half empty (1024 x 768 x 96 7.2 / 7.1, 160, NN, 8.5 / 8.0)
-      if (K >= kWaveK || (one && K > 64 && (K + 31) / 32 % 2 == 1)) {
+      // x 320 10.1 / 9.9, x 384 11.6 / 11.3), but where the last slice of 64 would be half empty (1024 x 768 x 96 7.2 / 7.1, 160, NN, 8.5 / 8.0), or tiles
+      // of 128 are what they replace (`waves`)
+      if (waves || K >= kWaveK || (one && K > 64 && (K + 31) / 32 % 2 == 1)) {
         if (one) hipLaunchKernelGGL((gemm_f32_wave_kernel<AKM, BKM, 8>), dim3(tm * tn, parts), dim3(512), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
         else hipLaunchKernelGGL((gemm_f32_wave_kernel<AKM, BKM, 4>), dim3(tm * tn, parts), dim3(256), 0, st, M, N, K, A, lda, B, ldb, ep, tm, tn, kchunk, NoGroup());
         return;
@@ -820,15 +823,40 @@ Choice choose(GemmLayout lay, int count, const int *Ms, const int *Ns, int K, bo
 
 }  // namespace
 
-void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool vec, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
-  const bool split = may_split && !ctx->gemm_tile;
-  Choice ch = choose(lay, 1, &M, &N, K, false, split, split_floats);
-  if (vec && K >= kWaveK) ch = choose(lay, 1, &M, &N, K, true, split, split_floats, chain_of(ch.tile, false, 0, (double)K / ch.parts));
-  if (ctx->gemm_tile) ch = {ctx->gemm_tile == 128 ? 128 : 64, 1};
+// Contractions below kWaveK whose place is on tiles of 128: whether tiles of 64 by waves that form the whole tile take less, by estimates of both for
+// operands that allow 16-byte loads (whole slices; the last round of the waves' steps may be short): 128 3 + n (8.2 + 1.32 per slice of 32), where the
+// output is beyond 600 MB 3 + n (7.8 + 1.55 per slice).  Fitted to 314 products of 13 to 1650 MB, K = 64 to 316: of the 107 that the waves take one is slower on them,
+// by 2 %, the mean is 0.88, and 41 of those they do not take would be 3 to 13 % faster; us, 128 / 64: 8192 x 768 x 256 39.8 / 32.8, 3000 x 3072 x 240 60 / 48.6, 4352 x
+// 50257 x 272 1251 / 1109; on the other side 8192 x 2048 x 224 72.5 / 83, 256 78 / 80.6, 1024 x 50257 x 128 176 / 178, 3000 x 32000 x 256 452 / 483.
+static bool waves_shorter(int M, int N, int K) {
+  const double n128 = (double)(((int64_t)((M + 127) / 128) * ((N + 127) / 128) + 255) / 256);
+  const int64_t n64 = ((int64_t)((M + 63) / 64) * ((N + 63) / 64) + 255) / 256;
+  const bool beyond = (double)M * N * 4 > 6e8;
+  const double by128 = 3.0 + n128 * ((beyond ? 7.8 : 8.2) + (beyond ? 1.55 : 1.32) * ((K + 31) / 32));
+  const double by64 = 4.5 + 2.05 * n64 + (0.745 * n64 + (n64 % 2 ? 0.25 : 0.0)) * std::min((double)((K + 63) / 64), K / 64.0 + 0.35);
+  return n64 > 2 && by64 < by128;
+}
+
+static Choice choice_of(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool vec, bool may_split, size_t split_floats, bool &waves) {
+  waves = false;
+  if (ctx->gemm_tile) return {ctx->gemm_tile == 128 ? 128 : 64, 1};
+  const Choice ch = choose(lay, 1, &M, &N, K, false, may_split, split_floats);
+  if (!vec) return ch;
+  if (K >= kWaveK) return choose(lay, 1, &M, &N, K, true, may_split, split_floats, chain_of(ch.tile, false, 0, (double)K / ch.parts));
+  waves = ch.tile == 128 && waves_shorter(M, N, K);
+  return waves ? Choice{64, 1} : ch;
+}
+
+static void cut_of(Choice ch, int K, int &tile, int &parts, int &kchunk) {
   const int bk = ch.tile == 128 ? 32 : 64;
   kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
   tile = ch.tile;
   parts = (K + kchunk - 1) / kchunk;
+}
+
+void twist_gemm_f32_choice(const twist_ctx *ctx, GemmLayout lay, int M, int N, int K, bool vec, bool may_split, size_t split_floats, int &tile, int &parts, int &kchunk) {
+  bool waves;
+  cut_of(choice_of(ctx, lay, M, N, K, vec, may_split, split_floats, waves), K, tile, parts, kchunk);
 }
 
 twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
@@ -836,7 +864,8 @@ twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int 
   Ep32 ep{e.alpha, static_cast<const float *>(e.bias), e.residual, static_cast<float *>(e.out), ldc};
   const bool vec = aligned16(A) && aligned16(B) && lda % 4 == 0 && ldb % 4 == 0;
   int tile, parts, kchunk;
-  twist_gemm_f32_choice(ctx, lay, M, N, K, vec, e.splitk_ws && !e.bias && !e.residual, e.splitk_floats, tile, parts, kchunk);
+  bool waves;
+  cut_of(choice_of(ctx, lay, M, N, K, vec, e.splitk_ws && !e.bias && !e.residual, e.splitk_floats, waves), K, tile, parts, kchunk);
   if (tile != 32 && std::max(lda, ldb) >= 1 << 23) {  // a slice of such rows exceeds the larger tiles' 32-bit offsets
     tile = 32;
     kchunk = (kchunk + 63) / 64 * 64;
@@ -845,8 +874,8 @@ twist_status twist_gemm_f32(twist_ctx *ctx, hipStream_t st, GemmLayout lay, int 
   if (parts > 1) ep = Ep32{1.f, nullptr, nullptr, e.splitk_ws, N};
 #define TW_F32(AKM, BKM)                                                                                \
   do {                                                                                                    \
-    if (vec) launch_tile<AKM, BKM, 1>(st, tile, M, N, K, A, lda, B, ldb, ep, parts, kchunk);              \
-    else launch_tile<AKM, BKM, 0>(st, tile, M, N, K, A, lda, B, ldb, ep, parts, kchunk);                  \
+    if (vec) launch_tile<AKM, BKM, 1>(st, tile, waves, M, N, K, A, lda, B, ldb, ep, parts, kchunk);              \
+    else launch_tile<AKM, BKM, 0>(st, tile, false, M, N, K, A, lda, B, ldb, ep, parts, kchunk);                  \
   } while (0)
   switch (lay) {
     case GEMM_NT: TW_F32(1, 1); break;
@@ -869,10 +898,7 @@ bool twist_gemm_f32_group_choice(int n, const int *Ms, const int *Ns, int K, siz
   }
   const Choice ch = choose(GEMM_TN, n, Ms, Ns, K, true, split_floats > 0, split_floats, longest);
   if (!ch.tile) return false;
-  const int bk = ch.tile == 128 ? 32 : 64;
-  kchunk = ((K + ch.parts - 1) / ch.parts + bk - 1) / bk * bk;
-  tile = ch.tile;
-  parts = (K + kchunk - 1) / kchunk;
+  cut_of(ch, K, tile, parts, kchunk);
   return true;
 }
 

@@ -238,6 +238,27 @@ def test_fp32_short_contractions_in_tiles_of_64(lib, layout, M, N, K, same):
     assert float((outs[1].double() - want).norm() / want.norm()) <= 1e-6
 
 
+# ... and some that tiles of 128 would take go to the waves of tiles of 64 (last steps, rounds and columns that are not whole): no coarser than on tiles of 128, which
+# rows that are not aligned run on.  (2 % for the norm over a million outputs)
+@pytest.mark.parametrize("layout,M,N,K", [(0, 4095, 763, 160), (0, 8190, 771, 100), (0, 3001, 3071, 244), (0, 1827, 5515, 316), (1, 4093, 764, 132), (1, 3001, 3076, 252), (1, 2599, 2340, 96),
+                                          (2, 4092, 764, 163), (2, 3712, 3700, 283), (2, 50252, 764, 257)])
+def test_fp32_short_contractions_by_waves_of_whole_tiles(lib, layout, M, N, K):
+    ctx = lib.Context(lib.desc_from_cfg(si.CFG1))
+    assert ctx.twist_gemm_kernel(layout, M, N, K, True) == (64, 64, 1)
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.randn((K, M) if layout == 2 else (M, K), generator=gen, device="cuda")
+    B = torch.randn((N, K) if layout == 0 else (K, N), generator=gen, device="cuda")
+    want = (A.double().T if layout == 2 else A.double()) @ (B.double().T if layout == 0 else B.double())
+    odd = lambda x: torch.cat((x[:, :1], x), 1)[:, 1:]
+    buf = torch.full((M * N + 64,), float("nan"), device="cuda")
+    out, err = buf[:M * N].view(M, N), []
+    for a, b in ((odd(A), odd(B)), (A, B)):
+        ctx.twist_gemm_raw(layout, M, N, K, a, b, out)
+        torch.cuda.synchronize()
+        err.append(float((out.double() - want).norm() / want.norm()))
+    assert err[1] <= 1.02 * err[0] and torch.isnan(buf[M * N:]).all(), err
+
+
 # aligned operands take kernels of their own: their sums are no coarser than those of the same product on rows that are not aligned.  Products that the
 # fp32 instruction, a shorter cut of the contraction or fewer waves to a tile would give a larger error for (1.3 to 3.7 times), and some where the
 # kernels agree.  (3 % for the norm over 1e5 outputs and more)
