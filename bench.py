@@ -624,7 +624,7 @@ def main():
                                f"subnets, batch 4x2048 Zipf(1.1) tokens, {args.local_steps} local AdamW steps per subnet, sample+extract+train+aggregate; "
                                "output projections stored unit-major",
                    "S": 4, "batch": 4, "seq_len": 2048, "local_steps": args.local_steps},
-        "roofline": {"bound": "mfma", "kernel": "gemm_nt_kernel / gemm_pp_kernel / gemm_dl_kernel: every projection launch of one forward+backward per subnet, "
+        "roofline": {"bound": "mfma", "kernel": "gemm_nt_kernel / gemm_pp_kernel / gemm_kp_kernel / gemm_dl_kernel: every projection launch of one forward+backward per subnet, "
                                                  "kernels serialised on one stream",
                      "achieved": g["tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": g["tflops"] / PEAK_BF16_TFLOPS,
                      "traffic": TRAFFIC_PROJECTION_LAUNCH, "traffic_unit": "bytes per launch behind the L2 (rocprofv3 FETCH_SIZE/WRITE_SIZE, calibrated)",

@@ -420,18 +420,18 @@ struct Kind { int bm, bn; double fixed, tile, tile32, s0, s1, lay[3]; };  // lay
 constexpr Kind kKinds[] = {{256, 256, 1.0, 9.1, 0.36, 0.434, 0.32, {1, 1, 1}}, {256, 128, 1.7, 4.4, 1.0, 0.344, 0.23, {1, 1, 1}},
                            {64, 64, 2.95, 0.875, 0.19, 0.12, 0.011, {1, 1, 1}}, {32, 32, 2.5, 0.81, 0.06, 0.068, 0.01, {0.71, 1, 1}},
 // Two groups that share the contraction (gemm_kp.hip).  Fitted to 600 products of their own, sizes 64 to 50257 (half of the estimates within
-// 4 %, 8 % for 64x96; nine tenths within 13 and 18 %).  They are taken where they are expected to be a twelfth faster than the others: of 200
+// 4 %, 8 % for 64x96; nine tenths within 13 and 18 %).  They are taken where they are expected to be a twelfth faster than the others (choose_any): of 200
 // products not fitted to, 33 then went to them, 20 % faster on average and one slower, by 4.6 %; with the bare estimates 43, one of them
 // 23 % slower.  Launches of fewer than 128 tiles (2048 x 896 x 3000, TN, 112 of 128x128: 22.8 us, 64x64 20.8), of fewer than 170 tiles of 96 columns, whose
 // CUs have too little in flight where operands come from memory (37 products 4 % faster with operands in the caches, 8 % slower otherwise; 1536 x 1024 x
 // 4096, NN, 132 tiles 26.2 / 28.0 and 29.9 / 36.4; 51 of 170 to 192 tiles 24 and 13 % faster), and of more than four rounds (50257 x 280 x 7007, TN: 383,
 // 256x256 329) are left out, and contractions beyond 8192 (choose_any).  us, the others' fastest / these:
-//   8192 x 768 x 768            16.2 / 15.2 (128x192)      2048 x 768 x 2048 (f32)       15.3 / 11.8 (64x96)
+//   2816 x 2048 x 8192 (TN)      105 / 94   (192x128)      2048 x 768 x 2048 (f32)       15.3 / 11.8 (64x96)
 //   4096 x 768 x 2560 (f32)     30.4 / 21.1 (128x96)       2048 x 1536 x 768             13.0 /  9.9 (128x96)
 //   2048 x 2048 x 768           16.0 / 11.4 (128x128)      3000 x 2048 x 2488 (f32)      48.3 / 39.2 (192x128)
 //   3000 x 2048 x 4976 (NN)     74.5 / 59.5 (192x128)      1024 x 2048 x 8192 (TN)       50.1 / 51.1 (128x128; 46 in two parts)
-//   2816 x 2048 x 8192 (TN)      119 / 95   (128x192)      3072 x 2048 x 8192 (TN)        121 / 94   (192x128)
-// and on the other side of the line 8192 x 768 x 192 (NN, f32) 9.6 / 13.1, 4096 x 1920 x 768 16.5 / 19.1, 8192 x 1024 x 2048 33.2 / 35.0,
+//   3072 x 2048 x 8192 (TN)      106 / 94   (192x128)
+// and on the other side of the line 8192 x 768 x 768 16.2 / 15.2 (128x192), 8192 x 768 x 192 (NN, f32) 9.6 / 13.1, 4096 x 1920 x 768 16.5 / 19.1, 8192 x 1024 x 2048 33.2 / 35.0,
 // 8192 x 5632 x 2048 144 / 200, 1024^3 7.2 / 7.9, 50257 x 768 x 8192 (TN) 594 / 732.
                            {128, 192, 1.62, 6.98, 0.31, 0.252, 0.118, {1, 1.045, 1.08}}, {192, 128, 1.09, 6.73, 0.33, 0.262, 0.1, {1, 1.005, 1.075}},
                            {128, 128, 1.98, 4.75, 0.34, 0.16, 0.09, {1, 1.01, 0.975}}, {128, 96, 2.66, 3.92, 0.35, 0.143, 0.058, {1, 1.105, 1.17}},
@@ -623,7 +623,7 @@ twist_status twist_gemm(twist_ctx *ctx, int bf16, GemmLayout lay, int M, int N, 
 
 // What bound them: the weight gradients of one layer of a small model are too few tiles each to fill the chip, cut into many parts with
 // a pass over the partial products behind each.  Together they fill it in fewer parts: 8192 x 768 x (192 heads, 768 hidden) in bf16 four
-// launches and four sums, 109 us, against 49 + 8; 2048 x 768 x (512, 2048) 77 us against 44.  In fp32 (one stream, so where they are
+// launches and four sums, 109 us, against 45 + 6; 2048 x 768 x (512, 2048) 77 us against 44.  In fp32 (one stream, so where they are
 // fewest): 256 x 128 x (64, 256) 20 us against 8, 1248 x 88 x (832, 344) 46 / 20, 1024 x 768 x (384, 1536) 98 / 63; of 156 such groups and pairs the
 // mean is two thirds.
 twist_status twist_weight_grads(twist_ctx *ctx, int bf16, int n, const WeightGrad *items, int K, float *scratch, size_t scratch_floats, hipStream_t st,

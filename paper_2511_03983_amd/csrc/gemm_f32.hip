@@ -24,8 +24,8 @@
 // Its chains are an eighth (a quarter) of the contraction long, and the error is smaller: K = 96 0.47e-7 (gemm_f32_kernel 0.53e-7), 768 0.8e-7 (1.1e-7),
 // 4096 1.9e-7 (2.7e-7), 50257 whole 5.0e-7 (10e-7).  us, before / now: 1024 x 768 x 1536 32.1 / 23.6, its NN form 35.3 / 23.8, 1152 x 768 x 1024 (TN) 25.2 / 18.8,
 // 1024 x 1536 x 768 31.6 / 25.5, 1536 x 768 x 1024 (TN) 37.7 / 27.5, 8192 x 768 x 768 89 / 78, 3072 x 768 x 8192 (TN) 330 / 262, 1024 x 768 x 50257 (NN, cut)
-// 580 / 490 (in eight parts; it runs on tiles of 128 in sixteen, whose sums are shorter: choose).  What bounds it: small products the fixed 6 us
-// (launch 2, first loads 2, sums and stores 2), large ones the power limit: 4096^3 797 us, in tiles of 128 824 to 830 on the same card.
+// 580 / 490.  What bounds it: small products the fixed 6 us (launch 2, first loads 2, sums and stores 2), large ones the power limit: 4096^3 797 us, in
+// tiles of 128 824 to 830 on the same card.
 //
 // gemm_f32_kernel and gemm_f32_small_kernel: four or eight waves, the contraction walked in slices of BK that are double-buffered in LDS, one
 // barrier per slice.  The waves divide the tile, and (WK) the slice: their results are added in wave order at the end.
